@@ -116,9 +116,23 @@ size_t estimate_ws(const sea_params* p) {
   return align256(p->dtype == SEA_BF16 ? estimate_bf16_workspace(s) : estimate_f64_workspace(s));
 }
 
+// bf16 attention on mask bits: the power-of-two form, else the form for any column widths
+bool bits_attn_supported(const Shape& s, sea_dtype dt) {
+  return tile_attn_supported(s, dt, nullptr) || column_attn_supported(s, dt);
+}
+
+hipError_t launch_bits_attn(const Shape& s, const void* Q, const void* K, const void* V, const uint32_t* mbits,
+                            void* O, void* ws, hipStream_t st) {
+  const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K),
+                 *v = static_cast<const uint16_t*>(V);
+  if (tile_attn_supported(s, SEA_BF16, nullptr))
+    return launch_tile_attn(s, q, k, v, mbits, static_cast<uint16_t*>(O), ws, st);
+  return launch_column_attn(s, q, k, v, mbits, static_cast<uint16_t*>(O), st);
+}
+
 // the fused estimator keeps the scores in registers: no A_hat buffer unless the caller wants one
 bool scores_stay_on_chip(const sea_params* p, const Shape& s) {
-  return tile_attn_supported(s, p->dtype, nullptr) && estimate_fused_supported(s) && s.grouping == 0;
+  return bits_attn_supported(s, p->dtype) && estimate_fused_supported(s) && s.grouping == 0;
 }
 
 // Scratch of the whole forward pass: estimator scratch, A_hat, then either the tiled path's mask
@@ -135,7 +149,7 @@ size_t forward_ws(const sea_params* p, bool lean) {
   const Shape s = make_shape(p, true);
   size_t bytes = estimate_ws(p);
   if (!(lean && scores_stay_on_chip(p, s))) bytes += align256(rows * p->K * sizeof(float));
-  if (tile_attn_supported(s, p->dtype, nullptr)) {
+  if (bits_attn_supported(s, p->dtype)) {
     bytes += align256(rows * ((p->K + 31) / 32) * sizeof(uint32_t));
     bytes += align256(tile_attn_workspace(s));
   } else if (p->dtype == SEA_F32 && tile_attn_f32_supported(s)) {
@@ -361,7 +375,7 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
     if (!A_hat) A_hat = reinterpret_cast<float*>(w);
     w += align256(rows * s.K * sizeof(float));
   }
-  const bool tiled = tile_attn_supported(s, p->dtype, nullptr);
+  const bool tiled = bits_attn_supported(s, p->dtype);
 
   hipError_t e;
   if (tiled) {
@@ -388,8 +402,7 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
       e = launch_topk_mask(s, A_hat, sel_opt, idx_opt, cnt_opt, mbits, st);
     }
     if (e != hipSuccess) return fail_hip(e);
-    e = launch_tile_attn(s, static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
-                         static_cast<const uint16_t*>(V), mbits, static_cast<uint16_t*>(O), w, st);
+    e = launch_bits_attn(s, Q, K, V, mbits, O, w, st);
     return e == hipSuccess ? SEA_OK : fail_hip(e);
   }
   if (s.geometry == 1)
@@ -500,7 +513,7 @@ DecFwdWs decoder_forward_layout(const sea_params* p) {
   w.s_prob = off; off += align256(rows * sizeof(float));
   w.att = off;
   off += align256(rows * ((s.K + 31) / 32) * sizeof(uint32_t));
-  if (tile_attn_supported(s, p->dtype, nullptr)) {
+  if (bits_attn_supported(s, p->dtype)) {
     off += align256(tile_attn_workspace(s));
   } else {
     off += align256(rows * static_cast<size_t>(s.L) * sizeof(int32_t));
@@ -569,11 +582,10 @@ int sea_decoder_forward(const sea_params* p, const sea_decoder_weights* w, const
   char* att = base + lay.att;
   uint32_t* mbits = reinterpret_cast<uint32_t*>(att);
   att += align256(rows * ((s.K + 31) / 32) * sizeof(uint32_t));
-  if (tile_attn_supported(s, p->dtype, nullptr)) {
+  if (bits_attn_supported(s, p->dtype)) {
     e = launch_topk_mask(s, A_hat, nullptr, nullptr, nullptr, mbits, st);
     if (e != hipSuccess) return fail_hip(e);
-    e = launch_tile_attn(s, static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
-                         static_cast<const uint16_t*>(V), mbits, static_cast<uint16_t*>(O), att, st);
+    e = launch_bits_attn(s, Q, K, V, mbits, O, att, st);
   } else {
     int32_t* idx = reinterpret_cast<int32_t*>(att);
     int32_t* cnt = reinterpret_cast<int32_t*>(att + align256(rows * static_cast<size_t>(s.L) * sizeof(int32_t)));

@@ -1,0 +1,372 @@
+// Tiled attention for column-selected masks of ANY column widths (Sec. 3.1.1 rho, sigma, A* V with
+// the mask of Sec. 3.1 "Linear Sparse Attention Mask Generation", App. A.5.3): K need not divide T
+// and a selected column may emit any number of keys.  bf16 tensors; the power-of-two shapes have a
+// kernel of their own (sea_tile_attn.hip), whose register groups share one mask bit.
+//
+// The keys a head can use form one compact list, ascending in position: all T keys when whole
+// columns are emitted, else r keys of each of the K columns.  A block of 4 waves takes 128 query
+// rows and walks it in 64-key steps staged through LDS, as the power-of-two kernel does.  With
+// columns of any width a lane's score registers belong to columns that change from step to step, so
+// bit tests per register would cost more than the softmax.  The mask goes through the matrix
+// product instead: the contraction is extended by NX slots, one per column of the 32-key sub-chunk.
+// On the key side slot x holds -2^126 for the keys of the sub-chunk's x-th column (one-hot, parked
+// in the padding of the staged K rows, the same for every row and head); on the query side it
+// holds 2 where the row did NOT select that column and 0 where it did.  One more 32x32x16 product
+// then lowers exactly the unselected scores by 2^127 and adds exact zeros to the others.  Building
+// the query side takes nine vector instructions per sub-chunk from the row's mask window.
+//
+// The softmax weights go into the second product as the sum of two bf16 values (the rounded weight
+// and the rounded remainder, 16 significant bits): these shapes used to run on the per-row kernel,
+// which multiplies in fp32.
+//
+// Bound: vector issue, as in the power-of-two kernel (about 190 vector instructions and 13 matrix
+// products per 32-key sub-chunk and wave; three waves per SIMD: held to four the compiler spills 14
+// registers and the kernel is 15 % slower).  Measured on the layer B = 8, H = 32, T = 2000 (padded by
+// 0-25 %), K = 256, k^ = 64: 0.29 ms; the per-row gather kernel that ran before took 2.71 ms and its
+// key lists another 0.57 ms to write.
+#include "sea_internal.h"
+#include "sea_tile.h"
+
+namespace sea {
+namespace {
+
+constexpr int kChunk = 64;  // keys staged per step (two 32-key sub-chunks)
+constexpr int kVRow = 64;   // halfwords per staged V row; halves of rows 2, 3 (mod 4) exchanged
+
+struct ColumnArgs {
+  const uint16_t* Q;
+  const uint16_t* K;
+  const uint16_t* V;
+  const uint32_t* mbits;  // [N][T][KW] selected-column bits
+  uint16_t* O;
+  const int32_t* seq_len;
+  int32_t N, H, T, Kc, KW;
+  int32_t r;         // keys per column, 0 = whole columns (the list is all T keys)
+  int32_t w0, rm;    // T = w0 Kc + rm
+  int32_t U;         // length of the compact list
+  // column of list entry u = floor(u A / D); 32 entries further: q32 more, remainder r32 more
+  int32_t A, D, q32, r32;
+  float invK, invr;  // 1 / Kc, 1 / r
+  int32_t causal, group_heads;
+  float c;           // scale * log2(e)
+};
+
+// floor(x / n) for 0 <= x < 2^21, inv = 1 / n rounded to fp32: x + 1/2 is at least 1 / (2 n) away from the
+// next multiple of n (in quotients), and the fused product is off by less than x / n 2^-23 < 1 / (4 n)
+__device__ __forceinline__ int32_t div_small(int32_t x, float inv) {
+  return static_cast<int32_t>(fmaf(static_cast<float>(x), inv, 0.5f * inv));
+}
+// first key of column c = ceil(c T / K) = c w0 + ceil(c rm / K)
+__device__ __forceinline__ int32_t column_start(const ColumnArgs& a, int32_t c) {
+  return c * a.w0 + div_small(c * a.rm + a.Kc - 1, a.invK);
+}
+// position of entry i of column c
+__device__ __forceinline__ int32_t entry_pos(const ColumnArgs& a, int32_t c, int32_t i) {
+  const int32_t s0 = column_start(a, c), w = column_start(a, c + 1) - s0;
+  return s0 + div_small(i * w, a.invr);
+}
+// number of list entries with position <= jmax
+__device__ __forceinline__ int32_t list_count(const ColumnArgs& a, int32_t jmax) {
+  if (jmax < 0) return 0;
+  if (a.r == 0) return jmax + 1;
+  const int32_t col = bucket_of(jmax, a.T, a.Kc);
+  const int32_t s0 = column_start(a, col), w = column_start(a, col + 1) - s0;
+  return col * a.r + min(a.r, ((jmax - s0 + 1) * a.r + w - 1) / w);
+}
+
+// NX = contraction slots for the mask: 8 (at least 5 keys per column: a 32-key sub-chunk touches at
+// most 8 columns), 16 (3 or 4 keys) or 32 (1 or 2 keys).
+template <int NX>
+__global__ __launch_bounds__(256, 3) void column_attn_kernel(ColumnArgs a) {
+  constexpr int kKRow = NX == 8 ? 72 : (NX == 16 ? 88 : 104);  // 64 dims | NX slots | padding: conflict-free
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kChunk * kKRow];
+  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][kChunk * kVRow];
+  extern __shared__ uint32_t Ms[];  // the 128 rows' mask words, inverted, KW + 1 per row (the last all ones)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ql = lane & 31, g = lane >> 5;
+  // launch order as in the power-of-two kernel: heads in groups whose keys fit the L2s, longest tiles first
+  const uint32_t wgs = (a.T + 127) / 128;
+  const uint32_t per_group = static_cast<uint32_t>(a.group_heads) * wgs;
+  const uint32_t grp = blockIdx.x / per_group, rem_b = blockIdx.x - grp * per_group;
+  const uint32_t nh = min(static_cast<uint32_t>(a.group_heads), static_cast<uint32_t>(a.N) - grp * a.group_heads);
+  const int64_t head = static_cast<int64_t>(grp) * a.group_heads + rem_b % nh;
+  const int32_t wg_tile = static_cast<int32_t>(wgs - 1 - rem_b / nh);
+  const int32_t row0 = wg_tile * 128, q0 = row0 + 32 * wid, t = q0 + ql;
+  const int32_t b = static_cast<int32_t>(head / a.H);
+  const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
+  const bool row_active = t < len;
+
+  const uint16_t* Qr = a.Q + (head * a.T + min(t, a.T - 1)) * kHeadDim + 8 * g;
+  bf16x8 bq[4];
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) bq[kc] = *reinterpret_cast<const bf16x8*>(Qr + 16 * kc);
+  // (through an empty asm: plain register values inside the loop, not results of pending loads)
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) asm volatile("" : "+v"(bq[kc]));
+
+  const int mstride = a.KW + 1;
+  {
+    const uint32_t* msrc = a.mbits + (head * a.T + row0) * a.KW;
+    for (int32_t x = tid; x < 128 * mstride; x += 256) {
+      const int32_t r = x / mstride, wi = x - r * mstride;
+      Ms[x] = (wi < a.KW && row0 + r < len) ? ~msrc[r * a.KW + wi] : 0xffffffffu;
+    }
+  }
+  const uint32_t* mrow = &Ms[(32 * wid + ql) * mstride];
+
+  const int32_t wg_hi = min(row0 + 127, a.T - 1), t_hi = min(q0 + 31, a.T - 1);
+  const int32_t u_end_wg = list_count(a, a.causal ? min(wg_hi, len - 1) : len - 1);
+  const int32_t u_end = q0 < a.T ? list_count(a, a.causal ? min(t_hi, len - 1) : len - 1) : 0;
+  // entries below u_free are admissible for every active row of the wave
+  const int32_t u_free = min(u_end, list_count(a, a.causal ? min(q0, len - 1) : len - 1));
+  const int32_t my_ucount = list_count(a, row_active ? (a.causal ? min(t, len - 1) : len - 1) : -1);
+  const int32_t nsteps = (u_end_wg + kChunk - 1) / kChunk;
+
+  // staging: 16-byte part tid & 7 of the K and V rows (tid >> 3) and (tid >> 3) + 32 of a step.  Rows
+  // past the list or past the sequence re-read its last row; their scores are masked.
+  const int srow = tid >> 3, spart = tid & 7;
+  const int vpart = spart ^ (((srow >> 1) & 1) << 2);
+  uint4 kreg0, kreg1, vreg0, vreg1;
+  uint32_t x0[NX == 32 ? 2 : 1], x1[NX == 32 ? 2 : 1];  // this thread's words of the two rows' one-hot slots
+  const uint32_t row_bytes = kHeadDim * 2, head_bytes = static_cast<uint32_t>(a.T) * row_bytes;
+  const uint16_t* Kh = a.K + head * static_cast<int64_t>(a.T) * kHeadDim;
+  const uint16_t* Vh = a.V + head * static_cast<int64_t>(a.T) * kHeadDim;
+  const __amdgpu_buffer_rsrc_t Kres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Kh), 0, head_bytes, kBufferFlags);
+  const __amdgpu_buffer_rsrc_t Vres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Vh), 0, head_bytes, kBufferFlags);
+  // column and remainder of this thread's next row, and of the next sub-chunk's first entry
+  int32_t ucur = srow, ccol = (srow * a.A) / a.D, crem = srow * a.A - ccol * a.D;
+  int32_t scol = 0, srem = 0;
+  auto advance = [&](int32_t& col, int32_t& rem) {
+    col += a.q32;
+    rem += a.r32;
+    const bool carry = rem >= a.D;
+    col += carry ? 1 : 0;
+    rem -= carry ? a.D : 0;
+  };
+  auto onehot = [&](int32_t lc, uint32_t* x) {
+    const uint32_t v = (lc & 1) ? 0xfe800000u : 0x0000fe80u;  // -2^126
+#pragma unroll
+    for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) x[e] = (lc >> 1) == spart + 8 * e ? v : 0u;
+  };
+  auto row_off = [&]() -> uint32_t {
+    const int32_t pos = a.r == 0 ? ucur : entry_pos(a, ccol, crem);
+    return static_cast<uint32_t>(min(pos, len - 1)) * row_bytes + spart * 16;
+  };
+  int32_t cs0 = 0, cs1 = 0, cs2 = 0;  // first columns of the fetched step's sub-chunks and of the one after
+#define SEA_CFETCH()                                                                                  \
+  do {                                                                                                \
+    cs0 = scol;                                                                                       \
+    advance(scol, srem);                                                                              \
+    cs1 = scol;                                                                                       \
+    advance(scol, srem);                                                                              \
+    cs2 = scol;                                                                                       \
+    const uint32_t oa = row_off();                                                                    \
+    onehot(ccol - cs0, x0);                                                                           \
+    ucur += 32;                                                                                       \
+    advance(ccol, crem);                                                                              \
+    const uint32_t ob = row_off();                                                                    \
+    onehot(ccol - cs1, x1);                                                                           \
+    ucur += 32;                                                                                       \
+    advance(ccol, crem);                                                                              \
+    kreg0 = buffer_load16(Kres, oa);                                                                  \
+    kreg1 = buffer_load16(Kres, ob);                                                                  \
+    vreg0 = buffer_load16(Vres, oa);                                                                  \
+    vreg1 = buffer_load16(Vres, ob);                                                                  \
+  } while (0)
+#define SEA_CPARK(stage_)                                                                             \
+  do {                                                                                                \
+    *reinterpret_cast<uint4*>(&Ks[stage_][srow * kKRow + spart * 8]) = kreg0;                          \
+    *reinterpret_cast<uint4*>(&Ks[stage_][(srow + 32) * kKRow + spart * 8]) = kreg1;                   \
+    *reinterpret_cast<uint4*>(&Vs[stage_][srow * kVRow + vpart * 8]) = vreg0;                          \
+    *reinterpret_cast<uint4*>(&Vs[stage_][(srow + 32) * kVRow + vpart * 8]) = vreg1;                   \
+    if (NX >= 16 || spart < NX / 2) {                                                                 \
+      _Pragma("unroll") for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) {                                 \
+        *reinterpret_cast<uint32_t*>(&Ks[stage_][srow * kKRow + kHeadDim + 2 * (spart + 8 * e)]) = x0[e];        \
+        *reinterpret_cast<uint32_t*>(&Ks[stage_][(srow + 32) * kKRow + kHeadDim + 2 * (spart + 8 * e)]) = x1[e]; \
+      }                                                                                               \
+    }                                                                                                 \
+  } while (0)
+
+  floatx16 oacc[2];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) { oacc[0][i] = 0.f; oacc[1][i] = 0.f; }
+  // Streaming softmax in log2 units, y = s c - m_ref.  A masked score is about -2^127 c (or -inf), far
+  // below m_thr's start value, so it never becomes a reference; afterwards m_thr is how far a row's
+  // maximum may exceed its reference before that is moved.
+  float m_ref = 0.f, m_thr = -fminf(a.c * 0x1p126f, 3.0e38f), l_run = 0.f;
+  constexpr float kRefSlack = 8.f;
+  const uint32_t gmask = (NX == 8 && g != 0) ? 0u : 0x40004000u;  // NX = 8: the upper half's slots are unused
+
+  // {-1, 0} and {0, -1} as bf16 pairs, kept in scalar registers: written as constants, the first is
+  // encoded as the inline operand -1.0, which the instruction reads as the fp32 pattern = {0, -1}
+  uint32_t neg_lo_bits = 0x0000bf80u, neg_hi_bits = 0xbf800000u;
+  asm volatile("" : "+s"(neg_lo_bits), "+s"(neg_hi_bits));
+
+  if (nsteps > 0) {
+    SEA_CFETCH();
+    SEA_CPARK(0);
+  }
+  __syncthreads();
+  for (int32_t step = 0; step < nsteps; ++step) {
+    const int stage = step & 1;
+    const int32_t c0[3] = {cs0, cs1, cs2};  // (uniform) columns at the start of this step's sub-chunks
+    if (step + 1 < nsteps) SEA_CFETCH();
+#pragma unroll
+    for (int sc = 0; sc < 2; ++sc) {
+      const int32_t u0 = step * kChunk + 32 * sc;
+      if (u0 >= u_end) break;  // wave-uniform: beyond what this wave's rows can see
+      const int32_t wi = c0[sc] >> 5;
+      // the row's inverted mask bits from the sub-chunk's first column on
+      const uint32_t win = __builtin_amdgcn_alignbit(mrow[min(wi + 1, a.KW)], mrow[wi], c0[sc] & 31);
+      const int32_t ncol = min(c0[sc + 1] - c0[sc] + 1, NX);
+      const uint32_t cmask = 0xffffffffu >> (32 - ncol);
+      if (__ballot((win & cmask) != cmask) == 0ull) continue;  // no row of the wave uses it
+      const uint16_t* Kr = &Ks[stage][(32 * sc + ql) * kKRow + 8 * g];
+      floatx16 sv;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sv[i] = 0.f;
+#pragma unroll
+      for (int kc = 0; kc < 4; ++kc)
+        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + 16 * kc), bq[kc],
+                                                     sv, 0, 0, 0);
+      // mask product: slots 8 g .. 8 g + 7 of this lane half (and 16 more for NX = 32)
+#pragma unroll
+      for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) {
+        const uint32_t un = NX == 8 ? (win & 0xffu) : ((win >> (16 * e + 8 * g)) & 0xffu);
+        const uint32_t xx = un | (un << 15);  // bits 2 j and 2 j + 1 sit at 2 j and 2 j + 16
+        const u32x4 bx = {(xx << 14) & gmask, (xx << 12) & gmask, (xx << 10) & gmask, (xx << 8) & gmask};
+        const uint16_t* Ke = &Ks[stage][(32 * sc + ql) * kKRow + kHeadDim + (NX == 8 ? 0 : 16 * e + 8 * g)];
+        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Ke),
+                                                     __builtin_bit_cast(bf16x8, bx), sv, 0, 0, 0);
+      }
+      float y[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) y[i] = fmaf(sv[i], a.c, -m_ref);
+      if (u0 + 32 > u_free) {  // straddles the causal diagonal or the end of the sequence
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int32_t slot = 8 * (i >> 2) + 4 * g + (i & 3);  // reg i <-> entry u0 + slot
+          y[i] = u0 + slot < my_ucount ? y[i] : -INFINITY;
+        }
+      }
+      // V^T fragments through the LDS transpose read, requested ahead of the softmax
+      bf16x8 av[2][2];
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const uint16_t* Vr = &Vs[stage][(32 * sc + 4 * g + ((ql & 15) >> 2)) * kVRow +
+                                        32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) {
+          const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kVRow);
+          const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kVRow);
+          av[mt][c2] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+      }
+      float ymax = fmaxf(fmaxf(y[0], y[1]), y[2]);
+#pragma unroll
+      for (int i = 3; i < 15; i += 2) ymax = fmaxf(fmaxf(ymax, y[i]), y[i + 1]);
+      ymax = half_max(fmaxf(ymax, y[15]));
+      const bool refresh = ymax > m_thr;
+      if (__ballot(refresh) != 0ull) {
+        const float delta = refresh ? ymax : 0.f;
+        const float corr = (refresh && m_thr > 0.f) ? __builtin_amdgcn_exp2f(-delta) : 1.f;
+        l_run *= corr;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { oacc[0][i] *= corr; oacc[1][i] *= corr; }
+        m_ref += delta;
+        m_thr = refresh ? kRefSlack : m_thr;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) y[i] -= delta;
+      }
+      // weights as rounded value + rounded remainder; the row sum is taken over what the products
+      // use.  O^T += V^T P^T, V^T fragments in the key order of the P registers.
+      const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+      const bf16x2 neg_lo = __builtin_bit_cast(bf16x2, neg_lo_bits), neg_hi = __builtin_bit_cast(bf16x2, neg_hi_bits);
+      auto frag = [](const bf16x2* p) {
+        const bf16x4 lo = __builtin_shufflevector(p[0], p[1], 0, 1, 2, 3);
+        const bf16x4 hi = __builtin_shufflevector(p[2], p[3], 0, 1, 2, 3);
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      };
+#pragma unroll
+      for (int c2 = 0; c2 < 2; ++c2) {
+        bf16x2 h[4], l[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p0 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * e]), p1 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * e + 1]);
+          const floatx2 f2 = {p0, p1};
+          h[e] = __builtin_convertvector(f2, bf16x2);
+          const floatx2 r2 = {__builtin_amdgcn_fdot2_f32_bf16(h[e], neg_lo, p0, false),
+                              __builtin_amdgcn_fdot2_f32_bf16(h[e], neg_hi, p1, false)};
+          l[e] = __builtin_convertvector(r2, bf16x2);
+          l_run = __builtin_amdgcn_fdot2_f32_bf16(h[e], ones, l_run, false);
+          l_run = __builtin_amdgcn_fdot2_f32_bf16(l[e], ones, l_run, false);
+        }
+        const bf16x8 ph = frag(h), pl = frag(l);
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+          oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], ph, oacc[mt], 0, 0, 0);
+          oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], pl, oacc[mt], 0, 0, 0);
+        }
+      }
+    }
+    if (step + 1 < nsteps) SEA_CPARK(stage ^ 1);
+    __syncthreads();
+  }
+#undef SEA_CFETCH
+#undef SEA_CPARK
+  l_run = half_sum(l_run);
+  if (t < a.T) {
+    const float inv = (row_active && l_run > 0.f) ? 1.f / l_run : 0.f;
+    uint16_t* Or = a.O + (head * a.T + t) * kHeadDim;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        // regs 4 q4 .. 4 q4 + 3 <-> d = 32 mt + 8 q4 + 4 g + 0..3
+        const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
+        const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
+        const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
+        *reinterpret_cast<bf16x4*>(Or + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
+      }
+  }
+}
+
+}  // namespace
+
+// Any fixed-bucket selection whose keys per column are either all of the column's or the same number
+// for every column (a cap between the two widths of a ragged split cannot occur: min(w, cap) is then
+// the cap for both).  div_small needs r (w + 1) < 2^21; the scale must leave -2^127 scale far below
+// every real score.
+bool column_attn_supported(const Shape& s, sea_dtype dt) {
+  if (dt != SEA_BF16 || s.geometry != 0 || s.T > (1 << 24) || !(s.scale > 1e-20f)) return false;
+  const int32_t w0 = s.T / s.K;
+  if (s.rep_cap > w0) return true;
+  return static_cast<int64_t>(s.rep_cap) * (w0 + 1) < (1 << 21);
+}
+
+hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
+                              const uint32_t* mbits, uint16_t* O, hipStream_t st) {
+  if (!column_attn_supported(s, SEA_BF16)) return hipErrorNotSupported;
+  StageScope scope(SEA_STAGE_SPARSE, st);
+  ColumnArgs a{};
+  a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;
+  a.N = s.N; a.H = s.H; a.T = s.T; a.Kc = s.K; a.KW = (s.K + 31) / 32;
+  a.w0 = s.T / s.K; a.rm = s.T % s.K;
+  a.r = s.rep_cap > a.w0 ? 0 : s.rep_cap;
+  a.U = a.r == 0 ? s.T : s.K * a.r;
+  a.A = a.r == 0 ? s.K : 1; a.D = a.r == 0 ? s.T : a.r;
+  a.q32 = 32 * a.A / a.D; a.r32 = 32 * a.A % a.D;
+  a.invK = 1.0f / static_cast<float>(s.K); a.invr = a.r == 0 ? 0.f : 1.0f / static_cast<float>(a.r);
+  a.causal = s.causal; a.c = s.scale * kLog2e;
+  a.group_heads = group_heads_for(s.N, a.U);
+  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128)), block(256);
+  const size_t shm = static_cast<size_t>(128) * (a.KW + 1) * sizeof(uint32_t);
+  const int32_t per = a.r == 0 ? a.w0 : a.r;  // least keys per column
+  if (per >= 5) hipLaunchKernelGGL(column_attn_kernel<8>, grid, block, shm, st, a);
+  else if (per >= 3) hipLaunchKernelGGL(column_attn_kernel<16>, grid, block, shm, st, a);
+  else hipLaunchKernelGGL(column_attn_kernel<32>, grid, block, shm, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace sea

@@ -1,0 +1,67 @@
+"""Column-selected masks whose columns have any width (K does not divide T, or a column emits a number
+of keys that is no power of two), bf16: the tiled attention that takes the mask through the matrix
+product, at the widths where its column slots, tiles and list ends change, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2310_01777_amd import synth
+from tests.util import TOL, assert_close, oracle_params, to_np64
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, T, m, K, k^, budget, causal, pad)
+CASES = [
+    (1, 2, 129, 64, 128, 31, 0, True, 0.0),      # one or two keys per column: 32 slots; a tile of one row
+    (2, 1, 383, 64, 128, 40, 0, False, 0.3),     # two or three: still 32 slots
+    (1, 2, 385, 128, 128, 17, 0, True, 0.0),     # three or four: 16 slots
+    (1, 1, 639, 64, 128, 50, 0, True, 0.3),      # four or five: 16 slots
+    (1, 2, 640, 64, 128, 50, 0, True, 0.0),      # exactly five: 8 slots, eight columns in a sub-chunk
+    (1, 2, 257, 256, 31, 9, 0, True, 0.0),       # eight or nine, K below one mask word
+    (2, 2, 1000, 128, 33, 8, 0, False, 0.3),     # 30 or 31, K just above one mask word
+    (1, 1, 2047, 64, 9, 4, 0, True, 0.0),        # columns of more than 64 keys
+    (1, 2, 1100, 64, 64, 10, 50, True, 0.0),     # five of the 17 or 18 keys of a column
+    (1, 2, 1025, 64, 64, 16, 48, False, 0.3),    # three of 16 or 17
+    (1, 1, 1500, 64, 100, 20, 20, True, 0.0),    # one of 15
+    (1, 1, 1300, 64, 13, 5, 500, True, 0.0),     # 100 of 100: the cap equals every width
+    (1, 1, 1030, 32, 1024, 100, 0, True, 0.0),   # the largest K
+    (1, 1, 37, 64, 5, 5, 0, False, 0.0),         # every column selected, less than one step of keys
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "_".join(str(int(v)) if not isinstance(v, float) else str(v) for v in c))
+def test_any_column_width(case):
+    from paper_2310_01777_amd import binding as sea
+    B, H, T, m, K, kh, kb, causal, pad = case
+    wl = synth.Workload("columns", B, H, T, 64, m, K, kh, kb, causal, "bf16", 4, pad)
+    x = synth.make_inputs(wl)
+    seq = None if x["seq_len"] is None else x["seq_len"].clone()
+    if seq is not None:
+        seq[-1] = 0 if B > 1 else T // 2         # a sequence without keys
+        for k in "KV":                           # what lies behind a sequence's end is never read
+            for b in range(B):
+                x[k][b, :, int(seq[b]):] = float("nan")
+    d = {k: x[k].cuda() for k in "QKVW"}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=m, K=K, k_hat=kh, k_budget=kb, causal=causal, scale=wl.scale,
+                      dtype="bf16", seq_len=None if seq is None else seq.cuda())
+    out, ws = sea.alloc_outputs(p), sea.alloc_workspace(p)
+    print(f"[case] columns {case}", flush=True)
+    sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], out["O"], out["A_hat"], out["sel"], out["idx"], out["cnt"], ws,
+                    mhat=out["mhat"])
+    O2 = torch.full_like(out["O"], float("nan"))   # and without any intermediate
+    sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], O2, workspace=ws)
+    torch.cuda.synchronize()
+    po = oracle_params(wl)
+    sl = None if seq is None else seq.numpy()
+    clean = {k: torch.nan_to_num(x[k]) for k in "QKV"}
+    A = out["A_hat"].cpu().numpy().astype(np.float64)
+    assert_close(A, oracle.estimate(po, to_np64(clean["Q"]), to_np64(clean["K"]), to_np64(x["W"]), seq_len=sl),
+                 TOL["bf16"], "A_hat")
+    sel, idx, cnt = oracle.topk_mask(po, A, seq_len=sl)
+    assert np.array_equal(out["sel"].cpu().numpy(), sel)
+    assert np.array_equal(out["idx"].cpu().numpy(), idx)
+    assert np.array_equal(out["cnt"].cpu().numpy(), cnt)
+    want = oracle.sparse_attn(po, to_np64(clean["Q"]), to_np64(clean["K"]), to_np64(clean["V"]), idx, cnt)
+    assert_close(to_np64(out["O"]), want, TOL["bf16"], "O")
+    assert torch.equal(O2, out["O"])
