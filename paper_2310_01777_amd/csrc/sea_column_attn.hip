@@ -24,6 +24,7 @@
 // registers and the kernel is 15 % slower).  Measured on the layer B = 8, H = 32, T = 2000 (padded by
 // 0-25 %), K = 256, k^ = 64: 0.29 ms; the per-row gather kernel that ran before took 2.71 ms and its
 // key lists another 0.57 ms to write.
+#include "sea_columns.h"
 #include "sea_internal.h"
 #include "sea_tile.h"
 
@@ -40,37 +41,28 @@ struct ColumnArgs {
   const uint32_t* mbits;  // [N][T][KW] selected-column bits
   uint16_t* O;
   const int32_t* seq_len;
-  int32_t N, H, T, Kc, KW;
+  int32_t N, H, T, KW;
+  Columns cg;
   int32_t r;         // keys per column, 0 = whole columns (the list is all T keys)
-  int32_t w0, rm;    // T = w0 Kc + rm
   int32_t U;         // length of the compact list
   // column of list entry u = floor(u A / D); 32 entries further: q32 more, remainder r32 more
   int32_t A, D, q32, r32;
-  float invK, invr;  // 1 / Kc, 1 / r
+  float invr;        // 1 / r
   int32_t causal, group_heads;
   float c;           // scale * log2(e)
 };
 
-// floor(x / n) for 0 <= x < 2^21, inv = 1 / n rounded to fp32: x + 1/2 is at least 1 / (2 n) away from the
-// next multiple of n (in quotients), and the fused product is off by less than x / n 2^-23 < 1 / (4 n)
-__device__ __forceinline__ int32_t div_small(int32_t x, float inv) {
-  return static_cast<int32_t>(fmaf(static_cast<float>(x), inv, 0.5f * inv));
-}
-// first key of column c = ceil(c T / K) = c w0 + ceil(c rm / K)
-__device__ __forceinline__ int32_t column_start(const ColumnArgs& a, int32_t c) {
-  return c * a.w0 + div_small(c * a.rm + a.Kc - 1, a.invK);
-}
 // position of entry i of column c
 __device__ __forceinline__ int32_t entry_pos(const ColumnArgs& a, int32_t c, int32_t i) {
-  const int32_t s0 = column_start(a, c), w = column_start(a, c + 1) - s0;
+  const int32_t s0 = column_start(a.cg, c), w = column_start(a.cg, c + 1) - s0;
   return s0 + div_small(i * w, a.invr);
 }
 // number of list entries with position <= jmax
 __device__ __forceinline__ int32_t list_count(const ColumnArgs& a, int32_t jmax) {
   if (jmax < 0) return 0;
   if (a.r == 0) return jmax + 1;
-  const int32_t col = bucket_of(jmax, a.T, a.Kc);
-  const int32_t s0 = column_start(a, col), w = column_start(a, col + 1) - s0;
+  const int32_t col = column_of(a.cg, jmax);
+  const int32_t s0 = column_start(a.cg, col), w = column_start(a.cg, col + 1) - s0;
   return col * a.r + min(a.r, ((jmax - s0 + 1) * a.r + w - 1) / w);
 }
 
@@ -351,18 +343,18 @@ hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t*
   StageScope scope(SEA_STAGE_SPARSE, st);
   ColumnArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;
-  a.N = s.N; a.H = s.H; a.T = s.T; a.Kc = s.K; a.KW = (s.K + 31) / 32;
-  a.w0 = s.T / s.K; a.rm = s.T % s.K;
-  a.r = s.rep_cap > a.w0 ? 0 : s.rep_cap;
+  a.N = s.N; a.H = s.H; a.T = s.T; a.KW = (s.K + 31) / 32;
+  a.cg = columns_of(s.T, s.K);
+  a.r = s.rep_cap > a.cg.w0 ? 0 : s.rep_cap;
   a.U = a.r == 0 ? s.T : s.K * a.r;
   a.A = a.r == 0 ? s.K : 1; a.D = a.r == 0 ? s.T : a.r;
   a.q32 = 32 * a.A / a.D; a.r32 = 32 * a.A % a.D;
-  a.invK = 1.0f / static_cast<float>(s.K); a.invr = a.r == 0 ? 0.f : 1.0f / static_cast<float>(a.r);
+  a.invr = a.r == 0 ? 0.f : 1.0f / static_cast<float>(a.r);
   a.causal = s.causal; a.c = s.scale * kLog2e;
   a.group_heads = group_heads_for(s.N, a.U);
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128)), block(256);
   const size_t shm = static_cast<size_t>(128) * (a.KW + 1) * sizeof(uint32_t);
-  const int32_t per = a.r == 0 ? a.w0 : a.r;  // least keys per column
+  const int32_t per = a.r == 0 ? a.cg.w0 : a.r;  // least keys per column
   if (per >= 5) hipLaunchKernelGGL(column_attn_kernel<8>, grid, block, shm, st, a);
   else if (per >= 3) hipLaunchKernelGGL(column_attn_kernel<16>, grid, block, shm, st, a);
   else hipLaunchKernelGGL(column_attn_kernel<32>, grid, block, shm, st, a);

@@ -1,5 +1,6 @@
-// Fused random-feature estimate for the common shapes (bf16, K | T, column width a power of two
-// up to 128, m in {64, 128, 256}, K <= 256): two kernels; no feature tensor reaches HBM.  For causal
+// Fused random-feature estimate for the common shapes (bf16, m in {64, 128, 256}, K <= 256): two kernels;
+// no feature tensor reaches HBM.  Columns of a power-of-two width have a key kernel of their own, all
+// other widths (K that does not divide T among them) take key_columns_kernel.  For causal
 // columns wider than 16 keys the key side also leaves, per 16-key tile, the sum of the rounded
 // features of the column's earlier tiles, split into three bf16 planes (24 bits, i.e. the fp32
 // sum itself), which is all the own-column term needs from outside the wave.
@@ -20,6 +21,7 @@
 // accumulators feed the next product without any shuffle or memory round trip.
 #include <algorithm>
 
+#include "sea_columns.h"
 #include "sea_internal.h"
 #include "sea_rowlanes.h"
 
@@ -378,12 +380,134 @@ __global__ __launch_bounds__(256) void wide_columns_kernel(Shape s, const float*
 }
 
 // ------------------------------------------------------------------------------------------
+// key side for columns of any width.  A block takes G consecutive columns of one head (G <= 16, about
+// 256 keys) and walks their keys in 16-key tiles; wave w owns a quarter of the features, whose rows of W
+// stay in registers as operands.  Column sums are matrix products as well: with the block's columns as
+// accumulator rows, sum[c][f] += onehot[c][key] phi[key][f], in fp32 (v_mfma_f32_16x16x4_f32: the
+// accumulator layout of the projection is the operand layout of this product, so phi goes from one to
+// the other in place), and the accumulators stay in registers over the whole walk -- no width, alignment
+// or column boundary needs a case of its own.  Norms and columns of a 64-key step are taken once per
+// block (wave w: its 16 keys) and shared through LDS.
+// Causal: the same product over the ROUNDED features (bf16, one 16x16x16 product per 16 features) gives
+// the running sum of the current column; before each tile that a column began in front of, the sum of
+// that column's earlier keys goes out as fp32.
+// Bound: vector and matrix issue together.  B = 8, H = 32, T = 2000, K = 256, m = 256: 0.10 ms (1.54 ms with
+// the three kernels that write the features to memory, rows kernel and selection included: 0.25 ms).
+// ------------------------------------------------------------------------------------------
+template <int MC, bool CAUSAL>
+__global__ __launch_bounds__(256) void key_columns_kernel(Shape s, Columns cg, const uint16_t* __restrict__ K,
+                                                          const uint16_t* __restrict__ W, uint16_t* __restrict__ state,
+                                                          float* __restrict__ pref, float c_dot, float c_norm,
+                                                          int32_t G) {
+  constexpr int m = 32 * MC, FT = MC / 2;  // FT = 16-feature tiles per wave
+  __shared__ __attribute__((aligned(16))) float bias_s[2][64];
+  __shared__ __attribute__((aligned(16))) int32_t col_s[2][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  const uint32_t groups = (s.K + G - 1) / G;
+  const int64_t head = blockIdx.x / groups;
+  const int32_t c0 = static_cast<int32_t>(blockIdx.x % groups) * G, c1 = min(c0 + G, s.K);
+  const int32_t b = static_cast<int32_t>(head / s.H);
+  const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
+  const int32_t key0 = column_start(cg, c0), key1 = min(column_start(cg, c1), len);
+  const uint16_t* Kh = K + head * static_cast<int64_t>(s.T) * kHeadDim;
+  // W rows of this wave's features, in slot order: slot 16 (wid FT + ft) + lr of a fragment-ordered row
+  bf16x8 w0[FT], w1[FT];
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft) {
+    const int slot = 16 * (wid * FT + ft) + lr;
+    const int f = (slot & ~31) + 16 * ((slot >> 2) & 1) + 4 * ((slot & 31) >> 3) + (slot & 3);
+    w0[ft] = *reinterpret_cast<const bf16x8*>(W + f * kHeadDim + 8 * lg);
+    w1[ft] = *reinterpret_cast<const bf16x8*>(W + f * kHeadDim + 32 + 8 * lg);
+  }
+  floatx4 sum[FT], rsum[CAUSAL ? FT : 1];
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft) sum[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (CAUSAL)
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft) rsum[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  const int32_t base = key0 & ~15;
+  const int32_t nsteps = key1 > key0 ? (key1 - base + 63) / 64 : 0;
+  for (int32_t st = 0; st < nsteps; ++st) {
+    const int32_t s0 = base + 64 * st, buf = st & 1;
+    {
+      // norm and local column of key s0 + 16 wid + lr (keys outside the block's columns: no column)
+      const int32_t j = s0 + 16 * wid + lr;
+      const uint16_t* X = Kh + static_cast<int64_t>(min(j, len - 1)) * kHeadDim;
+      float nx = sumsq8(*reinterpret_cast<const bf16x8*>(X + 8 * lg)) + sumsq8(*reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg));
+      nx += __shfl_xor(nx, 16, kWave);
+      nx += __shfl_xor(nx, 32, kWave);
+      if (lg == 0) {
+        bias_s[buf][16 * wid + lr] = c_norm * nx;
+        col_s[buf][16 * wid + lr] = (j >= key0 && j < key1) ? column_of(cg, j) - c0 : -1;
+      }
+    }
+    __syncthreads();  // (the buffers alternate: one barrier per step)
+#pragma unroll 1
+    for (int tile = 0; tile < 4; ++tile) {
+      const int32_t r0 = s0 + 16 * tile;
+      if (r0 >= key1) break;
+      const uint16_t* X = Kh + static_cast<int64_t>(min(r0 + lr, len - 1)) * kHeadDim;
+      const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(X + 8 * lg);
+      const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg);
+      const float4 bias = *reinterpret_cast<const float4*>(&bias_s[buf][16 * tile + 4 * lg]);
+      const int4 cl = *reinterpret_cast<const int4*>(&col_s[buf][16 * tile + 4 * lg]);
+      const float bv[4] = {bias.x, bias.y, bias.z, bias.w};
+      const float oh[4] = {cl.x == lr ? 1.f : 0.f, cl.y == lr ? 1.f : 0.f, cl.z == lr ? 1.f : 0.f, cl.w == lr ? 1.f : 0.f};
+      shortx4 ohb;
+      if (CAUSAL) {
+        const uint2 u = {pack_bf16(oh[0], oh[1]), pack_bf16(oh[2], oh[3])};
+        ohb = __builtin_bit_cast(shortx4, u);
+        // keys of the tile's first column that lie before the tile: their sum is accumulator row lc
+        const int32_t lc = col_s[buf][16 * tile];  // (uniform; -1: the column belongs to another block)
+        if (lc >= 0 && column_start(cg, c0 + lc) < r0) {
+          float* dst = pref + (head * ((s.T + 15) >> 4) + (r0 >> 4)) * m + 16 * wid * FT + lr;
+          const int ri = __builtin_amdgcn_readfirstlane(lc & 3);
+#pragma unroll
+          for (int ft = 0; ft < FT; ++ft) {
+            const float v = ri == 0 ? rsum[ft][0] : (ri == 1 ? rsum[ft][1] : (ri == 2 ? rsum[ft][2] : rsum[ft][3]));
+            if (lg == (lc >> 2)) dst[16 * ft] = v;
+          }
+        }
+      }
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc = mfma16(x0, w0[ft], acc);
+        acc = mfma16(x1, w1[ft], acc);
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, acc[i], -bv[i]));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh[i], v[i], sum[ft], 0, 0, 0);
+        if (CAUSAL) {
+          const uint2 u = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+          rsum[ft] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ohb, __builtin_bit_cast(shortx4, u), rsum[ft], 0, 0, 0);
+        }
+      }
+    }
+  }
+  // accumulator register i of a lane: column c0 + 4 lg + i
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (c0 + 4 * lg + i < c1)
+        state[(head * s.K + c0 + 4 * lg + i) * m + 16 * (wid * FT + ft) + lr] = f32_to_bf16(sum[ft][i]);
+}
+
+// ------------------------------------------------------------------------------------------
 // query side.  Block = 4 waves = 64 rows of one head (16 per wave).
 // ------------------------------------------------------------------------------------------
 constexpr int kColStage = 32;   // columns of the state staged in LDS per step
 
 // NCT = 16-column tiles a row can have (4, 8 or 16 for K <= 64, 128, 256).  WLOG = log2(column
-// width) for widths up to 16; 5 stands for every wider column (the shift is then read from the shape).
+// width) for widths up to 16; 5 stands for every wider power of two (the shift is then read from the
+// shape), kAnyWidth for widths that are none, or that differ from column to column (K does not divide T).
+constexpr int kAnyWidth = 6;
+
 template <int MC, bool CAUSAL, int WLOG, int NCT>
 __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                             const uint16_t* __restrict__ K,
@@ -393,9 +517,11 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
                                                             const uint16_t* __restrict__ bpref,
                                                             float* __restrict__ A_hat,
                                                             uint32_t* __restrict__ mbits, float c_dot,
-                                                            float c_norm, int32_t group_heads) {
+                                                            float c_norm, int32_t group_heads, Columns cg) {
   constexpr int m = 32 * MC;
+  constexpr bool ANYW = WLOG == kAnyWidth;
   const int wl = WLOG >= 5 ? 31 - __clz(s.T / s.K) : WLOG;  // log2(column width)
+  auto col_of = [&](int32_t j) { return ANYW ? column_of(cg, j) : j >> wl; };
   constexpr int kSRow = m + 8;  // halfwords per staged state row (+16 B pad): conflict-free b128 reads
   // W is dead once both projections are done; the state stages then reuse its space
   constexpr int kStageHalfwords = kColStage * kSRow;
@@ -427,7 +553,7 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   constexpr int kVecPerThread = kVecPerStage / 256;    // 1, 2 or 4 (m = 64..256); m = 32 -> 0
   static_assert(MC >= 2, "m >= 64");
   uint4 sreg0 = {0u, 0u, 0u, 0u}, sreg1 = sreg0, sreg2 = sreg0, sreg3 = sreg0;  // named: stay in VGPRs
-  const int32_t ncols_wg = CAUSAL ? min(s.K, (min(wg_r0 + 63, s.T - 1) >> wl) + 1) : s.K;
+  const int32_t ncols_wg = CAUSAL ? __builtin_amdgcn_readfirstlane(min(s.K, col_of(min(wg_r0 + 63, s.T - 1)) + 1)) : s.K;
   const int32_t nstages = (ncols_wg + kColStage - 1) / kColStage;
 #define SEA_SFETCH1(reg_, q_, st_)                                                              \
   if (kVecPerThread > (q_)) {                                                                  \
@@ -465,19 +591,42 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   // Prefix planes of the wave's tile inside its 128-key block (its column, if narrower): 3 m
   // halfwords, contiguous; lane l takes 16-byte pieces l and l + 64.
   bool tile_planes = false;
-  if (CAUSAL && WLOG >= 5) {
+  // Any width: the sum of the rounded features of the column's keys before the wave's tile comes as m
+  // fp32 values; each lane splits its share into the planes.
+  int32_t own0 = 0;  // first key of the column the wave's first row lies in
+  if (CAUSAL && ANYW) {
+    own0 = __builtin_amdgcn_readfirstlane(column_start(cg, col_of(min(r0, s.T - 1))));
+    tile_planes = r0 < s.T && own0 < r0;
+  } else if (CAUSAL && WLOG >= 5) {
     const int tl = min(wl, 7) - 4;  // log2(tiles per prefix group)
     tile_planes = r0 < s.T && ((r0 >> 4) & ((1 << tl) - 1)) != 0;  // wave-uniform
   }
   uint4 preg0 = {0u, 0u, 0u, 0u}, preg1 = preg0;
-  if (tile_planes) {
+  constexpr int kPieceLen = m >= 256 ? 4 : m / 64;  // any width: features per lane
+  float pw[kPieceLen];
+  if (ANYW && tile_planes) {
+    const float* psrc = reinterpret_cast<const float*>(pref) + (head * ((s.T + 15) >> 4) + (r0 >> 4)) * m + lane * kPieceLen;
+#pragma unroll
+    for (int q = 0; q < kPieceLen; ++q) pw[q] = psrc[q];
+  } else if (tile_planes) {
     const uint4* psrc = reinterpret_cast<const uint4*>(pref + (head * (s.T >> 4) + (r0 >> 4)) * 3 * m);
     constexpr int kPieces = 3 * m / 8;
     if (lane < kPieces) preg0 = psrc[lane];
     if (lane + 64 < kPieces) preg1 = psrc[lane + 64];
   }
   stage_w(W, Ws, m, tid);
-  if (tile_planes) {
+  if (ANYW && tile_planes) {
+    uint16_t* pdst = &planes_s[wid * 3 * m + lane * kPieceLen];
+#pragma unroll
+    for (int q = 0; q < kPieceLen; ++q) {
+      const uint16_t hi = f32_to_bf16(pw[q]);
+      const float r1 = pw[q] - bf16_to_f32(hi);
+      const uint16_t lo = f32_to_bf16(r1);
+      pdst[q] = hi;
+      pdst[m + q] = lo;
+      pdst[2 * m + q] = f32_to_bf16(r1 - bf16_to_f32(lo));
+    }
+  } else if (tile_planes) {
     constexpr int kPieces = 3 * m / 8;
     uint4* pdst = reinterpret_cast<uint4*>(&planes_s[wid * 3 * m]);
     if (lane < kPieces) pdst[lane] = preg0;
@@ -556,13 +705,15 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
     // the row's own column: sum over keys j <= t of that column of phi(q_t) . phi(k_j).  Those
     // keys are the wave's own 16 rows (S = phi(Q) phi(K_own)^T with a lower-triangular, same-column
     // mask) and, for columns wider than 16, the 16-key tiles of the column before the wave.
+    const int32_t own_t = ANYW ? column_start(cg, col_of(tc)) : 0;  // first key of the row's own column
     floatx4 sd = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < MC; ++kc) sd = mfma16(kfrag[kc], afrag[kc], sd);  // rows = keys 4 lg + i, col = query lr
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int rk = 4 * lg + i;  // key row within the wave; the query row within the wave is lr
-      const bool ok = (rk <= lr) && (WLOG >= 4 || (rk >> WLOG) == (lr >> WLOG));
+      const bool ok = ANYW ? (rk <= lr && r0 + rk >= own_t)
+                           : (rk <= lr) && (WLOG >= 4 || (rk >> WLOG) == (lr >> WLOG));
       sd[i] = ok ? sd[i] : 0.f;
     }
     // Earlier keys of the same column: every one of them precedes every row of the wave, so only
@@ -573,14 +724,22 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
     if (WLOG >= 5 && r0 < s.T) {
       if (tile_planes) {
         const uint16_t* src = &planes_s[(wid * 3 + min(lr, 2)) * m + 8 * lg];
+        // any width: only the rows of the wave's first column have keys before the tile
+        floatx4 sp = ANYW ? floatx4{0.f, 0.f, 0.f, 0.f} : sd;
 #pragma unroll
         for (int kc = 0; kc < MC; ++kc) {
           uint4 f = *reinterpret_cast<const uint4*>(src + 32 * kc);
           if (lr > 2) f = uint4{0u, 0u, 0u, 0u};
-          sd = mfma16(__builtin_bit_cast(bf16x8, f), afrag[kc], sd);
+          sp = mfma16(__builtin_bit_cast(bf16x8, f), afrag[kc], sp);
+        }
+        if (ANYW) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sd[i] += own_t == own0 ? sp[i] : 0.f;
+        } else {
+          sd = sp;
         }
       }
-      if (wl > 7 && ((r0 >> 7) & ((1 << (wl - 7)) - 1)) != 0) {
+      if (!ANYW && wl > 7 && ((r0 >> 7) & ((1 << (wl - 7)) - 1)) != 0) {
         const uint16_t* src = bpref + ((head * (s.T >> 7) + (r0 >> 7)) * 3 + min(lr, 2)) * m + 8 * lg;
 #pragma unroll
         for (int kc = 0; kc < MC; ++kc) {
@@ -600,7 +759,7 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   floatx4 acc[NCT];
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int32_t ncols_wave = CAUSAL ? min(s.K, (min(r0 + 15, s.T - 1) >> wl) + 1) : s.K;
+  const int32_t ncols_wave = CAUSAL ? __builtin_amdgcn_readfirstlane(min(s.K, col_of(min(r0 + 15, s.T - 1)) + 1)) : s.K;
 #pragma unroll
   for (int st = 0; st < NCT * 16 / kColStage; ++st) {
     if (st < nstages) {
@@ -634,10 +793,10 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   const int32_t trow = r0 + lr;
   const bool act = trow < len;
   const int32_t jmax = CAUSAL ? min(trow, len - 1) : len - 1;
-  const int32_t ncnd = act ? (jmax >> wl) + 1 : 0;
+  const int32_t ncnd = act ? col_of(jmax) + 1 : 0;
   const int32_t e = ncnd - 1 - 4 * lg;  // column 16 ct + 4 lg + i is the own one iff 16 ct + i == e
   const bool act_all = r0 + 15 < len;  // wave-uniform
-  const int32_t ct_free = act_all ? (((CAUSAL ? r0 : len - 1) >> wl) >> 4) : 0;
+  const int32_t ct_free = act_all ? __builtin_amdgcn_readfirstlane(col_of(CAUSAL ? r0 : len - 1)) >> 4 : 0;
   float rsum = 0.f;
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) {
@@ -907,8 +1066,7 @@ int wlog_of(const Shape& s) {
 }  // namespace
 
 bool estimate_fused_supported(const Shape& s) {
-  const int wl = wlog_of(s);
-  if (wl < 0 || wl > 20) return false;
+  if (s.geometry != 0 || s.T > (1 << 24) || wlog_of(s) > 20) return false;
   if (s.m != 64 && s.m != 128 && s.m != 256) return false;
   if (s.K > 256) return false;
   return true;
@@ -919,7 +1077,7 @@ size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 struct FusedWs {
   size_t state, pref, bsum_u, bsum_r, bpref, total;
 };
-// state | tile prefixes (causal, columns > 16) | for columns > 128: block sums, rounded block sums
+// state | tile prefixes (causal; columns > 16: three bf16 planes; columns of any width: fp32) | for columns > 128: block sums, rounded block sums
 // and block prefixes (the last two causal only)
 FusedWs fused_layout(const Shape& s) {
   const int wl = wlog_of(s);
@@ -927,7 +1085,9 @@ FusedWs fused_layout(const Shape& s) {
   FusedWs f{};
   size_t off = 0;
   f.state = off; off += up256(N * s.K * s.m * 2);
-  f.pref = off;  if (s.causal && wl > 4) off += up256(N * (s.T / 16) * 3 * s.m * 2);
+  f.pref = off;
+  if (s.causal && wl < 0) off += up256(N * ((s.T + 15) / 16) * s.m * 4);
+  if (s.causal && wl > 4) off += up256(N * (s.T / 16) * 3 * s.m * 2);
   f.bsum_u = off; if (wl > 7) off += up256(N * (s.T / 128) * s.m * 4);
   f.bsum_r = off; if (wl > 7 && s.causal) off += up256(N * (s.T / 128) * s.m * 4);
   f.bpref = off;  if (wl > 7 && s.causal) off += up256(N * (s.T / 128) * 3 * s.m * 2);
@@ -954,10 +1114,10 @@ void launch_rows(const Shape& s, const uint16_t* Q, const uint16_t* K, const uin
                  hipStream_t st) {
   if (s.causal)
     hipLaunchKernelGGL((estimate_rows_kernel<MC, true, WLOG, NCT>), grid, dim3(256), 0, st, s, Q, K, W, f.state,
-                       f.pref, f.bpref, A_hat, mbits, c_dot, c_norm, gh);
+                       f.pref, f.bpref, A_hat, mbits, c_dot, c_norm, gh, columns_of(s.T, s.K));
   else
     hipLaunchKernelGGL((estimate_rows_kernel<MC, false, WLOG, NCT>), grid, dim3(256), 0, st, s, Q, K, W, f.state,
-                       f.pref, f.bpref, A_hat, mbits, c_dot, c_norm, gh);
+                       f.pref, f.bpref, A_hat, mbits, c_dot, c_norm, gh, columns_of(s.T, s.K));
 }
 
 template <int MC, int WLOG>
@@ -971,6 +1131,22 @@ void launch_key(const Shape& s, const uint16_t* K, const uint16_t* W, const Fuse
   const uint32_t bph = (ktiles + iters - 1) / iters;
   hipLaunchKernelGGL((key_state_kernel<MC, WLOG>), dim3(static_cast<uint32_t>(s.N) * bph), dim3(64 * kKeyWaves), 0, st,
                      s, K, W, f.state, f.pref, f.bsum_u, f.bsum_r, c_dot, c_norm, iters);
+}
+
+// columns per block: about 256 keys, so that the 16 columns a product has room for are used where columns
+// are narrow and wide columns still give many blocks
+template <int MC>
+void launch_key_columns(const Shape& s, const uint16_t* K, const uint16_t* W, const FusedPtrs& f, float c_dot,
+                        float c_norm, hipStream_t st) {
+  const int32_t w0 = s.T / s.K;
+  const int32_t G = std::min(16, std::max(1, 256 / w0));
+  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.K + G - 1) / G));
+  float* pref = reinterpret_cast<float*>(f.pref);
+  const Columns cg = columns_of(s.T, s.K);
+  if (s.causal)
+    hipLaunchKernelGGL((key_columns_kernel<MC, true>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G);
+  else
+    hipLaunchKernelGGL((key_columns_kernel<MC, false>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G);
 }
 
 template <int MC, int WLOG>
@@ -995,6 +1171,7 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
   {
     StageScope scope(SEA_STAGE_STATE, st);
     switch (wl) {
+      case -1: launch_key_columns<MC>(s, K, W, f, c_dot, c_norm, st); break;
       case 0: launch_key<MC, 0>(s, K, W, f, c_dot, c_norm, st); break;
       case 1: launch_key<MC, 1>(s, K, W, f, c_dot, c_norm, st); break;
       case 2: launch_key<MC, 2>(s, K, W, f, c_dot, c_norm, st); break;
@@ -1010,6 +1187,7 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
   switch (wl) {
+    case -1: launch_rows_k<MC, kAnyWidth>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;
     case 0: launch_rows_k<MC, 0>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;
     case 1: launch_rows_k<MC, 1>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;
     case 2: launch_rows_k<MC, 2>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;
@@ -1029,7 +1207,7 @@ hipError_t launch_estimate_fused(const Shape& s, const uint16_t* Q, const uint16
   char* base = static_cast<char*>(ws);
   FusedPtrs f{};
   f.state = reinterpret_cast<uint16_t*>(base + lay.state);
-  if (s.causal && wl > 4) f.pref = reinterpret_cast<uint16_t*>(base + lay.pref);
+  if (s.causal && (wl < 0 || wl > 4)) f.pref = reinterpret_cast<uint16_t*>(base + lay.pref);
   if (wl > 7) {
     f.bsum_u = reinterpret_cast<float*>(base + lay.bsum_u);
     if (s.causal) {

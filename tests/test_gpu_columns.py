@@ -1,6 +1,7 @@
 """Column-selected masks whose columns have any width (K does not divide T, or a column emits a number
-of keys that is no power of two), bf16: the tiled attention that takes the mask through the matrix
-product, at the widths where its column slots, tiles and list ends change, against the oracle."""
+of keys that is no power of two), bf16: the estimator's key kernel for any width and the tiled attention
+that takes the mask through the matrix product, at the widths where column groups, column slots, tiles
+and list ends change, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -21,6 +22,8 @@ CASES = [
     (1, 2, 257, 256, 31, 9, 0, True, 0.0),       # eight or nine, K below one mask word
     (2, 2, 1000, 128, 33, 8, 0, False, 0.3),     # 30 or 31, K just above one mask word
     (1, 1, 2047, 64, 9, 4, 0, True, 0.0),        # columns of more than 64 keys
+    (2, 1, 2000, 64, 3, 2, 64, True, 0.3),       # columns of more than 256 keys: one per block on the key side
+    (1, 2, 250, 256, 250, 60, 0, True, 0.0),     # K = T, no power of two columns
     (1, 2, 1100, 64, 64, 10, 50, True, 0.0),     # five of the 17 or 18 keys of a column
     (1, 2, 1025, 64, 64, 16, 48, False, 0.3),    # three of 16 or 17
     (1, 1, 1500, 64, 100, 20, 20, True, 0.0),    # one of 15
