@@ -5,7 +5,12 @@
 // fetches 8 (bf16) or 4 (fp32) gathered rows per wave instruction, each row contiguous
 // across its lane group.  The softmax is the streaming (running max / running sum) form held
 // in registers; nothing of size T x T or T x L is ever written.
+//
+// Lists that hold a good part of the keys they span are better served by tiles: list_tile_kernel turns
+// the lists of 128 rows into key bits in LDS and walks the keys once for all of them on the matrix
+// cores.  Which form a 128-row block takes is decided on the device from the lists themselves.
 #include "sea_internal.h"
+#include "sea_tile.h"
 
 namespace sea {
 namespace {
@@ -13,7 +18,6 @@ namespace {
 constexpr int kWavesPerBlock = 4;
 constexpr int kUnroll = 4;
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ bf16x2 as_bf16x2(uint32_t w) {
   bf16x2 h;
   __builtin_memcpy(&h, &w, sizeof(h));
@@ -25,7 +29,7 @@ __device__ __forceinline__ double wave_xor_d(double v, int mask) { return __shfl
 // Where a row's key list lives.  Per-row lists: idx + row L, cnt[row] entries.  FlatCSR tensor
 // (crow != nullptr, idx = its column array): row (b, h, t) owns the entries of CSR row b T + t
 // whose column h' T + j has h' = h -- one contiguous run because columns ascend -- found by two
-// binary searches; the key is the entry minus h T.
+// searches; the key is the entry minus h T.
 struct KeyList {
   const int32_t* p;
   int32_t n;
@@ -38,36 +42,46 @@ __device__ __forceinline__ KeyList key_list(const Shape& s, int64_t row, const i
   const int64_t head = row / s.T, t = row - head * s.T;
   const int64_t b = head / s.H, h = head - b * s.H;
   const int64_t beg = crow[b * s.T + t], end = crow[b * s.T + t + 1];
-  int64_t bound[2];
+  // First entry >= h T and first entry >= (h + 1) T, both searches in step.  The heads of a time step list
+  // about equally many keys, so the first seven probes lie around where that puts the bound (mostly in
+  // one or two cache lines) and usually leave a few dozen entries; after that the range is cut in eight.
+  int64_t lo[2] = {beg, beg}, hi[2] = {end, end};
+  const int64_t key[2] = {h * s.T, (h + 1) * s.T};
+  for (bool first = true; lo[0] < hi[0] || lo[1] < hi[1]; first = false) {
+    int64_t at[2][7];
+    int32_t v[2][7];
 #pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const int64_t key = (h + e) * s.T;
-    int64_t a = beg, z = end;
-    while (a < z) {
-      const int64_t mid = (a + z) >> 1;
-      if (idx[mid] < key) a = mid + 1; else z = mid;
+    for (int e = 0; e < 2; ++e) {
+      const int64_t w = hi[e] - lo[e], guess = lo[e] + ((h + e) * w) / s.H;
+#pragma unroll
+      for (int i = 0; i < 7; ++i) {
+        constexpr int32_t kAround[7] = {-65, -17, -5, -1, 3, 15, 63};
+        at[e][i] = first ? min(max(guess + kAround[i], lo[e]), hi[e] - 1) : lo[e] + (((i + 1) * w) >> 3);
+        v[e][i] = idx[w > 0 ? at[e][i] : beg];
+      }
     }
-    bound[e] = a;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      if (lo[e] >= hi[e]) continue;
+#pragma unroll
+      for (int i = 0; i < 7; ++i) {
+        if (v[e][i] < key[e]) lo[e] = max(lo[e], at[e][i] + 1); else hi[e] = min(hi[e], at[e][i]);
+      }
+    }
   }
+  const int64_t bound[2] = {lo[0], lo[1]};
   return {idx + bound[0], static_cast<int32_t>(bound[1] - bound[0]), static_cast<int32_t>(h * s.T)};
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16: 8 lanes per row, 8 rows per wave load, fp32 logits (log2 domain) and accumulators
+// bf16: 8 lanes per row, 8 rows per wave load, fp32 logits (log2 domain) and accumulators.  One row.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel(
-    Shape s, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-    const uint16_t* __restrict__ V, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int32_t L, const int64_t* __restrict__ crow,
-    uint16_t* __restrict__ O) {
-  const uint32_t lb = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int64_t row = static_cast<int64_t>(lb) * kWavesPerBlock + (threadIdx.x >> 6);
-  const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
-  if (row >= nrows) return;
+__device__ __forceinline__ void gather_row_bf16(const Shape& s, int64_t head, int64_t row, const KeyList& kl,
+                                                const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+                                                const uint16_t* __restrict__ V, uint16_t* __restrict__ O) {
   const int lane = threadIdx.x & 63;
   const int g = lane >> 3;   // which of the 8 rows of a wave load
   const int c8 = lane & 7;   // which 16-byte chunk of the row
-  const int64_t head = row / s.T;
   const uint16_t* Kh = K + head * s.T * kHeadDim;
   const uint16_t* Vh = V + head * s.T * kHeadDim;
 
@@ -76,7 +90,6 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel
   const uint4 qv = *reinterpret_cast<const uint4*>(Q + row * kHeadDim + c8 * 8);
   const uint32_t qw[4] = {qv.x, qv.y, qv.z, qv.w};
   const float f = s.scale * kLog2e;
-  const KeyList kl = key_list(s, row, idx, cnt, L, crow);
   const int32_t n = kl.n;
   const int32_t* irow = kl.p;
 
@@ -151,6 +164,417 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel
     out.z = pack_bf16(o[4] * inv, o[5] * inv);
     out.w = pack_bf16(o[6] * inv, o[7] * inv);
     *reinterpret_cast<uint4*>(O + row * kHeadDim + c8 * 8) = out;
+  }
+}
+
+__global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel(
+    Shape s, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int32_t L, const int64_t* __restrict__ crow,
+    uint16_t* __restrict__ O) {
+  const uint32_t lb = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int64_t row = static_cast<int64_t>(lb) * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
+  if (row >= nrows) return;
+  gather_row_bf16(s, row / s.T, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
+}
+
+// ------------------------------------------------------------------------------------------
+// bf16, dense lists: 128 rows of one head per block, tiles of 64 keys on the matrix cores.
+//
+// The rows' lists are turned into key bits window by window (1024 keys).  A wave takes its 32 rows one
+// after the other: a row's entries of the window are at most 1024 consecutive list entries from its
+// cursor on; each sets a byte of a 1 KB strip in LDS (no atomics: different bytes), the strip is read
+// back as 16 keys per lane and packed.  The keys any row of the block uses are ORed together on the
+// way; steps without one are skipped, and the rows of unused keys are not read from memory (a buffer
+// load past the end returns zero), so what a list leaves out cannot leak into the result.
+//
+// This is right for lists that ascend without repetition.  Whatever else the caller passes is found out
+// by counting: the bits set over all windows equal the list lengths exactly when every entry was seen,
+// valid and unique.  A block that fails the count computes its rows again with the gather form.
+//
+// Bound: vector issue (key bits: one bit-extract and one select per score) and, in front of it, the list
+// bytes, 4 per (query, key) pair.  See the launcher for when a block takes this form and what it gives.
+// ------------------------------------------------------------------------------------------
+__device__ __forceinline__ int32_t wave_sum(int32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);   // quad xor 1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);   // quad xor 2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);  // row_half_mirror
+  x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false);  // row_mirror
+  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  const uint32_t y = a[0] + a[1];
+  const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return static_cast<int32_t>(b[0] + b[1]);
+}
+
+constexpr int kTileRows = 128, kWindow = 1024;
+constexpr int kChunk = 64, kKRow = 72, kVRow = 64;
+typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));  // lists start at any entry
+constexpr int kBitRow = kWindow / 32 + 1;  // words per row of key bits, padded
+
+// Are the lists of the 128 rows dense enough for tiles?  The break-even is about one listed key in twenty of
+// the keys spanned (70 G listed pairs/s gathered, 1.5 T spanned pairs/s in tiles); one in sixteen leaves
+// the unpacking its share.  The answer is that of all heads of the time steps together, with the span of the
+// last head: for a FlatCSR tensor that takes two row pointers instead of a search per row, and lists and
+// tensor of the same mask get the same answer.  Both kernels below ask; every thread of the block takes
+// part (one barrier), `red` has a place per wave.
+__device__ __forceinline__ bool block_is_dense(const Shape& s, int64_t head, int32_t row0, int tid,
+                                               const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
+                                               int32_t L, const int64_t* __restrict__ crow, int32_t (*red)[2]) {
+  const int32_t t = row0 + tid;
+  const bool mine = tid < kTileRows && t < s.T;
+  const int64_t b = head / s.H;
+  int32_t n = 0, last = 0;
+  if (mine && crow == nullptr) {
+    int64_t all = 0;
+    int32_t nh = 0;
+#pragma unroll 4
+    for (int32_t h = 0; h < s.H; ++h) {
+      nh = min(max(cnt[(b * s.H + h) * s.T + t], 0), L);
+      all += nh;
+    }
+    n = static_cast<int32_t>((all + s.H - 1) / s.H);
+    if (nh > 0) last = idx[((b * s.H + s.H - 1) * s.T + t) * L + nh - 1];
+  } else if (mine) {
+    const int64_t beg = crow[b * s.T + t], end = crow[b * s.T + t + 1];
+    n = end > beg ? static_cast<int32_t>((end - beg + s.H - 1) / s.H) : 0;
+    if (n > 0) last = static_cast<int32_t>(idx[end - 1] - static_cast<int64_t>(s.H - 1) * s.T);
+  }
+  if (n > 0) last = min(max(last, 0), s.T - 1) + 1;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    n += __shfl_xor(n, off, kWave);
+    last = max(last, __shfl_xor(last, off, kWave));
+  }
+  if ((tid & 63) == 0) { red[tid >> 6][0] = n; red[tid >> 6][1] = last; }
+  __syncthreads();
+  const int64_t total = static_cast<int64_t>(red[0][0]) + red[1][0];
+  return total > 0 && total * 16 >= static_cast<int64_t>(kTileRows) * max(red[0][1], red[1][1]);
+}
+// block -> (head, first row): heads in groups that share the L2s, the last (longest, if causal) rows first
+__device__ __forceinline__ void tile_block(const Shape& s, int32_t group_heads, int64_t* head, int32_t* row0) {
+  const uint32_t wgs = (s.T + kTileRows - 1) / kTileRows;
+  const uint32_t per_group = static_cast<uint32_t>(group_heads) * wgs;
+  const uint32_t grp = blockIdx.x / per_group, rem = blockIdx.x - grp * per_group;
+  const uint32_t nh = min(static_cast<uint32_t>(group_heads), static_cast<uint32_t>(s.N) - grp * group_heads);
+  *head = static_cast<int64_t>(grp) * group_heads + rem % nh;
+  *row0 = static_cast<int32_t>(wgs - 1 - rem / nh) * kTileRows;
+}
+
+// the rows of the blocks that do not take tiles, eight per wave
+__global__ __launch_bounds__(1024) void list_rest_kernel(Shape s, const uint16_t* __restrict__ Q,
+                                                         const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+                                                         const int32_t* __restrict__ idx,
+                                                         const int32_t* __restrict__ cnt, int32_t L,
+                                                         const int64_t* __restrict__ crow, uint16_t* __restrict__ O,
+                                                         int32_t group_heads) {
+  __shared__ int32_t red[16][2];
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int64_t head;
+  int32_t row0;
+  tile_block(s, group_heads, &head, &row0);
+  if (block_is_dense(s, head, row0, threadIdx.x, idx, cnt, L, crow, red)) return;
+  for (int32_t t = row0 + wid; t < min(row0 + kTileRows, s.T); t += 16) {
+    const int64_t row = head * s.T + t;
+    gather_row_bf16(s, head, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
+  }
+}
+
+__global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16_t* __restrict__ Q,
+                                                           const uint16_t* __restrict__ K,
+                                                           const uint16_t* __restrict__ V,
+                                                           const int32_t* __restrict__ idx,
+                                                           const int32_t* __restrict__ cnt, int32_t L,
+                                                           const int64_t* __restrict__ crow,
+                                                           uint16_t* __restrict__ O, int32_t group_heads) {
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[kChunk * kKRow];
+  __shared__ __attribute__((aligned(16))) uint16_t Vs[kChunk * kVRow];
+  __shared__ __attribute__((aligned(16))) uint8_t strip[4][kWindow + 16];
+  __shared__ uint32_t bits[kTileRows * kBitRow];
+  __shared__ uint32_t used[2][kWindow / 32];  // keys of the window any row of the block lists
+  __shared__ int32_t red[4][2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ql = lane & 31, g = lane >> 5;
+  int64_t head;
+  int32_t row0;
+  tile_block(s, group_heads, &head, &row0);
+  if (!block_is_dense(s, head, row0, tid, idx, cnt, L, crow, red)) return;
+
+  const int32_t t = row0 + 32 * wid + ql;
+  // lane r < 32 holds the list of row 32 wid + r
+  KeyList kl = {idx, 0, 0};
+  if (lane < 32 && t < s.T) kl = key_list(s, head * s.T + t, idx, cnt, L, crow);
+  kl.n = max(kl.n, 0);
+  int32_t total = kl.n, span = kl.n > 0 ? min(max(kl.p[kl.n - 1] - kl.base, 0), s.T - 1) + 1 : 0;
+  // 256-entry pieces of the row's list that a window of an evenly spread list takes, and a little more
+  const int32_t expect = span > 0 ? min(4, static_cast<int32_t>(static_cast<float>(kl.n) * static_cast<float>(kWindow) / static_cast<float>(span) + 64.f) / 256 + 1) : 1;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    total += __shfl_xor(total, off, kWave);
+    span = max(span, __shfl_xor(span, off, kWave));
+  }
+  __syncthreads();  // red[] has been read
+  if (lane == 0) { red[wid][0] = total; red[wid][1] = span; }
+  const uint16_t* Qr = Q + (head * s.T + min(t, s.T - 1)) * kHeadDim + 8 * g;
+  bf16x8 bq[4];
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) bq[kc] = *reinterpret_cast<const bf16x8*>(Qr + 16 * kc);
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) asm volatile("" : "+v"(bq[kc]));
+
+  const uint32_t row_bytes = kHeadDim * 2, head_bytes = static_cast<uint32_t>(s.T) * row_bytes;
+  const __amdgpu_buffer_rsrc_t Kres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(K + head * static_cast<int64_t>(s.T) * kHeadDim), 0, head_bytes, kBufferFlags);
+  const __amdgpu_buffer_rsrc_t Vres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(V + head * static_cast<int64_t>(s.T) * kHeadDim), 0, head_bytes, kBufferFlags);
+  const int srow = tid >> 3, spart = tid & 7;
+  const int vpart = spart ^ (((srow >> 1) & 1) << 2);
+  uint4 kreg0, kreg1, vreg0, vreg1;
+
+  floatx16 oacc[2];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) { oacc[0][i] = 0.f; oacc[1][i] = 0.f; }
+  float m_ref = 0.f, m_thr = -INFINITY, l_run = 0.f;
+  constexpr float kRefSlack = 8.f;
+  const float c = s.scale * kLog2e;
+  // bf16 pairs {-1, 0} and {0, -1} (in registers: the first would be encoded as the inline operand
+  // -1.0, which the dot product reads as its fp32 pattern)
+  uint32_t neg_lo_bits = 0x0000bf80u, neg_hi_bits = 0xbf800000u;
+  asm volatile("" : "+s"(neg_lo_bits), "+s"(neg_hi_bits));
+  const uint32_t inf_bits = 0xff800000u;
+
+  int32_t cursor = 0;    // lane r: list entries of row 32 wid + r taken so far
+  uint32_t nset = 0;     // bits this lane has packed
+  *reinterpret_cast<uint4*>(&strip[wid][16 * lane]) = make_uint4(0u, 0u, 0u, 0u);
+  if (tid < 2 * (kWindow / 32)) used[tid / (kWindow / 32)][tid % (kWindow / 32)] = 0u;
+  __syncthreads();
+  total = red[0][0] + red[1][0] + red[2][0] + red[3][0];
+  span = max(max(red[0][1], red[1][1]), max(red[2][1], red[3][1]));
+
+  const uint64_t lp = reinterpret_cast<uint64_t>(kl.p);
+  for (int32_t w0 = 0, win = 0; w0 < span; w0 += kWindow, ++win) {
+    uint32_t wave_used = 0u;  // bit i: key w0 + 16 lane + i
+    // Four consecutive entries per lane and load; a load that would reach past the list is moved back to
+    // end with it (entries unpacked twice set the same byte; lists of less than four are read one by
+    // one), so no entry needs a test of its place.  The next row's entries are on their way while a row
+    // is unpacked.
+    const uint32_t nkeys = static_cast<uint32_t>(min(kWindow, s.T - w0));
+    auto row_list = [&](int rr) {
+      return reinterpret_cast<const int32_t*>(
+          static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lp), rr)) |
+          (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lp >> 32), rr))) << 32));
+    };
+    auto load_row = [&](int rr, i32x4 (&e)[4]) {
+      const int32_t n = __builtin_amdgcn_readlane(kl.n, rr), cu = __builtin_amdgcn_readlane(cursor, rr);
+      const int32_t* p = row_list(rr);
+      const int32_t nq = __builtin_amdgcn_readlane(expect, rr);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q >= nq || cu + 256 * q >= n) break;
+        const int32_t at = cu + 256 * q + 4 * lane;
+        if (n >= 4) {
+          e[q] = *reinterpret_cast<const i32x4*>(p + min(at, n - 4));
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) e[q][i] = p[min(at + i, n - 1)];
+        }
+      }
+    };
+    auto take_row = [&](int rr, const i32x4 (&e)[4]) {
+      const int32_t n = __builtin_amdgcn_readlane(kl.n, rr), cu = __builtin_amdgcn_readlane(cursor, rr);
+      const int32_t key0 = __builtin_amdgcn_readlane(kl.base, rr) + w0;
+      uint32_t half = 0u;
+      if (cu < n) {  // wave-uniform
+        // entries of other windows (and invalid ones) go to the strip's spare byte
+        auto unpack = [&](const i32x4& v) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) strip[wid][min(static_cast<uint32_t>(v[i] - key0), nkeys)] = 1;
+        };
+        const int32_t nq = __builtin_amdgcn_readlane(expect, rr);
+        int32_t last = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (q >= nq || cu + 256 * q >= n) break;
+          unpack(e[q]);
+          last = __builtin_amdgcn_readlane(e[q][3], 63);
+        }
+        // more entries than expected: the last one requested still lies in the window
+        for (int32_t done = 256 * nq; done < kWindow && cu + done < n && static_cast<uint32_t>(last - key0) < nkeys; done += 256) {
+          const int32_t* p = row_list(rr);
+          i32x4 more;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) more[i] = p[min(cu + done + 4 * lane + i, n - 1)];
+          unpack(more);
+          last = __builtin_amdgcn_readlane(more[3], 63);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const uint4 v = *reinterpret_cast<const uint4*>(&strip[wid][16 * lane]);
+        *reinterpret_cast<uint4*>(&strip[wid][16 * lane]) = make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+        uint32_t rev = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // bytes 0 / 1 of d to four bits, first byte highest: bits 27..24
+          uint32_t x = d[i] | (d[i] << 9);
+          x |= x << 18;
+          rev |= ((x >> 24) & 0xfu) << (28 - 4 * i);
+        }
+        half = __builtin_bitreverse32(rev);
+        // (the spare byte lies inside the last window when T ends there)
+        half &= 0xffffu >> min(16, max(0, 16 * lane + 16 - static_cast<int>(nkeys)));
+        const int32_t got = __popc(half);
+        nset += got;
+        const int32_t took = wave_sum(got);
+        if (lane == rr) cursor = cu + took;
+      }
+      reinterpret_cast<uint16_t*>(&bits[(32 * wid + rr) * kBitRow])[lane] = static_cast<uint16_t>(half);
+      wave_used |= half;
+    };
+    {
+      i32x4 ea[4], eb[4];
+      load_row(0, ea);
+#pragma unroll 1
+      for (int rr = 0; rr < 32; rr += 2) {
+        load_row(rr + 1, eb);
+        take_row(rr, ea);
+        if (rr + 2 < 32) load_row(rr + 2, ea);
+        take_row(rr + 1, eb);
+      }
+    }
+    // keys used by the block, in 32-key words (lanes 2 i, 2 i + 1 hold the halves of word i)
+    const uint32_t upper = __shfl_xor(wave_used, 1, kWave);
+    if ((lane & 1) == 0) atomicOr(&used[win & 1][lane >> 1], wave_used | (upper << 16));
+    __syncthreads();
+    const uint32_t* uw = used[win & 1];
+    // 64-key steps with a used key (uniform): lanes 0..15 look at one step each
+    uint32_t steps = static_cast<uint32_t>(__ballot(lane < kWindow / 64 && (uw[2 * (lane & 15)] | uw[2 * (lane & 15) + 1]) != 0u));
+    auto fetch = [&](int step) {
+      const uint32_t k0 = static_cast<uint32_t>(w0 + 64 * step + srow);
+      // rows of unused keys: an offset past the resource's end, i.e. zeros
+      const uint32_t oa = (uw[2 * step] >> srow) & 1u ? k0 * row_bytes + spart * 16 : 0xfffffff0u;
+      const uint32_t ob = (uw[2 * step + 1] >> srow) & 1u ? (k0 + 32) * row_bytes + spart * 16 : 0xfffffff0u;
+      kreg0 = buffer_load16(Kres, oa);
+      kreg1 = buffer_load16(Kres, ob);
+      vreg0 = buffer_load16(Vres, oa);
+      vreg1 = buffer_load16(Vres, ob);
+    };
+    if (steps != 0u) fetch(__ffs(steps) - 1);
+    while (steps != 0u) {
+      const int step = __ffs(steps) - 1;
+      steps &= steps - 1u;
+      *reinterpret_cast<uint4*>(&Ks[srow * kKRow + spart * 8]) = kreg0;
+      *reinterpret_cast<uint4*>(&Ks[(srow + 32) * kKRow + spart * 8]) = kreg1;
+      *reinterpret_cast<uint4*>(&Vs[srow * kVRow + vpart * 8]) = vreg0;
+      *reinterpret_cast<uint4*>(&Vs[(srow + 32) * kVRow + vpart * 8]) = vreg1;
+      __syncthreads();
+      if (steps != 0u) fetch(__ffs(steps) - 1);
+#pragma unroll
+      for (int sc = 0; sc < 2; ++sc) {
+        const uint32_t word = bits[(32 * wid + ql) * kBitRow + 2 * step + sc];
+        if (__ballot(word != 0u) == 0ull) continue;  // no row of the wave uses these keys
+        const uint16_t* Kr = &Ks[(32 * sc + ql) * kKRow + 8 * g];
+        floatx16 sv;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sv[i] = 0.f;
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc)
+          sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + 16 * kc), bq[kc], sv, 0, 0, 0);
+        // reg i <-> key slot 8 (i / 4) + 4 g + i % 4
+        const uint32_t wg = word >> (4 * g);
+        float y[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const uint32_t sel = static_cast<uint32_t>(static_cast<int32_t>(wg << (31 - (8 * (i >> 2) + (i & 3)))) >> 31);
+          y[i] = __uint_as_float((sel & __float_as_uint(fmaf(sv[i], c, -m_ref))) | (~sel & inf_bits));
+        }
+        bf16x8 av[2][2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+          const uint16_t* Vr = &Vs[(32 * sc + 4 * g + ((ql & 15) >> 2)) * kVRow + 32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
+#pragma unroll
+          for (int c2 = 0; c2 < 2; ++c2) {
+            const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kVRow);
+            const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kVRow);
+            av[mt][c2] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          }
+        }
+        float ymax = fmaxf(fmaxf(y[0], y[1]), y[2]);
+#pragma unroll
+        for (int i = 3; i < 15; i += 2) ymax = fmaxf(fmaxf(ymax, y[i]), y[i + 1]);
+        ymax = half_max(fmaxf(ymax, y[15]));
+        const bool refresh = ymax > m_thr;
+        if (__ballot(refresh) != 0ull) {
+          const float delta = refresh ? ymax : 0.f;
+          const float corr = (refresh && m_thr > 0.f) ? __builtin_amdgcn_exp2f(-delta) : 1.f;
+          l_run *= corr;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) { oacc[0][i] *= corr; oacc[1][i] *= corr; }
+          m_ref += delta;
+          m_thr = refresh ? kRefSlack : m_thr;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) y[i] -= delta;
+        }
+        // weights as rounded value + rounded remainder (16 significant bits)
+        const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+        const bf16x2 neg_lo = __builtin_bit_cast(bf16x2, neg_lo_bits), neg_hi = __builtin_bit_cast(bf16x2, neg_hi_bits);
+        auto frag = [](const bf16x2* p2) {
+          const bf16x4 lo = __builtin_shufflevector(p2[0], p2[1], 0, 1, 2, 3);
+          const bf16x4 hi = __builtin_shufflevector(p2[2], p2[3], 0, 1, 2, 3);
+          return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) {
+          bf16x2 h[4], l[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float p0 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * i]), p1 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * i + 1]);
+            const floatx2 f2 = {p0, p1};
+            h[i] = __builtin_convertvector(f2, bf16x2);
+            const floatx2 r2 = {__builtin_amdgcn_fdot2_f32_bf16(h[i], neg_lo, p0, false),
+                                __builtin_amdgcn_fdot2_f32_bf16(h[i], neg_hi, p1, false)};
+            l[i] = __builtin_convertvector(r2, bf16x2);
+            l_run = __builtin_amdgcn_fdot2_f32_bf16(h[i], ones, l_run, false);
+            l_run = __builtin_amdgcn_fdot2_f32_bf16(l[i], ones, l_run, false);
+          }
+          const bf16x8 ph = frag(h), pl8 = frag(l);
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], ph, oacc[mt], 0, 0, 0);
+            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], pl8, oacc[mt], 0, 0, 0);
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if (tid < kWindow / 32) used[(win & 1) ^ 1][tid] = 0u;  // for the next window (nobody reads it now)
+    __syncthreads();
+  }
+  // every list entry seen exactly once?
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) nset += __shfl_xor(nset, off, kWave);
+  if (lane == 0) red[wid][0] = static_cast<int32_t>(nset);
+  __syncthreads();
+  if (red[0][0] + red[1][0] + red[2][0] + red[3][0] != total) {
+    for (int32_t r = row0 + wid; r < min(row0 + kTileRows, s.T); r += 4) {
+      const int64_t row = head * s.T + r;
+      gather_row_bf16(s, head, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
+    }
+    return;
+  }
+  l_run = half_sum(l_run);
+  if (t < s.T) {
+    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+    uint16_t* Or = O + (head * s.T + t) * kHeadDim;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
+        const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
+        const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
+        *reinterpret_cast<bf16x4*>(Or + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
+      }
   }
 }
 
@@ -246,6 +670,12 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_f32_kernel(
   }
 }
 
+// Tiles from one 128-row block per CU on.  Below that a block's walk (two windows of a 2048-key sequence are
+// about 0.1 ms) is longer than the gather of all rows with one wave each: 12 heads of 1024 rows 0.09 against
+// 0.11 ms; 48 heads of 1024 rows the tiles win by a third, 48 heads of 2048 rows (75 M listed pairs, three
+// quarters of the causal triangle) 1.05 -> 0.20 ms.
+constexpr int64_t kMinTileBlocks = 256;
+
 }  // namespace
 
 hipError_t launch_sparse_attn(const Shape& s, sea_dtype dt, const void* Q, const void* K,
@@ -254,7 +684,16 @@ hipError_t launch_sparse_attn(const Shape& s, sea_dtype dt, const void* Q, const
   const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
   const uint32_t grid = static_cast<uint32_t>((nrows + kWavesPerBlock - 1) / kWavesPerBlock);
   StageScope scope(SEA_STAGE_SPARSE, st);
-  if (dt == SEA_BF16) {
+  const int64_t tiles = static_cast<int64_t>(s.N) * ((s.T + kTileRows - 1) / kTileRows);
+  if (dt == SEA_BF16 && tiles >= kMinTileBlocks && s.T <= (1 << 24)) {
+    const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K),
+                   *v = static_cast<const uint16_t*>(V);
+    uint16_t* o = static_cast<uint16_t*>(O);
+    const int32_t gh = group_heads_for(s.N, s.T);
+    const dim3 tgrid(static_cast<uint32_t>(tiles));
+    hipLaunchKernelGGL(list_tile_kernel, tgrid, dim3(256), 0, st, s, q, k, v, idx, cnt, L, crow, o, gh);
+    hipLaunchKernelGGL(list_rest_kernel, tgrid, dim3(1024), 0, st, s, q, k, v, idx, cnt, L, crow, o, gh);
+  } else if (dt == SEA_BF16) {
     hipLaunchKernelGGL(sparse_attn_bf16_kernel, dim3(grid), dim3(kWavesPerBlock * kWave), 0, st, s,
                        static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
                        static_cast<const uint16_t*>(V), idx, cnt, L, crow, static_cast<uint16_t*>(O));

@@ -1,0 +1,84 @@
+"""Attention from per-row key lists and from the FlatCSR tensor where the lists are dense enough for tiles
+(bf16, at least 256 blocks of 128 rows): windows of 1024 keys, lists of every length and form, against
+the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2310_01777_amd import synth
+from tests.util import TOL, assert_close, oracle_params, to_np64
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(B, H, T, L, density, seed):
+    """Ascending lists: row (.., t) draws from the keys 0 .. t; every eighth row is empty, short or full."""
+    rng = np.random.default_rng(seed)
+    idx = np.full((B, H, T, L), -1, dtype=np.int32)
+    cnt = np.zeros((B, H, T), dtype=np.int32)
+    for b in range(B):
+        for h in range(H):
+            for t in range(T):
+                p = (density, density, density, 0.0, 1.0, density, density / 50, density)[t % 8]
+                keys = np.flatnonzero(rng.random(t + 1) < p)[:L]
+                idx[b, h, t, :len(keys)] = keys
+                cnt[b, h, t] = len(keys)
+    return idx, cnt
+
+
+@pytest.mark.parametrize("T,N,L,density", [(1100, 30, 1100, 0.4), (2080, 16, 2080, 0.9), (513, 52, 200, 0.2),
+                                           (1024, 32, 40, 0.03)])
+def test_dense_lists(T, N, L, density):
+    from paper_2310_01777_amd import binding as sea
+    B, H = 2, N // 2
+    wl = synth.Workload("lists", B, H, T, 64, 32, 16, 4, 0, True, "bf16", 4)
+    x = synth.make_inputs(wl)
+    idx, cnt = _lists(B, H, T, L, density, T)
+    # the last keys are nobody's (and hold what an unused row may hold); odd lists in a few tiles:
+    # entries out of order, repeated, outside [0, T)
+    idx[idx >= T - 3] = -1
+    cnt[:] = (idx >= 0).sum(-1)
+    for k in "KV":
+        x[k][:, :, T - 3:] = float("nan")
+    order = np.argsort(np.where(idx < 0, 1 << 30, idx), axis=-1, kind="stable")
+    idx = np.take_along_axis(idx, order, -1)
+    clean_idx, clean_cnt = idx.copy(), cnt.copy()
+    r = T // 2
+    n = int(cnt[0, 0, r])
+    if n > 2:
+        idx[0, 0, r, :n] = idx[0, 0, r, :n][::-1]                 # descending
+        idx[0, 1, r + 1, 1] = T + 5                               # invalid in the middle
+        keep = [v for v in idx[0, 1, r + 1, :cnt[0, 1, r + 1]] if v < T]
+        clean_idx[0, 1, r + 1] = -1
+        clean_idx[0, 1, r + 1, :len(keep)] = keep
+        clean_cnt[0, 1, r + 1] = len(keep)
+        idx[1, 0, r, 1] = idx[1, 0, r, 0]                         # listed twice: counts twice
+        clean_idx[1, 0, r] = idx[1, 0, r]
+    d = {k: x[k].cuda() for k in "QKV"}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=32, K=16, k_hat=4, causal=True, scale=wl.scale, dtype="bf16")
+    O = torch.full((B, H, T, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print(f"[case] lists T{T} N{N} L{L} density {density}", flush=True)
+    sea.sea_sparse_attn(p, d["Q"], d["K"], d["V"], torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda(), L, O)
+    torch.cuda.synchronize()
+    po = oracle_params(wl)
+    c = {k: to_np64(torch.nan_to_num(x[k])) for k in "QKV"}
+    want = oracle.sparse_attn(po, c["Q"], c["K"], c["V"], clean_idx, clean_cnt)
+    assert_close(to_np64(O), want, TOL["bf16"], "O from lists")
+
+    # the FlatCSR tensor of ordinary lists: bit-identical to the lists
+    idx, cnt = np.take_along_axis(clean_idx, np.argsort(np.where(clean_idx < 0, 1 << 30, clean_idx), -1), -1), clean_cnt
+    idx[1, 0, r], cnt[1, 0, r] = -1, 0
+    idx_d, cnt_d = torch.from_numpy(np.ascontiguousarray(idx)).cuda(), torch.from_numpy(cnt).cuda()
+    crow = torch.empty(B * T + 1, dtype=torch.int64, device="cuda")
+    col = torch.empty(int(cnt.sum()), dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(256, sea.sea_flatcsr_workspace_bytes(p)), dtype=torch.uint8, device="cuda")
+    O1, O2 = torch.empty_like(O), torch.empty_like(O)
+    sea.sea_flatcsr(p, idx_d, cnt_d, L, crow, col, ws)
+    sea.sea_flatcsr_attn(p, d["Q"], d["K"], d["V"], crow, col, O1)
+    sea.sea_sparse_attn(p, d["Q"], d["K"], d["V"], idx_d, cnt_d, L, O2)
+    torch.cuda.synchronize()
+    crow_o, col_o = oracle.flatcsr(po, idx, cnt)
+    assert np.array_equal(crow.cpu().numpy(), crow_o) and np.array_equal(col.cpu().numpy(), col_o)
+    assert torch.equal(O1, O2)
+    assert_close(to_np64(O1), oracle.sparse_attn(po, c["Q"], c["K"], c["V"], idx, cnt), TOL["bf16"], "O from the tensor")
