@@ -146,8 +146,16 @@ def _nbytes(t: Optional[torch.Tensor]) -> int:
     return 0 if t is None else t.numel() * t.element_size()
 
 
+# torch's current stream as a plain handle: building the Stream object it wraps costs more than all the
+# argument checks of a call together
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -161,20 +169,26 @@ def sea_k_hat(k: int, K: int, T: int) -> int:
     return int(_lib.sea_k_hat(k, K, T))
 
 
-def sea_row_stride(p: SeaParams) -> int:
-    cp = p.c()
-    L = int(_lib.sea_row_stride(ctypes.byref(cp)))
+def _row_stride(ref) -> int:
+    L = _lib.sea_row_stride(ref)
     if L < 0:
         raise SeaError(L, "sea_row_stride")
     return L
 
 
-def sea_sel_stride(p: SeaParams) -> int:
-    cp = p.c()
-    S = int(_lib.sea_sel_stride(ctypes.byref(cp)))
+def _sel_stride(ref) -> int:
+    S = _lib.sea_sel_stride(ref)
     if S < 0:
         raise SeaError(S, "sea_sel_stride")
     return S
+
+
+def sea_row_stride(p: SeaParams) -> int:
+    return _row_stride(ctypes.byref(p.c()))
+
+
+def sea_sel_stride(p: SeaParams) -> int:
+    return _sel_stride(ctypes.byref(p.c()))
 
 
 def sea_workspace_bytes(p: SeaParams) -> int:
@@ -196,10 +210,10 @@ def sea_estimate(p: SeaParams, Q, K, W, A_hat, workspace, stream=None):
 
 def sea_topk_mask(p: SeaParams, A_hat, sel, idx, cnt, stream=None):
     n = p.B * p.H * p.T
-    L = sea_row_stride(p)
-    cp = p.c()
-    _check(_lib.sea_topk_mask(ctypes.byref(cp), _ptr(A_hat, torch.float32, n * p.K, "A_hat"),
-                              _ptr(sel, torch.int32, n * sea_sel_stride(p), "sel"),
+    ref = ctypes.byref(p.c())
+    L = _row_stride(ref)
+    _check(_lib.sea_topk_mask(ref, _ptr(A_hat, torch.float32, n * p.K, "A_hat"),
+                              None if sel is None else _ptr(sel, torch.int32, n * _sel_stride(ref), "sel"),
                               _ptr(idx, torch.int32, n * L, "idx"),
                               _ptr(cnt, torch.int32, n, "cnt"), _stream(stream)),
            "sea_topk_mask")
@@ -277,15 +291,15 @@ def sea_mask_attn(p: SeaParams, Q, K, V, mhat, O, workspace=None, stream=None):
 def sea_forward(p: SeaParams, Q, K, V, W, O, A_hat=None, sel=None, idx=None, cnt=None,
                 workspace=None, stream=None, mhat=None):
     n = p.B * p.H * p.T
-    L = sea_row_stride(p)
-    cp = p.c()
-    _check(_lib.sea_forward(ctypes.byref(cp), _ptr(Q, p.torch_dtype, n * p.d, "Q"),
+    ref = ctypes.byref(p.c())
+    L = _row_stride(ref)
+    _check(_lib.sea_forward(ref, _ptr(Q, p.torch_dtype, n * p.d, "Q"),
                             _ptr(K, p.torch_dtype, n * p.d, "K"),
                             _ptr(V, p.torch_dtype, n * p.d, "V"),
                             _ptr(W, p.torch_dtype, p.m * p.d, "W"),
                             _ptr(O, p.torch_dtype, n * p.d, "O"),
                             _ptr(A_hat, torch.float32, n * p.K, "A_hat"),
-                            _ptr(sel, torch.int32, n * sea_sel_stride(p), "sel"),
+                            None if sel is None else _ptr(sel, torch.int32, n * _sel_stride(ref), "sel"),
                             _ptr(idx, torch.int32, n * L, "idx"),
                             _ptr(cnt, torch.int32, n, "cnt"),
                             _ptr(mhat, torch.int32, n * ((p.K + 31) // 32), "mhat"),
