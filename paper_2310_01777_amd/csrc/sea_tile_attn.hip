@@ -664,9 +664,17 @@ bool tile_attn_supported(const Shape& s, sea_dtype dt, int32_t* rlog_out) {
 
 namespace {
 // Few columns per row under per-query grouping: rows (k^ = 1) or (row, column) entries (k^ <= 8,
-// and no more than an eighth of the columns) are bucketed by column
+// and no more than an eighth of the columns) are bucketed by column -- from the list length on where that
+// pays.  A (row, column) entry costs the bucket form (counting, scattering, partial results, merge) as much
+// as 450 list keys cost the tile walk, whose rows walk half the list when causal: B = 8, H = 12, T = 512,
+// K = 64, k^ = 8 with 8 keys each 83 us in buckets, 34 us in tiles; B = 1, H = 12, T = 4096, K = 128,
+// k^ = 4 with 32 keys each, causal, 64 and 74 us.  One column per row needs no merge: from 512 keys on.
 bool bucket_mode(const Shape& s) {
-  return s.grouping == 0 && (s.k_hat == 1 || (s.k_hat <= kMaxSlots && 8 * s.k_hat <= s.K));
+  const int32_t w = s.T / s.K, r = w < s.rep_cap ? w : s.rep_cap;
+  const int64_t U = static_cast<int64_t>(s.K) * r;
+  if (s.grouping != 0) return false;
+  if (s.k_hat == 1) return U >= 512;
+  return s.k_hat <= kMaxSlots && 8 * s.k_hat <= s.K && (s.causal ? U / 2 : U) >= 450 * s.k_hat;
 }
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 struct BucketWs {
