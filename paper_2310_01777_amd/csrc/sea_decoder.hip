@@ -17,41 +17,23 @@
 //                         the state update; one wavefront per (head, 16 value columns); the values
 //                         are [V_I; V; 1], so column 128 is the row normaliser
 //   dec_concat_kernel     [C_perf; V] in bf16
-//   dec_conv_kernel       implicit GEMM for the linear layers (one tap) and the 3x3 convolutions
-//                         (nine taps, channels-last images, optional nearest resize on the read)
+//   dec_mlp_kernel        mu, nu, s_mix, s_prob (sea_decoder_mlp.hip)
+//   dec_conv_tile_kernel, dec_conv_softmax_kernel
+//                         the convolutions of images with up to 64 channels and the final softmax
+//                         (sea_decoder_conv.hip); wider layers:
+//   dec_conv3_kernel, dec_conv_lds_kernel, dec_conv_kernel
+//                         implicit GEMM on channels-last images, optional nearest resize on the read
 //   dec_softmax_kernel    softmax over the K columns of a row, rows past the sequence end zeroed
-//   dec_scalers_kernel    s_mix, s_prob = sigmoid(w . Z + b)
-#include <algorithm>
-
-#include "sea_internal.h"
+#include "sea_decoder.h"
 
 namespace sea {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kCs = 2;       // width reduction of the CNN's hidden image (c_s)
 constexpr int kCh = 4;       // channel expansion (c_h)
 constexpr int kTRow = 72;      // halfwords per LDS row of the transposed 64-token tile (16-byte aligned rows)
 constexpr int kValCols = 144;  // [V_I (64); V (64); 1; 15 unused]: nine 16-column slices
 
-__device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ bf16x8 load8(const uint16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
-__device__ __forceinline__ bf16x8 zero8() {
-  const uint4 z = {0u, 0u, 0u, 0u};
-  return __builtin_bit_cast(bf16x8, z);
-}
-__device__ __forceinline__ bf16x8 pack8(floatx4 lo, floatx4 hi) {
-  uint4 u;
-  u.x = pack_bf16(lo[0], lo[1]);
-  u.y = pack_bf16(lo[2], lo[3]);
-  u.z = pack_bf16(hi[0], hi[1]);
-  u.w = pack_bf16(hi[2], hi[3]);
-  return __builtin_bit_cast(bf16x8, u);
-}
 __device__ __forceinline__ float sumsq8(bf16x8 v) {
   const uint4 u = __builtin_bit_cast(uint4, v);
   const uint32_t w[4] = {u.x, u.y, u.z, u.w};
@@ -433,9 +415,7 @@ struct ConvArgs {
   const float* bias;     // [Cout]
   void* out;
   int32_t B, Tin, Xin, Cin, Tv, Xv, Tout, Xout, Cout, taps, stride_t, pad_top, relu;
-  int32_t mode;          // 0: bf16 channels-last; 1: nu's last layer into the CNN's input image; 2: fp32 planes
-  int32_t H, T, Wd, C;   // mode 1: rows are (b h, t); the image is [B][T][Wd][C]
-  const int32_t* seq_len;
+  int32_t mode;          // 0: bf16 channels-last; 2: fp32 planes
 };
 
 constexpr int kSlabK = 128;            // contraction elements of the weights staged per step
@@ -553,16 +533,6 @@ __global__ __launch_bounds__(256, 2) void dec_conv_lds_kernel(ConvArgs a) {
       if (a.mode == 0) {
         uint2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
         *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + p * a.Cout + co) = pk;
-      } else if (a.mode == 1) {
-        // row p = (b h, t); outputs co .. co + 3 = compressed column co / 4, extra channels 0..3
-        const int64_t n = p / a.T;
-        const int32_t t = static_cast<int32_t>(p - n * a.T);
-        const int32_t b = static_cast<int32_t>(n / a.H), h = static_cast<int32_t>(n - static_cast<int64_t>(b) * a.H);
-        const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
-        uint2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-        if (t >= len) pk = make_uint2(0u, 0u);
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) +
-                                  ((static_cast<int64_t>(b) * a.T + t) * a.Wd + (co >> 2)) * a.C + h * kCh) = pk;
       } else {
         float* o = static_cast<float*>(a.out);
 #pragma unroll
@@ -651,16 +621,6 @@ __global__ __launch_bounds__(256) void dec_conv_kernel(ConvArgs a) {
       if (a.mode == 0) {
         uint2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
         *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + p * a.Cout + co) = pk;
-      } else if (a.mode == 1) {
-        // row p = (b h, t); outputs co .. co + 3 = compressed column co / 4, extra channels 0..3
-        const int64_t n = p / a.T;
-        const int32_t t = static_cast<int32_t>(p - n * a.T);
-        const int32_t b = static_cast<int32_t>(n / a.H), h = static_cast<int32_t>(n - static_cast<int64_t>(b) * a.H);
-        const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
-        uint2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-        if (t >= len) pk = make_uint2(0u, 0u);
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) +
-                                  ((static_cast<int64_t>(b) * a.T + t) * a.Wd + (co >> 2)) * a.C + h * kCh) = pk;
       } else {
         float* o = static_cast<float*>(a.out);
 #pragma unroll
@@ -698,38 +658,10 @@ __global__ __launch_bounds__(256) void dec_softmax_kernel(float* __restrict__ A,
   for (int32_t c = lane; c < K; c += 64) r[c] = __expf(r[c] - mx) * inv;
 }
 
-// s_mix, s_prob = sigmoid(w . Z[row] + b); Z rows of 128 bf16; rows at or past seq_len -> 0
-__global__ __launch_bounds__(256) void dec_scalers_kernel(const uint16_t* __restrict__ Z, const uint16_t* __restrict__ mix_w,
-                                                          const float* __restrict__ mix_b, const uint16_t* __restrict__ prob_w,
-                                                          const float* __restrict__ prob_b, float* __restrict__ s_mix,
-                                                          float* __restrict__ s_prob, const int32_t* __restrict__ seq_len,
-                                                          int64_t rows, int32_t H, int32_t T) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const uint32_t z = *reinterpret_cast<const uint32_t*>(Z + row * 128 + 2 * lane);
-  const uint32_t wm = *reinterpret_cast<const uint32_t*>(mix_w + 2 * lane), wp = *reinterpret_cast<const uint32_t*>(prob_w + 2 * lane);
-  float am = bf16lo_to_f32(z) * bf16lo_to_f32(wm) + bf16hi_to_f32(z) * bf16hi_to_f32(wm);
-  float ap = bf16lo_to_f32(z) * bf16lo_to_f32(wp) + bf16hi_to_f32(z) * bf16hi_to_f32(wp);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    am += __shfl_xor(am, off, 64);
-    ap += __shfl_xor(ap, off, 64);
-  }
-  if (lane == 0) {
-    const int32_t t = static_cast<int32_t>(row % T);
-    const int32_t b = static_cast<int32_t>(row / (static_cast<int64_t>(T) * H));
-    const int32_t len = seq_len ? min(max(seq_len[b], 0), T) : T;
-    const bool on = t < len;
-    if (s_mix) s_mix[row] = on ? 1.f / (1.f + __expf(-(am + mix_b[0]))) : 0.f;
-    if (s_prob) s_prob[row] = on ? 1.f / (1.f + __expf(-(ap + prob_b[0]))) : 0.f;
-  }
-}
-
 size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct DecWs {
-  size_t phiQ, phiK, phiKT, Vt, acc, seg, X, Z, hid, img, y1, y2, total;
+  size_t phiQ, phiK, phiKT, Vt, acc, seg, X, img, y1, y2, total;
   int32_t Tp, T1, Wd, C;
   int32_t G, cps;  // linear attention: segments per sequence, chunks of 32 tokens per segment
 };
@@ -757,8 +689,6 @@ DecWs dec_layout(const Shape& s) {
     if (G > 1) off += up256(N * 9 * G * static_cast<size_t>(s.m) * 16 * 4);
   }
   w.X = off; off += up256(N * T * 192 * 2);
-  w.Z = off; off += up256(N * T * 128 * 2);
-  w.hid = off; off += up256(N * T * 128 * 2);
   w.img = off; off += up256(B * T * w.Wd * w.C * 2);
   w.y1 = off; off += up256(B * static_cast<size_t>(w.T1) * w.Wd * w.C * 2);
   w.y2 = off; off += up256(B * static_cast<size_t>(w.T1) * w.Wd * w.C * 2);
@@ -906,129 +836,6 @@ __global__ __launch_bounds__(64 * kConv3Waves) void dec_conv3_kernel(Conv3Args g
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// Linear layers (one tap) on rows of at most 256 inputs: the block parks the weights of its slab of
-// up to 128 output channels in LDS (operand-fragment order) and walks tiles of 32 rows; a wave
-// requests the operand fragments of its next tile (every step of the contraction) before it
-// multiplies the current one, so the row reads, which bound these layers, overlap the products.
-// ------------------------------------------------------------------------------------------
-constexpr int kLinSteps = 8;  // contraction steps of 32 a row may have (Cin <= 256)
-
-__global__ __launch_bounds__(256) void dec_linear_kernel(ConvArgs a, int32_t tiles_per_wave) {
-  extern __shared__ __attribute__((aligned(16))) uint4 wlin[];  // [kstep][8][64]
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int64_t nrows = static_cast<int64_t>(a.B) * a.Tout * a.Xout;
-  const int32_t cout0 = blockIdx.y * 128;
-  const int32_t ntiles_c = min(8, (a.Cout - cout0 + 15) / 16);
-  const int32_t ksteps = (a.Cin + 31) / 32;
-  for (int32_t id = tid; id < ksteps * 8 * 64; id += 256) {
-    const int32_t fl = id & 63, nt = (id >> 6) & 7, ks = id >> 9;
-    const int32_t co = cout0 + 16 * nt + (fl & 15), k0 = 32 * ks + 8 * (fl >> 4);
-    // unconditional load from a clamped address, cleared where the slab overruns the matrix
-    const uint4 v = *reinterpret_cast<const uint4*>(a.w + static_cast<int64_t>(min(co, a.Cout - 1)) * a.Cin + min(k0, a.Cin - 8));
-    wlin[id] = (co < a.Cout && k0 < a.Cin) ? v : make_uint4(0u, 0u, 0u, 0u);
-  }
-  __syncthreads();
-  const int64_t ntile = (nrows + 31) / 32;
-  const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + wid;
-  int64_t tile = wave * tiles_per_wave;
-  const int64_t tile_end = min(ntile, tile + tiles_per_wave);
-  bf16x8 nx[kLinSteps][2];
-  auto request = [&](int64_t tl) {
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      int64_t r = min(tl * 32 + 16 * mt + lr, nrows - 1);
-      if (a.mode == 1) {
-        // walk the rows (b h, t) as (b, t, h), heads fastest: the lanes of a wave then write next to
-        // each other in the channels-last image
-        const int64_t q = r / a.H, h = r - q * a.H, b = q / a.T, t = q - b * a.T;
-        r = (b * a.H + h) * a.T + t;
-      }
-      // a lane whose piece lies past the row's channels reads the row's last piece instead and
-      // clears it, so no load sits behind a per-lane branch and all of a tile's loads are in flight
-      // together
-      const uint16_t* row = a.in + r * a.Cin;
-#pragma unroll
-      for (int ks = 0; ks < kLinSteps; ++ks)
-        if (ks < ksteps) {
-          const int32_t k0 = 32 * ks + 8 * lg;
-          const bf16x8 x = load8(row + min(k0, a.Cin - 8));
-          nx[ks][mt] = k0 < a.Cin ? x : zero8();
-        }
-    }
-  };
-  if (tile < tile_end) request(tile);
-  for (; tile < tile_end; ++tile) {
-    bf16x8 xf[kLinSteps][2];
-#pragma unroll
-    for (int ks = 0; ks < kLinSteps; ++ks) { xf[ks][0] = nx[ks][0]; xf[ks][1] = nx[ks][1]; }
-    if (tile + 1 < tile_end) request(tile + 1);
-    floatx4 acc[8][2];
-#pragma unroll
-    for (int nt = 0; nt < 8; ++nt) acc[nt][0] = acc[nt][1] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < kLinSteps; ++ks) {
-      if (ks < ksteps) {
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt) {
-          if (nt < ntiles_c) {
-            const bf16x8 wf = __builtin_bit_cast(bf16x8, wlin[(ks * 8 + nt) * 64 + lane]);
-            acc[nt][0] = mfma16(wf, xf[ks][0], acc[nt][0]);
-            acc[nt][1] = mfma16(wf, xf[ks][1], acc[nt][1]);
-          }
-        }
-      }
-    }
-    // mode 1: where the lane's two rows (b, t, h) land in the channels-last image, and whether they
-    // lie inside their sequence -- once per tile, not once per channel tile (two 64-bit divisions
-    // and a load each)
-    int64_t orow[2] = {0, 0};
-    bool live[2] = {true, true};
-    if (a.mode != 0) {
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        const int64_t pp = min(tile * 32 + 16 * mt + lr, nrows - 1);
-        const int64_t q = pp / a.H;
-        const int32_t h = static_cast<int32_t>(pp - q * a.H);
-        const int32_t b = static_cast<int32_t>(q / a.T), t = static_cast<int32_t>(q - static_cast<int64_t>(b) * a.T);
-        const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
-        live[mt] = t < len;
-        orow[mt] = (static_cast<int64_t>(b) * a.T + t) * a.Wd * a.C + h * kCh;
-      }
-    }
-    // epilogue: tile (nt, mt): rows = output channels cout0 + 16 nt + 4 lg + i, column = row lr of tile mt
-#pragma unroll
-    for (int nt = 0; nt < 8; ++nt) {
-      if (nt >= ntiles_c) continue;
-      const int32_t co = cout0 + 16 * nt + 4 * lg;
-      if (co >= a.Cout) continue;
-      float bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) bv[i] = co + i < a.Cout ? a.bias[co + i] : 0.f;
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        const int64_t pp = tile * 32 + 16 * mt + lr;
-        if (pp >= nrows) continue;
-        float v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          v[i] = acc[nt][mt][i] + bv[i];
-          if (a.relu) v[i] = fmaxf(v[i], 0.f);
-        }
-        uint2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-        if (a.mode == 0) {
-          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + pp * a.Cout + co) = pk;
-        } else {
-          // row pp = (b, t, h); outputs co .. co + 3 = compressed column co / 4, extra channels 0..3
-          if (!live[mt]) pk = make_uint2(0u, 0u);
-          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + orow[mt] + static_cast<int64_t>(co >> 2) * a.C) = pk;
-        }
-      }
-    }
-  }
-}
-
 // log2 of virtual / stored size when that ratio is a power of two, else -1
 int32_t resize_shift(int32_t vsize, int32_t size) {
   for (int32_t sh = 0; sh < 16; ++sh)
@@ -1041,7 +848,7 @@ int32_t resize_shift(int32_t vsize, int32_t size) {
 // whose halo and weights fit the LDS budget.
 constexpr size_t kConv3LdsBudget = 72 << 10;  // two blocks per CU overlap one block's staging with the other's products
 bool conv3_plan(const ConvArgs& a, Conv3Args* g, int32_t* nt_out, size_t* lds_out) {
-  if (a.taps != 9 || a.Cin % 8 != 0 || (a.mode != 0 && a.mode != 2)) return false;
+  if (a.taps != 9 || a.Cin % 8 != 0 ) return false;
   if (a.mode == 0 && a.Cout % 4 != 0) return false;
   const int32_t ts = resize_shift(a.Tv, a.Tin), xs = resize_shift(a.Xv, a.Xin);
   if (ts < 0 || xs < 0) return false;
@@ -1084,16 +891,6 @@ void launch_conv3(const Conv3Args& g, uint32_t slabs, size_t lds, hipStream_t st
 
 void launch_conv(const ConvArgs& a, hipStream_t st) {
   const int64_t npix = static_cast<int64_t>(a.B) * a.Tout * a.Xout;
-  if (a.taps == 1 && a.Cin % 8 == 0 && a.Cin <= 32 * kLinSteps && a.Cout % 4 == 0 && (a.mode == 0 || a.mode == 1)) {
-    // tiles per wave: whole numbers, about eight waves per CU
-    const int64_t ntile = (npix + 31) / 32;
-    const int32_t per_wave = static_cast<int32_t>((ntile + 2047) / 2048);
-    const int64_t waves = (ntile + per_wave - 1) / per_wave;
-    const size_t lds = static_cast<size_t>((a.Cin + 31) / 32) * 8 * 1024;
-    hipLaunchKernelGGL(dec_linear_kernel, dim3(static_cast<uint32_t>((waves + 3) / 4), static_cast<uint32_t>((a.Cout + 127) / 128)),
-                       dim3(256), lds, st, a, per_wave);
-    return;
-  }
   Conv3Args g{};
   int32_t nt = 0;
   size_t lds = 0;
@@ -1119,6 +916,20 @@ void launch_conv(const ConvArgs& a, hipStream_t st) {
   }
 }
 
+}  // namespace
+
+namespace {
+// conv 1 or 2: the kernel with all weights in LDS where the layer fits it, else the channel-chunked one
+hipError_t conv_layer(const DecConv& c, uint16_t* out, hipStream_t st) {
+  const hipError_t e = launch_dec_conv(c, out, st);
+  if (e != hipErrorNotSupported) return e;
+  ConvArgs a{};
+  a.in = c.in; a.w = c.w; a.bias = c.bias; a.out = out; a.B = c.B; a.Cin = c.Cin; a.Cout = c.Cout;
+  a.Tin = a.Tv = c.Tin; a.Tout = c.Tout; a.Xin = a.Xv = a.Xout = c.X;
+  a.taps = 9; a.stride_t = c.stride_t; a.pad_top = c.pad_top; a.relu = 1; a.mode = 0;
+  launch_conv(a, st);
+  return hipGetLastError();
+}
 }  // namespace
 
 bool decoder_supported(const Shape& s, sea_dtype dt) {
@@ -1172,38 +983,28 @@ hipError_t launch_decoder_estimate(const Shape& s, const sea_decoder_weights& wt
                        u16(lay.X), rows);
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
-  ConvArgs a{};
-  a.seq_len = s.seq_len; a.H = s.H; a.T = s.T; a.Wd = lay.Wd; a.C = lay.C;
-  // mu: [rows][192] -> Z [rows][128], ReLU
-  a.in = u16(lay.X); a.w = static_cast<const uint16_t*>(wt.mu_w); a.bias = wt.mu_b; a.out = u16(lay.Z);
-  // a linear layer is the one-tap case on an "image" of N x T rows
-  a.B = 1; a.Tin = a.Tv = a.Tout = s.N; a.Xin = a.Xv = a.Xout = s.T;
-  a.Cin = 192; a.Cout = 128; a.taps = 1; a.stride_t = 1; a.pad_top = 0; a.relu = 1; a.mode = 0;
-  launch_conv(a, st);
-  hipLaunchKernelGGL(dec_scalers_kernel, dim3(static_cast<uint32_t>((rows + 3) / 4)), dim3(256), 0, st, u16(lay.Z),
-                     static_cast<const uint16_t*>(wt.mix_w), wt.mix_b, static_cast<const uint16_t*>(wt.prob_w), wt.prob_b,
-                     s_mix, s_prob, s.seq_len, rows, s.H, s.T);
-  // nu, first layer: Z -> hidden, ReLU
-  a.in = u16(lay.Z); a.w = static_cast<const uint16_t*>(wt.nu1_w); a.bias = wt.nu1_b; a.out = u16(lay.hid);
-  a.Cin = 128; a.Cout = 128;
-  launch_conv(a, st);
-  // nu, second layer: hidden -> the CNN's input image [B][T][Wd][C], channels h c_h + ch
-  a.in = u16(lay.hid); a.w = static_cast<const uint16_t*>(wt.nu2_w); a.bias = wt.nu2_b; a.out = u16(lay.img);
-  a.Cin = 128; a.Cout = lay.Wd * kCh; a.relu = 0; a.mode = 1;
-  launch_conv(a, st);
+  // mu, nu and the scalers: rows [C_perf; V] -> the CNN's input image [B][T][Wd][C], channels h c_h + ch
+  hipError_t e = launch_dec_mlp(s, wt, u16(lay.X), 192, u16(lay.X) + 128, 192, u16(lay.img), s_mix, s_prob, st);
+  if (e != hipSuccess) return e;
   // conv 1: [B][T][Wd][C] -> [B][T1][Wd][C], ReLU.  Causal: rows t-2..t; else stride c_s, rows i c_s - 1 .. + 1
-  a.in = u16(lay.img); a.w = static_cast<const uint16_t*>(wt.conv1_w); a.bias = wt.conv1_b; a.out = u16(lay.y1);
-  a.B = B; a.Tin = a.Tv = s.T; a.Xin = a.Xv = lay.Wd; a.Cin = lay.C;
-  a.Tout = lay.T1; a.Xout = lay.Wd; a.Cout = lay.C; a.taps = 9;
-  a.stride_t = s.causal ? 1 : kCs; a.pad_top = s.causal ? 2 : 1; a.relu = 1; a.mode = 0;
-  launch_conv(a, st);
+  DecConv c{};
+  c.in = u16(lay.img); c.w = static_cast<const uint16_t*>(wt.conv1_w); c.bias = wt.conv1_b;
+  c.B = B; c.Tin = s.T; c.X = lay.Wd; c.Cin = c.Cout = lay.C; c.Tout = lay.T1;
+  c.stride_t = s.causal ? 1 : kCs; c.pad_top = s.causal ? 2 : 1;
+  if ((e = conv_layer(c, u16(lay.y1), st)) != hipSuccess) return e;
   // conv 2
-  a.in = u16(lay.y1); a.w = static_cast<const uint16_t*>(wt.conv2_w); a.bias = wt.conv2_b; a.out = u16(lay.y2);
-  a.Tin = a.Tv = lay.T1; a.stride_t = 1;
-  launch_conv(a, st);
-  // conv 3 on the image resized to T x K (nearest, on the read) -> logits [B][H][T][K] fp32
-  a.in = u16(lay.y2); a.w = static_cast<const uint16_t*>(wt.conv3_w); a.bias = wt.conv3_b; a.out = A_hat;
-  a.Tv = s.T; a.Xv = s.K; a.Tout = s.T; a.Xout = s.K; a.Cout = s.H; a.relu = 0; a.mode = 2;
+  c.in = u16(lay.y1); c.w = static_cast<const uint16_t*>(wt.conv2_w); c.bias = wt.conv2_b;
+  c.Tin = lay.T1; c.stride_t = 1;
+  if ((e = conv_layer(c, u16(lay.y2), st)) != hipSuccess) return e;
+  // conv 3 on the image resized to T x K (nearest, on the read) and the softmax of its rows
+  c.in = u16(lay.y2); c.w = static_cast<const uint16_t*>(wt.conv3_w); c.bias = wt.conv3_b;
+  c.Tout = s.T; c.Cout = s.H;
+  e = launch_dec_conv_softmax(c, s.T, A_hat, s.seq_len, st);
+  if (e != hipErrorNotSupported) return e;
+  ConvArgs a{};
+  a.in = c.in; a.w = c.w; a.bias = c.bias; a.out = A_hat; a.B = B; a.Cin = lay.C; a.Cout = s.H;
+  a.Tin = lay.T1; a.Xin = lay.Wd; a.Tv = a.Tout = s.T; a.Xv = a.Xout = s.K;
+  a.taps = 9; a.stride_t = 1; a.pad_top = c.pad_top; a.relu = 0; a.mode = 2;
   launch_conv(a, st);
   hipLaunchKernelGGL(dec_softmax_kernel, dim3(static_cast<uint32_t>((rows + 3) / 4)), dim3(256), 0, st, A_hat, s.seq_len,
                      rows, s.H, s.T, s.K);

@@ -1,0 +1,241 @@
+// The decoder's MLPs in one kernel (Sec. 3.1 "CNN Decoder": mu on [C_perf; V], nu on mu's output; and the
+// scalers s_mix, s_prob of Sec. 3.1.1 "Output Calculation"): a wave takes 32 rows through
+//   Z = relu(mu_w [C_perf; V] + mu_b), (s_mix, s_prob) = sigmoid(w . Z + b), hidden = relu(nu1_w Z + nu1_b),
+//   image = nu2_w hidden + nu2_b
+// without leaving its registers.  Every product is taken transposed, C[channel][row] = weights x rows^T, so
+// an accumulator tile (lane = row l % 16, registers = channels 4 (l / 16) + i) packed in pairs is the
+// operand of the next layer, with contraction slot 8 g + e of a 32-channel step meaning channel
+// 16 (e / 4) + 4 g + e % 4; the weights of nu are parked in that order.  All weights live in LDS (148 KB for
+// K = 128: one block of eight waves per CU); more than 256 outputs of nu go through in slabs.
+// Z and the hidden layer are rounded to bf16 as the layers are defined.
+//
+// Bound: memory (reads 2 x 192, writes 8 K / 2 bytes per row).  B = 4, H = 12, T = 2048, K = 128: 0.14 -> 0.04 ms;
+// before, the concatenated rows, Z and the hidden layer made a round trip each and the scalers read Z again.
+#include "sea_decoder.h"
+
+namespace sea {
+namespace {
+
+constexpr int kMlpWaves = 8, kMlpThreads = 64 * kMlpWaves;
+constexpr int kMuSteps = 6, kHidSteps = 4;     // contraction steps of 32: 192 and 128 channels
+constexpr int kNu1Tiles = 9;                   // 128 outputs + one tile for the scalers
+constexpr int kSlabTiles = 16;                 // 256 outputs of nu's last layer per slab
+
+struct MlpArgs {
+  const uint16_t* Cp;   // C_perf rows, `cp_stride` apart
+  const uint16_t* V;    // value rows, `v_stride` apart
+  int32_t cp_stride, v_stride;
+  const uint16_t *mu_w, *nu1_w, *nu2_w, *mix_w, *prob_w;
+  const float *mu_b, *nu1_b, *nu2_b, *mix_b, *prob_b;
+  uint16_t* img;        // [B][T][Wd][C]
+  float *s_mix, *s_prob;
+  const int32_t* seq_len;
+  int32_t H, T, Wd, C;
+  int64_t rows;         // B T H
+  int32_t out2;         // outputs of nu's last layer, 4 Wd
+};
+
+__global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint4 mlp_lds[];
+  uint4* w_mu = mlp_lds;                                  // [6][8][64]
+  uint4* w_nu1 = w_mu + kMuSteps * 8 * 64;                // [4][9][64]
+  float* b_mu = reinterpret_cast<float*>(w_nu1 + kHidSteps * kNu1Tiles * 64);  // biases: 128, 128, 16 per tile of the slab
+  float* b_nu1 = b_mu + 128;
+  float* b_nu2 = b_nu1 + 128;
+  uint4* w_nu2 = reinterpret_cast<uint4*>(b_nu2 + 16 * kSlabTiles);            // [4][tiles][64]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  const int32_t slabs = (a.out2 + 16 * kSlabTiles - 1) / (16 * kSlabTiles);
+  const int32_t slab_tiles = min(kSlabTiles, (a.out2 + 15) / 16);
+
+  for (int32_t id = tid; id < kMuSteps * 8 * 64; id += kMlpThreads) {
+    const int32_t fl = id & 63, nt = (id >> 6) & 7, ks = id >> 9;
+    w_mu[id] = *reinterpret_cast<const uint4*>(a.mu_w + (16 * nt + (fl & 15)) * 192 + 32 * ks + 8 * (fl >> 4));
+  }
+  // eight channels of a 128-channel row in the order of packed accumulators
+  auto permuted = [](const uint16_t* row, int32_t ks, int32_t g) {
+    const uint2 p = *reinterpret_cast<const uint2*>(row + 32 * ks + 4 * g);
+    const uint2 q = *reinterpret_cast<const uint2*>(row + 32 * ks + 16 + 4 * g);
+    return make_uint4(p.x, p.y, q.x, q.y);
+  };
+  for (int32_t id = tid; id < kHidSteps * kNu1Tiles * 64; id += kMlpThreads) {
+    const int32_t fl = id & 63, q = id >> 6, ks = q / kNu1Tiles, nt = q - ks * kNu1Tiles;
+    const int32_t co = 16 * nt + (fl & 15);
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (co < 128) {
+      v = permuted(a.nu1_w + co * 128, ks, fl >> 4);
+    } else if (co < 130) {  // the scalers' vectors, whose alignment is only that of a pair
+      const uint32_t* r = reinterpret_cast<const uint32_t*>(co == 128 ? a.mix_w : a.prob_w) + 16 * ks + 2 * (fl >> 4);
+      v = make_uint4(r[0], r[1], r[8], r[9]);
+    }
+    w_nu1[id] = v;
+  }
+  if (tid < 128) b_mu[tid] = a.mu_b[tid];
+  else if (tid < 256) b_nu1[tid - 128] = a.nu1_b[tid - 128];
+  auto stage_nu2 = [&](int32_t slab) {
+    for (int32_t id = tid; id < kHidSteps * slab_tiles * 64; id += kMlpThreads) {
+      const int32_t fl = id & 63, q = id >> 6, ks = q / slab_tiles, nt = q - ks * slab_tiles;
+      const int32_t co = (slab * kSlabTiles + nt) * 16 + (fl & 15);
+      const uint4 v = permuted(a.nu2_w + static_cast<int64_t>(min(co, a.out2 - 1)) * 128, ks, fl >> 4);
+      w_nu2[id] = co < a.out2 ? v : make_uint4(0u, 0u, 0u, 0u);
+    }
+    if (tid < 16 * slab_tiles) b_nu2[tid] = a.nu2_b[min(slab * 16 * kSlabTiles + tid, a.out2 - 1)];
+  };
+  stage_nu2(0);
+
+  const int64_t ntile = (a.rows + 31) / 32;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kMlpWaves;
+  // rows in the order (b, t, h), heads fastest: a wave's stores lie next to each other in the image
+  auto split = [&](int64_t pp, int32_t* h, int32_t* t, int32_t* b) {
+    const int64_t q = pp / a.H;
+    *h = static_cast<int32_t>(pp - q * a.H);
+    *b = static_cast<int32_t>(q / a.T);
+    *t = static_cast<int32_t>(q - static_cast<int64_t>(*b) * a.T);
+  };
+  bf16x8 nx[kMuSteps][2];
+  auto request = [&](int64_t tile) {
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      int32_t h, t, b;
+      split(min(tile * 32 + 16 * mt + lr, a.rows - 1), &h, &t, &b);
+      const int64_t r = (static_cast<int64_t>(b) * a.H + h) * a.T + t;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) nx[ks][mt] = load8(a.Cp + r * a.cp_stride + 32 * ks + 8 * lg);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) nx[4 + ks][mt] = load8(a.V + r * a.v_stride + 32 * ks + 8 * lg);
+    }
+  };
+  const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * kMlpWaves + wid;
+  if (tile0 < ntile) request(tile0);
+  __syncthreads();
+  // with one slab the loop has no barrier and a wave without a tile leaves it; with several, every wave of
+  // the block stays for the barriers of the staging (the first wave's tile is the smallest)
+  for (int64_t tile = tile0; slabs == 1 ? tile < ntile : tile - wid < ntile; tile += stride) {
+    const bool on = tile < ntile;  // wave-uniform
+    bf16x8 zf[kHidSteps][2];
+    int64_t orow[2];
+    bool live[2], exists[2];
+    if (on) {
+      bf16x8 xf[kMuSteps][2];
+#pragma unroll
+      for (int ks = 0; ks < kMuSteps; ++ks) { xf[ks][0] = nx[ks][0]; xf[ks][1] = nx[ks][1]; }
+      if (tile + stride < ntile) request(tile + stride);
+      // mu, two 16-channel tiles at a time
+#pragma unroll
+      for (int kc = 0; kc < kHidSteps; ++kc) {
+        floatx4 acc[2][2];
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const float4 bv = *reinterpret_cast<const float4*>(b_mu + 16 * (2 * kc + hf) + 4 * lg);
+          acc[hf][0] = acc[hf][1] = floatx4{bv.x, bv.y, bv.z, bv.w};
+        }
+#pragma unroll
+        for (int ks = 0; ks < kMuSteps; ++ks)
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            const bf16x8 wf = __builtin_bit_cast(bf16x8, w_mu[(ks * 8 + 2 * kc + hf) * 64 + lane]);
+            acc[hf][0] = mfma16(wf, xf[ks][0], acc[hf][0]);
+            acc[hf][1] = mfma16(wf, xf[ks][1], acc[hf][1]);
+          }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) zf[kc][mt] = pack8(relu4(acc[0][mt]), relu4(acc[1][mt]));
+      }
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const int64_t pp = tile * 32 + 16 * mt + lr;
+        int32_t h, t, b;
+        split(min(pp, a.rows - 1), &h, &t, &b);
+        const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
+        exists[mt] = pp < a.rows;
+        live[mt] = t < len;
+        orow[mt] = (static_cast<int64_t>(b) * a.T + t) * a.Wd * a.C + h * 4;
+        // the scalers: rows 0 and 1 of nu1's ninth tile
+        floatx4 sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kc = 0; kc < kHidSteps; ++kc)
+          sc = mfma16(__builtin_bit_cast(bf16x8, w_nu1[(kc * kNu1Tiles + 8) * 64 + lane]), zf[kc][mt], sc);
+        if (lg == 0 && exists[mt]) {
+          const int64_t r = (static_cast<int64_t>(b) * a.H + h) * a.T + t;
+          if (a.s_mix) a.s_mix[r] = live[mt] ? 1.f / (1.f + __expf(-(sc[0] + a.mix_b[0]))) : 0.f;
+          if (a.s_prob) a.s_prob[r] = live[mt] ? 1.f / (1.f + __expf(-(sc[1] + a.prob_b[0]))) : 0.f;
+        }
+      }
+      // nu, first layer
+      bf16x8 hf8[kHidSteps][2];
+#pragma unroll
+      for (int kc = 0; kc < kHidSteps; ++kc) {
+        floatx4 acc[2][2];
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const float4 bv = *reinterpret_cast<const float4*>(b_nu1 + 16 * (2 * kc + hf) + 4 * lg);
+          acc[hf][0] = acc[hf][1] = floatx4{bv.x, bv.y, bv.z, bv.w};
+        }
+#pragma unroll
+        for (int ks = 0; ks < kHidSteps; ++ks)
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            const bf16x8 wf = __builtin_bit_cast(bf16x8, w_nu1[(ks * kNu1Tiles + 2 * kc + hf) * 64 + lane]);
+            acc[hf][0] = mfma16(wf, zf[ks][0], acc[hf][0]);
+            acc[hf][1] = mfma16(wf, zf[ks][1], acc[hf][1]);
+          }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) hf8[kc][mt] = pack8(relu4(acc[0][mt]), relu4(acc[1][mt]));
+      }
+#pragma unroll
+      for (int kc = 0; kc < kHidSteps; ++kc) { zf[kc][0] = hf8[kc][0]; zf[kc][1] = hf8[kc][1]; }
+    }
+    // nu, last layer: outputs 4 x .. 4 x + 3 of a row are the row's head's channels of image column x
+    for (int32_t slab = 0; slab < slabs; ++slab) {
+      if (slabs > 1) {
+        __syncthreads();
+        stage_nu2(slab);
+        __syncthreads();
+      }
+      if (!on) continue;
+      for (int32_t nt = 0; nt < slab_tiles; ++nt) {
+        const int32_t co = (slab * kSlabTiles + nt) * 16 + 4 * lg;
+        const float4 bv = *reinterpret_cast<const float4*>(b_nu2 + 16 * nt + 4 * lg);
+        floatx4 acc[2];
+        acc[0] = acc[1] = floatx4{bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+        for (int ks = 0; ks < kHidSteps; ++ks) {
+          const bf16x8 wf = __builtin_bit_cast(bf16x8, w_nu2[(ks * slab_tiles + nt) * 64 + lane]);
+          acc[0] = mfma16(wf, zf[ks][0], acc[0]);
+          acc[1] = mfma16(wf, zf[ks][1], acc[1]);
+        }
+        if (co >= a.out2) continue;
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+          uint2 pk = {pack_bf16(acc[mt][0], acc[mt][1]), pack_bf16(acc[mt][2], acc[mt][3])};
+          if (!live[mt]) pk = make_uint2(0u, 0u);
+          if (exists[mt]) *reinterpret_cast<uint2*>(a.img + orow[mt] + static_cast<int64_t>(co >> 2) * a.C) = pk;
+        }
+      }
+    }
+  }
+}
+
+}  // namespace
+
+hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const uint16_t* Cp, int32_t cp_stride,
+                          const uint16_t* V, int32_t v_stride, uint16_t* img, float* s_mix, float* s_prob, hipStream_t st) {
+  MlpArgs a{};
+  auto u16 = [](const void* p) { return static_cast<const uint16_t*>(p); };
+  a.Cp = Cp; a.cp_stride = cp_stride; a.V = V; a.v_stride = v_stride;
+  a.mu_w = u16(wt.mu_w); a.nu1_w = u16(wt.nu1_w); a.nu2_w = u16(wt.nu2_w); a.mix_w = u16(wt.mix_w); a.prob_w = u16(wt.prob_w);
+  a.mu_b = wt.mu_b; a.nu1_b = wt.nu1_b; a.nu2_b = wt.nu2_b; a.mix_b = wt.mix_b; a.prob_b = wt.prob_b;
+  a.img = img; a.s_mix = s_mix; a.s_prob = s_prob; a.seq_len = s.seq_len;
+  a.H = s.H; a.T = s.T; a.Wd = s.K / 2; a.C = 4 * s.H; a.rows = static_cast<int64_t>(s.N) * s.T; a.out2 = 4 * a.Wd;
+  const int32_t slab_tiles = std::min(kSlabTiles, (a.out2 + 15) / 16);
+  const size_t lds = static_cast<size_t>(kMuSteps * 8 + kHidSteps * kNu1Tiles + kHidSteps * slab_tiles) * 1024 +
+                     (256 + 16 * kSlabTiles) * sizeof(float);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dec_mlp_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  if (e != hipSuccess) return e;
+  const int64_t blocks = ((a.rows + 31) / 32 + kMlpWaves - 1) / kMlpWaves;
+  hipLaunchKernelGGL(dec_mlp_kernel, dim3(static_cast<uint32_t>(std::min<int64_t>(256, blocks))), dim3(kMlpThreads), lds, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace sea
