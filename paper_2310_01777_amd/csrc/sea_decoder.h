@@ -33,6 +33,10 @@ __device__ __forceinline__ floatx4 relu4(floatx4 x) {
 }
 #endif
 
+// C_perf = FAVOR+(Q, K, [V_I; V]), normalised: [N][T][128] bf16; `state` is dec_linattn_state_bytes() of scratch
+size_t dec_linattn_state_bytes(const Shape& s);
+hipError_t launch_dec_linattn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V, const uint16_t* W,
+                              uint16_t* Cp, void* state, float c_dot, float c_norm, hipStream_t st);
 // mu, nu and the scalers on rows [C_perf; V]: the CNN's input image [B][T][K / 2][4 H], s_mix, s_prob [B][H][T]
 hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const uint16_t* Cp, int32_t cp_stride,
                           const uint16_t* V, int32_t v_stride, uint16_t* img, float* s_mix, float* s_prob, hipStream_t st);

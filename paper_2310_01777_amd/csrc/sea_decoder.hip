@@ -9,14 +9,7 @@
 // fed back as an operand fragment of the next product without leaving the registers.
 //
 // Kernels, in the order a call runs them:
-//   dec_features_kernel   phi(Q), phi(K) (bf16, [N][T][m]); phi(K)^T and V^T as zero-padded
-//                         transposed copies ([N][m][Tp], [N][64][Tp]) for the products that contract
-//                         over the token index
-//   dec_linattn_kernel    chunked linear attention: per 32-token chunk the outputs from the running
-//                         state (tokens of earlier chunks) and from the masked in-chunk product, then
-//                         the state update; one wavefront per (head, 16 value columns); the values
-//                         are [V_I; V; 1], so column 128 is the row normaliser
-//   dec_concat_kernel     [C_perf; V] in bf16
+//   dec_linattn_kernel    C_perf from Q, K, V (sea_decoder_linattn.hip)
 //   dec_mlp_kernel        mu, nu, s_mix, s_prob (sea_decoder_mlp.hip)
 //   dec_conv_tile_kernel, dec_conv_softmax_kernel
 //                         the convolutions of images with up to 64 channels and the final softmax
@@ -31,372 +24,6 @@ namespace {
 
 constexpr int kCs = 2;       // width reduction of the CNN's hidden image (c_s)
 constexpr int kCh = 4;       // channel expansion (c_h)
-constexpr int kTRow = 72;      // halfwords per LDS row of the transposed 64-token tile (16-byte aligned rows)
-constexpr int kValCols = 144;  // [V_I (64); V (64); 1; 15 unused]: nine 16-column slices
-
-__device__ __forceinline__ float sumsq8(bf16x8 v) {
-  const uint4 u = __builtin_bit_cast(uint4, v);
-  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-  float a = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float lo = bf16lo_to_f32(w[i]), hi = bf16hi_to_f32(w[i]);
-    a = fmaf(lo, lo, a);
-    a = fmaf(hi, hi, a);
-  }
-  return a;
-}
-
-// ------------------------------------------------------------------------------------------
-// features.  Block = 4 waves, wave = 16 rows of one head; C[feature][row] = W X^T, so lane
-// l % 16 is the row and a lane holds four consecutive features per tile.
-// grid.x = 2 N ceil(Tp / 64): first half queries, second half keys (which also transpose V).
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void dec_features_kernel(Shape s, int32_t Tp, const uint16_t* __restrict__ Q,
-                                                           const uint16_t* __restrict__ K,
-                                                           const uint16_t* __restrict__ V,
-                                                           const uint16_t* __restrict__ W,
-                                                           uint16_t* __restrict__ phiQ, uint16_t* __restrict__ phiK,
-                                                           uint16_t* __restrict__ phiKT, uint16_t* __restrict__ Vt,
-                                                           float c_dot, float c_norm) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
-  const uint32_t tiles = Tp / 64;
-  const uint32_t half = static_cast<uint32_t>(s.N) * tiles;
-  const int which = blockIdx.x >= half;
-  const uint32_t bid = which ? blockIdx.x - half : blockIdx.x;
-  const int64_t head = bid / tiles;
-  const int32_t r0 = static_cast<int32_t>(bid % tiles) * 64 + wid * 16;
-  const int32_t t = r0 + lr;                  // this lane's row (as MFMA column), < Tp
-  const int32_t tc = min(t, s.T - 1);         // clamped for loads
-  const int32_t b = static_cast<int32_t>(head / s.H);
-  const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
-  const uint16_t* X = (which ? K : Q) + (head * s.T + tc) * kHeadDim;
-  const bf16x8 x0 = load8(X + 8 * lg), x1 = load8(X + 32 + 8 * lg);
-  float nx = sumsq8(x0) + sumsq8(x1);
-  nx += __shfl_xor(nx, 16, kWave);
-  nx += __shfl_xor(nx, 32, kWave);
-  const float bias = c_norm * nx;  // log2(e) * scale * |x|^2 / 2
-  const int ftiles = s.m / 16;
-  const bool active = t < len;
-
-  if (!which) {
-    if (r0 >= s.T) return;
-    float amax = -INFINITY;
-    for (int ft = 0; ft < ftiles; ++ft) {
-      const uint16_t* w = W + (ft * 16 + lr) * kHeadDim;
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-      acc = mfma16(load8(w + 8 * lg), x0, acc);
-      acc = mfma16(load8(w + 32 + 8 * lg), x1, acc);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fmaf(c_dot, acc[i], -bias));
-    }
-    amax = fmaxf(amax, __shfl_xor(amax, 16, kWave));
-    amax = fmaxf(amax, __shfl_xor(amax, 32, kWave));
-    const float shift = ceilf(amax);  // power-of-two row scale: cancels in the normaliser
-    uint16_t* out = phiQ + (head * s.T + tc) * s.m;
-    for (int ft = 0; ft < ftiles; ++ft) {
-      const uint16_t* w = W + (ft * 16 + lr) * kHeadDim;
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-      acc = mfma16(load8(w + 8 * lg), x0, acc);
-      acc = mfma16(load8(w + 32 + 8 * lg), x1, acc);
-      float v[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = active ? exp2f(fmaf(c_dot, acc[i], -bias) - shift) : 0.f;
-      if (t < s.T) {
-        uint2 pk;
-        pk.x = pack_bf16(v[0], v[1]);
-        pk.y = pack_bf16(v[2], v[3]);
-        *reinterpret_cast<uint2*>(out + ft * 16 + 4 * lg) = pk;
-      }
-    }
-    return;
-  }
-  // keys: natural and transposed copies; positions past the sequence end (and the padding up to Tp)
-  // hold zeros, so they drop out of every sum over keys.  The transposed copies (phi(K)^T and V^T,
-  // 64 tokens = 128 bytes per row and block) are gathered in LDS and leave as whole lines.
-  __shared__ __attribute__((aligned(16))) uint16_t tT[(256 + kHeadDim) * kTRow];
-  const int tcol = wid * 16 + lr;  // this lane's token inside the block's 64
-  uint16_t* out = phiK + (head * s.T + tc) * s.m;
-  for (int ft = 0; ft < ftiles; ++ft) {
-    const uint16_t* w = W + (ft * 16 + lr) * kHeadDim;
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma16(load8(w + 8 * lg), x0, acc);
-    acc = mfma16(load8(w + 32 + 8 * lg), x1, acc);
-    float v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = active ? exp2f(fmaf(c_dot, acc[i], -bias)) : 0.f;
-    uint2 pk;
-    pk.x = pack_bf16(v[0], v[1]);
-    pk.y = pack_bf16(v[2], v[3]);
-    if (t < s.T) *reinterpret_cast<uint2*>(out + ft * 16 + 4 * lg) = pk;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t word = i < 2 ? pk.x : pk.y;
-      tT[(ft * 16 + 4 * lg + i) * kTRow + tcol] = static_cast<uint16_t>((i & 1) ? (word >> 16) : (word & 0xffffu));
-    }
-  }
-  // V^T: this lane moves dims 16 lg .. + 15 of row t
-  const uint16_t* vrow = V + (head * s.T + tc) * kHeadDim + 16 * lg;
-  const uint4 va = *reinterpret_cast<const uint4*>(vrow), vb = *reinterpret_cast<const uint4*>(vrow + 8);
-  const uint32_t words[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const uint32_t word = words[e >> 1];
-    const uint16_t val = static_cast<uint16_t>((e & 1) ? (word >> 16) : (word & 0xffffu));
-    tT[(s.m + 16 * lg + e) * kTRow + tcol] = t < s.T ? val : static_cast<uint16_t>(0);
-  }
-  __syncthreads();
-  const int32_t blk_t0 = static_cast<int32_t>(bid % tiles) * 64;
-  uint16_t* kt_base = phiKT + head * static_cast<int64_t>(s.m) * Tp + blk_t0;
-  uint16_t* vt_base = Vt + head * static_cast<int64_t>(kHeadDim) * Tp + blk_t0;
-  for (int x = threadIdx.x; x < (s.m + kHeadDim) * 8; x += 256) {
-    const int row = x >> 3, piece = x & 7;
-    const uint4 v = *reinterpret_cast<const uint4*>(&tT[row * kTRow + 8 * piece]);
-    uint16_t* dst = row < s.m ? kt_base + static_cast<int64_t>(row) * Tp : vt_base + static_cast<int64_t>(row - s.m) * Tp;
-    *reinterpret_cast<uint4*>(dst + 8 * piece) = v;
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// linear attention with values U = [V_I; V; 1].  One wavefront per (head, slice of 16 value
-// columns).  State S[f][v] = sum over earlier keys of phi(k_j)[f] U[j][v], fp32, as accumulator
-// tiles whose rows stand for the features 32 kc + 8 (r / 4) + 4 h + r % 4 (tile 2 kc + h, row r):
-// packed in pairs they are the operand fragments of contraction step kc in natural feature
-// order.  Per chunk of 32 tokens: P^T = phi(K_c) phi(Q_c)^T (masked j <= t when causal),
-// O^T = S^T-fragments x phi(Q_c)^T + U_c^T x P^T, then S += phi(K_c)^T U_c.  Unnormalised sums go
-// out in fp32: acc[N][T][144].
-// ------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint16_t one_bf16() { return 0x3f80; }
-
-// eight values U[j][v] for consecutive or listed tokens j, as a bf16 fragment
-// [vi_lo, vi_hi): the tokens j with V_I[j][v] = 1, i.e. floor(j d / T) == v (empty for v >= 64)
-template <typename F>
-__device__ __forceinline__ bf16x8 value_frag(int32_t v, const uint16_t* VtRow, int32_t T, int32_t vi_lo, int32_t vi_hi,
-                                             F&& token_of) {
-  if (v >= 64 && v < 128) {
-    // V^T row v - 64: two 8-byte pieces (tokens token_of(0) .. + 3 and token_of(4) .. + 3)
-    const uint2 a = *reinterpret_cast<const uint2*>(VtRow + token_of(0));
-    const uint2 b = *reinterpret_cast<const uint2*>(VtRow + token_of(4));
-    const uint4 u = {a.x, a.y, b.x, b.y};
-    return __builtin_bit_cast(bf16x8, u);
-  }
-  uint32_t w[4];
-#pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    uint32_t pair = 0;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int32_t j = token_of(e + h);
-      bool on = false;
-      if (v < 64) on = j >= vi_lo && j < vi_hi;                                                 // V_I[j][v]
-      else if (v == 128) on = j < T;                                                            // normaliser column
-      pair |= on ? (static_cast<uint32_t>(one_bf16()) << (16 * h)) : 0u;
-    }
-    w[e >> 1] = pair;
-  }
-  const uint4 u = {w[0], w[1], w[2], w[3]};
-  return __builtin_bit_cast(bf16x8, u);
-}
-
-// Block = nine waves, one per slice of 16 value columns, all working on the same head and the
-// same chunk: the chunk's phi(Q), phi(K) and phi(K)^T tiles are fetched once per block and parked
-// in LDS in operand-fragment order (fragment = the 16 bytes one lane feeds to one product), so the
-// features are read from memory once per head instead of once per slice.
-// The sequence is cut into G segments of `cps` chunks so that enough blocks are in flight: with
-// PHASE 0 a wave sums phi(K)^T U over its own segment and leaves the tile registers in `seg_state`
-// ([head][slice][segment][2 MC tiles][64 lanes] float4); with PHASE 1 it starts from the sum of the
-// segments before its own (causal) or of all segments (bidirectional) and emits its chunks.  G = 1:
-// PHASE 1 alone walks the whole sequence.
-constexpr int kLinWaves = 9;
-template <int MC, int PHASE>
-__global__ __launch_bounds__(64 * kLinWaves) void dec_linattn_kernel(Shape s, int32_t Tp, int32_t G, int32_t cps,
-                                                                     const uint16_t* __restrict__ phiQ,
-                                                                     const uint16_t* __restrict__ phiK,
-                                                                     const uint16_t* __restrict__ phiKT,
-                                                                     const uint16_t* __restrict__ Vt,
-                                                                     float* __restrict__ acc_out,
-                                                                     float4* __restrict__ seg_state) {
-  constexpr int m = 32 * MC;
-  constexpr int kFrags = 2 * MC * 64;  // fragments per tile: Q and K [kc][half][lane], K^T [x][lane]
-  constexpr int kThreads = 64 * kLinWaves;
-  constexpr int kPer = (3 * kFrags + kThreads - 1) / kThreads;  // fragments a thread moves per chunk
-  __shared__ __attribute__((aligned(16))) uint4 tiles[3 * kFrags];
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
-  const int slice = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t seg = static_cast<int32_t>(blockIdx.x % static_cast<uint32_t>(G));
-  const int64_t head = blockIdx.x / static_cast<uint32_t>(G);
-  const int64_t hs = head * 9 + slice;  // (head, slice)
-  const int32_t v0 = slice * 16;
-  const int32_t vcol = v0 + lr;  // the value column this lane stands for as an operand row / column
-  // floor(j d / T) == v  <=>  ceil(v T / d) <= j < ceil((v + 1) T / d)
-  const int32_t vi_lo = vcol < 64 ? static_cast<int32_t>((static_cast<int64_t>(vcol) * s.T + kHeadDim - 1) / kHeadDim) : 0;
-  const int32_t vi_hi =
-      vcol < 64 ? min(s.T, static_cast<int32_t>((static_cast<int64_t>(vcol + 1) * s.T + kHeadDim - 1) / kHeadDim)) : 0;
-  const uint16_t* VtRow = Vt + (head * kHeadDim + max(0, min(vcol - 64, 63))) * static_cast<int64_t>(Tp);
-  const uint16_t* Qh = phiQ + head * static_cast<int64_t>(s.T) * m;
-  const uint16_t* Kh = phiK + head * static_cast<int64_t>(s.T) * m;
-  const uint16_t* KTh = phiKT + head * static_cast<int64_t>(m) * Tp;
-  float* Oh = acc_out + head * static_cast<int64_t>(s.T) * kValCols;
-  const int32_t nchunks = Tp / 32;
-
-  // the block's loader: fragment id -> its 16 bytes in memory.  `which` 0: phi(Q), 1: phi(K) (rows
-  // clamped to the last token; rows past it are masked or multiply zeros), 2: phi(K)^T.
-  uint4 held[kPer];
-  auto fetch = [&](int32_t t0, bool want_q, bool want_k, bool want_kt) {
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-      // a slot with nothing to fetch (past the last fragment, or a tile this pass does not use)
-      // reads the head's first 16 bytes instead: every load is unconditional, so all of a thread's
-      // loads are in flight together
-      const int id = min(tid + r * kThreads, 3 * kFrags - 1);
-      const int which = id / kFrags, fid = id % kFrags;
-      const int x = fid >> 6, fl = fid & 63, flr = fl & 15, flg = fl >> 4;
-      const uint16_t* src;
-      bool want;
-      if (which < 2) {
-        const int kc = x >> 1, half = x & 1;
-        const int32_t row = min(t0 + 16 * half + flr, s.T - 1);
-        src = (which ? Kh : Qh) + static_cast<int64_t>(row) * m + 32 * kc + 8 * flg;
-        want = which ? want_k : want_q;
-      } else {
-        const int f = 32 * (x >> 1) + 8 * (flr >> 2) + 4 * (x & 1) + (flr & 3);
-        src = KTh + static_cast<int64_t>(f) * Tp + t0 + 8 * flg;
-        want = want_kt;
-      }
-      held[r] = *reinterpret_cast<const uint4*>(want ? src : Qh);
-    }
-  };
-  auto park = [&]() {
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-      const int id = tid + r * kThreads;
-      if (id < 3 * kFrags) tiles[id] = held[r];
-    }
-  };
-  auto frag = [&](int which, int x) { return __builtin_bit_cast(bf16x8, tiles[which * kFrags + x * 64 + lane]); };
-
-  floatx4 S[2 * MC];
-#pragma unroll
-  for (int x = 0; x < 2 * MC; ++x) S[x] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  auto update = [&](int32_t t0) {
-    // S[f][v] += sum_j phi(K)^T[f][j] U[j][v]: A rows = features (in the order of the tile rows),
-    // B column = this lane's value column, contraction over the chunk's 32 tokens
-    const bf16x8 ub = value_frag(vcol, VtRow, s.T, vi_lo, vi_hi, [&](int e) { return t0 + 8 * lg + e; });
-#pragma unroll
-    for (int x = 0; x < 2 * MC; ++x) S[x] = mfma16(frag(2, x), ub, S[x]);
-  };
-  auto emit = [&](int32_t t0, bool causal) {
-    floatx4 OT[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
-    floatx4 PT[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) PT[a][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kc = 0; kc < MC; ++kc) {
-      const bf16x8 q0 = frag(0, 2 * kc), q1 = frag(0, 2 * kc + 1);
-      const bf16x8 sf = pack8(S[2 * kc], S[2 * kc + 1]);  // rows = this slice's value columns
-      OT[0] = mfma16(sf, q0, OT[0]);
-      OT[1] = mfma16(sf, q1, OT[1]);
-      if (causal) {
-        const bf16x8 k0 = frag(1, 2 * kc), k1 = frag(1, 2 * kc + 1);
-        PT[0][0] = mfma16(k0, q0, PT[0][0]);
-        PT[0][1] = mfma16(k0, q1, PT[0][1]);
-        PT[1][0] = mfma16(k1, q0, PT[1][0]);
-        PT[1][1] = mfma16(k1, q1, PT[1][1]);
-      }
-    }
-    if (causal) {
-      // P^T tile (jt, tt): rows = keys t0 + 16 jt + 4 lg + i, column = query t0 + 16 tt + lr
-#pragma unroll
-      for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int32_t j = t0 + 16 * jt + 4 * lg + i, t = t0 + 16 * tt + lr;
-            if (j > t || j >= s.T) PT[jt][tt][i] = 0.f;
-          }
-      // contraction slots of the second product follow the register order of P^T: slot e < 4 is
-      // key t0 + 4 lg + e, slot e >= 4 key t0 + 16 + 4 lg + e - 4
-      const bf16x8 ua = value_frag(vcol, VtRow, s.T, vi_lo, vi_hi,
-                                   [&](int e) { return t0 + (e < 4 ? 4 * lg + e : 16 + 4 * lg + e - 4); });
-      OT[0] = mfma16(ua, pack8(PT[0][0], PT[1][0]), OT[0]);
-      OT[1] = mfma16(ua, pack8(PT[0][1], PT[1][1]), OT[1]);
-    }
-    // O^T tile tt: rows = value columns v0 + 4 lg + i, column = query t0 + 16 tt + lr
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const int32_t t = t0 + 16 * tt + lr;
-      if (t < s.T)
-        *reinterpret_cast<float4*>(Oh + static_cast<int64_t>(t) * kValCols + v0 + 4 * lg) =
-            make_float4(OT[tt][0], OT[tt][1], OT[tt][2], OT[tt][3]);
-    }
-  };
-  // one pass over chunks [c0, c1): the next chunk's fragments travel while this one is computed.
-  // Every branch here is uniform over the block (barriers inside).
-  auto walk = [&](int32_t c0, int32_t c1, bool do_emit, bool causal, bool do_update) {
-    const bool want_q = do_emit, want_k = do_emit && causal, want_kt = do_update;
-    if (c0 < c1) fetch(32 * c0, want_q, want_k, want_kt);
-    for (int32_t c = c0; c < c1; ++c) {
-      __syncthreads();  // the previous chunk's fragments are no longer read
-      park();
-      __syncthreads();
-      if (c + 1 < c1) fetch(32 * (c + 1), want_q, want_k, want_kt);
-      if (do_emit) emit(32 * c, causal);
-      if (do_update && !(do_emit && c + 1 == c1)) update(32 * c);  // the state after the last emitted chunk is not used
-    }
-  };
-
-  const int32_t c_begin = min(nchunks, seg * cps), c_end = min(nchunks, c_begin + cps);
-  float4* my_state = seg_state + (hs * G + seg) * (2 * MC * 64) + lane;
-  if (PHASE == 0) {
-    if (s.causal && seg == G - 1) return;  // nothing comes after the last segment (uniform over the block)
-    walk(c_begin, c_end, false, false, true);
-#pragma unroll
-    for (int x = 0; x < 2 * MC; ++x) my_state[x * 64] = make_float4(S[x][0], S[x][1], S[x][2], S[x][3]);
-    return;
-  }
-  if (G > 1) {
-    const int32_t upto = s.causal ? seg : G;
-    const float4* st = seg_state + hs * G * (2 * MC * 64) + lane;
-    for (int32_t g = 0; g < upto; ++g) {
-#pragma unroll
-      for (int x = 0; x < 2 * MC; ++x) {
-        const float4 v = st[(static_cast<int64_t>(g) * 2 * MC + x) * 64];
-        S[x][0] += v.x; S[x][1] += v.y; S[x][2] += v.z; S[x][3] += v.w;
-      }
-    }
-  } else if (!s.causal) {
-    walk(0, nchunks, false, false, true);
-  }
-  walk(c_begin, c_end, true, s.causal != 0, s.causal != 0);
-}
-
-// [C_perf; V]: rows of 192 bf16; C_perf = sums / normaliser (column 128)
-__global__ __launch_bounds__(256) void dec_concat_kernel(const float* __restrict__ acc, const uint16_t* __restrict__ V,
-                                                         uint16_t* __restrict__ X, int64_t rows) {
-  const int64_t gid = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t row = gid / 24;
-  const int part = static_cast<int>(gid % 24);  // 8 elements each
-  if (row >= rows) return;
-  uint4 o;
-  if (part < 16) {
-    const float* a = acc + row * kValCols;
-    const float den = a[128];
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    const float4 x = *reinterpret_cast<const float4*>(a + 8 * part), y = *reinterpret_cast<const float4*>(a + 8 * part + 4);
-    o.x = pack_bf16(x.x * inv, x.y * inv);
-    o.y = pack_bf16(x.z * inv, x.w * inv);
-    o.z = pack_bf16(y.x * inv, y.y * inv);
-    o.w = pack_bf16(y.z * inv, y.w * inv);
-  } else {
-    o = *reinterpret_cast<const uint4*>(V + row * kHeadDim + 8 * (part - 16));
-  }
-  *reinterpret_cast<uint4*>(X + row * 192 + 8 * part) = o;
-}
 
 // ------------------------------------------------------------------------------------------
 // implicit GEMM: out[pixel][cout] = act(bias[cout] + sum over (tap, c) in[pixel + tap][c] w[cout][tap][c]).
@@ -661,34 +288,18 @@ __global__ __launch_bounds__(256) void dec_softmax_kernel(float* __restrict__ A,
 size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct DecWs {
-  size_t phiQ, phiK, phiKT, Vt, acc, seg, X, img, y1, y2, total;
-  int32_t Tp, T1, Wd, C;
-  int32_t G, cps;  // linear attention: segments per sequence, chunks of 32 tokens per segment
+  size_t seg, Cp, img, y1, y2, total;
+  int32_t T1, Wd, C;
 };
 DecWs dec_layout(const Shape& s) {
   DecWs w{};
   const size_t N = static_cast<size_t>(s.N), T = static_cast<size_t>(s.T), B = N / s.H;
-  w.Tp = static_cast<int32_t>((s.T + 63) / 64 * 64);
   w.T1 = s.causal ? s.T : (s.T + kCs - 1) / kCs;
   w.Wd = s.K / kCs;
   w.C = s.H * kCh;
   size_t off = 0;
-  w.phiQ = off; off += up256(N * T * s.m * 2);
-  w.phiK = off; off += up256(N * T * s.m * 2);
-  w.phiKT = off; off += up256(N * s.m * static_cast<size_t>(w.Tp) * 2);
-  w.Vt = off; off += up256(N * kHeadDim * static_cast<size_t>(w.Tp) * 2);
-  w.acc = off; off += up256(N * T * kValCols * 4);
-  {
-    // segments: enough (head, slice, segment) waves to fill the chip, at least four chunks each
-    const int32_t nchunks = w.Tp / 32;
-    int32_t G = 1;
-    while (static_cast<int64_t>(s.N) * 9 * G < 3072 && G < 16 && nchunks / (2 * G) >= 4) G *= 2;
-    w.G = G;
-    w.cps = (nchunks + G - 1) / G;
-    w.seg = off;
-    if (G > 1) off += up256(N * 9 * G * static_cast<size_t>(s.m) * 16 * 4);
-  }
-  w.X = off; off += up256(N * T * 192 * 2);
+  w.seg = off; off += up256(dec_linattn_state_bytes(s));
+  w.Cp = off; off += up256(N * T * 128 * 2);
   w.img = off; off += up256(B * T * w.Wd * w.C * 2);
   w.y1 = off; off += up256(B * static_cast<size_t>(w.T1) * w.Wd * w.C * 2);
   w.y2 = off; off += up256(B * static_cast<size_t>(w.T1) * w.Wd * w.C * 2);
@@ -955,36 +566,15 @@ hipError_t launch_decoder_estimate(const Shape& s, const sea_decoder_weights& wt
   const float c_norm = static_cast<float>(l2e * 0.5 * static_cast<double>(s.scale));
   const int32_t B = s.N / s.H;
   const int64_t rows = static_cast<int64_t>(s.N) * s.T;
-  {
-    StageScope scope(SEA_STAGE_FEATURES, st);
-    hipLaunchKernelGGL(dec_features_kernel, dim3(2u * s.N * (lay.Tp / 64)), dim3(256), 0, st, s, lay.Tp, Q, K, V, W,
-                       u16(lay.phiQ), u16(lay.phiK), u16(lay.phiKT), u16(lay.Vt), c_dot, c_norm);
-  }
+  hipError_t e;
   {
     StageScope scope(SEA_STAGE_STATE, st);
-    float* acc = reinterpret_cast<float*>(base + lay.acc);
-    const dim3 grid(static_cast<uint32_t>(s.N) * lay.G);
-    float4* seg = reinterpret_cast<float4*>(base + lay.seg);
-#define SEA_LINATTN(MC_)                                                                                  \
-    do {                                                                                                  \
-      if (lay.G > 1)                                                                                      \
-        hipLaunchKernelGGL((dec_linattn_kernel<MC_, 0>), grid, dim3(64 * kLinWaves), 0, st, s, lay.Tp, lay.G, lay.cps, \
-                           u16(lay.phiQ), u16(lay.phiK), u16(lay.phiKT), u16(lay.Vt), acc, seg);          \
-      hipLaunchKernelGGL((dec_linattn_kernel<MC_, 1>), grid, dim3(64 * kLinWaves), 0, st, s, lay.Tp, lay.G, lay.cps,   \
-                         u16(lay.phiQ), u16(lay.phiK), u16(lay.phiKT), u16(lay.Vt), acc, seg);            \
-    } while (0)
-    switch (s.m) {
-      case 64: SEA_LINATTN(2); break;
-      case 128: SEA_LINATTN(4); break;
-      default: SEA_LINATTN(8); break;
-    }
-#undef SEA_LINATTN
-    hipLaunchKernelGGL(dec_concat_kernel, dim3(static_cast<uint32_t>((rows * 24 + 255) / 256)), dim3(256), 0, st, acc, V,
-                       u16(lay.X), rows);
+    e = launch_dec_linattn(s, Q, K, V, W, u16(lay.Cp), base + lay.seg, c_dot, c_norm, st);
+    if (e != hipSuccess) return e;
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
   // mu, nu and the scalers: rows [C_perf; V] -> the CNN's input image [B][T][Wd][C], channels h c_h + ch
-  hipError_t e = launch_dec_mlp(s, wt, u16(lay.X), 192, u16(lay.X) + 128, 192, u16(lay.img), s_mix, s_prob, st);
+  e = launch_dec_mlp(s, wt, u16(lay.Cp), 128, V, kHeadDim, u16(lay.img), s_mix, s_prob, st);
   if (e != hipSuccess) return e;
   // conv 1: [B][T][Wd][C] -> [B][T1][Wd][C], ReLU.  Causal: rows t-2..t; else stride c_s, rows i c_s - 1 .. + 1
   DecConv c{};

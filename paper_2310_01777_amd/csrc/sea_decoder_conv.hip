@@ -7,9 +7,9 @@
 // their CU: a block takes tile after tile, and the next tile's input window is on its way to registers
 // while the current one, parked in LDS, is multiplied.  The contraction runs over (tap, 8-channel
 // unit) pairs; where a lane finds its unit inside the window is the same for every tile and pixel, so
-// a table of window offsets per step (one LDS word) replaces the index arithmetic, which is what bound the
-// chunked kernel of sea_decoder.hip on these sizes (about 100 vector instructions against 12 matrix
-// products per step).
+// offsets taken once (a register or a table word per step) replace the index arithmetic, which is what
+// bound the chunked kernel of sea_decoder.hip on these sizes (about 100 vector instructions against 12
+// matrix products per step).
 #include "sea_decoder.h"
 
 namespace sea {
@@ -39,34 +39,36 @@ __device__ __forceinline__ Piece piece_of(const ConvTile& g, int32_t id) {
   return {hr, px - hr * g.halo_cols, id - px * g.P};
 }
 
-// conv 1 and 2.  Block = 8 waves; wave = 16 MT pixels of the tile x 16 NT output channels.
-template <int NT, int MT>
+// conv 1 and 2, 8 P channels in and out.  Block = 8 waves; wave = 16 MT pixels of the tile x all channels.
+template <int P, int MT>
 __global__ __launch_bounds__(512, 2) void dec_conv_tile_kernel(ConvTile g, uint16_t* __restrict__ out) {
+  constexpr int NT = (P + 1) / 2, KS = (9 * P + 3) / 4, pxu = P | 1;
   extern __shared__ __attribute__((aligned(16))) uint4 conv_lds[];
-  uint4* halo = conv_lds;                                            // [halo_rows][halo_cols][pxu]
-  uint4* wts = halo + g.halo_rows * g.halo_cols * g.pxu;             // [kstep][NT][64]
-  int32_t* offs = reinterpret_cast<int32_t*>(wts + g.ksteps * NT * 64);  // [kstep][4]
-  float* bias_s = reinterpret_cast<float*>(offs + 4 * g.ksteps);
+  uint4* halo = conv_lds;                                     // [halo_rows][halo_cols][pxu]
+  uint4* wts = halo + g.halo_rows * g.halo_cols * pxu;        // [KS][NT][64]
+  float* bias_s = reinterpret_cast<float*>(wts + KS * NT * 64);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  for (int32_t id = tid; id < g.ksteps * NT * 64; id += 512) {
+  for (int32_t id = tid; id < KS * NT * 64; id += 512) {
     const int32_t fl = id & 63, q = id >> 6, ks = q / NT, nt = q - ks * NT;
-    const int32_t u = 4 * ks + (fl >> 4);
-    const int32_t tap = static_cast<int32_t>((static_cast<float>(u) + 0.5f) * g.invP), cu = u - tap * g.P;
+    const int32_t u = 4 * ks + (fl >> 4), tap = u / P, cu = u - tap * P;
     const int32_t co = 16 * nt + (fl & 15);
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
     if (tap < 9 && co < g.Cout) v = *reinterpret_cast<const uint4*>(g.w + static_cast<int64_t>(co * 9 + tap) * g.Cin + 8 * cu);
     wts[id] = v;
   }
-  if (tid < 4 * g.ksteps) {
-    // (a step's units past the ninth tap meet zero weights: any place in the window will do)
-    const int32_t tap = tid / g.P, cu = tid - tap * g.P, ky = tap / 3, kx = tap - 3 * ky;
-    offs[tid] = tap < 9 ? (ky * g.halo_cols + kx) * g.pxu + cu : 0;
+  // where this lane's unit of each step lies in a pixel's window (a step's units past the ninth tap meet
+  // zero weights: any place will do)
+  int32_t offs[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const int32_t u = 4 * ks + lg, tap = u / P, cu = u - tap * P, ky = tap / 3, kx = tap - 3 * ky;
+    offs[ks] = tap < 9 ? (ky * g.halo_cols + kx) * pxu + cu : 0;
   }
   if (tid < 16 * NT) bias_s[tid] = tid < g.Cout ? g.bias[tid] : 0.f;
 
-  const int32_t npiece = g.halo_rows * g.halo_cols * g.P;
+  const int32_t npiece = g.halo_rows * g.halo_cols * P;
   uint4 held[kMaxPieces];
   auto place = [&](int64_t tile, int64_t* b, int32_t* t0, int32_t* x0) {
     const int64_t q = tile / g.tiles_x;
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(512, 2) void dec_conv_tile_kernel(ConvTile g, uint1
       const int32_t id = tid + 512 * e;
       if (id >= npiece) break;
       const Piece p = piece_of(g, id);
-      halo[(p.hr * g.halo_cols + p.hc) * g.pxu + p.unit] = held[e];
+      halo[(p.hr * g.halo_cols + p.hc) * pxu + p.unit] = held[e];
     }
   };
   int32_t base[MT], prow[MT], pcol[MT];
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(512, 2) void dec_conv_tile_kernel(ConvTile g, uint1
     const int32_t pidx = (wid * MT + mt) * 16 + lr;
     prow[mt] = pidx >> g.cw_log;
     pcol[mt] = pidx & ((1 << g.cw_log) - 1);
-    base[mt] = (prow[mt] * g.stride_t * g.halo_cols + pcol[mt]) * g.pxu;
+    base[mt] = (prow[mt] * g.stride_t * g.halo_cols + pcol[mt]) * pxu;
   }
   const int64_t ntile = static_cast<int64_t>(g.B) * g.tiles_t * g.tiles_x;
   int64_t tile = blockIdx.x;
@@ -123,9 +125,9 @@ __global__ __launch_bounds__(512, 2) void dec_conv_tile_kernel(ConvTile g, uint1
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = floatx4{bv.x, bv.y, bv.z, bv.w};
     }
-#pragma unroll 2
-    for (int32_t ks = 0; ks < g.ksteps; ++ks) {
-      const int32_t o = offs[4 * ks + lg];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int32_t o = offs[ks];
       bf16x8 xf[MT];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) xf[mt] = __builtin_bit_cast(bf16x8, halo[base[mt] + o]);
@@ -317,24 +319,28 @@ __global__ __launch_bounds__(64 * NW, 2) void dec_conv_softmax_kernel(ConvTile g
 
 constexpr size_t kLdsMax = 160 << 10;
 
-template <int NT, int MT>
+template <int P, int MT>
 hipError_t start_conv(const ConvTile& g, size_t lds, uint16_t* out, hipStream_t st) {
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dec_conv_tile_kernel<NT, MT>),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dec_conv_tile_kernel<P, MT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;
   const int64_t ntile = static_cast<int64_t>(g.B) * g.tiles_t * g.tiles_x;
   const uint32_t per_cu = lds <= kLdsMax / 2 && MT == 1 ? 2 : 1;  // (more pixels per wave: registers for one block)
-  hipLaunchKernelGGL((dec_conv_tile_kernel<NT, MT>), dim3(static_cast<uint32_t>(std::min<int64_t>(ntile, 256 * per_cu))), dim3(512),
+  hipLaunchKernelGGL((dec_conv_tile_kernel<P, MT>), dim3(static_cast<uint32_t>(std::min<int64_t>(ntile, 256 * per_cu))), dim3(512),
                      lds, st, g, out);
   return hipGetLastError();
 }
 template <int MT>
-hipError_t start_conv_nt(const ConvTile& g, int nt, size_t lds, uint16_t* out, hipStream_t st) {
-  switch (nt) {
+hipError_t start_conv_p(const ConvTile& g, size_t lds, uint16_t* out, hipStream_t st) {
+  switch (g.P) {
     case 1: return start_conv<1, MT>(g, lds, out, st);
     case 2: return start_conv<2, MT>(g, lds, out, st);
     case 3: return start_conv<3, MT>(g, lds, out, st);
-    default: return start_conv<4, MT>(g, lds, out, st);
+    case 4: return start_conv<4, MT>(g, lds, out, st);
+    case 5: return start_conv<5, MT>(g, lds, out, st);
+    case 6: return start_conv<6, MT>(g, lds, out, st);
+    case 7: return start_conv<7, MT>(g, lds, out, st);
+    default: return start_conv<8, MT>(g, lds, out, st);
   }
 }
 template <int MT, int NW>
@@ -354,7 +360,7 @@ hipError_t start_softmax(const ConvTile& g, size_t lds, float* A, const int32_t*
 
 // hipErrorNotSupported: the layer does not fit (more than 64 channels); the caller has another kernel
 hipError_t launch_dec_conv(const DecConv& c, uint16_t* out, hipStream_t st) {
-  if (c.Cin % 8 != 0 || c.Cout % 4 != 0 || c.Cout > 64 || c.Cin > 64) return hipErrorNotSupported;
+  if (c.Cin % 8 != 0 || c.Cout != c.Cin || c.Cin > 64) return hipErrorNotSupported;
   ConvTile g{};
   g.in = c.in; g.w = c.w; g.bias = c.bias; g.B = c.B; g.Tin = g.Tv = c.Tin; g.Xin = g.Xout = c.X; g.Cin = c.Cin;
   g.Tout = c.Tout; g.Cout = c.Cout; g.stride_t = c.stride_t; g.pad_top = c.pad_top; g.relu = 1;
@@ -370,12 +376,12 @@ hipError_t launch_dec_conv(const DecConv& c, uint16_t* out, hipStream_t st) {
     if (g.rows_out < 1) break;
     g.halo_rows = (g.rows_out - 1) * g.stride_t + 3;
     g.tiles_t = (c.Tout + g.rows_out - 1) / g.rows_out;
-    const size_t lds = static_cast<size_t>(g.halo_rows * g.halo_cols * g.pxu + g.ksteps * nt * 64) * 16 + (4 * g.ksteps + 64) * 4;
+    const size_t lds = static_cast<size_t>(g.halo_rows * g.halo_cols * g.pxu + g.ksteps * nt * 64) * 16 + 64 * 4;
     if (lds > kLdsMax || g.halo_rows * g.halo_cols * g.P > 512 * kMaxPieces) continue;
     if (mt > 1 && static_cast<int64_t>(g.B) * g.tiles_t * g.tiles_x < 256) continue;
-    if (mt == 4) return start_conv_nt<4>(g, nt, lds, out, st);
-    if (mt == 2) return start_conv_nt<2>(g, nt, lds, out, st);
-    return start_conv_nt<1>(g, nt, lds, out, st);
+    if (mt == 4) return start_conv_p<4>(g, lds, out, st);
+    if (mt == 2) return start_conv_p<2>(g, lds, out, st);
+    return start_conv_p<1>(g, lds, out, st);
   }
   return hipErrorNotSupported;
 }
