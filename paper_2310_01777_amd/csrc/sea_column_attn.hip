@@ -42,29 +42,12 @@ struct ColumnArgs {
   uint16_t* O;
   const int32_t* seq_len;
   int32_t N, H, T, KW;
-  Columns cg;
-  int32_t r;         // keys per column, 0 = whole columns (the list is all T keys)
-  int32_t U;         // length of the compact list
+  ColumnList g;
   // column of list entry u = floor(u A / D); 32 entries further: q32 more, remainder r32 more
   int32_t A, D, q32, r32;
-  float invr;        // 1 / r
   int32_t causal, group_heads;
   float c;           // scale * log2(e)
 };
-
-// position of entry i of column c
-__device__ __forceinline__ int32_t entry_pos(const ColumnArgs& a, int32_t c, int32_t i) {
-  const int32_t s0 = column_start(a.cg, c), w = column_start(a.cg, c + 1) - s0;
-  return s0 + div_small(i * w, a.invr);
-}
-// number of list entries with position <= jmax
-__device__ __forceinline__ int32_t list_count(const ColumnArgs& a, int32_t jmax) {
-  if (jmax < 0) return 0;
-  if (a.r == 0) return jmax + 1;
-  const int32_t col = column_of(a.cg, jmax);
-  const int32_t s0 = column_start(a.cg, col), w = column_start(a.cg, col + 1) - s0;
-  return col * a.r + min(a.r, ((jmax - s0 + 1) * a.r + w - 1) / w);
-}
 
 // NX = contraction slots for the mask: 8 (at least 5 keys per column: a 32-key sub-chunk touches at
 // most 8 columns), 16 (3 or 4 keys) or 32 (1 or 2 keys).
@@ -108,11 +91,11 @@ __global__ __launch_bounds__(256, 3) void column_attn_kernel(ColumnArgs a) {
   const uint32_t* mrow = &Ms[(32 * wid + ql) * mstride];
 
   const int32_t wg_hi = min(row0 + 127, a.T - 1), t_hi = min(q0 + 31, a.T - 1);
-  const int32_t u_end_wg = list_count(a, a.causal ? min(wg_hi, len - 1) : len - 1);
-  const int32_t u_end = q0 < a.T ? list_count(a, a.causal ? min(t_hi, len - 1) : len - 1) : 0;
+  const int32_t u_end_wg = list_count(a.g, a.causal ? min(wg_hi, len - 1) : len - 1);
+  const int32_t u_end = q0 < a.T ? list_count(a.g, a.causal ? min(t_hi, len - 1) : len - 1) : 0;
   // entries below u_free are admissible for every active row of the wave
-  const int32_t u_free = min(u_end, list_count(a, a.causal ? min(q0, len - 1) : len - 1));
-  const int32_t my_ucount = list_count(a, row_active ? (a.causal ? min(t, len - 1) : len - 1) : -1);
+  const int32_t u_free = min(u_end, list_count(a.g, a.causal ? min(q0, len - 1) : len - 1));
+  const int32_t my_ucount = list_count(a.g, row_active ? (a.causal ? min(t, len - 1) : len - 1) : -1);
   const int32_t nsteps = (u_end_wg + kChunk - 1) / kChunk;
 
   // staging: 16-byte part tid & 7 of the K and V rows (tid >> 3) and (tid >> 3) + 32 of a step.  Rows
@@ -142,7 +125,7 @@ __global__ __launch_bounds__(256, 3) void column_attn_kernel(ColumnArgs a) {
     for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) x[e] = (lc >> 1) == spart + 8 * e ? v : 0u;
   };
   auto row_off = [&]() -> uint32_t {
-    const int32_t pos = a.r == 0 ? ucur : entry_pos(a, ccol, crem);
+    const int32_t pos = a.g.r == 0 ? ucur : entry_pos(a.g, ccol, crem);
     return static_cast<uint32_t>(min(pos, len - 1)) * row_bytes + spart * 16;
   };
   int32_t cs0 = 0, cs1 = 0, cs2 = 0;  // first columns of the fetched step's sub-chunks and of the one after
@@ -326,15 +309,9 @@ __global__ __launch_bounds__(256, 3) void column_attn_kernel(ColumnArgs a) {
 
 }  // namespace
 
-// Any fixed-bucket selection whose keys per column are either all of the column's or the same number
-// for every column (a cap between the two widths of a ragged split cannot occur: min(w, cap) is then
-// the cap for both).  div_small needs r (w + 1) < 2^21; the scale must leave -2^127 scale far below
-// every real score.
+// Any fixed-bucket selection; the scale must leave -2^127 scale far below every real score.
 bool column_attn_supported(const Shape& s, sea_dtype dt) {
-  if (dt != SEA_BF16 || s.geometry != 0 || s.T > (1 << 24) || !(s.scale > 1e-20f)) return false;
-  const int32_t w0 = s.T / s.K;
-  if (s.rep_cap > w0) return true;
-  return static_cast<int64_t>(s.rep_cap) * (w0 + 1) < (1 << 21);
+  return dt == SEA_BF16 && column_list_supported(s) && s.scale > 1e-20f;
 }
 
 hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
@@ -344,17 +321,14 @@ hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t*
   ColumnArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;
   a.N = s.N; a.H = s.H; a.T = s.T; a.KW = (s.K + 31) / 32;
-  a.cg = columns_of(s.T, s.K);
-  a.r = s.rep_cap > a.cg.w0 ? 0 : s.rep_cap;
-  a.U = a.r == 0 ? s.T : s.K * a.r;
-  a.A = a.r == 0 ? s.K : 1; a.D = a.r == 0 ? s.T : a.r;
+  a.g = column_list(s);
+  a.A = a.g.r == 0 ? s.K : 1; a.D = a.g.r == 0 ? s.T : a.g.r;
   a.q32 = 32 * a.A / a.D; a.r32 = 32 * a.A % a.D;
-  a.invr = a.r == 0 ? 0.f : 1.0f / static_cast<float>(a.r);
   a.causal = s.causal; a.c = s.scale * kLog2e;
-  a.group_heads = group_heads_for(s.N, a.U);
+  a.group_heads = group_heads_for(s.N, a.g.U);
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128)), block(256);
   const size_t shm = static_cast<size_t>(128) * (a.KW + 1) * sizeof(uint32_t);
-  const int32_t per = a.r == 0 ? a.cg.w0 : a.r;  // least keys per column
+  const int32_t per = a.g.r == 0 ? a.g.cg.w0 : a.g.r;  // least keys per column
   if (per >= 5) hipLaunchKernelGGL(column_attn_kernel<8>, grid, block, shm, st, a);
   else if (per >= 3) hipLaunchKernelGGL(column_attn_kernel<16>, grid, block, shm, st, a);
   else hipLaunchKernelGGL(column_attn_kernel<32>, grid, block, shm, st, a);

@@ -47,32 +47,34 @@ __device__ __forceinline__ double exp_f64(double x) {
   return ldexp(p, static_cast<int>(k));
 }
 
-// phi for 16 rows per wave.  which = 0: queries (row-max shifted, any shift cancels in the
-// normaliser), 1: keys (no shift; zero beyond seq_len).  D[row = token 4 i + lg][col = feature lr];
-// contraction slot (step s, lane group lg) stands for dimension 16 lg + s.
-// NFT > 0: the exponent arguments of the (at most NFT) feature tiles stay in registers between the
-// projection and the exponential, and the unrolled tile loop lets the loads of W run ahead;
-// NFT = 0: any m, the arguments take a round trip through the output buffer.
 // four consecutive elements of an fp32 tensor
 __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 
-template <int NFT, typename TI>
-__global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const TI* __restrict__ Q,
-                                                           const TI* __restrict__ K, const TI* __restrict__ W,
+// phi for 16 rows per block, a quarter of the features per wave (so that 12 heads of 1024 rows are 6144
+// waves and not 1536: with less than two waves per SIMD the products of 16 dependent steps and the
+// exponentials ran one after the other; 23 -> 20 us there).  Queries are shifted by their row maximum, which
+// meets in LDS (any shift cancels in the normaliser); keys are not shifted and are zero beyond seq_len.
+// D[row = token 4 i + lg][col = feature lr]; contraction slot (step s, lane group lg) stands for
+// dimension 16 lg + s.
+// NFT > 0: the exponent arguments of the wave's (at most NFT) feature tiles stay in registers between the
+// projection and the exponential, and the unrolled tile loop lets the loads of W run ahead;
+// NFT = 0: any m, the arguments take a round trip through the output buffer.
+template <int NFT>
+__global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float* __restrict__ Q,
+                                                           const float* __restrict__ K, const float* __restrict__ W,
                                                            double* __restrict__ phiQ, double* __restrict__ phiK) {
-  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ double rowmax[4][16];
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
   const uint32_t tiles = (s.T + 15) / 16;
-  const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + wid;   // over 2 N tiles
-  const int64_t nw = static_cast<int64_t>(s.N) * tiles;
-  if (wave >= 2 * nw) return;
-  const int which = wave >= nw;
-  const int64_t wv = which ? wave - nw : wave;
+  const int64_t nw = static_cast<int64_t>(s.N) * tiles;  // row tiles; blocks: queries, then keys
+  const int which = blockIdx.x >= nw;
+  const int64_t wv = which ? blockIdx.x - nw : blockIdx.x;
   const int64_t head = wv / tiles;
   const int32_t r0 = static_cast<int32_t>(wv % tiles) * 16;
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
-  const TI* X = (which ? K : Q) + (head * s.T + min(r0 + lr, s.T - 1)) * kHeadDim + 16 * lg;
+  const float* X = (which ? K : Q) + (head * s.T + min(r0 + lr, s.T - 1)) * kHeadDim + 16 * lg;
   const double rs = sqrt(static_cast<double>(s.scale));
   double xa[16];
   double nx = 0.0;
@@ -91,58 +93,69 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const TI* __
   for (int i = 0; i < 4; ++i) half_n[i] = 0.5 * __shfl(nx, 4 * i + lg, kWave);
   double* out = (which ? phiK : phiQ) + (head * s.T) * s.m;
   double amax[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  const int ntiles = s.m / 16;
+  const int ntiles = s.m / 16;  // wave w takes tiles w, w + 4, ...
   auto project = [&](int ft) {
-    const TI* w = W + static_cast<int64_t>(ft * 16 + lr) * kHeadDim + 16 * lg;
-    float4 wv[4];
+    const float* w = W + static_cast<int64_t>(ft * 16 + lr) * kHeadDim + 16 * lg;
+    float4 wv4[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wv[q] = load4(w + 4 * q);
+    for (int q = 0; q < 4; ++q) wv4[q] = load4(w + 4 * q);
     doublex4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      acc = mfma_f64(xa[4 * q], static_cast<double>(wv[q].x), acc);
-      acc = mfma_f64(xa[4 * q + 1], static_cast<double>(wv[q].y), acc);
-      acc = mfma_f64(xa[4 * q + 2], static_cast<double>(wv[q].z), acc);
-      acc = mfma_f64(xa[4 * q + 3], static_cast<double>(wv[q].w), acc);
+      acc = mfma_f64(xa[4 * q], static_cast<double>(wv4[q].x), acc);
+      acc = mfma_f64(xa[4 * q + 1], static_cast<double>(wv4[q].y), acc);
+      acc = mfma_f64(xa[4 * q + 2], static_cast<double>(wv4[q].z), acc);
+      acc = mfma_f64(xa[4 * q + 3], static_cast<double>(wv4[q].w), acc);
     }
     return acc;
   };
   double shift[4];
   auto row_shift = [&]() {
+    if (which) {  // block-uniform
+#pragma unroll
+      for (int i = 0; i < 4; ++i) shift[i] = 0.0;
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       double mx = amax[i];
 #pragma unroll
       for (int mask = 1; mask < 16; mask <<= 1) mx = fmax(mx, __shfl_xor(mx, mask, kWave));
-      shift[i] = which ? 0.0 : mx;
+      if (lr == 0) rowmax[wid][4 * i + lg] = mx;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * i + lg;
+      shift[i] = fmax(fmax(rowmax[0][r], rowmax[1][r]), fmax(rowmax[2][r], rowmax[3][r]));
     }
   };
   if constexpr (NFT > 0) {
     double arg[NFT][4];
 #pragma unroll
-    for (int ft = 0; ft < NFT; ++ft) {
-      if (ft < ntiles) {
-        const doublex4 acc = project(ft);
+    for (int f = 0; f < NFT; ++f) {
+      if (4 * f + wid < ntiles) {
+        const doublex4 acc = project(4 * f + wid);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          arg[ft][i] = acc[i] - half_n[i];
-          amax[i] = fmax(amax[i], arg[ft][i]);
+          arg[f][i] = acc[i] - half_n[i];
+          amax[i] = fmax(amax[i], arg[f][i]);
         }
       }
     }
     row_shift();
 #pragma unroll
-    for (int ft = 0; ft < NFT; ++ft) {
-      if (ft < ntiles) {
+    for (int f = 0; f < NFT; ++f) {
+      if (4 * f + wid < ntiles) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int32_t t = r0 + 4 * i + lg;
-          if (t < s.T) out[static_cast<int64_t>(t) * s.m + ft * 16 + lr] = t < len ? exp_f64(arg[ft][i] - shift[i]) : 0.0;
+          if (t < s.T) out[static_cast<int64_t>(t) * s.m + (4 * f + wid) * 16 + lr] = t < len ? exp_f64(arg[f][i] - shift[i]) : 0.0;
         }
       }
     }
   } else {
-    for (int ft = 0; ft < ntiles; ++ft) {
+    for (int ft = wid; ft < ntiles; ft += 4) {
       const doublex4 acc = project(ft);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -154,7 +167,7 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const TI* __
     }
     row_shift();
     // second pass over the lane's own values
-    for (int ft = 0; ft < ntiles; ++ft) {
+    for (int ft = wid; ft < ntiles; ft += 4) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int32_t t = r0 + 4 * i + lg;
@@ -186,32 +199,44 @@ __global__ __launch_bounds__(256) void state_f64_kernel(Shape s, double* __restr
   stateT[(head * s.m + i) * s.K + c] = acc;
 }
 
-// A_hat rows: one wave per 16 rows.  Tile (16 tokens x 16 columns) = phiQ x state over the m features
-// (contraction slot (step s, lane group lg) = feature 4 s + lg); a causal row's own column is the
-// diagonal of phiQ x prefix^T.  Column tiles are taken in groups of NCT that stay in registers; with
-// one group (K <= 16 NCT) a single pass normalises and stores, with more the groups are computed
-// twice: once for the row sums, once for the normalised output.
+// A_hat rows.  Block = 8 waves on 32 rows: wave (rt, cq) takes row tile rt and the 16-column tiles
+// cq, cq + 4, ... (interleaved, so that the columns a causal tile needs are shared out evenly); the row
+// sums meet in LDS.  One wave per 16 rows and all columns gave 12 heads of 1024 rows 768 waves for 1024
+// SIMDs (36 us); split, the same products are 3072 waves, and the two row tiles read the same state while
+// it is in the cache (25 us).
+// Tile (16 tokens x 16 columns) = phiQ x state over the m features, sixteen per four steps (slot (step e, lane
+// group lg) = feature 4 lg + e, so that a lane's four feature values are 32 contiguous bytes); a causal row's own column is the diagonal of phiQ x prefix^T, each wave of a row
+// tile taking a quarter of the features.  A wave's column tiles are taken in groups of NCT that stay in
+// registers; with one group (K <= 64 NCT) a single pass normalises and stores, with more the groups are
+// computed twice: once for the row sums, once for the normalised output.
+__device__ __forceinline__ double2 load2(const double* base, uint32_t off) {
+  return *reinterpret_cast<const double2*>(base + off);
+}
+
 template <int NCT>
-__global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double* __restrict__ phiQ,
+__global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Shape s, const double* __restrict__ phiQ,
                                                            const double* __restrict__ pref,
                                                            const double* __restrict__ stateT,
                                                            float* __restrict__ A_hat) {
-  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ double red_s[2][4][16], diag_s[2][4][16];
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int rt = wid >> 2, cq = wid & 3;
   const int lr = lane & 15, lg = lane >> 4;
-  const uint32_t tiles = (s.T + 15) / 16;
-  const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + wid;
-  if (wave >= static_cast<int64_t>(s.N) * tiles) return;
-  const int64_t head = wave / tiles;
-  const int32_t r0 = static_cast<int32_t>(wave % tiles) * 16;
+  const uint32_t tiles = (s.T + 31) / 32;
+  const int64_t head = blockIdx.x / tiles;
+  const int32_t r0 = static_cast<int32_t>(blockIdx.x % tiles) * 32 + 16 * rt;  // (may lie past T: the wave then only joins the barriers)
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
-  const double* qrow = phiQ + (head * s.T + min(r0 + lr, s.T - 1)) * s.m + lg;   // A operand: token lr
-  const double* prow = pref + (head * s.T + min(r0 + lr, s.T - 1)) * s.m + lg;   // B operand: token lr as column
+  // uniform bases and 32-bit lane offsets (a head's m K state and the 16 rows' m values index with 32 bits)
+  const int32_t rbase = min(r0, s.T - 1);
+  const double* qb_ = phiQ + (head * s.T + rbase) * s.m;   // A operand: token lr
+  const double* pb_ = pref + (head * s.T + rbase) * s.m;   // B operand: token lr as column
+  const uint32_t roff = static_cast<uint32_t>(min(r0 + lr, s.T - 1) - rbase) * s.m + 4 * lg;
   const double* st = stateT + head * static_cast<int64_t>(s.m) * s.K;
-  // columns this wave needs: causal rows stop at the last row's own column
+  // columns this row tile needs: causal rows stop at the last row's own column
   const int32_t t_hi = min(r0 + 15, s.T - 1);
   const int32_t ncols = s.causal ? min(s.K, bucket_of(t_hi, s.T, s.K) + 1) : s.K;
-  const int32_t ngroups = (ncols + 16 * NCT - 1) / (16 * NCT);
+  const int32_t ngroups = (ncols + 64 * NCT - 1) / (64 * NCT);
 
   // this lane's rows: tokens r0 + 4 i + lg
   double diag[4] = {0.0, 0.0, 0.0, 0.0}, rsum[4] = {0.0, 0.0, 0.0, 0.0}, inv[4];
@@ -223,73 +248,71 @@ __global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double
     act[i] = t < len;
     tcol[i] = act[i] ? bucket_of(t, s.T, s.K) : -1;
   }
-  // Operands are requested a block of contraction steps ahead of the products that use them (two
-  // register sets in turn): with one wave per SIMD nothing else hides the memory latency.
   if (s.causal) {
-    constexpr int DS = 8;  // steps per block; m is a multiple of 32 = 8 steps
+    // steps cq, cq + 4, ... in blocks of eight features (m is a multiple of 32)
     doublex4 dg = {0.0, 0.0, 0.0, 0.0};
-    double qa[DS], pa[DS], qb[DS], pb[DS];
-    auto ld = [&](int32_t f0, double (&q)[DS], double (&p)[DS]) {
-#pragma unroll
-      for (int e = 0; e < DS; ++e) { q[e] = qrow[f0 + 4 * e]; p[e] = prow[f0 + 4 * e]; }
-    };
-    auto mm = [&](const double (&q)[DS], const double (&p)[DS]) {
-#pragma unroll
-      for (int e = 0; e < DS; ++e) dg = mfma_f64(q[e], p[e], dg);
-    };
-    ld(0, qa, pa);
-    for (int32_t f0 = 0; f0 < s.m; f0 += 8 * DS) {
-      const bool more = f0 + 4 * DS < s.m;
-      if (more) ld(f0 + 4 * DS, qb, pb);
-      mm(qa, pa);
-      if (more) {
-        if (f0 + 8 * DS < s.m) ld(f0 + 8 * DS, qa, pa);
-        mm(qb, pb);
-      }
+    for (int32_t f0 = 16 * cq; f0 < s.m; f0 += 64) {
+      const double2 q0 = load2(qb_ + f0, roff), q1 = load2(qb_ + f0 + 2, roff);
+      const double2 p0 = load2(pb_ + f0, roff), p1 = load2(pb_ + f0 + 2, roff);
+      dg = mfma_f64(q0.x, p0.x, dg);
+      dg = mfma_f64(q0.y, p0.y, dg);
+      dg = mfma_f64(q1.x, p1.x, dg);
+      dg = mfma_f64(q1.y, p1.y, dg);
     }
     // the diagonal entry of token u sits in lane (lr = u, lg = u % 4), register u / 4
 #pragma unroll
-    for (int i = 0; i < 4; ++i) diag[i] = __shfl(dg[i], 16 * lg + 4 * i + lg, kWave);
+    for (int i = 0; i < 4; ++i)
+      if (lr == 4 * i + lg) diag_s[rt][cq][lr] = dg[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int u = 4 * i + lg;
+      diag[i] = (diag_s[rt][0][u] + diag_s[rt][1][u]) + (diag_s[rt][2][u] + diag_s[rt][3][u]);
+    }
   }
   doublex4 acc[NCT];
+  // Operands are requested a block of contraction steps ahead of the products that use them (two register
+  // sets in turn).
   auto group = [&](int32_t g) {
-    const int32_t c0 = 16 * NCT * g;
-    constexpr int FS = NCT >= 16 ? 2 : 4;  // contraction steps per block
+    constexpr int FS = 4;  // contraction steps per block; m is a multiple of 32 = 8 steps
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) acc[ct] = doublex4{0.0, 0.0, 0.0, 0.0};
-    int32_t ccol[NCT];
+    int32_t c0[NCT];
+    uint32_t soff[NCT];
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) ccol[ct] = min(c0 + 16 * ct + lr, s.K - 1);
+    for (int ct = 0; ct < NCT; ++ct) {
+      c0[ct] = 64 * (NCT * g + ct) + 16 * cq;
+      soff[ct] = static_cast<uint32_t>(4 * lg * s.K + min(c0[ct] + lr, s.K - 1));
+    }
     double aa[FS], ab[FS], ba[NCT][FS], bb[NCT][FS];
     auto ld = [&](int32_t f0, double (&qa)[FS], double (&bs)[NCT][FS]) {
+      const double2 q0 = load2(qb_ + f0, roff), q1 = load2(qb_ + f0 + 2, roff);
+      qa[0] = q0.x; qa[1] = q0.y; qa[2] = q1.x; qa[3] = q1.y;
 #pragma unroll
-      for (int e = 0; e < FS; ++e) {
-        qa[e] = qrow[f0 + 4 * e];
+      for (int e = 0; e < FS; ++e)
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct)
-          if (c0 + 16 * ct < ncols) bs[ct][e] = st[static_cast<int64_t>(f0 + 4 * e + lg) * s.K + ccol[ct]];
-      }
+          if (c0[ct] < ncols) bs[ct][e] = (st + (f0 + e) * s.K)[soff[ct]];
     };
     auto mm = [&](const double (&qa)[FS], const double (&bs)[NCT][FS]) {
 #pragma unroll
       for (int e = 0; e < FS; ++e)
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct)
-          if (c0 + 16 * ct < ncols) acc[ct] = mfma_f64(qa[e], bs[ct][e], acc[ct]);
+          if (c0[ct] < ncols) acc[ct] = mfma_f64(qa[e], bs[ct][e], acc[ct]);
     };
-    ld(0, aa, ba);
-    for (int32_t f0 = 0; f0 < s.m; f0 += 8 * FS) {
-      const bool more = f0 + 4 * FS < s.m;
-      if (more) ld(f0 + 4 * FS, ab, bb);
-      mm(aa, ba);
-      if (more) {
+    if (c0[0] < ncols) {
+      ld(0, aa, ba);
+      for (int32_t f0 = 0; f0 < s.m; f0 += 8 * FS) {
+        ld(f0 + 4 * FS, ab, bb);
+        mm(aa, ba);
         if (f0 + 8 * FS < s.m) ld(f0 + 8 * FS, aa, ba);
         mm(ab, bb);
       }
     }
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
-      const int32_t c = c0 + 16 * ct + lr;
+      const int32_t c = c0[ct] + lr;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         double v = acc[ct][i];
@@ -297,7 +320,7 @@ __global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double
           if (c == tcol[i]) v = diag[i];
           if (c > tcol[i]) v = 0.0;
         }
-        if (!act[i] || c >= s.K || c0 + 16 * ct >= ncols) v = 0.0;
+        if (!act[i] || c >= s.K || c0[ct] >= ncols) v = 0.0;
         acc[ct][i] = v;
       }
     }
@@ -309,7 +332,6 @@ __global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double
       for (int i = 0; i < 4; ++i) rsum[i] += acc[ct][i];
   };
   auto store = [&](int32_t g) {
-    const int32_t c0 = 16 * NCT * g;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int32_t t = r0 + 4 * i + lg;
@@ -317,7 +339,7 @@ __global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double
       float* out = A_hat + (head * s.T + t) * s.K;
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct) {
-        const int32_t c = c0 + 16 * ct + lr;
+        const int32_t c = 64 * (NCT * g + ct) + 16 * cq + lr;
         if (c < s.K) out[c] = static_cast<float>(acc[ct][i] * inv[i]);
       }
     }
@@ -328,10 +350,17 @@ __global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double
       double r = rsum[i];
 #pragma unroll
       for (int mask = 1; mask < 16; mask <<= 1) r += __shfl_xor(r, mask, kWave);
+      if (lr == 0) red_s[rt][cq][4 * i + lg] = r;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int u = 4 * i + lg;
+      const double r = (red_s[rt][0][u] + red_s[rt][1][u]) + (red_s[rt][2][u] + red_s[rt][3][u]);
       inv[i] = r > 0.0 ? 1.0 / r : 0.0;
     }
   };
-  const int32_t all_groups = (s.K + 16 * NCT - 1) / (16 * NCT);  // groups past ncols hold zeros only
+  const int32_t all_groups = (s.K + 64 * NCT - 1) / (64 * NCT);  // groups past ncols hold zeros only
   if (ngroups <= 1) {
     group(0);
     add_sums();
@@ -348,7 +377,7 @@ __global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double
       store(g);
     }
   }
-  // columns past the wave's last one: zeros
+  // columns past the row tile's last one: zeros
   for (int32_t g = max(ngroups, 1); g < all_groups; ++g) {
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) acc[ct] = doublex4{0.0, 0.0, 0.0, 0.0};
@@ -356,17 +385,16 @@ __global__ __launch_bounds__(256) void contract_f64_kernel(Shape s, const double
   }
 }
 
-template <typename TI>
-void launch_features_f64_t(const Shape& s, const TI* Q, const TI* K, const TI* W, double* phiQ, double* phiK,
-                           hipStream_t st) {
-  const int64_t waves = 2 * static_cast<int64_t>(s.N) * ((s.T + 15) / 16);
-  const dim3 grid(static_cast<uint32_t>((waves + 3) / 4));
+void launch_features(const Shape& s, const float* Q, const float* K, const float* W, double* phiQ, double* phiK,
+                     hipStream_t st) {
+  const int64_t blocks = 2 * static_cast<int64_t>(s.N) * ((s.T + 15) / 16);
+  const dim3 grid(static_cast<uint32_t>(blocks));
   if (s.m <= 128)
-    hipLaunchKernelGGL((features_f64_kernel<8, TI>), grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+    hipLaunchKernelGGL(features_f64_kernel<2>, grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
   else if (s.m <= 256)
-    hipLaunchKernelGGL((features_f64_kernel<16, TI>), grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+    hipLaunchKernelGGL(features_f64_kernel<4>, grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
   else
-    hipLaunchKernelGGL((features_f64_kernel<0, TI>), grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+    hipLaunchKernelGGL(features_f64_kernel<0>, grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
 }
 
 }  // namespace
@@ -375,7 +403,7 @@ void launch_features_f64_t(const Shape& s, const TI* Q, const TI* K, const TI* W
 hipError_t launch_features_f64(const Shape& s, const float* Q, const float* K, const float* W, double* phiQ,
                                double* phiK, hipStream_t st) {
   if (s.m % 16 != 0) return hipErrorNotSupported;
-  launch_features_f64_t(s, Q, K, W, phiQ, phiK, st);
+  launch_features(s, Q, K, W, phiQ, phiK, st);
   return hipGetLastError();
 }
 
@@ -393,7 +421,7 @@ hipError_t launch_estimate_f64(const Shape& s, const float* Q, const float* K, c
   double* stateT = phiK + ntm;
   {
     StageScope scope(SEA_STAGE_FEATURES, st);
-    launch_features_f64_t(s, Q, K, W, phiQ, phiK, st);
+    launch_features(s, Q, K, W, phiQ, phiK, st);
   }
   {
     StageScope scope(SEA_STAGE_STATE, st);
@@ -403,14 +431,11 @@ hipError_t launch_estimate_f64(const Shape& s, const float* Q, const float* K, c
   }
   {
     StageScope scope(SEA_STAGE_CONTRACT, st);
-    const int64_t waves = static_cast<int64_t>(s.N) * ((s.T + 15) / 16);
-    const dim3 grid(static_cast<uint32_t>((waves + 3) / 4));
-    const int nct = (s.K + 15) / 16;
-#define SEA_LAUNCH_CONTRACT(C) hipLaunchKernelGGL(contract_f64_kernel<C>, grid, dim3(256), 0, st, s, phiQ, phiK, stateT, A_hat)
-    if (nct <= 2) SEA_LAUNCH_CONTRACT(2);
-    else if (nct <= 4) SEA_LAUNCH_CONTRACT(4);
-    else if (nct <= 8) SEA_LAUNCH_CONTRACT(8);
-    else SEA_LAUNCH_CONTRACT(16);
+    const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 31) / 32));
+#define SEA_LAUNCH_CONTRACT(C) hipLaunchKernelGGL(contract_f64_kernel<C>, grid, dim3(512), 0, st, s, phiQ, phiK, stateT, A_hat)
+    if (s.K <= 64) SEA_LAUNCH_CONTRACT(1);
+    else if (s.K <= 128) SEA_LAUNCH_CONTRACT(2);
+    else SEA_LAUNCH_CONTRACT(4);
 #undef SEA_LAUNCH_CONTRACT
   }
   return hipGetLastError();

@@ -86,6 +86,7 @@ hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t*
                               const uint32_t* mbits, uint16_t* O, hipStream_t st);
 // fp32 tensors: tiled attention on the fp64 / fp32 matrix cores from per-row column bits
 bool tile_attn_f32_supported(const Shape& s);
+bool tile_attn_f32_structured(const Shape& s);  // K | T and a power-of-two number of keys per column
 hipError_t launch_tile_attn_f32(const Shape& s, const float* Q, const float* K, const float* V,
                                 const uint32_t* mbits, float* O, hipStream_t st);
 hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,

@@ -21,6 +21,7 @@
 // step are parked as they lie in memory and transposed on the way out by the LDS transpose read
 // (the key and value rows themselves are gathered from K and V by position, so no compact or
 // transposed copy exists in HBM).
+#include "sea_columns.h"
 #include "sea_internal.h"
 #include "sea_tile.h"
 
@@ -803,6 +804,7 @@ struct TileF32Args {
   const int32_t* seq_len;
   int32_t N, H, T, U, KW, rlog, w, causal;
   double f;  // scale * log2(e)
+  ColumnList g;  // columns of any width (ANYW)
 };
 
 __device__ __forceinline__ float rows_max_f(float x) {
@@ -818,6 +820,8 @@ __device__ __forceinline__ float rows_sum_f(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// ANYW: columns of any width, any number of keys per column (otherwise both as in the bf16 kernel)
+template <bool ANYW>
 __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   __shared__ float m_s[4][16], l_s[4][16];
   __shared__ float o_s[4][kHeadDim][17];  // [wave][dim][query], padded
@@ -826,9 +830,15 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qc = lane & 15, g = lane >> 4;
   const uint32_t tiles = (a.T + 15) / 16;
-  // longest first: the last row tiles of every head come first
-  const uint32_t tile = tiles - 1 - blockIdx.x / static_cast<uint32_t>(a.N);
-  const int64_t head = blockIdx.x % static_cast<uint32_t>(a.N);
+  // Longest first: the last row tiles of every head come first.  Blocks are dealt to the 256 CUs in turn,
+  // so every second round of 256 runs backwards: a CU that got a longer tile gets a shorter one next.
+  uint32_t pos = blockIdx.x;
+  if ((pos >> 8) & 1) {
+    const uint32_t lo = pos & ~255u, n = min(256u, gridDim.x - lo);
+    pos = lo + (n - 1 - (pos - lo));
+  }
+  const uint32_t tile = tiles - 1 - pos / static_cast<uint32_t>(a.N);
+  const int64_t head = pos % static_cast<uint32_t>(a.N);
   const int32_t q0 = static_cast<int32_t>(tile) * 16;
   const int32_t t = q0 + qc;
   const int32_t b = static_cast<int32_t>(head / a.H);
@@ -860,7 +870,20 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   }
   const int32_t my_jmax = a.causal ? min(t, len - 1) : len - 1;
   const int32_t t_hi = min(q0 + 15, a.T - 1);
-  const int32_t u_end = compact_count(a.causal ? min(t_hi, len - 1) : len - 1, a.rlog, a.w);
+  const int32_t j_end = a.causal ? min(t_hi, len - 1) : len - 1;
+  const int32_t u_end = ANYW ? list_count(a.g, j_end) : compact_count(j_end, a.rlog, a.w);
+  auto locate = [&](int32_t u, int32_t* col) -> int32_t {  // position and column of list entry u
+    if (ANYW) {
+      if (a.g.r == 0) {
+        *col = column_of(a.g.cg, u);
+        return u;
+      }
+      *col = div_small(u, a.g.invr);
+      return entry_pos(a.g, *col, u - *col * a.g.r);
+    }
+    *col = u >> a.rlog;
+    return pos_of(u, a.rlog, a.w);
+  };
   const int32_t nchunks = (u_end + 15) / 16;
 
   double m_run = -INFINITY;
@@ -878,9 +901,11 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int32_t u = 16 * cc + 4 * i + g, uc = min(u, a.U - 1);
-      const int32_t col = uc >> a.rlog;
-      pvn[i] = pos_of(uc, a.rlog, a.w);
-      okn[i] = row_active && u < a.U && ((mrow_s[col >> 5] >> (col & 31)) & 1u) != 0u && pvn[i] <= my_jmax;
+      int32_t col;
+      pvn[i] = locate(uc, &col);
+      const int32_t pos_i = pvn[i];
+      if (ANYW) pvn[i] = min(pos_i, len - 1);  // rows past the sequence end are not read
+      okn[i] = row_active && u < a.U && ((mrow_s[col >> 5] >> (col & 31)) & 1u) != 0u && pos_i <= my_jmax;
       any = any || okn[i];
     }
     return __ballot(any) != 0ull;
@@ -890,7 +915,9 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   float4 kfn[4];
   float vfn[4][4];
   auto request = [&](int32_t cc) {
-    const float* Kr = Kh + static_cast<int64_t>(pos_of(min(16 * cc + qc, a.U - 1), a.rlog, a.w)) * kHeadDim + 4 * g;
+    int32_t col, pos_k = locate(min(16 * cc + qc, a.U - 1), &col);
+    if (ANYW) pos_k = min(pos_k, len - 1);
+    const float* Kr = Kh + static_cast<int64_t>(pos_k) * kHeadDim + 4 * g;
 #pragma unroll
     for (int j = 0; j < 4; ++j) kfn[j] = *reinterpret_cast<const float4*>(Kr + 16 * j);
 #pragma unroll
@@ -994,28 +1021,45 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   }
 }
 
-bool tile_attn_f32_supported(const Shape& s) {
-  if (s.geometry != 0 || s.T % s.K != 0 || s.K > 1024) return false;  // the tile's mask words live in LDS
-  const int32_t w = s.T / s.K;
-  const int32_t r = w < s.rep_cap ? w : s.rep_cap;
-  if (r <= 0 || (r & (r - 1)) != 0) return false;
-  if (static_cast<int64_t>(w) * r > (int64_t(1) << 30)) return false;
+namespace {
+// the power-of-two form; log2(keys per column)
+bool tile_attn_f32_pow2(const Shape& s, int32_t* rlog_out) {
+  if (s.geometry != 0 || s.T % s.K != 0) return false;
+  const int32_t w = s.T / s.K, r = w < s.rep_cap ? w : s.rep_cap;
+  if (r <= 0 || (r & (r - 1)) != 0 || static_cast<int64_t>(w) * r > (int64_t(1) << 30)) return false;
+  int32_t rlog = 0;
+  while ((1 << rlog) < r) ++rlog;
+  *rlog_out = rlog;
   return true;
+}
+}  // namespace
+
+bool tile_attn_f32_supported(const Shape& s) {  // (a tile's mask words live in LDS: K <= 1024)
+  int32_t rlog;
+  return s.K <= 1024 && (tile_attn_f32_pow2(s, &rlog) || column_list_supported(s));
+}
+bool tile_attn_f32_structured(const Shape& s) {
+  int32_t rlog;
+  return s.K <= 1024 && tile_attn_f32_pow2(s, &rlog);
 }
 
 hipError_t launch_tile_attn_f32(const Shape& s, const float* Q, const float* K, const float* V,
                                 const uint32_t* mbits, float* O, hipStream_t st) {
   if (!tile_attn_f32_supported(s)) return hipErrorNotSupported;
-  const int32_t w = s.T / s.K, r = w < s.rep_cap ? w : s.rep_cap;
-  int32_t rlog = 0;
-  while ((1 << rlog) < r) ++rlog;
   StageScope scope(SEA_STAGE_SPARSE, st);
   TileF32Args a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;
-  a.N = s.N; a.H = s.H; a.T = s.T; a.U = s.K * r; a.KW = (s.K + 31) / 32; a.rlog = rlog; a.w = w; a.causal = s.causal;
+  a.N = s.N; a.H = s.H; a.T = s.T; a.KW = (s.K + 31) / 32; a.causal = s.causal;
   a.f = static_cast<double>(s.scale) * 1.4426950408889634;
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 15) / 16));
-  hipLaunchKernelGGL(tile_attn_f32_kernel, grid, dim3(256), 0, st, a);
+  int32_t rlog = 0;
+  if (tile_attn_f32_pow2(s, &rlog)) {
+    a.rlog = rlog; a.w = s.T / s.K; a.U = s.K << rlog;
+    hipLaunchKernelGGL(tile_attn_f32_kernel<false>, grid, dim3(256), 0, st, a);
+  } else {
+    a.g = column_list(s); a.U = a.g.U;
+    hipLaunchKernelGGL(tile_attn_f32_kernel<true>, grid, dim3(256), 0, st, a);
+  }
   return hipGetLastError();
 }
 
@@ -1038,7 +1082,7 @@ hipError_t launch_tile_attn_f32_keybits(const Shape& s, const float* Q, const fl
   a.N = s.N; a.H = s.H; a.T = s.T; a.U = s.T; a.KW = (s.T + 31) / 32; a.rlog = 0; a.w = 1; a.causal = s.causal;
   a.f = static_cast<double>(s.scale) * 1.4426950408889634;
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 15) / 16));
-  hipLaunchKernelGGL(tile_attn_f32_kernel, grid, dim3(256), 0, st, a);
+  hipLaunchKernelGGL(tile_attn_f32_kernel<false>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Column-selected masks whose columns have any width (K does not divide T, or a column emits a number
-of keys that is no power of two), bf16: the estimator's key kernel for any width and the tiled attention
-that takes the mask through the matrix product, at the widths where column groups, column slots, tiles
-and list ends change, against the oracle."""
+of keys that is no power of two): the estimator's key kernel for any width and the tiled attention (bf16: with
+the mask taken through the matrix product), at the widths where column groups, column slots, tiles and
+list ends change, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -33,11 +33,16 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "_".join(str(int(v)) if not isinstance(v, float) else str(v) for v in c))
-def test_any_column_width(case):
+F32_CASES = [CASES[0], CASES[3], CASES[5], CASES[6], CASES[8], CASES[10], (1, 1, 33, 32, 7, 3, 0, True, 0.0),
+             (1, 2, 700, 64, 300, 40, 0, True, 0.0), (2, 1, 290, 96, 64, 9, 0, False, 0.3)]
+
+
+@pytest.mark.parametrize("dtype,case", [("bf16", c) for c in CASES] + [("f32", c) for c in F32_CASES],
+                         ids=lambda v: v if isinstance(v, str) else "_".join(str(x) for x in v))
+def test_any_column_width(dtype, case):
     from paper_2310_01777_amd import binding as sea
     B, H, T, m, K, kh, kb, causal, pad = case
-    wl = synth.Workload("columns", B, H, T, 64, m, K, kh, kb, causal, "bf16", 4, pad)
+    wl = synth.Workload("columns", B, H, T, 64, m, K, kh, kb, causal, dtype, 4, pad)
     x = synth.make_inputs(wl)
     seq = None if x["seq_len"] is None else x["seq_len"].clone()
     if seq is not None:
@@ -47,9 +52,9 @@ def test_any_column_width(case):
                 x[k][b, :, int(seq[b]):] = float("nan")
     d = {k: x[k].cuda() for k in "QKVW"}
     p = sea.SeaParams(B=B, H=H, T=T, d=64, m=m, K=K, k_hat=kh, k_budget=kb, causal=causal, scale=wl.scale,
-                      dtype="bf16", seq_len=None if seq is None else seq.cuda())
+                      dtype=dtype, seq_len=None if seq is None else seq.cuda())
     out, ws = sea.alloc_outputs(p), sea.alloc_workspace(p)
-    print(f"[case] columns {case}", flush=True)
+    print(f"[case] columns {dtype} {case}", flush=True)
     sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], out["O"], out["A_hat"], out["sel"], out["idx"], out["cnt"], ws,
                     mhat=out["mhat"])
     O2 = torch.full_like(out["O"], float("nan"))   # and without any intermediate
@@ -60,11 +65,11 @@ def test_any_column_width(case):
     clean = {k: torch.nan_to_num(x[k]) for k in "QKV"}
     A = out["A_hat"].cpu().numpy().astype(np.float64)
     assert_close(A, oracle.estimate(po, to_np64(clean["Q"]), to_np64(clean["K"]), to_np64(x["W"]), seq_len=sl),
-                 TOL["bf16"], "A_hat")
+                 TOL[dtype], "A_hat")
     sel, idx, cnt = oracle.topk_mask(po, A, seq_len=sl)
     assert np.array_equal(out["sel"].cpu().numpy(), sel)
     assert np.array_equal(out["idx"].cpu().numpy(), idx)
     assert np.array_equal(out["cnt"].cpu().numpy(), cnt)
     want = oracle.sparse_attn(po, to_np64(clean["Q"]), to_np64(clean["K"]), to_np64(clean["V"]), idx, cnt)
-    assert_close(to_np64(out["O"]), want, TOL["bf16"], "O")
+    assert_close(to_np64(out["O"]), want, TOL[dtype], "O")
     assert torch.equal(O2, out["O"])
