@@ -441,46 +441,59 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
   }
 }
 
-// ---- k^ = 1: group the rows of a head by the one column each selected (Sec. 3.1, App. A.5.3:
+// ---- few columns per row: group the rows of a head by the columns each selected (Sec. 3.1, App. A.5.3:
 // the long-sequence regime where k K < T) ----
-constexpr int kBucketRows = 256;
+// A block takes 256 RPT rows of a head, RPT per thread, so that its counters meet memory once for all of
+// them (one row per thread cost 675 K global atomics for 12 heads of 131072 rows: counting 23 us, scattering
+// 32 us; with eight 10 and 15 us).  RPT S <= 8 entries of a thread wait in registers between ranking and
+// scattering, S >= the columns a row may select.
+constexpr int kMaxSlots = 8;
 
 __global__ __launch_bounds__(256) void zero_i32_kernel(int32_t* __restrict__ p, int64_t n) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (i < n) p[i] = 0;
 }
 
+// calls take(column) for the first `slots` set bits of a row's mask words (further bits of a foreign mask
+// are ignored); rows of whole, aligned 16-byte pieces: one load per four words
+template <typename F>
+__device__ __forceinline__ void row_columns(const uint32_t* __restrict__ mw, int32_t KW, bool vec, int32_t slots, F&& take) {
+  int n = 0;
+  auto word = [&](uint32_t w, int32_t j) {
+    while (w != 0u && n < slots) {
+      take(n, 32 * j + __ffs(static_cast<int>(w)) - 1);
+      w &= w - 1u;
+      ++n;
+    }
+  };
+  if (vec) {
+    for (int32_t j = 0; j < KW; j += 4) {
+      const uint4 w4 = *reinterpret_cast<const uint4*>(mw + j);
+      word(w4.x, j); word(w4.y, j + 1); word(w4.z, j + 2); word(w4.w, j + 3);
+    }
+  } else {
+    for (int32_t j = 0; j < KW; ++j) word(mw[j], j);
+  }
+}
+
 // bucket sizes: every set mask bit of a row is one entry of that column's bucket
-__global__ __launch_bounds__(kBucketRows) void bucket_count_kernel(const uint32_t* __restrict__ mbits,
-                                                                   int32_t* __restrict__ cnt, int32_t T,
-                                                                   int32_t KW, int32_t Kc, int32_t slots) {
+template <int RPT>
+__global__ __launch_bounds__(256) void bucket_count_kernel(const uint32_t* __restrict__ mbits,
+                                                           int32_t* __restrict__ cnt, int32_t T, int32_t KW,
+                                                           int32_t Kc, int32_t slots) {
   extern __shared__ int32_t hist[];  // Kc counters
   const int64_t head = blockIdx.y;
-  const int32_t row = blockIdx.x * kBucketRows + threadIdx.x;
-  for (int c = threadIdx.x; c < Kc; c += kBucketRows) hist[c] = 0;
+  const bool vec = (KW & 3) == 0 && (reinterpret_cast<uintptr_t>(mbits) & 15) == 0;
+  for (int c = threadIdx.x; c < Kc; c += 256) hist[c] = 0;
   __syncthreads();
-  if (row < T) {
-    const uint32_t* mw = mbits + (head * T + row) * KW;
-    int n = 0;  // a row has at most `slots` entries: further bits of a foreign mask are ignored
-    auto take = [&](uint32_t word, int32_t j) {
-      while (word != 0u && n < slots) {
-        const int bit = __ffs(static_cast<int>(word)) - 1;
-        word &= word - 1u;
-        atomicAdd(&hist[32 * j + bit], 1);
-        ++n;
-      }
-    };
-    if ((KW & 3) == 0 && (reinterpret_cast<uintptr_t>(mbits) & 15) == 0) {  // rows of whole, aligned 16-byte pieces: one load per four words
-      for (int32_t j = 0; j < KW; j += 4) {
-        const uint4 w4 = *reinterpret_cast<const uint4*>(mw + j);
-        take(w4.x, j); take(w4.y, j + 1); take(w4.z, j + 2); take(w4.w, j + 3);
-      }
-    } else {
-      for (int32_t j = 0; j < KW; ++j) take(mw[j], j);
-    }
+#pragma unroll
+  for (int q = 0; q < RPT; ++q) {
+    const int32_t row = (blockIdx.x * RPT + q) * 256 + threadIdx.x;
+    if (row < T)
+      row_columns(mbits + (head * T + row) * KW, KW, vec, slots, [&](int, int32_t col) { atomicAdd(&hist[col], 1); });
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < Kc; c += kBucketRows)
+  for (int c = threadIdx.x; c < Kc; c += 256)
     if (hist[c] != 0) atomicAdd(&cnt[head * Kc + c], hist[c]);
 }
 
@@ -491,89 +504,94 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(const int32_t* __rest
                                                            int32_t* __restrict__ cursor,
                                                            int32_t* __restrict__ chunk_col, int32_t Kc,
                                                            int32_t max_chunks) {
-  __shared__ int32_t rows_s[1024], chunks_s[1024];
+  __shared__ int32_t wrows[16], wchunks[16], first[1024];
   const int64_t head = blockIdx.x;
-  const int c = threadIdx.x;
+  const int c = threadIdx.x, lane = c & 63, wave = c >> 6;
   const int32_t n = c < Kc ? cnt[head * Kc + c] : 0;
   const int32_t nch = (n + 127) >> 7;
-  rows_s[c] = n;
-  chunks_s[c] = nch;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {  // inclusive scans
-    const int32_t ar = c >= off ? rows_s[c - off] : 0, ac = c >= off ? chunks_s[c - off] : 0;
-    __syncthreads();
-    rows_s[c] += ar;
-    chunks_s[c] += ac;
-    __syncthreads();
+  int32_t r = n, k = nch;  // inclusive scans: inside the wave, then over the waves' totals
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int32_t ar = __shfl_up(r, off, kWave), ak = __shfl_up(k, off, kWave);
+    if (lane >= off) { r += ar; k += ak; }
   }
-  const int32_t r0 = rows_s[c] - n, c0 = chunks_s[c] - nch;
-  const int32_t total_chunks = chunks_s[1023];
+  if (lane == kWave - 1) { wrows[wave] = r; wchunks[wave] = k; }
+  __syncthreads();
+  int32_t total_rows = 0, total_chunks = 0, r0 = r - n, c0 = k - nch;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    if (w < wave) { r0 += wrows[w]; c0 += wchunks[w]; }
+    total_rows += wrows[w];
+    total_chunks += wchunks[w];
+  }
   if (c < Kc) {
     bstart[head * (Kc + 1) + c] = r0;
     cstart[head * (Kc + 1) + c] = c0;
     cursor[head * Kc + c] = r0;
-    for (int32_t j = 0; j < nch; ++j) chunk_col[head * max_chunks + c0 + j] = c;
   }
+  first[c] = c0;
+  __syncthreads();
   if (c == 0) {
-    bstart[head * (Kc + 1) + Kc] = rows_s[1023];
+    bstart[head * (Kc + 1) + Kc] = total_rows;
     cstart[head * (Kc + 1) + Kc] = total_chunks;
   }
-  for (int32_t x = total_chunks + c; x < max_chunks; x += 1024) chunk_col[head * max_chunks + x] = -1;
+  // the column of chunk x: the last one whose first chunk is <= x (empty buckets share their successor's
+  // first chunk, so that is the one that owns x); a thread per chunk, however the chunks are spread
+  for (int32_t x = c; x < max_chunks; x += 1024) {
+    int32_t lo = 0, hi = Kc - 1;
+    while (lo < hi) {
+      const int32_t mid = (lo + hi + 1) >> 1;
+      if (first[mid] <= x) lo = mid; else hi = mid - 1;
+    }
+    chunk_col[head * max_chunks + x] = x < total_chunks ? lo : -1;
+  }
 }
 
 // entries into their buckets (order inside a bucket is whatever the atomics give: no result
 // depends on it).  An entry is the row id with, above bit 24, its rank among the row's selected
 // columns.  With one column per row, rows that selected nothing (padding, no admissible key) get
 // their zero output here; with several, the merge kernel writes every row.
-constexpr int kMaxSlots = 8;
-__global__ __launch_bounds__(kBucketRows) void bucket_scatter_kernel(const uint32_t* __restrict__ mbits,
-                                                                     int32_t* __restrict__ cursor,
-                                                                     int32_t* __restrict__ perm,
-                                                                     uint16_t* __restrict__ O_zero, int32_t T,
-                                                                     int32_t KW, int32_t Kc, int64_t perm_stride,
-                                                                     int32_t slots) {
+template <int S, int RPT>
+__global__ __launch_bounds__(256) void bucket_scatter_kernel(const uint32_t* __restrict__ mbits,
+                                                             int32_t* __restrict__ cursor, int32_t* __restrict__ perm,
+                                                             uint16_t* __restrict__ O_zero, int32_t T, int32_t KW,
+                                                             int32_t Kc, int64_t perm_stride, int32_t slots) {
   extern __shared__ int32_t hist[];  // Kc counters, then Kc bases
   int32_t* base = hist + Kc;
   const int64_t head = blockIdx.y;
-  const int32_t row = blockIdx.x * kBucketRows + threadIdx.x;
-  for (int c = threadIdx.x; c < Kc; c += kBucketRows) hist[c] = 0;
+  const bool vec = (KW & 3) == 0 && (reinterpret_cast<uintptr_t>(mbits) & 15) == 0;
+  for (int c = threadIdx.x; c < Kc; c += 256) hist[c] = 0;
   __syncthreads();
-  int32_t cols[kMaxSlots], ranks[kMaxSlots];
-  int n = 0;
-  if (row < T) {
-    const uint32_t* mw = mbits + (head * T + row) * KW;
-    auto take = [&](uint32_t word, int32_t j) {
-      while (word != 0u && n < slots) {
-        const int bit = __ffs(static_cast<int>(word)) - 1;
-        word &= word - 1u;
-        const int32_t col = 32 * j + bit;
-        const int32_t rank = atomicAdd(&hist[col], 1);
+  uint32_t entry[RPT][S];  // column | rank in the block's part of its bucket << 10, all ones: none
 #pragma unroll
-        for (int q = 0; q < kMaxSlots; ++q)
-          if (q == n) { cols[q] = col; ranks[q] = rank; }
-        ++n;
-      }
-    };
-    if ((KW & 3) == 0 && (reinterpret_cast<uintptr_t>(mbits) & 15) == 0) {  // rows of whole, aligned 16-byte pieces: one load per four words
-      for (int32_t j = 0; j < KW; j += 4) {
-        const uint4 w4 = *reinterpret_cast<const uint4*>(mw + j);
-        take(w4.x, j); take(w4.y, j + 1); take(w4.z, j + 2); take(w4.w, j + 3);
-      }
-    } else {
-      for (int32_t j = 0; j < KW; ++j) take(mw[j], j);
-    }
+  for (int q = 0; q < RPT; ++q) {
+#pragma unroll
+    for (int e = 0; e < S; ++e) entry[q][e] = 0xffffffffu;
+    const int32_t row = (blockIdx.x * RPT + q) * 256 + threadIdx.x;
+    if (row < T)
+      row_columns(mbits + (head * T + row) * KW, KW, vec, slots, [&](int n, int32_t col) {
+        const uint32_t v = static_cast<uint32_t>(col) | (static_cast<uint32_t>(atomicAdd(&hist[col], 1)) << 10);
+#pragma unroll
+        for (int e = 0; e < S; ++e)
+          if (e == n) entry[q][e] = v;
+      });
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < Kc; c += kBucketRows)
+  for (int c = threadIdx.x; c < Kc; c += 256)
     base[c] = hist[c] != 0 ? atomicAdd(&cursor[head * Kc + c], hist[c]) : 0;
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kMaxSlots; ++q)
-    if (q < n) perm[head * perm_stride + base[cols[q]] + ranks[q]] = row | (q << 24);
-  if (O_zero && n == 0 && row < T) {
-    uint4* o = reinterpret_cast<uint4*>(O_zero + (head * T + row) * kHeadDim);
+  for (int q = 0; q < RPT; ++q) {
+    const int32_t row = (blockIdx.x * RPT + q) * 256 + threadIdx.x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int e = 0; e < S; ++e)
+      if (entry[q][e] != 0xffffffffu)
+        perm[head * perm_stride + base[entry[q][e] & 1023u] + static_cast<int32_t>(entry[q][e] >> 10)] = row | (e << 24);
+    if (O_zero && row < T && entry[q][0] == 0xffffffffu) {
+      uint4* o = reinterpret_cast<uint4*>(O_zero + (head * T + row) * kHeadDim);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
   }
 }
 
@@ -730,13 +748,25 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
     const bool multi = s.k_hat > 1;
     const int64_t ncnt = static_cast<int64_t>(s.N) * s.K;
     hipLaunchKernelGGL(zero_i32_kernel, dim3(static_cast<uint32_t>((ncnt + 255) / 256)), dim3(256), 0, st, cnt, ncnt);
-    const dim3 rgrid((s.T + kBucketRows - 1) / kBucketRows, static_cast<uint32_t>(s.N));
-    hipLaunchKernelGGL(bucket_count_kernel, rgrid, dim3(kBucketRows), s.K * sizeof(int32_t), st, mbits, cnt, s.T, KW,
-                       s.K, s.k_hat);
+    uint16_t* O_zero = multi ? nullptr : O;
+    auto grid_of = [&](int rpt) { return dim3((s.T + 256 * rpt - 1) / (256 * rpt), static_cast<uint32_t>(s.N)); };
+    // rows per thread: eight entries, fewer where that leaves less than two blocks per CU
+    const int64_t rows256 = static_cast<int64_t>(s.N) * ((s.T + 255) / 256);
+    const int rpt = rows256 >= 8 * 512 ? 8 : (rows256 >= 2 * 512 ? 2 : 1);
+    if (rpt == 8) hipLaunchKernelGGL(bucket_count_kernel<8>, grid_of(8), dim3(256), s.K * sizeof(int32_t), st, mbits, cnt, s.T, KW, s.K, s.k_hat);
+    else if (rpt == 2) hipLaunchKernelGGL(bucket_count_kernel<2>, grid_of(2), dim3(256), s.K * sizeof(int32_t), st, mbits, cnt, s.T, KW, s.K, s.k_hat);
+    else hipLaunchKernelGGL(bucket_count_kernel<1>, grid_of(1), dim3(256), s.K * sizeof(int32_t), st, mbits, cnt, s.T, KW, s.K, s.k_hat);
     hipLaunchKernelGGL(bucket_scan_kernel, dim3(static_cast<uint32_t>(s.N)), dim3(1024), 0, st, cnt, bstart, cstart,
                        cursor, chunk_col, s.K, lay.max_chunks);
-    hipLaunchKernelGGL(bucket_scatter_kernel, rgrid, dim3(kBucketRows), 2 * s.K * sizeof(int32_t), st, mbits, cursor,
-                       perm, multi ? static_cast<uint16_t*>(nullptr) : O, s.T, KW, s.K, lay.entries, s.k_hat);
+#define SEA_SCATTER(S_, RPT_)                                                                                    \
+    hipLaunchKernelGGL((bucket_scatter_kernel<S_, RPT_>), grid_of(RPT_), dim3(256), 2 * s.K * sizeof(int32_t), st, mbits, cursor, \
+                       perm, O_zero, s.T, KW, s.K, lay.entries, s.k_hat)
+    if (s.k_hat == 1 && rpt == 8) SEA_SCATTER(1, 8);
+    else if (s.k_hat == 1 && rpt == 2) SEA_SCATTER(1, 2);
+    else if (s.k_hat == 1) SEA_SCATTER(1, 1);
+    else if (s.k_hat <= 4 && rpt >= 2) SEA_SCATTER(4, 2);
+    else SEA_SCATTER(8, 1);
+#undef SEA_SCATTER
     TileArgs a{};
     a.Q = Q; a.K = K; a.V = V; a.mbits = nullptr; a.O = O; a.seq_len = s.seq_len;
     a.N = s.N; a.H = s.H; a.T = s.T; a.U = U; a.KW = 0; a.rlog = rlog; a.w = w; a.causal = s.causal;
