@@ -499,6 +499,292 @@ __global__ __launch_bounds__(256) void key_columns_kernel(Shape s, Columns cg, c
 }
 
 // ------------------------------------------------------------------------------------------
+// Per-row top-k^ on 16 rows of a wave, in registers.  A row lives in the four lanes l % 16 + 16 q; key[ct][i]
+// is the order-preserving key of its column 16 ct + 4 lg + i (bit patterns of negated scores in [0, 1];
+// 0x40000000 for columns that are no candidates), nsel its quota, ncnd its number of candidates; columns
+// from 16 nct on hold no candidate of the wave's rows.  nib[ct]: bit i set iff that column is selected.
+// ------------------------------------------------------------------------------------------
+template <int NCT>
+__device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], uint32_t nsel, int32_t ncnd, int32_t nct_wave,
+                                               int32_t k_hat, int lg, uint32_t (&nib)[NCT]) {
+  uint32_t tau = 0x80000000u, cge = static_cast<uint32_t>(ncnd);
+  // The compare-and-count loop runs over the tiles that hold candidates of this wave's rows only
+  // (causal: the leading ones), in even steps so that a handful of loop bodies covers all cases.
+  // Bits 29..16 are searched on the keys' high halves, two keys per register: both halves of
+  // hp - trial (16-bit wrap-around differences; candidates and trial lie in [0x8000, 0xc000),
+  // non-candidates are 0x4000) have bit 15 set exactly for keys below the trial; a byte permute
+  // spreads each sign over a byte, four differences at a time, and the matrix product adds the bytes
+  // up.  The trial's
+  // low half is zero in that phase, so the counts are those of the full keys.  Bits 15..0 then
+  // compare whole keys.
+#define SEA_SEARCH_STEP(COUNT_BODY_, REDUCE_)                                                    \
+    /* done when every row's count of keys >= tau equals its quota */                            \
+    const bool pend = (cge != nsel) && (nsel != 0u);                                             \
+    if (__ballot(pend) == 0ull) break;                                                           \
+    const uint32_t trial = tau | (1u << bit);                                                    \
+    uint32_t cnt = 0;                                                                            \
+    COUNT_BODY_                                                                                  \
+    REDUCE_                                                                                      \
+    const bool take = pend && cnt >= nsel;                                                       \
+    tau = take ? trial : tau;                                                                    \
+    cge = take ? cnt : cge;
+#define SEA_SEARCH(NT_)                                                                          \
+  {                                                                                              \
+    ushort2v hp[2 * (NT_)];                                                                      \
+    _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct) {                                        \
+      hp[2 * ct] = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(key[ct][1], key[ct][0], 0x07060302u)); \
+      hp[2 * ct + 1] = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(key[ct][3], key[ct][2], 0x07060302u)); \
+    }                                                                                            \
+    /* Count of the ROW's keys at or above a trial whose low half is zero.  A byte permute turns  \
+       the signs of four differences into four bytes 0x00 / 0xff (selectors 8..11 take the sign \
+       of bytes 1, 3, 5, 7), i.e. 0 / -1 as 8-bit integers; sixteen of them are one operand of  \
+       the 8-bit matrix product, whose column is the query row (lane % 16) and whose           \
+       contraction runs over the lane's sixteen keys and the row's four lanes: against an      \
+       all -1 operand every result row is the number of the row's keys BELOW the trial, summed \
+       over the four lanes, so the counting and the cross-lane sum leave the vector pipe. */    \
+    auto count_high = [&](uint32_t trial_) {                                                     \
+      const uint32_t th = trial_ >> 16;                                                          \
+      const ushort2v th2 = __builtin_bit_cast(ushort2v, th | (th << 16));                        \
+      const intx4 neg1 = {-1, -1, -1, -1};                                                       \
+      intx4 below = {0, 0, 0, 0};                                                                \
+      _Pragma("unroll") for (int q4 = 0; q4 < ((NT_) + 3) / 4; ++q4) {                            \
+        intx4 fl = {0, 0, 0, 0};                                                                 \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                           \
+          if (4 * q4 + j < (NT_)) {                                                              \
+            const int pr = 2 * (4 * q4 + j);                                                     \
+            const uint32_t d0 = __builtin_bit_cast(uint32_t, static_cast<ushort2v>(hp[pr] - th2)); \
+            const uint32_t d1 = __builtin_bit_cast(uint32_t, static_cast<ushort2v>(hp[pr + 1] - th2)); \
+            fl[j] = static_cast<int>(__builtin_amdgcn_perm(d1, d0, 0x0b0a0908u));                \
+          }                                                                                      \
+        }                                                                                        \
+        below = __builtin_amdgcn_mfma_i32_16x16x64_i8(neg1, fl, below, 0, 0, 0);                 \
+      }                                                                                          \
+      return 16u * static_cast<uint32_t>(NT_) - static_cast<uint32_t>(below[0]);                 \
+    };                                                                                           \
+    /* Bits 29..27 at once: a row whose quota of scores lies at or above 2^-15 (rows sum to 1    \
+       over at most 256 columns, so nearly every row) would take all three bits, because the     \
+       count only grows as the trial falls; one count then stands for three steps.  A wave with  \
+       a row that fails the test searches from bit 29 as before. */                              \
+    int bit_top = 29;                                                                            \
+    {                                                                                            \
+      const bool pend = (cge != nsel) && (nsel != 0u);                                           \
+      const uint32_t trial = 0xb8000000u;                                                        \
+      const uint32_t cnt = count_high(trial);                                                    \
+      if (__ballot(pend && cnt < nsel) == 0ull) {                                                \
+        tau = pend ? trial : tau;                                                                \
+        cge = pend ? cnt : cge;                                                                  \
+        bit_top = 26;                                                                            \
+      }                                                                                          \
+    }                                                                                            \
+    _Pragma("unroll 1") for (int bit = bit_top; bit >= 16; --bit) {                               \
+      SEA_SEARCH_STEP(cnt = count_high(trial);, )                                                \
+    }                                                                                            \
+  }                                                                                              \
+  _Pragma("unroll 1") for (int bit = 15; bit >= 0; --bit) {                                       \
+    SEA_SEARCH_STEP(                                                                             \
+      _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct)                                        \
+        _Pragma("unroll") for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= trial) ? 1u : 0u;,   \
+      cnt = rows_sum_u(cnt);)                                                                    \
+  }
+  if (k_hat == 1) {
+    // one column per row: the threshold is the row maximum itself (several columns holding it
+    // are told apart by the tie rule below)
+    uint32_t mx = 0u;
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mx = max(mx, key[ct][i]);
+    mx = rows_max_u(mx);
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= mx) ? 1u : 0u;
+    tau = mx;
+    cge = rows_sum_u(cnt);
+  } else if (NCT >= 16 && nct_wave > 12) {
+    SEA_SEARCH(NCT >= 16 ? 16 : NCT)
+  } else if (NCT >= 16 && nct_wave > 8) {
+    SEA_SEARCH(NCT >= 16 ? 12 : NCT)
+  } else if (NCT >= 8 && nct_wave > 6) {
+    SEA_SEARCH(NCT >= 8 ? 8 : NCT)
+  } else if (NCT >= 8 && nct_wave > 4) {
+    SEA_SEARCH(NCT >= 8 ? 6 : NCT)
+  } else if (nct_wave > 2) {
+    SEA_SEARCH(4)
+  } else {
+    SEA_SEARCH(2)
+  }
+#undef SEA_SEARCH
+#undef SEA_SEARCH_STEP
+  // selection: keys >= tau; when more keys than the quota tie at tau (exact duplicates at the
+  // boundary), the lowest columns among them win.  nib[ct]: bit i set iff column 16 ct + 4 lg + i
+  // of this lane's row is selected.
+  const bool excess = (cge != nsel) && (nsel != 0u);
+  if (__ballot(excess) == 0ull) {
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bits |= (nsel != 0u && key[ct][i] >= tau) ? (1u << i) : 0u;
+      nib[ct] = bits;
+    }
+  } else {
+    uint32_t cgt = 0;
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cgt += (key[ct][i] > tau) ? 1u : 0u;
+    cgt = rows_sum_u(cgt);
+    int32_t need_eq = static_cast<int32_t>(nsel) - static_cast<int32_t>(cgt);  // ties still to take, in column order
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      uint32_t eqm = 0, gtm = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        eqm |= (key[ct][i] == tau && nsel != 0u) ? (1u << i) : 0u;
+        gtm |= (key[ct][i] > tau && nsel != 0u) ? (1u << i) : 0u;
+      }
+      // columns ascend with (ct, lg, i): ties of lower lane rows of this tile come first
+      uint32_t below;
+      const uint32_t total = rows_sum_prefix_u(static_cast<uint32_t>(__popc(eqm)), lg, &below);
+      uint32_t bits = gtm;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int32_t rank = static_cast<int32_t>(below) + __popc(eqm & ((1u << i) - 1u));
+        if (((eqm >> i) & 1u) && rank < need_eq) bits |= 1u << i;
+      }
+      nib[ct] = bits;
+      need_eq -= min(need_eq, static_cast<int32_t>(total));
+    }
+  }
+}
+
+// the 16 rows' selected columns as mask words
+template <int NCT>
+__device__ __forceinline__ void store_mask_words(const Shape& s, const uint32_t (&nib)[NCT], int64_t head, int32_t trow, int lg,
+                                                 uint32_t* __restrict__ mbits) {
+  // mask words: word j holds columns 32 j .. 32 j + 31 = tiles 2 j (low half) and 2 j + 1; this lane's
+  // four columns of a tile sit at bits 4 lg .. 4 lg + 3 of the tile's half.  The four lanes of a row
+  // combine their parts; the lane of the first row stores them as vectors.
+  const int32_t kw = (s.K + 31) >> 5;
+  constexpr int kWords = NCT / 2;
+  if constexpr (kWords % 4 == 0) {
+    // Four words at a time: a row swap of two words' parts and an OR leave word a's halves in the
+    // even lane groups and word b's in the odd ones; a half swap of two such registers and an OR
+    // leave the four finished words in lane groups 0..3 (three swaps for four words instead of
+    // eight), and every lane stores the word of its group.
+    uint32_t* mrow = mbits + (head * s.T + min(trow, s.T - 1)) * kw;
+#pragma unroll
+    for (int j = 0; j < kWords; j += 4) {
+      uint32_t pw[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) pw[q] = (nib[2 * (j + q)] << (4 * lg)) | (nib[2 * (j + q) + 1] << (16 + 4 * lg));
+      const auto ab = __builtin_amdgcn_permlane16_swap(pw[0], pw[1], false, false);
+      const auto cd = __builtin_amdgcn_permlane16_swap(pw[2], pw[3], false, false);
+      const auto t = __builtin_amdgcn_permlane32_swap(ab[0] | ab[1], cd[0] | cd[1], false, false);
+      if (trow < s.T && j + lg < kw) mrow[j + lg] = t[0] | t[1];
+    }
+  } else {
+    uint32_t words[kWords];
+#pragma unroll
+    for (int j = 0; j < kWords; ++j)
+      words[j] = rows_or_u((nib[2 * j] << (4 * lg)) | (nib[2 * j + 1] << (16 + 4 * lg)));
+    if (trow >= s.T || lg != 0) return;
+    uint32_t* mrow = mbits + (head * s.T + trow) * kw;
+    if (kw == kWords) {
+      *reinterpret_cast<uint2*>(mrow) = make_uint2(words[0], words[1]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < kWords; ++j)
+        if (j < kw) mrow[j] = words[j];
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// From raw scores to mask bits, for 16 rows of a wave.  acc[ct][i] = raw score of row trow, column
+// cc = 16 ct + 4 lg + i; ncnd = the row's number of admissible columns (0: inactive row), a causal row takes its
+// own column (the last of them) from diag.  Tiles below ct_free lie wholly below every row's last column and
+// need no test; tiles from column ncols_wave on are cleared.
+// ------------------------------------------------------------------------------------------
+template <bool CAUSAL, int NCT>
+__device__ __forceinline__ void finish_rows(const Shape& s, floatx4 (&acc)[NCT], int64_t head, int32_t trow, int32_t ncnd,
+                                            int32_t ct_free, int32_t ncols_wave, float diag, int lg,
+                                            float* __restrict__ A_hat, uint32_t* __restrict__ mbits) {
+  const int32_t e = ncnd - 1 - 4 * lg;  // column 16 ct + 4 lg + i is the last admissible one iff 16 ct + i == e
+  float rsum = 0.f;
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+    if (ct < ct_free) {
+      rsum += (acc[ct][0] + acc[ct][1]) + (acc[ct][2] + acc[ct][3]);
+    } else if (ct * 16 < ncols_wave) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float v = acc[ct][i];
+        if (CAUSAL && ct * 16 + i == e) v = diag;
+        if (ct * 16 + i > e) v = 0.f;
+        acc[ct][i] = v;
+        rsum += v;
+      }
+    } else {
+      acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  {
+    const float r = rows_sum(rsum);
+    // The normalised scores are kept NEGATED from here on: the bit pattern of -x (x >= +0) is
+    // 0x80000000 | bits(x), which is the selection key itself, so the keys cost no instruction.
+    const float ninv = r > 0.f ? -1.f / r : -0.f;
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[ct][i] *= ninv;
+    if (A_hat && trow < s.T) {
+      float* out = A_hat + (head * s.T + trow) * s.K;
+      if ((s.K & 3) == 0) {
+        // a scratch A_hat read only by the grouped selection needs no zeros past a row's candidates
+        const int32_t cend = s.cand_only ? min(s.K, ncnd) : s.K;
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+          if (ct * 16 + 4 * lg < cend)
+            *reinterpret_cast<float4*>(out + ct * 16 + 4 * lg) = make_float4(-acc[ct][0], -acc[ct][1], -acc[ct][2], -acc[ct][3]);
+      } else {
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (ct * 16 + 4 * lg + i < s.K) out[ct * 16 + 4 * lg + i] = -acc[ct][i];
+      }
+    }
+  }
+  if (!mbits) return;
+
+  // ---- per-row top-k^ on the normalised scores, in registers (Sec. 3.1 "Grouped Top-k^
+  // Selection", per-query grouping).  A row lives in four lanes, 4 NCT scores each.  The k^-th
+  // largest score is found by a bitwise search on order-preserving integer keys (the bit patterns
+  // of the negated scores); the counts of a step are taken over the whole row by an 8-bit integer
+  // matrix product (high halves) or per lane with two row-swap steps (low halves).  Scores are in
+  // [0, 1], so the key's two top bits are known and the search starts below them.
+  const uint32_t nsel = static_cast<uint32_t>(min(s.k_hat, ncnd));
+  uint32_t key[NCT][4];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+    if (ct < ct_free) {  // every column of the tile is a candidate of every row
+#pragma unroll
+      for (int i = 0; i < 4; ++i) key[ct][i] = __float_as_uint(acc[ct][i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        key[ct][i] = ct * 16 + i <= e ? __float_as_uint(acc[ct][i]) : 0x40000000u;
+    }
+  }
+  uint32_t nib[NCT];
+  select_columns<NCT>(key, nsel, ncnd, CAUSAL ? min(NCT, (ncols_wave + 15) >> 4) : NCT, s.k_hat, lg, nib);
+  store_mask_words<NCT>(s, nib, head, trow, lg, mbits);
+}
+
+// ------------------------------------------------------------------------------------------
 // query side.  Block = 4 waves = 64 rows of one head (16 per wave).
 // ------------------------------------------------------------------------------------------
 constexpr int kColStage = 32;   // columns of the state staged in LDS per step
@@ -785,272 +1071,114 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
 #undef SEA_SPARK1
   if (r0 >= s.T) return;  // no barrier below
 
-  // ---- masking, the own column, normalisation ----
-  // acc[ct][i] = raw score of row r0 + lr, column cc = 16 ct + 4 lg + i.  last = last admissible
-  // column of the row (-1: inactive row); a causal row takes its own column (= last) from diag.
-  // Tiles wholly below every row's last column need no test, tiles above the wave's last one are
-  // cleared.
+  // ---- masking, the own column, normalisation, selection ----
   const int32_t trow = r0 + lr;
-  const bool act = trow < len;
-  const int32_t jmax = CAUSAL ? min(trow, len - 1) : len - 1;
-  const int32_t ncnd = act ? col_of(jmax) + 1 : 0;
-  const int32_t e = ncnd - 1 - 4 * lg;  // column 16 ct + 4 lg + i is the own one iff 16 ct + i == e
+  const int32_t ncnd = trow < len ? col_of(CAUSAL ? min(trow, len - 1) : len - 1) + 1 : 0;
   const bool act_all = r0 + 15 < len;  // wave-uniform
   const int32_t ct_free = act_all ? __builtin_amdgcn_readfirstlane(col_of(CAUSAL ? r0 : len - 1)) >> 4 : 0;
-  float rsum = 0.f;
-#pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    if (ct < ct_free) {
-      rsum += (acc[ct][0] + acc[ct][1]) + (acc[ct][2] + acc[ct][3]);
-    } else if (ct * 16 < ncols_wave) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float v = acc[ct][i];
-        if (CAUSAL && ct * 16 + i == e) v = diag;
-        if (ct * 16 + i > e) v = 0.f;
-        acc[ct][i] = v;
-        rsum += v;
-      }
-    } else {
-      acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-  }
-  {
-    const float r = rows_sum(rsum);
-    // The normalised scores are kept NEGATED from here on: the bit pattern of -x (x >= +0) is
-    // 0x80000000 | bits(x), which is the selection key itself, so the keys cost no instruction.
-    const float ninv = r > 0.f ? -1.f / r : -0.f;
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[ct][i] *= ninv;
-    if (A_hat && trow < s.T) {
-      float* out = A_hat + (head * s.T + trow) * s.K;
-      if ((s.K & 3) == 0) {
-        // a scratch A_hat read only by the grouped selection needs no zeros past a row's candidates
-        const int32_t cend = s.cand_only ? min(s.K, ncnd) : s.K;
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-          if (ct * 16 + 4 * lg < cend)
-            *reinterpret_cast<float4*>(out + ct * 16 + 4 * lg) = make_float4(-acc[ct][0], -acc[ct][1], -acc[ct][2], -acc[ct][3]);
-      } else {
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (ct * 16 + 4 * lg + i < s.K) out[ct * 16 + 4 * lg + i] = -acc[ct][i];
-      }
-    }
-  }
-  if (!mbits) return;
+  finish_rows<CAUSAL, NCT>(s, acc, head, trow, ncnd, ct_free, ncols_wave, diag, lg, A_hat, mbits);
+}
 
-  // ---- per-row top-k^ on the normalised scores, in registers (Sec. 3.1 "Grouped Top-k^
-  // Selection", per-query grouping).  A row lives in four lanes, 4 NCT scores each.  The k^-th
-  // largest score is found by a bitwise search on order-preserving integer keys (the bit patterns
-  // of the negated scores); the counts of a step are taken over the whole row by an 8-bit integer
-  // matrix product (high halves) or per lane with two row-swap steps (low halves).  Scores are in
-  // [0, 1], so the key's two top bits are known and the search starts below them.
-  const uint32_t nsel = static_cast<uint32_t>(min(s.k_hat, ncnd));
-  uint32_t tau = 0x80000000u, cge = static_cast<uint32_t>(ncnd);
-  uint32_t key[NCT][4];
-#pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    if (ct < ct_free) {  // every column of the tile is a candidate of every row
-#pragma unroll
-      for (int i = 0; i < 4; ++i) key[ct][i] = __float_as_uint(acc[ct][i]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        key[ct][i] = ct * 16 + i <= e ? __float_as_uint(acc[ct][i]) : 0x40000000u;
+// ------------------------------------------------------------------------------------------
+// query side, bidirectional, one column of 65 to 128 per row (k^ = 1, m <= 128), every row active: with no
+// search to do, what is left of a row is two contractions and a maximum.  W and a head's whole state fit LDS
+// together (53 KB for m = K = 128), so a block stages them once per head and its waves take 16 rows after 16
+// rows with no barrier in between (the kernel above stages W per 64 rows and steps the state through LDS
+// behind four barriers).  Two blocks of eight waves per CU, each with an equal share of all heads' row groups.
+// Same arithmetic per row, bit for bit.  B = 1, H = 12, T = 131072, m = K = 128: the whole
+// forward 381 -> 360 us.  The search for
+// k^ > 1 wants more waves than stay resident here (c5's shape without padding: 97 -> 108 us for the whole
+// forward), shares of sequences of different lengths are unequal, K <= 64 needs no steps to begin with, and
+// two row tiles per wave (an operand read from LDS then serves twice) cost the occupancy they would need.
+// ------------------------------------------------------------------------------------------
+constexpr int kBidirWaves = 8, kBidirBlocks = 512;  // two blocks per CU
+template <int MC, int NCT>
+__global__ __launch_bounds__(64 * kBidirWaves, 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,
+                                                                                  const uint16_t* __restrict__ W,
+                                                                                  const uint16_t* __restrict__ state,
+                                                                                  float* __restrict__ A_hat,
+                                                                                  uint32_t* __restrict__ mbits, float c_dot,
+                                                                                  float c_norm, Columns cg) {
+  s.k_hat = 1;  // (the search over several is not part of this kernel)
+  constexpr int m = 32 * MC, kThreads = 64 * kBidirWaves;
+  constexpr int kSRow = m + 8;
+  constexpr int kGroup = 16 * kBidirWaves;    // rows per block and round
+  extern __shared__ __attribute__((aligned(16))) uint16_t rows_lds[];
+  uint16_t* const Ws = rows_lds;              // [m][kWRow]
+  uint16_t* const Ss = rows_lds + m * kWRow;  // [16 NCT][kSRow]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  // this block's share of all heads' groups, in order: [lo, hi)
+  const uint32_t groups = (s.T + kGroup - 1) / kGroup;
+  const uint64_t all = static_cast<uint64_t>(groups) * s.N;
+  const uint32_t lb = xcd_contiguous(blockIdx.x, gridDim.x);
+  const uint32_t lo = static_cast<uint32_t>(all * lb / gridDim.x), hi = static_cast<uint32_t>(all * (lb + 1) / gridDim.x);
+
+  bf16x8 x0, x1;  // the next rows on their way
+  auto request = [&](uint32_t at) {
+    const uint32_t g = at % groups;
+    const uint16_t* X = Q + (static_cast<int64_t>(at / groups) * s.T + min(static_cast<int32_t>(g) * kGroup + 16 * wid + lr, s.T - 1)) * kHeadDim;
+    x0 = *reinterpret_cast<const bf16x8*>(X + 8 * lg);
+    x1 = *reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg);
+  };
+  request(lo);
+  for (int v = tid; v < m * 8; v += kThreads)
+    *reinterpret_cast<uint4*>(&Ws[(v >> 3) * kWRow + (v & 7) * 8]) = *reinterpret_cast<const uint4*>(W + (v >> 3) * kHeadDim + (v & 7) * 8);
+  const int32_t ncnd_all = column_of(cg, s.T - 1) + 1;  // every column is a candidate of every row
+  int64_t staged = -1;
+  for (uint32_t at = lo; at < hi; ++at) {
+    const int64_t head = at / groups;
+    if (head != staged) {
+      if (staged >= 0) __syncthreads();  // every wave is done with the last head's state
+      const uint16_t* sh = state + head * static_cast<int64_t>(s.K) * m;
+      for (int v = tid; v < 16 * NCT * m / 8; v += kThreads) {
+        const int col = v / (m / 8), part = v % (m / 8);
+        *reinterpret_cast<uint4*>(&Ss[col * kSRow + 8 * part]) =
+            *reinterpret_cast<const uint4*>(sh + static_cast<int64_t>(min(col, s.K - 1)) * m + 8 * part);
+      }
+      __syncthreads();
+      staged = head;
     }
-  }
-  // The compare-and-count loop runs over the tiles that hold candidates of this wave's rows only
-  // (causal: the leading ones), in even steps so that a handful of loop bodies covers all cases.
-  // Bits 29..16 are searched on the keys' high halves, two keys per register: both halves of
-  // hp - trial (16-bit wrap-around differences; candidates and trial lie in [0x8000, 0xc000),
-  // non-candidates are 0x4000) have bit 15 set exactly for keys below the trial; a byte permute
-  // spreads each sign over a byte, four differences at a time, and the matrix product adds the bytes
-  // up.  The trial's
-  // low half is zero in that phase, so the counts are those of the full keys.  Bits 15..0 then
-  // compare whole keys.
-#define SEA_SEARCH_STEP(COUNT_BODY_, REDUCE_)                                                    \
-    /* done when every row's count of keys >= tau equals its quota */                            \
-    const bool pend = (cge != nsel) && (nsel != 0u);                                             \
-    if (__ballot(pend) == 0ull) break;                                                           \
-    const uint32_t trial = tau | (1u << bit);                                                    \
-    uint32_t cnt = 0;                                                                            \
-    COUNT_BODY_                                                                                  \
-    REDUCE_                                                                                      \
-    const bool take = pend && cnt >= nsel;                                                       \
-    tau = take ? trial : tau;                                                                    \
-    cge = take ? cnt : cge;
-#define SEA_SEARCH(NT_)                                                                          \
-  {                                                                                              \
-    ushort2v hp[2 * (NT_)];                                                                      \
-    _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct) {                                        \
-      hp[2 * ct] = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(key[ct][1], key[ct][0], 0x07060302u)); \
-      hp[2 * ct + 1] = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(key[ct][3], key[ct][2], 0x07060302u)); \
-    }                                                                                            \
-    /* Count of the ROW's keys at or above a trial whose low half is zero.  A byte permute turns  \
-       the signs of four differences into four bytes 0x00 / 0xff (selectors 8..11 take the sign \
-       of bytes 1, 3, 5, 7), i.e. 0 / -1 as 8-bit integers; sixteen of them are one operand of  \
-       the 8-bit matrix product, whose column is the query row (lane % 16) and whose           \
-       contraction runs over the lane's sixteen keys and the row's four lanes: against an      \
-       all -1 operand every result row is the number of the row's keys BELOW the trial, summed \
-       over the four lanes, so the counting and the cross-lane sum leave the vector pipe. */    \
-    auto count_high = [&](uint32_t trial_) {                                                     \
-      const uint32_t th = trial_ >> 16;                                                          \
-      const ushort2v th2 = __builtin_bit_cast(ushort2v, th | (th << 16));                        \
-      const intx4 neg1 = {-1, -1, -1, -1};                                                       \
-      intx4 below = {0, 0, 0, 0};                                                                \
-      _Pragma("unroll") for (int q4 = 0; q4 < ((NT_) + 3) / 4; ++q4) {                            \
-        intx4 fl = {0, 0, 0, 0};                                                                 \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                           \
-          if (4 * q4 + j < (NT_)) {                                                              \
-            const int pr = 2 * (4 * q4 + j);                                                     \
-            const uint32_t d0 = __builtin_bit_cast(uint32_t, static_cast<ushort2v>(hp[pr] - th2)); \
-            const uint32_t d1 = __builtin_bit_cast(uint32_t, static_cast<ushort2v>(hp[pr + 1] - th2)); \
-            fl[j] = static_cast<int>(__builtin_amdgcn_perm(d1, d0, 0x0b0a0908u));                \
-          }                                                                                      \
-        }                                                                                        \
-        below = __builtin_amdgcn_mfma_i32_16x16x64_i8(neg1, fl, below, 0, 0, 0);                 \
-      }                                                                                          \
-      return 16u * static_cast<uint32_t>(NT_) - static_cast<uint32_t>(below[0]);                 \
-    };                                                                                           \
-    /* Bits 29..27 at once: a row whose quota of scores lies at or above 2^-15 (rows sum to 1    \
-       over at most 256 columns, so nearly every row) would take all three bits, because the     \
-       count only grows as the trial falls; one count then stands for three steps.  A wave with  \
-       a row that fails the test searches from bit 29 as before. */                              \
-    int bit_top = 29;                                                                            \
-    {                                                                                            \
-      const bool pend = (cge != nsel) && (nsel != 0u);                                           \
-      const uint32_t trial = 0xb8000000u;                                                        \
-      const uint32_t cnt = count_high(trial);                                                    \
-      if (__ballot(pend && cnt < nsel) == 0ull) {                                                \
-        tau = pend ? trial : tau;                                                                \
-        cge = pend ? cnt : cge;                                                                  \
-        bit_top = 26;                                                                            \
-      }                                                                                          \
-    }                                                                                            \
-    _Pragma("unroll 1") for (int bit = bit_top; bit >= 16; --bit) {                               \
-      SEA_SEARCH_STEP(cnt = count_high(trial);, )                                                \
-    }                                                                                            \
-  }                                                                                              \
-  _Pragma("unroll 1") for (int bit = 15; bit >= 0; --bit) {                                       \
-    SEA_SEARCH_STEP(                                                                             \
-      _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct)                                        \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= trial) ? 1u : 0u;,   \
-      cnt = rows_sum_u(cnt);)                                                                    \
-  }
-  const int32_t nct_wave = CAUSAL ? min(NCT, (ncols_wave + 15) >> 4) : NCT;
-  if (s.k_hat == 1) {
-    // one column per row: the threshold is the row maximum itself (several columns holding it
-    // are told apart by the tie rule below)
-    uint32_t mx = 0u;
+    const int32_t r0 = static_cast<int32_t>(at % groups) * kGroup + 16 * wid;
+    float nx = sumsq8(x0) + sumsq8(x1);
+    nx += __shfl_xor(nx, 16, kWave);
+    nx += __shfl_xor(nx, 32, kWave);
+    floatx4 dots[2 * MC];
+    project_dots<MC>(Ws, x0, x1, lr, lg, dots);
+    if (at + 1 < hi) request(at + 1);
+    float dmax = -INFINITY;
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
+    for (int ft = 0; ft < 2 * MC; ++ft)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) mx = max(mx, key[ct][i]);
-    mx = rows_max_u(mx);
-    uint32_t cnt = 0;
+      for (int i = 0; i < 4; ++i) dmax = fmaxf(dmax, dots[ft][i]);
+    dmax = fmaxf(dmax, __shfl_xor(dmax, 16, kWave));
+    dmax = fmaxf(dmax, __shfl_xor(dmax, 32, kWave));
+    const float bias = c_norm * nx;
+    const float shift = r0 + lr < s.T ? ceilf(fmaf(c_dot, dmax, -bias)) : INFINITY;
+    const float off = -(bias + shift);
+    bf16x8 afrag[MC];
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= mx) ? 1u : 0u;
-    tau = mx;
-    cge = rows_sum_u(cnt);
-  } else if (NCT >= 16 && nct_wave > 12) {
-    SEA_SEARCH(NCT >= 16 ? 16 : NCT)
-  } else if (NCT >= 16 && nct_wave > 8) {
-    SEA_SEARCH(NCT >= 16 ? 12 : NCT)
-  } else if (NCT >= 8 && nct_wave > 6) {
-    SEA_SEARCH(NCT >= 8 ? 8 : NCT)
-  } else if (NCT >= 8 && nct_wave > 4) {
-    SEA_SEARCH(NCT >= 8 ? 6 : NCT)
-  } else if (nct_wave > 2) {
-    SEA_SEARCH(4)
-  } else {
-    SEA_SEARCH(2)
-  }
-#undef SEA_SEARCH
-#undef SEA_SEARCH_STEP
-  // selection: keys >= tau; when more keys than the quota tie at tau (exact duplicates at the
-  // boundary), the lowest columns among them win.  nib[ct]: bit i set iff column 16 ct + 4 lg + i
-  // of this lane's row is selected.
-  uint32_t nib[NCT];
-  const bool excess = (cge != nsel) && (nsel != 0u);
-  if (__ballot(excess) == 0ull) {
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) {
-      uint32_t bits = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) bits |= (nsel != 0u && key[ct][i] >= tau) ? (1u << i) : 0u;
-      nib[ct] = bits;
-    }
-  } else {
-    uint32_t cgt = 0;
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) cgt += (key[ct][i] > tau) ? 1u : 0u;
-    cgt = rows_sum_u(cgt);
-    int32_t need_eq = static_cast<int32_t>(nsel) - static_cast<int32_t>(cgt);  // ties still to take, in column order
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) {
-      uint32_t eqm = 0, gtm = 0;
+    for (int kc = 0; kc < MC; ++kc) {
+      float lo[4], hi[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        eqm |= (key[ct][i] == tau && nsel != 0u) ? (1u << i) : 0u;
-        gtm |= (key[ct][i] > tau && nsel != 0u) ? (1u << i) : 0u;
+        lo[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, dots[2 * kc][i], off));
+        hi[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, dots[2 * kc + 1][i], off));
       }
-      // columns ascend with (ct, lg, i): ties of lower lane rows of this tile come first
-      uint32_t below;
-      const uint32_t total = rows_sum_prefix_u(static_cast<uint32_t>(__popc(eqm)), lg, &below);
-      uint32_t bits = gtm;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int32_t rank = static_cast<int32_t>(below) + __popc(eqm & ((1u << i) - 1u));
-        if (((eqm >> i) & 1u) && rank < need_eq) bits |= 1u << i;
-      }
-      nib[ct] = bits;
-      need_eq -= min(need_eq, static_cast<int32_t>(total));
+      afrag[kc] = pack8(lo, hi);
     }
-  }
-  // mask words: word j holds columns 32 j .. 32 j + 31 = tiles 2 j (low half) and 2 j + 1; this lane's
-  // four columns of a tile sit at bits 4 lg .. 4 lg + 3 of the tile's half.  The four lanes of a row
-  // combine their parts; the lane of the first row stores them as vectors.
-  const int32_t kw = (s.K + 31) >> 5;
-  constexpr int kWords = NCT / 2;
-  if constexpr (kWords % 4 == 0) {
-    // Four words at a time: a row swap of two words' parts and an OR leave word a's halves in the
-    // even lane groups and word b's in the odd ones; a half swap of two such registers and an OR
-    // leave the four finished words in lane groups 0..3 (three swaps for four words instead of
-    // eight), and every lane stores the word of its group.
-    uint32_t* mrow = mbits + (head * s.T + min(trow, s.T - 1)) * kw;
+    floatx4 acc[NCT];
 #pragma unroll
-    for (int j = 0; j < kWords; j += 4) {
-      uint32_t pw[4];
+    for (int ct = 0; ct < NCT; ++ct) {
+      const uint16_t* brow = &Ss[(16 * ct + lr) * kSRow + 8 * lg];
+      acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) pw[q] = (nib[2 * (j + q)] << (4 * lg)) | (nib[2 * (j + q) + 1] << (16 + 4 * lg));
-      const auto ab = __builtin_amdgcn_permlane16_swap(pw[0], pw[1], false, false);
-      const auto cd = __builtin_amdgcn_permlane16_swap(pw[2], pw[3], false, false);
-      const auto t = __builtin_amdgcn_permlane32_swap(ab[0] | ab[1], cd[0] | cd[1], false, false);
-      if (trow < s.T && j + lg < kw) mrow[j + lg] = t[0] | t[1];
+      for (int kc = 0; kc < MC; ++kc) acc[ct] = mfma16(*reinterpret_cast<const bf16x8*>(brow + 32 * kc), afrag[kc], acc[ct]);
     }
-  } else {
-    uint32_t words[kWords];
-#pragma unroll
-    for (int j = 0; j < kWords; ++j)
-      words[j] = rows_or_u((nib[2 * j] << (4 * lg)) | (nib[2 * j + 1] << (16 + 4 * lg)));
-    if (trow >= s.T || lg != 0) return;
-    uint32_t* mrow = mbits + (head * s.T + trow) * kw;
-    if (kw == kWords) {
-      *reinterpret_cast<uint2*>(mrow) = make_uint2(words[0], words[1]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kWords; ++j)
-        if (j < kw) mrow[j] = words[j];
-    }
+    const int32_t trow = r0 + lr;
+    finish_rows<false, NCT>(s, acc, head, trow, trow < s.T ? ncnd_all : 0, r0 + 15 < s.T ? (ncnd_all - 1) >> 4 : 0, s.K, 0.f, lg,
+                            A_hat, mbits);
   }
 }
 
@@ -1115,8 +1243,8 @@ void launch_rows(const Shape& s, const uint16_t* Q, const uint16_t* K, const uin
   if (s.causal)
     hipLaunchKernelGGL((estimate_rows_kernel<MC, true, WLOG, NCT>), grid, dim3(256), 0, st, s, Q, K, W, f.state,
                        f.pref, f.bpref, A_hat, mbits, c_dot, c_norm, gh, columns_of(s.T, s.K));
-  else
-    hipLaunchKernelGGL((estimate_rows_kernel<MC, false, WLOG, NCT>), grid, dim3(256), 0, st, s, Q, K, W, f.state,
+  else  // (a bidirectional row has no column of its own: any width will do)
+    hipLaunchKernelGGL((estimate_rows_kernel<MC, false, kAnyWidth, NCT>), grid, dim3(256), 0, st, s, Q, K, W, f.state,
                        f.pref, f.bpref, A_hat, mbits, c_dot, c_norm, gh, columns_of(s.T, s.K));
 }
 
@@ -1147,6 +1275,15 @@ void launch_key_columns(const Shape& s, const uint16_t* K, const uint16_t* W, co
     hipLaunchKernelGGL((key_columns_kernel<MC, true>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G);
   else
     hipLaunchKernelGGL((key_columns_kernel<MC, false>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G);
+}
+
+template <int MC, int NCT>
+void launch_bidir(const Shape& s, const uint16_t* Q, const uint16_t* W, float* A_hat, uint32_t* mbits, const FusedPtrs& f,
+                  float c_dot, float c_norm, hipStream_t st) {
+  constexpr size_t lds = (static_cast<size_t>(32 * MC) * kWRow + static_cast<size_t>(16) * NCT * (32 * MC + 8)) * 2;
+  static_assert(lds <= (64u << 10), "no larger LDS has to be asked for");
+  hipLaunchKernelGGL((estimate_rows_bidir_kernel<MC, NCT>), dim3(kBidirBlocks), dim3(64 * kBidirWaves), lds, st, s, Q, W, f.state,
+                     A_hat, mbits, c_dot, c_norm, columns_of(s.T, s.K));
 }
 
 template <int MC, int WLOG>
@@ -1186,6 +1323,12 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
                          f.bsum_u, f.bsum_r, f.state, f.bpref, 1 << (wl - 7));
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
+  if constexpr (MC <= 4) {
+    // from two row groups per resident block on (equal to the other kernel there, ahead from four on)
+    const int64_t groups = (s.T + 16 * kBidirWaves - 1) / (16 * kBidirWaves) * s.N;
+    if (!s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks && groups < (1ll << 31))
+      return launch_bidir<MC, 8>(s, Q, W, A_hat, mbits, f, c_dot, c_norm, st);
+  }
   switch (wl) {
     case -1: launch_rows_k<MC, kAnyWidth>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;
     case 0: launch_rows_k<MC, 0>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;

@@ -30,6 +30,8 @@ CASES = [
     (1, 1, 1300, 64, 13, 5, 500, True, 0.0),     # 100 of 100: the cap equals every width
     (1, 1, 1030, 32, 1024, 100, 0, True, 0.0),   # the largest K
     (1, 1, 37, 64, 5, 5, 0, False, 0.0),         # every column selected, less than one step of keys
+    (3, 11, 4001, 64, 65, 1, 3, False, 0.0),     # one column per row: row groups end inside heads, shares between them
+    (1, 8, 16384, 128, 128, 1, 4, False, 0.0),   # and with full tiles, as few groups as the row kernel takes
 ]
 
 
