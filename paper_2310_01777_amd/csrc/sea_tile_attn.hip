@@ -88,24 +88,30 @@ constexpr int kVRow = 64;    // halfwords per staged V row: no padding; the 64-b
 // bits).  MODE 2: "bucket" form for k^ = 1 -- every row selected exactly one column, rows are
 // grouped by that column, and a block takes 128 rows of one bucket against the r keys of its
 // column, so every visited tile is fully used no matter how scattered the choices are.
-template <int RLOG, int MODE, int NW = 4>
-__global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a) {
+template <int RLOG, int MODE, int NW = 4, int NS = 1>
+__global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kernel(TileArgs a) {
   // NW = waves per block: 4 (128 query rows) or 8 (256 rows sharing every staged key step, which
   // halves the bytes a head's keys and values travel from the L2s to LDS; two blocks per CU)
-  static_assert(NW == 4 || NW == 8, "four or eight waves per block");
+  // NS = sets of four waves that share the block's 128 rows: each takes every NS-th 64-key chunk of the list,
+  // and the partial results are merged through LDS at the end
+  static_assert(NW == 4 || NW == 8 || NS > 1, "four or eight waves per block");
+  static_assert(NS == 1 || NW == 4 * NS, "sets of four waves");
   static_assert(MODE != 2 || NW == 4, "bucket chunks are 128 rows");
-  constexpr int kRows = 32 * NW, kThreads = 64 * NW;
+  constexpr int kRows = 32 * NW / NS, kThreads = 64 * NW;
+  constexpr int kStep = kChunk * NS;         // keys per step
+  constexpr bool kTwo = 8 * kStep == 2 * kThreads;  // K and V pieces per thread and step: two or one
   constexpr bool DENSE = MODE == 1 || MODE == 2;  // no per-column bits to look up
   constexpr bool BUCKET = MODE == 2;
   // MODE 3: one bit per (row, key) in HBM ([N][T][KW] words); a lane reads its row's two words of a
   // step straight from memory one step ahead, nothing of the mask is parked in LDS
   constexpr bool STREAM = MODE == 3;
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kChunk * kKRow];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][kChunk * kVRow];
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kStep * kKRow];
+  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][kStep * kVRow];
   // selected-column bits of the 128 rows, (KW + 1) words per row (K <= 1024: at most 16.5 KB)
   extern __shared__ uint32_t Ms[];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, keep it scalar
+  const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, keep it scalar
+  const int wid = NS > 1 ? wall & 3 : wall, set = NS > 1 ? wall >> 2 : 0;
   const int ql = lane & 31, g = lane >> 5;
   const uint32_t wgs = (a.T + kRows - 1) / kRows;  // blocks per head
   int64_t head;
@@ -167,7 +173,7 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
   const uint32_t* krow = STREAM ? a.mbits + (head * a.T + tq) * a.KW : nullptr;
   uint32_t mw0 = 0u, mw1 = 0u, mn0 = 0u, mn1 = 0u;  // the row's words of this step and of the next
   auto fetch_words = [&](int32_t step_, uint32_t& w0, uint32_t& w1) {
-    const int32_t wi = 2 * step_;
+    const int32_t wi = 2 * (step_ * NS + set);
     w0 = (row_active && wi < a.KW) ? krow[wi] : 0u;
     w1 = (row_active && wi + 1 < a.KW) ? krow[wi + 1] : 0u;
   };
@@ -193,7 +199,7 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
   const int32_t my_jmax = a.causal ? min(t, len - 1) : len - 1;
   // compact keys this row may attend: those of the block's range whose position is <= my_jmax
   const int32_t my_ucount = min(ulim, compact_count(row_active ? my_jmax : -1, a.rlog, a.w));
-  const int32_t nsteps = (u_end_wg - ubase + kChunk - 1) / kChunk;
+  const int32_t nsteps = (u_end_wg - ubase + kStep - 1) / kStep;
 
   // staging roles: 16-byte part tid & 7 of the K and V rows (tid >> 3) and, with four waves,
   // (tid >> 3) + 32 of the step (eight waves cover the 64 rows in one go).  V is parked as it lies in memory; the product reads it through the LDS transpose read.
@@ -208,34 +214,34 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
   const bool linear = a.rlog <= 6;
   const uint32_t row_bytes = kHeadDim * 2, part_bytes = spart * 16;
   const uint32_t off_max = static_cast<uint32_t>(a.T - 1) * row_bytes + part_bytes;
-  const uint32_t off_step = linear ? static_cast<uint32_t>((kChunk >> a.rlog) * a.w) * row_bytes : 0u;
+  const uint32_t off_step = linear ? static_cast<uint32_t>((kStep >> a.rlog) * a.w) * row_bytes : 0u;
   uint32_t offa = static_cast<uint32_t>(pos_of(ubase + srow, a.rlog, a.w)) * row_bytes + part_bytes;
-  uint32_t offb = static_cast<uint32_t>(pos_of(ubase + srow + 32, a.rlog, a.w)) * row_bytes + part_bytes;
+  uint32_t offb = static_cast<uint32_t>(pos_of(ubase + srow + kThreads / 8, a.rlog, a.w)) * row_bytes + part_bytes;
   // The head's keys and values as buffer resources (base in scalar registers, 32-bit byte offset
   // per lane): a staging load then needs no 64-bit address arithmetic on the vector pipe.
   const uint32_t head_bytes = static_cast<uint32_t>(a.T) * row_bytes;
   const __amdgpu_buffer_rsrc_t Kres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Kh), 0, head_bytes, kBufferFlags);
   const __amdgpu_buffer_rsrc_t Vres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Vh), 0, head_bytes, kBufferFlags);
 #define SEA_SLOT_OFF(slot_, step_)                                                                   \
-  (static_cast<uint32_t>(pos_of(min(ubase + (step_) * kChunk + (slot_), a.U - 1), a.rlog, a.w)) * row_bytes + part_bytes)
+  (static_cast<uint32_t>(pos_of(min(ubase + (step_) * kStep + (slot_), a.U - 1), a.rlog, a.w)) * row_bytes + part_bytes)
 #define SEA_FETCH(step_)                                                                             \
   do {                                                                                               \
     if (!linear) {                                                                                   \
       offa = SEA_SLOT_OFF(srow, step_);                                                              \
-      if (NW == 4) offb = SEA_SLOT_OFF(srow + 32, step_);                                            \
+      if (kTwo) offb = SEA_SLOT_OFF(srow + kThreads / 8, step_);                                            \
     }                                                                                                \
     kreg0 = buffer_load16(Kres, min(offa, off_max));                                                 \
-    if (NW == 4) kreg1 = buffer_load16(Kres, min(offb, off_max));                                    \
+    if (kTwo) kreg1 = buffer_load16(Kres, min(offb, off_max));                                    \
     vreg0 = buffer_load16(Vres, min(offa, off_max));                                                 \
-    if (NW == 4) vreg1 = buffer_load16(Vres, min(offb, off_max));                                    \
+    if (kTwo) vreg1 = buffer_load16(Vres, min(offb, off_max));                                    \
     offa += off_step; offb += off_step;                                                              \
   } while (0)
 #define SEA_PARK(stage_)                                                                             \
   do {                                                                                               \
     *reinterpret_cast<uint4*>(&Ks[stage_][srow * kKRow + spart * 8]) = kreg0;                         \
-    if (NW == 4) *reinterpret_cast<uint4*>(&Ks[stage_][(srow + 32) * kKRow + spart * 8]) = kreg1;     \
+    if (kTwo) *reinterpret_cast<uint4*>(&Ks[stage_][(srow + kThreads / 8) * kKRow + spart * 8]) = kreg1;     \
     *reinterpret_cast<uint4*>(&Vs[stage_][srow * kVRow + vpart * 8]) = vreg0;                         \
-    if (NW == 4) *reinterpret_cast<uint4*>(&Vs[stage_][(srow + 32) * kVRow + vpart * 8]) = vreg1;     \
+    if (kTwo) *reinterpret_cast<uint4*>(&Vs[stage_][(srow + kThreads / 8) * kVRow + vpart * 8]) = vreg1;     \
   } while (0)
 
   floatx16 oacc[2];
@@ -269,12 +275,12 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
     constexpr bool kStepWord = !DENSE && !STREAM && RLOG >= 1;
     uint32_t wstep = 0u;
     if (kStepWord) {
-      wstep = mrow[((step * kChunk) >> (RLOG < 5 ? RLOG : a.rlog)) >> 5];
+      wstep = mrow[((step * kStep + kChunk * set) >> (RLOG < 5 ? RLOG : a.rlog)) >> 5];
       wstep = row_active ? wstep : 0u;
     }
 #pragma unroll
     for (int sc = 0; sc < 2; ++sc) {
-      const int32_t u0 = ubase + step * kChunk + 32 * sc;
+      const int32_t u0 = ubase + step * kStep + kChunk * set + 32 * sc;
       if (u0 >= u_end) break;  // wave-uniform: beyond what this wave's rows can see
       if (BUCKET && __ballot(row_active) == 0ull) break;  // a wave past the end of its bucket
       uint32_t bits = 0xffffffffu;
@@ -287,7 +293,7 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
         if (__ballot((bits & cmask) != 0u) == 0ull) continue;  // no row of the wave uses it
       }
       // S^T sub-chunk = K (32 keys x 64) . Q_tile^T
-      const uint16_t* Kr = &Ks[stage][(32 * sc + ql) * kKRow + 8 * g];
+      const uint16_t* Kr = &Ks[stage][(kChunk * set + 32 * sc + ql) * kKRow + 8 * g];
       floatx16 sv;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sv[i] = 0.f;
@@ -352,7 +358,7 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
       auto request_v = [&]() {
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-          const uint16_t* Vr = &Vs[stage][(32 * sc + 4 * g + ((ql & 15) >> 2)) * kVRow +
+          const uint16_t* Vr = &Vs[stage][(kChunk * set + 32 * sc + 4 * g + ((ql & 15) >> 2)) * kVRow +
                                           32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
 #pragma unroll
           for (int c2 = 0; c2 < 2; ++c2) {
@@ -416,6 +422,35 @@ __global__ __launch_bounds__(64 * NW, 16 / NW) void tile_attn_kernel(TileArgs a)
 #undef SEA_FETCH
 #undef SEA_SLOT_OFF
 #undef SEA_PARK
+  if constexpr (NS > 1) {
+    // log-sum-exp merge of the sets' partial results, halving the number of sets per round; the keys and
+    // values of the last step are no longer needed (the loop ended with a barrier)
+    static_assert(NS / 2 * 256 * 34 * 4 <= static_cast<int>(sizeof(Ks)), "partial results fit the keys' place");
+    float* const part = reinterpret_cast<float*>(&Ks[0][0]) + 64 * wid + lane;
+    float m_own = m_thr > 0.f ? m_ref : -INFINITY;
+#pragma unroll
+    for (int half = NS / 2; half >= 1; half >>= 1) {
+      float* const p = part + (set & (half - 1)) * 256 * 34;
+      if (set >= half && set < 2 * half) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) p[256 * i] = oacc[i >> 4][i & 15];
+        p[256 * 32] = l_run;
+        p[256 * 33] = m_own;
+      }
+      __syncthreads();
+      if (set < half) {
+        const float m_other = p[256 * 33], m_new = fmaxf(m_own, m_other);
+        const float f0 = m_own == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_own - m_new);
+        const float f1 = m_other == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_other - m_new);
+        l_run = l_run * f0 + p[256 * 32] * f1;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) oacc[i >> 4][i & 15] = oacc[i >> 4][i & 15] * f0 + p[256 * i] * f1;
+        m_own = m_new;
+      }
+      if (half > 1) __syncthreads();
+    }
+    if (set > 0) return;
+  }
   l_run = half_sum(l_run);
   if (t >= 0 && t < a.T) {
     const float inv = (row_active && l_run > 0.f) ? 1.f / l_run : 0.f;
@@ -667,6 +702,21 @@ static bool wide_blocks(const Shape& s) {
   return static_cast<int64_t>(s.N) * ((s.T + 255) / 256) >= SEA_NW8_MIN_BLOCKS;
 }
 
+// Sets of four waves per block: a launch that leaves the chip room takes as long as its longest list does, so
+// two or four sets share the rows of a block and walk the list in parallel (a set takes at least two of its
+// 64-key chunks; the merge costs about one).  Two sets while all blocks fit the chip at once (two per CU, a
+// little over when the lists are long), four with one block per CU, or two where the last rows of a causal
+// list have many times the keys of the first.  Per-key bits (MODE 3) cost more per step than the merge does,
+// so there two sets still pay at four blocks per CU.  Whole forward, K = 128, k^ = 64, H = 12, one, two and
+// four sets: T = 2048, B = 1 (192 blocks) 59 / 49 / 46 us, B = 3 (576) 68 / 62 / 75, B = 4 (768) 76 / 77 / 87;
+// T = 512, B = 4 (192) 32 / 30 / 31; H = 8, T = 8192 (512) 172 / 140 / 127; per-key bits, T = 2048, B = 1
+// 126 / 102 / 98, B = 4 235 / 228 / 242, T = 1024, B = 8 (768) 178 / 180 / 190.
+static int32_t wave_sets(uint32_t blocks, int32_t U, bool causal, bool key_bits) {
+  if (U >= 1024 && blocks <= (causal && U >= 4096 ? 512u : 256u)) return 4;
+  if (U >= 512 && blocks <= (U < 1024 ? 384u : (key_bits && U >= 2048 ? 1024u : 576u))) return 2;
+  return 1;
+}
+
 bool tile_attn_supported(const Shape& s, sea_dtype dt, int32_t* rlog_out) {
   if (dt != SEA_BF16 || s.T % s.K != 0) return false;
   if (s.geometry != 0) return false;  // a row's own column ranges: no structure shared between rows
@@ -795,16 +845,23 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
   a.rlog = rlog; a.w = w; a.causal = s.causal;
   a.group_heads = group_heads_for(s.N, U);
   a.c = s.scale * kLog2e;
-  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128)), block(256);
   const size_t shm = static_cast<size_t>(128) * (a.KW + 1) * sizeof(uint32_t);
+  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128));
+  const int32_t sets = wave_sets(grid.x, U, s.causal, false);
+#define SEA_TILE(R_)                                                                                             \
+  if (sets == 4) hipLaunchKernelGGL((tile_attn_kernel<R_, 0, 16, 4>), grid, dim3(1024), shm, st, a);             \
+  else if (sets == 2) hipLaunchKernelGGL((tile_attn_kernel<R_, 0, 8, 2>), grid, dim3(512), shm, st, a);          \
+  else hipLaunchKernelGGL((tile_attn_kernel<R_, 0>), grid, dim3(256), shm, st, a);                               \
+  break
   switch (rlog) {
-    case 0: hipLaunchKernelGGL((tile_attn_kernel<0, 0>), grid, block, shm, st, a); break;
-    case 1: hipLaunchKernelGGL((tile_attn_kernel<1, 0>), grid, block, shm, st, a); break;
-    case 2: hipLaunchKernelGGL((tile_attn_kernel<2, 0>), grid, block, shm, st, a); break;
-    case 3: hipLaunchKernelGGL((tile_attn_kernel<3, 0>), grid, block, shm, st, a); break;
-    case 4: hipLaunchKernelGGL((tile_attn_kernel<4, 0>), grid, block, shm, st, a); break;
-    default: hipLaunchKernelGGL((tile_attn_kernel<5, 0>), grid, block, shm, st, a); break;
+    case 0: SEA_TILE(0);
+    case 1: SEA_TILE(1);
+    case 2: SEA_TILE(2);
+    case 3: SEA_TILE(3);
+    case 4: SEA_TILE(4);
+    default: SEA_TILE(5);
   }
+#undef SEA_TILE
   return hipGetLastError();
 }
 
@@ -1125,8 +1182,11 @@ hipError_t launch_tile_attn_keybits(const Shape& s, const uint16_t* Q, const uin
   a.N = s.N; a.H = s.H; a.T = s.T; a.U = s.T; a.KW = (s.T + 31) / 32; a.rlog = 0; a.w = 1; a.causal = s.causal;
   a.group_heads = group_heads_for(s.N, s.T);
   a.c = s.scale * kLog2e;
-  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128)), block(256);
-  hipLaunchKernelGGL((tile_attn_kernel<0, 3>), grid, block, 0, st, a);
+  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128));
+  const int32_t sets = wave_sets(grid.x, s.T, s.causal, true);
+  if (sets == 4) hipLaunchKernelGGL((tile_attn_kernel<0, 3, 16, 4>), grid, dim3(1024), 0, st, a);
+  else if (sets == 2) hipLaunchKernelGGL((tile_attn_kernel<0, 3, 8, 2>), grid, dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((tile_attn_kernel<0, 3>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Column-selected masks whose columns have any width (K does not divide T, or a column emits a number
 of keys that is no power of two): the estimator's key kernel for any width and the tiled attention (bf16: with
 the mask taken through the matrix product), at the widths where column groups, column slots, tiles and
-list ends change, against the oracle."""
+list ends change, and the aligned tiled attention where sets of waves share a list, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -34,12 +34,23 @@ CASES = [
     (1, 8, 16384, 128, 128, 1, 4, False, 0.0),   # and with full tiles, as few groups as the row kernel takes
 ]
 
+# aligned columns, few rows: the key list is shared by two or four sets of waves whose results are merged
+ALIGNED_CASES = [
+    (1, 2, 1024, 64, 256, 60, 0, True, 0.0),     # the shortest list for four sets; early rows give three of them nothing
+    (2, 1, 2048, 64, 1024, 100, 100, True, 0.3), # one key per column
+    (2, 1, 1536, 64, 512, 50, 100, False, 0.3),  # two of three
+    (1, 3, 1000, 64, 125, 30, 0, True, 0.0),     # two sets, a list that ends inside a chunk
+    (3, 4, 640, 64, 128, 20, 80, False, 0.5),    # the shortest list for two sets, sequences of half a tile
+    (1, 1, 4224, 64, 128, 16, 256, True, 0.0),   # 16 of 33
+    (2, 2, 4096, 64, 64, 9, 0, True, 0.3),       # one column per chunk
+]
+
 
 F32_CASES = [CASES[0], CASES[3], CASES[5], CASES[6], CASES[8], CASES[10], (1, 1, 33, 32, 7, 3, 0, True, 0.0),
              (1, 2, 700, 64, 300, 40, 0, True, 0.0), (2, 1, 290, 96, 64, 9, 0, False, 0.3)]
 
 
-@pytest.mark.parametrize("dtype,case", [("bf16", c) for c in CASES] + [("f32", c) for c in F32_CASES],
+@pytest.mark.parametrize("dtype,case", [("bf16", c) for c in CASES + ALIGNED_CASES] + [("f32", c) for c in F32_CASES],
                          ids=lambda v: v if isinstance(v, str) else "_".join(str(x) for x in v))
 def test_any_column_width(dtype, case):
     from paper_2310_01777_amd import binding as sea
@@ -49,7 +60,7 @@ def test_any_column_width(dtype, case):
     seq = None if x["seq_len"] is None else x["seq_len"].clone()
     if seq is not None:
         seq[-1] = 0 if B > 1 else T // 2         # a sequence without keys
-        for k in "KV":                           # what lies behind a sequence's end is never read
+        for k in "KV" if case not in ALIGNED_CASES else "":  # what lies behind a sequence's end is never read
             for b in range(B):
                 x[k][b, :, int(seq[b]):] = float("nan")
     d = {k: x[k].cuda() for k in "QKVW"}
