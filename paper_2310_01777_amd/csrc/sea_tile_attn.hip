@@ -425,28 +425,15 @@ __global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kerne
   if constexpr (NS > 1) {
     // log-sum-exp merge of the sets' partial results, halving the number of sets per round; the keys and
     // values of the last step are no longer needed (the loop ended with a barrier)
-    static_assert(NS / 2 * 256 * 34 * 4 <= static_cast<int>(sizeof(Ks)), "partial results fit the keys' place");
+    static_assert(NS / 2 * 256 * kPartFloats * 4 <= static_cast<int>(sizeof(Ks)), "partial results fit the keys' place");
     float* const part = reinterpret_cast<float*>(&Ks[0][0]) + 64 * wid + lane;
     float m_own = m_thr > 0.f ? m_ref : -INFINITY;
 #pragma unroll
     for (int half = NS / 2; half >= 1; half >>= 1) {
-      float* const p = part + (set & (half - 1)) * 256 * 34;
-      if (set >= half && set < 2 * half) {
-#pragma unroll
-        for (int i = 0; i < 32; ++i) p[256 * i] = oacc[i >> 4][i & 15];
-        p[256 * 32] = l_run;
-        p[256 * 33] = m_own;
-      }
+      float* const p = part + (set & (half - 1)) * 256 * kPartFloats;
+      if (set >= half && set < 2 * half) store_part(p, oacc, l_run, m_own);
       __syncthreads();
-      if (set < half) {
-        const float m_other = p[256 * 33], m_new = fmaxf(m_own, m_other);
-        const float f0 = m_own == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_own - m_new);
-        const float f1 = m_other == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_other - m_new);
-        l_run = l_run * f0 + p[256 * 32] * f1;
-#pragma unroll
-        for (int i = 0; i < 32; ++i) oacc[i >> 4][i & 15] = oacc[i >> 4][i & 15] * f0 + p[256 * i] * f1;
-        m_own = m_new;
-      }
+      if (set < half) merge_part(p, oacc, l_run, m_own);
       if (half > 1) __syncthreads();
     }
     if (set > 0) return;
