@@ -323,11 +323,11 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
     float* const p1 = reinterpret_cast<float*>(&Ks[0][0]) + 64 * wid + lane;
     float* const p2 = reinterpret_cast<float*>(&Vs[0][0]) + 64 * wid + lane;
     float m_own = m_thr > 0.f ? m_ref : -INFINITY;
-    if (set > 0) store_part(set == 1 ? p1 : p2, oacc, l_run, m_own);
+    if (set > 0) store_part<256>(set == 1 ? p1 : p2, oacc, l_run, m_own);
     __syncthreads();
     if (set > 0) return;
-    merge_part(p1, oacc, l_run, m_own);
-    merge_part(p2, oacc, l_run, m_own);
+    merge_part<256>(p1, oacc, l_run, m_own);
+    merge_part<256>(p2, oacc, l_run, m_own);
   }
   l_run = half_sum(l_run);
   if (t < a.T) {

@@ -44,22 +44,24 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
 // heads whose keys and values (2 x U x 128 B each) share the L2s at one time
 int32_t group_heads_for(int32_t N, int64_t U);
 
-// Partial result of a set of waves (O^T accumulators, row sum, reference maximum or -inf) in LDS, 256 lanes a
+// Partial result of a set of waves (O^T accumulators, row sum, reference maximum or -inf) in LDS, LANES lanes a
 // set, and its log-sum-exp merge into the registers of the set that goes on.
 constexpr int kPartFloats = 34;
+template <int LANES>
 __device__ __forceinline__ void store_part(float* p, const floatx16 (&oacc)[2], float l, float m) {
 #pragma unroll
-  for (int i = 0; i < 32; ++i) p[256 * i] = oacc[i >> 4][i & 15];
-  p[256 * 32] = l;
-  p[256 * 33] = m;
+  for (int i = 0; i < 32; ++i) p[LANES * i] = oacc[i >> 4][i & 15];
+  p[LANES * 32] = l;
+  p[LANES * 33] = m;
 }
+template <int LANES>
 __device__ __forceinline__ void merge_part(const float* p, floatx16 (&oacc)[2], float& l, float& m) {
-  const float m_other = p[256 * 33], m_new = fmaxf(m, m_other);
+  const float m_other = p[LANES * 33], m_new = fmaxf(m, m_other);
   const float f0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
   const float f1 = m_other == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_other - m_new);
-  l = l * f0 + p[256 * 32] * f1;
+  l = l * f0 + p[LANES * 32] * f1;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) oacc[i >> 4][i & 15] = oacc[i >> 4][i & 15] * f0 + p[256 * i] * f1;
+  for (int i = 0; i < 32; ++i) oacc[i >> 4][i & 15] = oacc[i >> 4][i & 15] * f0 + p[LANES * i] * f1;
   m = m_new;
 }
 

@@ -72,15 +72,14 @@ __device__ __forceinline__ int32_t compact_count(int32_t jmax, int32_t rlog, int
   return col * r + inside;
 }
 
-constexpr int kChunk = 64;   // keys staged in LDS per step (two 32-key MFMA sub-chunks)
 constexpr int kKRow = 72;    // halfwords per staged K row: 128 B + 16 B pad, conflict-free b128 reads
 constexpr int kVRow = 64;    // halfwords per staged V row: no padding; the 64-byte halves of rows 2, 3 (mod 4)
                              // are exchanged, which makes the four rows of a transpose read hit distinct banks
 
-// Block = 4 waves = 128 consecutive query rows of one head (32 per wave).  The block walks the
-// compact key list in steps of 64 keys; each step's K and V rows are fetched once with full-line
-// 128-bit loads, parked in LDS (K as rows, V transposed; double buffered, one barrier per step)
-// and read by all four waves as MFMA fragments.
+// Block = 4 waves = 128 consecutive query rows of one head (32 per wave); other splits below.  The block
+// walks the compact key list in steps of 64 keys (two 32-key sub-chunks); each step's K and V rows are fetched
+// once with full-line 128-bit loads, parked in LDS (K as rows, V transposed; double buffered, one barrier per
+// step) and read by all four waves as MFMA fragments.
 // RLOG = log2(keys per column) for 1..16 keys per column, 5 for 32 or more (then a 32-key
 // sub-chunk lies inside one column and the actual shift is a.rlog).
 //
@@ -88,18 +87,18 @@ constexpr int kVRow = 64;    // halfwords per staged V row: no padding; the 64-b
 // bits).  MODE 2: "bucket" form for k^ = 1 -- every row selected exactly one column, rows are
 // grouped by that column, and a block takes 128 rows of one bucket against the r keys of its
 // column, so every visited tile is fully used no matter how scattered the choices are.
-template <int RLOG, int MODE, int NW = 4, int NS = 1>
-__global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kernel(TileArgs a) {
-  // NW = waves per block: 4 (128 query rows) or 8 (256 rows sharing every staged key step, which
-  // halves the bytes a head's keys and values travel from the L2s to LDS; two blocks per CU)
-  // NS = sets of four waves that share the block's 128 rows: each takes every NS-th 64-key chunk of the list,
-  // and the partial results are merged through LDS at the end
-  static_assert(NW == 4 || NW == 8 || NS > 1, "four or eight waves per block");
-  static_assert(NS == 1 || NW == 4 * NS, "sets of four waves");
-  static_assert(MODE != 2 || NW == 4, "bucket chunks are 128 rows");
-  constexpr int kRows = 32 * NW / NS, kThreads = 64 * NW;
-  constexpr int kStep = kChunk * NS;         // keys per step
+template <int RLOG, int MODE, int RW = 4, int NS = 1, int SC = 2>
+__global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_kernel(TileArgs a) {
+  // RW = waves side by side: 32 RW query rows share every staged key step (8 instead of 4 halve the bytes a
+  // head's keys and values travel from the L2s to LDS; two blocks per CU).
+  // NS = sets of RW waves that share the block's rows: each takes every NS-th SC sub-chunks of the list, and
+  // the partial results are merged through LDS at the end.
+  static_assert(MODE != 2 || (RW == 4 && NS == 1), "bucket chunks are 128 rows");
+  static_assert(NS > 1 || SC == 2, "one set takes whole chunks");
+  constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS;
+  constexpr int kStep = 32 * SC * NS;        // keys per step
   constexpr bool kTwo = 8 * kStep == 2 * kThreads;  // K and V pieces per thread and step: two or one
+  static_assert(kTwo || 8 * kStep == kThreads, "one or two pieces");
   constexpr bool DENSE = MODE == 1 || MODE == 2;  // no per-column bits to look up
   constexpr bool BUCKET = MODE == 2;
   // MODE 3: one bit per (row, key) in HBM ([N][T][KW] words); a lane reads its row's two words of a
@@ -111,7 +110,7 @@ __global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kerne
   extern __shared__ uint32_t Ms[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, keep it scalar
-  const int wid = NS > 1 ? wall & 3 : wall, set = NS > 1 ? wall >> 2 : 0;
+  const int wid = NS > 1 ? wall % RW : wall, set = NS > 1 ? wall / RW : 0;
   const int ql = lane & 31, g = lane >> 5;
   const uint32_t wgs = (a.T + kRows - 1) / kRows;  // blocks per head
   int64_t head;
@@ -173,9 +172,9 @@ __global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kerne
   const uint32_t* krow = STREAM ? a.mbits + (head * a.T + tq) * a.KW : nullptr;
   uint32_t mw0 = 0u, mw1 = 0u, mn0 = 0u, mn1 = 0u;  // the row's words of this step and of the next
   auto fetch_words = [&](int32_t step_, uint32_t& w0, uint32_t& w1) {
-    const int32_t wi = 2 * (step_ * NS + set);
+    const int32_t wi = SC * (step_ * NS + set);
     w0 = (row_active && wi < a.KW) ? krow[wi] : 0u;
-    w1 = (row_active && wi + 1 < a.KW) ? krow[wi + 1] : 0u;
+    w1 = (SC == 2 && row_active && wi + 1 < a.KW) ? krow[wi + 1] : 0u;
   };
 
   // keys the block / this wave can see: position <= min(last row, len - 1) when causal
@@ -275,12 +274,12 @@ __global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kerne
     constexpr bool kStepWord = !DENSE && !STREAM && RLOG >= 1;
     uint32_t wstep = 0u;
     if (kStepWord) {
-      wstep = mrow[((step * kStep + kChunk * set) >> (RLOG < 5 ? RLOG : a.rlog)) >> 5];
+      wstep = mrow[((step * kStep + 32 * SC * set) >> (RLOG < 5 ? RLOG : a.rlog)) >> 5];
       wstep = row_active ? wstep : 0u;
     }
 #pragma unroll
-    for (int sc = 0; sc < 2; ++sc) {
-      const int32_t u0 = ubase + step * kStep + kChunk * set + 32 * sc;
+    for (int sc = 0; sc < SC; ++sc) {
+      const int32_t u0 = ubase + step * kStep + 32 * (SC * set + sc);
       if (u0 >= u_end) break;  // wave-uniform: beyond what this wave's rows can see
       if (BUCKET && __ballot(row_active) == 0ull) break;  // a wave past the end of its bucket
       uint32_t bits = 0xffffffffu;
@@ -293,7 +292,7 @@ __global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kerne
         if (__ballot((bits & cmask) != 0u) == 0ull) continue;  // no row of the wave uses it
       }
       // S^T sub-chunk = K (32 keys x 64) . Q_tile^T
-      const uint16_t* Kr = &Ks[stage][(kChunk * set + 32 * sc + ql) * kKRow + 8 * g];
+      const uint16_t* Kr = &Ks[stage][(32 * (SC * set + sc) + ql) * kKRow + 8 * g];
       floatx16 sv;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sv[i] = 0.f;
@@ -358,7 +357,7 @@ __global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kerne
       auto request_v = [&]() {
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-          const uint16_t* Vr = &Vs[stage][(kChunk * set + 32 * sc + 4 * g + ((ql & 15) >> 2)) * kVRow +
+          const uint16_t* Vr = &Vs[stage][(32 * (SC * set + sc) + 4 * g + ((ql & 15) >> 2)) * kVRow +
                                           32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
 #pragma unroll
           for (int c2 = 0; c2 < 2; ++c2) {
@@ -425,15 +424,15 @@ __global__ __launch_bounds__(64 * NW, NS > 1 ? 4 : 16 / NW) void tile_attn_kerne
   if constexpr (NS > 1) {
     // log-sum-exp merge of the sets' partial results, halving the number of sets per round; the keys and
     // values of the last step are no longer needed (the loop ended with a barrier)
-    static_assert(NS / 2 * 256 * kPartFloats * 4 <= static_cast<int>(sizeof(Ks)), "partial results fit the keys' place");
+    static_assert(NS / 2 * 64 * RW * kPartFloats * 4 <= static_cast<int>(sizeof(Ks)), "partial results fit the keys' place");
     float* const part = reinterpret_cast<float*>(&Ks[0][0]) + 64 * wid + lane;
     float m_own = m_thr > 0.f ? m_ref : -INFINITY;
 #pragma unroll
     for (int half = NS / 2; half >= 1; half >>= 1) {
-      float* const p = part + (set & (half - 1)) * 256 * kPartFloats;
-      if (set >= half && set < 2 * half) store_part(p, oacc, l_run, m_own);
+      float* const p = part + (set & (half - 1)) * 64 * RW * kPartFloats;
+      if (set >= half && set < 2 * half) store_part<64 * RW>(p, oacc, l_run, m_own);
       __syncthreads();
-      if (set < half) merge_part(p, oacc, l_run, m_own);
+      if (set < half) merge_part<64 * RW>(p, oacc, l_run, m_own);
       if (half > 1) __syncthreads();
     }
     if (set > 0) return;
@@ -689,19 +688,32 @@ static bool wide_blocks(const Shape& s) {
   return static_cast<int64_t>(s.N) * ((s.T + 255) / 256) >= SEA_NW8_MIN_BLOCKS;
 }
 
-// Sets of four waves per block: a launch that leaves the chip room takes as long as its longest list does, so
-// two or four sets share the rows of a block and walk the list in parallel (a set takes at least two of its
-// 64-key chunks; the merge costs about one).  Two sets while all blocks fit the chip at once (two per CU, a
-// little over when the lists are long), four with one block per CU, or two where the last rows of a causal
-// list have many times the keys of the first.  Per-key bits (MODE 3) cost more per step than the merge does,
-// so there two sets still pay at four blocks per CU.  Whole forward, K = 128, k^ = 64, H = 12, one, two and
-// four sets: T = 2048, B = 1 (192 blocks) 59 / 49 / 46 us, B = 3 (576) 68 / 62 / 75, B = 4 (768) 76 / 77 / 87;
-// T = 512, B = 4 (192) 32 / 30 / 31; H = 8, T = 8192 (512) 172 / 140 / 127; per-key bits, T = 2048, B = 1
-// 126 / 102 / 98, B = 4 235 / 228 / 242, T = 1024, B = 8 (768) 178 / 180 / 190.
-static int32_t wave_sets(uint32_t blocks, int32_t U, bool causal, bool key_bits) {
-  if (U >= 1024 && blocks <= (causal && U >= 4096 ? 512u : 256u)) return 4;
-  if (U >= 512 && blocks <= (U < 1024 ? 384u : (key_bits && U >= 2048 ? 1024u : 576u))) return 2;
-  return 1;
+// How the waves of a block are split.  A launch that leaves the chip room takes as long as its longest list
+// does, so sets of waves share the rows of a block and walk the list in parallel (the merge costs about one
+// 64-key chunk).  kPairs: 64 rows, four sets of two waves, while the 128-row blocks number at most one per CU
+// (half the rows halve a CU's longest work as well); per-key bits (MODE 3) cost more per step, so there a
+// little longer.  kFour, kTwo: 128 rows, four or two sets of four waves, up to what is resident at once (kFour
+// where the last rows of a causal list have many times the keys of the first; per-key bits again longer).
+// Whole forward, K = 128, k^ = 64, H = 12, causal, us as kOne / kTwo / kFour / kPairs: T = 512, B = 1 (48 blocks)
+// 30 / 29 / 29 / 25, B = 4 (192) 32 / 31 / 32 / 28; T = 1024, B = 4 (384) 43 / 38 / 41 / 39; T = 2048, B = 1
+// (192) 60 / 50 / 46 / 40, B = 3 (576) 67 / 60 / 72 / 64, B = 4 (768) 73 / 73 / 84 / 77; T = 4096, B = 1 (384)
+// 100 / 79 / 69 / 72; per-key bits, T = 2048, B = 1 125 / 102 / 99 / 88, B = 2 153 / 131 / 127 / 122, B = 4
+// 220 / 214 / 228 / 219; bidirectional, T = 1024, B = 4 52 / 49 / 55 / 48, T = 512, B = 8 42 / 43 / 50 / 42.
+enum WaveSplit { kOne, kTwo, kFour, kPairs };
+static WaveSplit wave_split(const Shape& s, int32_t U, bool key_bits) {
+  const int64_t blocks = static_cast<int64_t>(s.N) * ((s.T + 127) / 128);
+  if (U >= 256 && blocks <= (key_bits ? 384 : 256)) return kPairs;
+  if (U >= 4096 && blocks <= 512 && s.causal) return kFour;
+  if (U >= 1024 && blocks <= (key_bits && U >= 2048 ? 1024 : 576)) return kTwo;
+  return kOne;
+}
+
+template <int RLOG, int MODE, int RW, int NS, int SC>
+static void launch_tile(const Shape& s, const TileArgs& a, hipStream_t st) {
+  constexpr int kRows = 32 * RW;
+  const size_t shm = MODE == 0 ? static_cast<size_t>(kRows) * (a.KW + 1) * sizeof(uint32_t) : 0;
+  hipLaunchKernelGGL((tile_attn_kernel<RLOG, MODE, RW, NS, SC>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
+                     dim3(64 * RW * NS), shm, st, a);
 }
 
 bool tile_attn_supported(const Shape& s, sea_dtype dt, int32_t* rlog_out) {
@@ -832,13 +844,14 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
   a.rlog = rlog; a.w = w; a.causal = s.causal;
   a.group_heads = group_heads_for(s.N, U);
   a.c = s.scale * kLog2e;
-  const size_t shm = static_cast<size_t>(128) * (a.KW + 1) * sizeof(uint32_t);
-  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128));
-  const int32_t sets = wave_sets(grid.x, U, s.causal, false);
-#define SEA_TILE(R_)                                                                                             \
-  if (sets == 4) hipLaunchKernelGGL((tile_attn_kernel<R_, 0, 16, 4>), grid, dim3(1024), shm, st, a);             \
-  else if (sets == 2) hipLaunchKernelGGL((tile_attn_kernel<R_, 0, 8, 2>), grid, dim3(512), shm, st, a);          \
-  else hipLaunchKernelGGL((tile_attn_kernel<R_, 0>), grid, dim3(256), shm, st, a);                               \
+  const WaveSplit split = wave_split(s, U, false);
+#define SEA_TILE(R_)                                                                        \
+  switch (split) {                                                                          \
+    case kPairs: launch_tile<R_, 0, 2, 4, 1>(s, a, st); break;                              \
+    case kFour: launch_tile<R_, 0, 4, 4, 2>(s, a, st); break;                               \
+    case kTwo: launch_tile<R_, 0, 4, 2, 2>(s, a, st); break;                                \
+    default: launch_tile<R_, 0, 4, 1, 2>(s, a, st); break;                                  \
+  }                                                                                         \
   break
   switch (rlog) {
     case 0: SEA_TILE(0);
@@ -1169,11 +1182,12 @@ hipError_t launch_tile_attn_keybits(const Shape& s, const uint16_t* Q, const uin
   a.N = s.N; a.H = s.H; a.T = s.T; a.U = s.T; a.KW = (s.T + 31) / 32; a.rlog = 0; a.w = 1; a.causal = s.causal;
   a.group_heads = group_heads_for(s.N, s.T);
   a.c = s.scale * kLog2e;
-  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128));
-  const int32_t sets = wave_sets(grid.x, s.T, s.causal, true);
-  if (sets == 4) hipLaunchKernelGGL((tile_attn_kernel<0, 3, 16, 4>), grid, dim3(1024), 0, st, a);
-  else if (sets == 2) hipLaunchKernelGGL((tile_attn_kernel<0, 3, 8, 2>), grid, dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((tile_attn_kernel<0, 3>), grid, dim3(256), 0, st, a);
+  switch (wave_split(s, s.T, true)) {
+    case kPairs: launch_tile<0, 3, 2, 4, 1>(s, a, st); break;
+    case kFour: launch_tile<0, 3, 4, 4, 2>(s, a, st); break;
+    case kTwo: launch_tile<0, 3, 4, 2, 2>(s, a, st); break;
+    default: launch_tile<0, 3, 4, 1, 2>(s, a, st); break;
+  }
   return hipGetLastError();
 }
 
@@ -1191,13 +1205,8 @@ hipError_t launch_dense_attn(const Shape& s, sea_dtype dt, const void* Q, const 
   a.N = s.N; a.H = s.H; a.T = s.T; a.U = s.T; a.KW = 0; a.rlog = 0; a.w = 1;
   a.causal = s.causal; a.c = s.scale * kLog2e;
   a.group_heads = group_heads_for(s.N, s.T);
-  if (wide_blocks(s)) {
-    const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 255) / 256)), block(512);
-    hipLaunchKernelGGL((tile_attn_kernel<0, 1, 8>), grid, block, 0, st, a);
-    return hipGetLastError();
-  }
-  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128)), block(256);
-  hipLaunchKernelGGL((tile_attn_kernel<0, 1>), grid, block, 0, st, a);
+  if (wide_blocks(s)) launch_tile<0, 1, 8, 1, 2>(s, a, st);
+  else launch_tile<0, 1, 4, 1, 2>(s, a, st);
   return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Column-selected masks whose columns have any width (K does not divide T, or a column emits a number
 of keys that is no power of two): the estimator's key kernel for any width and the tiled attention (bf16: with
 the mask taken through the matrix product), at the widths where column groups, column slots, tiles and
-list ends change, and the aligned tiled attention where sets of waves share a list, against the oracle."""
+list ends change, and the aligned tiled attention at the sizes where its waves are split differently, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -37,15 +37,22 @@ CASES = [
     (1, 8, 16384, 128, 128, 1, 4, False, 0.0),   # and with full tiles, as few groups as the row kernel takes
 ]
 
-# aligned columns, few rows: the key list is shared by two or four sets of waves whose results are merged
+# aligned columns: how waves share the key list depends on the number of row blocks and the list's length
 ALIGNED_CASES = [
-    (1, 2, 1024, 64, 256, 60, 0, True, 0.0),     # the shortest list for four sets; early rows give three of them nothing
+    (1, 2, 1024, 64, 256, 60, 0, True, 0.0),     # four sets of two waves; early rows give three of them nothing
     (2, 1, 2048, 64, 1024, 100, 100, True, 0.3), # one key per column
     (2, 1, 1536, 64, 512, 50, 100, False, 0.3),  # two of three
-    (1, 3, 1000, 64, 125, 30, 0, True, 0.0),     # two sets, a list that ends inside a chunk
-    (3, 4, 640, 64, 128, 20, 80, False, 0.5),    # the shortest list for two sets, sequences of half a tile
+    (1, 3, 1000, 64, 125, 30, 0, True, 0.0),     # a list that ends inside a chunk
+    (3, 4, 640, 64, 64, 20, 80, False, 0.5),     # the shortest list for sets, sequences of half a tile
     (1, 1, 4224, 64, 128, 16, 256, True, 0.0),   # 16 of 33
     (2, 2, 4096, 64, 64, 9, 0, True, 0.3),       # one column per chunk
+    (2, 17, 1000, 64, 250, 60, 0, True, 0.3),    # (too short for) two sets of four waves
+    (2, 17, 1024, 64, 256, 60, 0, True, 0.3),    # two sets of four waves
+    (1, 9, 4096, 64, 128, 16, 0, True, 0.0),     # four
+    (1, 2, 128, 64, 128, 31, 0, True, 0.0),      # one set, one key per column
+    (2, 1, 200, 64, 100, 25, 0, False, 0.3),     # two
+    (1, 2, 240, 64, 60, 20, 0, True, 0.0),       # four
+    (1, 1, 192, 64, 3, 2, 0, True, 0.0),         # 64
 ]
 
 
