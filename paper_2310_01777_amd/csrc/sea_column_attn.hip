@@ -5,7 +5,7 @@
 //
 // The keys a head can use form one compact list, ascending in position: all T keys when whole
 // columns are emitted, else r keys of each of the K columns.  A block of 4 waves takes 128 query
-// rows and walks it in 64-key steps staged through LDS, as the power-of-two kernel does.  With
+// rows (other splits below) and walks it in 64-key steps staged through LDS, as the power-of-two kernel does.  With
 // columns of any width a lane's score registers belong to columns that change from step to step, so
 // bit tests per register would cost more than the softmax.  The mask goes through the matrix
 // product instead: the contraction is extended by NX slots, one per column of the 32-key sub-chunk.
@@ -23,8 +23,8 @@
 // products per 32-key sub-chunk and wave; three waves per SIMD: held to four the compiler spills 14
 // registers and the kernel is 15 % slower).  Measured on the layer B = 8, H = 32, T = 2000 (padded by
 // 0-25 %), K = 256, k^ = 64: 0.29 ms; the per-row gather kernel that ran before took 2.71 ms and its
-// key lists another 0.57 ms to write.  Small launches take as long as their longest list: there three sets of
-// waves share it (see the launch).
+// key lists another 0.57 ms to write.  Small launches take as long as their longest list: there three or six sets
+// of waves share it.
 #include "sea_columns.h"
 #include "sea_internal.h"
 #include "sea_tile.h"
@@ -32,7 +32,6 @@
 namespace sea {
 namespace {
 
-constexpr int kChunk = 64;  // keys staged per step (two 32-key sub-chunks)
 constexpr int kVRow = 64;   // halfwords per staged V row; halves of rows 2, 3 (mod 4) exchanged
 
 struct ColumnArgs {
@@ -46,34 +45,36 @@ struct ColumnArgs {
   ColumnList g;
   // column of list entry u = floor(u A / D); 32 entries further: q32 more, remainder r32 more
   int32_t A, D, q32, r32;
-  int32_t q96, r96, q192, r192;  // and 96, 192 entries further
+  int32_t qh, rh, qs, rs;  // and half a step, a step further
   int32_t causal, group_heads;
   float c;           // scale * log2(e)
 };
 
 // NX = contraction slots for the mask: 8 (at least 5 keys per column: a 32-key sub-chunk touches at
 // most 8 columns), 16 (3 or 4 keys) or 32 (1 or 2 keys).
-// NS = sets of four waves that share the block's rows, each with every NS-th 64-key chunk of the list (1 or 3).
-template <int NX, int NS>
-__global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) {
-  static_assert(NS == 1 || NS == 3, "one or three sets");
-  constexpr int kStep = kChunk * NS, kThreads = 256 * NS;
+// RW waves side by side take 32 rows each; NS sets of them share the rows, each with every NS-th SC sub-chunks of
+// the list (see the launch).
+template <int NX, int RW, int NS, int SC>
+__global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs a) {
+  constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS, kWaves = RW * NS;
+  constexpr int kStep = 32 * SC * NS;  // keys per step
+  static_assert(8 * kStep == 2 * kThreads, "two K and V pieces per thread and step");
   constexpr int kKRow = NX == 8 ? 72 : (NX == 16 ? 88 : 104);  // 64 dims | NX slots | padding: conflict-free
   __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kStep * kKRow];
   __shared__ __attribute__((aligned(16))) uint16_t Vs[2][kStep * kVRow];
   extern __shared__ uint32_t Ms[];  // the 128 rows' mask words, inverted, KW + 1 per row (the last all ones)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wid = wall & 3, set = NS > 1 ? wall >> 2 : 0;
+  const int wid = NS > 1 ? wall % RW : wall, set = NS > 1 ? wall / RW : 0;
   const int ql = lane & 31, g = lane >> 5;
   // launch order as in the power-of-two kernel: heads in groups whose keys fit the L2s, longest tiles first
-  const uint32_t wgs = (a.T + 127) / 128;
+  const uint32_t wgs = (a.T + kRows - 1) / kRows;
   const uint32_t per_group = static_cast<uint32_t>(a.group_heads) * wgs;
   const uint32_t grp = blockIdx.x / per_group, rem_b = blockIdx.x - grp * per_group;
   const uint32_t nh = min(static_cast<uint32_t>(a.group_heads), static_cast<uint32_t>(a.N) - grp * a.group_heads);
   const int64_t head = static_cast<int64_t>(grp) * a.group_heads + rem_b % nh;
   const int32_t wg_tile = static_cast<int32_t>(wgs - 1 - rem_b / nh);
-  const int32_t row0 = wg_tile * 128, q0 = row0 + 32 * wid, t = q0 + ql;
+  const int32_t row0 = wg_tile * kRows, q0 = row0 + 32 * wid, t = q0 + ql;
   const int32_t b = static_cast<int32_t>(head / a.H);
   const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
   const bool row_active = t < len;
@@ -89,14 +90,14 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
   const int mstride = a.KW + 1;
   {
     const uint32_t* msrc = a.mbits + (head * a.T + row0) * a.KW;
-    for (int32_t x = tid; x < 128 * mstride; x += kThreads) {
+    for (int32_t x = tid; x < kRows * mstride; x += kThreads) {
       const int32_t r = x / mstride, wi = x - r * mstride;
       Ms[x] = (wi < a.KW && row0 + r < len) ? ~msrc[r * a.KW + wi] : 0xffffffffu;
     }
   }
   const uint32_t* mrow = &Ms[(32 * wid + ql) * mstride];
 
-  const int32_t wg_hi = min(row0 + 127, a.T - 1), t_hi = min(q0 + 31, a.T - 1);
+  const int32_t wg_hi = min(row0 + kRows - 1, a.T - 1), t_hi = min(q0 + 31, a.T - 1);
   const int32_t u_end_wg = list_count(a.g, a.causal ? min(wg_hi, len - 1) : len - 1);
   const int32_t u_end = q0 < a.T ? list_count(a.g, a.causal ? min(t_hi, len - 1) : len - 1) : 0;
   // entries below u_free are admissible for every active row of the wave
@@ -104,8 +105,8 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
   const int32_t my_ucount = list_count(a.g, row_active ? (a.causal ? min(t, len - 1) : len - 1) : -1);
   const int32_t nsteps = (u_end_wg + kStep - 1) / kStep;
 
-  // staging: 16-byte part tid & 7 of the K and V rows (tid >> 3) and (tid >> 3) + 32 NS of a step: its wave's
-  // rows lie in the step's sub-chunks `set` and `set` + NS.  Rows
+  // staging: 16-byte part tid & 7 of the K and V rows (tid >> 3) and (tid >> 3) + 8 kWaves of a step: its wave's
+  // first rows lie in the step's sub-chunk wall / 4, its second ones in sub-chunk (wall + kWaves) / 4.  Rows
   // past the list or past the sequence re-read its last row; their scores are masked.
   const int srow = tid >> 3, spart = tid & 7;
   const int vpart = spart ^ (((srow >> 1) & 1) << 2);
@@ -127,12 +128,14 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
     rem -= carry ? a.D : 0;
   };
   auto advance = [&](int32_t& col, int32_t& rem) { advance_by(col, rem, a.q32, a.r32); };
-  auto advance_half = [&](int32_t& col, int32_t& rem) { advance_by(col, rem, NS == 1 ? a.q32 : a.q96, NS == 1 ? a.r32 : a.r96); };
-  // (several sets) first column of this wave's staged sub-chunk, of its next one
-  int32_t tcol = 0, trem = 0;
+  // half a step and a whole one further (NS == 1: two sub-chunks per step)
+  auto advance_half = [&](int32_t& col, int32_t& rem) { advance_by(col, rem, a.qh, a.rh); };
+  // (several sets) first columns of the sub-chunks this wave's two rows lie in
+  int32_t tcol0 = 0, trem0 = 0, tcol1 = 0, trem1 = 0;
   if (NS > 1) {
-    for (int e = 0; e < set; ++e) advance(tcol, trem);
-    for (int e = 0; e < 2 * set; ++e) advance(scol, srem);
+    for (int e = 0; e < (wall >> 2); ++e) advance(tcol0, trem0);
+    for (int e = 0; e < ((wall + kWaves) >> 2); ++e) advance(tcol1, trem1);
+    for (int e = 0; e < SC * set; ++e) advance(scol, srem);
   }
   auto onehot = [&](int32_t lc, uint32_t* x) {
     const uint32_t v = (lc & 1) ? 0xfe800000u : 0x0000fe80u;  // -2^126
@@ -156,20 +159,20 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
       int32_t ncol_ = scol, nrem_ = srem;                                                             \
       advance(ncol_, nrem_);                                                                          \
       cs1 = ncol_;                                                                                    \
-      advance(ncol_, nrem_);                                                                          \
+      if (SC == 2) advance(ncol_, nrem_);                                                             \
       cs2 = ncol_;                                                                                    \
-      advance_by(scol, srem, a.q192, a.r192);                                                         \
+      advance_by(scol, srem, a.qs, a.rs);                                                             \
     }                                                                                                 \
     const uint32_t oa = row_off();                                                                    \
-    onehot(ccol - (NS == 1 ? cs0 : tcol), x0);                                                        \
-    ucur += 32 * NS;                                                                                  \
+    onehot(ccol - (NS == 1 ? cs0 : tcol0), x0);                                                       \
+    ucur += kStep / 2;                                                                                \
     advance_half(ccol, crem);                                                                         \
-    if (NS > 1) advance_half(tcol, trem);                                                             \
     const uint32_t ob = row_off();                                                                    \
-    onehot(ccol - (NS == 1 ? cs1 : tcol), x1);                                                        \
-    ucur += 32 * NS;                                                                                  \
+    onehot(ccol - (NS == 1 ? cs1 : tcol1), x1);                                                       \
+    ucur += kStep / 2;                                                                                \
     advance_half(ccol, crem);                                                                         \
-    if (NS > 1) advance_half(tcol, trem);                                                             \
+    if (NS > 1) advance_by(tcol0, trem0, a.qs, a.rs);                                                 \
+    if (NS > 1) advance_by(tcol1, trem1, a.qs, a.rs);                                                 \
     kreg0 = buffer_load16(Kres, oa);                                                                  \
     kreg1 = buffer_load16(Kres, ob);                                                                  \
     vreg0 = buffer_load16(Vres, oa);                                                                  \
@@ -178,13 +181,13 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
 #define SEA_CPARK(stage_)                                                                             \
   do {                                                                                                \
     *reinterpret_cast<uint4*>(&Ks[stage_][srow * kKRow + spart * 8]) = kreg0;                          \
-    *reinterpret_cast<uint4*>(&Ks[stage_][(srow + 32 * NS) * kKRow + spart * 8]) = kreg1;                   \
+    *reinterpret_cast<uint4*>(&Ks[stage_][(srow + 8 * kWaves) * kKRow + spart * 8]) = kreg1;                   \
     *reinterpret_cast<uint4*>(&Vs[stage_][srow * kVRow + vpart * 8]) = vreg0;                          \
-    *reinterpret_cast<uint4*>(&Vs[stage_][(srow + 32 * NS) * kVRow + vpart * 8]) = vreg1;                   \
+    *reinterpret_cast<uint4*>(&Vs[stage_][(srow + 8 * kWaves) * kVRow + vpart * 8]) = vreg1;                   \
     if (NX >= 16 || spart < NX / 2) {                                                                 \
       _Pragma("unroll") for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) {                                 \
         *reinterpret_cast<uint32_t*>(&Ks[stage_][srow * kKRow + kHeadDim + 2 * (spart + 8 * e)]) = x0[e];        \
-        *reinterpret_cast<uint32_t*>(&Ks[stage_][(srow + 32 * NS) * kKRow + kHeadDim + 2 * (spart + 8 * e)]) = x1[e]; \
+        *reinterpret_cast<uint32_t*>(&Ks[stage_][(srow + 8 * kWaves) * kKRow + kHeadDim + 2 * (spart + 8 * e)]) = x1[e]; \
       }                                                                                               \
     }                                                                                                 \
   } while (0)
@@ -214,8 +217,8 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
     const int32_t c0[3] = {cs0, cs1, cs2};  // (uniform) columns at the start of this step's sub-chunks
     if (step + 1 < nsteps) SEA_CFETCH();
 #pragma unroll
-    for (int sc = 0; sc < 2; ++sc) {
-      const int32_t u0 = step * kStep + kChunk * set + 32 * sc;
+    for (int sc = 0; sc < SC; ++sc) {
+      const int32_t u0 = step * kStep + 32 * (SC * set + sc);
       if (u0 >= u_end) break;  // wave-uniform: beyond what this wave's rows can see
       const int32_t wi = c0[sc] >> 5;
       // the row's inverted mask bits from the sub-chunk's first column on
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
       const int32_t ncol = min(c0[sc + 1] - c0[sc] + 1, NX);
       const uint32_t cmask = 0xffffffffu >> (32 - ncol);
       if (__ballot((win & cmask) != cmask) == 0ull) continue;  // no row of the wave uses it
-      const uint16_t* Kr = &Ks[stage][(kChunk * set + 32 * sc + ql) * kKRow + 8 * g];
+      const uint16_t* Kr = &Ks[stage][(32 * (SC * set + sc) + ql) * kKRow + 8 * g];
       floatx16 sv;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sv[i] = 0.f;
@@ -237,7 +240,7 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
         const uint32_t un = NX == 8 ? (win & 0xffu) : ((win >> (16 * e + 8 * g)) & 0xffu);
         const uint32_t xx = un | (un << 15);  // bits 2 j and 2 j + 1 sit at 2 j and 2 j + 16
         const u32x4 bx = {(xx << 14) & gmask, (xx << 12) & gmask, (xx << 10) & gmask, (xx << 8) & gmask};
-        const uint16_t* Ke = &Ks[stage][(kChunk * set + 32 * sc + ql) * kKRow + kHeadDim + (NX == 8 ? 0 : 16 * e + 8 * g)];
+        const uint16_t* Ke = &Ks[stage][(32 * (SC * set + sc) + ql) * kKRow + kHeadDim + (NX == 8 ? 0 : 16 * e + 8 * g)];
         sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Ke),
                                                      __builtin_bit_cast(bf16x8, bx), sv, 0, 0, 0);
       }
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
       bf16x8 av[2][2];
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
-        const uint16_t* Vr = &Vs[stage][(kChunk * set + 32 * sc + 4 * g + ((ql & 15) >> 2)) * kVRow +
+        const uint16_t* Vr = &Vs[stage][(32 * (SC * set + sc) + 4 * g + ((ql & 15) >> 2)) * kVRow +
                                         32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2) {
@@ -319,15 +322,17 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
   if constexpr (NS > 1) {
     // merge of the sets' partial results in the place of the last step's keys and values (the loop ended
     // with a barrier)
-    static_assert(NS == 3 && sizeof(Ks) >= 256 * kPartFloats * 4 && sizeof(Vs) >= 256 * kPartFloats * 4, "a set's result each");
-    float* const p1 = reinterpret_cast<float*>(&Ks[0][0]) + 64 * wid + lane;
-    float* const p2 = reinterpret_cast<float*>(&Vs[0][0]) + 64 * wid + lane;
+    constexpr int kPart = 64 * RW * kPartFloats, kInK = sizeof(Ks) / (4 * kPart);
+    static_assert(NS - 1 - kInK <= static_cast<int>(sizeof(Vs) / (4 * kPart)), "every set's result has a place");
+    auto place = [&](int e) {
+      return (e <= kInK ? reinterpret_cast<float*>(&Ks[0][0]) + (e - 1) * kPart
+                        : reinterpret_cast<float*>(&Vs[0][0]) + (e - 1 - kInK) * kPart) + 64 * wid + lane;
+    };
     float m_own = m_thr > 0.f ? m_ref : -INFINITY;
-    if (set > 0) store_part<256>(set == 1 ? p1 : p2, oacc, l_run, m_own);
+    if (set > 0) store_part<64 * RW>(place(set), oacc, l_run, m_own);
     __syncthreads();
     if (set > 0) return;
-    merge_part<256>(p1, oacc, l_run, m_own);
-    merge_part<256>(p2, oacc, l_run, m_own);
+    for (int e = 1; e < NS; ++e) merge_part<64 * RW>(place(e), oacc, l_run, m_own);
   }
   l_run = half_sum(l_run);
   if (t < a.T) {
@@ -344,6 +349,15 @@ __global__ __launch_bounds__(256 * NS, 3) void column_attn_kernel(ColumnArgs a) 
         *reinterpret_cast<bf16x4*>(Or + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
       }
   }
+}
+
+template <int NX, int RW, int NS, int SC>
+void launch_column(const Shape& s, ColumnArgs a, hipStream_t st) {
+  constexpr int kRows = 32 * RW, kStep = 32 * SC * NS;
+  a.qh = kStep / 2 * a.A / a.D; a.rh = kStep / 2 * a.A % a.D;
+  a.qs = kStep * a.A / a.D; a.rs = kStep * a.A % a.D;
+  hipLaunchKernelGGL((column_attn_kernel<NX, RW, NS, SC>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
+                     dim3(64 * RW * NS), static_cast<size_t>(kRows) * (a.KW + 1) * sizeof(uint32_t), st, a);
 }
 
 }  // namespace
@@ -363,22 +377,23 @@ hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t*
   a.g = column_list(s);
   a.A = a.g.r == 0 ? s.K : 1; a.D = a.g.r == 0 ? s.T : a.g.r;
   a.q32 = 32 * a.A / a.D; a.r32 = 32 * a.A % a.D;
-  a.q96 = 96 * a.A / a.D; a.r96 = 96 * a.A % a.D;
-  a.q192 = 192 * a.A / a.D; a.r192 = 192 * a.A % a.D;
   a.causal = s.causal; a.c = s.scale * kLog2e;
   a.group_heads = group_heads_for(s.N, a.g.U);
-  const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 127) / 128));
-  // Three sets of waves where the launch leaves room (one block per CU; causal, two, since half of the blocks
-  // are short) or its longest lists dominate it.  Whole forward, K = 128, k^ = 48, one and three sets:
-  // H = 12, T = 2041, B = 1 (192 blocks) 83 / 66 us, B = 2 (384) 86 / 69, B = 4 (768) 108 / 119; T = 501, B = 1
-  // 35 / 33; T = 8001 (756) 359 / 305, T = 16001 (1512) 1095 / 859; bidirectional B = 2, T = 2041 104 / 104.
-  const bool sets = grid.x <= 256 || (s.causal && (grid.x <= 512 || (grid.x <= 2048 && a.g.U >= 8000)));
-  const dim3 block(sets ? 768 : 256);
-  const size_t shm = static_cast<size_t>(128) * (a.KW + 1) * sizeof(uint32_t);
+  // How the waves of a block are split: three sets of four waves where the launch leaves room (128-row blocks:
+  // one per CU; causal, two, since half of them are short) or its longest lists dominate it, and six sets of
+  // two on 64 rows where those still leave room.  Whole forward, K = 128, k^ = 48, H = 12, causal, us with one /
+  // three / six sets: T = 501, B = 1 (48 blocks) 35 / 33 / 29, B = 4 (192) 38 / 36 / 38; T = 1001, B = 1 (96)
+  // 51 / 44 / 37, B = 4 (384) 59 / 55 / 62; T = 2041, B = 1 (192) 83 / 66 / 55, B = 2 (384) 86 / 70 / 80, B = 4
+  // (768) 106 / 118 / 140; whole columns of T = 8001 (756) 355 / 303 / 299, T = 16001 (1512) 1095 / 859 / -;
+  // bidirectional, T = 2041, B = 1 81 / 64 / 75, B = 2 104 / 104 / 103.
+  const int64_t blocks = static_cast<int64_t>(s.N) * ((s.T + 127) / 128);
+  const bool six = blocks <= (s.causal && a.g.U >= 2000 ? 256 : 128);
+  const bool three = blocks <= 256 || (s.causal && (blocks <= 512 || (blocks <= 2048 && a.g.U >= 8000)));
   const int32_t per = a.g.r == 0 ? a.g.cg.w0 : a.g.r;  // least keys per column
-#define SEA_COLUMN(NX_)                                                                             \
-  if (sets) hipLaunchKernelGGL((column_attn_kernel<NX_, 3>), grid, block, shm, st, a);              \
-  else hipLaunchKernelGGL((column_attn_kernel<NX_, 1>), grid, block, shm, st, a)
+#define SEA_COLUMN(NX_)                                     \
+  if (six) launch_column<NX_, 2, 6, 1>(s, a, st);           \
+  else if (three) launch_column<NX_, 4, 3, 2>(s, a, st);    \
+  else launch_column<NX_, 4, 1, 2>(s, a, st)
   if (per >= 5) { SEA_COLUMN(8); }
   else if (per >= 3) { SEA_COLUMN(16); }
   else { SEA_COLUMN(32); }

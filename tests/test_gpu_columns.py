@@ -29,7 +29,10 @@ CASES = [
     (1, 1, 1500, 64, 100, 20, 20, True, 0.0),    # one of 15
     (1, 1, 1300, 64, 13, 5, 500, True, 0.0),     # 100 of 100: the cap equals every width
     (1, 1, 1030, 32, 1024, 100, 0, True, 0.0),   # the largest K
-    (5, 9, 700, 64, 100, 20, 0, False, 0.3),     # more row blocks than sets of waves share lists for: 8 slots,
+    (1, 26, 601, 64, 100, 20, 0, False, 0.3),    # more row blocks than six sets of waves share lists for: 8 slots,
+    (1, 34, 500, 64, 128, 30, 0, True, 0.0),     # 16 slots
+    (1, 75, 249, 32, 140, 60, 0, True, 0.0),     # and 32
+    (5, 9, 700, 64, 100, 20, 0, False, 0.3),     # more than three sets do: 8 slots,
     (2, 33, 401, 64, 128, 30, 0, False, 0.0),    # 16 slots
     (3, 45, 250, 32, 249, 60, 0, False, 0.3),    # and 32
     (1, 1, 37, 64, 5, 5, 0, False, 0.0),         # every column selected, less than one step of keys
