@@ -405,7 +405,13 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
     e = launch_bits_attn(s, Q, K, V, mbits, O, w, st);
     return e == hipSuccess ? SEA_OK : fail_hip(e);
   }
-  if (s.geometry == 1)
+  // per-row widths, no row lists wanted: the estimator selects and writes the key bits itself
+  const bool fused_select = keybit_path(s, p->dtype) && rowwidth_select_supported(s, p->dtype) && !sel_opt && !idx_opt && !cnt_opt;
+  if (fused_select) {
+    uint32_t* kb = reinterpret_cast<uint32_t*>(w + align256(rows * ((s.K + 31) / 32) * sizeof(uint32_t)));
+    e = launch_rowwidth_mfma(s, static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(W),
+                             A_hat_opt, est_ws, st, mhat_opt, kb);
+  } else if (s.geometry == 1)
     e = launch_estimate_rowwidth(s, p->dtype, Q, K, W, A_hat, est_ws, st);
   else if (p->dtype == SEA_BF16)
     e = launch_estimate_bf16(s, static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
@@ -427,7 +433,9 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
     uint32_t* mbits = mhat_opt ? mhat_opt : reinterpret_cast<uint32_t*>(w);
     w += align256(rows * ((s.K + 31) / 32) * sizeof(uint32_t));
     uint32_t* kb = reinterpret_cast<uint32_t*>(w);
-    if (s.grouping == 0) {
+    if (fused_select) {
+      e = hipSuccess;
+    } else if (s.grouping == 0) {
       // per-query selection: the kernel that selects a row also expands it to its key bits
       e = launch_topk_mask(s, A_hat, sel_opt, idx_opt, cnt_opt, mbits, st, kb);
     } else {

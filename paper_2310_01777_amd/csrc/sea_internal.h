@@ -59,8 +59,11 @@ hipError_t launch_estimate_rowwidth(const Shape& s, sea_dtype dt, const void* Q,
 // the same estimate for bf16 tensors on the bf16 matrix cores (features rounded to bf16, per-key products binned in LDS)
 bool rowwidth_mfma_supported(const Shape& s, sea_dtype dt);
 size_t rowwidth_mfma_workspace(const Shape& s);
+// kb (rowwidth_select_supported shapes): also the per-query selection, as column bits (mbits, may be nullptr) and
+// as one bit per key up to the end of the row's 128-row tile; A_hat may then be nullptr
+bool rowwidth_select_supported(const Shape& s, sea_dtype dt);
 hipError_t launch_rowwidth_mfma(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W,
-                                float* A_hat, void* ws, hipStream_t st);
+                                float* A_hat, void* ws, hipStream_t st, uint32_t* mbits = nullptr, uint32_t* kb = nullptr);
 
 // sel, idx, cnt, mbits may each be nullptr; mbits is [N][T][ceil(K/32)] selected-column bits
 // kb (per-query grouping, keybits_supported shapes only): also the selection expanded to one bit per key

@@ -23,7 +23,9 @@
 // own columns: the work is split, not repeated.
 #include <algorithm>
 
+#include "sea_columns.h"
 #include "sea_internal.h"
+#include "sea_select.h"
 
 namespace sea {
 namespace {
@@ -168,11 +170,20 @@ __global__ __launch_bounds__(256) void rw_features_kernel(Shape s, const uint16_
 // the row's bins, so no product needs a predicate.  Padding keys and rows past the end have
 // all-zero features and add zeros.
 // ------------------------------------------------------------------------------------------
-template <int MS, bool WIDE>  // MS = m / 16: contraction steps
+// NCT > 0: the block also selects its rows' k^ columns (per-query grouping) and writes them as one bit per
+// key of the row, which is all the attention needs; the scores then leave the chip only if A_hat is given.
+// A wave takes 16 rows once the sums are known: a row's K <= 16 NCT scores go from the bins into four
+// lanes, the search runs in registers, and each lane ORs the keys of its selected columns into the row's
+// words.  B = 4, H = 12, T = 2048, K = 128: the pass over a score matrix in HBM that this replaces took
+// 57 us (one row per wave), tiles and selection together 150 us, now NEW.
+// ------------------------------------------------------------------------------------------
+template <int MS, bool WIDE, int NCT>  // MS = m / 16: contraction steps
 __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4* __restrict__ phiQ,
                                                             const uint4* __restrict__ phiK,
                                                             float* __restrict__ A_hat, int32_t parts,
-                                                            int32_t part_cols, int32_t stride, int32_t cshift) {
+                                                            int32_t part_cols, int32_t stride, int32_t cshift,
+                                                            uint32_t* __restrict__ mbits, uint32_t* __restrict__ kb,
+                                                            int32_t KWk) {
   extern __shared__ __align__(16) double lds[];  // [P][64 rows][stride] bins, [64][P] row sums, [64] inverses
   const int lane = threadIdx.x & 63, q = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -311,7 +322,8 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
     inv_s[lane] = (r0 + lane < len && total > 0.0) ? 1.0 / total : 0.0;
   }
   __syncthreads();
-  if (passes == 1) {
+  if (NCT > 0 && !A_hat) {
+  } else if (passes == 1) {
     const int32_t c_lo = min(wave * part_cols, s.K), ncols = min(s.K, c_lo + part_cols) - c_lo;
     for (int32_t row = rsub; row < kTileRows && r0 + row < s.T; row += kTileRows >> cshift)
       if (csub < ncols)
@@ -326,6 +338,111 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
           float* out = A_hat + (head * s.T + r0 + row) * s.K + c_lo + csub;
           *out = static_cast<float>(static_cast<double>(*out) * inv_s[row]);
         }
+    }
+  }
+  if constexpr (NCT > 0) {
+    const int lr = lane & 15, lg = lane >> 4;
+    const int32_t row = 16 * wave + lr, t = r0 + row;  // (waves past the fourth have no rows)
+    const bool active = wave < 4 && t < len;
+    const int32_t Tw = t + 1, ncnd = active ? min(s.K, Tw) : 0;  // columns that hold a key
+    const uint32_t nsel = static_cast<uint32_t>(min(s.k_hat, ncnd));
+    const int32_t w0 = Tw / s.K, rm = Tw - w0 * s.K;
+    const float invK = 1.0f / static_cast<float>(s.K);
+    // first key of column c: ceil(c (t + 1) / K)
+    auto start = [&](int32_t c) { return c * w0 + div_small(c * rm + s.K - 1, invK); };
+    uint32_t key[NCT][4];
+    if (wave < 4) {
+      const double inv = inv_s[row];
+      const uint32_t by_part = 65536u / static_cast<uint32_t>(part_cols) + 1u;  // c / part_cols, exact for c < 256
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct) {
+        const int32_t c0 = 16 * ct + 4 * lg;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int32_t c = min(c0 + i, s.K - 1);
+          const int32_t part = static_cast<int32_t>((static_cast<uint32_t>(c) * by_part) >> 16);
+          const double sum = lds[(part * kTileRows + row) * stride + 1 + c - part * part_cols];
+          bool cand = active && c0 + i < s.K;
+          if (w0 == 0) cand = cand && start(c + 1) > start(c);
+          key[ct][i] = cand ? __float_as_uint(static_cast<float>(sum * inv)) | 0x80000000u : 0x40000000u;
+        }
+      }
+    }
+    __syncthreads();  // the bins are in registers: their place takes the rows' key bits
+    if (wave >= 4) return;
+    uint32_t nib[NCT];
+    select_columns<NCT>(key, nsel, ncnd, NCT, s.k_hat, lg, nib);
+    if (mbits) {
+      const int32_t kw = (s.K + 31) >> 5;
+#pragma unroll
+      for (int j = 0; j < NCT / 2; ++j) {
+        const uint32_t word = rows_or_u((nib[2 * j] << (4 * lg)) | (nib[2 * j + 1] << (16 + 4 * lg)));
+        if (lg == 0 && j < kw && t < s.T) mbits[(head * s.T + t) * kw + j] = word;
+      }
+    }
+    // words of the 128-row tile the attention may look at; one word of padding per row keeps the rows' words in
+    // different banks
+    const int32_t nw = min(KWk, ((r0 | 127) >> 5) + 1), wstride = nw | 1;
+    uint32_t* const words = reinterpret_cast<uint32_t*>(bins);
+    for (int32_t x = lane; x < 16 * wstride; x += 64) words[x] = 0u;
+    __builtin_amdgcn_wave_barrier();
+    uint32_t* const wrow = words + lr * wstride;
+    const bool whole = w0 + (rm > 0 ? 1 : 0) <= s.rep_cap;  // no column is wider than the cap: all its keys are emitted
+    if (__ballot(active && !whole) == 0ull) {
+      // A key's bit is the parity of the selection changes at or before it: one bit is flipped where a selected
+      // column follows an unselected one or the reverse (columns without keys flip nothing: their flips meet in
+      // one place), and the words are made of the flips on their way out.
+      uint32_t carry = 0u;  // is column 16 ct - 1 selected (lane group 3 of the tile before)
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct) {
+        const uint32_t top = nib[ct] >> 3;
+        const uint32_t below = __shfl_up(top, 16, kWave);  // bit 3 of the lane group below
+        const uint32_t prev = (nib[ct] << 1) | (lg == 0 ? carry : below);
+        carry = __shfl(top, 48 + lr, kWave);
+        const uint32_t flips = (nib[ct] ^ prev) & 15u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int32_t c = 16 * ct + 4 * lg + i, at = start(c);
+          if (((flips >> i) & 1u) && c < s.K) atomicXor(&wrow[at >> 5], 1u << (at & 31));
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      for (int32_t rr = 0; rr < 16 && r0 + 16 * wave + rr < s.T; ++rr) {
+        const int32_t tr = r0 + 16 * wave + rr;
+        uint32_t* const dst = kb + (head * s.T + tr) * KWk;
+        uint32_t in = 0u;  // parity of all flips in earlier words
+        for (int32_t x0 = 0; x0 < nw; x0 += 64) {
+          const int32_t x = x0 + lane;
+          uint32_t v = x < nw ? words[rr * wstride + x] : 0u;
+#pragma unroll
+          for (int d = 1; d < 32; d <<= 1) v ^= v << d;
+          const uint64_t odd = __ballot((v >> 31) != 0u);
+          const uint32_t before = in ^ (static_cast<uint32_t>(__popcll(odd & ((1ull << lane) - 1ull))) & 1u);
+          v ^= 0u - before;
+          // nothing past the row's own keys (the last column may be selected)
+          const int32_t past = tr + 1 - 32 * x;
+          v &= past >= 32 ? 0xffffffffu : (past <= 0 ? 0u : (1u << past) - 1u);
+          if (x < nw) dst[x] = v;
+          in ^= static_cast<uint32_t>(__popcll(odd)) & 1u;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if ((nib[ct] >> i) & 1u) {
+            const int32_t c = 16 * ct + 4 * lg + i, s0 = start(c), w = start(c + 1) - s0, r = min(w, s.rep_cap);
+            for (int32_t e = 0; e < r; ++e) {
+              const int32_t j = s0 + (e * w) / r;
+              atomicOr(&wrow[j >> 5], 1u << (j & 31));
+            }
+          }
+      __builtin_amdgcn_wave_barrier();
+      for (int32_t rr = 0; rr < 16 && r0 + 16 * wave + rr < s.T; ++rr) {
+        uint32_t* const dst = kb + (head * s.T + r0 + 16 * wave + rr) * KWk;
+        for (int32_t x = lane; x < nw; x += 64) dst[x] = words[rr * wstride + x];
+      }
     }
   }
 }
@@ -349,9 +466,23 @@ size_t side_bytes(const Shape& s) {
   return (static_cast<size_t>(s.N) * t32 * s.m * sizeof(uint16_t) + 255) & ~size_t(255);
 }
 
+template <int MS, bool WIDE, int NCT>
+hipError_t launch_tiles(const Shape& s, const Plan& p, const uint4* phiQ, const uint4* phiK, float* A_hat, uint32_t* mbits,
+                        uint32_t* kb, hipStream_t st) {
+  if (p.lds > (64u << 10)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_tiles_mfma_kernel<MS, WIDE, NCT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(p.lds));
+    if (e != hipSuccess) return e;
+  }
+  const uint32_t tiles = (s.T + kTileRows - 1) / kTileRows;
+  hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT>), dim3(static_cast<uint32_t>(s.N) * tiles), dim3(64 * p.waves), p.lds, st, s,
+                     phiQ, phiK, A_hat, p.parts, p.part_cols, p.stride, p.cshift, mbits, kb, (s.T + 31) / 32);
+  return hipGetLastError();
+}
+
 template <int MC>
 hipError_t launch(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W, float* A_hat,
-                  void* ws, hipStream_t st) {
+                  uint32_t* mbits, uint32_t* kb, void* ws, hipStream_t st) {
   uint4* phiQ = static_cast<uint4*>(ws);
   uint4* phiK = reinterpret_cast<uint4*>(static_cast<char*>(ws) + side_bytes(s));
   const double l2e = 1.4426950408889634;
@@ -370,21 +501,11 @@ hipError_t launch(const Shape& s, const uint16_t* Q, const uint16_t* K, const ui
   StageScope scope(SEA_STAGE_CONTRACT, st);
   const Plan p = plan(s);
   const bool wide = static_cast<int64_t>(s.K) * s.T > (int64_t{1} << 21);
-  const void* fn = wide ? reinterpret_cast<const void*>(&rw_tiles_mfma_kernel<2 * MC, true>)
-                        : reinterpret_cast<const void*>(&rw_tiles_mfma_kernel<2 * MC, false>);
-  if (p.lds > (64u << 10)) {
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(p.lds));
-    if (e != hipSuccess) return e;
-  }
-  const uint32_t tiles = (s.T + kTileRows - 1) / kTileRows;
-  const dim3 grid(static_cast<uint32_t>(s.N) * tiles), block(64 * p.waves);
-  if (wide)
-    hipLaunchKernelGGL((rw_tiles_mfma_kernel<2 * MC, true>), grid, block, p.lds, st, s, phiQ, phiK, A_hat, p.parts,
-                       p.part_cols, p.stride, p.cshift);
-  else
-    hipLaunchKernelGGL((rw_tiles_mfma_kernel<2 * MC, false>), grid, block, p.lds, st, s, phiQ, phiK, A_hat, p.parts,
-                       p.part_cols, p.stride, p.cshift);
-  return hipGetLastError();
+  if (kb)  // K T <= 2^21 there
+    return s.K <= 128 ? launch_tiles<2 * MC, false, 8>(s, p, phiQ, phiK, A_hat, mbits, kb, st)
+                      : launch_tiles<2 * MC, false, 16>(s, p, phiQ, phiK, A_hat, mbits, kb, st);
+  return wide ? launch_tiles<2 * MC, true, 0>(s, p, phiQ, phiK, A_hat, nullptr, nullptr, st)
+              : launch_tiles<2 * MC, false, 0>(s, p, phiQ, phiK, A_hat, nullptr, nullptr, st);
 }
 
 }  // namespace
@@ -395,12 +516,19 @@ bool rowwidth_mfma_supported(const Shape& s, sea_dtype dt) {
 
 size_t rowwidth_mfma_workspace(const Shape& s) { return 2 * side_bytes(s); }
 
+// the selection as key bits straight from the estimate: four to eight column parts (a wave has the bins of one
+// and selects for at most 16 rows), key-bit rows of at most 256 words
+bool rowwidth_select_supported(const Shape& s, sea_dtype dt) {
+  return rowwidth_mfma_supported(s, dt) && s.grouping == 0 && s.K > 96 && s.K <= 256 && s.T <= 8192;
+}
+
 hipError_t launch_rowwidth_mfma(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W,
-                                float* A_hat, void* ws, hipStream_t st) {
+                                float* A_hat, void* ws, hipStream_t st, uint32_t* mbits, uint32_t* kb) {
+  if (kb && !rowwidth_select_supported(s, SEA_BF16)) return hipErrorNotSupported;
   switch (s.m) {
-    case 64: return launch<2>(s, Q, K, W, A_hat, ws, st);
-    case 128: return launch<4>(s, Q, K, W, A_hat, ws, st);
-    default: return launch<8>(s, Q, K, W, A_hat, ws, st);
+    case 64: return launch<2>(s, Q, K, W, A_hat, mbits, kb, ws, st);
+    case 128: return launch<4>(s, Q, K, W, A_hat, mbits, kb, ws, st);
+    default: return launch<8>(s, Q, K, W, A_hat, mbits, kb, ws, st);
   }
 }
 
