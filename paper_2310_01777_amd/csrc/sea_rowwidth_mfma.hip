@@ -5,7 +5,7 @@
 //   A^[t][c] = sum over the keys j of row t's column c of  phi~(q_t) . phi~(k_j),  then / row sum
 //
 // with phi~ the features rounded to bf16 (queries after a power-of-two row shift).  The products
-// a_tj of 64 query rows x 32 keys are two tiles of phi~(K) phi~(Q)^T (v_mfma_f32_32x32x16_bf16,
+// a_tj of 32 query rows x 32 keys are a tile of phi~(K) phi~(Q)^T (v_mfma_f32_32x32x16_bf16,
 // fp32 accumulation); every a_tj is then added to the bin of its column floor(j K / (t + 1)) in LDS.
 // Nothing is differenced, so there is no cancellation, and no prefix state exists.  The bins are
 // fp64: the LDS adds 64 doubles in about 11 clocks but needs about 170 for 64 floats (measured,
@@ -14,11 +14,11 @@
 //   rw_features_kernel   phi~(Q), phi~(K) -> HBM, already in the order the tile kernel's lanes
 //                        consume them: [head][32-token chunk][step][lane][8 features], so every
 //                        operand load of the tile kernel is one contiguous 1 KB piece
-//   rw_tiles_mfma_kernel one wavefront per (head, 64 query rows, column part): walks the 32-key
+//   rw_tiles_mfma_kernel one wavefront per (head, 32 or 64 query rows, column part): walks the 32-key
 //                        chunks its columns cover, bins, normalises, writes fp32 A^
 //
-// Column parts: a wave keeps the bins of at most 32 columns ([64 rows][<= 32] fp64 = 18 KB), so that
-// a CU holds eight waves, two per SIMD; the ceil(K / 32) parts of a row tile are taken by the (at
+// Column parts: a wave keeps the bins of at most 32 columns ([32 rows][<= 32] fp64 = 9 KB), so that
+// a CU holds sixteen waves, four per SIMD; the ceil(K / 32) parts of a row tile are taken by the (at
 // most eight) waves of one block, which meet only for the row sums.  The columns of a row are monotone in the key index, so part p walks only the keys of its
 // own columns: the work is split, not repeated.
 #include <algorithm>
@@ -36,7 +36,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kWRow = 72;      // halfwords per staged W row (128 B + 16 B pad): conflict-free b128 reads
 constexpr int kChunk = 32;     // tokens per feature chunk = keys per step of the tile kernel
-constexpr int kTileRows = 64;  // query rows of a wavefront
 constexpr int kPartCols = 32;  // columns whose bins one wavefront keeps
 
 __device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c) {
@@ -154,9 +153,9 @@ __global__ __launch_bounds__(256) void rw_features_kernel(Shape s, const uint16_
 }
 
 // ------------------------------------------------------------------------------------------
-// Tiles.  Block = P <= 8 wavefronts working on one (head, 64-row tile); wave w takes the column
+// Tiles.  Block = P <= 8 wavefronts working on one (head, 32 U rows); wave w takes the column
 // parts w, w + P, ... (one pass of the loop below per part; a single pass whenever K <= 256).  Lane l of
-// a wave owns the query rows r0 + l % 32 and r0 + 32 + l % 32 and, in every 32-key chunk, the 16
+// a wave owns the query rows r0 + 32 u + l % 32 and, in every 32-key chunk, the 16
 // keys 16 (l / 32) + i of the chunk (see the key permutation above).
 //
 // Column of key j in row t: floor(j K / (t + 1)).  WIDE = false takes it in fp32 as
@@ -175,16 +174,17 @@ __global__ __launch_bounds__(256) void rw_features_kernel(Shape s, const uint16_
 // A wave takes 16 rows once the sums are known: a row's K <= 16 NCT scores go from the bins into four
 // lanes, the search runs in registers, and each lane ORs the keys of its selected columns into the row's
 // words.  B = 4, H = 12, T = 2048, K = 128: the pass over a score matrix in HBM that this replaces took
-// 57 us (one row per wave), tiles and selection together 150 us, now NEW.
+// 57 us (one row per wave), the whole forward 214 us, now 181.
 // ------------------------------------------------------------------------------------------
-template <int MS, bool WIDE, int NCT>  // MS = m / 16: contraction steps
-__global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4* __restrict__ phiQ,
+template <int MS, bool WIDE, int NCT, int U>  // MS = m / 16: contraction steps
+__global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shape s, const uint4* __restrict__ phiQ,
                                                             const uint4* __restrict__ phiK,
                                                             float* __restrict__ A_hat, int32_t parts,
                                                             int32_t part_cols, int32_t stride, int32_t cshift,
                                                             uint32_t* __restrict__ mbits, uint32_t* __restrict__ kb,
                                                             int32_t KWk) {
-  extern __shared__ __align__(16) double lds[];  // [P][64 rows][stride] bins, [64][P] row sums, [64] inverses
+  constexpr int kTileRows = 32 * U;  // query rows of the block
+  extern __shared__ __align__(16) double lds[];  // [P][rows][stride] bins, [rows][P] row sums, [rows] inverses
   const int lane = threadIdx.x & 63, q = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int P = blockDim.x >> 6;
@@ -206,12 +206,12 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
   // lane <-> (row, column) of a part when its bins leave: 2^cshift >= part_cols columns side by side
   const int32_t csub = lane & ((1 << cshift) - 1), rsub = lane >> cshift;
 
-  bf16x8 qf[2][MS];
-  float kinv[2], hinv[2];
-  double winv[2];
+  bf16x8 qf[U][MS];
+  float kinv[U], hinv[U];
+  double winv[U];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const uint32_t tile32 = 2 * tile + u;
+  for (int u = 0; u < U; ++u) {
+    const uint32_t tile32 = U * tile + u;
     const uint4* qp = phiQ + ((head * nch + min(tile32, nch - 1)) * MS) * 64 + lane;
 #pragma unroll
     for (int st = 0; st < MS; ++st) {
@@ -231,72 +231,80 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
     for (int st = 0; st < MS; ++st)
       kf[st] = __builtin_bit_cast(bf16x8, kp[(static_cast<int64_t>(c) * MS + st) * 64]);
   };
-  double rowtot[2] = {0.0, 0.0};  // row sums over the parts this wave has finished (rows q, 32 + q)
+  double rowtot[U] = {};  // row sums over the parts this wave has finished (rows 32 u + q)
 
   for (int32_t pass = 0; pass < passes; ++pass) {
     const int32_t part = pass * P + wave;
     const int32_t c_lo = min(part * part_cols, s.K), c_hi = min(s.K, c_lo + part_cols);
     const int32_t ncols = c_hi - c_lo;
-    for (int32_t x = lane; x < kTileRows * stride; x += 64) bins[x] = 0.0;
-    // index in `bins` of column 0 of the lane's two rows: column c sits in slot c - (c_lo - 1), the
+    // index in `bins` of column 0 of the lane's rows: column c sits in slot c - (c_lo - 1), the
     // guards in slots 0 and ncols + 1
-    const int32_t base[2] = {q * stride - (c_lo - 1), (32 + q) * stride - (c_lo - 1)};
+    int32_t base[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) base[u] = (32 * u + q) * stride - (c_lo - 1);
     // keys the wave's columns cover over the active rows: column starts grow with the row, so the
     // first key is row r0's start of c_lo and the last one precedes the last active row's start of c_hi
     int32_t cb = 0, ce = 0;
     if (r_last >= r0 && ncols > 0) {
-      const int64_t j_begin = (static_cast<int64_t>(c_lo) * (r0 + 1) + s.K - 1) / s.K;
-      const int64_t j_end = (static_cast<int64_t>(c_hi) * (r_last + 1) + s.K - 1) / s.K;
-      cb = static_cast<int32_t>(j_begin / kChunk);
-      ce = static_cast<int32_t>((j_end + kChunk - 1) / kChunk);
+      if (WIDE) {
+        const int64_t j_begin = (static_cast<int64_t>(c_lo) * (r0 + 1) + s.K - 1) / s.K;
+        const int64_t j_end = (static_cast<int64_t>(c_hi) * (r_last + 1) + s.K - 1) / s.K;
+        cb = static_cast<int32_t>(j_begin / kChunk);
+        ce = static_cast<int32_t>((j_end + kChunk - 1) / kChunk);
+      } else {  // (everything below 2^22)
+        cb = (c_lo * (r0 + 1) + s.K - 1) / s.K / kChunk;
+        ce = ((c_hi * (r_last + 1) + s.K - 1) / s.K + kChunk - 1) / kChunk;
+      }
     }
+    bf16x8 kf[MS];
+    if (cb < ce) request(kf, cb);
+    for (int32_t x = lane; x < kTileRows * stride; x += 64) bins[x] = 0.0;
     const float lo_f = static_cast<float>(c_lo - 1), hi_f = static_cast<float>(c_hi);  // the guards
     // product i of chunk c in lane half h belongs to key 32 c + 16 h + i
-    auto bin = [&](const floatx16 (&acc)[2], int32_t c, int i) {
-      const int32_t j = c * kChunk + 16 * h + i;
+    auto bin = [&](const floatx16 (&acc)[U], int32_t c, float jf, int i) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
+      for (int u = 0; u < U; ++u) {
         int32_t slot;
         if (WIDE) {
-          const int32_t col = static_cast<int32_t>((static_cast<double>(static_cast<int64_t>(j) * s.K) + 0.5) * winv[u]);
+          const int64_t j = c * kChunk + 16 * h + i;
+          const int32_t col = static_cast<int32_t>((static_cast<double>(j * s.K) + 0.5) * winv[u]);
           slot = min(max(col, c_lo - 1), c_hi);
         } else {
           // quotient clamped to the guards first: both are integers, so truncation commutes with the clamp
-          slot = static_cast<int32_t>(__builtin_amdgcn_fmed3f(fmaf(static_cast<float>(j), kinv[u], hinv[u]), lo_f, hi_f));
+          slot = static_cast<int32_t>(__builtin_amdgcn_fmed3f(fmaf(jf + static_cast<float>(i), kinv[u], hinv[u]), lo_f, hi_f));
         }
         atomicAdd(&bins[base[u] + slot], static_cast<double>(acc[u][i]));
       }
     };
     __syncthreads();  // bins are clear (and, after the first pass, the previous part has left them)
     if (cb < ce) {
-      // A SIMD holds two waves of this kernel: one's matrix products run under the other's binning.
+      // A SIMD holds two to four waves of this kernel: one's matrix products run under the other's binning.
       // Within the wave the next chunk's fragments are requested as soon as the products have
       // consumed the current ones, and arrive while the products are binned.
-      bf16x8 kf[MS];
-      request(kf, cb);
       for (int32_t c = cb; c < ce; ++c) {
-        floatx16 acc[2];
+        floatx16 acc[U];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int i = 0; i < 16; ++i) acc[u][i] = 0.f;
 #pragma unroll
         for (int st = 0; st < MS; ++st) {
-          acc[0] = mfma32(kf[st], qf[0][st], acc[0]);
-          acc[1] = mfma32(kf[st], qf[1][st], acc[1]);
+#pragma unroll
+          for (int u = 0; u < U; ++u) acc[u] = mfma32(kf[st], qf[u][st], acc[u]);
         }
+        const float jf = static_cast<float>(c * kChunk + 16 * h);  // (exact, as is jf + i)
         __builtin_amdgcn_sched_barrier(0);
         if (c + 1 < ce) request(kf, c + 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) bin(acc, c, i);
+        for (int i = 0; i < 16; ++i) bin(acc, c, jf, i);
       }
     }
     __syncthreads();  // every product of the part is in its bin
-    // row sums of the part: lane (q, h) adds the columns c = h (mod 2) of its two rows, the halves
+    // row sums of the part: lane (q, h) adds the columns c = h (mod 2) of its rows, the halves
     // meet by a lane swap
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
       const double* row = bins + (32 * u + q) * stride + 1;
       double part_sum = 0.0;
       for (int32_t c = h; c < ncols; c += 2) part_sum += row[c];
@@ -305,35 +313,34 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
     }
     if (passes > 1) {
       // more parts than the block has waves: the bins leave as they are, the rows are scaled at the end
-      for (int32_t row = rsub; row < kTileRows && r0 + row < s.T; row += kTileRows >> cshift)
+      for (int32_t row = rsub; row < kTileRows && r0 + row < s.T; row += 64 >> cshift)
         if (csub < ncols)
           A_hat[(head * s.T + r0 + row) * s.K + c_lo + csub] = static_cast<float>(bins[row * stride + 1 + csub]);
     }
   }
   if (h == 0) {
-    tot_s[q * P + wave] = rowtot[0];
-    tot_s[(32 + q) * P + wave] = rowtot[1];
+#pragma unroll
+    for (int u = 0; u < U; ++u) tot_s[(32 * u + q) * P + wave] = rowtot[u];
   }
   __syncthreads();
-  double* inv_s = tot_s + kTileRows * P;  // [64] 1 / row sum
-  if (wave == 0) {
+  double* inv_s = tot_s + kTileRows * P;  // [rows] 1 / row sum
+  if (wave == 0 && lane < kTileRows) {
     double total = 0.0;
     for (int32_t w = 0; w < P; ++w) total += tot_s[lane * P + w];
     inv_s[lane] = (r0 + lane < len && total > 0.0) ? 1.0 / total : 0.0;
   }
   __syncthreads();
-  if (NCT > 0 && !A_hat) {
-  } else if (passes == 1) {
+  if (passes == 1 && (NCT == 0 || A_hat)) {
     const int32_t c_lo = min(wave * part_cols, s.K), ncols = min(s.K, c_lo + part_cols) - c_lo;
-    for (int32_t row = rsub; row < kTileRows && r0 + row < s.T; row += kTileRows >> cshift)
+    for (int32_t row = rsub; row < kTileRows && r0 + row < s.T; row += 64 >> cshift)
       if (csub < ncols)
         A_hat[(head * s.T + r0 + row) * s.K + c_lo + csub] =
             static_cast<float>(bins[row * stride + 1 + csub] * inv_s[row]);
-  } else {
+  } else if (passes > 1) {
     // every lane scales the values it wrote itself (same wave, same part, same lane mapping)
     for (int32_t pass = 0; pass < passes; ++pass) {
       const int32_t c_lo = min((pass * P + wave) * part_cols, s.K), ncols = min(s.K, c_lo + part_cols) - c_lo;
-      for (int32_t row = rsub; row < kTileRows && r0 + row < s.T; row += kTileRows >> cshift)
+      for (int32_t row = rsub; row < kTileRows && r0 + row < s.T; row += 64 >> cshift)
         if (csub < ncols) {
           float* out = A_hat + (head * s.T + r0 + row) * s.K + c_lo + csub;
           *out = static_cast<float>(static_cast<double>(*out) * inv_s[row]);
@@ -342,8 +349,8 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
   }
   if constexpr (NCT > 0) {
     const int lr = lane & 15, lg = lane >> 4;
-    const int32_t row = 16 * wave + lr, t = r0 + row;  // (waves past the fourth have no rows)
-    const bool active = wave < 4 && t < len;
+    const int32_t row = 16 * wave + lr, t = r0 + row;  // (the other waves have no rows)
+    const bool active = wave < 2 * U && t < len;
     const int32_t Tw = t + 1, ncnd = active ? min(s.K, Tw) : 0;  // columns that hold a key
     const uint32_t nsel = static_cast<uint32_t>(min(s.k_hat, ncnd));
     const int32_t w0 = Tw / s.K, rm = Tw - w0 * s.K;
@@ -351,25 +358,30 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
     // first key of column c: ceil(c (t + 1) / K)
     auto start = [&](int32_t c) { return c * w0 + div_small(c * rm + s.K - 1, invK); };
     uint32_t key[NCT][4];
-    if (wave < 4) {
+    if (wave < 2 * U) {
       const double inv = inv_s[row];
       const uint32_t by_part = 65536u / static_cast<uint32_t>(part_cols) + 1u;  // c / part_cols, exact for c < 256
+      const double* const row_bins = lds + row * stride + 1;
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct) {
         const int32_t c0 = 16 * ct + 4 * lg;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int32_t c = min(c0 + i, s.K - 1);
-          const int32_t part = static_cast<int32_t>((static_cast<uint32_t>(c) * by_part) >> 16);
-          const double sum = lds[(part * kTileRows + row) * stride + 1 + c - part * part_cols];
+          int32_t at = ct / 2 * (kTileRows * stride) + 16 * (ct & 1) + 4 * lg + i;  // parts of 32 columns
+          if (part_cols != 32 || 16 * ct + 16 > s.K) {
+            const int32_t c = min(c0 + i, s.K - 1);
+            const int32_t part = static_cast<int32_t>((static_cast<uint32_t>(c) * by_part) >> 16);
+            at = part * kTileRows * stride + c - part * part_cols;
+          }
+          const double sum = row_bins[at];
           bool cand = active && c0 + i < s.K;
-          if (w0 == 0) cand = cand && start(c + 1) > start(c);
+          if (w0 == 0) cand = cand && start(c0 + i + 1) > start(c0 + i);
           key[ct][i] = cand ? __float_as_uint(static_cast<float>(sum * inv)) | 0x80000000u : 0x40000000u;
         }
       }
     }
     __syncthreads();  // the bins are in registers: their place takes the rows' key bits
-    if (wave >= 4) return;
+    if (wave >= 2 * U) return;
     uint32_t nib[NCT];
     select_columns<NCT>(key, nsel, ncnd, NCT, s.k_hat, lg, nib);
     if (mbits) {
@@ -383,7 +395,7 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
     // words of the 128-row tile the attention may look at; one word of padding per row keeps the rows' words in
     // different banks
     const int32_t nw = min(KWk, ((r0 | 127) >> 5) + 1), wstride = nw | 1;
-    uint32_t* const words = reinterpret_cast<uint32_t*>(bins);
+    uint32_t* const words = reinterpret_cast<uint32_t*>(lds + static_cast<size_t>(wave) * (P / (2 * U)) * kTileRows * stride);
     for (int32_t x = lane; x < 16 * wstride; x += 64) words[x] = 0u;
     __builtin_amdgcn_wave_barrier();
     uint32_t* const wrow = words + lr * wstride;
@@ -447,18 +459,22 @@ __global__ __launch_bounds__(512) void rw_tiles_mfma_kernel(Shape s, const uint4
   }
 }
 
+// 32-row tiles of a block: one (four waves per SIMD; the selection and the start and end of a block are chains of
+// latencies: 189 -> 181 us for the forward of the kernel's comment), two where m = 256 leaves no registers for that
+constexpr int row_tiles(int m) { return m == 256 ? 2 : 1; }
+
 struct Plan {
   int32_t parts, part_cols, stride, waves, cshift;
   size_t lds;
 };
-Plan plan(const Shape& s) {
+Plan plan(const Shape& s, int32_t rows) {
   Plan p{};
   p.parts = (s.K + kPartCols - 1) / kPartCols;
   p.part_cols = (s.K + p.parts - 1) / p.parts;
   p.stride = (p.part_cols + 2) | 1;  // two guards; odd, so the 32 rows of a step fall into different banks
-  p.waves = std::min(p.parts, 8);    // eight waves' bins fit a CU's LDS: two waves per SIMD
+  p.waves = std::min(p.parts, 8);
   while ((1 << p.cshift) < p.part_cols) ++p.cshift;
-  p.lds = (static_cast<size_t>(p.waves) * kTileRows * p.stride + static_cast<size_t>(kTileRows) * (p.waves + 1)) * sizeof(double);
+  p.lds = (static_cast<size_t>(p.waves) * rows * p.stride + static_cast<size_t>(rows) * (p.waves + 1)) * sizeof(double);
   return p;
 }
 size_t side_bytes(const Shape& s) {
@@ -466,16 +482,17 @@ size_t side_bytes(const Shape& s) {
   return (static_cast<size_t>(s.N) * t32 * s.m * sizeof(uint16_t) + 255) & ~size_t(255);
 }
 
-template <int MS, bool WIDE, int NCT>
-hipError_t launch_tiles(const Shape& s, const Plan& p, const uint4* phiQ, const uint4* phiK, float* A_hat, uint32_t* mbits,
-                        uint32_t* kb, hipStream_t st) {
+template <int MS, bool WIDE, int NCT, int U>
+hipError_t launch_tiles(const Shape& s, const uint4* phiQ, const uint4* phiK, float* A_hat, uint32_t* mbits, uint32_t* kb,
+                        hipStream_t st) {
+  const Plan p = plan(s, 32 * U);
   if (p.lds > (64u << 10)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_tiles_mfma_kernel<MS, WIDE, NCT>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_tiles_mfma_kernel<MS, WIDE, NCT, U>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(p.lds));
     if (e != hipSuccess) return e;
   }
-  const uint32_t tiles = (s.T + kTileRows - 1) / kTileRows;
-  hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT>), dim3(static_cast<uint32_t>(s.N) * tiles), dim3(64 * p.waves), p.lds, st, s,
+  const uint32_t tiles = (s.T + 32 * U - 1) / (32 * U);
+  hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT, U>), dim3(static_cast<uint32_t>(s.N) * tiles), dim3(64 * p.waves), p.lds, st, s,
                      phiQ, phiK, A_hat, p.parts, p.part_cols, p.stride, p.cshift, mbits, kb, (s.T + 31) / 32);
   return hipGetLastError();
 }
@@ -499,13 +516,13 @@ hipError_t launch(const Shape& s, const uint16_t* Q, const uint16_t* K, const ui
     if (e != hipSuccess) return e;
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
-  const Plan p = plan(s);
   const bool wide = static_cast<int64_t>(s.K) * s.T > (int64_t{1} << 21);
+  constexpr int U = row_tiles(32 * MC);
   if (kb)  // K T <= 2^21 there
-    return s.K <= 128 ? launch_tiles<2 * MC, false, 8>(s, p, phiQ, phiK, A_hat, mbits, kb, st)
-                      : launch_tiles<2 * MC, false, 16>(s, p, phiQ, phiK, A_hat, mbits, kb, st);
-  return wide ? launch_tiles<2 * MC, true, 0>(s, p, phiQ, phiK, A_hat, nullptr, nullptr, st)
-              : launch_tiles<2 * MC, false, 0>(s, p, phiQ, phiK, A_hat, nullptr, nullptr, st);
+    return s.K <= 128 ? launch_tiles<2 * MC, false, 8, U>(s, phiQ, phiK, A_hat, mbits, kb, st)
+                      : launch_tiles<2 * MC, false, 16, U>(s, phiQ, phiK, A_hat, mbits, kb, st);
+  return wide ? launch_tiles<2 * MC, true, 0, 2>(s, phiQ, phiK, A_hat, nullptr, nullptr, st)
+              : launch_tiles<2 * MC, false, 0, U>(s, phiQ, phiK, A_hat, nullptr, nullptr, st);
 }
 
 }  // namespace
@@ -516,10 +533,14 @@ bool rowwidth_mfma_supported(const Shape& s, sea_dtype dt) {
 
 size_t rowwidth_mfma_workspace(const Shape& s) { return 2 * side_bytes(s); }
 
-// the selection as key bits straight from the estimate: four to eight column parts (a wave has the bins of one
-// and selects for at most 16 rows), key-bit rows of at most 256 words
+// the selection as key bits straight from the estimate: at most eight column parts, a wave for every 16 rows of a
+// block, and room for those rows' key bits in the place of the bins
 bool rowwidth_select_supported(const Shape& s, sea_dtype dt) {
-  return rowwidth_mfma_supported(s, dt) && s.grouping == 0 && s.K > 96 && s.K <= 256 && s.T <= 8192;
+  if (!rowwidth_mfma_supported(s, dt) || s.grouping != 0 || s.K > 256 || s.T > 8192) return false;
+  const int32_t U = row_tiles(s.m);
+  const Plan p = plan(s, 32 * U);
+  const size_t room = static_cast<size_t>(p.waves / (2 * U)) * 32 * U * p.stride * sizeof(double);
+  return room >= static_cast<size_t>(16) * (((s.T + 31) / 32) | 1) * sizeof(uint32_t);
 }
 
 hipError_t launch_rowwidth_mfma(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W,
