@@ -688,6 +688,242 @@ __global__ __launch_bounds__(256) void topk_group_kernel(Shape s, const float* _
 }
 
 // ------------------------------------------------------------------------------------------
+// The same selection when only the mask words are wanted and K is a power of two from 32 to 1024 (fixed key
+// buckets): a thread's column is then the same in all its groups, a group's address is a uniform base and one
+// lane offset, and a mask word is eight lanes' nibbles.
+//
+// Bound: vector issue (one block of VPT = 32 is 256 threads with 32 keys each, 64 blocks per CU at c3's size).
+// So the keys are taken raw (score bits with the sign bit set; one OR of all of them tells whether every score
+// lies in [0, 2), else the general search below reads the slab again), the first pass counts the scores from
+// 2^-15 on in bins of 1/64 octave (over whole octaves the scores of a slab crowd into a few dozen bins, and the
+// LDS adds of a wave queue at the same words), and the few keys of the threshold's bin are ranked directly
+// instead of by two more passes.  B = 8, H = 32, T = 2048, K = 256, k^ = 64: 147 -> 110 us.
+// ------------------------------------------------------------------------------------------
+constexpr uint32_t kRanked = 64;  // keys of a bin that one wave ranks
+template <int VPT>
+__global__ __launch_bounds__(256) void topk_group_bits_kernel(Shape s, const float* __restrict__ A_hat,
+                                                              uint32_t* __restrict__ mbits) {
+  constexpr int G = VPT / 4;
+  __shared__ __align__(16) uint32_t hist[2048];
+  __shared__ uint32_t scan[4], red[2][4], found[3], list[kRanked], listed;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int32_t t = static_cast<int32_t>(blockIdx.x % s.T);
+  const int32_t b = static_cast<int32_t>(blockIdx.x / s.T);
+  const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
+  const int32_t kw = s.K >> 5, klog = 31 - __clz(s.K), hstep = 1024 >> klog;  // heads per group
+  const int32_t jmax = t < len ? (s.causal ? t : len - 1) : -1;
+  const int32_t ncand = jmax >= 0 ? bucket_of(jmax, s.T, s.K) + 1 : 0;
+  const uint32_t total = static_cast<uint32_t>(s.H * ncand), n = static_cast<uint32_t>(s.H * min(s.k_hat, ncand));
+  // the thread's first head and its column; group gi is hstep gi heads further on
+  const int32_t gh = (4 * tid) >> klog, gc = 4 * tid & (s.K - 1);
+  const int32_t nvalid = min(max(ncand - gc, 0), 4);
+  const float* slab = A_hat + (static_cast<int64_t>(b) * s.H * s.T + t) * s.K;  // head 0 of the step
+  const uint32_t lane_off = static_cast<uint32_t>(gh) * static_cast<uint32_t>(s.T) * s.K + gc;  // (below 2^29)
+  const int64_t gstride = static_cast<int64_t>(hstep) * s.T * s.K;
+  auto valid = [&](int gi) { return gh < s.H - gi * hstep ? nvalid : 0; };
+
+  uint32_t key[VPT];  // 0: no candidate
+  uint32_t all_bits = 0u;
+  constexpr int kBatch = G < 8 ? G : 8;  // loads in flight
+#pragma unroll
+  for (int g0 = 0; g0 < G; g0 += kBatch) {
+    float4 f[kBatch];
+#pragma unroll
+    for (int gj = 0; gj < kBatch; ++gj) {
+      const int gi = g0 + gj;
+      f[gj] = make_float4(0.f, 0.f, 0.f, 0.f);
+      // (a lane without a candidate reads the group's first column; a uniform branch skips groups past the heads)
+      if (gi * hstep < s.H) f[gj] = *reinterpret_cast<const float4*>(slab + gi * gstride + (valid(gi) > 0 ? lane_off : 0u));
+    }
+#pragma unroll
+    for (int gj = 0; gj < kBatch; ++gj) {
+      const int nv = valid(g0 + gj);
+      const float fv[4] = {f[gj].x, f[gj].y, f[gj].z, f[gj].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t u = q < nv ? __float_as_uint(fv[q]) : 0u;
+        all_bits |= u;
+        key[4 * (g0 + gj) + q] = q < nv ? (u | 0x80000000u) : 0u;
+      }
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x) reinterpret_cast<uint4*>(hist)[tid + 256 * x] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) listed = 0u;
+  const bool in_range = __syncthreads_and((all_bits >> 30) == 0u ? 1 : 0) != 0;
+
+  // tau with c_ge keys >= tau, c_gt of them above it
+  uint32_t tau = 0x80000000u, c_ge = total, c_gt = 0u;
+  if (n != total && in_range) {
+    uint32_t shift = 16, width = 11, prefix = 0xb8000000u, end = 0xc0000000u, need = n;  // keys in [prefix, end)
+    for (;;) {
+      const uint32_t nb = 1u << width;
+#pragma unroll
+      for (int v = 0; v < VPT; ++v)
+        if (key[v] >= prefix && key[v] < end) atomicAdd(&hist[(key[v] >> shift) & (nb - 1u)], 1u);
+      __syncthreads();
+      // thread tid owns eight consecutive bins (one in a pass of 256)
+      uint32_t h[8];
+      if (width == 11) {
+        const uint4 lo = reinterpret_cast<const uint4*>(hist)[2 * tid], hi = reinterpret_cast<const uint4*>(hist)[2 * tid + 1];
+        h[0] = lo.x; h[1] = lo.y; h[2] = lo.z; h[3] = lo.w; h[4] = hi.x; h[5] = hi.y; h[6] = hi.z; h[7] = hi.w;
+      } else {
+        h[0] = hist[tid];
+#pragma unroll
+        for (int q = 1; q < 8; ++q) h[q] = 0u;
+      }
+      uint32_t incl = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += o;
+      }
+      if (lane == kWave - 1) scan[wid] = incl;
+      __syncthreads();
+      const uint32_t all = scan[0] + scan[1] + scan[2] + scan[3];
+      for (int q = 0; q < wid; ++q) incl += scan[q];
+      uint32_t g = all - incl;  // keys of the pass in bins above this thread's
+      if (all >= need && g < need) {
+#pragma unroll
+        for (int q = 7; q >= 0; --q) {
+          if (g < need && g + h[q] >= need) {
+            found[0] = width == 11 ? 8 * tid + q : tid;
+            found[1] = g;
+            found[2] = h[q];
+          }
+          g += h[q];
+        }
+      }
+      // (every thread has read its bins)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) reinterpret_cast<uint4*>(hist)[tid + 256 * x] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+      if (all < need) {  // fewer than n scores reach 2^-15: over all octaves, in bins of 1/8
+        prefix = 0x80000000u;
+        shift = 19;
+        continue;
+      }
+      const uint32_t at = found[2];
+      tau = prefix | (found[0] << shift);
+      need -= found[1];
+      c_gt = n - need;
+      c_ge = c_gt + at;
+      if (c_ge == n || shift == 0) break;
+      if (at <= kRanked) {
+        // the bin's keys, ranked: every wave finds the need-th largest of them
+#pragma unroll
+        for (int v = 0; v < VPT; ++v)
+          if (((key[v] ^ tau) >> shift) == 0u) list[atomicAdd(&listed, 1u)] = key[v];
+        __syncthreads();
+        const uint32_t mine = static_cast<uint32_t>(lane) < at ? list[lane] : 0u;
+        uint32_t above = 0u, from = 0u;
+        for (uint32_t i = 0; i < at; ++i) {
+          const uint32_t o = list[i];
+          above += o > mine ? 1u : 0u;
+          from += o >= mine ? 1u : 0u;
+        }
+        const int who = __builtin_ctzll(__ballot(static_cast<uint32_t>(lane) < at && above < need && need <= from));
+        tau = __builtin_amdgcn_readlane(mine, who);
+        c_ge = c_gt + __builtin_amdgcn_readlane(from, who);
+        c_gt += __builtin_amdgcn_readlane(above, who);
+        break;
+      }
+      prefix = tau;
+      end = tau + (1u << shift);
+      width = shift == 19 ? 11 : 8;
+      shift = shift == 19 || shift == 16 ? 8 : 0;
+    }
+  } else if (n != total) {
+    // some score is negative, 2 or more, or no number: ordered keys, one bit per step
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        key[4 * gi + q] = q < valid(gi) ? ordered_key(slab[gi * gstride + lane_off + q]) : 0u;
+    tau = 0u;
+    c_ge = 256u * VPT;
+#pragma unroll 1
+    for (int bit = 31; bit >= 0 && c_ge != n; --bit) {
+      const uint32_t trial = tau | (1u << bit);
+      uint32_t c = 0;
+#pragma unroll
+      for (int v = 0; v < VPT; ++v) c += key[v] >= trial ? 1u : 0u;
+      c = wave_sum_u32(c);
+      if (lane == 0) red[bit & 1][wid] = c;
+      __syncthreads();  // the buffers alternate, so one barrier per step is enough
+      const uint32_t ct = red[bit & 1][0] + red[bit & 1][1] + red[bit & 1][2] + red[bit & 1][3];
+      if (ct >= n) { tau = trial; c_ge = ct; }
+    }
+    if (c_ge != n) {
+      uint32_t c = 0;
+#pragma unroll
+      for (int v = 0; v < VPT; ++v) c += key[v] > tau ? 1u : 0u;
+      c = wave_sum_u32(c);
+      __syncthreads();
+      if (lane == 0) red[0][wid] = c;
+      __syncthreads();
+      c_gt = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    }
+  } else if (!in_range) {
+    // every candidate is taken
+#pragma unroll
+    for (int v = 0; v < VPT; ++v) key[v] = (v & 3) < valid(v >> 2) ? 0x80000000u : 0u;
+  }
+
+  uint32_t* const mstep = mbits + (static_cast<int64_t>(b) * s.H * s.T + t) * kw;
+  const uint32_t word_off = static_cast<uint32_t>(gh) * static_cast<uint32_t>(s.T) * kw + (gc >> 5);
+  const int64_t wstride = static_cast<int64_t>(hstep) * s.T * kw;
+  auto put = [&](int gi, uint32_t nib) {
+    uint32_t word = nib << (4 * (lane & 7));
+    word |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(word), 0xB1, 0xf, 0xf, false));
+    word |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(word), 0x4E, 0xf, 0xf, false));
+    word |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(word), 0x141, 0xf, 0xf, false));
+    if ((lane & 7) == 0 && gh < s.H - gi * hstep) mstep[gi * wstride + word_off] = word;
+  };
+  if (c_ge == n) {
+    const uint32_t least = n == 0u ? 0xffffffffu : tau;  // (no key is that large)
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi) {
+      uint32_t nib = 0;
+#pragma unroll
+      for (int q = 3; q >= 0; --q) nib = nib + nib + (key[4 * gi + q] >= least ? 1u : 0u);
+      put(gi, nib);
+    }
+    return;
+  }
+  // ties at the threshold, lowest flattened index first: the groups in order, each with an exclusive prefix
+  // over the threads of its number of entries equal to tau
+  const uint32_t need_eq = n - c_gt;
+  uint32_t base = 0;
+#pragma unroll
+  for (int gi = 0; gi < G; ++gi) {
+    uint32_t my_eq = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) my_eq += key[4 * gi + q] == tau ? 1u : 0u;
+    uint32_t incl = my_eq;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const uint32_t o = __shfl_up(incl, off, kWave);
+      if (lane >= off) incl += o;
+    }
+    __syncthreads();  // scan[] has been read
+    if (lane == kWave - 1) scan[wid] = incl;
+    __syncthreads();
+    uint32_t before = base + incl - my_eq;
+    for (int q = 0; q < wid; ++q) before += scan[q];
+    base += scan[0] + scan[1] + scan[2] + scan[3];
+    uint32_t nib = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool eq = key[4 * gi + q] == tau;
+      if (key[4 * gi + q] > tau || (eq && before < need_eq)) nib |= 1u << q;
+      before += eq ? 1u : 0u;
+    }
+    put(gi, nib);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // The selection of a row, expanded to one bit per key (Sec. 3.1 "Linear Sparse Attention Mask
 // Generation", with App. A.4's per-row widths when geometry = 1; App. A.5.3 for the replication
 // cap): bit j of row t is set iff key j belongs to a selected column of that row and is one of the
@@ -773,7 +1009,14 @@ hipError_t launch_topk_mask(const Shape& s, const float* A_hat, int32_t* sel, in
     const int vpt = (HK + 255) / 256;
     const dim3 ggrid(static_cast<uint32_t>(s.N / s.H) * s.T);
     const size_t shm = static_cast<size_t>(HK);
-    if (vpt <= 4) hipLaunchKernelGGL(topk_group_kernel<4>, ggrid, block, shm, st, s, A_hat, sel_g, idx_g, cnt_g, mbits);
+    if (mbits && !sel_g && !idx_g && !cnt_g && s.geometry == 0 && s.K >= 32 && s.K <= 1024 && (s.K & (s.K - 1)) == 0 && vpt <= 64 &&
+        static_cast<int64_t>(s.T) << 10 < (int64_t{1} << 29)) {
+      if (vpt <= 4) hipLaunchKernelGGL(topk_group_bits_kernel<4>, ggrid, block, 0, st, s, A_hat, mbits);
+      else if (vpt <= 8) hipLaunchKernelGGL(topk_group_bits_kernel<8>, ggrid, block, 0, st, s, A_hat, mbits);
+      else if (vpt <= 16) hipLaunchKernelGGL(topk_group_bits_kernel<16>, ggrid, block, 0, st, s, A_hat, mbits);
+      else if (vpt <= 32) hipLaunchKernelGGL(topk_group_bits_kernel<32>, ggrid, block, 0, st, s, A_hat, mbits);
+      else hipLaunchKernelGGL(topk_group_bits_kernel<64>, ggrid, block, 0, st, s, A_hat, mbits);
+    } else if (vpt <= 4) hipLaunchKernelGGL(topk_group_kernel<4>, ggrid, block, shm, st, s, A_hat, sel_g, idx_g, cnt_g, mbits);
     else if (vpt <= 8) hipLaunchKernelGGL(topk_group_kernel<8>, ggrid, block, shm, st, s, A_hat, sel_g, idx_g, cnt_g, mbits);
     else if (vpt <= 16) hipLaunchKernelGGL(topk_group_kernel<16>, ggrid, block, shm, st, s, A_hat, sel_g, idx_g, cnt_g, mbits);
     else if (vpt <= 32) hipLaunchKernelGGL(topk_group_kernel<32>, ggrid, block, shm, st, s, A_hat, sel_g, idx_g, cnt_g, mbits);
