@@ -391,10 +391,13 @@ __global__ __launch_bounds__(256) void wide_columns_kernel(Shape s, const float*
 // the running sum of the current column; before each tile that a column began in front of, the sum of
 // that column's earlier keys goes out as fp32.
 // Bound: vector and matrix issue together.  B = 8, H = 32, T = 2000, K = 256, m = 256: 0.10 ms (1.54 ms with
-// the three kernels that write the features to memory, rows kernel and selection included: 0.25 ms).
+// the three kernels that write the features to memory, rows kernel and selection included: 0.25 ms).  Columns
+// of four keys or more (BY4) take two fp32 products per 16 features and keys instead of four, and the rows of
+// the next tile and step are requested ahead: whole forward 513 -> 502 us, B = 4, H = 12, T = 2041, m = K = 128
+// 107 -> 104 us.
 // ------------------------------------------------------------------------------------------
-template <int MC, bool CAUSAL>
-__global__ __launch_bounds__(256) void key_columns_kernel(Shape s, Columns cg, const uint16_t* __restrict__ K,
+template <int MC, bool CAUSAL, bool BY4>
+__global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg, const uint16_t* __restrict__ K,
                                                           const uint16_t* __restrict__ W, uint16_t* __restrict__ state,
                                                           float* __restrict__ pref, float c_dot, float c_norm,
                                                           int32_t G) {
@@ -429,13 +432,22 @@ __global__ __launch_bounds__(256) void key_columns_kernel(Shape s, Columns cg, c
 
   const int32_t base = key0 & ~15;
   const int32_t nsteps = key1 > key0 ? (key1 - base + 63) / 64 : 0;
+  // rows requested ahead: the next tile's, and the next step's own tile for its norms
+  bf16x8 x0, x1, y0, y1;
+  auto request = [&](int32_t j, bf16x8& a, bf16x8& b) {
+    const uint16_t* X = Kh + static_cast<int64_t>(max(min(j, len - 1), 0)) * kHeadDim;
+    a = *reinterpret_cast<const bf16x8*>(X + 8 * lg);
+    b = *reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg);
+  };
+  request(base + 16 * wid + lr, y0, y1);
+  request(base + lr, x0, x1);
   for (int32_t st = 0; st < nsteps; ++st) {
     const int32_t s0 = base + 64 * st, buf = st & 1;
     {
       // norm and local column of key s0 + 16 wid + lr (keys outside the block's columns: no column)
       const int32_t j = s0 + 16 * wid + lr;
-      const uint16_t* X = Kh + static_cast<int64_t>(min(j, len - 1)) * kHeadDim;
-      float nx = sumsq8(*reinterpret_cast<const bf16x8*>(X + 8 * lg)) + sumsq8(*reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg));
+      float nx = sumsq8(y0) + sumsq8(y1);
+      request(j + 64, y0, y1);
       nx += __shfl_xor(nx, 16, kWave);
       nx += __shfl_xor(nx, 32, kWave);
       if (lg == 0) {
@@ -448,13 +460,26 @@ __global__ __launch_bounds__(256) void key_columns_kernel(Shape s, Columns cg, c
     for (int tile = 0; tile < 4; ++tile) {
       const int32_t r0 = s0 + 16 * tile;
       if (r0 >= key1) break;
-      const uint16_t* X = Kh + static_cast<int64_t>(min(r0 + lr, len - 1)) * kHeadDim;
-      const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(X + 8 * lg);
-      const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg);
+      const bf16x8 k0 = x0, k1 = x1;
+      request(r0 + 16 + lr, x0, x1);
       const float4 bias = *reinterpret_cast<const float4*>(&bias_s[buf][16 * tile + 4 * lg]);
       const int4 cl = *reinterpret_cast<const int4*>(&col_s[buf][16 * tile + 4 * lg]);
       const float bv[4] = {bias.x, bias.y, bias.z, bias.w};
       const float oh[4] = {cl.x == lr ? 1.f : 0.f, cl.y == lr ? 1.f : 0.f, cl.z == lr ? 1.f : 0.f, cl.w == lr ? 1.f : 0.f};
+      // BY4 (columns of at least four keys): the lane's four keys lie in one column or two; they are added up
+      // per column, weighted 0 or 1, and the products take the two sums
+      float in0[4], in1[4], oh0 = 0.f, oh1 = 0.f;
+      if (BY4) {
+        const int32_t second = cl.y != cl.x ? cl.y : (cl.z != cl.x ? cl.z : cl.w);
+        const int32_t c4[4] = {cl.x, cl.y, cl.z, cl.w};
+        oh0 = oh[0];
+        oh1 = second == lr && second != cl.x ? 1.f : 0.f;
+#pragma unroll
+        for (int i = 1; i < 4; ++i) {
+          in0[i] = c4[i] == cl.x ? 1.f : 0.f;
+          in1[i] = c4[i] == second ? 1.f : 0.f;  // (oh1 = 0 where that is the first column)
+        }
+      }
       shortx4 ohb;
       if (CAUSAL) {
         const uint2 u = {pack_bf16(oh[0], oh[1]), pack_bf16(oh[2], oh[3])};
@@ -474,13 +499,20 @@ __global__ __launch_bounds__(256) void key_columns_kernel(Shape s, Columns cg, c
 #pragma unroll
       for (int ft = 0; ft < FT; ++ft) {
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mfma16(x0, w0[ft], acc);
-        acc = mfma16(x1, w1[ft], acc);
+        acc = mfma16(k0, w0[ft], acc);
+        acc = mfma16(k1, w1[ft], acc);
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, acc[i], -bv[i]));
+        if (BY4) {
+          const float a = fmaf(in0[3], v[3], fmaf(in0[2], v[2], fmaf(in0[1], v[1], v[0])));
+          const float c = fmaf(in1[3], v[3], fmaf(in1[2], v[2], in1[1] * v[1]));
+          sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh0, a, sum[ft], 0, 0, 0);
+          sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh1, c, sum[ft], 0, 0, 0);
+        } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh[i], v[i], sum[ft], 0, 0, 0);
+          for (int i = 0; i < 4; ++i) sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh[i], v[i], sum[ft], 0, 0, 0);
+        }
         if (CAUSAL) {
           const uint2 u = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
           rsum[ft] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ohb, __builtin_bit_cast(shortx4, u), rsum[ft], 0, 0, 0);
@@ -1108,10 +1140,13 @@ void launch_key_columns(const Shape& s, const uint16_t* K, const uint16_t* W, co
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.K + G - 1) / G));
   float* pref = reinterpret_cast<float*>(f.pref);
   const Columns cg = columns_of(s.T, s.K);
-  if (s.causal)
-    hipLaunchKernelGGL((key_columns_kernel<MC, true>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G);
-  else
-    hipLaunchKernelGGL((key_columns_kernel<MC, false>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G);
+#define SEA_KEY_COLUMNS(CAUSAL_, BY4_) \
+  hipLaunchKernelGGL((key_columns_kernel<MC, CAUSAL_, BY4_>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G)
+  if (s.causal && w0 >= 4) SEA_KEY_COLUMNS(true, true);
+  else if (s.causal) SEA_KEY_COLUMNS(true, false);
+  else if (w0 >= 4) SEA_KEY_COLUMNS(false, true);
+  else SEA_KEY_COLUMNS(false, false);
+#undef SEA_KEY_COLUMNS
 }
 
 template <int MC, int NCT>
