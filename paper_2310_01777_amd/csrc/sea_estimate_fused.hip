@@ -769,6 +769,8 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
     if (lane < kPieces) preg0 = psrc[lane];
     if (lane + 64 < kPieces) preg1 = psrc[lane + 64];
   }
+  // bidirectional: the same candidates for every row (taken here, while the rows are on their way)
+  const int32_t ncnd_all = CAUSAL ? 0 : __builtin_amdgcn_readfirstlane(col_of(max(len - 1, 0)) + 1);
   stage_w(W, Ws, m, tid);
   if (ANYW && tile_planes) {
     uint16_t* pdst = &planes_s[wid * 3 * m + lane * kPieceLen];
@@ -942,9 +944,9 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
 
   // ---- masking, the own column, normalisation, selection ----
   const int32_t trow = r0 + lr;
-  const int32_t ncnd = trow < len ? col_of(CAUSAL ? min(trow, len - 1) : len - 1) + 1 : 0;
+  const int32_t ncnd = trow < len ? (CAUSAL ? col_of(min(trow, len - 1)) + 1 : ncnd_all) : 0;
   const bool act_all = r0 + 15 < len;  // wave-uniform
-  const int32_t ct_free = act_all ? __builtin_amdgcn_readfirstlane(col_of(CAUSAL ? r0 : len - 1)) >> 4 : 0;
+  const int32_t ct_free = act_all ? (CAUSAL ? __builtin_amdgcn_readfirstlane(col_of(r0)) : ncnd_all - 1) >> 4 : 0;
   finish_rows<CAUSAL, NCT>(s, acc, head, trow, ncnd, ct_free, ncols_wave, diag, lg, A_hat, mbits);
 }
 
