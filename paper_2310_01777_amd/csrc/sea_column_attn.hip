@@ -15,15 +15,15 @@
 // then lowers exactly the unselected scores by 2^127 and adds exact zeros to the others.  Building
 // the query side takes nine vector instructions per sub-chunk from the row's mask window.
 //
-// The softmax weights go into the second product as the sum of two bf16 values (the rounded weight
-// and the rounded remainder, 16 significant bits): these shapes used to run on the per-row kernel,
-// which multiplies in fp32.
+// The softmax weights go into the second product as the sum of three bf16 values (sea_tile.h), i.e. as the
+// fp32 numbers they are: products of weights and values are exact, as in the per-row kernel.
 //
-// Bound: vector issue, as in the power-of-two kernel (about 190 vector instructions and 13 matrix
-// products per 32-key sub-chunk and wave; three waves per SIMD: held to four the compiler spills 14
-// registers and the kernel is 15 % slower).  Measured on the layer B = 8, H = 32, T = 2000 (padded by
-// 0-25 %), K = 256, k^ = 64: 0.29 ms; the per-row gather kernel that ran before took 2.71 ms and its
-// key lists another 0.57 ms to write.  Small launches take as long as their longest list: there three or six sets
+// Bound: vector issue, as in the power-of-two kernel (about 200 vector instructions and 17 matrix
+// products per 32-key sub-chunk and wave; three waves per SIMD: held to four the compiler spills
+// registers and the kernel is slower).  Measured on the layer B = 8, H = 32, T = 2000 (padded by
+// 0-25 %), K = 256, k^ = 64: 0.32 ms (0.29 ms with weights of 16 significant bits, 27 instructions and
+// four products fewer); the per-row gather kernel that ran before took 2.71 ms and its key lists another
+// 0.57 ms to write.  Small launches take as long as their longest list: there three or six sets
 // of waves share it.
 #include "sea_columns.h"
 #include "sea_internal.h"
@@ -202,10 +202,7 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   constexpr float kRefSlack = 8.f;
   const uint32_t gmask = (NX == 8 && g != 0) ? 0u : 0x40004000u;  // NX = 8: the upper half's slots are unused
 
-  // {-1, 0} and {0, -1} as bf16 pairs, kept in scalar registers: written as constants, the first is
-  // encoded as the inline operand -1.0, which the instruction reads as the fp32 pattern = {0, -1}
-  uint32_t neg_lo_bits = 0x0000bf80u, neg_hi_bits = 0xbf800000u;
-  asm volatile("" : "+s"(neg_lo_bits), "+s"(neg_hi_bits));
+  const MinusOnes minus = minus_ones();
 
   if (nsteps > 0) {
     SEA_CFETCH();
@@ -283,36 +280,8 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
 #pragma unroll
         for (int i = 0; i < 16; ++i) y[i] -= delta;
       }
-      // weights as rounded value + rounded remainder; the row sum is taken over what the products
-      // use.  O^T += V^T P^T, V^T fragments in the key order of the P registers.
-      const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-      const bf16x2 neg_lo = __builtin_bit_cast(bf16x2, neg_lo_bits), neg_hi = __builtin_bit_cast(bf16x2, neg_hi_bits);
-      auto frag = [](const bf16x2* p) {
-        const bf16x4 lo = __builtin_shufflevector(p[0], p[1], 0, 1, 2, 3);
-        const bf16x4 hi = __builtin_shufflevector(p[2], p[3], 0, 1, 2, 3);
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      };
-#pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2) {
-        bf16x2 h[4], l[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float p0 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * e]), p1 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * e + 1]);
-          const floatx2 f2 = {p0, p1};
-          h[e] = __builtin_convertvector(f2, bf16x2);
-          const floatx2 r2 = {__builtin_amdgcn_fdot2_f32_bf16(h[e], neg_lo, p0, false),
-                              __builtin_amdgcn_fdot2_f32_bf16(h[e], neg_hi, p1, false)};
-          l[e] = __builtin_convertvector(r2, bf16x2);
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(h[e], ones, l_run, false);
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(l[e], ones, l_run, false);
-        }
-        const bf16x8 ph = frag(h), pl = frag(l);
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], ph, oacc[mt], 0, 0, 0);
-          oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], pl, oacc[mt], 0, 0, 0);
-        }
-      }
+      // O^T += V^T P^T, V^T fragments in the key order of the P registers
+      l_run += add_weighted_rows(y, av, minus, oacc);
     }
     if (step + 1 < nsteps) SEA_CPARK(stage ^ 1);
     __syncthreads();

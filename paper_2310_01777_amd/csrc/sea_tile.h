@@ -31,6 +31,56 @@ __device__ __forceinline__ float half_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// O^T += V^T P^T for one 32-key sub-chunk with weights p = 2^y held in fp32: a weight enters the bf16 product
+// as the sum of three bf16 values, its rounded value, the rounded remainder and what then remains.  Eight
+// significant bits each, to nearest, cover the 24 of an fp32 number, so the products are those of the fp32
+// weights (two values, 16 bits, left an error of 2^-18 of an output row's values against 2^-24).  Register
+// order of y: key slot 8 (i / 4) + 4 g + i % 4 of register i; av = V^T fragments in that order.  Returns the
+// sum of the weights.
+struct MinusOnes {
+  bf16x2 lo, hi;  // {-1, 0}, {0, -1}
+};
+// (kept in scalar registers: written as constants, the first is encoded as the inline operand -1.0, which
+// the dot product reads as the fp32 pattern = {0, -1})
+__device__ __forceinline__ MinusOnes minus_ones() {
+  uint32_t lo = 0x0000bf80u, hi = 0xbf800000u;
+  asm volatile("" : "+s"(lo), "+s"(hi));
+  return {__builtin_bit_cast(bf16x2, lo), __builtin_bit_cast(bf16x2, hi)};
+}
+__device__ __forceinline__ bf16x8 join_pairs(const bf16x2* p) {
+  const bf16x4 lo = __builtin_shufflevector(p[0], p[1], 0, 1, 2, 3);
+  const bf16x4 hi = __builtin_shufflevector(p[2], p[3], 0, 1, 2, 3);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+__device__ __forceinline__ float add_weighted_rows(const float (&y)[16], const bf16x8 (&av)[2][2], const MinusOnes& minus,
+                                                   floatx16 (&oacc)[2]) {
+  float sum = 0.f;
+#pragma unroll
+  for (int c2 = 0; c2 < 2; ++c2) {
+    bf16x2 part[3][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      floatx2 f = {__builtin_amdgcn_exp2f(y[8 * c2 + 2 * e]), __builtin_amdgcn_exp2f(y[8 * c2 + 2 * e + 1])};
+      sum += f[0];
+      sum += f[1];
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        part[n][e] = __builtin_convertvector(f, bf16x2);
+        if (n < 2)
+          f = floatx2{__builtin_amdgcn_fdot2_f32_bf16(part[n][e], minus.lo, f[0], false),
+                      __builtin_amdgcn_fdot2_f32_bf16(part[n][e], minus.hi, f[1], false)};
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < 3; ++n) {
+      const bf16x8 p = join_pairs(part[n]);
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], p, oacc[mt], 0, 0, 0);
+    }
+  }
+  return sum;
+}
+
 // raw buffer resource, word 3: 32-bit data format, no swizzle; loads past num_records return zero
 constexpr int kBufferFlags = 0x00020000;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
