@@ -338,10 +338,7 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
   float m_ref = 0.f, m_thr = -INFINITY, l_run = 0.f;
   constexpr float kRefSlack = 8.f;
   const float c = s.scale * kLog2e;
-  // bf16 pairs {-1, 0} and {0, -1} (in registers: the first would be encoded as the inline operand
-  // -1.0, which the dot product reads as its fp32 pattern)
-  uint32_t neg_lo_bits = 0x0000bf80u, neg_hi_bits = 0xbf800000u;
-  asm volatile("" : "+s"(neg_lo_bits), "+s"(neg_hi_bits));
+  const MinusOnes minus = minus_ones();
   const uint32_t inf_bits = 0xff800000u;
 
   int32_t cursor = 0;    // lane r: list entries of row 32 wid + r taken so far
@@ -515,35 +512,7 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
 #pragma unroll
           for (int i = 0; i < 16; ++i) y[i] -= delta;
         }
-        // weights as rounded value + rounded remainder (16 significant bits)
-        const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-        const bf16x2 neg_lo = __builtin_bit_cast(bf16x2, neg_lo_bits), neg_hi = __builtin_bit_cast(bf16x2, neg_hi_bits);
-        auto frag = [](const bf16x2* p2) {
-          const bf16x4 lo = __builtin_shufflevector(p2[0], p2[1], 0, 1, 2, 3);
-          const bf16x4 hi = __builtin_shufflevector(p2[2], p2[3], 0, 1, 2, 3);
-          return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        };
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-          bf16x2 h[4], l[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float p0 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * i]), p1 = __builtin_amdgcn_exp2f(y[8 * c2 + 2 * i + 1]);
-            const floatx2 f2 = {p0, p1};
-            h[i] = __builtin_convertvector(f2, bf16x2);
-            const floatx2 r2 = {__builtin_amdgcn_fdot2_f32_bf16(h[i], neg_lo, p0, false),
-                                __builtin_amdgcn_fdot2_f32_bf16(h[i], neg_hi, p1, false)};
-            l[i] = __builtin_convertvector(r2, bf16x2);
-            l_run = __builtin_amdgcn_fdot2_f32_bf16(h[i], ones, l_run, false);
-            l_run = __builtin_amdgcn_fdot2_f32_bf16(l[i], ones, l_run, false);
-          }
-          const bf16x8 ph = frag(h), pl8 = frag(l);
-#pragma unroll
-          for (int mt = 0; mt < 2; ++mt) {
-            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], ph, oacc[mt], 0, 0, 0);
-            oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], pl8, oacc[mt], 0, 0, 0);
-          }
-        }
+        l_run += add_weighted_rows(y, av, minus, oacc);
       }
       __syncthreads();
     }

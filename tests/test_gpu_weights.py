@@ -8,9 +8,9 @@ from paper_2310_01777_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-# (B, H, T, K): 8, 16 and 32 column slots, six, three and one set of waves
+# (B, H, T, K): 8, 16 and 32 column slots, six, three and one set of waves; lists in tiles
 @pytest.mark.parametrize("how,B,H,T,K", [("layer", 1, 24, 601, 100), ("layer", 1, 64, 499, 128), ("layer", 4, 64, 250, 140),
-                                         ("layer", 2, 64, 333, 50)])
+                                         ("layer", 2, 64, 333, 50), ("lists", 1, 64, 601, 100)])
 def test_weights_keep_their_bits(how, B, H, T, K):
     from paper_2310_01777_amd import binding as sea
     g = torch.Generator(device="cuda").manual_seed(T)
@@ -20,8 +20,12 @@ def test_weights_keep_their_bits(how, B, H, T, K):
     p = sea.SeaParams(B=B, H=H, T=T, d=64, m=64, K=K, k_hat=K, causal=False, scale=0.125, dtype="bf16")
     O = torch.empty_like(q)
     print(f"[case] weights {how} {(B, H, T, K)}", flush=True)
-    W = synth.gaussian_orthogonal(64, 64, 3).bfloat16().cuda()
-    sea.sea_forward(p, q, k, v, W, O, workspace=sea.alloc_workspace(p))
+    if how == "layer":
+        W = synth.gaussian_orthogonal(64, 64, 3).bfloat16().cuda()
+        sea.sea_forward(p, q, k, v, W, O, workspace=sea.alloc_workspace(p))
+    else:
+        idx = torch.arange(T, dtype=torch.int32, device="cuda").expand(B, H, T, T).contiguous()
+        sea.sea_sparse_attn(p, q, k, v, idx, torch.full((B, H, T), T, dtype=torch.int32, device="cuda"), T, O)
     want = torch.softmax(q.double() @ k.double().transpose(-1, -2).contiguous() * 0.125, -1) @ v.double()
     rms = want.square().mean().sqrt()
     small = want.abs() < rms * 2.0 ** -12
