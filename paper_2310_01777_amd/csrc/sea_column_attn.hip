@@ -9,11 +9,17 @@
 // columns of any width a lane's score registers belong to columns that change from step to step, so
 // bit tests per register would cost more than the softmax.  The mask goes through the matrix
 // product instead: the contraction is extended by NX slots, one per column of the 32-key sub-chunk.
-// On the key side slot x holds -2^126 for the keys of the sub-chunk's x-th column (one-hot, parked
-// in the padding of the staged K rows, the same for every row and head); on the query side it
-// holds 2 where the row did NOT select that column and 0 where it did.  One more 32x32x16 product
-// then lowers exactly the unselected scores by 2^127 and adds exact zeros to the others.  Building
-// the query side takes nine vector instructions per sub-chunk from the row's mask window.
+// On the key side slot x holds the lowest bf16 value, -(1 - 2^-8) 2^128, for the keys of the sub-chunk's
+// x-th column (one-hot, parked in the padding of the staged K rows, the same for every row and head); on
+// the query side it holds 2 where the row did NOT select that column and 0 where it did.  One more
+// 32x32x16 product then takes every finite unselected score below -(1 - 2^-6) 2^128 and adds exact zeros to
+// the others.  Building the query side takes nine vector instructions per sub-chunk from the row's mask
+// window.
+//
+// What a row does not select cannot reach it: a score that is not finite passes the mask as NaN, and a value
+// that is not finite gives NaN against a weight of zero, so a row whose accumulators and sum are finite met
+// neither.  The others (and rows whose scores all lie at the mask's level) are computed again from their own
+// keys at the end of the block.
 //
 // The softmax weights go into the second product as the sum of three bf16 values (sea_tile.h), i.e. as the
 // fp32 numbers they are: products of weights and values are exact, as in the per-row kernel.
@@ -26,6 +32,7 @@
 // 0.57 ms to write.  Small launches take as long as their longest list: there three or six sets
 // of waves share it.
 #include "sea_columns.h"
+#include "sea_gather.h"
 #include "sea_internal.h"
 #include "sea_tile.h"
 
@@ -138,7 +145,7 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
     for (int e = 0; e < SC * set; ++e) advance(scol, srem);
   }
   auto onehot = [&](int32_t lc, uint32_t* x) {
-    const uint32_t v = (lc & 1) ? 0xfe800000u : 0x0000fe80u;  // -2^126
+    const uint32_t v = (lc & 1) ? 0xff7f0000u : 0x0000ff7fu;  // the lowest value
 #pragma unroll
     for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) x[e] = (lc >> 1) == spart + 8 * e ? v : 0u;
   };
@@ -195,7 +202,7 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   floatx16 oacc[2];
 #pragma unroll
   for (int i = 0; i < 16; ++i) { oacc[0][i] = 0.f; oacc[1][i] = 0.f; }
-  // Streaming softmax in log2 units, y = s c - m_ref.  A masked score is about -2^127 c (or -inf), far
+  // Streaming softmax in log2 units, y = s c - m_ref.  A masked score is about -2^128 c (or -inf), far
   // below m_thr's start value, so it never becomes a reference; afterwards m_thr is how far a row's
   // maximum may exceed its reference before that is moved.
   float m_ref = 0.f, m_thr = -fminf(a.c * 0x1p126f, 3.0e38f), l_run = 0.f;
@@ -304,7 +311,31 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
     for (int e = 1; e < NS; ++e) merge_part<64 * RW>(place(e), oacc, l_run, m_own);
   }
   l_run = half_sum(l_run);
-  if (t < a.T) {
+  float zero = 0.f * l_run;  // NaN if anything is not finite
+#pragma unroll
+  for (int i = 0; i < 16; ++i) zero = fmaf(0.f, oacc[0][i], fmaf(0.f, oacc[1][i], zero));
+  bool again = zero != 0.f;
+  if (!row_active) {  // zero times what it met need not be zero
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { oacc[0][i] = 0.f; oacc[1][i] = 0.f; }
+  }
+  if (!(l_run > 0.f)) {  // no weight at all: rows without keys, or scores at the mask's level
+    uint32_t none = 0xffffffffu;
+    for (int32_t wi = 0; wi < a.KW; ++wi) none &= mrow[wi];
+    again = again || none != 0xffffffffu;
+  }
+  const uint64_t lanes_again = __ballot(again && row_active);
+  const uint32_t rows_again = static_cast<uint32_t>(lanes_again | (lanes_again >> 32));
+  if (rows_again != 0u) {
+    // (the column list takes the place of the mask words of the wave's rows, which no other wave reads now)
+    uint16_t* const place = reinterpret_cast<uint16_t*>(&Ms[32 * wid * mstride]);
+    for (uint32_t rows = rows_again; rows != 0u; rows &= rows - 1u) {
+      const int64_t tr = q0 + __ffs(static_cast<int>(rows)) - 1, row = head * a.T + tr;
+      const ColumnKeys keys(a.g, a.mbits + row * a.KW, a.KW, a.causal ? min(static_cast<int32_t>(tr), len - 1) : len - 1, place);
+      gather_row_bf16(keys, a.c, a.Q + row * kHeadDim, Kh, Vh, a.O + row * kHeadDim);
+    }
+  }
+  if (t < a.T && ((rows_again >> ql) & 1u) == 0u) {
     const float inv = (row_active && l_run > 0.f) ? 1.f / l_run : 0.f;
     uint16_t* Or = a.O + (head * a.T + t) * kHeadDim;
 #pragma unroll

@@ -63,9 +63,10 @@ __device__ __forceinline__ int32_t column_of(const Columns& g, int32_t j) {
 
 // The keys a head's rows can use, as one list ascending in position: all keys (r = 0: whole columns are
 // emitted) or r keys start + floor(i w / r) of every column.
+__device__ __forceinline__ int32_t entry_offset(const ColumnList& g, int32_t i, int32_t w) { return div_small(i * w, g.invr); }
 __device__ __forceinline__ int32_t entry_pos(const ColumnList& g, int32_t c, int32_t i) {
   const int32_t s0 = column_start(g.cg, c), w = column_start(g.cg, c + 1) - s0;
-  return s0 + div_small(i * w, g.invr);
+  return s0 + entry_offset(g, i, w);
 }
 // number of list entries with position <= jmax
 __device__ __forceinline__ int32_t list_count(const ColumnList& g, int32_t jmax) {

@@ -1,0 +1,66 @@
+"""A key that a row does not list is no part of the row's result, whatever its value row holds and however large
+its scores are: keys with infinities, NaN and scores beyond fp32 among ordinary ones, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2310_01777_amd import synth
+from tests.util import TOL, assert_close, oracle_params, to_np64
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, B, H, T, m, K, k^, budget, causal, pad)
+COLUMNS = [
+    ("bf16", 1, 2, 601, 64, 100, 20, 0, True, 0.0),     # columns of any width: 8 slots, six sets of waves
+    ("bf16", 1, 2, 385, 64, 128, 17, 0, False, 0.0),    # 16 slots
+    ("bf16", 2, 1, 129, 64, 128, 31, 0, True, 0.3),     # 32 slots
+    ("bf16", 1, 26, 601, 64, 100, 30, 0, False, 0.0),   # three sets
+    ("bf16", 5, 9, 700, 64, 100, 20, 0, False, 0.3),    # one
+    ("bf16", 1, 1, 1300, 64, 13, 5, 100, True, 0.0),    # 20 of 100 keys a column
+]
+
+
+def _check(O, idx, cnt, x, wl, bad, bad_rows_nan):
+    """Rows that list none of the keys `bad` hold what they would without those keys' values; rows that list
+    one with a NaN value are NaN."""
+    po = oracle_params(wl)
+    c = {k: to_np64(x[k]).copy() for k in "QKV"}
+    c["K"][:, :, bad], c["V"][:, :, bad] = 0.0, 0.0
+    want = oracle.sparse_attn(po, c["Q"], c["K"], c["V"], idx, cnt)
+    listed = np.isin(idx, bad).any(-1)
+    assert not listed.all()
+    got = to_np64(O)
+    clean = np.where(listed[..., None], 0.0, got)
+    assert_close(clean, np.where(listed[..., None], 0.0, want), TOL[wl.dtype], "rows without the keys")
+    if bad_rows_nan:
+        assert listed.any() and np.isnan(got[..., 5][listed]).all()
+
+
+@pytest.mark.parametrize("case", COLUMNS, ids=lambda c: "_".join(str(v) for v in c))
+def test_unselected_keys_stay_out(case):
+    from paper_2310_01777_amd import binding as sea
+    dtype, B, H, T, m, K, kh, kb, causal, pad = case
+    wl = synth.Workload("nonfinite", B, H, T, 64, m, K, kh, kb, causal, dtype, 4, pad)
+    x = synth.make_inputs(wl)
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=m, K=K, k_hat=kh, k_budget=kb, causal=causal, scale=wl.scale, dtype=dtype,
+                      seq_len=None if x["seq_len"] is None else x["seq_len"].cuda())
+    last = T if x["seq_len"] is None else int(x["seq_len"].min())
+    bad = np.unique([last // 3, last // 2, last - 1])
+    out, ws = sea.alloc_outputs(p), sea.alloc_workspace(p)
+    for what in ("values", "scores"):
+        y = {k: x[k].clone() for k in "QKVW"}
+        if what == "values":
+            y["V"][:, :, bad] = float("inf")
+            y["V"][:, :, bad, 5] = float("nan")
+        else:  # finite keys whose features vanish and whose scores overflow
+            y["K"][:, :, bad] = 1e37 * torch.sign(y["K"][:, :, bad].float()).to(y["K"].dtype)
+        d = {k: v.cuda() for k, v in y.items()}
+        print(f"[case] nonfinite {what} {case}", flush=True)
+        sea.sea_estimate(p, d["Q"], d["K"], d["W"], out["A_hat"], ws)
+        assert torch.isfinite(out["A_hat"]).all()
+        sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], out["O"], out["A_hat"], out["sel"], out["idx"], out["cnt"], ws)
+        O2 = torch.zeros_like(out["O"])
+        sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], O2, workspace=ws)
+        assert torch.equal(O2.view(torch.uint8), out["O"].view(torch.uint8))
+        _check(out["O"], out["idx"].cpu().numpy(), out["cnt"].cpu().numpy(), y, wl, bad, what == "values")
