@@ -311,21 +311,16 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
     for (int e = 1; e < NS; ++e) merge_part<64 * RW>(place(e), oacc, l_run, m_own);
   }
   l_run = half_sum(l_run);
-  float zero = 0.f * l_run;  // NaN if anything is not finite
-#pragma unroll
-  for (int i = 0; i < 16; ++i) zero = fmaf(0.f, oacc[0][i], fmaf(0.f, oacc[1][i], zero));
-  bool again = zero != 0.f;
+  uint32_t rows_again = rows_not_finite(l_run, oacc) & static_cast<uint32_t>(__ballot(row_active));
   if (!row_active) {  // zero times what it met need not be zero
 #pragma unroll
     for (int i = 0; i < 16; ++i) { oacc[0][i] = 0.f; oacc[1][i] = 0.f; }
   }
+  uint32_t selected = 0u;
   if (!(l_run > 0.f)) {  // no weight at all: rows without keys, or scores at the mask's level
-    uint32_t none = 0xffffffffu;
-    for (int32_t wi = 0; wi < a.KW; ++wi) none &= mrow[wi];
-    again = again || none != 0xffffffffu;
+    for (int32_t wi = 0; wi < a.KW; ++wi) selected |= ~mrow[wi];
   }
-  const uint64_t lanes_again = __ballot(again && row_active);
-  const uint32_t rows_again = static_cast<uint32_t>(lanes_again | (lanes_again >> 32));
+  rows_again |= static_cast<uint32_t>(__ballot(row_active && selected != 0u));  // (both halves hold the row's words)
   if (rows_again != 0u) {
     // (the column list takes the place of the mask words of the wave's rows, which no other wave reads now)
     uint16_t* const place = reinterpret_cast<uint16_t*>(&Ms[32 * wid * mstride]);
@@ -362,7 +357,7 @@ void launch_column(const Shape& s, ColumnArgs a, hipStream_t st) {
 
 }  // namespace
 
-// Any fixed-bucket selection; the scale must leave -2^127 scale far below every real score.
+// Any fixed-bucket selection; the scale must leave -2^128 scale far below every real score.
 bool column_attn_supported(const Shape& s, sea_dtype dt) {
   return dt == SEA_BF16 && column_list_supported(s) && s.scale > 1e-20f;
 }

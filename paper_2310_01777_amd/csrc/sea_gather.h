@@ -189,5 +189,80 @@ __device__ __forceinline__ void gather_row_bf16(Keys keys, float f, const uint16
   }
 }
 
+// fp32: f q.k with fp64 sums, so that logits of magnitude ~40 still leave the probabilities accurate to ~1e-7;
+// weights and accumulators in fp32
+template <typename Keys>
+__device__ __forceinline__ void gather_row_f32(Keys keys, double f, const float* __restrict__ Qr,
+                                               const float* __restrict__ Kh, const float* __restrict__ Vh,
+                                               float* __restrict__ Or) {
+  const int lane = threadIdx.x & 63;
+  const int g = lane >> 4;    // which of the 4 rows of a wave load
+  const int c16 = lane & 15;  // which 16-byte chunk of the row
+
+  const float4 q4 = *reinterpret_cast<const float4*>(Qr + c16 * 4);
+  const double qd[4] = {q4.x, q4.y, q4.z, q4.w};
+  const int32_t n = keys.n;
+
+  double m_run = -INFINITY;
+  float l_run = 0.f;
+  float o[4] = {0.f, 0.f, 0.f, 0.f};
+
+  for (int32_t k0 = 0; k0 < n; k0 += 4 * kGatherUnroll) {
+    float4 kv[kGatherUnroll], vv[kGatherUnroll];
+    bool ok[kGatherUnroll];
+    int32_t j[kGatherUnroll];
+    keys.template next<4>(g, j, ok);
+#pragma unroll
+    for (int u = 0; u < kGatherUnroll; ++u) {
+      kv[u] = *reinterpret_cast<const float4*>(Kh + static_cast<int64_t>(j[u]) * kHeadDim + c16 * 4);
+      vv[u] = *reinterpret_cast<const float4*>(Vh + static_cast<int64_t>(j[u]) * kHeadDim + c16 * 4);
+    }
+    double sc[kGatherUnroll];
+    double mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kGatherUnroll; ++u) {
+      double a = qd[0] * kv[u].x;
+      a = fma(qd[1], static_cast<double>(kv[u].y), a);
+      a = fma(qd[2], static_cast<double>(kv[u].z), a);
+      a = fma(qd[3], static_cast<double>(kv[u].w), a);
+      a += __shfl_xor(a, 1, kWave);
+      a += __shfl_xor(a, 2, kWave);
+      a += __shfl_xor(a, 4, kWave);
+      a += __shfl_xor(a, 8, kWave);
+      sc[u] = ok[u] ? a * f : -INFINITY;
+      mx = fmax(mx, sc[u]);
+    }
+    mx = fmax(mx, __shfl_xor(mx, 16, kWave));
+    mx = fmax(mx, __shfl_xor(mx, 32, kWave));
+    const double m_new = fmax(m_run, mx);
+    if (m_new == -INFINITY) continue;
+    const float corr = exp2f(static_cast<float>(m_run - m_new));
+    m_run = m_new;
+    l_run *= corr;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] *= corr;
+#pragma unroll
+    for (int u = 0; u < kGatherUnroll; ++u) {
+      const float pj = exp2f(static_cast<float>(sc[u] - m_new));
+      l_run += pj;
+      o[0] = fmaf(pj, vv[u].x, o[0]);
+      o[1] = fmaf(pj, vv[u].y, o[1]);
+      o[2] = fmaf(pj, vv[u].z, o[2]);
+      o[3] = fmaf(pj, vv[u].w, o[3]);
+    }
+  }
+#pragma unroll
+  for (int mask = 16; mask <= 32; mask <<= 1) {
+    l_run += __shfl_xor(l_run, mask, kWave);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] += __shfl_xor(o[e], mask, kWave);
+  }
+  if (g == 0) {
+    float4 out = {0.f, 0.f, 0.f, 0.f};
+    if (l_run > 0.f) out = {o[0] / l_run, o[1] / l_run, o[2] / l_run, o[3] / l_run};
+    *reinterpret_cast<float4*>(Or + c16 * 4) = out;
+  }
+}
+
 #endif  // __HIPCC__
 }  // namespace sea

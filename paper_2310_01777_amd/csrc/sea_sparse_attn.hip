@@ -14,10 +14,6 @@ namespace sea {
 namespace {
 
 constexpr int kWavesPerBlock = 4;
-constexpr int kUnroll = 4;
-
-__device__ __forceinline__ float wave_xor_f(float v, int mask) { return __shfl_xor(v, mask, kWave); }
-__device__ __forceinline__ double wave_xor_d(double v, int mask) { return __shfl_xor(v, mask, kWave); }
 
 // Where a row's key list lives.  Per-row lists: idx + row L, cnt[row] entries.  FlatCSR tensor
 // (crow != nullptr, idx = its column array): row (b, h, t) owns the entries of CSR row b T + t
@@ -89,7 +85,9 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel
 // cursor on; each sets a byte of a 1 KB strip in LDS (no atomics: different bytes), the strip is read
 // back as 16 keys per lane and packed.  The keys any row of the block uses are ORed together on the
 // way; steps without one are skipped, and the rows of unused keys are not read from memory (a buffer
-// load past the end returns zero), so what a list leaves out cannot leak into the result.
+// load past the end returns zero).  What another row of the block lists cannot reach a row either: a value
+// that is not finite gives NaN against a weight of zero, and rows whose accumulators are not finite are
+// computed again with the gather form.
 //
 // This is right for lists that ascend without repetition.  Whatever else the caller passes is found out
 // by counting: the bits set over all windows equal the list lengths exactly when every entry was seen,
@@ -426,15 +424,11 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
   for (int off = 32; off >= 1; off >>= 1) nset += __shfl_xor(nset, off, kWave);
   if (lane == 0) red[wid][0] = static_cast<int32_t>(nset);
   __syncthreads();
-  if (red[0][0] + red[1][0] + red[2][0] + red[3][0] != total) {
-    for (int32_t r = row0 + wid; r < min(row0 + kTileRows, s.T); r += 4) {
-      const int64_t row = head * s.T + r;
-      gather_list_row(s, head, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
-    }
-    return;
-  }
+  const bool lists_ok = red[0][0] + red[1][0] + red[2][0] + red[3][0] == total;
   l_run = half_sum(l_run);
-  if (t < s.T) {
+  const uint32_t rows_here = static_cast<uint32_t>(__ballot(t < s.T));
+  const uint32_t rows_again = lists_ok ? rows_not_finite(l_run, oacc) & rows_here : rows_here;
+  if (t < s.T && ((rows_again >> ql) & 1u) == 0u) {
     const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
     uint16_t* Or = O + (head * s.T + t) * kHeadDim;
 #pragma unroll
@@ -447,12 +441,12 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         *reinterpret_cast<bf16x4*>(Or + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
       }
   }
+  for (uint32_t rows = rows_again; rows != 0u; rows &= rows - 1u) {
+    const int64_t row = head * s.T + row0 + 32 * wid + __ffs(static_cast<int>(rows)) - 1;
+    gather_list_row(s, head, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
+  }
 }
 
-// ------------------------------------------------------------------------------------------
-// fp32: 16 lanes per row, 4 rows per wave load; q.k accumulates in fp64 so that logits of
-// magnitude ~40 still leave the probabilities accurate to ~1e-7
-// ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_f32_kernel(
     Shape s, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int32_t L,
@@ -461,84 +455,9 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_f32_kernel(
   const int64_t row = static_cast<int64_t>(lb) * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
   if (row >= nrows) return;
-  const int lane = threadIdx.x & 63;
-  const int g = lane >> 4;    // which of the 4 rows of a wave load
-  const int c16 = lane & 15;  // which 16-byte chunk of the row
-  const int64_t head = row / s.T;
-  const float* Kh = K + head * s.T * kHeadDim;
-  const float* Vh = V + head * s.T * kHeadDim;
-
-  const float4 q4 = *reinterpret_cast<const float4*>(Q + row * kHeadDim + c16 * 4);
-  const double qd[4] = {q4.x, q4.y, q4.z, q4.w};
-  const double f = static_cast<double>(s.scale) * 1.4426950408889634;
-  const ListKeys kl = key_list(s, row, idx, cnt, L, crow);
-  const int32_t n = kl.n;
-  const int32_t* irow = kl.p;
-
-  double m_run = -INFINITY;
-  float l_run = 0.f;
-  float o[4] = {0.f, 0.f, 0.f, 0.f};
-
-  for (int32_t k0 = 0; k0 < n; k0 += 4 * kUnroll) {
-    float4 kv[kUnroll], vv[kUnroll];
-    bool ok[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int32_t p = k0 + u * 4 + g;
-      // the index is read unconditionally (a slot past the list re-reads its last entry and is
-      // then discarded): a load behind `p < n` would be waited for before the next slot's is issued
-      int32_t j = irow[min(p, n - 1)] - kl.base;
-      j = (p < n) ? j : -1;
-      ok[u] = static_cast<uint32_t>(j) < static_cast<uint32_t>(s.T);
-      j = ok[u] ? j : 0;
-      kv[u] = *reinterpret_cast<const float4*>(Kh + static_cast<int64_t>(j) * kHeadDim + c16 * 4);
-      vv[u] = *reinterpret_cast<const float4*>(Vh + static_cast<int64_t>(j) * kHeadDim + c16 * 4);
-    }
-    double sc[kUnroll];
-    double mx = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      double a = qd[0] * kv[u].x;
-      a = fma(qd[1], static_cast<double>(kv[u].y), a);
-      a = fma(qd[2], static_cast<double>(kv[u].z), a);
-      a = fma(qd[3], static_cast<double>(kv[u].w), a);
-      a += wave_xor_d(a, 1);
-      a += wave_xor_d(a, 2);
-      a += wave_xor_d(a, 4);
-      a += wave_xor_d(a, 8);
-      sc[u] = ok[u] ? a * f : -INFINITY;
-      mx = fmax(mx, sc[u]);
-    }
-    mx = fmax(mx, wave_xor_d(mx, 16));
-    mx = fmax(mx, wave_xor_d(mx, 32));
-    const double m_new = fmax(m_run, mx);
-    if (m_new == -INFINITY) continue;
-    const float corr = exp2f(static_cast<float>(m_run - m_new));
-    m_run = m_new;
-    l_run *= corr;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] *= corr;
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const float pj = exp2f(static_cast<float>(sc[u] - m_new));
-      l_run += pj;
-      o[0] = fmaf(pj, vv[u].x, o[0]);
-      o[1] = fmaf(pj, vv[u].y, o[1]);
-      o[2] = fmaf(pj, vv[u].z, o[2]);
-      o[3] = fmaf(pj, vv[u].w, o[3]);
-    }
-  }
-#pragma unroll
-  for (int mask = 16; mask <= 32; mask <<= 1) {
-    l_run += wave_xor_f(l_run, mask);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] += wave_xor_f(o[e], mask);
-  }
-  if (g == 0) {
-    float4 out = {0.f, 0.f, 0.f, 0.f};
-    if (l_run > 0.f) out = {o[0] / l_run, o[1] / l_run, o[2] / l_run, o[3] / l_run};
-    *reinterpret_cast<float4*>(O + row * kHeadDim + c16 * 4) = out;
-  }
+  const int64_t head = row / s.T, first = head * s.T * kHeadDim, at = row * kHeadDim;
+  gather_row_f32(key_list(s, row, idx, cnt, L, crow), static_cast<double>(s.scale) * 1.4426950408889634, Q + at, K + first,
+                 V + first, O + at);
 }
 
 // Tiles from one 128-row block per CU on.  Below that a block's walk (two windows of a 2048-key sequence are

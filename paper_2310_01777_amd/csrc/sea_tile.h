@@ -81,6 +81,15 @@ __device__ __forceinline__ float add_weighted_rows(const float (&y)[16], const b
   return sum;
 }
 
+// Rows of a wave (one per lane and half-wave, bit r = row r) whose sum or accumulators are not finite
+__device__ __forceinline__ uint32_t rows_not_finite(float l, const floatx16 (&oacc)[2]) {
+  float zero = 0.f * l;  // NaN if anything is not finite
+#pragma unroll
+  for (int i = 0; i < 16; ++i) zero = fmaf(0.f, oacc[0][i], fmaf(0.f, oacc[1][i], zero));
+  const uint64_t lanes = __ballot(zero != 0.f);
+  return static_cast<uint32_t>(lanes | (lanes >> 32));
+}
+
 // raw buffer resource, word 3: 32-bit data format, no swizzle; loads past num_records return zero
 constexpr int kBufferFlags = 0x00020000;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

@@ -6,6 +6,7 @@ import torch
 
 import oracle
 from paper_2310_01777_amd import synth
+from tests.test_gpu_lists import _lists
 from tests.util import TOL, assert_close, oracle_params, to_np64
 
 pytestmark = pytest.mark.gpu
@@ -64,3 +65,20 @@ def test_unselected_keys_stay_out(case):
         sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], O2, workspace=ws)
         assert torch.equal(O2.view(torch.uint8), out["O"].view(torch.uint8))
         _check(out["O"], out["idx"].cpu().numpy(), out["cnt"].cpu().numpy(), y, wl, bad, what == "values")
+
+
+def test_unlisted_keys_stay_out():
+    from paper_2310_01777_amd import binding as sea
+    B, H, T, L = 2, 15, 1100, 1100   # lists dense enough, and blocks enough, for tiles
+    wl = synth.Workload("lists", B, H, T, 64, 32, 16, 4, 0, True, "bf16", 4)
+    x = synth.make_inputs(wl)
+    idx, cnt = _lists(B, H, T, L, 0.4, T)
+    bad = np.array([0, 500, 1090])
+    x["V"][:, :, bad] = float("inf")
+    x["V"][:, :, bad, 5] = float("nan")
+    d = {k: x[k].cuda() for k in "QKV"}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=32, K=16, k_hat=4, causal=True, scale=wl.scale, dtype="bf16")
+    O = torch.zeros(B, H, T, 64, dtype=torch.bfloat16, device="cuda")
+    print("[case] nonfinite lists", flush=True)
+    sea.sea_sparse_attn(p, d["Q"], d["K"], d["V"], torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda(), L, O)
+    _check(O, idx, cnt, x, wl, bad, True)
