@@ -22,6 +22,7 @@
 // (the key and value rows themselves are gathered from K and V by position, so no compact or
 // transposed copy exists in HBM).
 #include "sea_columns.h"
+#include "sea_gather.h"
 #include "sea_internal.h"
 #include "sea_tile.h"
 
@@ -907,12 +908,16 @@ __device__ __forceinline__ float rows_sum_f(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// ANYW: columns of any width, any number of keys per column (otherwise both as in the bf16 kernel)
+// ANYW: columns of any width, any number of keys per column (otherwise both as in the bf16 kernel).  These
+// layers also have a per-row form, in which a key that is not selected is not read: a row whose result is not
+// finite may have met such a key (a value that is not finite against a weight of zero) and is computed again
+// from its own keys.
 template <bool ANYW>
 __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   __shared__ float m_s[4][16], l_s[4][16];
   __shared__ float o_s[4][kHeadDim][17];  // [wave][dim][query], padded
   __shared__ uint32_t mask_s[16 * 129];    // at most 128 mask words per row (K <= 1024 columns, or T <= 4096 keys)
+  __shared__ uint32_t again_s;             // rows to compute again, a bit each
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qc = lane & 15, g = lane >> 4;
@@ -942,6 +947,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
       const int32_t r = x / a.KW, wi = x - r * a.KW;
       mask_s[r * (a.KW + 1) + wi] = x < nwords ? msrc[x] : 0u;
     }
+    if (ANYW && tid == 0) again_s = 0u;
   }
   __syncthreads();
   const uint32_t* mrow_s = &mask_s[qc * (a.KW + 1)];
@@ -1100,10 +1106,28 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc4[e] = fmaf(wgt, o_s[w][4 * dq + e][q], acc4[e]);
     }
+    if (ANYW) {
+      float zero = 0.f * L;  // NaN if anything is not finite
+#pragma unroll
+      for (int e = 0; e < 4; ++e) zero = fmaf(0.f, acc4[e], zero);
+      if (tt >= len) acc4[0] = acc4[1] = acc4[2] = acc4[3] = 0.f;  // zero times what it met need not be zero
+      else if (zero != 0.f) atomicOr(&again_s, 1u << q);
+    }
     if (tt < a.T) {
       const float inv = (tt < len && L > 0.f) ? 1.f / L : 0.f;
       *reinterpret_cast<float4*>(a.O + (head * a.T + tt) * kHeadDim + 4 * dq) =
           make_float4(acc4[0] * inv, acc4[1] * inv, acc4[2] * inv, acc4[3] * inv);
+    }
+  }
+  if constexpr (ANYW) {
+    __syncthreads();  // (also: the rows' stores above come first, and the mask words are no longer read)
+    uint16_t* const place = reinterpret_cast<uint16_t*>(mask_s) + 1024 * wid;
+    for (uint32_t rows = again_s; rows != 0u; rows &= rows - 1u) {
+      const int r = __builtin_amdgcn_readfirstlane(__ffs(static_cast<int>(rows)) - 1);
+      if ((r & 3) != wid) continue;
+      const int64_t row = head * a.T + q0 + r;
+      const ColumnKeys keys(a.g, a.mbits + row * a.KW, a.KW, a.causal ? min(q0 + r, len - 1) : len - 1, place);
+      gather_row_f32(keys, a.f, a.Q + row * kHeadDim, Kh, Vh, a.O + row * kHeadDim);
     }
   }
 }
