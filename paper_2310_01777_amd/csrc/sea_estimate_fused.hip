@@ -390,6 +390,8 @@ __global__ __launch_bounds__(256) void wide_columns_kernel(Shape s, const float*
 // Causal: the same product over the ROUNDED features (bf16, one 16x16x16 product per 16 features) gives
 // the running sum of the current column; before each tile that a column began in front of, the sum of
 // that column's earlier keys goes out as fp32.
+// A key whose features are not finite must not leave its column (causal rows before it do not know it): a block
+// that finds such a sum takes its columns one by one.
 // Bound: vector and matrix issue together.  B = 8, H = 32, T = 2000, K = 256, m = 256: 0.10 ms (1.54 ms with
 // the three kernels that write the features to memory, rows kernel and selection included: 0.25 ms).  Columns
 // of four keys or more (BY4) take two fp32 products per 16 features and keys instead of four, and the rows of
@@ -519,6 +521,50 @@ __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg
         }
       }
     }
+  }
+  float zero = 0.f;  // NaN if a sum is not finite
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) zero = fmaf(0.f, sum[ft][i], CAUSAL ? fmaf(0.f, rsum[CAUSAL ? ft : 0][i], zero) : zero);
+  if (__ballot(zero != 0.f) != 0ull) {
+    // A feature that is not finite has reached every column of the block (zero times it): the wave's sums again,
+    // column by column from the keys of each alone.
+    __threadfence();  // (after the sums the walk has stored)
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft) {
+      const int64_t f = 16 * (wid * FT + ft) + lr;
+#pragma unroll 1
+      for (int32_t c = c0; c < c1; ++c) {
+        const int32_t first = column_start(cg, c), end = min(column_start(cg, c + 1), len);
+        float total = 0.f, rounded = 0.f;
+#pragma unroll 1
+        for (int32_t r0 = first & ~15; r0 < end; r0 += 16) {
+          if (CAUSAL && r0 > first && lg == 0) pref[(head * ((s.T + 15) >> 4) + (r0 >> 4)) * m + f] = rounded;
+          request(r0 + lr, x0, x1);
+          float nx = sumsq8(x0) + sumsq8(x1);
+          nx += __shfl_xor(nx, 16, kWave);
+          nx += __shfl_xor(nx, 32, kWave);
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+          acc = mfma16(x0, w0[ft], acc);
+          acc = mfma16(x1, w1[ft], acc);
+          float part = 0.f, part_r = 0.f;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int32_t j = r0 + 4 * lg + i;
+            const float v = __builtin_amdgcn_exp2f(fmaf(c_dot, acc[i], -c_norm * __shfl(nx, 4 * lg + i, kWave)));
+            part += j >= first && j < end ? v : 0.f;
+            part_r += j >= first && j < end ? bf16_to_f32(f32_to_bf16(v)) : 0.f;
+          }
+          part += __shfl_xor(part, 16, kWave);
+          part_r += __shfl_xor(part_r, 16, kWave);
+          total += part + __shfl_xor(part, 32, kWave);
+          rounded += part_r + __shfl_xor(part_r, 32, kWave);
+        }
+        if (lg == 0) state[(head * s.K + c) * m + f] = f32_to_bf16(total);
+      }
+    }
+    return;
   }
   // accumulator register i of a lane: column c0 + 4 lg + i
 #pragma unroll

@@ -72,6 +72,28 @@ def test_unselected_keys_stay_out(case):
         _check(out["O"], out["idx"].cpu().numpy(), out["cnt"].cpu().numpy(), y, wl, bad, what == "values")
 
 
+@pytest.mark.parametrize("T,m,K,pad", [(500, 128, 64, 0.0), (129, 64, 128, 0.0), (700, 256, 100, 0.3), (301, 64, 128, 0.0),
+                                       (1000, 64, 33, 0.0), (2000, 64, 3, 0.0)])
+def test_causal_estimate_before_a_key(T, m, K, pad):
+    """Scores of causal rows do not know the keys after them."""
+    from paper_2310_01777_amd import binding as sea
+    wl = synth.Workload("nonfinite", 1, 3, T, 64, m, K, 2, 0, True, "bf16", 4, pad)
+    x = synth.make_inputs(wl)
+    seq = x["seq_len"]
+    j = (T if seq is None else int(seq[0])) // 2
+    clean = {k: to_np64(x[k]) for k in "QKW"}
+    x["K"][0, 1, j] = float("nan")
+    x["K"][0, 2, j, 3] = float("inf")
+    p = sea.SeaParams(B=1, H=3, T=T, d=64, m=m, K=K, k_hat=2, causal=True, scale=wl.scale, dtype="bf16",
+                      seq_len=None if seq is None else seq.cuda())
+    A = torch.empty(1, 3, T, K, device="cuda")
+    print(f"[case] nonfinite estimate {(T, m, K, pad)}", flush=True)
+    sea.sea_estimate(p, x["Q"].cuda(), x["K"].cuda(), x["W"].cuda(), A, sea.alloc_workspace(p))
+    want = oracle.estimate(oracle_params(wl), clean["Q"], clean["K"], clean["W"], seq_len=None if seq is None else seq.numpy())
+    assert_close(to_np64(A)[:, :, :j], want[:, :, :j], TOL["bf16"], "A_hat")
+    assert torch.isnan(A[0, 1, j]).any()
+
+
 def test_unlisted_keys_stay_out():
     from paper_2310_01777_amd import binding as sea
     B, H, T, L = 2, 15, 1100, 1100   # lists dense enough, and blocks enough, for tiles
