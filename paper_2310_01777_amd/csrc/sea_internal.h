@@ -87,6 +87,10 @@ hipError_t launch_tile_attn_f32_keybits(const Shape& s, const float* Q, const fl
 bool column_attn_supported(const Shape& s, sea_dtype dt);
 hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
                               const uint32_t* mbits, uint16_t* O, hipStream_t st);
+// both tensor types, few selected keys: a wavefront per row, and when that is the faster form
+bool column_gather_pays(const Shape& s, sea_dtype dt);
+hipError_t launch_column_gather(const Shape& s, sea_dtype dt, const void* Q, const void* K, const void* V,
+                                const uint32_t* mbits, void* O, hipStream_t st);
 // fp32 tensors: tiled attention on the fp64 / fp32 matrix cores from per-row column bits
 bool tile_attn_f32_supported(const Shape& s);
 bool tile_attn_f32_structured(const Shape& s);  // K | T and a power-of-two number of keys per column

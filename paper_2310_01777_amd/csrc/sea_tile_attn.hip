@@ -1157,14 +1157,16 @@ bool tile_attn_f32_structured(const Shape& s) {
 hipError_t launch_tile_attn_f32(const Shape& s, const float* Q, const float* K, const float* V,
                                 const uint32_t* mbits, float* O, hipStream_t st) {
   if (!tile_attn_f32_supported(s)) return hipErrorNotSupported;
+  int32_t rlog = 0;
+  const bool pow2 = tile_attn_f32_pow2(s, &rlog);
+  if (!pow2 && column_gather_pays(s, SEA_F32)) return launch_column_gather(s, SEA_F32, Q, K, V, mbits, O, st);
   StageScope scope(SEA_STAGE_SPARSE, st);
   TileF32Args a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;
   a.N = s.N; a.H = s.H; a.T = s.T; a.KW = (s.K + 31) / 32; a.causal = s.causal;
   a.f = static_cast<double>(s.scale) * 1.4426950408889634;
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 15) / 16));
-  int32_t rlog = 0;
-  if (tile_attn_f32_pow2(s, &rlog)) {
+  if (pow2) {
     a.rlog = rlog; a.w = s.T / s.K; a.U = s.K << rlog;
     hipLaunchKernelGGL(tile_attn_f32_kernel<false>, grid, dim3(256), 0, st, a);
   } else {

@@ -99,3 +99,46 @@ def test_any_column_width(dtype, case):
     want = oracle.sparse_attn(po, to_np64(clean["Q"]), to_np64(clean["K"]), to_np64(clean["V"]), idx, cnt)
     assert_close(to_np64(out["O"]), want, TOL[dtype], "O")
     assert torch.equal(O2, out["O"])
+
+
+# few keys per row: a wavefront per row reads them from the mask words (fp32: 6.3 n + 23 keys or more in the
+# list that tiles would walk; half the list when causal)
+# (dtype, B, H, T, m, K, k^, budget, causal, pad, grouping)
+FEW_CASES = [
+    ("f32", 2, 2, 333, 64, 64, 2, 0, True, 0.3, 0),
+    ("f32", 1, 1, 130, 32, 128, 1, 0, False, 0.0, 0),       # one or two keys
+    ("f32", 1, 2, 1300, 64, 13, 1, 50, False, 0.0, 0),
+    ("f32", 1, 1, 5003, 64, 1000, 20, 20, False, 0.3, 0),   # one of five or six
+    ("f32", 1, 3, 700, 64, 60, 2, 0, True, 0.0, 1),
+    ("f32", 1, 2, 1000, 64, 62, 8, 0, False, 0.0, 0),       # 136 keys of 1000: rows; 153: tiles
+    ("f32", 1, 2, 1000, 64, 62, 9, 0, False, 0.0, 0),
+]
+
+
+@pytest.mark.parametrize("case", FEW_CASES, ids=lambda v: "_".join(str(x) for x in v))
+def test_few_keys_per_row(case):
+    from paper_2310_01777_amd import binding as sea
+    dtype, B, H, T, m, K, kh, kb, causal, pad, grouping = case
+    wl = synth.Workload("columns", B, H, T, 64, m, K, kh, kb, causal, dtype, 4, pad, grouping=grouping)
+    x = synth.make_inputs(wl)
+    d = {k: x[k].cuda() for k in "QKVW"}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=m, K=K, k_hat=kh, k_budget=kb, causal=causal, scale=wl.scale, dtype=dtype,
+                      grouping=grouping, seq_len=None if x["seq_len"] is None else x["seq_len"].cuda())
+    out, ws = sea.alloc_outputs(p), sea.alloc_workspace(p)
+    print(f"[case] few keys {case}", flush=True)
+    sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], out["O"], out["A_hat"], out["sel"], out["idx"], out["cnt"], ws)
+    O2 = torch.full_like(out["O"], float("nan"))
+    sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], O2, workspace=ws)
+    lists = torch.full_like(out["O"], float("nan"))
+    sea.sea_sparse_attn(p, d["Q"], d["K"], d["V"], out["idx"], out["cnt"], sea.sea_row_stride(p), lists)
+    torch.cuda.synchronize()
+    po = oracle_params(wl)
+    idx, cnt = out["idx"].cpu().numpy(), out["cnt"].cpu().numpy()
+    _, idx_o, cnt_o = oracle.topk_mask(po, out["A_hat"].cpu().numpy().astype(np.float64),
+                                       seq_len=None if x["seq_len"] is None else x["seq_len"].numpy())
+    assert np.array_equal(idx, idx_o) and np.array_equal(cnt, cnt_o)
+    want = oracle.sparse_attn(po, to_np64(x["Q"]), to_np64(x["K"]), to_np64(x["V"]), idx, cnt)
+    assert_close(to_np64(out["O"]), want, TOL[dtype], "O")
+    assert torch.equal(O2, out["O"])
+    if kb:  # a fixed number of keys per column: the rows' keys in the order of the lists, so the same sums
+        assert torch.equal(out["O"], lists)

@@ -24,6 +24,7 @@ F32 = [
     ("f32", 1, 2, 385, 64, 128, 33, 0, True, 0.0),      # columns of any width
     ("f32", 2, 1, 290, 96, 64, 20, 0, False, 0.3),
     ("f32", 1, 1, 1300, 64, 13, 5, 500, True, 0.0),     # 100 of 100 keys a column
+    ("f32", 1, 2, 700, 64, 60, 2, 0, False, 0.3),       # few keys per row
 ]
 
 
