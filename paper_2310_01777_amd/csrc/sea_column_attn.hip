@@ -1,7 +1,8 @@
 // Tiled attention for column-selected masks of ANY column widths (Sec. 3.1.1 rho, sigma, A* V with
 // the mask of Sec. 3.1 "Linear Sparse Attention Mask Generation", App. A.5.3): K need not divide T
 // and a selected column may emit any number of keys.  bf16 tensors; the power-of-two shapes have a
-// kernel of their own (sea_tile_attn.hip), whose register groups share one mask bit.
+// kernel of their own (sea_tile_attn.hip), whose register groups share one mask bit, and so have layers
+// whose rows select few keys (sea_column_gather.hip).
 //
 // The keys a head can use form one compact list, ascending in position: all T keys when whole
 // columns are emitted, else r keys of each of the K columns.  A block of 4 waves takes 128 query
@@ -365,6 +366,7 @@ bool column_attn_supported(const Shape& s, sea_dtype dt) {
 hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
                               const uint32_t* mbits, uint16_t* O, hipStream_t st) {
   if (!column_attn_supported(s, SEA_BF16)) return hipErrorNotSupported;
+  if (column_gather_pays(s, SEA_BF16)) return launch_column_gather(s, SEA_BF16, Q, K, V, mbits, O, st);
   StageScope scope(SEA_STAGE_SPARSE, st);
   ColumnArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;

@@ -58,18 +58,22 @@ hipError_t launch(const Shape& s, const void* Q, const void* K, const void* V, c
 
 }  // namespace
 
-// Both forms cost about a fixed time per row and one per key: a row of its own n = k^ r keys, gathered (fp32 0.45
-// ns + 27 ps a key), against the U keys of the list that a tile walks for all its rows, half of them when
-// causal (0.35 ns + 4.3 ps; fewer where rows leave chunks out).  Whole forward in us, tiles / rows, K = 128,
-// H = 12, B = 1, T = 3200: bidirectional, k^ = 4, 16, 32 460 / 242, 670 / 538, 715 / 950; causal 327 / 250,
-// 404 / 526, 415 / 883.
+// Both forms cost about a fixed time per row and one per key: a row of its own n = k^ r keys, gathered (bf16 0.45
+// ns + 10 ps a key, never less than a batch of 32; fp32 0.45 ns + 27 ps), against the U keys of the list that a
+// tile walks for all its rows, half of them when causal (bf16 0.65 ps a key, fp32 0.35 ns + 4.3 ps; fewer
+// where rows leave chunks out, which is what moves the line).  Whole forward in us, tiles / rows, K = 128,
+// H = 12: bf16, bidirectional, B = 2, T = 8001 k^ = 2, 4, 8 525 / 354, 658 / 606, 767 / 1108, T = 2041 k^ = 2, 4, 8,
+// 16 97 / 59, 109 / 76, 112 / 107, 113 / 173, B = 1, T = 65535 one column of 64 keys 1626 / 863; causal, T = 8001
+// k^ = 2, 4 453 / 357, 496 / 601; fp32, bidirectional, B = 1, T = 3200 k^ = 4, 16, 32 460 / 242, 670 / 538,
+// 715 / 950, causal 327 / 250, 404 / 526, 415 / 883.  Short rows stay in tiles in bf16: H = 32, K = 256, B = 4,
+// T = 1000, k^ = 1 120 / 142.
 // (A grid has at most 2^32 threads.)
 bool column_gather_pays(const Shape& s, sea_dtype dt) {
   if (!column_list_supported(s) || s.K > kMaxColumns || static_cast<int64_t>(s.N) * s.T > (int64_t(1) << 25)) return false;
   const ColumnList g = column_list(s);
   const int64_t r = g.r == 0 ? g.cg.w0 + (g.cg.rm > 0 ? 1 : 0) : g.r;
   const int64_t n = s.k_hat * r, walked = s.causal ? g.U / 2 : g.U;
-  return dt == SEA_F32 && 10 * walked >= 63 * n + 230;
+  return dt == SEA_BF16 ? walked >= 15 * ((n > 32 ? n : 32) + 45) : 10 * walked >= 63 * n + 230;
 }
 
 hipError_t launch_column_gather(const Shape& s, sea_dtype dt, const void* Q, const void* K, const void* V,

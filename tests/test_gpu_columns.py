@@ -101,10 +101,18 @@ def test_any_column_width(dtype, case):
     assert torch.equal(O2, out["O"])
 
 
-# few keys per row: a wavefront per row reads them from the mask words (fp32: 6.3 n + 23 keys or more in the
-# list that tiles would walk; half the list when causal)
+# few keys per row: a wavefront per row reads them from the mask words (bf16: 15 (n + 45) keys or more in the list
+# that tiles would walk, fp32: 6.3 n + 23; half the list when causal)
 # (dtype, B, H, T, m, K, k^, budget, causal, pad, grouping)
 FEW_CASES = [
+    ("bf16", 1, 3, 4001, 64, 128, 2, 60, False, 0.0, 0),    # 30 of 31 or 32 keys
+    ("bf16", 2, 2, 3001, 64, 1000, 1, 0, False, 0.3, 0),    # three or four, 32 mask words
+    ("bf16", 1, 2, 5003, 64, 100, 1, 40, True, 0.0, 0),     # 40 of 50 or 51, rows that end inside
+    ("bf16", 2, 1, 9001, 64, 64, 1, 100, True, 0.5, 0),     # more slots than lanes
+    ("bf16", 1, 2, 4001, 64, 128, 1, 0, True, 0.0, 0),      # whole columns
+    ("bf16", 1, 3, 3001, 64, 100, 1, 0, True, 0.0, 1),      # heads share the quota
+    ("bf16", 1, 1, 2041, 64, 64, 2, 0, False, 0.0, 0),      # 64 keys of 2041: rows; 96: tiles
+    ("bf16", 1, 1, 2041, 64, 64, 3, 0, False, 0.0, 0),
     ("f32", 2, 2, 333, 64, 64, 2, 0, True, 0.3, 0),
     ("f32", 1, 1, 130, 32, 128, 1, 0, False, 0.0, 0),       # one or two keys
     ("f32", 1, 2, 1300, 64, 13, 1, 50, False, 0.0, 0),

@@ -19,6 +19,7 @@ COLUMNS = [
     ("bf16", 1, 26, 601, 64, 100, 30, 0, False, 0.0),   # three sets
     ("bf16", 5, 9, 700, 64, 100, 20, 0, False, 0.3),    # one
     ("bf16", 1, 1, 1300, 64, 13, 5, 100, True, 0.0),    # 20 of 100 keys a column
+    ("bf16", 1, 4, 4001, 64, 128, 2, 0, True, 0.3),     # few keys per row: row by row
 ]
 F32 = [
     ("f32", 1, 2, 385, 64, 128, 33, 0, True, 0.0),      # columns of any width
