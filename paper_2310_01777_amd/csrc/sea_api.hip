@@ -287,7 +287,7 @@ int sea_sparse_attn(const sea_params* p, const void* Q, const void* K, const voi
   if (rc != SEA_OK) return rc;
   if (!Q || !K || !V || !idx || !cnt || !O || row_stride <= 0) return SEA_EINVAL;
   const Shape s = make_shape(p, false);
-  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, row_stride, nullptr, O,
+  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, row_stride, nullptr, row_stride, O,
                                           static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? SEA_OK : fail_hip(e);
 }
@@ -331,7 +331,9 @@ int sea_flatcsr_attn(const sea_params* p, const void* Q, const void* K, const vo
   if (!Q || !K || !V || !crow || !col || !O) return SEA_EINVAL;
   if (static_cast<int64_t>(p->H) * p->T > INT32_MAX) return SEA_ENOTSUP;
   const Shape s = make_shape(p, false);
-  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, col, nullptr, 0, crow, O,
+  // how long the lists can be is known where the parameters are those of a selection
+  const int32_t stride = check_mask_params(p) == SEA_OK ? row_stride_of(p) : -1;
+  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, col, nullptr, 0, crow, stride > 0 ? stride : s.T, O,
                                           static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? SEA_OK : fail_hip(e);
 }
@@ -460,7 +462,7 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
   if (!mbits && s.grouping == 1) mbits = reinterpret_cast<uint32_t*>(w);  // selection as bits, lists from them
   e = launch_topk_mask(s, A_hat, sel_opt, idx, cnt, mbits, st);
   if (e != hipSuccess) return fail_hip(e);
-  e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, O, st);
+  e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, s.L, O, st);
   return e == hipSuccess ? SEA_OK : fail_hip(e);
 }
 }  // namespace
@@ -599,7 +601,7 @@ int sea_decoder_forward(const sea_params* p, const sea_decoder_weights* w, const
     int32_t* cnt = reinterpret_cast<int32_t*>(att + align256(rows * static_cast<size_t>(s.L) * sizeof(int32_t)));
     e = launch_topk_mask(s, A_hat, nullptr, idx, cnt, s.grouping == 1 ? mbits : nullptr, st);
     if (e != hipSuccess) return fail_hip(e);
-    e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, O, st);
+    e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, s.L, O, st);
   }
   if (e != hipSuccess) return fail_hip(e);
   e = launch_output_mix(s, p->dtype, O, V, A_hat, s_prob, s_mix, O, base + lay.mix, st);

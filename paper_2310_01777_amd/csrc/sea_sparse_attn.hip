@@ -15,14 +15,14 @@ namespace {
 
 constexpr int kWavesPerBlock = 4;
 
-// Where a row's key list lives.  Per-row lists: idx + row L, cnt[row] entries.  FlatCSR tensor
-// (crow != nullptr, idx = its column array): row (b, h, t) owns the entries of CSR row b T + t
-// whose column h' T + j has h' = h -- one contiguous run because columns ascend -- found by two
-// searches; the key is the entry minus h T.
+// Where a row's key list lives.  Per-row lists (FLAT = false): idx + row L, cnt[row] entries.  FlatCSR tensor
+// (idx = its column array): row (b, h, t) owns the entries of CSR row b T + t whose column h' T + j has
+// h' = h -- one contiguous run because columns ascend -- found by two searches; the key is the entry minus h T.
+template <bool FLAT>
 __device__ __forceinline__ ListKeys key_list(const Shape& s, int64_t row, const int32_t* __restrict__ idx,
                                             const int32_t* __restrict__ cnt, int32_t L,
                                             const int64_t* __restrict__ crow) {
-  if (crow == nullptr) return {idx + row * L, min(cnt[row], L), 0, s.T};
+  if (!FLAT) return {idx + row * L, min(cnt[row], L), 0, s.T};
   const int64_t head = row / s.T, t = row - head * s.T;
   const int64_t b = head / s.H, h = head - b * s.H;
   const int64_t beg = crow[b * s.T + t], end = crow[b * s.T + t + 1];
@@ -57,24 +57,56 @@ __device__ __forceinline__ ListKeys key_list(const Shape& s, int64_t row, const 
   return {idx + bound[0], static_cast<int32_t>(bound[1] - bound[0]), static_cast<int32_t>(h * s.T), s.T};
 }
 
+// The row (or rows) of a wave.  A grid dimension holds fewer than 2^32 threads: from 2^26 rows on, slices of 2^22 blocks.
+constexpr uint32_t kSlice = 1u << 22;
+dim3 row_grid(int64_t nrows) {
+  const int64_t blocks = (nrows + kWavesPerBlock - 1) / kWavesPerBlock;
+  return blocks < (int64_t(1) << 24) ? dim3(static_cast<uint32_t>(blocks)) : dim3(kSlice, static_cast<uint32_t>((blocks + kSlice - 1) / kSlice));
+}
+__device__ __forceinline__ int64_t wave_row() {
+  const int64_t block = static_cast<int64_t>(blockIdx.y) * gridDim.x + xcd_contiguous(blockIdx.x, gridDim.x);
+  return block * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+// key_list for one row, by the whole wave: half the lanes search the run's first entry, half its end.  The heads of a
+// time step list about equally many keys, so the first 32 probes lie side by side around where that puts the
+// bound (one or two cache lines); after that 32 probes cut the range evenly.
+template <bool FLAT>
+__device__ __forceinline__ ListKeys wave_key_list(const Shape& s, int64_t row, const int32_t* __restrict__ idx,
+                                                 const int32_t* __restrict__ cnt, int32_t L,
+                                                 const int64_t* __restrict__ crow) {
+  if (!FLAT) return key_list<false>(s, row, idx, cnt, L, crow);
+  const int64_t head = row / s.T, t = row - head * s.T;
+  const int64_t b = head / s.H, h = head - b * s.H;
+  const int64_t beg = crow[b * s.T + t], end = crow[b * s.T + t + 1];
+  const int lane = threadIdx.x & 63, probe = lane & 31;
+  const int64_t bound = (h + (lane >> 5)) * s.T;
+  int32_t lo = 0, hi = static_cast<int32_t>(max(end - beg, static_cast<int64_t>(0)));
+  auto passed_by = [&](int32_t at) {  // how many of the half's probes lie below its bound
+    const uint64_t mask = __ballot(at < hi && idx[beg + at] < bound);
+    return __popc(static_cast<uint32_t>(lane < 32 ? mask : mask >> 32));
+  };
+  {
+    const int32_t guess = static_cast<int32_t>((h + (lane >> 5)) * hi / s.H);
+    const int32_t from = max(min(guess - 16, hi - 32), 0), passed = passed_by(from + probe);
+    if (passed < 32 && from + passed < hi) hi = from + passed;
+    if (passed > 0) lo = from + passed;
+  }
+  while (__ballot(lo < hi) != 0ull) {
+    const int32_t step = (hi - lo + 31) >> 5, passed = passed_by(lo + (probe + 1) * step - 1);
+    hi = min(hi, lo + (passed + 1) * step - 1);
+    lo += passed * step;
+  }
+  const int32_t first = __builtin_amdgcn_readlane(lo, 0), past = __builtin_amdgcn_readlane(lo, 32);
+  return {idx + beg + first, past - first, static_cast<int32_t>(h * s.T), s.T};
+}
+
 // one row of the bf16 lists
 __device__ __forceinline__ void gather_list_row(const Shape& s, int64_t head, int64_t row, const ListKeys& kl,
                                                 const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                                                 const uint16_t* __restrict__ V, uint16_t* __restrict__ O) {
   const int64_t first = head * s.T * kHeadDim, at = row * kHeadDim;
   gather_row_bf16(kl, s.scale * kLog2e, Q + at, K + first, V + first, O + at);
-}
-
-__global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel(
-    Shape s, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-    const uint16_t* __restrict__ V, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int32_t L, const int64_t* __restrict__ crow,
-    uint16_t* __restrict__ O) {
-  const uint32_t lb = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int64_t row = static_cast<int64_t>(lb) * kWavesPerBlock + (threadIdx.x >> 6);
-  const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
-  if (row >= nrows) return;
-  gather_list_row(s, row / s.T, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -87,11 +119,12 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel
 // way; steps without one are skipped, and the rows of unused keys are not read from memory (a buffer
 // load past the end returns zero).  What another row of the block lists cannot reach a row either: a value
 // that is not finite gives NaN against a weight of zero, and rows whose accumulators are not finite are
-// computed again with the gather form.
+// left to the gather form.
 //
 // This is right for lists that ascend without repetition.  Whatever else the caller passes is found out
 // by counting: the bits set over all windows equal the list lengths exactly when every entry was seen,
-// valid and unique.  A block that fails the count computes its rows again with the gather form.
+// valid and unique.  A block leaves its rows to the gather form at the first window after which a cursor is
+// not where it should be.
 //
 // Bound: vector issue (key bits: one bit-extract and one select per score) and, in front of it, the list
 // bytes, 4 per (query, key) pair.  See the launcher for when a block takes this form and what it gives.
@@ -112,44 +145,38 @@ constexpr int kChunk = 64, kKRow = 72, kVRow = 64;
 typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));  // lists start at any entry
 constexpr int kBitRow = kWindow / 32 + 1;  // words per row of key bits, padded
 
-// Are the lists of the 128 rows dense enough for tiles?  The break-even is about one listed key in twenty of
-// the keys spanned (70 G listed pairs/s gathered, 1.5 T spanned pairs/s in tiles); one in sixteen leaves
-// the unpacking its share.  The answer is that of all heads of the time steps together, with the span of the
-// last head: for a FlatCSR tensor that takes two row pointers instead of a search per row, and lists and
-// tensor of the same mask get the same answer.  Both kernels below ask; every thread of the block takes
-// part (one barrier), `red` has a place per wave.
-__device__ __forceinline__ bool block_is_dense(const Shape& s, int64_t head, int32_t row0, int tid,
-                                               const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                               int32_t L, const int64_t* __restrict__ crow, int32_t (*red)[2]) {
-  const int32_t t = row0 + tid;
-  const bool mine = tid < kTileRows && t < s.T;
+// Do the 128 rows from row0 on take tiles?  Both forms cost about a fixed time and one per key.  With the chip
+// full: 128 rows read one by one 58 ns + 1.28 ns a listed key per row, the tile walk 96 ns per 1024 keys spanned.
+// Inside a launch that has tiles a little less than that counts, since rows left over pay for a second tail,
+// and a block takes no less than 115 ns.  The answer comes from eight rows of the block, the lists of all heads
+// together and the span of the last one: for a FlatCSR tensor that takes row pointers instead of searches, and
+// lists and tensor of the same mask get the same answer.  The whole wave calls.
+constexpr float kRowsNs = 58.f, kRowKeyNs = 1.28f, kWindowNs = 96.f, kBlockNs = 115.f;
+template <bool FLAT>
+__device__ __forceinline__ bool takes_tiles(const Shape& s, int64_t head, int32_t row0, const int32_t* __restrict__ idx,
+                                            const int32_t* __restrict__ cnt, int32_t L,
+                                            const int64_t* __restrict__ crow) {
+  const int lane = threadIdx.x & 63;
+  const int32_t t = min(row0 + 16 * (lane & 7) + 15, s.T - 1);
   const int64_t b = head / s.H;
   int32_t n = 0, last = 0;
-  if (mine && crow == nullptr) {
-    int64_t all = 0;
-    int32_t nh = 0;
-#pragma unroll 4
-    for (int32_t h = 0; h < s.H; ++h) {
-      nh = min(max(cnt[(b * s.H + h) * s.T + t], 0), L);
-      all += nh;
+  if (!FLAT) {
+    for (int32_t h = lane >> 3; h < s.H; h += 8) {
+      const int64_t at = (b * s.H + h) * s.T + t;
+      const int32_t nh = min(max(cnt[at], 0), L);
+      n += nh;
+      if (h == s.H - 1 && nh > 0) last = idx[at * L + nh - 1];
     }
-    n = static_cast<int32_t>((all + s.H - 1) / s.H);
-    if (nh > 0) last = idx[((b * s.H + s.H - 1) * s.T + t) * L + nh - 1];
-  } else if (mine) {
+  } else if (lane < 8) {
     const int64_t beg = crow[b * s.T + t], end = crow[b * s.T + t + 1];
-    n = end > beg ? static_cast<int32_t>((end - beg + s.H - 1) / s.H) : 0;
+    n = static_cast<int32_t>(max(end - beg, static_cast<int64_t>(0)));
     if (n > 0) last = static_cast<int32_t>(idx[end - 1] - static_cast<int64_t>(s.H - 1) * s.T);
   }
-  if (n > 0) last = min(max(last, 0), s.T - 1) + 1;
+  n = wave_sum(n);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    n += __shfl_xor(n, off, kWave);
-    last = max(last, __shfl_xor(last, off, kWave));
-  }
-  if ((tid & 63) == 0) { red[tid >> 6][0] = n; red[tid >> 6][1] = last; }
-  __syncthreads();
-  const int64_t total = static_cast<int64_t>(red[0][0]) + red[1][0];
-  return total > 0 && total * 16 >= static_cast<int64_t>(kTileRows) * max(red[0][1], red[1][1]);
+  for (int off = 32; off >= 1; off >>= 1) last = max(last, __shfl_xor(last, off, kWave));
+  const float rows = 8.f * static_cast<float>(s.H), windows = static_cast<float>(min(last, s.T - 1) + 1) / static_cast<float>(kWindow);
+  return n > 0 && fmaf(kRowKeyNs, static_cast<float>(n), kRowsNs * rows) >= rows * fmaxf(0.9f * kWindowNs * windows, kBlockNs);
 }
 // block -> (head, first row): heads in groups that share the L2s, the last (longest, if causal) rows first
 __device__ __forceinline__ void tile_block(const Shape& s, int32_t group_heads, int64_t* head, int32_t* row0) {
@@ -161,25 +188,38 @@ __device__ __forceinline__ void tile_block(const Shape& s, int32_t group_heads, 
   *row0 = static_cast<int32_t>(wgs - 1 - rem / nh) * kTileRows;
 }
 
-// the rows of the blocks that do not take tiles, eight per wave
-__global__ __launch_bounds__(1024) void list_rest_kernel(Shape s, const uint16_t* __restrict__ Q,
-                                                         const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
-                                                         const int32_t* __restrict__ idx,
-                                                         const int32_t* __restrict__ cnt, int32_t L,
-                                                         const int64_t* __restrict__ crow, uint16_t* __restrict__ O,
-                                                         int32_t group_heads) {
-  __shared__ int32_t red[16][2];
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int64_t head;
-  int32_t row0;
-  tile_block(s, group_heads, &head, &row0);
-  if (block_is_dense(s, head, row0, threadIdx.x, idx, cnt, L, crow, red)) return;
-  for (int32_t t = row0 + wid; t < min(row0 + kTileRows, s.T); t += 16) {
-    const int64_t row = head * s.T + t;
-    gather_list_row(s, head, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
+template <bool FLAT>
+__global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_bf16_kernel(
+    Shape s, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int32_t L, const int64_t* __restrict__ crow,
+    uint16_t* __restrict__ O) {
+  const int64_t row = wave_row();
+  const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
+  if (row >= nrows) return;
+  gather_list_row(s, row / s.T, row, wave_key_list<FLAT>(s, row, idx, cnt, L, crow), Q, K, V, O);
+}
+
+// The tile walk leaves rows to the kernel that follows it, four rows a wave, by this pattern in place of their
+// result (its first word, where the block took no tiles).  A result may look like that (it is a NaN); the row is
+// then computed twice.
+constexpr uint32_t kRowLeft = 0xffffffffu;
+constexpr int kRestRows = 4;
+template <bool FLAT>
+__global__ __launch_bounds__(kWavesPerBlock* kWave) void list_rest_kernel(
+    Shape s, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int32_t L, const int64_t* __restrict__ crow,
+    uint16_t* __restrict__ O) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row0 = wave_row() * kRestRows, nrows = static_cast<int64_t>(s.N) * s.T, mine = row0 + lane;
+  const bool left = lane < kRestRows && mine < nrows && *reinterpret_cast<const uint32_t*>(O + mine * kHeadDim) == kRowLeft;
+  for (uint64_t rows = __ballot(left); rows != 0ull; rows &= rows - 1ull) {
+    const int64_t row = row0 + __ffsll(static_cast<unsigned long long>(rows)) - 1;
+    gather_list_row(s, row / s.T, row, wave_key_list<FLAT>(s, row, idx, cnt, L, crow), Q, K, V, O);
   }
 }
 
+template <bool FLAT>
 __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                            const uint16_t* __restrict__ K,
                                                            const uint16_t* __restrict__ V,
@@ -192,30 +232,31 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
   __shared__ __attribute__((aligned(16))) uint8_t strip[4][kWindow + 16];
   __shared__ uint32_t bits[kTileRows * kBitRow];
   __shared__ uint32_t used[2][kWindow / 32];  // keys of the window any row of the block lists
-  __shared__ int32_t red[4][2];
+  __shared__ int32_t red[4];
+  __shared__ uint32_t astray;  // a row whose list is not what the walk takes it for
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ql = lane & 31, g = lane >> 5;
   int64_t head;
   int32_t row0;
   tile_block(s, group_heads, &head, &row0);
-  if (!block_is_dense(s, head, row0, tid, idx, cnt, L, crow, red)) return;
+  if (!takes_tiles<FLAT>(s, head, row0, idx, cnt, L, crow)) {
+    if (tid < kTileRows && row0 + tid < s.T) *reinterpret_cast<uint32_t*>(O + (head * s.T + row0 + tid) * kHeadDim) = kRowLeft;
+    return;
+  }
 
   const int32_t t = row0 + 32 * wid + ql;
   // lane r < 32 holds the list of row 32 wid + r
   ListKeys kl = {idx, 0, 0, s.T};
-  if (lane < 32 && t < s.T) kl = key_list(s, head * s.T + t, idx, cnt, L, crow);
+  if (lane < 32 && t < s.T) kl = key_list<FLAT>(s, head * s.T + t, idx, cnt, L, crow);
   kl.n = max(kl.n, 0);
-  int32_t total = kl.n, span = kl.n > 0 ? min(max(kl.p[kl.n - 1] - kl.base, 0), s.T - 1) + 1 : 0;
+  int32_t span = kl.n > 0 ? min(max(kl.p[kl.n - 1] - kl.base, 0), s.T - 1) + 1 : 0;
   // 256-entry pieces of the row's list that a window of an evenly spread list takes, and a little more
   const int32_t expect = span > 0 ? min(4, static_cast<int32_t>(static_cast<float>(kl.n) * static_cast<float>(kWindow) / static_cast<float>(span) + 64.f) / 256 + 1) : 1;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    total += __shfl_xor(total, off, kWave);
-    span = max(span, __shfl_xor(span, off, kWave));
-  }
-  __syncthreads();  // red[] has been read
-  if (lane == 0) { red[wid][0] = total; red[wid][1] = span; }
+  for (int off = 32; off >= 1; off >>= 1) span = max(span, __shfl_xor(span, off, kWave));
+  if (lane == 0) red[wid] = span;
+  if (tid == 0) astray = 0u;
   const uint16_t* Qr = Q + (head * s.T + min(t, s.T - 1)) * kHeadDim + 8 * g;
   bf16x8 bq[4];
 #pragma unroll
@@ -242,12 +283,10 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
   const uint32_t inf_bits = 0xff800000u;
 
   int32_t cursor = 0;    // lane r: list entries of row 32 wid + r taken so far
-  uint32_t nset = 0;     // bits this lane has packed
   *reinterpret_cast<uint4*>(&strip[wid][16 * lane]) = make_uint4(0u, 0u, 0u, 0u);
   if (tid < 2 * (kWindow / 32)) used[tid / (kWindow / 32)][tid % (kWindow / 32)] = 0u;
   __syncthreads();
-  total = red[0][0] + red[1][0] + red[2][0] + red[3][0];
-  span = max(max(red[0][1], red[1][1]), max(red[2][1], red[3][1]));
+  span = max(max(red[0], red[1]), max(red[2], red[3]));
 
   const uint64_t lp = reinterpret_cast<uint64_t>(kl.p);
   for (int32_t w0 = 0, win = 0; w0 < span; w0 += kWindow, ++win) {
@@ -321,7 +360,6 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         // (the spare byte lies inside the last window when T ends there)
         half &= 0xffffu >> min(16, max(0, 16 * lane + 16 - static_cast<int>(nkeys)));
         const int32_t got = __popc(half);
-        nset += got;
         const int32_t took = wave_sum(got);
         if (lane == rr) cursor = cu + took;
       }
@@ -339,10 +377,16 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         take_row(rr + 1, eb);
       }
     }
+    // A row's next entry lies past the window, and after the last window there is none.  (The keys found are
+    // different entries of the list, so a cursor that ends with the list has met every entry once.)
+    const bool lost = w0 + kWindow >= span ? cursor != kl.n : (cursor < kl.n && kl.p[cursor] - kl.base < w0 + kWindow);
+    const uint64_t rows_lost = __ballot(lost);
+    if (lane == 0 && rows_lost != 0ull) atomicOr(&astray, 1u);
     // keys used by the block, in 32-key words (lanes 2 i, 2 i + 1 hold the halves of word i)
     const uint32_t upper = __shfl_xor(wave_used, 1, kWave);
     if ((lane & 1) == 0) atomicOr(&used[win & 1][lane >> 1], wave_used | (upper << 16));
     __syncthreads();
+    if (astray != 0u) break;
     const uint32_t* uw = used[win & 1];
     // 64-key steps with a used key (uniform): lanes 0..15 look at one step each
     uint32_t steps = static_cast<uint32_t>(__ballot(lane < kWindow / 64 && (uw[2 * (lane & 15)] | uw[2 * (lane & 15) + 1]) != 0u));
@@ -419,79 +463,80 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
     if (tid < kWindow / 32) used[(win & 1) ^ 1][tid] = 0u;  // for the next window (nobody reads it now)
     __syncthreads();
   }
-  // every list entry seen exactly once?
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) nset += __shfl_xor(nset, off, kWave);
-  if (lane == 0) red[wid][0] = static_cast<int32_t>(nset);
-  __syncthreads();
-  const bool lists_ok = red[0][0] + red[1][0] + red[2][0] + red[3][0] == total;
   l_run = half_sum(l_run);
-  const uint32_t rows_here = static_cast<uint32_t>(__ballot(t < s.T));
-  const uint32_t rows_again = lists_ok ? rows_not_finite(l_run, oacc) & rows_here : rows_here;
-  if (t < s.T && ((rows_again >> ql) & 1u) == 0u) {
+  const bool left = astray != 0u || ((rows_not_finite(l_run, oacc) >> ql) & 1u) != 0u;
+  if (t < s.T) {
     const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
     uint16_t* Or = O + (head * s.T + t) * kHeadDim;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
-        const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
-        const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
-        *reinterpret_cast<bf16x4*>(Or + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
+        uint2 o = {pack_bf16(oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv),
+                   pack_bf16(oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv)};
+        if (left) o = {kRowLeft, kRowLeft};
+        *reinterpret_cast<uint2*>(Or + 32 * mt + 8 * q4 + 4 * g) = o;
       }
-  }
-  for (uint32_t rows = rows_again; rows != 0u; rows &= rows - 1u) {
-    const int64_t row = head * s.T + row0 + 32 * wid + __ffs(static_cast<int>(rows)) - 1;
-    gather_list_row(s, head, row, key_list(s, row, idx, cnt, L, crow), Q, K, V, O);
   }
 }
 
+template <bool FLAT>
 __global__ __launch_bounds__(kWavesPerBlock* kWave) void sparse_attn_f32_kernel(
     Shape s, const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int32_t L,
     const int64_t* __restrict__ crow, float* __restrict__ O) {
-  const uint32_t lb = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int64_t row = static_cast<int64_t>(lb) * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t row = wave_row();
   const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
   if (row >= nrows) return;
   const int64_t head = row / s.T, first = head * s.T * kHeadDim, at = row * kHeadDim;
-  gather_row_f32(key_list(s, row, idx, cnt, L, crow), static_cast<double>(s.scale) * 1.4426950408889634, Q + at, K + first,
+  gather_row_f32(wave_key_list<FLAT>(s, row, idx, cnt, L, crow), static_cast<double>(s.scale) * 1.4426950408889634, Q + at, K + first,
                  V + first, O + at);
 }
 
-// Tiles from one 128-row block per CU on.  Below that a block's walk (two windows of a 2048-key sequence are
-// about 0.1 ms) is longer than the gather of all rows with one wave each: 12 heads of 1024 rows 0.09 against
-// 0.11 ms; 48 heads of 1024 rows the tiles win by a third, 48 heads of 2048 rows (75 M listed pairs, three
-// quarters of the causal triangle) 1.05 -> 0.20 ms.
-constexpr int64_t kMinTileBlocks = 256;
+// Tiles from one 128-row block per CU on, where lists of `longest` keys would take them over the whole sequence
+// (causal: over three quarters of it, earlier rows span less; a launch of which only a part takes tiles pays for
+// both forms' tails), and not where the rows, read one by one, are done before a block could be: alone on its CU a
+// block takes 58 us per window.
+// us, rows / tiles: 48 heads, T = 2048, bidirectional, 128 keys 150 / 165, 256 keys 285 / 165, causal 128 keys 150 /
+// 115; 64 heads, T = 4096, 256 keys 830 / 790, causal 810 / 530; 32 heads, T = 1024, 64 keys 34 / 62, 256 keys 104 /
+// 63.
+bool tiles_worth_a_launch(const Shape& s, int64_t blocks, int32_t longest) {
+  if (blocks < 256 || s.T > (1 << 24) || static_cast<int64_t>(s.H) * s.T > (1 << 28)) return false;
+  const float rows = kRowsNs + kRowKeyNs * static_cast<float>(longest), windows = static_cast<float>(s.T) / static_cast<float>(kWindow);
+  return rows >= (s.causal ? 0.75f : 1.f) * windows * kWindowNs &&
+         rows * static_cast<float>(blocks) >= 58e3f * (windows > 1.f ? windows : 1.f);
+}
+
+template <bool FLAT>
+void launch_lists(const Shape& s, sea_dtype dt, const void* Q, const void* K, const void* V, const int32_t* idx,
+                  const int32_t* cnt, int32_t L, const int64_t* crow, int32_t longest, void* O, hipStream_t st) {
+  const int64_t nrows = static_cast<int64_t>(s.N) * s.T, tiles = static_cast<int64_t>(s.N) * ((s.T + kTileRows - 1) / kTileRows);
+  const dim3 block(kWavesPerBlock * kWave);
+  if (dt == SEA_F32) {
+    hipLaunchKernelGGL(sparse_attn_f32_kernel<FLAT>, row_grid(nrows), block, 0, st, s, static_cast<const float*>(Q),
+                       static_cast<const float*>(K), static_cast<const float*>(V), idx, cnt, L, crow, static_cast<float*>(O));
+    return;
+  }
+  const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K), *v = static_cast<const uint16_t*>(V);
+  uint16_t* o = static_cast<uint16_t*>(O);
+  if (tiles_worth_a_launch(s, tiles, longest)) {
+    hipLaunchKernelGGL(list_tile_kernel<FLAT>, dim3(static_cast<uint32_t>(tiles)), dim3(256), 0, st, s, q, k, v, idx, cnt, L,
+                       crow, o, group_heads_for(s.N, s.T));
+    hipLaunchKernelGGL(list_rest_kernel<FLAT>, row_grid((nrows + kRestRows - 1) / kRestRows), block, 0, st, s, q, k, v, idx,
+                       cnt, L, crow, o);
+  } else {
+    hipLaunchKernelGGL(sparse_attn_bf16_kernel<FLAT>, row_grid(nrows), block, 0, st, s, q, k, v, idx, cnt, L, crow, o);
+  }
+}
 
 }  // namespace
 
 hipError_t launch_sparse_attn(const Shape& s, sea_dtype dt, const void* Q, const void* K,
                               const void* V, const int32_t* idx, const int32_t* cnt, int32_t L,
-                              const int64_t* crow, void* O, hipStream_t st) {
-  const int64_t nrows = static_cast<int64_t>(s.N) * s.T;
-  const uint32_t grid = static_cast<uint32_t>((nrows + kWavesPerBlock - 1) / kWavesPerBlock);
+                              const int64_t* crow, int32_t longest, void* O, hipStream_t st) {
   StageScope scope(SEA_STAGE_SPARSE, st);
-  const int64_t tiles = static_cast<int64_t>(s.N) * ((s.T + kTileRows - 1) / kTileRows);
-  if (dt == SEA_BF16 && tiles >= kMinTileBlocks && s.T <= (1 << 24)) {
-    const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K),
-                   *v = static_cast<const uint16_t*>(V);
-    uint16_t* o = static_cast<uint16_t*>(O);
-    const int32_t gh = group_heads_for(s.N, s.T);
-    const dim3 tgrid(static_cast<uint32_t>(tiles));
-    hipLaunchKernelGGL(list_tile_kernel, tgrid, dim3(256), 0, st, s, q, k, v, idx, cnt, L, crow, o, gh);
-    hipLaunchKernelGGL(list_rest_kernel, tgrid, dim3(1024), 0, st, s, q, k, v, idx, cnt, L, crow, o, gh);
-  } else if (dt == SEA_BF16) {
-    hipLaunchKernelGGL(sparse_attn_bf16_kernel, dim3(grid), dim3(kWavesPerBlock * kWave), 0, st, s,
-                       static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
-                       static_cast<const uint16_t*>(V), idx, cnt, L, crow, static_cast<uint16_t*>(O));
-  } else {
-    hipLaunchKernelGGL(sparse_attn_f32_kernel, dim3(grid), dim3(kWavesPerBlock * kWave), 0, st, s,
-                       static_cast<const float*>(Q), static_cast<const float*>(K),
-                       static_cast<const float*>(V), idx, cnt, L, crow, static_cast<float*>(O));
-  }
+  if (crow != nullptr) launch_lists<true>(s, dt, Q, K, V, idx, cnt, L, crow, longest, O, st);
+  else launch_lists<false>(s, dt, Q, K, V, idx, cnt, L, crow, longest, O, st);
   return hipGetLastError();
 }
 

@@ -28,7 +28,7 @@ def _lists(B, H, T, L, density, seed):
 
 
 @pytest.mark.parametrize("T,N,L,density", [(1100, 30, 1100, 0.4), (2080, 16, 2080, 0.9), (513, 52, 200, 0.2),
-                                           (1024, 32, 40, 0.03)])
+                                           (1024, 32, 40, 0.03), (1100, 60, 1100, 0.5), (513, 104, 513, 0.5)])
 def test_dense_lists(T, N, L, density):
     from paper_2310_01777_amd import binding as sea
     B, H = 2, N // 2
@@ -82,3 +82,36 @@ def test_dense_lists(T, N, L, density):
     assert np.array_equal(crow.cpu().numpy(), crow_o) and np.array_equal(col.cpu().numpy(), col_o)
     assert torch.equal(O1, O2)
     assert_close(to_np64(O1), oracle.sparse_attn(po, c["Q"], c["K"], c["V"], idx, cnt), TOL["bf16"], "O from the tensor")
+
+
+def test_lists_astray_in_later_windows():
+    """Lists that stop ascending, repeat or leave the sequence behind the first 1024 keys, in blocks of dense lists."""
+    from paper_2310_01777_amd import binding as sea
+    B, H, T = 1, 16, 2080
+    wl = synth.Workload("lists", B, H, T, 64, 32, 16, 4, 0, True, "bf16", 4)
+    x = synth.make_inputs(wl)
+    L = T + 1
+    idx = np.full((B, H, T, L), -1, dtype=np.int32)
+    for t in range(T):
+        idx[:, :, t, :t + 1] = np.arange(t + 1)
+    cnt = np.broadcast_to(np.arange(1, T + 1, dtype=np.int32), (B, H, T)).copy()
+    idx[0, 0, 2000, [1499, 1500]] = [1500, 1499]                        # out of order
+    idx[0, 1, 1900, 1025:1901] = 1024                                   # 1024 many times, at the window's edge
+    idx[0, 2, 2079, 2079] = T + 7                                       # outside, at the end
+    idx[0, 3, 1030, 1026] = -5                                          # outside, among the last
+    idx[0, 4, 2079, 2080], cnt[0, 4, 2079] = 3, T + 1                   # back to the first window
+    idx[0, 5, 1200, 600:1200] = np.arange(600)                          # the first half twice
+    idx[0, 6, 1500, 1:1501] = np.concatenate([np.arange(1030, 1501), np.arange(1, 1030)])  # windows exchanged
+    d = {k: x[k].cuda() for k in "QKV"}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=32, K=16, k_hat=4, causal=True, scale=wl.scale, dtype="bf16")
+    O = torch.full((B, H, T, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print("[case] lists astray", flush=True)
+    sea.sea_sparse_attn(p, d["Q"], d["K"], d["V"], torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda(), L, O)
+    ok_idx, ok_cnt = idx.copy(), cnt.copy()
+    for h, t, bad in ((2, 2079, T + 7), (3, 1030, -5)):
+        keep = idx[0, h, t, :cnt[0, h, t]]
+        keep = keep[keep != bad]
+        ok_idx[0, h, t], ok_cnt[0, h, t] = -1, len(keep)
+        ok_idx[0, h, t, :len(keep)] = keep
+    want = oracle.sparse_attn(oracle_params(wl), to_np64(x["Q"]), to_np64(x["K"]), to_np64(x["V"]), ok_idx, ok_cnt)
+    assert_close(to_np64(O), want, TOL["bf16"], "O from lists")
