@@ -5,7 +5,8 @@
 //
 // Built from the per-(head, row) key lists in three launches: per-row entry counts with an
 // exclusive scan inside each 256-row block, a one-block scan of the block totals, and a copy that
-// moves each list to its place with one block per CSR row (reads and writes contiguous).
+// moves each list to its place with one block (short lists: one wave) per CSR row (reads and writes
+// contiguous).
 #include "sea_internal.h"
 
 namespace sea {
@@ -120,6 +121,50 @@ __global__ __launch_bounds__(256) void flat_copy_kernel(Shape s, const int32_t* 
   }
 }
 
+// Lists of at most 4 G entries: one wave per CSR row, G lanes per head, a 16-byte piece each, so that 64 / G heads
+// move at a time and a row costs no barrier.  All three launches in us, a wave per CSR row with 4-byte pieces / a
+// block per CSR row / this: B = 4, H = 12, T = 2048, 16 entries 16 / 25 / 13, 64 entries 21 / 29 / 18, 128 entries 29 /
+// 29 / 25; H = 8, T = 8192, 64 entries 17 / 24 / 14; H = 32, T = 2048, 128 entries 46 / 27 / 27.
+template <int G>
+__global__ __launch_bounds__(256) void flat_copy_short_kernel(Shape s, const int32_t* __restrict__ idx,
+                                                              const int32_t* __restrict__ cnt, int32_t L, int64_t R,
+                                                              int64_t* __restrict__ crow,
+                                                              const int64_t* __restrict__ bsum,
+                                                              int32_t* __restrict__ col, int64_t cap) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row >= R) return;
+  const int64_t b = row / s.T, t = row - b * s.T;
+  const int64_t start = crow[row] + bsum[row / kScanRows];
+  int64_t off0 = start;
+  for (int32_t hb = 0; hb < s.H; hb += kWave) {
+    const int32_t nh = min(s.H - hb, static_cast<int32_t>(kWave));
+    const int32_t n_l = lane < nh ? list_len(cnt, (b * s.H + hb + lane) * s.T + t, L) : 0;
+    int32_t incl = n_l;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int32_t below = __shfl_up(incl, off, kWave);
+      if (lane >= off) incl += below;
+    }
+#pragma unroll 4
+    for (int32_t h0 = 0; h0 < nh; h0 += kWave / G) {
+      const int32_t hi = h0 + lane / G, i = 4 * (lane % G), h = hb + hi;
+      const int32_t n = __shfl(n_l, hi, kWave), left = n - i;  // (0 entries past the last head)
+      const int64_t at = off0 + __shfl(incl, hi, kWave) - left;
+      const int32_t* src = idx + ((b * s.H + h) * s.T + t) * L + i;
+      const int32_t add = h * s.T;
+      if (left >= 4 && at + 4 <= cap) {
+        *reinterpret_cast<i32x4*>(col + at) = *reinterpret_cast<const i32x4*>(src) + add;
+      } else {
+        for (int32_t e = 0; e < min(left, 4); ++e)
+          if (at + e < cap) col[at + e] = add + src[e];
+      }
+    }
+    off0 += __builtin_amdgcn_readlane(incl, kWave - 1);
+  }
+  if (lane == 0) crow[row] = start;  // only this wave reads crow[row], before this store
+}
+
 }  // namespace
 
 size_t flatcsr_workspace(const Shape& s) {
@@ -136,7 +181,10 @@ hipError_t launch_flatcsr(const Shape& s, const int32_t* idx, const int32_t* cnt
   hipLaunchKernelGGL(flat_count_kernel, dim3(static_cast<uint32_t>(nblk)), dim3(kScanRows), 0, st, s, cnt, L, R,
                      crow, bsum);
   hipLaunchKernelGGL(flat_scan_kernel, dim3(1), dim3(1024), 0, st, bsum, nblk, crow + R);
-  hipLaunchKernelGGL(flat_copy_kernel, dim3(static_cast<uint32_t>(R)), dim3(256), 0, st, s, idx, cnt, L, crow, bsum, col, cap);
+  const dim3 rows4(static_cast<uint32_t>((R + 3) / 4));
+  if (L <= 64) hipLaunchKernelGGL(flat_copy_short_kernel<16>, rows4, dim3(256), 0, st, s, idx, cnt, L, R, crow, bsum, col, cap);
+  else if (L <= 128) hipLaunchKernelGGL(flat_copy_short_kernel<32>, rows4, dim3(256), 0, st, s, idx, cnt, L, R, crow, bsum, col, cap);
+  else hipLaunchKernelGGL(flat_copy_kernel, dim3(static_cast<uint32_t>(R)), dim3(256), 0, st, s, idx, cnt, L, crow, bsum, col, cap);
   return hipGetLastError();
 }
 

@@ -115,3 +115,27 @@ def test_lists_astray_in_later_windows():
         ok_idx[0, h, t, :len(keep)] = keep
     want = oracle.sparse_attn(oracle_params(wl), to_np64(x["Q"]), to_np64(x["K"]), to_np64(x["V"]), ok_idx, ok_cnt)
     assert_close(to_np64(O), want, TOL["bf16"], "O from lists")
+
+
+@pytest.mark.parametrize("B,H,T,L", [(1, 1, 5, 1), (2, 3, 70, 4), (1, 7, 300, 63), (2, 5, 257, 64), (1, 4, 130, 65),
+                                     (1, 67, 40, 30), (1, 66, 150, 128), (2, 3, 140, 129)])
+def test_flatcsr_of_short_lists(B, H, T, L):
+    """Lists of any length up to L, the tensor whole and cut inside a list."""
+    from paper_2310_01777_amd import binding as sea
+    rng = np.random.default_rng(L)
+    cnt = rng.integers(0, min(L, T) + 1, (B, H, T)).astype(np.int32)
+    idx = np.full((B, H, T, L), -1, dtype=np.int32)
+    for at in np.ndindex(B, H, T):
+        idx[at][:cnt[at]] = np.sort(rng.choice(T, cnt[at], replace=False))
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=32, K=1, k_hat=1)
+    po = oracle.Params(B=B, H=H, T=T, d=64, m=32, K=1, k_hat=1)
+    crow_o, col_o = oracle.flatcsr(po, idx, cnt)
+    idx_d, cnt_d = torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda()
+    ws = torch.empty(max(256, sea.sea_flatcsr_workspace_bytes(p)), dtype=torch.uint8, device="cuda")
+    print(f"[case] flatcsr {(B, H, T, L)}", flush=True)
+    for cut in (len(col_o), max(len(col_o) // 2, 1), max(len(col_o) - 1, 1)):
+        crow = torch.full((B * T + 1,), -7, dtype=torch.int64, device="cuda")
+        col = torch.full((len(col_o) + 8,), -7, dtype=torch.int32, device="cuda")
+        sea.sea_flatcsr(p, idx_d, cnt_d, L, crow, col[:cut], ws)
+        assert np.array_equal(crow.cpu().numpy(), crow_o)
+        assert np.array_equal(col[:cut].cpu().numpy(), col_o[:cut]) and bool((col[cut:] == -7).all())
