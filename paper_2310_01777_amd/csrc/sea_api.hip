@@ -108,6 +108,15 @@ Shape make_shape(const sea_params* p, bool with_mask) {
   return s;
 }
 
+// Keys a row of one head lists at most, in the mean over the heads (heads that share a quota may list more each),
+// where the parameters are those of a selection whose lists have this stride (0: of any); otherwise `unknown`
+int32_t mean_list_bound(const sea_params* p, int32_t stride, int32_t unknown) {
+  if (check_mask_params(p) != SEA_OK) return unknown;
+  const int32_t L = row_stride_of(p);
+  if (L <= 0 || (stride > 0 && stride != L)) return unknown;
+  return L / sel_stride_of(p) * p->k_hat;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 size_t estimate_ws(const sea_params* p) {
@@ -287,7 +296,8 @@ int sea_sparse_attn(const sea_params* p, const void* Q, const void* K, const voi
   if (rc != SEA_OK) return rc;
   if (!Q || !K || !V || !idx || !cnt || !O || row_stride <= 0) return SEA_EINVAL;
   const Shape s = make_shape(p, false);
-  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, row_stride, nullptr, row_stride, O,
+  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, row_stride, nullptr,
+                                          mean_list_bound(p, row_stride, row_stride), O,
                                           static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? SEA_OK : fail_hip(e);
 }
@@ -331,9 +341,7 @@ int sea_flatcsr_attn(const sea_params* p, const void* Q, const void* K, const vo
   if (!Q || !K || !V || !crow || !col || !O) return SEA_EINVAL;
   if (static_cast<int64_t>(p->H) * p->T > INT32_MAX) return SEA_ENOTSUP;
   const Shape s = make_shape(p, false);
-  // how long the lists can be is known where the parameters are those of a selection
-  const int32_t stride = check_mask_params(p) == SEA_OK ? row_stride_of(p) : -1;
-  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, col, nullptr, 0, crow, stride > 0 ? stride : s.T, O,
+  const hipError_t e = launch_sparse_attn(s, p->dtype, Q, K, V, col, nullptr, 0, crow, mean_list_bound(p, 0, s.T), O,
                                           static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? SEA_OK : fail_hip(e);
 }
@@ -462,7 +470,7 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
   if (!mbits && s.grouping == 1) mbits = reinterpret_cast<uint32_t*>(w);  // selection as bits, lists from them
   e = launch_topk_mask(s, A_hat, sel_opt, idx, cnt, mbits, st);
   if (e != hipSuccess) return fail_hip(e);
-  e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, s.L, O, st);
+  e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, mean_list_bound(p, s.L, s.L), O, st);
   return e == hipSuccess ? SEA_OK : fail_hip(e);
 }
 }  // namespace
@@ -601,7 +609,7 @@ int sea_decoder_forward(const sea_params* p, const sea_decoder_weights* w, const
     int32_t* cnt = reinterpret_cast<int32_t*>(att + align256(rows * static_cast<size_t>(s.L) * sizeof(int32_t)));
     e = launch_topk_mask(s, A_hat, nullptr, idx, cnt, s.grouping == 1 ? mbits : nullptr, st);
     if (e != hipSuccess) return fail_hip(e);
-    e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, s.L, O, st);
+    e = launch_sparse_attn(s, p->dtype, Q, K, V, idx, cnt, s.L, nullptr, mean_list_bound(p, s.L, s.L), O, st);
   }
   if (e != hipSuccess) return fail_hip(e);
   e = launch_output_mix(s, p->dtype, O, V, A_hat, s_prob, s_mix, O, base + lay.mix, st);

@@ -101,7 +101,7 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
 size_t dense_attn_workspace(const Shape& s);
 
 // per-row lists (crow == nullptr: idx [N][T][L], cnt [N][T]) or the FlatCSR tensor (crow [B T + 1],
-// idx = its column array, cnt and L unused); a row of one head lists `longest` keys at most, all heads together
+// idx = its column array, cnt and L unused); a row lists `longest` keys per head at most, in the mean over the heads
 hipError_t launch_sparse_attn(const Shape& s, sea_dtype dt, const void* Q, const void* K,
                               const void* V, const int32_t* idx, const int32_t* cnt, int32_t L,
                               const int64_t* crow, int32_t longest, void* O, hipStream_t st);
