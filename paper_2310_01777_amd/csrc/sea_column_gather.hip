@@ -1,6 +1,8 @@
 // Attention over columns of any width where few keys are selected: one wavefront per query row reads the keys of
 // the row's selected columns one by one, straight from the mask words (sea_gather.h; no key lists are
 // written).
+#include <algorithm>
+
 #include "sea_columns.h"
 #include "sea_gather.h"
 #include "sea_internal.h"
@@ -58,22 +60,27 @@ hipError_t launch(const Shape& s, const void* Q, const void* K, const void* V, c
 
 }  // namespace
 
-// Both forms cost about a fixed time per row and one per key: a row of its own n = k^ r keys, gathered (bf16 0.45
-// ns + 10 ps a key, never less than a batch of 32; fp32 0.45 ns + 27 ps), against the U keys of the list that a
-// tile walks for all its rows, half of them when causal (bf16 0.65 ps a key, fp32 0.35 ns + 4.3 ps; fewer
-// where rows leave chunks out, which is what moves the line).  Whole forward in us, tiles / rows, K = 128,
-// H = 12: bf16, bidirectional, B = 2, T = 8001 k^ = 2, 4, 8 525 / 354, 658 / 606, 767 / 1108, T = 2041 k^ = 2, 4, 8,
-// 16 97 / 59, 109 / 76, 112 / 107, 113 / 173, B = 1, T = 65535 one column of 64 keys 1626 / 863; causal, T = 8001
-// k^ = 2, 4 453 / 357, 496 / 601; fp32, bidirectional, B = 1, T = 3200 k^ = 4, 16, 32 460 / 242, 670 / 538,
-// 715 / 950, causal 327 / 250, 404 / 526, 415 / 883.  Short rows stay in tiles in bf16: H = 32, K = 256, B = 4,
-// T = 1000, k^ = 1 120 / 142.
+// Times of the two forms in us, from sweeps over T = 101 to 65535, K = 25 to 300 and 1 to 384 heads.  A row of its
+// own takes a time per row and one per key it selects, n = k^ r of them (never less than a batch of 32); tiles walk
+// the U keys of the list for all their rows, half of them when causal (chunks that no row selected are left out,
+// which moves the line a little).  Launches that do not fill the chip take as long as one row or the longest
+// list does.  Whole forward in us, tiles / rows, K = 128, H = 12: bf16, bidirectional, B = 2, T = 8001 k^ = 2, 4, 8
+// 525 / 354, 658 / 606, 767 / 1108, T = 2041 k^ = 2, 4, 8, 16 97 / 59, 109 / 76, 112 / 107, 113 / 173, B = 1,
+// T = 65535 one column of 64 keys 1626 / 863; causal, T = 8001 k^ = 2, 4 453 / 357, 496 / 601; H = 32, K = 256,
+// B = 4, T = 1000, k^ = 1 120 / 142; H = 2, B = 1, T = 3001, k^ = 4, 16, 32 54 / 29, 55 / 48, 56 / 75.  fp32,
+// B = 1, T = 3200 k^ = 4, 16, 32 460 / 242, 670 / 538, 715 / 950, causal 327 / 250, 404 / 526, 415 / 883.
 // (A grid has at most 2^32 threads.)
 bool column_gather_pays(const Shape& s, sea_dtype dt) {
-  if (!column_list_supported(s) || s.K > kMaxColumns || static_cast<int64_t>(s.N) * s.T > (int64_t(1) << 25)) return false;
+  const int64_t rows = static_cast<int64_t>(s.N) * s.T;
+  if (!column_list_supported(s) || s.K > kMaxColumns || rows > (int64_t(1) << 25)) return false;
   const ColumnList g = column_list(s);
-  const int64_t r = g.r == 0 ? g.cg.w0 + (g.cg.rm > 0 ? 1 : 0) : g.r;
-  const int64_t n = s.k_hat * r, walked = s.causal ? g.U / 2 : g.U;
-  return dt == SEA_BF16 ? walked >= 15 * ((n > 32 ? n : 32) + 45) : 10 * walked >= 63 * n + 230;
+  const double r = g.r == 0 ? g.cg.w0 + (g.cg.rm > 0 ? 1 : 0) : g.r;
+  const double n = s.k_hat * r, U = g.U, walked = s.causal ? U / 2 : U, krows = rows * 1e-3;
+  const bool bf16 = dt == SEA_BF16;
+  const double one_row = (bf16 ? 0.05 : 0.06) * n, all_rows = krows * std::max(0.72, 0.45 + (bf16 ? 0.010 : 0.027) * n);
+  const double one_list = bf16 ? 3.5 + 0.0115 * U : 2.0 + 0.0165 * U;
+  const double all_lists = krows * (bf16 ? 0.65e-3 * walked : 0.35 + 4.3e-3 * walked);
+  return std::max(one_row, all_rows) <= std::max(one_list, all_lists);
 }
 
 hipError_t launch_column_gather(const Shape& s, sea_dtype dt, const void* Q, const void* K, const void* V,

@@ -38,6 +38,15 @@ CASES = [
     (1, 1, 37, 64, 5, 5, 0, False, 0.0),         # every column selected, less than one step of keys
     (3, 11, 4001, 64, 65, 1, 3, False, 0.0),     # one column per row: row groups end inside heads, shares between them
     (1, 8, 16384, 128, 128, 1, 4, False, 0.0),   # and with full tiles, as few groups as the row kernel takes
+    # most columns selected: tiles, six sets of waves
+    (1, 2, 129, 64, 128, 120, 0, True, 0.0),     # 32 slots
+    (2, 1, 383, 64, 128, 110, 0, False, 0.3),
+    (1, 1, 1030, 32, 1024, 900, 0, True, 0.0),
+    (1, 4, 385, 128, 128, 100, 0, True, 0.0),    # 16 slots
+    (1, 2, 1025, 64, 64, 60, 180, False, 0.3),   # three of 16 or 17 keys
+    (1, 2, 257, 256, 31, 28, 0, True, 0.0),      # 8 slots
+    (1, 2, 1100, 64, 64, 50, 250, True, 0.0),    # five of the 17 or 18 keys of a column
+    (2, 1, 2000, 64, 3, 3, 192, True, 0.3),      # 64 of more than 256
 ]
 
 # aligned columns: how waves share the key list depends on the number of row blocks and the list's length
@@ -101,8 +110,7 @@ def test_any_column_width(dtype, case):
     assert torch.equal(O2, out["O"])
 
 
-# few keys per row: a wavefront per row reads them from the mask words (bf16: 15 (n + 45) keys or more in the list
-# that tiles would walk, fp32: 6.3 n + 23; half the list when causal)
+# few keys per row: a wavefront per row reads them from the mask words, where that is faster than tiles
 # (dtype, B, H, T, m, K, k^, budget, causal, pad, grouping)
 FEW_CASES = [
     ("bf16", 1, 3, 4001, 64, 128, 2, 60, False, 0.0, 0),    # 30 of 31 or 32 keys
@@ -111,15 +119,16 @@ FEW_CASES = [
     ("bf16", 2, 1, 9001, 64, 64, 1, 100, True, 0.5, 0),     # more slots than lanes
     ("bf16", 1, 2, 4001, 64, 128, 1, 0, True, 0.0, 0),      # whole columns
     ("bf16", 1, 3, 3001, 64, 100, 1, 0, True, 0.0, 1),      # heads share the quota
-    ("bf16", 1, 1, 2041, 64, 64, 2, 0, False, 0.0, 0),      # 64 keys of 2041: rows; 96: tiles
-    ("bf16", 1, 1, 2041, 64, 64, 3, 0, False, 0.0, 0),
+    ("bf16", 1, 1, 2041, 64, 64, 16, 0, False, 0.0, 0),     # 512 keys of 2041: rows; 544: tiles
+    ("bf16", 1, 1, 2041, 64, 64, 17, 0, False, 0.0, 0),
+    ("bf16", 1, 2, 100, 64, 100, 1, 0, False, 0.3, 1),      # K = T, heads share the quota
     ("f32", 2, 2, 333, 64, 64, 2, 0, True, 0.3, 0),
     ("f32", 1, 1, 130, 32, 128, 1, 0, False, 0.0, 0),       # one or two keys
     ("f32", 1, 2, 1300, 64, 13, 1, 50, False, 0.0, 0),
     ("f32", 1, 1, 5003, 64, 1000, 20, 20, False, 0.3, 0),   # one of five or six
     ("f32", 1, 3, 700, 64, 60, 2, 0, True, 0.0, 1),
-    ("f32", 1, 2, 1000, 64, 62, 8, 0, False, 0.0, 0),       # 136 keys of 1000: rows; 153: tiles
-    ("f32", 1, 2, 1000, 64, 62, 9, 0, False, 0.0, 0),
+    ("f32", 1, 2, 1000, 64, 62, 18, 0, False, 0.0, 0),      # 306 keys of 1000: rows; 323: tiles
+    ("f32", 1, 2, 1000, 64, 62, 19, 0, False, 0.0, 0),
 ]
 
 

@@ -13,19 +13,25 @@ pytestmark = pytest.mark.gpu
 
 # (dtype, B, H, T, m, K, k^, budget, causal, pad)
 COLUMNS = [
-    ("bf16", 1, 2, 601, 64, 100, 20, 0, True, 0.0),     # columns of any width: 8 slots, six sets of waves
-    ("bf16", 1, 2, 385, 64, 128, 17, 0, False, 0.0),    # 16 slots
-    ("bf16", 2, 1, 129, 64, 128, 31, 0, True, 0.3),     # 32 slots
-    ("bf16", 1, 26, 601, 64, 100, 30, 0, False, 0.0),   # three sets
+    ("bf16", 1, 2, 601, 64, 100, 20, 0, True, 0.0),     # columns of any width, small launches: row by row
+    ("bf16", 1, 2, 385, 64, 128, 17, 0, False, 0.0),
+    ("bf16", 2, 1, 129, 64, 128, 31, 0, True, 0.3),
+    ("bf16", 1, 26, 601, 64, 100, 30, 0, False, 0.0),   # tiles: three sets of waves,
     ("bf16", 5, 9, 700, 64, 100, 20, 0, False, 0.3),    # one
     ("bf16", 1, 1, 1300, 64, 13, 5, 100, True, 0.0),    # 20 of 100 keys a column
     ("bf16", 1, 4, 4001, 64, 128, 2, 0, True, 0.3),     # few keys per row: row by row
+    ("bf16", 1, 12, 601, 64, 100, 60, 0, True, 0.0),    # many: tiles, six sets of waves, 8 slots,
+    ("bf16", 1, 4, 385, 64, 128, 90, 0, False, 0.0),    # 16 slots,
+    ("bf16", 2, 2, 129, 64, 128, 100, 0, True, 0.3),    # and 32
+    ("bf16", 1, 2, 1300, 64, 13, 12, 240, True, 0.0),   # 20 of 100 keys a column
 ]
 F32 = [
     ("f32", 1, 2, 385, 64, 128, 33, 0, True, 0.0),      # columns of any width
     ("f32", 2, 1, 290, 96, 64, 20, 0, False, 0.3),
     ("f32", 1, 1, 1300, 64, 13, 5, 500, True, 0.0),     # 100 of 100 keys a column
     ("f32", 1, 2, 700, 64, 60, 2, 0, False, 0.3),       # few keys per row
+    ("f32", 1, 2, 385, 64, 128, 90, 0, True, 0.0),      # many: tiles
+    ("f32", 2, 1, 290, 96, 64, 50, 0, False, 0.3),
 ]
 
 
