@@ -50,16 +50,21 @@ __device__ __forceinline__ double exp_f64(double x) {
 // four consecutive elements of an fp32 tensor
 __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 
-// phi for 16 rows per block, a quarter of the features per wave (so that 12 heads of 1024 rows are 6144
-// waves and not 1536: with less than two waves per SIMD the products of 16 dependent steps and the
-// exponentials ran one after the other; 23 -> 20 us there).  Queries are shifted by their row maximum, which
-// meets in LDS (any shift cancels in the normaliser); keys are not shifted and are zero beyond seq_len.
+// phi for 16 rows per WPT waves, each of which takes its share of the features.  WPT = 4 in small launches (12
+// heads of 1024 rows are then 6144 waves and not 1536: with less than two waves per SIMD the products of 16
+// dependent steps and the exponentials ran one after the other; 23 -> 20 us at m = 128) and where a wave would
+// hold more than 8 feature tiles (m = 256, 12 heads of 2048 rows 61 -> 52 us).  From 3072 row tiles on, queries and
+// keys, one wave per tile is the faster form, which loads its rows once (12 heads of 2048 rows 33 -> 31 us at
+// m = 128, 23 -> 20 us at m = 64) and leaves the features where the kernels that follow read them (per-row widths,
+// m = 64, 24 heads of 2048 rows: tiles 278 -> 254 us).
+// Queries are shifted by their row maximum (WPT = 4: it meets in LDS; any shift cancels in the normaliser);
+// keys are not shifted and are zero beyond seq_len.
 // D[row = token 4 i + lg][col = feature lr]; contraction slot (step s, lane group lg) stands for
 // dimension 16 lg + s.
 // NFT > 0: the exponent arguments of the wave's (at most NFT) feature tiles stay in registers between the
 // projection and the exponential, and the unrolled tile loop lets the loads of W run ahead;
 // NFT = 0: any m, the arguments take a round trip through the output buffer.
-template <int NFT>
+template <int NFT, int WPT>
 __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float* __restrict__ Q,
                                                            const float* __restrict__ K, const float* __restrict__ W,
                                                            double* __restrict__ phiQ, double* __restrict__ phiK) {
@@ -67,9 +72,12 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
   const uint32_t tiles = (s.T + 15) / 16;
-  const int64_t nw = static_cast<int64_t>(s.N) * tiles;  // row tiles; blocks: queries, then keys
-  const int which = blockIdx.x >= nw;
-  const int64_t wv = which ? blockIdx.x - nw : blockIdx.x;
+  const int64_t nw = static_cast<int64_t>(s.N) * tiles;  // row tiles of the queries, then of the keys
+  const int64_t tile = WPT == 4 ? blockIdx.x : static_cast<int64_t>(blockIdx.x) * 4 + wid;
+  if (WPT == 1 && tile >= 2 * nw) return;
+  const int part = WPT == 4 ? wid : 0;  // this wave's share of the features
+  const int which = tile >= nw;
+  const int64_t wv = which ? tile - nw : tile;
   const int64_t head = wv / tiles;
   const int32_t r0 = static_cast<int32_t>(wv % tiles) * 16;
   const int32_t b = static_cast<int32_t>(head / s.H);
@@ -93,7 +101,7 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
   for (int i = 0; i < 4; ++i) half_n[i] = 0.5 * __shfl(nx, 4 * i + lg, kWave);
   double* out = (which ? phiK : phiQ) + (head * s.T) * s.m;
   double amax[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  const int ntiles = s.m / 16;  // wave w takes tiles w, w + 4, ...
+  const int ntiles = s.m / 16;  // share p: tiles p, p + WPT, ...
   auto project = [&](int ft) {
     const float* w = W + static_cast<int64_t>(ft * 16 + lr) * kHeadDim + 16 * lg;
     float4 wv4[4];
@@ -121,8 +129,10 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
       double mx = amax[i];
 #pragma unroll
       for (int mask = 1; mask < 16; mask <<= 1) mx = fmax(mx, __shfl_xor(mx, mask, kWave));
-      if (lr == 0) rowmax[wid][4 * i + lg] = mx;
+      shift[i] = mx;
+      if (WPT == 4 && lr == 0) rowmax[wid][4 * i + lg] = mx;
     }
+    if (WPT == 1) return;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -134,8 +144,8 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
     double arg[NFT][4];
 #pragma unroll
     for (int f = 0; f < NFT; ++f) {
-      if (4 * f + wid < ntiles) {
-        const doublex4 acc = project(4 * f + wid);
+      if (WPT * f + part < ntiles) {
+        const doublex4 acc = project(WPT * f + part);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           arg[f][i] = acc[i] - half_n[i];
@@ -146,16 +156,16 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
     row_shift();
 #pragma unroll
     for (int f = 0; f < NFT; ++f) {
-      if (4 * f + wid < ntiles) {
+      if (WPT * f + part < ntiles) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int32_t t = r0 + 4 * i + lg;
-          if (t < s.T) out[static_cast<int64_t>(t) * s.m + (4 * f + wid) * 16 + lr] = t < len ? exp_f64(arg[f][i] - shift[i]) : 0.0;
+          if (t < s.T) out[static_cast<int64_t>(t) * s.m + (WPT * f + part) * 16 + lr] = t < len ? exp_f64(arg[f][i] - shift[i]) : 0.0;
         }
       }
     }
   } else {
-    for (int ft = wid; ft < ntiles; ft += 4) {
+    for (int ft = part; ft < ntiles; ft += WPT) {
       const doublex4 acc = project(ft);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -167,7 +177,7 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
     }
     row_shift();
     // second pass over the lane's own values
-    for (int ft = wid; ft < ntiles; ft += 4) {
+    for (int ft = part; ft < ntiles; ft += WPT) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int32_t t = r0 + 4 * i + lg;
@@ -387,14 +397,16 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
 
 void launch_features(const Shape& s, const float* Q, const float* K, const float* W, double* phiQ, double* phiK,
                      hipStream_t st) {
-  const int64_t blocks = 2 * static_cast<int64_t>(s.N) * ((s.T + 15) / 16);
-  const dim3 grid(static_cast<uint32_t>(blocks));
-  if (s.m <= 128)
-    hipLaunchKernelGGL(features_f64_kernel<2>, grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+  const int64_t tiles = 2 * static_cast<int64_t>(s.N) * ((s.T + 15) / 16);
+  const dim3 split(static_cast<uint32_t>(tiles)), whole(static_cast<uint32_t>((tiles + 3) / 4));
+  if (s.m <= 128 && tiles >= 3072)
+    hipLaunchKernelGGL((features_f64_kernel<8, 1>), whole, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+  else if (s.m <= 128)
+    hipLaunchKernelGGL((features_f64_kernel<2, 4>), split, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
   else if (s.m <= 256)
-    hipLaunchKernelGGL(features_f64_kernel<4>, grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+    hipLaunchKernelGGL((features_f64_kernel<4, 4>), split, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
   else
-    hipLaunchKernelGGL(features_f64_kernel<0>, grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+    hipLaunchKernelGGL((features_f64_kernel<0, 4>), split, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
 }
 
 }  // namespace

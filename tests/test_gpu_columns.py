@@ -159,3 +159,18 @@ def test_few_keys_per_row(case):
     assert torch.equal(O2, out["O"])
     if kb:  # a fixed number of keys per column: the rows' keys in the order of the lists, so the same sums
         assert torch.equal(out["O"], lists)
+
+
+@pytest.mark.parametrize("m,T,K", [(64, 1000, 60), (96, 1025, 33), (128, 1000, 125)])
+def test_f32_features_of_many_rows(m, T, K):
+    """fp32 scores where one wave takes the features of 16 rows (3072 row tiles, queries and keys, and more)."""
+    from paper_2310_01777_amd import binding as sea
+    wl = synth.Workload("features", 2, 13, T, 64, m, K, 4, 0, True, "f32", 4, 0.3)
+    x = synth.make_inputs(wl)
+    p = sea.SeaParams(B=2, H=13, T=T, d=64, m=m, K=K, k_hat=4, causal=True, scale=wl.scale, dtype="f32",
+                      seq_len=x["seq_len"].cuda())
+    A = torch.full((2, 13, T, K), float("nan"), device="cuda")
+    print(f"[case] f32 features {(m, T, K)}", flush=True)
+    sea.sea_estimate(p, x["Q"].cuda(), x["K"].cuda(), x["W"].cuda(), A, sea.alloc_workspace(p))
+    want = oracle.estimate(oracle_params(wl), to_np64(x["Q"]), to_np64(x["K"]), to_np64(x["W"]), seq_len=x["seq_len"].numpy())
+    assert_close(to_np64(A), want, TOL["f32"], "A_hat")
