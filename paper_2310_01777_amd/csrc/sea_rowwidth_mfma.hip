@@ -519,8 +519,7 @@ hipError_t launch(const Shape& s, const uint16_t* Q, const uint16_t* K, const ui
   const bool wide = static_cast<int64_t>(s.K) * s.T > (int64_t{1} << 21);
   constexpr int U = row_tiles(32 * MC);
   if (kb)  // K T <= 2^21 there
-    return s.K <= 128 ? launch_tiles<2 * MC, false, 8, U>(s, phiQ, phiK, A_hat, mbits, kb, st)
-                      : launch_tiles<2 * MC, false, 16, U>(s, phiQ, phiK, A_hat, mbits, kb, st);
+    return launch_tiles<2 * MC, false, 8, U>(s, phiQ, phiK, A_hat, mbits, kb, st);
   return wide ? launch_tiles<2 * MC, true, 0, 2>(s, phiQ, phiK, A_hat, nullptr, nullptr, st)
               : launch_tiles<2 * MC, false, 0, U>(s, phiQ, phiK, A_hat, nullptr, nullptr, st);
 }
@@ -533,10 +532,16 @@ bool rowwidth_mfma_supported(const Shape& s, sea_dtype dt) {
 
 size_t rowwidth_mfma_workspace(const Shape& s) { return 2 * side_bytes(s); }
 
-// the selection as key bits straight from the estimate: at most eight column parts, a wave for every 16 rows of a
-// block, and room for those rows' key bits in the place of the bins
+// The selection as key bits straight from the estimate: a wave for every 16 rows of a block, and room for those
+// rows' key bits in the place of the bins.  Up to 128 columns: there a row's search is shorter than the way of its
+// scores through memory.  Above, it is not: half of a block's waves stand by meanwhile, and a kernel of its own
+// searches with all of them (whole forward, us, in the estimate / on its own: 12 heads, T = 1500, m = 128, K = 256, B = 2
+// 114 / 92; 32 heads, m = K = 256, T = 2048, B = 1 229 / 209, B = 8 1718 / 1585, T = 260, B = 8 204 / 167; K = 128,
+// T = 2048, 48 heads, m = 128 173 / 197, 24 heads, m = 256 134 / 144).  And only from one 64-row block per CU on:
+// smaller launches leave the search the whole chip (12 heads of 500 rows, K = 128, 35 / 30; 48 heads 47 / 50).
 bool rowwidth_select_supported(const Shape& s, sea_dtype dt) {
-  if (!rowwidth_mfma_supported(s, dt) || s.grouping != 0 || s.K > 256 || s.T > 8192) return false;
+  if (!rowwidth_mfma_supported(s, dt) || s.grouping != 0 || s.K > 128 || s.T > 8192) return false;
+  if (static_cast<int64_t>(s.N) * ((s.T + 63) / 64) < 256) return false;
   const int32_t U = row_tiles(s.m);
   const Plan p = plan(s, 32 * U);
   const size_t room = static_cast<size_t>(p.waves / (2 * U)) * 32 * U * p.stride * sizeof(double);

@@ -23,6 +23,17 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1025, 256, 200, 1, 0, 0.3),     # seven parts, one column
     (1, 1, 2049, 64, 64, 20, 0, 0.0),      # two parts share two waves' room
     (1, 1, 4100, 128, 128, 20, 0, 0.0),    # rows of 129 words
+    # a 64-row block per CU: where the estimate selects
+    (4, 64, 40, 64, 40, 3, 0, 0.0),
+    (4, 32, 65, 64, 33, 9, 0, 0.3),
+    (2, 43, 129, 128, 128, 40, 0, 0.0),
+    (4, 8, 500, 128, 100, 30, 60, 0.0),
+    (2, 12, 700, 64, 125, 30, 250, 0.5),   # eight keys of up to six: every key
+    (3, 18, 300, 256, 128, 128, 0, 0.0),
+    (1, 16, 1025, 256, 128, 1, 0, 0.3),
+    (1, 8, 2049, 64, 64, 20, 0, 0.0),
+    (1, 4, 4100, 128, 128, 20, 0, 0.0),
+    (3, 28, 130, 64, 129, 40, 0, 0.0),     # K above 128: not there
 ], ids=lambda c: "_".join(str(x) for x in c))
 def test_selection_in_the_estimate(case):
     from paper_2310_01777_amd import binding as sea
