@@ -54,8 +54,8 @@ __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_ca
 // heads of 1024 rows are then 6144 waves and not 1536: with less than two waves per SIMD the products of 16
 // dependent steps and the exponentials ran one after the other; 23 -> 20 us at m = 128) and where a wave would
 // hold more than 8 feature tiles (m = 256, 12 heads of 2048 rows 61 -> 52 us).  From 3072 row tiles on, queries and
-// keys, one wave per tile is the faster form, which loads its rows once (12 heads of 2048 rows 33 -> 31 us at
-// m = 128, 23 -> 20 us at m = 64) and leaves the features where the kernels that follow read them (per-row widths,
+// keys (m = 64: 2048), one wave per tile is the faster form, which loads its rows once (12 heads of 2048 rows
+// 33 -> 31 us at m = 128, 23 -> 20 us at m = 64, 16 heads of 1024 rows 20 -> 17 us there) and leaves the features where the kernels that follow read them (per-row widths,
 // m = 64, 24 heads of 2048 rows: tiles 278 -> 254 us).
 // Queries are shifted by their row maximum (WPT = 4: it meets in LDS; any shift cancels in the normaliser);
 // keys are not shifted and are zero beyond seq_len.
@@ -399,7 +399,7 @@ void launch_features(const Shape& s, const float* Q, const float* K, const float
                      hipStream_t st) {
   const int64_t tiles = 2 * static_cast<int64_t>(s.N) * ((s.T + 15) / 16);
   const dim3 split(static_cast<uint32_t>(tiles)), whole(static_cast<uint32_t>((tiles + 3) / 4));
-  if (s.m <= 128 && tiles >= 3072)
+  if (s.m <= 128 && tiles >= (s.m <= 64 ? 2048 : 3072))
     hipLaunchKernelGGL((features_f64_kernel<8, 1>), whole, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
   else if (s.m <= 128)
     hipLaunchKernelGGL((features_f64_kernel<2, 4>), split, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);

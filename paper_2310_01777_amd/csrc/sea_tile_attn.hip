@@ -700,12 +700,16 @@ static bool wide_blocks(const Shape& s) {
 // (192) 60 / 50 / 46 / 40, B = 3 (576) 67 / 60 / 72 / 64, B = 4 (768) 73 / 73 / 84 / 77; T = 4096, B = 1 (384)
 // 100 / 79 / 69 / 72; per-key bits, T = 2048, B = 1 125 / 102 / 99 / 88, B = 2 153 / 131 / 127 / 122, B = 4
 // 220 / 214 / 228 / 219; bidirectional, T = 1024, B = 4 52 / 49 / 55 / 48, T = 512, B = 8 42 / 43 / 50 / 42.
+// Where the lines of kTwo lie (kOne / kTwo): two of its blocks are resident per CU, 512, which is the line when all
+// blocks are equally long (bidirectional, T = 1536, H = 24, B = 2 (576) 76.7 / 79.4); per-key bits gain up to three
+// 128-row blocks per CU (the attention alone, H = 32, T = 3000 (768) 110 / 87, H = 16, T = 6000 (752) 187 / 147, H = 12,
+// T = 8000 (756) 290 / 220) and lose above (H = 32, T = 3500 (896) 138 / 151).
 enum WaveSplit { kOne, kTwo, kFour, kPairs };
 static WaveSplit wave_split(const Shape& s, int32_t U, bool key_bits) {
   const int64_t blocks = static_cast<int64_t>(s.N) * ((s.T + 127) / 128);
   if (U >= 256 && blocks <= (key_bits ? 384 : 256)) return kPairs;
   if (U >= 4096 && blocks <= 512 && s.causal) return kFour;
-  if (U >= 1024 && blocks <= (key_bits && U >= 2048 ? 1024 : 576)) return kTwo;
+  if (U >= 1024 && blocks <= (key_bits && U >= 2048 ? 768 : (s.causal ? 576 : 512))) return kTwo;
   return kOne;
 }
 
