@@ -77,7 +77,8 @@ bool column_gather_pays(const Shape& s, sea_dtype dt) {
   const double r = g.r == 0 ? g.cg.w0 + (g.cg.rm > 0 ? 1 : 0) : g.r;
   const double n = s.k_hat * r, U = g.U, walked = s.causal ? U / 2 : U, krows = rows * 1e-3;
   const bool bf16 = dt == SEA_BF16;
-  const double one_row = (bf16 ? 0.05 : 0.06) * n, all_rows = krows * std::max(0.72, 0.45 + (bf16 ? 0.010 : 0.027) * n);
+  // (heads that share a quota: a row may select up to sel_stride columns)
+  const double one_row = (bf16 ? 0.05 : 0.06) * s.sel_stride * r, all_rows = krows * std::max(0.72, 0.45 + (bf16 ? 0.010 : 0.027) * n);
   const double one_list = bf16 ? 3.5 + 0.0115 * U : 2.0 + 0.0165 * U;
   const double all_lists = krows * (bf16 ? 0.65e-3 * walked : 0.35 + 4.3e-3 * walked);
   return std::max(one_row, all_rows) <= std::max(one_list, all_lists);

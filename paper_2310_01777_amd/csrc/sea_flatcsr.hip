@@ -124,7 +124,9 @@ __global__ __launch_bounds__(256) void flat_copy_kernel(Shape s, const int32_t* 
 // Lists of at most 4 G entries: one wave per CSR row, G lanes per head, a 16-byte piece each, so that 64 / G heads
 // move at a time and a row costs no barrier.  All three launches in us, a wave per CSR row with 4-byte pieces / a
 // block per CSR row / this: B = 4, H = 12, T = 2048, 16 entries 16 / 25 / 13, 64 entries 21 / 29 / 18, 128 entries 29 /
-// 29 / 25; H = 8, T = 8192, 64 entries 17 / 24 / 14; H = 32, T = 2048, 128 entries 46 / 27 / 27.
+// 29 / 25; H = 8, T = 8192, 64 entries 17 / 24 / 14; H = 32, T = 2048, 128 entries 46 / 27 / 27.  Above 64 entries only
+// with 4096 rows and more, since a wave per row leaves the chip idle otherwise (B = 2, H = 32, T = 1000, up to 128
+// entries 47 / 28 / 35).
 template <int G>
 __global__ __launch_bounds__(256) void flat_copy_short_kernel(Shape s, const int32_t* __restrict__ idx,
                                                               const int32_t* __restrict__ cnt, int32_t L, int64_t R,
@@ -183,7 +185,7 @@ hipError_t launch_flatcsr(const Shape& s, const int32_t* idx, const int32_t* cnt
   hipLaunchKernelGGL(flat_scan_kernel, dim3(1), dim3(1024), 0, st, bsum, nblk, crow + R);
   const dim3 rows4(static_cast<uint32_t>((R + 3) / 4));
   if (L <= 64) hipLaunchKernelGGL(flat_copy_short_kernel<16>, rows4, dim3(256), 0, st, s, idx, cnt, L, R, crow, bsum, col, cap);
-  else if (L <= 128) hipLaunchKernelGGL(flat_copy_short_kernel<32>, rows4, dim3(256), 0, st, s, idx, cnt, L, R, crow, bsum, col, cap);
+  else if (L <= 128 && R >= 4096) hipLaunchKernelGGL(flat_copy_short_kernel<32>, rows4, dim3(256), 0, st, s, idx, cnt, L, R, crow, bsum, col, cap);
   else hipLaunchKernelGGL(flat_copy_kernel, dim3(static_cast<uint32_t>(R)), dim3(256), 0, st, s, idx, cnt, L, crow, bsum, col, cap);
   return hipGetLastError();
 }
