@@ -38,8 +38,8 @@ size_t dec_linattn_state_bytes(const Shape& s);
 hipError_t launch_dec_linattn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V, const uint16_t* W,
                               uint16_t* Cp, void* state, float c_dot, float c_norm, hipStream_t st);
 // mu, nu and the scalers on rows [C_perf; V]: the CNN's input image [B][T][K / 2][4 H], s_mix, s_prob [B][H][T]
-hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const uint16_t* Cp, int32_t cp_stride,
-                          const uint16_t* V, int32_t v_stride, uint16_t* img, float* s_mix, float* s_prob, hipStream_t st);
+hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const uint16_t* Cp, const uint16_t* V,
+                          uint16_t* img, float* s_mix, float* s_prob, hipStream_t st);
 
 // a 3x3 layer on a channels-last image [B][Tin][X][Cin], weights [Cout][3][3][Cin]; the columns keep their
 // number, rows i stride_t - pad_top .. + 2 make output row i, zeros outside

@@ -27,9 +27,8 @@ constexpr int kCh = 4;       // channel expansion (c_h)
 
 // ------------------------------------------------------------------------------------------
 // implicit GEMM: out[pixel][cout] = act(bias[cout] + sum over (tap, c) in[pixel + tap][c] w[cout][tap][c]).
-// One tap: a linear layer on rows.  Nine taps: a 3x3 convolution on a channels-last image
-// [B][Tin][Xin][Cin], read through an optional nearest resize to Tv x Xv (source index
-// floor(v * size / vsize)); zero outside the (virtual) image.  Computed transposed,
+// A 3x3 convolution on a channels-last image [B][Tin][Xin][Cin], read through an optional nearest
+// resize to Tv x Xv (source index floor(v * size / vsize)); zero outside the (virtual) image.  Computed transposed,
 // C[cout][pixel] = W x X^T: the lane is the pixel, a lane holds four consecutive output channels.
 // Wide layers (dec_conv_lds_kernel): block = 4 waves, wave = 64 pixels x up to 128 output channels
 // (blockIdx.y picks the channel slab); the weights of the block's channels go through LDS in slabs of
@@ -38,10 +37,10 @@ constexpr int kCh = 4;       // channel expansion (c_h)
 // ------------------------------------------------------------------------------------------
 struct ConvArgs {
   const uint16_t* in;
-  const uint16_t* w;     // [Cout][taps * Cin]
+  const uint16_t* w;     // [Cout][3][3][Cin]
   const float* bias;     // [Cout]
   void* out;
-  int32_t B, Tin, Xin, Cin, Tv, Xv, Tout, Xout, Cout, taps, stride_t, pad_top, relu;
+  int32_t B, Tin, Xin, Cin, Tv, Xv, Tout, Xout, Cout, stride_t, pad_top, relu;
   int32_t mode;          // 0: bf16 channels-last; 2: fp32 planes
 };
 
@@ -57,7 +56,7 @@ __global__ __launch_bounds__(256, 2) void dec_conv_lds_kernel(ConvArgs a) {
   const int64_t pix0 = (static_cast<int64_t>(blockIdx.x) * 4 + wid) * 64;  // may lie past the end: the wave then only stages
   const int32_t cout0 = blockIdx.y * 128;
   const int32_t ntiles = min(8, (a.Cout - cout0 + 15) / 16);
-  const int32_t ktot = a.taps * a.Cin;
+  const int32_t ktot = 9 * a.Cin;
   const int32_t nslabs = (ktot + kSlabK - 1) / kSlabK;
   // this lane's four pixels (operand columns)
   int32_t pb[4], pt[4], px[4];
@@ -106,12 +105,12 @@ __global__ __launch_bounds__(256, 2) void dec_conv_lds_kernel(ConvArgs a) {
         const int32_t k0 = kbase + 8 * lg;
         const bool kok = k0 < ktot;
         const int32_t tap = kok ? k0 / a.Cin : 0, c0 = kok ? k0 - tap * a.Cin : 0;
-        const int32_t ky = a.taps == 9 ? tap / 3 : 0, kx = a.taps == 9 ? tap - 3 * ky : 0;
+        const int32_t ky = tap / 3, kx = tap - 3 * ky;
         bf16x8 xf[4];
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
           const int32_t tv = pt[mt] * a.stride_t + ky - a.pad_top;
-          const int32_t xv = a.taps == 9 ? px[mt] + kx - 1 : px[mt];
+          const int32_t xv = px[mt] + kx - 1;
           const bool ok = kok && pok[mt] && tv >= 0 && tv < a.Tv && xv >= 0 && xv < a.Xv;
           if (ok) {
             const int32_t ts = a.Tv == a.Tin ? tv : static_cast<int32_t>((static_cast<int64_t>(tv) * a.Tin) / a.Tv);
@@ -181,7 +180,7 @@ __global__ __launch_bounds__(256) void dec_conv_kernel(ConvArgs a) {
   if (pix0 >= npix) return;
   const int32_t cout0 = blockIdx.y * 128;
   const int32_t ntiles = min(8, (a.Cout - cout0 + 15) / 16);
-  const int32_t ktot = a.taps * a.Cin;
+  const int32_t ktot = 9 * a.Cin;
   // this lane's two pixels (operand columns)
   int32_t pb[2], pt[2], px[2];
   bool pok[2];
@@ -201,12 +200,12 @@ __global__ __launch_bounds__(256) void dec_conv_kernel(ConvArgs a) {
   for (int32_t k0 = 8 * lg; k0 - 8 * lg < ktot; k0 += 32) {
     const bool kok = k0 < ktot;
     const int32_t tap = kok ? k0 / a.Cin : 0, c0 = kok ? k0 - tap * a.Cin : 0;
-    const int32_t ky = a.taps == 9 ? tap / 3 : 0, kx = a.taps == 9 ? tap - 3 * ky : 0;
+    const int32_t ky = tap / 3, kx = tap - 3 * ky;
     bf16x8 xf[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       const int32_t tv = pt[mt] * a.stride_t + ky - a.pad_top;
-      const int32_t xv = a.taps == 9 ? px[mt] + kx - 1 : px[mt];
+      const int32_t xv = px[mt] + kx - 1;
       const bool ok = kok && pok[mt] && tv >= 0 && tv < a.Tv && xv >= 0 && xv < a.Xv;
       if (ok) {
         const int32_t ts = a.Tv == a.Tin ? tv : static_cast<int32_t>((static_cast<int64_t>(tv) * a.Tin) / a.Tv);
@@ -459,7 +458,7 @@ int32_t resize_shift(int32_t vsize, int32_t size) {
 // whose halo and weights fit the LDS budget.
 constexpr size_t kConv3LdsBudget = 72 << 10;  // two blocks per CU overlap one block's staging with the other's products
 bool conv3_plan(const ConvArgs& a, Conv3Args* g, int32_t* nt_out, size_t* lds_out) {
-  if (a.taps != 9 || a.Cin % 8 != 0 ) return false;
+  if (a.Cin % 8 != 0) return false;
   if (a.mode == 0 && a.Cout % 4 != 0) return false;
   const int32_t ts = resize_shift(a.Tv, a.Tin), xs = resize_shift(a.Xv, a.Xin);
   if (ts < 0 || xs < 0) return false;
@@ -520,7 +519,7 @@ void launch_conv(const ConvArgs& a, hipStream_t st) {
     return;
   }
   const uint32_t slabs = static_cast<uint32_t>((a.Cout + 127) / 128);
-  if (a.Cout >= 96 && a.taps * a.Cin >= 512) {
+  if (a.Cout >= 96 && 9 * a.Cin >= 512) {
     hipLaunchKernelGGL(dec_conv_lds_kernel, dim3(static_cast<uint32_t>((npix + 255) / 256), slabs), dim3(256), 0, st, a);
   } else {
     hipLaunchKernelGGL(dec_conv_kernel, dim3(static_cast<uint32_t>((npix + 127) / 128), slabs), dim3(256), 0, st, a);
@@ -537,7 +536,7 @@ hipError_t conv_layer(const DecConv& c, uint16_t* out, hipStream_t st) {
   ConvArgs a{};
   a.in = c.in; a.w = c.w; a.bias = c.bias; a.out = out; a.B = c.B; a.Cin = c.Cin; a.Cout = c.Cout;
   a.Tin = a.Tv = c.Tin; a.Tout = c.Tout; a.Xin = a.Xv = a.Xout = c.X;
-  a.taps = 9; a.stride_t = c.stride_t; a.pad_top = c.pad_top; a.relu = 1; a.mode = 0;
+  a.stride_t = c.stride_t; a.pad_top = c.pad_top; a.relu = 1; a.mode = 0;
   launch_conv(a, st);
   return hipGetLastError();
 }
@@ -574,7 +573,7 @@ hipError_t launch_decoder_estimate(const Shape& s, const sea_decoder_weights& wt
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
   // mu, nu and the scalers: rows [C_perf; V] -> the CNN's input image [B][T][Wd][C], channels h c_h + ch
-  e = launch_dec_mlp(s, wt, u16(lay.Cp), 128, V, kHeadDim, u16(lay.img), s_mix, s_prob, st);
+  e = launch_dec_mlp(s, wt, u16(lay.Cp), V, u16(lay.img), s_mix, s_prob, st);
   if (e != hipSuccess) return e;
   // conv 1: [B][T][Wd][C] -> [B][T1][Wd][C], ReLU.  Causal: rows t-2..t; else stride c_s, rows i c_s - 1 .. + 1
   DecConv c{};
@@ -594,7 +593,7 @@ hipError_t launch_decoder_estimate(const Shape& s, const sea_decoder_weights& wt
   ConvArgs a{};
   a.in = c.in; a.w = c.w; a.bias = c.bias; a.out = A_hat; a.B = B; a.Cin = lay.C; a.Cout = s.H;
   a.Tin = lay.T1; a.Xin = lay.Wd; a.Tv = a.Tout = s.T; a.Xv = a.Xout = s.K;
-  a.taps = 9; a.stride_t = 1; a.pad_top = c.pad_top; a.relu = 0; a.mode = 2;
+  a.stride_t = 1; a.pad_top = c.pad_top; a.relu = 0; a.mode = 2;
   launch_conv(a, st);
   hipLaunchKernelGGL(dec_softmax_kernel, dim3(static_cast<uint32_t>((rows + 3) / 4)), dim3(256), 0, st, A_hat, s.seq_len,
                      rows, s.H, s.T, s.K);

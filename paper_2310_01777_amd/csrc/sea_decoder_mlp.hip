@@ -16,15 +16,15 @@
 namespace sea {
 namespace {
 
+constexpr int kCpDim = 128;   // [V_I; V] through the Performer: two value widths
 constexpr int kMlpWaves = 8, kMlpThreads = 64 * kMlpWaves;
 constexpr int kMuSteps = 6, kHidSteps = 4;     // contraction steps of 32: 192 and 128 channels
 constexpr int kNu1Tiles = 9;                   // 128 outputs + one tile for the scalers
 constexpr int kSlabTiles = 16;                 // 256 outputs of nu's last layer per slab
 
 struct MlpArgs {
-  const uint16_t* Cp;   // C_perf rows, `cp_stride` apart
-  const uint16_t* V;    // value rows, `v_stride` apart
-  int32_t cp_stride, v_stride;
+  const uint16_t* Cp;   // C_perf rows, kCpDim wide
+  const uint16_t* V;    // value rows, kHeadDim wide
   const uint16_t *mu_w, *nu1_w, *nu2_w, *mix_w, *prob_w;
   const float *mu_b, *nu1_b, *nu2_b, *mix_b, *prob_b;
   uint16_t* img;        // [B][T][Wd][C]
@@ -101,9 +101,9 @@ __global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
       split(min(tile * 32 + 16 * mt + lr, a.rows - 1), &h, &t, &b);
       const int64_t r = (static_cast<int64_t>(b) * a.H + h) * a.T + t;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) nx[ks][mt] = load8(a.Cp + r * a.cp_stride + 32 * ks + 8 * lg);
+      for (int ks = 0; ks < 4; ++ks) nx[ks][mt] = load8(a.Cp + r * kCpDim + 32 * ks + 8 * lg);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) nx[4 + ks][mt] = load8(a.V + r * a.v_stride + 32 * ks + 8 * lg);
+      for (int ks = 0; ks < 2; ++ks) nx[4 + ks][mt] = load8(a.V + r * kHeadDim + 32 * ks + 8 * lg);
     }
   };
   const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * kMlpWaves + wid;
@@ -218,11 +218,11 @@ __global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
 
 }  // namespace
 
-hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const uint16_t* Cp, int32_t cp_stride,
-                          const uint16_t* V, int32_t v_stride, uint16_t* img, float* s_mix, float* s_prob, hipStream_t st) {
+hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const uint16_t* Cp, const uint16_t* V,
+                          uint16_t* img, float* s_mix, float* s_prob, hipStream_t st) {
   MlpArgs a{};
   auto u16 = [](const void* p) { return static_cast<const uint16_t*>(p); };
-  a.Cp = Cp; a.cp_stride = cp_stride; a.V = V; a.v_stride = v_stride;
+  a.Cp = Cp; a.V = V;
   a.mu_w = u16(wt.mu_w); a.nu1_w = u16(wt.nu1_w); a.nu2_w = u16(wt.nu2_w); a.mix_w = u16(wt.mix_w); a.prob_w = u16(wt.prob_w);
   a.mu_b = wt.mu_b; a.nu1_b = wt.nu1_b; a.nu2_b = wt.nu2_b; a.mix_b = wt.mix_b; a.prob_b = wt.prob_b;
   a.img = img; a.s_mix = s_mix; a.s_prob = s_prob; a.seq_len = s.seq_len;
