@@ -267,11 +267,16 @@ def measure(torch, sea, synth, wl, steps, warmup, detail):
                              "note": "achieved counts the selected (query, key) pairs only; the upper bound of the issued "
                                      "flops counts every 32 x 32 tile at or below the diagonal (padding ignored)"}
     elif sparse_ms > 0:
-        # per-row list kernel: the bytes that must cross HBM once are Q, K, V, O and the lists; the
-        # repeated K / V row gathers of the pairs are served by the caches
-        once_bytes = 4 * nrows * wl.d * es + pairs * 4 + nrows * 4
+        # fixed buckets of other widths read the selected-column bits, longer per-row width layers index
+        # lists; the bytes that must cross HBM once are Q, K, V, O and the bits or lists, the repeated
+        # K / V rows of the pairs are served by the caches
+        fixed = wl.geometry == 0
+        once_bytes = 4 * nrows * wl.d * es + (nrows * ((wl.K + 31) // 32) * 4 if fixed else pairs * 4 + nrows * 4)
         ach = once_bytes / (sparse_ms * 1e-3) / 1e9
-        kernels["sparse"] = {"kernel": "sparse_attn_kernel", "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS,
+        name = (("column_attn_kernel" if wl.dtype == "bf16" else "tile_attn_f32_kernel, columns of any width")
+                + " or column_gather_kernel" if fixed else
+                "list_tile_kernel with list_rest_kernel" if wl.dtype == "bf16" else "sparse_attn_kernel")
+        kernels["sparse"] = {"kernel": name, "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS,
                              "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "avg_kernel_ms": sparse_ms,
                              "algorithmic_bytes": once_bytes, "pairs": pairs}
     # estimator: dense flop counts of the contractions (2 T d m per projection, 2 T m K)
@@ -291,7 +296,7 @@ def measure(torch, sea, synth, wl, steps, warmup, detail):
         # causal-per-batch selection: every time step's H x K slab of fp32 scores is read once, mask bits written
         gms = avg["topk_mask"]
         gbytes = float(nrows) * wl.K * 4 + float(nrows) * ((wl.K + 31) // 32) * 4
-        kernels["topk_mask"] = {"kernel": "topk_group_kernel", "bound": "hbm", "achieved": gbytes / (gms * 1e-3) / 1e9,
+        kernels["topk_mask"] = {"kernel": "topk_group_bits_kernel", "bound": "hbm", "achieved": gbytes / (gms * 1e-3) / 1e9,
                                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbytes / (gms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                                 "avg_kernel_ms": gms, "algorithmic_bytes": gbytes,
                                 "note": "reads A_hat (fp32) once and writes the mask bits"}

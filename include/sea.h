@@ -344,9 +344,11 @@ int sea_last_hip_error(void);
  * number of keys per selected column, fixed key buckets), 2 = its fp32 counterpart (same shapes,
  * fp32 tensors: logits on the fp64 matrix cores, weights and P V in fp32; sea_forward only),
  * 3 = the same tiled kernel on a per-(row, key) bit mask expanded from the selection (per-row width
- * geometry, T <= 8192 for bf16 and T <= 4096 for fp32 tensors; sea_forward only), 0 = none of these:
- * fixed buckets of other widths run on a tiled kernel of their own on bf16 tensors, everything else
- * on the per-row index-list kernel.
+ * geometry, T <= 8192 for bf16 and T <= 4096 for fp32 tensors; sea_forward only), 0 = none of these.
+ * Fixed buckets of other widths (K does not divide T, or a column emits a number of keys that is not a
+ * power of two) then run from the selected-column bits as well, on bf16 and fp32 tensors: on tiled
+ * kernels of their own or, where rows select few keys, one wave per row.  Longer per-row width layers
+ * run on index lists: on bf16 tensors in tiles where neighbouring rows share keys, else one wave per row.
  * Negative: the sea_status the parameters would be rejected with.  Pure host computation.
  */
 int sea_attention_path(const sea_params* p);

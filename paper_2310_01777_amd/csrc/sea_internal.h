@@ -93,7 +93,7 @@ hipError_t launch_column_gather(const Shape& s, sea_dtype dt, const void* Q, con
                                 const uint32_t* mbits, void* O, hipStream_t st);
 // fp32 tensors: tiled attention on the fp64 / fp32 matrix cores from per-row column bits
 bool tile_attn_f32_supported(const Shape& s);
-bool tile_attn_f32_structured(const Shape& s);  // K | T and a power-of-two number of keys per column
+bool tile_attn_f32_structured(const Shape& s);  // of these, K | T and a power-of-two number of keys per column
 hipError_t launch_tile_attn_f32(const Shape& s, const float* Q, const float* K, const float* V,
                                 const uint32_t* mbits, float* O, hipStream_t st);
 hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
