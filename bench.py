@@ -29,8 +29,8 @@ SWEEP = ("c1", "c2", "c3", "c4_T4096", "c4_T8192", "c4_T16384", "c5")
 # HBM bytes per launch (fetched, written) from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
 # script, scaled by the copy-kernel factors; they cannot be read inside this process, so they are
 # quoted from the committed summary and only for the workload and kernel that summary covers.
-TRAFFIC_FROM_PROFILES = {("c4_T32768", "sparse"): (190.8e6, 134.2e6), ("c4_T32768", "contract"): (361.7e6, 33.6e6),
-                         ("c4_T32768", "state"): (135.1e6, 92.3e6)}
+TRAFFIC_FROM_PROFILES = {("c4_T32768", "sparse"): (190.0e6, 134.2e6), ("c4_T32768", "contract"): (361.7e6, 33.6e6),
+                         ("c4_T32768", "state"): (135.0e6, 92.3e6)}
 TRAFFIC_SOURCE = "profiles/sea_forward_c4_T32768.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, not measured in this run)"
 
 
@@ -283,7 +283,8 @@ def measure(torch, sea, synth, wl, steps, warmup, detail):
     proj = 2.0 * wl.T * wl.d * wl.m * N
     contr = 2.0 * wl.T * wl.m * wl.K * N
     if fused:
-        for name, kern, fl in (("state", "key_state_kernel", proj), ("contract", "estimate_rows_kernel", proj + contr)):
+        rows_kernel = "estimate_rows_kernel" if wl.causal or wl.k_hat > 1 else "estimate_rows_kernel or estimate_rows_bidir_kernel"
+        for name, kern, fl in (("state", "key_state_kernel", proj), ("contract", rows_kernel, proj + contr)):
             ms = avg.get(name, 0.0)
             if ms > 0:
                 ach = fl / (ms * 1e-3) / 1e12
@@ -417,7 +418,7 @@ def decoder_leg(torch, sea, synth, name, steps):
             "mlp_cnn_tflops": (conv_flops + mlp_flops) / (cms * 1e-3) / 1e12 if cms > 0 else None,
             "mlp_cnn_frac_of_bf16_mfma_peak": (conv_flops + mlp_flops) / (cms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS if cms > 0 else None,
             "performer_flops": lin_flops, "weights": "random (Gaussian, fan-in scaled), seed 7",
-            "note": "stages: features = phi(Q), phi(K); state = linear attention on [V_I; V]; contract = mu, nu, "
+            "note": "stages: state = features and linear attention on [V_I; V]; contract = mu, nu, "
                     "CNN, softmax; topk_mask + sparse = selection and sparse attention"}
 
 

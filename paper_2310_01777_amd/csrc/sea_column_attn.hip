@@ -25,13 +25,13 @@
 // The softmax weights go into the second product as the sum of three bf16 values (sea_tile.h), i.e. as the
 // fp32 numbers they are: products of weights and values are exact, as in the per-row kernel.
 //
-// Bound: vector issue, as in the power-of-two kernel (about 200 vector instructions and 17 matrix
-// products per 32-key sub-chunk and wave; three waves per SIMD: held to four the compiler spills
-// registers and the kernel is slower).  Measured on the layer B = 8, H = 32, T = 2000 (padded by
-// 0-25 %), K = 256, k^ = 64: 0.32 ms (0.29 ms with weights of 16 significant bits, 27 instructions and
-// four products fewer); the per-row gather kernel that ran before took 2.71 ms and its key lists another
-// 0.57 ms to write.  Small launches take as long as their longest list: there three or six sets
-// of waves share it.
+// Bound: issue (about 200 vector instructions and 17 matrix products per 32-key sub-chunk and wave).  On the
+// layer B = 8, H = 32, T = 2000 (padded by 0-25 %), K = 256, k^ = 64 the counters show the vector pipe with an
+// instruction 56 % and the matrix pipe 31 % of the time, 2.4 waves resident per SIMD on average (three fit: held
+// to four the compiler spills registers and the kernel is slower) that wait to issue for a third of theirs.  It
+// takes 0.31 ms there (0.28 ms with weights of 16 significant bits, 27 instructions and four products fewer);
+// the per-row gather kernel that ran before took 2.71 ms and its key lists another 0.57 ms to write.  Small
+// launches take as long as their longest list: there three or six sets of waves share it.
 #include "sea_columns.h"
 #include "sea_gather.h"
 #include "sea_internal.h"

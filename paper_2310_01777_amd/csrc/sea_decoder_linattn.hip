@@ -17,8 +17,9 @@
 //
 // For parallelism the sequence is cut into G segments: a first launch (EMIT = false) leaves each segment's
 // state, the second starts from the sum of the earlier ones (causal) or of all (bidirectional).
-// Bound: latency between the barriers and vector issue (features).  B = 4, H = 12, T = 2048, m = 128: 20 + 44 us;
-// separate feature, attention and concatenation kernels, their tensors in memory, took 190 us.
+// Bound: latency between the barriers: one block per CU, whose waves wait for two thirds of their residency (vector
+// pipe busy a quarter, matrix pipe a tenth of the time).  B = 4, H = 12, T = 2048, m = 128: 20 + 44 us; separate
+// feature, attention and concatenation kernels, their tensors in memory, took 190 us.
 #include "sea_decoder.h"
 
 namespace sea {

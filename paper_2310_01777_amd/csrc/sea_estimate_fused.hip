@@ -392,11 +392,11 @@ __global__ __launch_bounds__(256) void wide_columns_kernel(Shape s, const float*
 // that column's earlier keys goes out as fp32.
 // A key whose features are not finite must not leave its column (causal rows before it do not know it): a block
 // that finds such a sum takes its columns one by one.
-// Bound: vector and matrix issue together.  B = 8, H = 32, T = 2000, K = 256, m = 256: 0.10 ms (1.54 ms with
-// the three kernels that write the features to memory, rows kernel and selection included: 0.25 ms).  Columns
-// of four keys or more (BY4) take two fp32 products per 16 features and keys instead of four, and the rows of
-// the next tile and step are requested ahead: whole forward 513 -> 502 us, B = 4, H = 12, T = 2041, m = K = 128
-// 107 -> 104 us.
+// Bound: issue of products that wait for each other (vector pipe 46 %, matrix pipe 25 % busy, 2.7 waves per SIMD that
+// wait to issue for half of their residency).  B = 8, H = 32, T = 2000, K = 256, m = 256: 0.09 ms, 0.28 ms with the
+// rows kernel and the selection (1.54 ms with the three kernels that write the features to memory).  Columns of
+// four keys or more (BY4) take two fp32 products per 16 features and keys instead of four: 93 -> 87 us there.  The
+// rows of the next tile and step are requested ahead.
 // ------------------------------------------------------------------------------------------
 template <int MC, bool CAUSAL, bool BY4>
 __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg, const uint16_t* __restrict__ K,

@@ -692,12 +692,13 @@ __global__ __launch_bounds__(256) void topk_group_kernel(Shape s, const float* _
 // buckets): a thread's column is then the same in all its groups, a group's address is a uniform base and one
 // lane offset, and a mask word is eight lanes' nibbles.
 //
-// Bound: vector issue (one block of VPT = 32 is 256 threads with 32 keys each, 64 blocks per CU at c3's size).
+// Bound: vector issue (pipe busy 78 % of the time at 3 TB/s; one block of VPT = 32 is 256 threads with 32 keys each,
+// 64 blocks per CU with B T = 16384 time steps).
 // So the keys are taken raw (score bits with the sign bit set; one OR of all of them tells whether every score
 // lies in [0, 2), else the general search below reads the slab again), the first pass counts the scores from
 // 2^-15 on in bins of 1/64 octave (over whole octaves the scores of a slab crowd into a few dozen bins, and the
 // LDS adds of a wave queue at the same words), and the few keys of the threshold's bin are ranked directly
-// instead of by two more passes.  B = 8, H = 32, T = 2048, K = 256, k^ = 64: 147 -> 110 us.
+// instead of by two more passes.  B = 8, H = 32, T = 2048, K = 256, k^ = 64: 147 -> 100 to 108 us.
 // ------------------------------------------------------------------------------------------
 constexpr uint32_t kRanked = 64;  // keys of a bin that one wave ranks
 template <int VPT>
