@@ -1004,7 +1004,7 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
 // behind four barriers).  Two blocks of eight waves per CU, each with an equal share of all heads' row groups.
 // Same arithmetic per row, bit for bit.  B = 1, H = 12, T = 131072, m = K = 128: the whole
 // forward 381 -> 360 us.  The search for
-// k^ > 1 wants more waves than stay resident here (c5's shape without padding: 97 -> 108 us for the whole
+// k^ > 1 wants more waves than stay resident here (B = 32, H = 12, T = 512, K = 64, no padding: 97 -> 108 us for the whole
 // forward), shares of sequences of different lengths are unequal, K <= 64 needs no steps to begin with, and
 // two row tiles per wave (an operand read from LDS then serves twice) cost the occupancy they would need.
 // ------------------------------------------------------------------------------------------

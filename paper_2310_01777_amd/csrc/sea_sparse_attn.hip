@@ -128,7 +128,8 @@ __device__ __forceinline__ void gather_list_row(const Shape& s, int64_t head, in
 //
 // Bound: the latency of the list entries (4 bytes per (query, key) pair) and the barriers between unpacking and
 // products, which take turns: waves wait for 62 % of their residency, the vector pipe is busy 30 %, the matrix
-// pipe 10 % of the time (B = 4, H = 12, T = 2048, 75 M entries from the FlatCSR tensor: 210 us, 2.6 TB/s).  See the launcher for when a block takes this form and what it gives.
+// pipe 10 % of the time (B = 4, H = 12, T = 2048, 75 M entries from the FlatCSR tensor: 210 us, 2.6 TB/s).  See the
+// launcher for when a block takes this form and what it gives.
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ int32_t wave_sum(int32_t x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);   // quad xor 1
@@ -520,7 +521,10 @@ void launch_lists(const Shape& s, sea_dtype dt, const void* Q, const void* K, co
   }
   const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K), *v = static_cast<const uint16_t*>(V);
   uint16_t* o = static_cast<uint16_t*>(O);
-  if (tiles_worth_a_launch(s, tiles, longest)) {
+  // (rows the tiles leave are marked in O and read Q afterwards: not where O lies in the place of Q)
+  const uintptr_t at_o = reinterpret_cast<uintptr_t>(o), at_q = reinterpret_cast<uintptr_t>(q), bytes = static_cast<uintptr_t>(nrows) * kHeadDim * 2;
+  const bool apart = at_o >= at_q + bytes || at_q >= at_o + bytes;
+  if (apart && tiles_worth_a_launch(s, tiles, longest)) {
     hipLaunchKernelGGL(list_tile_kernel<FLAT>, dim3(static_cast<uint32_t>(tiles)), dim3(256), 0, st, s, q, k, v, idx, cnt, L,
                        crow, o, group_heads_for(s.N, s.T));
     hipLaunchKernelGGL(list_rest_kernel<FLAT>, row_grid((nrows + kRestRows - 1) / kRestRows), block, 0, st, s, q, k, v, idx,

@@ -1119,15 +1119,16 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
       for (int e = 0; e < 4; ++e) zero = fmaf(0.f, acc4[e], zero);
       if (tt >= len) acc4[0] = acc4[1] = acc4[2] = acc4[3] = 0.f;  // zero times what it met need not be zero
       else if (zero != 0.f) atomicOr(&again_s, 1u << q);
+      __syncthreads();  // (also: the mask words are no longer read)
     }
-    if (tt < a.T) {
+    // (a row to compute again is left alone: O may lie in the place of Q)
+    if (tt < a.T && !(ANYW && ((again_s >> q) & 1u) != 0u)) {
       const float inv = (tt < len && L > 0.f) ? 1.f / L : 0.f;
       *reinterpret_cast<float4*>(a.O + (head * a.T + tt) * kHeadDim + 4 * dq) =
           make_float4(acc4[0] * inv, acc4[1] * inv, acc4[2] * inv, acc4[3] * inv);
     }
   }
   if constexpr (ANYW) {
-    __syncthreads();  // (also: the rows' stores above come first, and the mask words are no longer read)
     uint16_t* const place = reinterpret_cast<uint16_t*>(mask_s) + 1024 * wid;
     for (uint32_t rows = again_s; rows != 0u; rows &= rows - 1u) {
       const int r = __builtin_amdgcn_readfirstlane(__ffs(static_cast<int>(rows)) - 1);
