@@ -207,7 +207,6 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   // below m_thr's start value, so it never becomes a reference; afterwards m_thr is how far a row's
   // maximum may exceed its reference before that is moved.
   float m_ref = 0.f, m_thr = -fminf(a.c * 0x1p126f, 3.0e38f), l_run = 0.f;
-  constexpr float kRefSlack = 8.f;
   const uint32_t gmask = (NX == 8 && g != 0) ? 0u : 0x40004000u;  // NX = 8: the upper half's slots are unused
 
   const MinusOnes minus = minus_ones();
@@ -275,10 +274,11 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
       float ymax = fmaxf(fmaxf(y[0], y[1]), y[2]);
 #pragma unroll
       for (int i = 3; i < 15; i += 2) ymax = fmaxf(fmaxf(ymax, y[i]), y[i + 1]);
-      ymax = half_max(fmaxf(ymax, y[15]));
-      const bool refresh = ymax > m_thr;
-      if (__ballot(refresh) != 0ull) {
-        const float delta = refresh ? ymax : 0.f;
+      ymax = fmaxf(ymax, y[15]);
+      if (__ballot(ymax > m_thr) != 0ull) {
+        ymax = half_max(ymax);
+        const bool refresh = ymax > m_thr;
+        const float delta = refresh ? ymax + kRefRise : 0.f;
         const float corr = (refresh && m_thr > 0.f) ? __builtin_amdgcn_exp2f(-delta) : 1.f;
         l_run *= corr;
 #pragma unroll

@@ -279,7 +279,6 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
 #pragma unroll
   for (int i = 0; i < 16; ++i) { oacc[0][i] = 0.f; oacc[1][i] = 0.f; }
   float m_ref = 0.f, m_thr = -INFINITY, l_run = 0.f;
-  constexpr float kRefSlack = 8.f;
   const float c = s.scale * kLog2e;
   const MinusOnes minus = minus_ones();
   const uint32_t inf_bits = 0xff800000u;
@@ -445,10 +444,11 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         float ymax = fmaxf(fmaxf(y[0], y[1]), y[2]);
 #pragma unroll
         for (int i = 3; i < 15; i += 2) ymax = fmaxf(fmaxf(ymax, y[i]), y[i + 1]);
-        ymax = half_max(fmaxf(ymax, y[15]));
-        const bool refresh = ymax > m_thr;
-        if (__ballot(refresh) != 0ull) {
-          const float delta = refresh ? ymax : 0.f;
+        ymax = fmaxf(ymax, y[15]);
+        if (__ballot(ymax > m_thr) != 0ull) {
+          ymax = half_max(ymax);
+          const bool refresh = ymax > m_thr;
+          const float delta = refresh ? ymax + kRefRise : 0.f;
           const float corr = (refresh && m_thr > 0.f) ? __builtin_amdgcn_exp2f(-delta) : 1.f;
           l_run *= corr;
 #pragma unroll

@@ -253,7 +253,6 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   // m_thr = how far a row's maximum may exceed its reference: -inf until the row has one.  Both
   // halves of a row (lanes l, l + 32) always hold the same m_ref and m_thr.
   float m_ref = 0.f, m_thr = -INFINITY, l_run = 0.f;
-  constexpr float kRefSlack = 8.f;
 
   if (nsteps > 0) {
     SEA_FETCH(0);
@@ -372,16 +371,16 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
       float ymax = fmaxf(fmaxf(y[0], y[1]), y[2]);
 #pragma unroll
       for (int i = 3; i < 15; i += 2) ymax = fmaxf(fmaxf(ymax, y[i]), y[i + 1]);
-      ymax = half_max(fmaxf(ymax, y[15]));
-      // The reference only has to keep the exponentials in range, so it is moved (and the
-      // accumulators rescaled) when some row's maximum exceeds it by more than 8 in the exponent,
-      // or when the row has none yet; until then p may reach 256 instead of 1, which fp32 sums and
-      // bf16 P carry as well.
-      const bool refresh = ymax > m_thr;
-      if (__ballot(refresh) != 0ull) {
+      ymax = fmaxf(ymax, y[15]);
+      // The reference only has to keep the exponentials in range: it is moved (and the accumulators
+      // rescaled) when some row's maximum exceeds it by more than kRefSlack, or when the row has none yet,
+      // and then goes kRefRise past that maximum (sea_tile.h).
+      if (__ballot(ymax > m_thr) != 0ull) {
         // rows that did not ask keep their reference (factor exactly 1): a row's arithmetic
         // never depends on the other rows of its wave
-        const float delta = refresh ? ymax : 0.f;
+        ymax = half_max(ymax);
+        const bool refresh = ymax > m_thr;
+        const float delta = refresh ? ymax + kRefRise : 0.f;
         const float corr = (refresh && m_thr > 0.f) ? __builtin_amdgcn_exp2f(-delta) : 1.f;
         l_run *= corr;
 #pragma unroll
