@@ -441,10 +441,7 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
             av[mt][c2] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
           }
         }
-        float ymax = fmaxf(fmaxf(y[0], y[1]), y[2]);
-#pragma unroll
-        for (int i = 3; i < 15; i += 2) ymax = fmaxf(fmaxf(ymax, y[i]), y[i + 1]);
-        ymax = fmaxf(ymax, y[15]);
+        float ymax = max_of(y);
         if (__ballot(ymax > m_thr) != 0ull) {
           ymax = half_max(ymax);
           const bool refresh = ymax > m_thr;

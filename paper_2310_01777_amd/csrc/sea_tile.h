@@ -31,6 +31,23 @@ __device__ __forceinline__ float half_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// largest of a lane's sixteen scores, NaNs left out.  (Written as the instruction: behind a branch the compiler
+// does not know the scores for results of arithmetic and quiets them one by one first.)
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float d;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+__device__ __forceinline__ float max_of(const float (&y)[16]) {
+  float a = max3(y[0], y[1], y[2]), b = max3(y[3], y[4], y[5]);
+  a = max3(a, y[6], y[7]);
+  b = max3(b, y[8], y[9]);
+  a = max3(a, y[10], y[11]);
+  b = max3(b, y[12], y[13]);
+  a = max3(a, y[14], y[15]);
+  return max3(a, b, b);
+}
+
 // Running reference of a streaming softmax, log2 units.  Any reference gives the same weights up to a factor that
 // the row sum takes out again, so it only has to keep sums and products in range.  A row's first reference, and
 // every later one, lies kRefRise above the largest score met so far, and stays until a score exceeds it by

@@ -26,6 +26,8 @@
 #include "sea_internal.h"
 #include "sea_tile.h"
 
+#include <type_traits>
+
 namespace sea {
 namespace {
 
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   };
 
   // keys the block / this wave can see: position <= min(last row, len - 1) when causal
-  int32_t u_end_wg, u_end, j_free;
+  int32_t u_end_wg, u_end, u_free;  // below u_free every entry is admissible for every active row of the wave
   if (BUCKET) {
     u_end_wg = u_end = ulim;
     // rows of a bucket come from anywhere in the sequence: positions are compared only in the
@@ -187,14 +189,13 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
     int32_t jm = row_active ? (a.causal ? min(t, len - 1) : len - 1) : 0x7fffffff;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) jm = min(jm, __shfl_xor(jm, off, 64));
-    j_free = jm;
+    u_free = min(u_end, compact_count(jm, a.rlog, a.w));
   } else {
     const int32_t wg_hi = min(wg_tile * kRows + kRows - 1, a.T - 1);
     u_end_wg = compact_count(a.causal ? min(wg_hi, len - 1) : len - 1, a.rlog, a.w);
     const int32_t t_hi = min(q0 + 31, a.T - 1);
     u_end = q0 < a.T ? compact_count(a.causal ? min(t_hi, len - 1) : len - 1, a.rlog, a.w) : 0;
-    // below this position every key is admissible for every active row of the wave
-    j_free = a.causal ? min(q0, len - 1) : len - 1;
+    u_free = min(u_end, compact_count(a.causal ? min(q0, len - 1) : len - 1, a.rlog, a.w));
   }
   const int32_t my_jmax = a.causal ? min(t, len - 1) : len - 1;
   // compact keys this row may attend: those of the block's range whose position is <= my_jmax
@@ -260,8 +261,10 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
     if (STREAM) fetch_words(0, mn0, mn1);
   }
   __syncthreads();
-  for (int32_t step = 0; step < nsteps; ++step) {
-    const int stage = step & 1;
+  // One step, its keys and values at a place that the compiler knows: all LDS addresses of the loop are then a
+  // per-lane base and an immediate offset.
+  auto walk = [&](int32_t step, auto stage_c) __attribute__((always_inline)) {
+    constexpr int stage = decltype(stage_c)::value;
     if (step + 1 < nsteps) SEA_FETCH(step + 1);
     if (STREAM) {
       mw0 = mn0;
@@ -303,8 +306,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
       // admissibility of each (key, query) entry: reg i <-> key slot 8(i/4) + 4g + i%4.
       // Interior sub-chunks need only the column bits; the few that straddle the causal
       // diagonal or the end of the sequence also compare key positions.
-      const bool boundary =
-          (u0 + 32 > u_end) || (pos_of(min(u0 + 31, a.U - 1), a.rlog, a.w) > j_free);
+      const bool boundary = u0 + 32 > u_free;
       // Registers of one lane fall into groups that share a column (and so a mask bit): 4 for 4
       // or 8 keys per column, 8 for 16, all 16 for 32 or more and for the dense kernel.  One
       // bit-select per group picks its offset (-m_ref or -inf).
@@ -368,10 +370,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
         }
       };
       if (!STREAM) request_v();
-      float ymax = fmaxf(fmaxf(y[0], y[1]), y[2]);
-#pragma unroll
-      for (int i = 3; i < 15; i += 2) ymax = fmaxf(fmaxf(ymax, y[i]), y[i + 1]);
-      ymax = fmaxf(ymax, y[15]);
+      float ymax = max_of(y);
       // The reference only has to keep the exponentials in range: it is moved (and the accumulators
       // rescaled) when some row's maximum exceeds it by more than kRefSlack, or when the row has none yet,
       // and then goes kRefRise past that maximum (sea_tile.h).
@@ -417,6 +416,10 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
     }
     if (step + 1 < nsteps) SEA_PARK(stage ^ 1);
     __syncthreads();
+  };
+  for (int32_t step = 0; step < nsteps; step += 2) {
+    walk(step, std::integral_constant<int, 0>{});
+    if (step + 1 < nsteps) walk(step + 1, std::integral_constant<int, 1>{});
   }
 #undef SEA_FETCH
 #undef SEA_SLOT_OFF
