@@ -123,6 +123,25 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes at + 8 l.  `at` and the resource (the
+// words of buffer_words) are wave-uniform.  Nothing the compiler does waits for these loads: lds_loads_done() does, and
+// the barrier behind it makes the waves' pieces each other's.  (The builtin for this load makes the compiler wait for
+// it in front of every transpose read, i.e. in the middle of the step that it is meant to run under.)
+__device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t bytes) {
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  return u32x4{static_cast<uint32_t>(p), static_cast<uint32_t>(p >> 32) & 0xffffu, bytes, static_cast<uint32_t>(kBufferFlags)};
+}
+__device__ __forceinline__ void buffer_load_lds16(u32x4 r, uint16_t* at, uint32_t byte_off) {
+  const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
+}
+// the same with 4 bytes per lane: lane l writes word l
+__device__ __forceinline__ void buffer_load_lds4(u32x4 r, uint32_t* at, uint32_t byte_off) {
+  const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
+}
+__device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 #endif  // __HIPCC__
 
 // heads whose keys and values (2 x U x 128 B each) share the L2s at one time

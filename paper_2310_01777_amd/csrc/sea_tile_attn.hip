@@ -75,9 +75,10 @@ __device__ __forceinline__ int32_t compact_count(int32_t jmax, int32_t rlog, int
   return col * r + inside;
 }
 
-constexpr int kKRow = 72;    // halfwords per staged K row: 128 B + 16 B pad, conflict-free b128 reads
-constexpr int kVRow = 64;    // halfwords per staged V row: no padding; the 64-byte halves of rows 2, 3 (mod 4)
-                             // are exchanged, which makes the four rows of a transpose read hit distinct banks
+// Staged rows are 128 bytes without padding.  K: the 16-byte part p of row r lies at slot p ^ (r & 7), so that the
+// eight rows of eight neighbouring lanes' reads hit distinct banks; V: the 64-byte halves of rows 2, 3 (mod 4) are
+// exchanged, which does the same for the four rows of a transpose read.
+constexpr int kRow = kHeadDim;
 
 // Block = 4 waves = 128 consecutive query rows of one head (32 per wave); other splits below.  The block
 // walks the compact key list in steps of 64 keys (two 32-key sub-chunks); each step's K and V rows are fetched
@@ -107,9 +108,8 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   // MODE 3: one bit per (row, key) in HBM ([N][T][KW] words); a lane reads its row's two words of a
   // step straight from memory one step ahead, nothing of the mask is parked in LDS
   constexpr bool STREAM = MODE == 3;
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kStep * kKRow];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][kStep * kVRow];
-  // selected-column bits of the 128 rows, (KW + 1) words per row (K <= 1024: at most 16.5 KB)
+  __shared__ __attribute__((aligned(16))) uint16_t KVs[2][2][kStep * kRow];  // [place][K, V]
+  // selected-column bits of the block's rows, KW words per row (K <= 1024: at most 16 KB)
   extern __shared__ uint32_t Ms[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, keep it scalar
@@ -117,18 +117,13 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   const int ql = lane & 31, g = lane >> 5;
   const uint32_t wgs = (a.T + kRows - 1) / kRows;  // blocks per head
   int64_t head;
-  int32_t wg_tile = 0, q0 = 0, t, eslot = 0;
+  int32_t wg_tile = 0, q0 = 0, t, eslot = 0, col = 0, chunk = 0;
   int32_t ubase = 0, ulim = a.U;  // compact keys this block may touch: [ubase, ulim)
   if (BUCKET) {
     head = blockIdx.x / static_cast<uint32_t>(a.max_chunks);
-    const int32_t chunk = static_cast<int32_t>(blockIdx.x % static_cast<uint32_t>(a.max_chunks));
-    const int32_t col = a.chunk_col[head * a.max_chunks + chunk];
+    chunk = static_cast<int32_t>(blockIdx.x % static_cast<uint32_t>(a.max_chunks));
+    col = a.chunk_col[head * a.max_chunks + chunk];
     if (col < 0) return;  // past the last chunk of this head (block-uniform)
-    const int32_t* bs = a.bstart + head * (a.Kcols + 1);
-    const int32_t slot = bs[col] + (chunk - a.cstart[head * (a.Kcols + 1) + col]) * 128 + 32 * wid + ql;
-    const int32_t entry = slot < bs[col + 1] ? a.perm[head * a.perm_stride + slot] : -1;
-    t = entry < 0 ? -1 : (entry & 0xffffff);
-    eslot = entry < 0 ? 0 : (entry >> 24);
     ubase = col << a.rlog;
     ulim = ubase + (1 << a.rlog);
   } else {
@@ -142,6 +137,65 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
     head = static_cast<int64_t>(grp) * a.group_heads + rem % nh;
     wg_tile = static_cast<int32_t>(wgs - 1 - rem / nh);
     q0 = wg_tile * kRows + 32 * wid;  // first row of this wave
+  }
+  const uint16_t* Kh = a.K + head * static_cast<int64_t>(a.T) * kHeadDim;
+  const uint16_t* Vh = a.V + head * static_cast<int64_t>(a.T) * kHeadDim;
+
+  // The first step's rows and the mask words are requested ahead of everything else: they go straight to LDS, so
+  // their latency runs beside that of the rows' own loads.  Against rows that pass through registers (16 of them,
+  // four LDS stores and a wait per step), us per layer: c2 71.2 -> 66.2, c4 at T = 32768 763 -> 758, c5 76.6 -> 74.0,
+  // per-row widths at c2 171 -> 165.
+  // Staging roles: slot tid & 7 of the K and V rows (tid >> 3) and, with four waves, (tid >> 3) + 32 of the step
+  // (eight waves cover the 64 rows in one go).  The rows go from memory to LDS without a register between; a wave's
+  // 64 pieces are eight rows, one after the other.  The slots past the list re-read its last key; their scores are
+  // masked.
+  const int srow = tid >> 3;
+  const uint32_t kpart = 16 * ((tid & 7) ^ (srow & 7)), vpart = 16 * ((tid & 7) ^ (((srow >> 1) & 1) << 2));
+  // With at most 64 keys per column a step of 64 compact keys advances every slot's position by
+  // the same amount, so the four row offsets (bytes inside the head, 32 bits) just step by a
+  // constant; they are clamped to the last row, since slots past the list only need an address
+  // that is in bounds.  Steps are fetched in order, one fetch() per step.
+  const bool linear = a.rlog <= 6;
+  const uint32_t row_bytes = kHeadDim * 2, off_max = static_cast<uint32_t>(a.T - 1) * row_bytes;
+  const uint32_t off_step = linear ? static_cast<uint32_t>((kStep >> a.rlog) * a.w) * row_bytes : 0u;
+  uint32_t offa = static_cast<uint32_t>(pos_of(ubase + srow, a.rlog, a.w)) * row_bytes;
+  uint32_t offb = static_cast<uint32_t>(pos_of(ubase + srow + kThreads / 8, a.rlog, a.w)) * row_bytes;
+  // The head's keys and values as buffer resources (base in scalar registers, 32-bit byte offset
+  // per lane): a staging load then needs no 64-bit address arithmetic on the vector pipe.
+  const uint32_t head_bytes = static_cast<uint32_t>(a.T) * row_bytes;
+  const u32x4 Kres = buffer_words(Kh, head_bytes), Vres = buffer_words(Vh, head_bytes);
+  auto slot_off = [&](int32_t step, int32_t slot) {
+    return static_cast<uint32_t>(pos_of(min(ubase + step * kStep + slot, a.U - 1), a.rlog, a.w)) * row_bytes;
+  };
+  auto fetch = [&](int32_t step, int place) __attribute__((always_inline)) {
+    if (!linear) {
+      offa = slot_off(step, srow);
+      if (kTwo) offb = slot_off(step, srow + kThreads / 8);
+    }
+    uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
+    const uint32_t oa = min(offa, off_max), ob = min(offb, off_max);
+    buffer_load_lds16(Kres, at, oa + kpart);
+    if (kTwo) buffer_load_lds16(Kres, at + kThreads / 8 * kRow, ob + kpart);
+    buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
+    if (kTwo) buffer_load_lds16(Vres, at + (kStep + kThreads / 8) * kRow, ob + vpart);
+    offa += off_step;
+    offb += off_step;
+  };
+  fetch(0, 0);
+  // mask words of the block's rows -> LDS, KW words a row (words past the last row repeat the last one)
+  if (!DENSE && !STREAM) {
+    const int32_t row0 = wg_tile * kRows, nwords = min(kRows, a.T - row0) * a.KW;
+    const u32x4 Mres = buffer_words(a.mbits + (head * a.T + row0) * a.KW, static_cast<uint32_t>(nwords) * 4u);
+    for (int32_t x = 0; x < kRows * a.KW; x += kThreads)
+      buffer_load_lds4(Mres, &Ms[x + 64 * wall], static_cast<uint32_t>(min(x + tid, nwords - 1)) * 4u);
+  }
+  if (BUCKET) {
+    const int32_t* bs = a.bstart + head * (a.Kcols + 1);
+    const int32_t slot = bs[col] + (chunk - a.cstart[head * (a.Kcols + 1) + col]) * 128 + 32 * wid + ql;
+    const int32_t entry = slot < bs[col + 1] ? a.perm[head * a.perm_stride + slot] : -1;
+    t = entry < 0 ? -1 : (entry & 0xffffff);
+    eslot = entry < 0 ? 0 : (entry >> 24);
+  } else {
     t = q0 + ql;
   }
   const int32_t b = static_cast<int32_t>(head / a.H);
@@ -158,20 +212,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
 #pragma unroll
   for (int kc = 0; kc < 4; ++kc) asm volatile("" : "+v"(bq[kc]));
 
-  const uint16_t* Kh = a.K + head * static_cast<int64_t>(a.T) * kHeadDim;
-  const uint16_t* Vh = a.V + head * static_cast<int64_t>(a.T) * kHeadDim;
-  // mask words of the block's rows -> LDS (row stride KW + 1 words: conflict-free per-row reads)
-  const int mstride = a.KW + 1;
-  if (!DENSE && !STREAM) {
-    const int32_t row0 = wg_tile * kRows;
-    const uint32_t* msrc = a.mbits + (head * a.T + row0) * a.KW;
-    const int32_t nwords = min(kRows, a.T - row0) * a.KW;
-    for (int32_t x = tid; x < kRows * a.KW; x += kThreads) {
-      const int32_t r = x / a.KW, wi = x - r * a.KW;
-      Ms[r * mstride + wi] = x < nwords ? msrc[x] : 0u;
-    }
-  }
-  const uint32_t* mrow = (DENSE || STREAM) ? nullptr : &Ms[(32 * wid + ql) * mstride];
+  const uint32_t* mrow = (DENSE || STREAM) ? nullptr : &Ms[(32 * wid + ql) * a.KW];
   const uint32_t* krow = STREAM ? a.mbits + (head * a.T + tq) * a.KW : nullptr;
   uint32_t mw0 = 0u, mw1 = 0u, mn0 = 0u, mn1 = 0u;  // the row's words of this step and of the next
   auto fetch_words = [&](int32_t step_, uint32_t& w0, uint32_t& w1) {
@@ -202,48 +243,10 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   const int32_t my_ucount = min(ulim, compact_count(row_active ? my_jmax : -1, a.rlog, a.w));
   const int32_t nsteps = (u_end_wg - ubase + kStep - 1) / kStep;
 
-  // staging roles: 16-byte part tid & 7 of the K and V rows (tid >> 3) and, with four waves,
-  // (tid >> 3) + 32 of the step (eight waves cover the 64 rows in one go).  V is parked as it lies in memory; the product reads it through the LDS transpose read.
-  // Slots past the list re-read its last key; their scores are masked.
-  const int srow = tid >> 3, spart = tid & 7;
-  const int vpart = spart ^ (((srow >> 1) & 1) << 2);  // V rows 2, 3 (mod 4): halves exchanged
-  uint4 kreg0, kreg1 = {0u, 0u, 0u, 0u}, vreg0, vreg1 = {0u, 0u, 0u, 0u};
-  // With at most 64 keys per column a step of 64 compact keys advances every slot's position by
-  // the same amount, so the four row offsets (bytes inside the head, 32 bits) just step by a
-  // constant; they are clamped to the last row, since slots past the list only need an address
-  // that is in bounds.  Steps are fetched in order, one SEA_FETCH per step.
-  const bool linear = a.rlog <= 6;
-  const uint32_t row_bytes = kHeadDim * 2, part_bytes = spart * 16;
-  const uint32_t off_max = static_cast<uint32_t>(a.T - 1) * row_bytes + part_bytes;
-  const uint32_t off_step = linear ? static_cast<uint32_t>((kStep >> a.rlog) * a.w) * row_bytes : 0u;
-  uint32_t offa = static_cast<uint32_t>(pos_of(ubase + srow, a.rlog, a.w)) * row_bytes + part_bytes;
-  uint32_t offb = static_cast<uint32_t>(pos_of(ubase + srow + kThreads / 8, a.rlog, a.w)) * row_bytes + part_bytes;
-  // The head's keys and values as buffer resources (base in scalar registers, 32-bit byte offset
-  // per lane): a staging load then needs no 64-bit address arithmetic on the vector pipe.
-  const uint32_t head_bytes = static_cast<uint32_t>(a.T) * row_bytes;
-  const __amdgpu_buffer_rsrc_t Kres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Kh), 0, head_bytes, kBufferFlags);
-  const __amdgpu_buffer_rsrc_t Vres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Vh), 0, head_bytes, kBufferFlags);
-#define SEA_SLOT_OFF(slot_, step_)                                                                   \
-  (static_cast<uint32_t>(pos_of(min(ubase + (step_) * kStep + (slot_), a.U - 1), a.rlog, a.w)) * row_bytes + part_bytes)
-#define SEA_FETCH(step_)                                                                             \
-  do {                                                                                               \
-    if (!linear) {                                                                                   \
-      offa = SEA_SLOT_OFF(srow, step_);                                                              \
-      if (kTwo) offb = SEA_SLOT_OFF(srow + kThreads / 8, step_);                                            \
-    }                                                                                                \
-    kreg0 = buffer_load16(Kres, min(offa, off_max));                                                 \
-    if (kTwo) kreg1 = buffer_load16(Kres, min(offb, off_max));                                    \
-    vreg0 = buffer_load16(Vres, min(offa, off_max));                                                 \
-    if (kTwo) vreg1 = buffer_load16(Vres, min(offb, off_max));                                    \
-    offa += off_step; offb += off_step;                                                              \
-  } while (0)
-#define SEA_PARK(stage_)                                                                             \
-  do {                                                                                               \
-    *reinterpret_cast<uint4*>(&Ks[stage_][srow * kKRow + spart * 8]) = kreg0;                         \
-    if (kTwo) *reinterpret_cast<uint4*>(&Ks[stage_][(srow + kThreads / 8) * kKRow + spart * 8]) = kreg1;     \
-    *reinterpret_cast<uint4*>(&Vs[stage_][srow * kVRow + vpart * 8]) = vreg0;                         \
-    if (kTwo) *reinterpret_cast<uint4*>(&Vs[stage_][(srow + kThreads / 8) * kVRow + vpart * 8]) = vreg1;     \
-  } while (0)
+  // this lane's pieces of a K row: slots 2 kc + g of row ql
+  int kat[4];
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ (ql & 7));
 
   floatx16 oacc[2];
 #pragma unroll
@@ -255,17 +258,14 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   // halves of a row (lanes l, l + 32) always hold the same m_ref and m_thr.
   float m_ref = 0.f, m_thr = -INFINITY, l_run = 0.f;
 
-  if (nsteps > 0) {
-    SEA_FETCH(0);
-    SEA_PARK(0);
-    if (STREAM) fetch_words(0, mn0, mn1);
-  }
+  if (STREAM && nsteps > 0) fetch_words(0, mn0, mn1);
+  lds_loads_done();
   __syncthreads();
   // One step, its keys and values at a place that the compiler knows: all LDS addresses of the loop are then a
   // per-lane base and an immediate offset.
   auto walk = [&](int32_t step, auto stage_c) __attribute__((always_inline)) {
     constexpr int stage = decltype(stage_c)::value;
-    if (step + 1 < nsteps) SEA_FETCH(step + 1);
+    if (step + 1 < nsteps) fetch(step + 1, stage ^ 1);
     if (STREAM) {
       mw0 = mn0;
       mw1 = mn1;
@@ -295,13 +295,13 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
         if (__ballot((bits & cmask) != 0u) == 0ull) continue;  // no row of the wave uses it
       }
       // S^T sub-chunk = K (32 keys x 64) . Q_tile^T
-      const uint16_t* Kr = &Ks[stage][(32 * (SC * set + sc) + ql) * kKRow + 8 * g];
+      const uint16_t* Kr = &KVs[stage][0][32 * (SC * set + sc) * kRow];
       floatx16 sv;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sv[i] = 0.f;
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc)
-        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + 16 * kc), bq[kc],
+        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + kat[kc]), bq[kc],
                                                      sv, 0, 0, 0);
       // admissibility of each (key, query) entry: reg i <-> key slot 8(i/4) + 4g + i%4.
       // Interior sub-chunks need only the column bits; the few that straddle the causal
@@ -359,12 +359,12 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
       auto request_v = [&]() {
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-          const uint16_t* Vr = &Vs[stage][(32 * (SC * set + sc) + 4 * g + ((ql & 15) >> 2)) * kVRow +
+          const uint16_t* Vr = &KVs[stage][1][(32 * (SC * set + sc) + 4 * g + ((ql & 15) >> 2)) * kRow +
                                           32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
 #pragma unroll
           for (int c2 = 0; c2 < 2; ++c2) {
-            const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kVRow);
-            const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kVRow);
+            const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kRow);
+            const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kRow);
             av[mt][c2] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
           }
         }
@@ -414,21 +414,18 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
         for (int c2 = 0; c2 < 2; ++c2)
           oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], bp[c2], oacc[mt], 0, 0, 0);
     }
-    if (step + 1 < nsteps) SEA_PARK(stage ^ 1);
+    lds_loads_done();
     __syncthreads();
   };
   for (int32_t step = 0; step < nsteps; step += 2) {
     walk(step, std::integral_constant<int, 0>{});
     if (step + 1 < nsteps) walk(step + 1, std::integral_constant<int, 1>{});
   }
-#undef SEA_FETCH
-#undef SEA_SLOT_OFF
-#undef SEA_PARK
   if constexpr (NS > 1) {
     // log-sum-exp merge of the sets' partial results, halving the number of sets per round; the keys and
     // values of the last step are no longer needed (the loop ended with a barrier)
-    static_assert(NS / 2 * 64 * RW * kPartFloats * 4 <= static_cast<int>(sizeof(Ks)), "partial results fit the keys' place");
-    float* const part = reinterpret_cast<float*>(&Ks[0][0]) + 64 * wid + lane;
+    static_assert(NS / 2 * 64 * RW * kPartFloats * 4 <= static_cast<int>(sizeof(KVs)), "partial results fit the keys' and values' place");
+    float* const part = reinterpret_cast<float*>(&KVs[0][0][0]) + 64 * wid + lane;
     float m_own = m_thr > 0.f ? m_ref : -INFINITY;
 #pragma unroll
     for (int half = NS / 2; half >= 1; half >>= 1) {
@@ -717,8 +714,8 @@ static WaveSplit wave_split(const Shape& s, int32_t U, bool key_bits) {
 
 template <int RLOG, int MODE, int RW, int NS, int SC>
 static void launch_tile(const Shape& s, const TileArgs& a, hipStream_t st) {
-  constexpr int kRows = 32 * RW;
-  const size_t shm = MODE == 0 ? static_cast<size_t>(kRows) * (a.KW + 1) * sizeof(uint32_t) : 0;
+  constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS;  // (mask words arrive kThreads at a time)
+  const size_t shm = MODE == 0 ? static_cast<size_t>((kRows * a.KW + kThreads - 1) / kThreads * kThreads) * sizeof(uint32_t) : 0;
   hipLaunchKernelGGL((tile_attn_kernel<RLOG, MODE, RW, NS, SC>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
                      dim3(64 * RW * NS), shm, st, a);
 }
