@@ -25,22 +25,23 @@
 // The softmax weights go into the second product as the sum of three bf16 values (sea_tile.h), i.e. as the
 // fp32 numbers they are: products of weights and values are exact, as in the per-row kernel.
 //
-// Bound: issue (about 200 vector instructions and 17 matrix products per 32-key sub-chunk and wave).  On the
-// layer B = 8, H = 32, T = 2000 (padded by 0-25 %), K = 256, k^ = 64 the counters show the vector pipe with an
-// instruction 56 % and the matrix pipe 31 % of the time, 2.4 waves resident per SIMD on average (three fit: held
-// to four the compiler spills registers and the kernel is slower) that wait to issue for a third of theirs.  It
-// takes 0.31 ms there (0.28 ms with weights of 16 significant bits, 27 instructions and four products fewer);
-// the per-row gather kernel that ran before took 2.71 ms and its key lists another 0.57 ms to write.  Small
-// launches take as long as their longest list: there three or six sets of waves share it.
+// Bound: issue (about 200 vector instructions and 17 matrix products per 32-key sub-chunk and wave).  The keys and
+// values of a step go straight to LDS, which leaves registers for four waves per SIMD (three before).  On the layer
+// B = 8, H = 32, T = 2000 (padded by 0-25 %), K = 256, k^ = 64 the kernel takes 0.25 ms (0.29 ms with three waves per
+// SIMD and rows that pass through registers); the per-row gather kernel takes 2.71 ms and its key lists another
+// 0.57 ms to write.  Small launches take as long as their longest list: there three or six sets of waves share it.
 #include "sea_columns.h"
 #include "sea_gather.h"
 #include "sea_internal.h"
 #include "sea_tile.h"
 
+#include <type_traits>
+
 namespace sea {
 namespace {
 
-constexpr int kVRow = 64;   // halfwords per staged V row; halves of rows 2, 3 (mod 4) exchanged
+// Staged rows are 128 bytes, their 16-byte pieces exchanged by row as in the power-of-two kernel.
+constexpr int kRow = kHeadDim;
 
 struct ColumnArgs {
   const uint16_t* Q;
@@ -63,14 +64,13 @@ struct ColumnArgs {
 // RW waves side by side take 32 rows each; NS sets of them share the rows, each with every NS-th SC sub-chunks of
 // the list (see the launch).
 template <int NX, int RW, int NS, int SC>
-__global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs a) {
+__global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_kernel(ColumnArgs a) {
   constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS, kWaves = RW * NS;
   constexpr int kStep = 32 * SC * NS;  // keys per step
   static_assert(8 * kStep == 2 * kThreads, "two K and V pieces per thread and step");
-  constexpr int kKRow = NX == 8 ? 72 : (NX == 16 ? 88 : 104);  // 64 dims | NX slots | padding: conflict-free
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][kStep * kKRow];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][kStep * kVRow];
-  extern __shared__ uint32_t Ms[];  // the 128 rows' mask words, inverted, KW + 1 per row (the last all ones)
+  __shared__ __attribute__((aligned(16))) uint16_t KVs[2][2][kStep * kRow];  // [place][K, V]
+  __shared__ __attribute__((aligned(16))) uint16_t Xs[2][kStep * NX];        // the keys' slots of the mask product
+  extern __shared__ uint32_t Ms[];  // the block's rows' mask words, KW per row
   const int tid = threadIdx.x, lane = tid & 63;
   const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wid = NS > 1 ? wall % RW : wall, set = NS > 1 ? wall / RW : 0;
@@ -78,7 +78,8 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   // launch order as in the power-of-two kernel: heads in groups whose keys fit the L2s, longest tiles first
   const uint32_t wgs = (a.T + kRows - 1) / kRows;
   const uint32_t per_group = static_cast<uint32_t>(a.group_heads) * wgs;
-  const uint32_t grp = blockIdx.x / per_group, rem_b = blockIdx.x - grp * per_group;
+  const uint32_t place_b = dealt_in_turn(blockIdx.x, gridDim.x, NS == 1 ? 4 : 1, a.causal);
+  const uint32_t grp = place_b / per_group, rem_b = place_b - grp * per_group;
   const uint32_t nh = min(static_cast<uint32_t>(a.group_heads), static_cast<uint32_t>(a.N) - grp * a.group_heads);
   const int64_t head = static_cast<int64_t>(grp) * a.group_heads + rem_b % nh;
   const int32_t wg_tile = static_cast<int32_t>(wgs - 1 - rem_b / nh);
@@ -86,25 +87,6 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   const int32_t b = static_cast<int32_t>(head / a.H);
   const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
   const bool row_active = t < len;
-
-  const uint16_t* Qr = a.Q + (head * a.T + min(t, a.T - 1)) * kHeadDim + 8 * g;
-  bf16x8 bq[4];
-#pragma unroll
-  for (int kc = 0; kc < 4; ++kc) bq[kc] = *reinterpret_cast<const bf16x8*>(Qr + 16 * kc);
-  // (through an empty asm: plain register values inside the loop, not results of pending loads)
-#pragma unroll
-  for (int kc = 0; kc < 4; ++kc) asm volatile("" : "+v"(bq[kc]));
-
-  const int mstride = a.KW + 1;
-  {
-    const uint32_t* msrc = a.mbits + (head * a.T + row0) * a.KW;
-    for (int32_t x = tid; x < kRows * mstride; x += kThreads) {
-      const int32_t r = x / mstride, wi = x - r * mstride;
-      Ms[x] = (wi < a.KW && row0 + r < len) ? ~msrc[r * a.KW + wi] : 0xffffffffu;
-    }
-  }
-  const uint32_t* mrow = &Ms[(32 * wid + ql) * mstride];
-
   const int32_t wg_hi = min(row0 + kRows - 1, a.T - 1), t_hi = min(q0 + 31, a.T - 1);
   const int32_t u_end_wg = list_count(a.g, a.causal ? min(wg_hi, len - 1) : len - 1);
   const int32_t u_end = q0 < a.T ? list_count(a.g, a.causal ? min(t_hi, len - 1) : len - 1) : 0;
@@ -113,18 +95,16 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   const int32_t my_ucount = list_count(a.g, row_active ? (a.causal ? min(t, len - 1) : len - 1) : -1);
   const int32_t nsteps = (u_end_wg + kStep - 1) / kStep;
 
-  // staging: 16-byte part tid & 7 of the K and V rows (tid >> 3) and (tid >> 3) + 8 kWaves of a step: its wave's
-  // first rows lie in the step's sub-chunk wall / 4, its second ones in sub-chunk (wall + kWaves) / 4.  Rows
-  // past the list or past the sequence re-read its last row; their scores are masked.
+  // staging: slot tid & 7 of the K and V rows (tid >> 3) and (tid >> 3) + 8 kWaves of a step: its wave's
+  // first rows lie in the step's sub-chunk wall / 4, its second ones in sub-chunk (wall + kWaves) / 4.  The rows go
+  // straight to LDS.  Rows past the list or past the sequence re-read its last row; their scores are masked.
   const int srow = tid >> 3, spart = tid & 7;
-  const int vpart = spart ^ (((srow >> 1) & 1) << 2);
-  uint4 kreg0, kreg1, vreg0, vreg1;
+  const uint32_t kpart = 16 * (spart ^ (srow & 7)), vpart = 16 * (spart ^ (((srow >> 1) & 1) << 2));
   uint32_t x0[NX == 32 ? 2 : 1], x1[NX == 32 ? 2 : 1];  // this thread's words of the two rows' one-hot slots
   const uint32_t row_bytes = kHeadDim * 2, head_bytes = static_cast<uint32_t>(a.T) * row_bytes;
   const uint16_t* Kh = a.K + head * static_cast<int64_t>(a.T) * kHeadDim;
   const uint16_t* Vh = a.V + head * static_cast<int64_t>(a.T) * kHeadDim;
-  const __amdgpu_buffer_rsrc_t Kres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Kh), 0, head_bytes, kBufferFlags);
-  const __amdgpu_buffer_rsrc_t Vres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Vh), 0, head_bytes, kBufferFlags);
+  const u32x4 Kres = buffer_words(Kh, head_bytes), Vres = buffer_words(Vh, head_bytes);
   // column and remainder of this thread's next row, and of the next sub-chunk's first entry
   int32_t ucur = srow, ccol = (srow * a.A) / a.D, crem = srow * a.A - ccol * a.D;
   int32_t scol = 0, srem = 0;
@@ -152,53 +132,69 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   };
   auto row_off = [&]() -> uint32_t {
     const int32_t pos = a.g.r == 0 ? ucur : entry_pos(a.g, ccol, crem);
-    return static_cast<uint32_t>(min(pos, len - 1)) * row_bytes + spart * 16;
+    return static_cast<uint32_t>(max(min(pos, len - 1), 0)) * row_bytes;
   };
   int32_t cs0 = 0, cs1 = 0, cs2 = 0;  // first columns of the fetched step's sub-chunks and of the one after
-#define SEA_CFETCH()                                                                                  \
-  do {                                                                                                \
-    cs0 = scol;                                                                                       \
-    if (NS == 1) {                                                                                    \
-      advance(scol, srem);                                                                            \
-      cs1 = scol;                                                                                     \
-      advance(scol, srem);                                                                            \
-      cs2 = scol;                                                                                     \
-    } else {                                                                                          \
-      int32_t ncol_ = scol, nrem_ = srem;                                                             \
-      advance(ncol_, nrem_);                                                                          \
-      cs1 = ncol_;                                                                                    \
-      if (SC == 2) advance(ncol_, nrem_);                                                             \
-      cs2 = ncol_;                                                                                    \
-      advance_by(scol, srem, a.qs, a.rs);                                                             \
-    }                                                                                                 \
-    const uint32_t oa = row_off();                                                                    \
-    onehot(ccol - (NS == 1 ? cs0 : tcol0), x0);                                                       \
-    ucur += kStep / 2;                                                                                \
-    advance_half(ccol, crem);                                                                         \
-    const uint32_t ob = row_off();                                                                    \
-    onehot(ccol - (NS == 1 ? cs1 : tcol1), x1);                                                       \
-    ucur += kStep / 2;                                                                                \
-    advance_half(ccol, crem);                                                                         \
-    if (NS > 1) advance_by(tcol0, trem0, a.qs, a.rs);                                                 \
-    if (NS > 1) advance_by(tcol1, trem1, a.qs, a.rs);                                                 \
-    kreg0 = buffer_load16(Kres, oa);                                                                  \
-    kreg1 = buffer_load16(Kres, ob);                                                                  \
-    vreg0 = buffer_load16(Vres, oa);                                                                  \
-    vreg1 = buffer_load16(Vres, ob);                                                                  \
-  } while (0)
-#define SEA_CPARK(stage_)                                                                             \
-  do {                                                                                                \
-    *reinterpret_cast<uint4*>(&Ks[stage_][srow * kKRow + spart * 8]) = kreg0;                          \
-    *reinterpret_cast<uint4*>(&Ks[stage_][(srow + 8 * kWaves) * kKRow + spart * 8]) = kreg1;                   \
-    *reinterpret_cast<uint4*>(&Vs[stage_][srow * kVRow + vpart * 8]) = vreg0;                          \
-    *reinterpret_cast<uint4*>(&Vs[stage_][(srow + 8 * kWaves) * kVRow + vpart * 8]) = vreg1;                   \
-    if (NX >= 16 || spart < NX / 2) {                                                                 \
-      _Pragma("unroll") for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) {                                 \
-        *reinterpret_cast<uint32_t*>(&Ks[stage_][srow * kKRow + kHeadDim + 2 * (spart + 8 * e)]) = x0[e];        \
-        *reinterpret_cast<uint32_t*>(&Ks[stage_][(srow + 8 * kWaves) * kKRow + kHeadDim + 2 * (spart + 8 * e)]) = x1[e]; \
-      }                                                                                               \
-    }                                                                                                 \
-  } while (0)
+  auto fetch = [&](int place) __attribute__((always_inline)) {
+    cs0 = scol;
+    if (NS == 1) {
+      advance(scol, srem);
+      cs1 = scol;
+      advance(scol, srem);
+      cs2 = scol;
+    } else {
+      int32_t ncol = scol, nrem = srem;
+      advance(ncol, nrem);
+      cs1 = ncol;
+      if (SC == 2) advance(ncol, nrem);
+      cs2 = ncol;
+      advance_by(scol, srem, a.qs, a.rs);
+    }
+    const uint32_t oa = row_off();
+    onehot(ccol - (NS == 1 ? cs0 : tcol0), x0);
+    ucur += kStep / 2;
+    advance_half(ccol, crem);
+    const uint32_t ob = row_off();
+    onehot(ccol - (NS == 1 ? cs1 : tcol1), x1);
+    ucur += kStep / 2;
+    advance_half(ccol, crem);
+    if (NS > 1) advance_by(tcol0, trem0, a.qs, a.rs);
+    if (NS > 1) advance_by(tcol1, trem1, a.qs, a.rs);
+    uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
+    buffer_load_lds16(Kres, at, oa + kpart);
+    buffer_load_lds16(Kres, at + 8 * kWaves * kRow, ob + kpart);
+    buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
+    buffer_load_lds16(Vres, at + (kStep + 8 * kWaves) * kRow, ob + vpart);
+    if (NX >= 16 || spart < NX / 2) {
+#pragma unroll
+      for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) {
+        *reinterpret_cast<uint32_t*>(&Xs[place][srow * NX + 2 * (spart + 8 * e)]) = x0[e];
+        *reinterpret_cast<uint32_t*>(&Xs[place][(srow + 8 * kWaves) * NX + 2 * (spart + 8 * e)]) = x1[e];
+      }
+    }
+  };
+  // the first step's rows and the mask words are requested ahead of the query rows
+  if (nsteps > 0) fetch(0);
+  {
+    const int32_t nwords = min(kRows, a.T - row0) * a.KW;  // (words past the last row repeat the last one)
+    const u32x4 Mres = buffer_words(a.mbits + (head * a.T + row0) * a.KW, static_cast<uint32_t>(nwords) * 4u);
+    for (int32_t x = 0; x < kRows * a.KW; x += kThreads)
+      buffer_load_lds4(Mres, &Ms[x + 64 * wall], static_cast<uint32_t>(min(x + tid, nwords - 1)) * 4u);
+  }
+  const uint32_t* mrow = &Ms[(32 * wid + ql) * a.KW];
+  const uint32_t row_closed = row_active ? 0u : 0xffffffffu;
+  const uint16_t* Qr = a.Q + (head * a.T + min(t, a.T - 1)) * kHeadDim + 8 * g;
+  bf16x8 bq[4];
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) bq[kc] = *reinterpret_cast<const bf16x8*>(Qr + 16 * kc);
+  // (through an empty asm: plain register values inside the loop, not results of pending loads)
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) asm volatile("" : "+v"(bq[kc]));
+
+  // this lane's pieces of a K row: slots 2 kc + g of row ql
+  int kat[4];
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ (ql & 7));
 
   floatx16 oacc[2];
 #pragma unroll
@@ -211,32 +207,30 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
 
   const MinusOnes minus = minus_ones();
 
-  if (nsteps > 0) {
-    SEA_CFETCH();
-    SEA_CPARK(0);
-  }
+  lds_loads_done();
   __syncthreads();
-  for (int32_t step = 0; step < nsteps; ++step) {
-    const int stage = step & 1;
+  // one step, its place in the double buffer known to the compiler
+  auto walk = [&](int32_t step, auto stage_c) __attribute__((always_inline)) {
+    constexpr int stage = decltype(stage_c)::value;
     const int32_t c0[3] = {cs0, cs1, cs2};  // (uniform) columns at the start of this step's sub-chunks
-    if (step + 1 < nsteps) SEA_CFETCH();
+    if (step + 1 < nsteps) fetch(stage ^ 1);
 #pragma unroll
     for (int sc = 0; sc < SC; ++sc) {
       const int32_t u0 = step * kStep + 32 * (SC * set + sc);
       if (u0 >= u_end) break;  // wave-uniform: beyond what this wave's rows can see
       const int32_t wi = c0[sc] >> 5;
-      // the row's inverted mask bits from the sub-chunk's first column on
-      const uint32_t win = __builtin_amdgcn_alignbit(mrow[min(wi + 1, a.KW)], mrow[wi], c0[sc] & 31);
+      // the row's unselected columns from the sub-chunk's first one on (past the last column: of entries past the list)
+      const uint32_t win = ~__builtin_amdgcn_alignbit(mrow[min(wi + 1, a.KW - 1)], mrow[min(wi, a.KW - 1)], c0[sc] & 31) | row_closed;
       const int32_t ncol = min(c0[sc + 1] - c0[sc] + 1, NX);
       const uint32_t cmask = 0xffffffffu >> (32 - ncol);
       if (__ballot((win & cmask) != cmask) == 0ull) continue;  // no row of the wave uses it
-      const uint16_t* Kr = &Ks[stage][(32 * (SC * set + sc) + ql) * kKRow + 8 * g];
+      const uint16_t* Kr = &KVs[stage][0][32 * (SC * set + sc) * kRow];
       floatx16 sv;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sv[i] = 0.f;
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc)
-        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + 16 * kc), bq[kc],
+        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + kat[kc]), bq[kc],
                                                      sv, 0, 0, 0);
       // mask product: slots 8 g .. 8 g + 7 of this lane half (and 16 more for NX = 32)
 #pragma unroll
@@ -244,7 +238,7 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
         const uint32_t un = NX == 8 ? (win & 0xffu) : ((win >> (16 * e + 8 * g)) & 0xffu);
         const uint32_t xx = un | (un << 15);  // bits 2 j and 2 j + 1 sit at 2 j and 2 j + 16
         const u32x4 bx = {(xx << 14) & gmask, (xx << 12) & gmask, (xx << 10) & gmask, (xx << 8) & gmask};
-        const uint16_t* Ke = &Ks[stage][(32 * (SC * set + sc) + ql) * kKRow + kHeadDim + (NX == 8 ? 0 : 16 * e + 8 * g)];
+        const uint16_t* Ke = &Xs[stage][(32 * (SC * set + sc) + ql) * NX + (NX == 8 ? 0 : 16 * e + 8 * g)];
         sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Ke),
                                                      __builtin_bit_cast(bf16x8, bx), sv, 0, 0, 0);
       }
@@ -262,12 +256,12 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
       bf16x8 av[2][2];
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
-        const uint16_t* Vr = &Vs[stage][(32 * (SC * set + sc) + 4 * g + ((ql & 15) >> 2)) * kVRow +
+        const uint16_t* Vr = &KVs[stage][1][(32 * (SC * set + sc) + 4 * g + ((ql & 15) >> 2)) * kRow +
                                         32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2) {
-          const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kVRow);
-          const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kVRow);
+          const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kRow);
+          const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kRow);
           av[mt][c2] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         }
       }
@@ -288,20 +282,19 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
       // O^T += V^T P^T, V^T fragments in the key order of the P registers
       l_run += add_weighted_rows(y, av, minus, oacc);
     }
-    if (step + 1 < nsteps) SEA_CPARK(stage ^ 1);
+    lds_loads_done();
     __syncthreads();
+  };
+  for (int32_t step = 0; step < nsteps; step += 2) {
+    walk(step, std::integral_constant<int, 0>{});
+    if (step + 1 < nsteps) walk(step + 1, std::integral_constant<int, 1>{});
   }
-#undef SEA_CFETCH
-#undef SEA_CPARK
   if constexpr (NS > 1) {
     // merge of the sets' partial results in the place of the last step's keys and values (the loop ended
     // with a barrier)
-    constexpr int kPart = 64 * RW * kPartFloats, kInK = sizeof(Ks) / (4 * kPart);
-    static_assert(NS - 1 - kInK <= static_cast<int>(sizeof(Vs) / (4 * kPart)), "every set's result has a place");
-    auto place = [&](int e) {
-      return (e <= kInK ? reinterpret_cast<float*>(&Ks[0][0]) + (e - 1) * kPart
-                        : reinterpret_cast<float*>(&Vs[0][0]) + (e - 1 - kInK) * kPart) + 64 * wid + lane;
-    };
+    constexpr int kPart = 64 * RW * kPartFloats;
+    static_assert((NS - 1) * kPart * 4 <= static_cast<int>(sizeof(KVs)), "every set's result has a place");
+    auto place = [&](int e) { return reinterpret_cast<float*>(&KVs[0][0][0]) + (e - 1) * kPart + 64 * wid + lane; };
     float m_own = m_thr > 0.f ? m_ref : -INFINITY;
     if (set > 0) store_part<64 * RW>(place(set), oacc, l_run, m_own);
     __syncthreads();
@@ -316,12 +309,12 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
   }
   uint32_t selected = 0u;
   if (!(l_run > 0.f)) {  // no weight at all: rows without keys, or scores at the mask's level
-    for (int32_t wi = 0; wi < a.KW; ++wi) selected |= ~mrow[wi];
+    for (int32_t wi = 0; wi < a.KW; ++wi) selected |= mrow[wi];
   }
   rows_again |= static_cast<uint32_t>(__ballot(row_active && selected != 0u));  // (both halves hold the row's words)
   if (rows_again != 0u) {
     // (the column list takes the place of the mask words of the wave's rows, which no other wave reads now)
-    uint16_t* const place = reinterpret_cast<uint16_t*>(&Ms[32 * wid * mstride]);
+    uint16_t* const place = reinterpret_cast<uint16_t*>(&Ms[32 * wid * a.KW]);
     for (uint32_t rows = rows_again; rows != 0u; rows &= rows - 1u) {
       const int64_t tr = q0 + __ffs(static_cast<int>(rows)) - 1, row = head * a.T + tr;
       const ColumnKeys keys(a.g, a.mbits + row * a.KW, a.KW, a.causal ? min(static_cast<int32_t>(tr), len - 1) : len - 1, place);
@@ -346,11 +339,11 @@ __global__ __launch_bounds__(64 * RW * NS, 3) void column_attn_kernel(ColumnArgs
 
 template <int NX, int RW, int NS, int SC>
 void launch_column(const Shape& s, ColumnArgs a, hipStream_t st) {
-  constexpr int kRows = 32 * RW, kStep = 32 * SC * NS;
+  constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS, kStep = 32 * SC * NS;  // (mask words arrive kThreads at a time)
   a.qh = kStep / 2 * a.A / a.D; a.rh = kStep / 2 * a.A % a.D;
   a.qs = kStep * a.A / a.D; a.rs = kStep * a.A % a.D;
   hipLaunchKernelGGL((column_attn_kernel<NX, RW, NS, SC>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
-                     dim3(64 * RW * NS), static_cast<size_t>(kRows) * (a.KW + 1) * sizeof(uint32_t), st, a);
+                     dim3(64 * RW * NS), static_cast<size_t>((kRows * a.KW + kThreads - 1) / kThreads * kThreads) * sizeof(uint32_t), st, a);
 }
 
 }  // namespace

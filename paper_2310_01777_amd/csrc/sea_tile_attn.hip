@@ -132,7 +132,8 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
     // fastest.  Blocks are dealt round-robin to the 8 XCDs, so with 8 | group size a head stays on
     // one XCD, and blocks that start late are the short ones that fill the gaps.
     const uint32_t per_group = static_cast<uint32_t>(a.group_heads) * wgs;
-    const uint32_t grp = blockIdx.x / per_group, rem = blockIdx.x - grp * per_group;
+    const uint32_t place_b = dealt_in_turn(blockIdx.x, gridDim.x, 16 / (RW * NS), a.causal);
+    const uint32_t grp = place_b / per_group, rem = place_b - grp * per_group;
     const uint32_t nh = min(static_cast<uint32_t>(a.group_heads), static_cast<uint32_t>(a.N) - grp * a.group_heads);
     head = static_cast<int64_t>(grp) * a.group_heads + rem % nh;
     wg_tile = static_cast<int32_t>(wgs - 1 - rem / nh);
