@@ -10,6 +10,8 @@
 #include "sea_internal.h"
 #include "sea_tile.h"
 
+#include <type_traits>
+
 namespace sea {
 namespace {
 
@@ -114,22 +116,23 @@ __device__ __forceinline__ void gather_list_row(const Shape& s, int64_t head, in
 //
 // The rows' lists are turned into key bits window by window (1024 keys).  A wave takes its 32 rows one
 // after the other: a row's entries of the window are at most 1024 consecutive list entries from its
-// cursor on; each sets a byte of a 1 KB strip in LDS (no atomics: different bytes), the strip is read
-// back as 16 keys per lane and packed.  The keys any row of the block uses are ORed together on the
-// way; steps without one are skipped, and the rows of unused keys are not read from memory (a buffer
-// load past the end returns zero).  What another row of the block lists cannot reach a row either: a value
-// that is not finite gives NaN against a weight of zero, and rows whose accumulators are not finite are
-// left to the gather form.
+// cursor on.  They come straight to LDS, up to eight pieces of 256 entries ahead, and set the row's bits with one
+// atomic OR for four entries of one word.  Then the keys any row of the block uses are ORed together; steps
+// without one are skipped, and unused keys of a step are replaced by a used one.  What another row of the block
+// lists cannot reach a row either: a value that is not finite gives NaN against a weight of zero, and rows whose
+// accumulators are not finite are left to the gather form.
 //
 // This is right for lists that ascend without repetition.  Whatever else the caller passes is found out
 // by counting: the bits set over all windows equal the list lengths exactly when every entry was seen,
 // valid and unique.  A block leaves its rows to the gather form at the first window after which a cursor is
 // not where it should be.
 //
-// Bound: the latency of the list entries (4 bytes per (query, key) pair) and the barriers between unpacking and
-// products, which take turns: waves wait for 62 % of their residency, the vector pipe is busy 30 %, the matrix
-// pipe 10 % of the time (B = 4, H = 12, T = 2048, 75 M entries from the FlatCSR tensor: 210 us, 2.6 TB/s).  See the
-// launcher for when a block takes this form and what it gives.
+// Bound: unpacking and products take turns.  B = 4, H = 12, T = 2048, 75 M entries from the FlatCSR tensor: 160 us, of
+// which the start of a block (its rows' places in the tensor) 28, unpacking alone 78 (3.8 TB/s), products alone 85.
+// Before, 210 us: entries loaded through generic pointers, whose loads the compiler lets out one at a time, a byte
+// strip per row that was read back and packed, and products on one buffer with two barriers a step.  Windows that
+// start staggered over the blocks of a CU, so that their phases alternate, took 171.  See the launcher for when a
+// block takes this form and what it gives.
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ int32_t wave_sum(int32_t x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);   // quad xor 1
@@ -143,9 +146,9 @@ __device__ __forceinline__ int32_t wave_sum(int32_t x) {
 }
 
 constexpr int kTileRows = 128, kWindow = 1024;
-constexpr int kChunk = 64, kKRow = 72, kVRow = 64;
-typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));  // lists start at any entry
-constexpr int kBitRow = kWindow / 32 + 1;  // words per row of key bits, padded
+constexpr int kChunk = 64, kRow = kHeadDim;  // staged rows as in the power-of-two kernel
+constexpr int kRing = 8;                  // pieces of 256 list entries a wave has on their way
+constexpr int kBitRow = kWindow / 32 + 4;  // words per row of key bits, padded
 
 // Do the 128 rows from row0 on take tiles?  Both forms cost about a fixed time and one per key.  With the chip
 // full: 128 rows read one by one 58 ns + 1.28 ns a listed key per row, the tile walk 96 ns per 1024 keys spanned.
@@ -184,7 +187,8 @@ __device__ __forceinline__ bool takes_tiles(const Shape& s, int64_t head, int32_
 __device__ __forceinline__ void tile_block(const Shape& s, int32_t group_heads, int64_t* head, int32_t* row0) {
   const uint32_t wgs = (s.T + kTileRows - 1) / kTileRows;
   const uint32_t per_group = static_cast<uint32_t>(group_heads) * wgs;
-  const uint32_t grp = blockIdx.x / per_group, rem = blockIdx.x - grp * per_group;
+  const uint32_t place = dealt_in_turn(blockIdx.x, gridDim.x, 3, s.causal);
+  const uint32_t grp = place / per_group, rem = place - grp * per_group;
   const uint32_t nh = min(static_cast<uint32_t>(group_heads), static_cast<uint32_t>(s.N) - grp * group_heads);
   *head = static_cast<int64_t>(grp) * group_heads + rem % nh;
   *row0 = static_cast<int32_t>(wgs - 1 - rem / nh) * kTileRows;
@@ -229,10 +233,8 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
                                                            const int32_t* __restrict__ cnt, int32_t L,
                                                            const int64_t* __restrict__ crow,
                                                            uint16_t* __restrict__ O, int32_t group_heads) {
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[kChunk * kKRow];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[kChunk * kVRow];
-  __shared__ __attribute__((aligned(16))) uint8_t strip[4][kWindow + 16];
-  __shared__ uint32_t bits[kTileRows * kBitRow];
+  __shared__ __attribute__((aligned(16))) uint16_t KVs[2][2][kChunk * kRow];  // [place][K, V]
+  __shared__ __attribute__((aligned(16))) uint32_t bits[kTileRows * kBitRow];
   __shared__ uint32_t used[2][kWindow / 32];  // keys of the window any row of the block lists
   __shared__ int32_t red[4];
   __shared__ uint32_t astray;  // a row whose list is not what the walk takes it for
@@ -267,13 +269,13 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
   for (int kc = 0; kc < 4; ++kc) asm volatile("" : "+v"(bq[kc]));
 
   const uint32_t row_bytes = kHeadDim * 2, head_bytes = static_cast<uint32_t>(s.T) * row_bytes;
-  const __amdgpu_buffer_rsrc_t Kres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(K + head * static_cast<int64_t>(s.T) * kHeadDim), 0, head_bytes, kBufferFlags);
-  const __amdgpu_buffer_rsrc_t Vres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(V + head * static_cast<int64_t>(s.T) * kHeadDim), 0, head_bytes, kBufferFlags);
-  const int srow = tid >> 3, spart = tid & 7;
-  const int vpart = spart ^ (((srow >> 1) & 1) << 2);
-  uint4 kreg0, kreg1, vreg0, vreg1;
+  const u32x4 Kres = buffer_words(K + head * static_cast<int64_t>(s.T) * kHeadDim, head_bytes);
+  const u32x4 Vres = buffer_words(V + head * static_cast<int64_t>(s.T) * kHeadDim, head_bytes);
+  const int srow = tid >> 3;
+  const uint32_t kpart = 16 * ((tid & 7) ^ (srow & 7)), vpart = 16 * ((tid & 7) ^ (((srow >> 1) & 1) << 2));
+  int kat[4];  // this lane's pieces of a K row: slots 2 kc + g of row ql
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ (ql & 7));
 
   floatx16 oacc[2];
 #pragma unroll
@@ -284,144 +286,154 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
   const uint32_t inf_bits = 0xff800000u;
 
   int32_t cursor = 0;    // lane r: list entries of row 32 wid + r taken so far
-  *reinterpret_cast<uint4*>(&strip[wid][16 * lane]) = make_uint4(0u, 0u, 0u, 0u);
   if (tid < 2 * (kWindow / 32)) used[tid / (kWindow / 32)][tid % (kWindow / 32)] = 0u;
   __syncthreads();
   span = max(max(red[0], red[1]), max(red[2], red[3]));
 
   const uint64_t lp = reinterpret_cast<uint64_t>(kl.p);
   for (int32_t w0 = 0, win = 0; w0 < span; w0 += kWindow, ++win) {
-    uint32_t wave_used = 0u;  // bit i: key w0 + 16 lane + i
     // Four consecutive entries per lane and load; a load that would reach past the list is moved back to
-    // end with it (entries unpacked twice set the same byte; lists of less than four are read one by
-    // one), so no entry needs a test of its place.  The next row's entries are on their way while a row
-    // is unpacked.
+    // end with it (entries unpacked twice set the same bit), so no entry needs a test of its place.
+    {
+      uint32_t* const rows = &bits[32 * wid * kBitRow];  // the wave's rows
+      for (int x = 4 * lane; x < 32 * kBitRow; x += 4 * kWave) *reinterpret_cast<uint4*>(rows + x) = make_uint4(0u, 0u, 0u, 0u);
+    }
     const uint32_t nkeys = static_cast<uint32_t>(min(kWindow, s.T - w0));
-    auto row_list = [&](int rr) {
+    // The entries come 256 at a time, straight to LDS in the order of the rows: a ring of eight pieces in the wave's
+    // quarter of the place that the products' keys and values take later.
+    const int32_t pieces = cursor < kl.n ? min(expect, (kl.n - cursor + 255) >> 8) : 0;
+    int32_t issued = 0, taken = 0, next = 0;  // pieces asked for, pieces unpacked, the next row to ask for
+    uint16_t* const ring = &KVs[0][0][0] + wid * (kRing * 512);
+    auto row_base = [&](int rr) {
       return reinterpret_cast<const int32_t*>(
           static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lp), rr)) |
           (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lp >> 32), rr))) << 32));
     };
-    auto load_row = [&](int rr, i32x4 (&e)[4]) {
-      const int32_t n = __builtin_amdgcn_readlane(kl.n, rr), cu = __builtin_amdgcn_readlane(cursor, rr);
-      const int32_t* p = row_list(rr);
-      const int32_t nq = __builtin_amdgcn_readlane(expect, rr);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (q >= nq || cu + 256 * q >= n) break;
-        const int32_t at = cu + 256 * q + 4 * lane;
-        if (n >= 4) {
-          e[q] = *reinterpret_cast<const i32x4*>(p + min(at, n - 4));
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) e[q][i] = p[min(at + i, n - 1)];
+    auto entry_off = [&](int32_t at, int32_t n) { return static_cast<uint32_t>(4 * min(at, max(n - 4, 0))); };
+    auto ask = [&]() {
+      while (next < 32) {
+        const int32_t c = __builtin_amdgcn_readlane(pieces, next);
+        if (issued - taken + c > kRing) break;
+        if (c > 0) {
+          const int32_t n = __builtin_amdgcn_readlane(kl.n, next), cu = __builtin_amdgcn_readlane(cursor, next);
+          const u32x4 list = buffer_words(row_base(next), static_cast<uint32_t>(min(n, 1 << 29)) * 4u);
+          for (int32_t q = 0; q < c; ++q, ++issued)
+            buffer_load_lds16<true>(list, ring + (issued & (kRing - 1)) * 512, entry_off(cu + 256 * q + 4 * lane, n));
         }
+        ++next;
       }
     };
-    auto take_row = [&](int rr, const i32x4 (&e)[4]) {
+    auto take_row = [&](int rr) {
       const int32_t n = __builtin_amdgcn_readlane(kl.n, rr), cu = __builtin_amdgcn_readlane(cursor, rr);
       const int32_t key0 = __builtin_amdgcn_readlane(kl.base, rr) + w0;
-      uint32_t half = 0u;
-      if (cu < n) {  // wave-uniform
-        // entries of other windows (and invalid ones) go to the strip's spare byte
-        auto unpack = [&](const i32x4& v) {
+      const int32_t c = __builtin_amdgcn_readlane(pieces, rr);
+      if (c == 0) return;  // wave-uniform
+      uint32_t* const row = &bits[(32 * wid + rr) * kBitRow];
+      // Four entries of one whole word are set at once, which is most of them where lists hold runs of keys.  Entries of
+      // other windows (and invalid ones) set nothing, or the spare bit past the window's last key.
+      // (not the lanes past the list's end, which all read its last entries)
+      auto unpack = [&](const uint4& v, int32_t from) {
+        if (from + 4 * lane >= n) return;
+        const uint32_t k0 = static_cast<uint32_t>(key0);
+        uint32_t e[4] = {v.x - k0, v.y - k0, v.z - k0, v.w - k0};
+        if (n < 4) {  // (words past the list are no entries)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) strip[wid][min(static_cast<uint32_t>(v[i] - key0), nkeys)] = 1;
-        };
-        const int32_t nq = __builtin_amdgcn_readlane(expect, rr);
-        int32_t last = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (q >= nq || cu + 256 * q >= n) break;
-          unpack(e[q]);
-          last = __builtin_amdgcn_readlane(e[q][3], 63);
+          for (int i = 1; i < 4; ++i) e[i] = i < n ? e[i] : e[0];
         }
-        // more entries than expected: the last one requested still lies in the window
-        for (int32_t done = 256 * nq; done < kWindow && cu + done < n && static_cast<uint32_t>(last - key0) < nkeys; done += 256) {
-          const int32_t* p = row_list(rr);
-          i32x4 more;
+        const uint32_t apart = (e[0] ^ e[1]) | (e[0] ^ e[2]) | (e[0] ^ e[3]);
+        if (apart < 32u && e[0] < (nkeys & ~31u)) {
+          atomicOr(&row[e[0] >> 5], (1u << (e[0] & 31u)) | (1u << (e[1] & 31u)) | (1u << (e[2] & 31u)) | (1u << (e[3] & 31u)));
+        } else if (min(min(e[0], e[1]), min(e[2], e[3])) < nkeys) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) more[i] = p[min(cu + done + 4 * lane + i, n - 1)];
-          unpack(more);
-          last = __builtin_amdgcn_readlane(more[3], 63);
+          for (int i = 0; i < 4; ++i) {
+            const uint32_t at = min(e[i], nkeys);
+            atomicOr(&row[at >> 5], 1u << (at & 31u));
+          }
         }
-        __builtin_amdgcn_wave_barrier();
-        const uint4 v = *reinterpret_cast<const uint4*>(&strip[wid][16 * lane]);
-        *reinterpret_cast<uint4*>(&strip[wid][16 * lane]) = make_uint4(0u, 0u, 0u, 0u);
-        const uint32_t d[4] = {v.x, v.y, v.z, v.w};
-        uint32_t rev = 0u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          // bytes 0 / 1 of d to four bits, first byte highest: bits 27..24
-          uint32_t x = d[i] | (d[i] << 9);
-          x |= x << 18;
-          rev |= ((x >> 24) & 0xfu) << (28 - 4 * i);
-        }
-        half = __builtin_bitreverse32(rev);
-        // (the spare byte lies inside the last window when T ends there)
-        half &= 0xffffu >> min(16, max(0, 16 * lane + 16 - static_cast<int>(nkeys)));
-        const int32_t got = __popc(half);
-        const int32_t took = wave_sum(got);
-        if (lane == rr) cursor = cu + took;
+      };
+      lds_loads_pending(issued - taken - c);
+      int32_t last = 0;
+      for (int32_t q = 0; q < c; ++q, ++taken) {
+        const uint4 v = *reinterpret_cast<const uint4*>(ring + (taken & (kRing - 1)) * 512 + 8 * lane);
+        unpack(v, cu + 256 * q);
+        last = __builtin_amdgcn_readlane(static_cast<int>(v.w), 63);
       }
-      reinterpret_cast<uint16_t*>(&bits[(32 * wid + rr) * kBitRow])[lane] = static_cast<uint16_t>(half);
-      wave_used |= half;
+      // more entries than expected: the last one requested still lies in the window
+      for (int32_t done = 256 * c; done < kWindow && cu + done < n && static_cast<uint32_t>(last - key0) < nkeys; done += 256) {
+        const auto list = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(row_base(rr)), 0, min(n, 1 << 29) * 4, kBufferFlags);
+        const uint4 v = buffer_load16(list, entry_off(cu + done + 4 * lane, n));
+        unpack(v, cu + done);
+        last = __builtin_amdgcn_readlane(static_cast<int>(v.w), 63);
+      }
     };
-    {
-      i32x4 ea[4], eb[4];
-      load_row(0, ea);
+    ask();
 #pragma unroll 1
-      for (int rr = 0; rr < 32; rr += 2) {
-        load_row(rr + 1, eb);
-        take_row(rr, ea);
-        if (rr + 2 < 32) load_row(rr + 2, ea);
-        take_row(rr + 1, eb);
+    for (int rr = 0; rr < 32; ++rr) {
+      take_row(rr);
+      ask();
+    }
+    __builtin_amdgcn_wave_barrier();
+    // (the spare bit lies among the window's words when T ends there)
+    if (nkeys < kWindow && lane < 32) bits[(32 * wid + lane) * kBitRow + (nkeys >> 5)] &= ~(1u << (nkeys & 31u));
+    __builtin_amdgcn_wave_barrier();
+    {
+      // entries taken: the bits of row lane / 2, half a row each
+      const uint4* const half = reinterpret_cast<const uint4*>(&bits[(32 * wid + (lane >> 1)) * kBitRow + (kWindow / 64) * (lane & 1)]);
+      int32_t got = 0;
+#pragma unroll
+      for (int x = 0; x < kWindow / 256; ++x) {
+        const uint4 v = half[x];
+        got += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
       }
+      got += __shfl_xor(got, 1, kWave);
+      got = __shfl(got, 2 * (lane & 31), kWave);
+      cursor += lane < 32 ? got : 0;
     }
     // A row's next entry lies past the window, and after the last window there is none.  (The keys found are
     // different entries of the list, so a cursor that ends with the list has met every entry once.)
     const bool lost = w0 + kWindow >= span ? cursor != kl.n : (cursor < kl.n && kl.p[cursor] - kl.base < w0 + kWindow);
     const uint64_t rows_lost = __ballot(lost);
     if (lane == 0 && rows_lost != 0ull) atomicOr(&astray, 1u);
-    // keys used by the block, in 32-key words (lanes 2 i, 2 i + 1 hold the halves of word i)
-    const uint32_t upper = __shfl_xor(wave_used, 1, kWave);
-    if ((lane & 1) == 0) atomicOr(&used[win & 1][lane >> 1], wave_used | (upper << 16));
+    // keys used by the block, in 32-key words: lanes i and i + 32 go over 16 of the wave's rows each
+    static_assert(kWindow == 32 * 32, "a word per lane of half a wave");
+    uint32_t wave_used = 0u;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) wave_used |= bits[(32 * wid + 16 * g + r) * kBitRow + ql];
+    atomicOr(&used[win & 1][ql], wave_used);
     __syncthreads();
     if (astray != 0u) break;
     const uint32_t* uw = used[win & 1];
     // 64-key steps with a used key (uniform): lanes 0..15 look at one step each
     uint32_t steps = static_cast<uint32_t>(__ballot(lane < kWindow / 64 && (uw[2 * (lane & 15)] | uw[2 * (lane & 15) + 1]) != 0u));
-    auto fetch = [&](int step) {
-      const uint32_t k0 = static_cast<uint32_t>(w0 + 64 * step + srow);
-      // rows of unused keys: an offset past the resource's end, i.e. zeros
-      const uint32_t oa = (uw[2 * step] >> srow) & 1u ? k0 * row_bytes + spart * 16 : 0xfffffff0u;
-      const uint32_t ob = (uw[2 * step + 1] >> srow) & 1u ? (k0 + 32) * row_bytes + spart * 16 : 0xfffffff0u;
-      kreg0 = buffer_load16(Kres, oa);
-      kreg1 = buffer_load16(Kres, ob);
-      vreg0 = buffer_load16(Vres, oa);
-      vreg1 = buffer_load16(Vres, ob);
+    auto fetch = [&](int step, int place) __attribute__((always_inline)) {
+      // (rows of unused keys repeat the step's first used one)
+      const uint32_t u0 = uw[2 * step], u1 = uw[2 * step + 1];
+      const uint32_t k0 = static_cast<uint32_t>(w0 + 64 * step);
+      const uint32_t first = k0 + (u0 != 0u ? __ffs(u0) - 1 : 31 + __ffs(u1));
+      const uint32_t oa = ((u0 >> srow) & 1u ? k0 + srow : first) * row_bytes;
+      const uint32_t ob = ((u1 >> srow) & 1u ? k0 + 32 + srow : first) * row_bytes;
+      uint16_t* const at = &KVs[place][0][wid * 8 * kRow];
+      buffer_load_lds16(Kres, at, oa + kpart);
+      buffer_load_lds16(Kres, at + 32 * kRow, ob + kpart);
+      buffer_load_lds16(Vres, at + kChunk * kRow, oa + vpart);
+      buffer_load_lds16(Vres, at + (kChunk + 32) * kRow, ob + vpart);
     };
-    if (steps != 0u) fetch(__ffs(steps) - 1);
-    while (steps != 0u) {
+    auto walk = [&](auto place_c) __attribute__((always_inline)) {
+      constexpr int place = decltype(place_c)::value;
       const int step = __ffs(steps) - 1;
       steps &= steps - 1u;
-      *reinterpret_cast<uint4*>(&Ks[srow * kKRow + spart * 8]) = kreg0;
-      *reinterpret_cast<uint4*>(&Ks[(srow + 32) * kKRow + spart * 8]) = kreg1;
-      *reinterpret_cast<uint4*>(&Vs[srow * kVRow + vpart * 8]) = vreg0;
-      *reinterpret_cast<uint4*>(&Vs[(srow + 32) * kVRow + vpart * 8]) = vreg1;
-      __syncthreads();
-      if (steps != 0u) fetch(__ffs(steps) - 1);
+      if (steps != 0u) fetch(__ffs(steps) - 1, place ^ 1);
 #pragma unroll
       for (int sc = 0; sc < 2; ++sc) {
         const uint32_t word = bits[(32 * wid + ql) * kBitRow + 2 * step + sc];
         if (__ballot(word != 0u) == 0ull) continue;  // no row of the wave uses these keys
-        const uint16_t* Kr = &Ks[(32 * sc + ql) * kKRow + 8 * g];
+        const uint16_t* Kr = &KVs[place][0][32 * sc * kRow];
         floatx16 sv;
 #pragma unroll
         for (int i = 0; i < 16; ++i) sv[i] = 0.f;
 #pragma unroll
         for (int kc = 0; kc < 4; ++kc)
-          sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + 16 * kc), bq[kc], sv, 0, 0, 0);
+          sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Kr + kat[kc]), bq[kc], sv, 0, 0, 0);
         // reg i <-> key slot 8 (i / 4) + 4 g + i % 4
         const uint32_t wg = word >> (4 * g);
         float y[16];
@@ -433,11 +445,11 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         bf16x8 av[2][2];
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-          const uint16_t* Vr = &Vs[(32 * sc + 4 * g + ((ql & 15) >> 2)) * kVRow + 32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
+          const uint16_t* Vr = &KVs[place][1][(32 * sc + 4 * g + ((ql & 15) >> 2)) * kRow + 32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
 #pragma unroll
           for (int c2 = 0; c2 < 2; ++c2) {
-            const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kVRow);
-            const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kVRow);
+            const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kRow);
+            const bf16x4 hi = lds_transpose4(Vr + (16 * c2 + 8) * kRow);
             av[mt][c2] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
           }
         }
@@ -457,7 +469,17 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         }
         l_run += add_weighted_rows(y, av, minus, oacc);
       }
+      lds_loads_done();
       __syncthreads();
+    };
+    if (steps != 0u) {
+      fetch(__ffs(steps) - 1, 0);
+      lds_loads_done();
+    }
+    __syncthreads();
+    while (steps != 0u) {
+      walk(std::integral_constant<int, 0>{});
+      if (steps != 0u) walk(std::integral_constant<int, 1>{});
     }
     if (tid < kWindow / 32) used[(win & 1) ^ 1][tid] = 0u;  // for the next window (nobody reads it now)
     __syncthreads();
