@@ -7,6 +7,7 @@
 // found exactly by a bitwise search on order-preserving integer keys, using wave ballots and
 // population counts only; ties at the threshold go to the lower column.  Selected columns
 // are compacted in ascending order with ballot prefix counts, then expanded.
+#include "sea_columns.h"
 #include "sea_internal.h"
 #include "sea_rowlanes.h"
 
@@ -189,20 +190,31 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
     const int32_t w = s.T / s.K;
     const int32_t r = min(w, s.rep_cap);
     total = n_sel * r;
-    int32_t kept = 0;
-    for (int32_t x0 = 0; x0 < s.L; x0 += kWave) {
-      const int32_t x = x0 + lane;
-      int32_t j = -1;
-      if (x < total) {
-        const int32_t si = x / r, i = x - si * r;
-        const int32_t c = sh_sel[wid][si];
-        j = c * w + static_cast<int32_t>((static_cast<int64_t>(i) * w) / r);
-        if (j > jmax) j = -1;
+    if (irow) {
+      // Entry x is key floor(i w / r) of selected column x / r, i = x % r.  Four entries per lane and store, quotients
+      // by the reciprocal (exact below 2^21; i w < r w).  Taking 64 entries at a time with integer divisions, whose
+      // 64-bit one alone is some forty instructions, the kernel took 122 us at c2 (B = 4, H = 12, T = 2048, K = 128, k^ = 64: 477 MB
+      // read and written), this way 99.
+      const float invr = 1.0f / static_cast<float>(r);
+      const bool small = s.L < (1 << 21) && static_cast<int64_t>(r) * w < (1 << 21);
+      auto entry = [&](int32_t x) {
+        if (x >= total) return -1;
+        const int32_t si = small ? div_small(x, invr) : x / r, i = x - si * r;
+        const int32_t in = r == w ? i : (small ? div_small(i * w, invr) : static_cast<int32_t>((static_cast<int64_t>(i) * w) / r));
+        const int32_t j = sh_sel[wid][si] * w + in;
+        return j <= jmax ? j : -1;  // dropped keys are a suffix: only the last selected column can overrun jmax
+      };
+      if ((s.L & 3) == 0 && (reinterpret_cast<uintptr_t>(idx) & 15) == 0) {
+        for (int32_t x = 4 * lane; x < s.L; x += 4 * kWave)
+          *reinterpret_cast<int4*>(irow + x) = x < total ? make_int4(entry(x), entry(x + 1), entry(x + 2), entry(x + 3)) : make_int4(-1, -1, -1, -1);
+      } else {
+        for (int32_t x = lane; x < s.L; x += kWave) irow[x] = entry(x);
       }
-      if (irow && x < s.L) irow[x] = j;
-      kept += popc64(__ballot(j >= 0));
     }
-    total = kept;  // dropped keys are a suffix: only the last selected column can overrun jmax
+    if (n_sel > 0) {  // keys of the last selected column up to jmax
+      const int64_t seen = min(jmax - sh_sel[wid][n_sel - 1] * w, w - 1) + 1;
+      total = (n_sel - 1) * r + static_cast<int32_t>(min(static_cast<int64_t>(r), (seen * r + w - 1) / w));
+    }
   } else {
     // ragged columns: offsets of the selections by wave prefix scans, then one pass over the
     // list -- entry x belongs to the last selection si with off[si] <= x (binary search in LDS)
