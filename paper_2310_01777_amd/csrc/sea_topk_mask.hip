@@ -11,6 +11,8 @@
 #include "sea_internal.h"
 #include "sea_rowlanes.h"
 
+#include <type_traits>
+
 namespace sea {
 namespace {
 
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
       // Entry x is key floor(i w / r) of selected column x / r, i = x % r.  Four entries per lane and store, quotients
       // by the reciprocal (exact below 2^21; i w < r w).  Taking 64 entries at a time with integer divisions, whose
       // 64-bit one alone is some forty instructions, the kernel took 122 us at c2 (B = 4, H = 12, T = 2048, K = 128, k^ = 64: 477 MB
-      // read and written), this way 99.
+      // read and written), this way 99, and 84 with stores past the caches.
       const float invr = 1.0f / static_cast<float>(r);
       const bool small = s.L < (1 << 21) && static_cast<int64_t>(r) * w < (1 << 21);
       auto entry = [&](int32_t x) {
@@ -204,9 +206,18 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
         const int32_t j = sh_sel[wid][si] * w + in;
         return j <= jmax ? j : -1;  // dropped keys are a suffix: only the last selected column can overrun jmax
       };
+      typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
       if ((s.L & 3) == 0 && (reinterpret_cast<uintptr_t>(idx) & 15) == 0) {
-        for (int32_t x = 4 * lane; x < s.L; x += 4 * kWave)
-          *reinterpret_cast<int4*>(irow + x) = x < total ? make_int4(entry(x), entry(x + 1), entry(x + 2), entry(x + 3)) : make_int4(-1, -1, -1, -1);
+        auto fill = [&](auto past_cache) {
+          for (int32_t x = 4 * lane; x < s.L; x += 4 * kWave) {
+            const i32x4 v = x < total ? i32x4{entry(x), entry(x + 1), entry(x + 2), entry(x + 3)} : i32x4{-1, -1, -1, -1};
+            i32x4* const at = reinterpret_cast<i32x4*>(irow + x);
+            if constexpr (decltype(past_cache)::value) __builtin_nontemporal_store(v, at); else *at = v;
+          }
+        };
+        // (two loops: the compiler makes one ordinary store of two kinds of store to one place)
+        if (lists_outgrow_cache(static_cast<int64_t>(s.N) * s.T, s.L)) fill(std::true_type{});
+        else fill(std::false_type{});
       } else {
         for (int32_t x = lane; x < s.L; x += kWave) irow[x] = entry(x);
       }

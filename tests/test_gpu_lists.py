@@ -139,3 +139,27 @@ def test_flatcsr_of_short_lists(B, H, T, L):
         sea.sea_flatcsr(p, idx_d, cnt_d, L, crow, col[:cut], ws)
         assert np.array_equal(crow.cpu().numpy(), crow_o)
         assert np.array_equal(col[:cut].cpu().numpy(), col_o[:cut]) and bool((col[cut:] == -7).all())
+
+
+@pytest.mark.parametrize("B,H,T,k_hat", [(1, 12, 2048, 96), (1, 13, 2048, 64), (1, 14, 2048, 64), (2, 12, 2048, 48)])
+def test_lists_past_the_caches(B, H, T, k_hat):
+    """Lists and the tensor built from them on both sides of the size at which they bypass the caches (27.3 M entries),
+    against torch's own selection: every score distinct, whole columns of 16 keys."""
+    from paper_2310_01777_amd import binding as sea
+    K, w = 128, T // 128
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=64, K=K, k_hat=k_hat, causal=False)
+    g = torch.Generator(device="cuda").manual_seed(T + k_hat)
+    A_hat = torch.rand(B, H, T, K, generator=g, device="cuda").argsort(-1).float() / K
+    out = sea.alloc_outputs(p)
+    print(f"[case] lists past the caches {(B, H, T, k_hat)}", flush=True)
+    sea.sea_topk_mask(p, A_hat, out["sel"], out["idx"], out["cnt"])
+    sel = A_hat.topk(k_hat, -1).indices.sort(-1).values.int()
+    idx = (sel[..., None] * w + torch.arange(w, dtype=torch.int32, device="cuda")).flatten(-2)
+    assert torch.equal(out["sel"], sel) and torch.equal(out["idx"], idx) and bool((out["cnt"] == k_hat * w).all())
+    crow = torch.empty(B * T + 1, dtype=torch.int64, device="cuda")
+    col = torch.empty(idx.numel(), dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(256, sea.sea_flatcsr_workspace_bytes(p)), dtype=torch.uint8, device="cuda")
+    sea.sea_flatcsr(p, out["idx"], out["cnt"], sea.sea_row_stride(p), crow, col, ws)
+    heads = torch.arange(H, dtype=torch.int32, device="cuda")[:, None, None] * T
+    assert torch.equal(col, (idx + heads).transpose(1, 2).flatten())
+    assert torch.equal(crow, torch.arange(B * T + 1, device="cuda") * (H * k_hat * w))
