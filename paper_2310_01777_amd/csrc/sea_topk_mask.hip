@@ -63,6 +63,24 @@ __device__ __forceinline__ void or_column_keys(uint32_t* words, int32_t c, int32
   }
 }
 
+// What the rows of a launch share, so that no row divides: equal columns of w keys of which a selection emits r
+// (w = 0: the columns are not equal), reciprocals, and whether every quotient is one of div_small's.
+struct EqualColumns {
+  int32_t w, r;
+  float invw, invr;
+  bool small;
+};
+EqualColumns equal_columns(const Shape& s) {
+  EqualColumns e{};
+  if (s.geometry != 0 || s.T % s.K != 0) return e;
+  e.w = s.T / s.K;
+  e.r = e.w < s.rep_cap ? e.w : s.rep_cap;
+  e.invw = 1.0f / static_cast<float>(e.w);
+  e.invr = 1.0f / static_cast<float>(e.r);
+  e.small = s.T < (1 << 21) && s.L < (1 << 21) && static_cast<int64_t>(e.r + 1) * e.w < (1 << 21);
+  return e;
+}
+
 // ROWW: per-row width geometry -- a causal row t spreads its K columns over its own t + 1 keys
 // (column c = keys [ceil(c (t+1) / K), ceil((c+1)(t+1) / K)); empty columns are no candidates).
 // FROMBITS: the selection was already made (mbits holds it, A_hat is not read); only the lists
@@ -70,7 +88,7 @@ __device__ __forceinline__ void or_column_keys(uint32_t* words, int32_t c, int32
 template <int SLOTS, bool ROWW, bool FROMBITS>
 __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
     Shape s, const float* __restrict__ A_hat, int32_t* __restrict__ sel, int32_t* __restrict__ idx,
-    int32_t* __restrict__ cnt, uint32_t* __restrict__ mbits, uint32_t* __restrict__ kb, int32_t KWk) {
+    int32_t* __restrict__ cnt, uint32_t* __restrict__ mbits, uint32_t* __restrict__ kb, int32_t KWk, EqualColumns eq_cols) {
   __shared__ int32_t sh_sel[kWavesPerBlock][SLOTS * kWave];
   __shared__ int32_t sh_off[kWavesPerBlock][SLOTS * kWave + 1];
   __shared__ uint32_t sh_kb[kWavesPerBlock][kKeyBitWordsMax];  // the row's key bits (kb != nullptr)
@@ -81,8 +99,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
   const int32_t t = static_cast<int32_t>(blockIdx.x - head * bph) * kWavesPerBlock + wid;
   if (t >= s.T) return;  // whole wave leaves; no block-wide barrier is used below
   const int64_t row = static_cast<int64_t>(head) * s.T + t;
-  const int32_t b = static_cast<int32_t>(head / static_cast<uint32_t>(s.H));
-  const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
+  const int32_t len = s.seq_len ? min(max(s.seq_len[head / static_cast<uint32_t>(s.H)], 0), s.T) : s.T;
   int32_t* irow = idx ? idx + row * s.L : nullptr;
   int32_t* srow = sel ? sel + row * s.sel_stride : nullptr;
   const int32_t kw = (s.K + 31) / 32;  // mask words per row
@@ -102,7 +119,8 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
   }
   const int32_t jmax = (s.causal && t < len - 1) ? t : len - 1;  // last admissible key
   const int32_t Tw = ROWW ? t + 1 : s.T;                         // width the K columns are spread over
-  const int32_t ncand = bucket_of(jmax, Tw, s.K) + 1;            // candidate columns 0..ncand-1
+  // candidate columns 0..ncand-1
+  const int32_t ncand = (!ROWW && eq_cols.small ? div_small(jmax, eq_cols.invw) : bucket_of(jmax, Tw, s.K)) + 1;
   const int32_t n = min(s.k_hat, ROWW ? min(s.K, Tw) : ncand);   // ROWW: min(K, t + 1) columns hold a key
 
   int n_sel = 0;
@@ -140,8 +158,23 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
     }
     // largest tau with #{key >= tau} >= n  ==  the n-th largest key
     uint32_t tau = 0;
+    int bit = 31;
+    {
+      // Scores below 2 of which the quota lies at or above 2^-15, as nearly every row of an estimate: bits 31..27 are
+      // those of 2^-15 (the scalar unit counts, and the four SIMDs of a CU share it; rows of K = 128 whose lists are short, PLACEHOLDER)
+      int c_ge = 0, c_two = 0;
+  #pragma unroll
+      for (int q = 0; q < SLOTS; ++q) {
+        c_ge += popc64(__ballot(key[q] >= 0xb8000000u));
+        c_two += popc64(__ballot(key[q] >= 0xc0000000u));
+      }
+      if (c_two == 0 && c_ge >= n) {
+        tau = 0xb8000000u;
+        bit = c_ge == n ? -1 : 26;
+      }
+    }
   #pragma unroll 1
-    for (int bit = 31; bit >= 0; --bit) {
+    for (; bit >= 0; --bit) {
       const uint32_t trial = tau | (1u << bit);
       int c_ge = 0;
   #pragma unroll
@@ -186,19 +219,17 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
 
   if (!irow && !cnt) return;
   // expansion: selected column c emits r keys start + floor(i w / r), i < r
-  const bool uniform = !ROWW && (s.T % s.K) == 0;
   int32_t total;
-  if (uniform) {
-    const int32_t w = s.T / s.K;
-    const int32_t r = min(w, s.rep_cap);
+  if (!ROWW && eq_cols.w > 0) {
+    const int32_t w = eq_cols.w, r = eq_cols.r;
+    const float invr = eq_cols.invr;
+    const bool small = eq_cols.small;
     total = n_sel * r;
     if (irow) {
       // Entry x is key floor(i w / r) of selected column x / r, i = x % r.  Four entries per lane and store, quotients
       // by the reciprocal (exact below 2^21; i w < r w).  Taking 64 entries at a time with integer divisions, whose
       // 64-bit one alone is some forty instructions, the kernel took 122 us at c2 (B = 4, H = 12, T = 2048, K = 128, k^ = 64: 477 MB
-      // read and written), this way 99, and 84 with stores past the caches.
-      const float invr = 1.0f / static_cast<float>(r);
-      const bool small = s.L < (1 << 21) && static_cast<int64_t>(r) * w < (1 << 21);
+      // read and written), this way 99, with stores past the caches 84, and 72 without a division per row.
       auto entry = [&](int32_t x) {
         if (x >= total) return -1;
         const int32_t si = small ? div_small(x, invr) : x / r, i = x - si * r;
@@ -223,8 +254,11 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
       }
     }
     if (n_sel > 0) {  // keys of the last selected column up to jmax
-      const int64_t seen = min(jmax - sh_sel[wid][n_sel - 1] * w, w - 1) + 1;
-      total = (n_sel - 1) * r + static_cast<int32_t>(min(static_cast<int64_t>(r), (seen * r + w - 1) / w));
+      const int32_t seen = min(jmax - sh_sel[wid][n_sel - 1] * w, w - 1) + 1;
+      const int32_t in = r == w ? seen
+                                : (small ? div_small(seen * r + w - 1, eq_cols.invw)
+                                         : static_cast<int32_t>((static_cast<int64_t>(seen) * r + w - 1) / w));
+      total = (n_sel - 1) * r + min(r, in);
     }
   } else {
     // ragged columns: offsets of the selections by wave prefix scans, then one pass over the
@@ -1048,20 +1082,21 @@ hipError_t launch_topk_mask(const Shape& s, const float* A_hat, int32_t* sel, in
     else return hipErrorNotSupported;
     if (!from_bits) return hipGetLastError();
   }
+  const EqualColumns eq_cols = equal_columns(s);
 #define SEA_TOPK(SL)                                                                                               \
   do {                                                                                                             \
     if (from_bits && s.geometry == 1)                                                                              \
       hipLaunchKernelGGL((topk_mask_kernel<SL, true, true>), dim3(grid), block, 0, st, s, A_hat, sel, idx, cnt,    \
-                         mbits, kb, KWk);                                                                                   \
+                         mbits, kb, KWk, eq_cols);                                                                 \
     else if (from_bits)                                                                                            \
       hipLaunchKernelGGL((topk_mask_kernel<SL, false, true>), dim3(grid), block, 0, st, s, A_hat, sel, idx, cnt,   \
-                         mbits, kb, KWk);                                                                                   \
+                         mbits, kb, KWk, eq_cols);                                                                 \
     else if (s.geometry == 1)                                                                                      \
       hipLaunchKernelGGL((topk_mask_kernel<SL, true, false>), dim3(grid), block, 0, st, s, A_hat, sel, idx, cnt,   \
-                         mbits, kb, KWk);                                                                                   \
+                         mbits, kb, KWk, eq_cols);                                                                 \
     else                                                                                                           \
       hipLaunchKernelGGL((topk_mask_kernel<SL, false, false>), dim3(grid), block, 0, st, s, A_hat, sel, idx, cnt,  \
-                         mbits, kb, KWk);                                                                                   \
+                         mbits, kb, KWk, eq_cols);                                                                 \
   } while (0)
   if (slots <= 1) SEA_TOPK(1);
   else if (slots <= 2) SEA_TOPK(2);
