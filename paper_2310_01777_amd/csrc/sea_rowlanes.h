@@ -26,6 +26,12 @@ __device__ __forceinline__ uint32_t rows_max_u(uint32_t x) {
   const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
   return max(b[0], b[1]);
 }
+__device__ __forceinline__ uint32_t rows_min_u(uint32_t x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  const uint32_t y = min(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return min(b[0], b[1]);
+}
 __device__ __forceinline__ float rows_sum(float x) {
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);

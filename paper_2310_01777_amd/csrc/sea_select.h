@@ -14,6 +14,7 @@ template <int NCT>
 __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], uint32_t nsel, int32_t ncnd, int32_t nct_wave,
                                                int32_t k_hat, int lg, uint32_t (&nib)[NCT]) {
   uint32_t tau = 0x80000000u, cge = static_cast<uint32_t>(ncnd);
+  bool dropped = false;  // the row's threshold lies just above the one key too many that it had found
   // The compare-and-count loop runs over the tiles that hold candidates of this wave's rows only
   // (causal: the leading ones), in even steps so that a handful of loop bodies covers all cases.
   // Bits 29..16 are searched on the keys' high halves, two keys per register: both halves of
@@ -24,9 +25,9 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
   // low half is zero in that phase, so the counts are those of the full keys.  Bits 15..0 then
   // compare whole keys.
 #define SEA_SEARCH_STEP(COUNT_BODY_, REDUCE_)                                                    \
-    /* done when every row's count of keys >= tau equals its quota */                            \
+    /* done when every row's count of keys >= tau is its quota or one more */                    \
+    if (__ballot(cge > nsel + 1u && nsel != 0u) == 0ull) break;                                  \
     const bool pend = (cge != nsel) && (nsel != 0u);                                             \
-    if (__ballot(pend) == 0ull) break;                                                           \
     const uint32_t trial = tau | (1u << bit);                                                    \
     uint32_t cnt = 0;                                                                            \
     COUNT_BODY_                                                                                  \
@@ -91,6 +92,19 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
       _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct)                                        \
         _Pragma("unroll") for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= trial) ? 1u : 0u;,   \
       cnt = rows_sum_u(cnt);)                                                                    \
+  }                                                                                              \
+  /* A row with one key too many drops its smallest at or above tau (differences that wrap belong \
+     to keys below tau).  The slowest of 16 rows would take three more steps of the search for   \
+     it, some of them on whole keys.  Layers, us without / with: c4 at T = 32768 758 / 727, c3   \
+     400 / 389, c5 74.0 / 70.7, one short sentence 17.4 / 16.1. */                               \
+  dropped = cge == nsel + 1u && nsel != 0u;                                                      \
+  if (__ballot(dropped) != 0ull) {                                                               \
+    uint32_t least = 0xffffffffu;                                                                \
+    _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct)                                          \
+      _Pragma("unroll") for (int i = 0; i < 4; ++i) least = min(least, key[ct][i] - tau);         \
+    least = rows_min_u(least);                                                                   \
+    tau = dropped ? tau + least + 1u : tau;                                                      \
+    cge = dropped ? nsel : cge;                                                                  \
   }
   if (k_hat == 1) {
     // one column per row: the threshold is the row maximum itself (several columns holding it
@@ -126,8 +140,8 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
   // selection: keys >= tau; when more keys than the quota tie at tau (exact duplicates at the
   // boundary), the lowest columns among them win.  nib[ct]: bit i set iff column 16 ct + 4 lg + i
   // of this lane's row is selected.
-  const bool excess = (cge != nsel) && (nsel != 0u);
-  if (__ballot(excess) == 0ull) {
+  bool tied = __ballot(cge != nsel && nsel != 0u) != 0ull;
+  if (!tied) {
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
       uint32_t bits = 0;
@@ -135,7 +149,15 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
       for (int i = 0; i < 4; ++i) bits |= (nsel != 0u && key[ct][i] >= tau) ? (1u << i) : 0u;
       nib[ct] = bits;
     }
-  } else {
+    if (__ballot(dropped) != 0ull) {  // where the key that went had equals, they went with it
+      uint32_t cnt = 0;
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct) cnt += __popc(nib[ct]);
+      tied = __ballot(rows_sum_u(cnt) != nsel) != 0ull;
+    }
+  }
+  if (tied) {
+    tau = dropped ? tau - 1u : tau;
     uint32_t cgt = 0;
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct)
