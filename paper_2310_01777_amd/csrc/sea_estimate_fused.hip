@@ -23,6 +23,7 @@
 
 #include "sea_columns.h"
 #include "sea_internal.h"
+#include "sea_lds.h"
 #include "sea_rowlanes.h"
 #include "sea_select.h"
 
@@ -105,15 +106,6 @@ __device__ __forceinline__ float group_sum(float x) {
   if (W >= 8) x = dpp_add<kRowHalfMirror>(x);
   if (W >= 16) x = dpp_add<kRowMirror>(x);
   return x;
-}
-
-// stage W (m rows of 64 bf16) into LDS with padded rows
-__device__ __forceinline__ void stage_w(const uint16_t* __restrict__ W, uint16_t* Ws, int m, int tid) {
-  for (int x = tid; x < m * 8; x += 256) {
-    const int r = x >> 3, part = x & 7;
-    *reinterpret_cast<uint4*>(&Ws[r * kWRow + part * 8]) =
-        *reinterpret_cast<const uint4*>(W + r * kHeadDim + part * 8);
-  }
 }
 
 // raw projections w_f . x of 16 rows x m features: dots[ft][i] for feature 16 ft + 4 lg + i
@@ -723,15 +715,18 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   constexpr bool ANYW = WLOG == kAnyWidth;
   const int wl = WLOG >= 5 ? 31 - __clz(s.T / s.K) : WLOG;  // log2(column width)
   auto col_of = [&](int32_t j) { return ANYW ? column_of(cg, j) : j >> wl; };
-  constexpr int kSRow = m + 8;  // halfwords per staged state row (+16 B pad): conflict-free b128 reads
-  // W is dead once both projections are done; the state stages then reuse its space
-  constexpr int kStageHalfwords = kColStage * kSRow;
-  constexpr int kSmemHalfwords = m * kWRow > 2 * kStageHalfwords ? m * kWRow : 2 * kStageHalfwords;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemHalfwords];
-  // causal, columns wider than 16 keys: the three prefix planes of each wave's tile (requested with
-  // the wave's rows, parked here, read as operand rows once phi(Q) is ready)
-  __shared__ __attribute__((aligned(16))) uint16_t planes_s[(CAUSAL && WLOG >= 5) ? 4 * 3 * m : 8];
+  // W, then the even stages of the state, each row without padding and its 16-byte pieces p at slot p ^ (row & 7):
+  // rows come straight from memory, and the reads of eight neighbouring lanes hit distinct banks.  W is dead once
+  // both projections are done; the odd stages and, causal with columns wider than 16 keys, the three prefix planes of
+  // each wave's tile (requested with the wave's rows) then take its place.  (Through registers a stage cost 28 vector
+  // instructions, four LDS stores and sixteen registers; this kernel, us without / with: c4 at T = 32768 359 / 342, ragged
+  // T = 2000 183 / 168.)
+  constexpr int kStageHalfwords = kColStage * m;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[m * kHeadDim + kStageHalfwords];
+  static_assert(kStageHalfwords + 4 * 3 * m <= m * kHeadDim, "an odd stage and the planes fit W's place");
   uint16_t* const Ws = smem;
+  uint16_t* const planes_s = smem + kStageHalfwords;
+  auto stage_at = [&](int st) { return (st & 1) ? smem : smem + m * kHeadDim; };
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
@@ -748,37 +743,32 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
 
-  // state staging: 32 columns x m halfwords per step, contiguous in memory
-  const uint16_t* sh = state + head * static_cast<int64_t>(s.K) * m;
-  constexpr int kVecPerStage = kColStage * m / 8;      // 16-byte vectors per step
-  constexpr int kVecPerThread = kVecPerStage / 256;    // 1, 2 or 4 (m = 64..256); m = 32 -> 0
+  // state staging: 32 columns x m halfwords per step, contiguous in memory; piece tid + 256 q of a step
+  constexpr int kVecPerThread = m / 64;  // 16-byte pieces per thread and step
   static_assert(MC >= 2, "m >= 64");
-  uint4 sreg0 = {0u, 0u, 0u, 0u}, sreg1 = sreg0, sreg2 = sreg0, sreg3 = sreg0;  // named: stay in VGPRs
   const int32_t ncols_wg = CAUSAL ? __builtin_amdgcn_readfirstlane(min(s.K, col_of(min(wg_r0 + 63, s.T - 1)) + 1)) : s.K;
   const int32_t nstages = (ncols_wg + kColStage - 1) / kColStage;
-#define SEA_SFETCH1(reg_, q_, st_)                                                              \
-  if (kVecPerThread > (q_)) {                                                                  \
-    const int x_ = tid + 256 * (q_);                                                           \
-    const int col_ = min((st_) * kColStage + x_ / (m / 8), s.K - 1);                            \
-    reg_ = *reinterpret_cast<const uint4*>(sh + static_cast<int64_t>(col_) * m + (x_ % (m / 8)) * 8); \
+  const uint32_t state_bytes = static_cast<uint32_t>(s.K) * m * 2;
+  const u32x4 Sres = buffer_words(state + head * static_cast<int64_t>(s.K) * m, state_bytes);
+  auto fetch_stage = [&](int st, int tid_) __attribute__((always_inline)) {
+    const int srow = tid_ / (m / 8), spart = tid_ % (m / 8);
+    const uint32_t soff = srow * m * 2 + 16 * (spart ^ (srow & 7));
+#pragma unroll
+    for (int q = 0; q < kVecPerThread; ++q) {
+      // (columns past K read the state's last piece; nobody looks at them)
+      const uint32_t from = static_cast<uint32_t>(st) * kStageHalfwords * 2 + q * 4096u;
+      buffer_load_lds16(Sres, stage_at(st) + q * 2048 + wid * 512, min(soff + from, state_bytes - 16u));
+    }
+  };
+  if (nstages > 0) fetch_stage(0, tid);
+  {
+    const u32x4 Wres = buffer_words(W, m * kHeadDim * 2);
+    const uint32_t woff = (tid >> 3) * (kHeadDim * 2) + 16 * ((tid & 7) ^ ((tid >> 3) & 7));
+#pragma unroll
+    for (int q = 0; q < m / 32; ++q) buffer_load_lds16(Wres, Ws + q * 2048 + wid * 512, woff + q * 4096u);
   }
-#define SEA_SFETCH(st_)          \
-  SEA_SFETCH1(sreg0, 0, st_)     \
-  SEA_SFETCH1(sreg1, 1, st_)     \
-  SEA_SFETCH1(sreg2, 2, st_)     \
-  SEA_SFETCH1(sreg3, 3, st_)
-#define SEA_SPARK1(reg_, q_, buf_)                                                              \
-  if (kVecPerThread > (q_)) {                                                                  \
-    const int x_ = tid + 256 * (q_);                                                           \
-    *reinterpret_cast<uint4*>(&smem[(buf_) * kStageHalfwords + (x_ / (m / 8)) * kSRow + (x_ % (m / 8)) * 8]) = reg_;    \
-  }
-#define SEA_SPARK(buf_)          \
-  SEA_SPARK1(sreg0, 0, buf_)     \
-  SEA_SPARK1(sreg1, 1, buf_)     \
-  SEA_SPARK1(sreg2, 2, buf_)     \
-  SEA_SPARK1(sreg3, 3, buf_)
 
-  // the wave's query (and, causal, key) rows are requested before the staging waits
+  // the wave's query (and, causal, key) rows
   const int32_t t = r0 + lr, tc = min(t, s.T - 1);
   const uint16_t* Xq = Q + (head * s.T + tc) * kHeadDim;
   const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(Xq + 8 * lg);
@@ -817,27 +807,11 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   }
   // bidirectional: the same candidates for every row (taken here, while the rows are on their way)
   const int32_t ncnd_all = CAUSAL ? 0 : __builtin_amdgcn_readfirstlane(col_of(max(len - 1, 0)) + 1);
-  stage_w(W, Ws, m, tid);
-  if (ANYW && tile_planes) {
-    uint16_t* pdst = &planes_s[wid * 3 * m + lane * kPieceLen];
-#pragma unroll
-    for (int q = 0; q < kPieceLen; ++q) {
-      const uint16_t hi = f32_to_bf16(pw[q]);
-      const float r1 = pw[q] - bf16_to_f32(hi);
-      const uint16_t lo = f32_to_bf16(r1);
-      pdst[q] = hi;
-      pdst[m + q] = lo;
-      pdst[2 * m + q] = f32_to_bf16(r1 - bf16_to_f32(lo));
-    }
-  } else if (tile_planes) {
-    constexpr int kPieces = 3 * m / 8;
-    uint4* pdst = reinterpret_cast<uint4*>(&planes_s[wid * 3 * m]);
-    if (lane < kPieces) pdst[lane] = preg0;
-    if (lane + 64 < kPieces) pdst[lane + 64] = preg1;
-  }
-  if (nstages > 0) { SEA_SFETCH(0); }  // parked in LDS after the projections
+  lds_loads_done();
   __syncthreads();
 
+  // this lane's pieces lg and lg + 4 (mod 8) of a row of W
+  const int wat0 = lr * kHeadDim + 8 * (lg ^ (lr & 7)), wat1 = lr * kHeadDim + 8 * ((lg + 4) ^ (lr & 7));
   // ---- phi(Q) of this wave's 16 rows, as contraction fragments ----
   bf16x8 afrag[MC];
   // causal: phi(K) of the same 16 rows (the keys of the rows' own column inside the wave), taken in
@@ -860,8 +834,8 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int ft = 2 * kc + h;
-          const uint16_t* w = &Ws[(ft * 16 + lr) * kWRow + 8 * lg];
-          const bf16x8 w0 = *reinterpret_cast<const bf16x8*>(w), w1 = *reinterpret_cast<const bf16x8*>(w + 32);
+          const bf16x8 w0 = *reinterpret_cast<const bf16x8*>(Ws + ft * 16 * kHeadDim + wat0);
+          const bf16x8 w1 = *reinterpret_cast<const bf16x8*>(Ws + ft * 16 * kHeadDim + wat1);
           floatx4 acc = {0.f, 0.f, 0.f, 0.f};
           acc = mfma16(w0, x0, acc);
           dots[ft] = mfma16(w1, x1, acc);
@@ -872,9 +846,15 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
           for (int i = 0; i < 4; ++i) (h == 0 ? lo : hi)[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, ka[i], -kbias));
         }
         kfrag[kc] = pack8(lo, hi);
+        asm volatile("" : "+v"(kfrag[kc]));  // (now, not where it is used: sixteen values would wait in place of eight)
       }
     } else {
-      project_dots<MC>(Ws, x0, x1, lr, lg, dots);
+#pragma unroll
+      for (int ft = 0; ft < 2 * MC; ++ft) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc = mfma16(*reinterpret_cast<const bf16x8*>(Ws + ft * 16 * kHeadDim + wat0), x0, acc);
+        dots[ft] = mfma16(*reinterpret_cast<const bf16x8*>(Ws + ft * 16 * kHeadDim + wat1), x1, acc);
+      }
     }
     float dmax = -INFINITY;
 #pragma unroll
@@ -903,6 +883,28 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   // From here on every product is taken with the query rows as accumulator COLUMNS: lane l % 16 is
   // the query row, so a row of A_hat lives in the four lanes l % 16 + 16 q (16 values each per 64
   // columns) and every per-row reduction is two row-swap steps.
+  __syncthreads();  // every wave is done with W
+  int tid2 = tid;  // (what the stages need from here on is computed from here on: registers are short before)
+  asm volatile("" : "+v"(tid2));
+  const int sat0 = (tid2 & 15) * m + 8 * (((tid2 >> 4) & 3) ^ (tid2 & 7)), sat1 = sat0 ^ 32;
+  if (nstages > 1) fetch_stage(1, tid2);
+  if (ANYW && tile_planes) {
+    uint16_t* pdst = &planes_s[wid * 3 * m + lane * kPieceLen];
+#pragma unroll
+    for (int q = 0; q < kPieceLen; ++q) {
+      const uint16_t hi = f32_to_bf16(pw[q]);
+      const float r1 = pw[q] - bf16_to_f32(hi);
+      const uint16_t lo = f32_to_bf16(r1);
+      pdst[q] = hi;
+      pdst[m + q] = lo;
+      pdst[2 * m + q] = f32_to_bf16(r1 - bf16_to_f32(lo));
+    }
+  } else if (tile_planes) {
+    constexpr int kPieces = 3 * m / 8;
+    uint4* pdst = reinterpret_cast<uint4*>(&planes_s[wid * 3 * m]);
+    if (lane < kPieces) pdst[lane] = preg0;
+    if (lane + 64 < kPieces) pdst[lane + 64] = preg1;
+  }
   float diag = 0.f;
   if (CAUSAL) {
     // the row's own column: sum over keys j <= t of that column of phi(q_t) . phi(k_j).  Those
@@ -956,9 +958,6 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   }
 
   // ---- A_hat tile = phi(Q) state^T, state streamed through LDS ----
-  __syncthreads();  // every wave is done with W
-  if (nstages > 0) { SEA_SPARK(0); }
-  __syncthreads();
   floatx4 acc[NCT];
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -966,26 +965,22 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
 #pragma unroll
   for (int st = 0; st < NCT * 16 / kColStage; ++st) {
     if (st < nstages) {
-      if (st + 1 < nstages) { SEA_SFETCH(st + 1); }
+      if (st > 0 && st + 1 < nstages) fetch_stage(st + 1, tid2);
       if (r0 < s.T && st * kColStage < ncols_wave) {
 #pragma unroll
         for (int h = 0; h < kColStage / 16; ++h) {
-          const uint16_t* brow = &smem[(st & 1) * kStageHalfwords + (16 * h + lr) * kSRow + 8 * lg];
+          const uint16_t* brow = stage_at(st) + 16 * h * m;
           floatx4 a4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int kc = 0; kc < MC; ++kc)
-            a4 = mfma16(*reinterpret_cast<const bf16x8*>(brow + 32 * kc), afrag[kc], a4);
+            a4 = mfma16(*reinterpret_cast<const bf16x8*>(brow + 64 * (kc >> 1) + ((kc & 1) ? sat1 : sat0)), afrag[kc], a4);
           acc[st * (kColStage / 16) + h] = a4;
         }
       }
-      if (st + 1 < nstages) { SEA_SPARK((st + 1) & 1); }
+      lds_loads_done();
       __syncthreads();
     }
   }
-#undef SEA_SFETCH
-#undef SEA_SFETCH1
-#undef SEA_SPARK
-#undef SEA_SPARK1
   if (r0 >= s.T) return;  // no barrier below
 
   // ---- masking, the own column, normalisation, selection ----

@@ -2,6 +2,7 @@
 // query per lane and half-wave, K and V steps staged through LDS).
 #pragma once
 #include "sea_internal.h"
+#include "sea_lds.h"
 
 namespace sea {
 
@@ -115,9 +116,6 @@ __device__ __forceinline__ uint32_t rows_not_finite(float l, const floatx16 (&oa
   return static_cast<uint32_t>(lanes | (lanes >> 32));
 }
 
-// raw buffer resource, word 3: 32-bit data format, no swizzle; loads past num_records return zero
-constexpr int kBufferFlags = 0x00020000;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(byte_off), 0, 0);
   return make_uint4(v[0], v[1], v[2], v[3]);
@@ -133,44 +131,6 @@ __device__ __forceinline__ uint32_t dealt_in_turn(uint32_t block, uint32_t grid,
   if (!causal || grid > 256u * per_cu || ((block >> 8) & 1u) == 0u) return block;
   const uint32_t lo = block & ~255u, n8 = min(256u, grid - lo) >> 3, at8 = (block - lo) >> 3;
   return at8 < n8 ? lo + 8u * (n8 - 1u - at8) + (block & 7u) : block;
-}
-
-// 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes at + 8 l.  `at` and the resource (the
-// words of buffer_words) are wave-uniform.  Nothing the compiler does waits for these loads: lds_loads_done() does, and
-// the barrier behind it makes the waves' pieces each other's.  (The builtin for this load makes the compiler wait for
-// it in front of every transpose read, i.e. in the middle of the step that it is meant to run under.)
-__device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t bytes) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  return u32x4{static_cast<uint32_t>(p), static_cast<uint32_t>(p >> 32) & 0xffffu, bytes, static_cast<uint32_t>(kBufferFlags)};
-}
-// FRESH: the resource's words may come from vector instructions just before (read lanes), whose results a load may read
-// five wait states later.
-template <bool FRESH = false>
-__device__ __forceinline__ void buffer_load_lds16(u32x4 r, uint16_t* at, uint32_t byte_off) {
-  const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at));
-  if (FRESH)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
-}
-// the same with 4 bytes per lane: lane l writes word l
-__device__ __forceinline__ void buffer_load_lds4(u32x4 r, uint32_t* at, uint32_t byte_off) {
-  const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at));
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
-}
-__device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// waits until at most n (uniform, below eight) of the loads asked for last are on their way
-__device__ __forceinline__ void lds_loads_pending(int n) {
-  switch (n) {
-    case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
-    case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
-    case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
-    case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
-    case 5: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
-    case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
-    case 7: asm volatile("s_waitcnt vmcnt(7)" ::: "memory"); break;
-    default: lds_loads_done(); break;
-  }
 }
 
 #endif  // __HIPCC__
