@@ -15,6 +15,7 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
                                                int32_t k_hat, int lg, uint32_t (&nib)[NCT]) {
   uint32_t tau = 0x80000000u, cge = static_cast<uint32_t>(ncnd);
   bool dropped = false;  // the row's threshold lies just above the one key too many that it had found
+  bool counted = false;  // (uniform) some row's selection may hold equals of one key
   // The compare-and-count loop runs over the tiles that hold candidates of this wave's rows only
   // (causal: the leading ones), in even steps so that a handful of loop bodies covers all cases.
   // Bits 29..16 are searched on the keys' high halves, two keys per register: both halves of
@@ -114,14 +115,10 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
     for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
       for (int i = 0; i < 4; ++i) mx = max(mx, key[ct][i]);
-    mx = rows_max_u(mx);
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= mx) ? 1u : 0u;
-    tau = mx;
-    cge = rows_sum_u(cnt);
+    // (taken for the one key it is; the count of the selection below finds its equals)
+    tau = rows_max_u(mx);
+    cge = nsel;
+    counted = true;
   } else if (NCT >= 16 && nct_wave > 12) {
     SEA_SEARCH(NCT >= 16 ? 16 : NCT)
   } else if (NCT >= 16 && nct_wave > 8) {
@@ -149,7 +146,7 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
       for (int i = 0; i < 4; ++i) bits |= (nsel != 0u && key[ct][i] >= tau) ? (1u << i) : 0u;
       nib[ct] = bits;
     }
-    if (__ballot(dropped) != 0ull) {  // where the key that went had equals, they went with it
+    if (counted || __ballot(dropped) != 0ull) {  // where the key that went had equals, they went with it
       uint32_t cnt = 0;
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct) cnt += __popc(nib[ct]);
