@@ -617,6 +617,174 @@ __global__ __launch_bounds__(256) void bucket_scatter_kernel(const uint32_t* __r
   }
 }
 
+// Attention of buckets whose columns hold at most 64 keys: a block takes CH consecutive 128-row chunks of a head, so
+// that a column's keys and values are staged once for the chunks of it that follow one another, and the next chunk's
+// query rows are on their way while a chunk is computed.  All keys of a row are there at once: no running reference.
+// Bound: memory (rows gathered and scattered).  Rows come and go as whole lines, eight lanes of 16 bytes each, through
+// LDS: 12 heads of 131072 rows in 128 buckets, 64 keys each, 77 us (5.2 TB/s) against 118 with the one-chunk blocks of
+// the kernel above, whose lanes each move 16 and 8 bytes of their own row per instruction; with CH chunks per block but
+// rows moved like that 138.
+template <int CH>
+__global__ __launch_bounds__(256, 4) void bucket_attn_kernel(TileArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t KVs[2][64 * kRow];    // [K, V]
+  __shared__ __attribute__((aligned(16))) uint16_t rows_s[4][32 * kRow];  // a wave's query rows on their way in, its results on their way out
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ql = lane & 31, g = lane >> 5;
+  const uint32_t groups = (static_cast<uint32_t>(a.max_chunks) + CH - 1) / CH;
+  const int64_t head = blockIdx.x / groups;
+  const int32_t first = static_cast<int32_t>(blockIdx.x % groups) * CH;
+  const int32_t* cols = a.chunk_col + head * a.max_chunks;
+  int32_t col[CH], entry[CH];
+#pragma unroll
+  for (int i = 0; i < CH; ++i) col[i] = first + i < a.max_chunks ? cols[first + i] : -1;
+  if (col[0] < 0) return;  // past the last chunk of this head (block-uniform)
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    const int32_t c = max(col[i], 0);
+    const int32_t* bs = a.bstart + head * (a.Kcols + 1);
+    const int32_t slot = bs[c] + (first + i - a.cstart[head * (a.Kcols + 1) + c]) * 128 + 32 * wid + ql;
+    entry[i] = col[i] >= 0 && slot < bs[c + 1] ? a.perm[head * a.perm_stride + slot] : -1;
+  }
+  const int32_t r = 1 << a.rlog, subs = r > 32 ? 2 : 1;
+  const int32_t b = static_cast<int32_t>(head / a.H);
+  const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
+  const uint32_t row_bytes = kHeadDim * 2, head_bytes = static_cast<uint32_t>(a.T) * row_bytes;
+  const u32x4 Kres = buffer_words(a.K + head * static_cast<int64_t>(a.T) * kHeadDim, head_bytes);
+  const u32x4 Vres = buffer_words(a.V + head * static_cast<int64_t>(a.T) * kHeadDim, head_bytes);
+  const u32x4 Qres = buffer_words(a.Q + head * static_cast<int64_t>(a.T) * kHeadDim, head_bytes);
+  auto stage = [&](int32_t c) {
+    const int srow = tid >> 3;
+    const uint32_t kpart = 16 * ((tid & 7) ^ (srow & 7)), vpart = 16 * ((tid & 7) ^ (((srow >> 1) & 1) << 2));
+    for (int e = 0; e < subs; ++e) {
+      const uint32_t at = static_cast<uint32_t>(pos_of((c << a.rlog) + min(srow + 32 * e, r - 1), a.rlog, a.w)) * row_bytes;
+      buffer_load_lds16(Kres, &KVs[0][(8 * wid + 32 * e) * kRow], at + kpart);
+      buffer_load_lds16(Vres, &KVs[1][(8 * wid + 32 * e) * kRow], at + vpart);
+    }
+  };
+  // Rows move whole: eight lanes of 16 bytes each, piece p of row r at slot p ^ (r & 7) of the wave's place.
+  uint16_t* const place = rows_s[wid];
+  const int mrow = lane >> 3, mpart = lane & 7;
+  auto ask_rows = [&](int32_t en) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int32_t e = __shfl(en, 8 * j + mrow, kWave);
+      buffer_load_lds16(Qres, place + 8 * j * kRow, static_cast<uint32_t>(e < 0 ? 0 : (e & 0xffffff)) * row_bytes + 16 * (mpart ^ mrow));
+    }
+  };
+  int kat[4];
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ (ql & 7));
+  bf16x8 bq[4];
+  auto take_rows = [&]() {
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) bq[kc] = *reinterpret_cast<const bf16x8*>(place + kat[kc]);
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) asm volatile("" : "+v"(bq[kc])::"memory");  // (read before the place is used again)
+  };
+  ask_rows(entry[0]);
+  int32_t staged = -1;
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    if (col[i] < 0) break;
+    if (col[i] != staged) {
+      if (i > 0) __syncthreads();  // every wave is done with the column before
+      stage(col[i]);
+      staged = col[i];
+      lds_loads_done();
+      __syncthreads();
+    }
+    if (i == 0) take_rows();
+    const bool more = i + 1 < CH && col[i + 1 < CH ? i + 1 : i] >= 0;
+    if (more) ask_rows(entry[i + 1 < CH ? i + 1 : i]);
+    const int32_t t = entry[i] < 0 ? -1 : (entry[i] & 0xffffff);
+    const bool active = t >= 0 && t < len;
+    // keys of the column that the row may attend: the first mine
+    const int32_t jmax = active ? (a.causal ? min(t, len - 1) : len - 1) : -1;
+    const int32_t mine = max(min(compact_count(jmax, a.rlog, a.w) - (col[i] << a.rlog), r), 0);
+    const bool whole = __ballot(mine < 32 * subs) == 0ull;
+    float y[2][16];
+#pragma unroll
+    for (int sc = 0; sc < 2; ++sc) {
+      floatx16 sv;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) sv[x] = 0.f;
+      if (sc < subs) {
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc)
+          sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(&KVs[0][32 * sc * kRow] + kat[kc]), bq[kc], sv, 0, 0, 0);
+      }
+#pragma unroll
+      for (int x = 0; x < 16; ++x) y[sc][x] = sv[x] * a.c;
+      if (!whole || sc >= subs) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) y[sc][x] = sc < subs && 32 * sc + 8 * (x >> 2) + 4 * g + (x & 3) < mine ? y[sc][x] : -INFINITY;
+      }
+    }
+    const float m = half_max(fmaxf(max_of(y[0]), max_of(y[1]))), ref = m == -INFINITY ? 0.f : m;
+    float l = 0.f;
+    floatx16 oacc[2];
+#pragma unroll
+    for (int x = 0; x < 16; ++x) { oacc[0][x] = 0.f; oacc[1][x] = 0.f; }
+    const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+#pragma unroll
+    for (int sc = 0; sc < 2; ++sc) {
+      if (sc >= subs) break;
+      bf16x2 h[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const floatx2 f2 = {__builtin_amdgcn_exp2f(y[sc][2 * e] - ref), __builtin_amdgcn_exp2f(y[sc][2 * e + 1] - ref)};
+        h[e] = __builtin_convertvector(f2, bf16x2);
+        l = __builtin_amdgcn_fdot2_f32_bf16(h[e], ones, l, false);
+      }
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const uint16_t* Vr = &KVs[1][(32 * sc + 4 * g + ((ql & 15) >> 2)) * kRow + 32 * (mt ^ ((ql >> 3) & 1)) + (ql & 16) + 4 * (ql & 3)];
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) {
+          const bf16x4 lo = lds_transpose4(Vr + (16 * c2) * kRow), hi = lds_transpose4(Vr + (16 * c2 + 8) * kRow);
+          oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7),
+                                                             join_pairs(h + 4 * c2), oacc[mt], 0, 0, 0);
+        }
+      }
+    }
+    l = half_sum(l);
+    const float inv = (active && l > 0.f) ? 1.f / l : 0.f;
+    if (a.part_o && t >= 0 && g == 0) {
+      const int64_t e = (head * a.T + t) * a.slots + (entry[i] >> 24);
+      a.part_ml[2 * e] = m;
+      a.part_ml[2 * e + 1] = active ? l : 0.f;
+    }
+    if (more) {
+      lds_loads_done();
+      take_rows();
+    }
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        // regs 4 q4 .. 4 q4 + 3 <-> d = 32 mt + 8 q4 + 4 g + 0..3
+        const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
+        const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
+        const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
+        *reinterpret_cast<bf16x4*>(place + ql * kRow + 8 * ((4 * mt + q4) ^ (ql & 7)) + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
+      }
+    __builtin_amdgcn_wave_barrier();
+    uint4 out[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[j] = *reinterpret_cast<const uint4*>(place + (8 * j + mrow) * kRow + 8 * (mpart ^ mrow));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int32_t e = __shfl(entry[i], 8 * j + mrow, kWave);
+      if (e < 0) continue;
+      const int64_t row = head * a.T + (e & 0xffffff);
+      uint16_t* const Or = a.part_o ? a.part_o + (row * a.slots + (e >> 24)) * kHeadDim : a.O + row * kHeadDim;
+      *reinterpret_cast<uint4*>(Or + 8 * mpart) = out[j];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // several columns per row: O[t] = sum_s w_s On_s / sum_s w_s with w_s = l_s 2^(m_s - M), over the
 // row's entries (On_s normalised partial outputs, m_s references in log2 units, l_s sums)
 __global__ __launch_bounds__(256) void bucket_merge_kernel(const uint32_t* __restrict__ mbits,
@@ -834,7 +1002,10 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
       a.part_ml = reinterpret_cast<float*>(base + lay.part_ml);
     }
     const int32_t max_chunks = lay.max_chunks;
-    hipLaunchKernelGGL((tile_attn_kernel<0, 2>), dim3(static_cast<uint32_t>(s.N) * max_chunks), dim3(256), 0, st, a);
+    if (rlog <= 6)
+      hipLaunchKernelGGL(bucket_attn_kernel<4>, dim3(static_cast<uint32_t>(s.N) * ((max_chunks + 3) / 4)), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL((tile_attn_kernel<0, 2>), dim3(static_cast<uint32_t>(s.N) * max_chunks), dim3(256), 0, st, a);
     if (multi) {
       const int64_t rows = static_cast<int64_t>(s.N) * s.T;
       hipLaunchKernelGGL(bucket_merge_kernel, dim3(static_cast<uint32_t>((rows * 8 + 255) / 256)), dim3(256), 0, st,
