@@ -321,20 +321,13 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
       gather_row_bf16(keys, a.c, a.Q + row * kHeadDim, Kh, Vh, a.O + row * kHeadDim);
     }
   }
-  if (t < a.T && ((rows_again >> ql) & 1u) == 0u) {
-    const float inv = (row_active && l_run > 0.f) ? 1.f / l_run : 0.f;
-    uint16_t* Or = a.O + (head * a.T + t) * kHeadDim;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        // regs 4 q4 .. 4 q4 + 3 <-> d = 32 mt + 8 q4 + 4 g + 0..3
-        const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
-        const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
-        const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
-        *reinterpret_cast<bf16x4*>(Or + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
-      }
-  }
+  const float inv = (row_active && l_run > 0.f) ? 1.f / l_run : 0.f;
+  // (behind the partial results of other waves, where there are such)
+  constexpr int kPartBytes = (NS - 1) * 64 * RW * kPartFloats * 4;
+  static_assert(kPartBytes + RW * 32 * kRow * 2 <= static_cast<int>(sizeof(KVs)), "rows on their way out fit the keys' and values' place");
+  store_rows(&KVs[0][0][0] + kPartBytes / 2 + wid * 32 * kRow, oacc, inv, 0u, [&](int r) -> uint16_t* {
+    return q0 + r < a.T && ((rows_again >> r) & 1u) == 0u ? a.O + (head * a.T + q0 + r) * kHeadDim : nullptr;
+  });
 }
 
 template <int NX, int RW, int NS, int SC>
@@ -356,7 +349,8 @@ bool column_attn_supported(const Shape& s, sea_dtype dt) {
 hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
                               const uint32_t* mbits, uint16_t* O, hipStream_t st) {
   if (!column_attn_supported(s, SEA_BF16)) return hipErrorNotSupported;
-  if (column_gather_pays(s, SEA_BF16)) return launch_column_gather(s, SEA_BF16, Q, K, V, mbits, O, st);
+  if (starts_odd(K) || starts_odd(V) || column_gather_pays(s, SEA_BF16))
+    return launch_column_gather(s, SEA_BF16, Q, K, V, mbits, O, st);
   StageScope scope(SEA_STAGE_SPARSE, st);
   ColumnArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;

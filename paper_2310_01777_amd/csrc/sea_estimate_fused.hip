@@ -764,8 +764,13 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   {
     const u32x4 Wres = buffer_words(W, m * kHeadDim * 2);
     const uint32_t woff = (tid >> 3) * (kHeadDim * 2) + 16 * ((tid & 7) ^ ((tid >> 3) & 7));
+    if ((Wres[0] & 3u) == 0u) {
 #pragma unroll
-    for (int q = 0; q < m / 32; ++q) buffer_load_lds16(Wres, Ws + q * 2048 + wid * 512, woff + q * 4096u);
+      for (int q = 0; q < m / 32; ++q) buffer_load_lds16(Wres, Ws + q * 2048 + wid * 512, woff + q * 4096u);
+    } else {
+#pragma unroll 1
+      for (int q = 0; q < m / 32; ++q) buffer_load_lds16_odd(Wres, Ws + q * 2048 + wid * 512, woff + q * 4096u);
+    }
   }
 
   // the wave's query (and, causal, key) rows

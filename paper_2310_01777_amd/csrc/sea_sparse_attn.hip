@@ -485,20 +485,13 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
     __syncthreads();
   }
   l_run = half_sum(l_run);
-  const bool left = astray != 0u || ((rows_not_finite(l_run, oacc) >> ql) & 1u) != 0u;
-  if (t < s.T) {
-    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-    uint16_t* Or = O + (head * s.T + t) * kHeadDim;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        uint2 o = {pack_bf16(oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv),
-                   pack_bf16(oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv)};
-        if (left) o = {kRowLeft, kRowLeft};
-        *reinterpret_cast<uint2*>(Or + 32 * mt + 8 * q4 + 4 * g) = o;
-      }
-  }
+  const uint32_t left = astray != 0u ? ~0u : rows_not_finite(l_run, oacc);
+  __syncthreads();  // (blocks that stop early leave the loop in front of its last barrier)
+  const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+  store_rows(&KVs[0][0][0] + wid * 32 * kRow, oacc, inv, left, [&](int r) -> uint16_t* {
+    const int32_t tr = row0 + 32 * wid + r;
+    return tr < s.T ? O + (head * s.T + tr) * kHeadDim : nullptr;
+  });
 }
 
 template <bool FLAT>
@@ -543,7 +536,7 @@ void launch_lists(const Shape& s, sea_dtype dt, const void* Q, const void* K, co
   // (rows the tiles leave are marked in O and read Q afterwards: not where O lies in the place of Q)
   const uintptr_t at_o = reinterpret_cast<uintptr_t>(o), at_q = reinterpret_cast<uintptr_t>(q), bytes = static_cast<uintptr_t>(nrows) * kHeadDim * 2;
   const bool apart = at_o >= at_q + bytes || at_q >= at_o + bytes;
-  if (apart && tiles_worth_a_launch(s, tiles, longest)) {
+  if (apart && !starts_odd(k) && !starts_odd(v) && tiles_worth_a_launch(s, tiles, longest)) {
     hipLaunchKernelGGL(list_tile_kernel<FLAT>, dim3(static_cast<uint32_t>(tiles)), dim3(256), 0, st, s, q, k, v, idx, cnt, L,
                        crow, o, group_heads_for(s.N, s.T));
     hipLaunchKernelGGL(list_rest_kernel<FLAT>, row_grid((nrows + kRestRows - 1) / kRestRows), block, 0, st, s, q, k, v, idx,

@@ -138,6 +138,50 @@ __device__ __forceinline__ uint32_t dealt_in_turn(uint32_t block, uint32_t grid,
 // heads whose keys and values (2 x U x 128 B each) share the L2s at one time
 int32_t group_heads_for(int32_t N, int64_t U);
 
+// A lane's half of its row of a result (O^T accumulators times inv), 8 bytes at a time
+__device__ __forceinline__ void store_row(uint16_t* row, const floatx16 (&oacc)[2], float inv) {
+  const int g = (threadIdx.x >> 5) & 1;
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      // regs 4 q4 .. 4 q4 + 3 <-> d = 32 mt + 8 q4 + 4 g + 0..3
+      const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
+      const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
+      const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
+      *reinterpret_cast<bf16x4*>(row + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
+    }
+}
+
+// The 32 rows of a wave's result (O^T accumulators times inv, a row's factor) to memory as whole lines: through the
+// wave's 4 KB of LDS at `place`, piece p of row r at slot p ^ (r & 7), then eight lanes of 16 bytes per row.  dest(r) is
+// row r's place in memory, or nullptr; rows of the mask `marked` are written as all ones.  (With store_row, whose
+// instructions each touch 32 lines, us per attention stage: c5 42 against 39.4, c2 44.4 / 43.9.)
+template <typename F>
+__device__ __forceinline__ void store_rows(uint16_t* place, const floatx16 (&oacc)[2], float inv, uint32_t marked, F&& dest) {
+  const int lane = threadIdx.x & 63, ql = lane & 31, g = lane >> 5, row = lane >> 3, part = lane & 7;
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      // regs 4 q4 .. 4 q4 + 3 <-> d = 32 mt + 8 q4 + 4 g + 0..3
+      const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
+      const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
+      const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
+      *reinterpret_cast<bf16x4*>(place + ql * kHeadDim + 8 * ((4 * mt + q4) ^ (ql & 7)) + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
+    }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = 8 * j + row;
+    uint4 v = *reinterpret_cast<const uint4*>(place + r * kHeadDim + 8 * (part ^ row));
+    if ((marked >> r) & 1u) v = make_uint4(~0u, ~0u, ~0u, ~0u);
+    uint16_t* const at = dest(r);
+    if (at) *reinterpret_cast<uint4*>(at + 8 * part) = v;
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Partial result of a set of waves (O^T accumulators, row sum, reference maximum or -inf) in LDS, LANES lanes a
 // set, and its log-sum-exp merge into the registers of the set that goes on.
 constexpr int kPartFloats = 34;

@@ -91,7 +91,8 @@ constexpr int kRow = kHeadDim;
 // bits).  MODE 2: "bucket" form for k^ = 1 -- every row selected exactly one column, rows are
 // grouped by that column, and a block takes 128 rows of one bucket against the r keys of its
 // column, so every visited tile is fully used no matter how scattered the choices are.
-template <int RLOG, int MODE, int RW = 4, int NS = 1, int SC = 2>
+// ODD: K or V starts between two 4-byte words.
+template <int RLOG, int MODE, int RW = 4, int NS = 1, int SC = 2, bool ODD = false>
 __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_kernel(TileArgs a) {
   // RW = waves side by side: 32 RW query rows share every staged key step (8 instead of 4 halve the bytes a
   // head's keys and values travel from the L2s to LDS; two blocks per CU).
@@ -168,6 +169,9 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   auto slot_off = [&](int32_t step, int32_t slot) {
     return static_cast<uint32_t>(pos_of(min(ubase + step * kStep + slot, a.U - 1), a.rlog, a.w)) * row_bytes;
   };
+  auto load = [](u32x4 r, uint16_t* at, uint32_t off) __attribute__((always_inline)) {
+    if constexpr (ODD) buffer_load_lds16_odd(r, at, off); else buffer_load_lds16(r, at, off);
+  };
   auto fetch = [&](int32_t step, int place) __attribute__((always_inline)) {
     if (!linear) {
       offa = slot_off(step, srow);
@@ -175,10 +179,10 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
     }
     uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
     const uint32_t oa = min(offa, off_max), ob = min(offb, off_max);
-    buffer_load_lds16(Kres, at, oa + kpart);
-    if (kTwo) buffer_load_lds16(Kres, at + kThreads / 8 * kRow, ob + kpart);
-    buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
-    if (kTwo) buffer_load_lds16(Vres, at + (kStep + kThreads / 8) * kRow, ob + vpart);
+    load(Kres, at, oa + kpart);
+    if (kTwo) load(Kres, at + kThreads / 8 * kRow, ob + kpart);
+    load(Vres, at + kStep * kRow, oa + vpart);
+    if (kTwo) load(Vres, at + (kStep + kThreads / 8) * kRow, ob + vpart);
     offa += off_step;
     offb += off_step;
   };
@@ -439,28 +443,28 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
     if (set > 0) return;
   }
   l_run = half_sum(l_run);
-  if (t >= 0 && t < a.T) {
-    const float inv = (row_active && l_run > 0.f) ? 1.f / l_run : 0.f;
-    uint16_t* Or = a.O + (head * a.T + t) * kHeadDim;
-    if (BUCKET && a.part_o) {
-      const int64_t e = (head * a.T + t) * a.slots + eslot;
-      Or = a.part_o + e * kHeadDim;
-      if (g == 0) {
-        a.part_ml[2 * e] = m_thr > 0.f ? m_ref : -INFINITY;
-        a.part_ml[2 * e + 1] = row_active ? l_run : 0.f;
-      }
-    }
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        // regs 4 q4 .. 4 q4 + 3 <-> d = 32 mt + 8 q4 + 4 g + 0..3
-        const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
-        const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
-        const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
-        *reinterpret_cast<bf16x4*>(Or + 32 * mt + 8 * q4 + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
-      }
+  const float inv = (row_active && l_run > 0.f) ? 1.f / l_run : 0.f;
+  if (BUCKET && a.part_o && t >= 0 && g == 0) {
+    const int64_t e = (head * a.T + t) * a.slots + eslot;
+    a.part_ml[2 * e] = m_thr > 0.f ? m_ref : -INFINITY;
+    a.part_ml[2 * e + 1] = row_active ? l_run : 0.f;
   }
+  // (behind the partial results of other waves, where there are such)
+  constexpr int kPartBytes = NS > 1 ? NS / 2 * 64 * RW * kPartFloats * 4 : 0;
+  static_assert(kPartBytes + RW * 32 * kRow * 2 <= static_cast<int>(sizeof(KVs)), "rows on their way out fit the keys' and values' place");
+  if constexpr (RW == 2) {
+    // (64-row blocks are for the smallest launches, which wait for the trip through LDS: 7.5 against 7.1 us)
+    if (t < a.T) store_row(a.O + (head * a.T + t) * kHeadDim, oacc, inv);
+    return;
+  }
+  store_rows(&KVs[0][0][0] + kPartBytes / 2 + wid * 32 * kRow, oacc, inv, 0u, [&](int r) -> uint16_t* {
+    if (BUCKET) {
+      const int32_t tr = __shfl(t, r, kWave), slot = __shfl(eslot, r, kWave);
+      if (tr < 0) return nullptr;
+      return a.part_o ? a.part_o + ((head * a.T + tr) * a.slots + slot) * kHeadDim : a.O + (head * a.T + tr) * kHeadDim;
+    }
+    return q0 + r < a.T ? a.O + (head * a.T + q0 + r) * kHeadDim : nullptr;
+  });
 }
 
 // ---- few columns per row: group the rows of a head by the columns each selected (Sec. 3.1, App. A.5.3:
@@ -759,29 +763,12 @@ __global__ __launch_bounds__(256, 4) void bucket_attn_kernel(TileArgs a) {
       lds_loads_done();
       take_rows();
     }
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        // regs 4 q4 .. 4 q4 + 3 <-> d = 32 mt + 8 q4 + 4 g + 0..3
-        const floatx2 f01 = {oacc[mt][4 * q4] * inv, oacc[mt][4 * q4 + 1] * inv};
-        const floatx2 f23 = {oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv};
-        const bf16x2 h01 = __builtin_convertvector(f01, bf16x2), h23 = __builtin_convertvector(f23, bf16x2);
-        *reinterpret_cast<bf16x4*>(place + ql * kRow + 8 * ((4 * mt + q4) ^ (ql & 7)) + 4 * g) = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
-      }
-    __builtin_amdgcn_wave_barrier();
-    uint4 out[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) out[j] = *reinterpret_cast<const uint4*>(place + (8 * j + mrow) * kRow + 8 * (mpart ^ mrow));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int32_t e = __shfl(entry[i], 8 * j + mrow, kWave);
-      if (e < 0) continue;
+    store_rows(place, oacc, inv, 0u, [&](int rr) -> uint16_t* {
+      const int32_t e = __shfl(entry[i], rr, kWave);
+      if (e < 0) return nullptr;
       const int64_t row = head * a.T + (e & 0xffffff);
-      uint16_t* const Or = a.part_o ? a.part_o + (row * a.slots + (e >> 24)) * kHeadDim : a.O + row * kHeadDim;
-      *reinterpret_cast<uint4*>(Or + 8 * mpart) = out[j];
-    }
-    __builtin_amdgcn_wave_barrier();
+      return a.part_o ? a.part_o + (row * a.slots + (e >> 24)) * kHeadDim : a.O + row * kHeadDim;
+    });
   }
 }
 
@@ -881,11 +868,14 @@ static WaveSplit wave_split(const Shape& s, int32_t U, bool key_bits) {
   return kOne;
 }
 
-template <int RLOG, int MODE, int RW, int NS, int SC>
+template <int RLOG, int MODE, int RW, int NS, int SC, bool ODD = false>
 static void launch_tile(const Shape& s, const TileArgs& a, hipStream_t st) {
+  if constexpr (!ODD) {  // (keys or values that start between two words: one split of the waves for all)
+    if (starts_odd(a.K) || starts_odd(a.V)) return launch_tile<RLOG, MODE, 4, 1, 2, true>(s, a, st);
+  }
   constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS;  // (mask words arrive kThreads at a time)
   const size_t shm = MODE == 0 ? static_cast<size_t>((kRows * a.KW + kThreads - 1) / kThreads * kThreads) * sizeof(uint32_t) : 0;
-  hipLaunchKernelGGL((tile_attn_kernel<RLOG, MODE, RW, NS, SC>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
+  hipLaunchKernelGGL((tile_attn_kernel<RLOG, MODE, RW, NS, SC, ODD>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
                      dim3(64 * RW * NS), shm, st, a);
 }
 
@@ -1002,10 +992,14 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
       a.part_ml = reinterpret_cast<float*>(base + lay.part_ml);
     }
     const int32_t max_chunks = lay.max_chunks;
-    if (rlog <= 6)
+    const dim3 chunks(static_cast<uint32_t>(s.N) * max_chunks);
+    const bool odd = starts_odd(K) || starts_odd(V);
+    if (rlog <= 6 && !odd && !starts_odd(Q))
       hipLaunchKernelGGL(bucket_attn_kernel<4>, dim3(static_cast<uint32_t>(s.N) * ((max_chunks + 3) / 4)), dim3(256), 0, st, a);
+    else if (odd)
+      hipLaunchKernelGGL((tile_attn_kernel<0, 2, 4, 1, 2, true>), chunks, dim3(256), 0, st, a);
     else
-      hipLaunchKernelGGL((tile_attn_kernel<0, 2>), dim3(static_cast<uint32_t>(s.N) * max_chunks), dim3(256), 0, st, a);
+      hipLaunchKernelGGL((tile_attn_kernel<0, 2>), chunks, dim3(256), 0, st, a);
     if (multi) {
       const int64_t rows = static_cast<int64_t>(s.N) * s.T;
       hipLaunchKernelGGL(bucket_merge_kernel, dim3(static_cast<uint32_t>((rows * 8 + 255) / 256)), dim3(256), 0, st,

@@ -1,0 +1,79 @@
+"""Tensors that start anywhere in memory: at whole 4-byte words and, for bf16, between two of them, where some stages
+take another kernel.  Same results as with tensors at the start of an allocation."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2310_01777_amd import synth
+from tests.util import TOL, assert_close, to_np64
+
+pytestmark = pytest.mark.gpu
+
+# dtype, B, H, T, m, K, k_hat, k_budget, causal, geometry
+LAYERS = [
+    ("bf16", 1, 3, 512, 64, 64, 16, 0, True, 0),    # columns of a power of two of keys
+    ("bf16", 1, 2, 512, 256, 256, 32, 0, False, 0),
+    ("bf16", 1, 2, 4096, 64, 64, 1, 16, False, 0),  # one column a row: buckets
+    ("bf16", 1, 2, 601, 64, 100, 60, 0, True, 0),   # columns of any width, tiles
+    ("bf16", 1, 2, 700, 64, 64, 16, 0, True, 1),    # per-row widths
+    ("f32", 1, 2, 512, 64, 64, 16, 0, True, 0),
+]
+
+
+def _shifted(t, by):
+    """A copy of t that starts `by` elements into its allocation."""
+    at = torch.empty(t.numel() + by, dtype=t.dtype, device="cuda")[by:].view(t.shape)
+    return at.copy_(t)
+
+
+@pytest.mark.parametrize("by", [1, 2])
+@pytest.mark.parametrize("case", LAYERS, ids=lambda c: "_".join(str(v) for v in c))
+def test_layers(case, by):
+    from paper_2310_01777_amd import binding as sea
+    dtype, B, H, T, m, K, kh, kb, causal, geometry = case
+    wl = synth.Workload("anywhere", B, H, T, 64, m, K, kh, kb, causal, dtype, 4)
+    d = {k: v.cuda() for k, v in synth.make_inputs(wl).items() if v is not None}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=m, K=K, k_hat=kh, k_budget=kb, causal=causal, scale=wl.scale, dtype=dtype,
+                      geometry=geometry)
+    ws, O = sea.alloc_workspace(p), torch.empty_like(d["Q"])
+    print(f"[case] tensors {by} elements in {case}", flush=True)
+    sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], O, workspace=ws)
+    s = {k: _shifted(d[k], by) for k in "QKVW"}
+    O_s = _shifted(torch.empty_like(O), by)
+    sea.sea_forward(p, s["Q"], s["K"], s["V"], s["W"], O_s, workspace=ws)
+    # (weights of 8 or 24 significant bits: two outputs within the tolerance of the definition each)
+    assert_close(to_np64(O_s), to_np64(O), TOL[dtype], "O of tensors elsewhere")
+
+
+@pytest.mark.parametrize("by", [1, 2])
+def test_dense(by):
+    from paper_2310_01777_amd import binding as sea
+    wl = synth.Workload("anywhere", 1, 2, 300, 64, 32, 10, 4, 0, True, "bf16", 4)
+    d = {k: v.cuda() for k, v in synth.make_inputs(wl).items() if v is not None}
+    p = sea.SeaParams(B=1, H=2, T=300, d=64, m=32, K=10, k_hat=4, causal=True, scale=wl.scale, dtype="bf16")
+    O = torch.empty_like(d["Q"])
+    print(f"[case] dense, tensors {by} elements in", flush=True)
+    sea.sea_dense_attn(p, d["Q"], d["K"], d["V"], O)
+    s = {k: _shifted(d[k], by) for k in "QKV"}
+    O_s = _shifted(torch.empty_like(O), by)
+    sea.sea_dense_attn(p, s["Q"], s["K"], s["V"], O_s)
+    assert torch.equal(O, O_s)
+
+
+@pytest.mark.parametrize("by", [1, 2])
+def test_lists(by):
+    from paper_2310_01777_amd import binding as sea
+    H, T, L = 30, 1100, 600
+    wl = synth.Workload("anywhere", 1, H, T, 64, 32, 16, 4, 0, True, "bf16", 4)
+    d = {k: v.cuda() for k, v in synth.make_inputs(wl).items() if v is not None}
+    p = sea.SeaParams(B=1, H=H, T=T, d=64, m=32, K=16, k_hat=4, causal=True, scale=wl.scale, dtype="bf16")
+    cnt = torch.arange(1, T + 1, dtype=torch.int32).clamp(max=L).expand(1, H, T).contiguous().cuda()
+    idx = torch.from_numpy(np.maximum(np.arange(T)[:, None] - np.minimum(np.arange(T)[:, None], L - 1) + np.arange(L), 0).astype(np.int32))
+    idx = idx.clamp(max=T - 1).expand(1, H, T, L).contiguous().cuda()
+    O = torch.empty_like(d["Q"])
+    print(f"[case] lists, tensors {by} elements in", flush=True)
+    sea.sea_sparse_attn(p, d["Q"], d["K"], d["V"], idx, cnt, L, O)
+    s = {k: _shifted(d[k], by) for k in "QKV"}
+    O_s = _shifted(torch.empty_like(O), by)
+    sea.sea_sparse_attn(p, s["Q"], s["K"], s["V"], _shifted(idx, by), cnt, L, O_s)
+    assert_close(to_np64(O_s), to_np64(O), TOL["bf16"], "O of tensors elsewhere")
