@@ -233,8 +233,17 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
   const int rt = wid >> 2, cq = wid & 3;
   const int lr = lane & 15, lg = lane >> 4;
   const uint32_t tiles = (s.T + 31) / 32;
-  const int64_t head = blockIdx.x / tiles;
-  const int32_t r0 = static_cast<int32_t>(blockIdx.x % tiles) * 32 + 16 * rt;  // (may lie past T: the wave then only joins the barriers)
+  // Causal rows need columns up to their own, so the blocks of a head's last rows take longest.  A launch of one to two
+  // blocks per CU is resident at once and dealt to the 256 CUs in turn: those that get one block take the longest
+  // ones, and the others one of the next with one of the shortest (head by head, both blocks of a CU had the same
+  // rows of two heads: 12 heads of 1024 rows 24.9 -> 20.0 us).  Other launches: longest first.
+  uint32_t rank = blockIdx.x;
+  if (gridDim.x > 256u && gridDim.x <= 512u) {
+    const uint32_t pairs = gridDim.x - 256u;
+    rank = rank >= 256u ? gridDim.x - 1u - (rank - 256u) : (rank < pairs ? 256u - pairs + rank : rank - pairs);
+  }
+  const int64_t head = rank % static_cast<uint32_t>(s.N);
+  const int32_t r0 = static_cast<int32_t>(tiles - 1u - rank / static_cast<uint32_t>(s.N)) * 32 + 16 * rt;  // (may lie past T: the wave then only joins the barriers)
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
   // uniform bases and 32-bit lane offsets (a head's m K state and the 16 rows' m values index with 32 bits)
