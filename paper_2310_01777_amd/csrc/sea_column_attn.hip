@@ -269,13 +269,13 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
       if (__ballot(ymax > m_thr) != 0ull) {
         ymax = half_max(ymax);
         const bool refresh = ymax > m_thr;
-        const float delta = refresh ? ymax + kRefRise : 0.f;
+        const float delta = refresh ? ymax : 0.f;
         const float corr = (refresh && m_thr > 0.f) ? __builtin_amdgcn_exp2f(-delta) : 1.f;
         l_run *= corr;
 #pragma unroll
         for (int i = 0; i < 16; ++i) { oacc[0][i] *= corr; oacc[1][i] *= corr; }
         m_ref += delta;
-        m_thr = refresh ? kRefSlack : m_thr;
+        m_thr = refresh ? kRefSlackFine : m_thr;
 #pragma unroll
         for (int i = 0; i < 16; ++i) y[i] -= delta;
       }
