@@ -11,7 +11,7 @@
 // bit tests per register would cost more than the softmax.  The mask goes through the matrix
 // product instead: the contraction is extended by NX slots, one per column of the 32-key sub-chunk.
 // On the key side slot x holds the lowest bf16 value, -(1 - 2^-8) 2^128, for the keys of the sub-chunk's
-// x-th column (one-hot, parked in the padding of the staged K rows, the same for every row and head); on
+// x-th column (one-hot, staged beside the keys, the same for every row and head); on
 // the query side it holds 2 where the row did NOT select that column and 0 where it did.  One more
 // 32x32x16 product then takes every finite unselected score below -(1 - 2^-6) 2^128 and adds exact zeros to
 // the others.  Building the query side takes nine vector instructions per sub-chunk from the row's mask
@@ -27,7 +27,7 @@
 //
 // Bound: issue (about 200 vector instructions and 17 matrix products per 32-key sub-chunk and wave).  The keys and
 // values of a step go straight to LDS, which leaves registers for four waves per SIMD (three before).  On the layer
-// B = 8, H = 32, T = 2000 (padded by 0-25 %), K = 256, k^ = 64 the kernel takes 0.25 ms (0.29 ms with three waves per
+// B = 8, H = 32, T = 2000 (padded by 0-25 %), K = 256, k^ = 64 the kernel takes 0.26 ms (0.29 ms with three waves per
 // SIMD and rows that pass through registers); the per-row gather kernel takes 2.71 ms and its key lists another
 // 0.57 ms to write.  Small launches take as long as their longest list: there three or six sets of waves share it.
 #include "sea_columns.h"

@@ -1085,8 +1085,8 @@ __device__ __forceinline__ float rows_sum_f(float x) {
 // ANYW: columns of any width, any number of keys per column (otherwise both as in the bf16 kernel).  These
 // layers also have a per-row form, in which a key that is not selected is not read: a row whose result is not
 // finite may have met such a key (a value that is not finite against a weight of zero) and is computed again
-// from its own keys.
-template <bool ANYW>
+// from its own keys.  WIDE: columns of 2^24 keys and more.
+template <bool ANYW, bool WIDE = false>
 __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   __shared__ float m_s[4][16], l_s[4][16];
   __shared__ float o_s[4][kHeadDim][17];  // [wave][dim][query], padded
@@ -1152,7 +1152,8 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
       return entry_pos(a.g, *col, u - *col * a.g.r);
     }
     *col = u >> a.rlog;
-    // pos_of(u, rlog, w) in two products at the full rate: columns, keys of a column and w lie below 2^24
+    if (WIDE) return pos_of(u, a.rlog, a.w);
+    // the same in two products at the full rate: columns, keys of a column and w lie below 2^24
     return static_cast<int32_t>(__umul24(*col, a.w) + (__umul24(u & ((1 << a.rlog) - 1), a.w) >> a.rlog));
   };
   const int32_t nchunks = (u_end + 15) / 16;
@@ -1320,7 +1321,7 @@ namespace {
 bool tile_attn_f32_pow2(const Shape& s, int32_t* rlog_out) {
   if (s.geometry != 0 || s.T % s.K != 0) return false;
   const int32_t w = s.T / s.K, r = w < s.rep_cap ? w : s.rep_cap;
-  if (r <= 0 || (r & (r - 1)) != 0 || w >= 1 << 24 || static_cast<int64_t>(w) * r > (int64_t(1) << 30)) return false;
+  if (r <= 0 || (r & (r - 1)) != 0 || static_cast<int64_t>(w) * r > (int64_t(1) << 30)) return false;
   int32_t rlog = 0;
   while ((1 << rlog) < r) ++rlog;
   *rlog_out = rlog;
@@ -1351,7 +1352,8 @@ hipError_t launch_tile_attn_f32(const Shape& s, const float* Q, const float* K, 
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 15) / 16));
   if (pow2) {
     a.rlog = rlog; a.w = s.T / s.K; a.U = s.K << rlog;
-    hipLaunchKernelGGL(tile_attn_f32_kernel<false>, grid, dim3(256), 0, st, a);
+    if (a.w < 1 << 24) hipLaunchKernelGGL(tile_attn_f32_kernel<false>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((tile_attn_f32_kernel<false, true>), grid, dim3(256), 0, st, a);
   } else {
     a.g = column_list(s); a.U = a.g.U;
     hipLaunchKernelGGL(tile_attn_f32_kernel<true>, grid, dim3(256), 0, st, a);

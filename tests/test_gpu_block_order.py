@@ -1,0 +1,56 @@
+"""Launches whose blocks are all resident deal their row tiles to the CUs in another order than shorter and longer
+ones: a head computed among many has to come out as it does alone.  Column buckets of 1, 2 and 4 keys."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2310_01777_amd import synth
+from util import TOL
+
+pytestmark = pytest.mark.gpu
+
+
+# (dtype, heads, T, K): 296 tiles of 128 rows; 352 contraction and 693 attention tiles; 259 tiles of ragged columns
+@pytest.mark.parametrize("dtype,H,T,K", [("bf16", 37, 1024, 64), ("f32", 11, 1000, 40), ("f32", 11, 1024, 128),
+                                         ("bf16", 37, 999, 60)])
+def test_a_head_among_many(dtype, H, T, K):
+    from paper_2310_01777_amd import binding as sea
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(T + H)
+    q, k, v = (torch.randn(1, H, T, 64, generator=g, device="cuda").to(td) for _ in range(3))
+    W = synth.gaussian_orthogonal(64, 64, 3).to(td).cuda()
+
+    def layer(q, k, v):
+        p = sea.SeaParams(B=1, H=q.shape[1], T=T, d=64, m=64, K=K, k_hat=K // 4, causal=True, scale=0.125, dtype=dtype)
+        O = torch.full_like(q, float("nan"))
+        sea.sea_forward(p, q, k, v, W, O, workspace=sea.alloc_workspace(p))
+        return O
+
+    print(f"[case] block order {(dtype, H, T, K)}", flush=True)
+    many = layer(q, k, v)
+    for h in (0, 1, H // 2, H - 1):
+        alone = layer(*(x[:, h:h + 1].contiguous() for x in (q, k, v)))
+        # the same products, perhaps merged from other parts: each within the contract's tolerance
+        assert float((many[:, h] - alone[:, 0]).abs().max()) <= 2 * TOL[dtype] * float(alone.abs().max())
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("r,T", [(1, 1024), (2, 1024), (4, 2048)])
+def test_buckets_of_few_keys(r, T, causal):
+    import oracle
+    from paper_2310_01777_amd import binding as sea
+    from util import assert_close, oracle_params, to_np64
+    K = 512
+    g = torch.Generator().manual_seed(T + r)
+    q, k, v = (torch.randn(1, 2, T, 64, generator=g).bfloat16() for _ in range(3))
+    W = synth.gaussian_orthogonal(64, 64, 3).bfloat16()
+    p = sea.SeaParams(B=1, H=2, T=T, d=64, m=64, K=K, k_hat=1, k_budget=r, causal=causal, scale=0.125, dtype="bf16")
+    O = torch.empty_like(q).cuda()
+    print(f"[case] buckets of few keys {(r, T, causal)}", flush=True)
+    args = (p, q.cuda(), k.cuda(), v.cuda(), W.cuda())
+    sea.sea_forward(*args, O, workspace=sea.alloc_workspace(p))
+    idx, cnt = (torch.full(s, -1, dtype=torch.int32, device="cuda") for s in ((1, 2, T, r), (1, 2, T)))
+    sea.sea_forward(*args, torch.empty_like(O), idx=idx, cnt=cnt, workspace=sea.alloc_workspace(p))
+    want = oracle.sparse_attn(oracle_params(p), to_np64(q), to_np64(k), to_np64(v), idx.cpu().numpy(), cnt.cpu().numpy())
+    assert np.isfinite(want).all()
+    assert_close(to_np64(O), want, TOL["bf16"], "O")
