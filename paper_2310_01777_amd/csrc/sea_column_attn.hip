@@ -99,7 +99,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
   // first rows lie in the step's sub-chunk wall / 4, its second ones in sub-chunk (wall + kWaves) / 4.  The rows go
   // straight to LDS.  Rows past the list or past the sequence re-read its last row; their scores are masked.
   const int srow = tid >> 3, spart = tid & 7;
-  const uint32_t kpart = 16 * (spart ^ (srow & 7)), vpart = 16 * (spart ^ (((srow >> 1) & 1) << 2));
+  const uint32_t kpart = 16 * (spart ^ ((srow >> 1) & 7)), vpart = 16 * (spart ^ (((srow >> 1) & 1) << 2));
   uint32_t x0[NX == 32 ? 2 : 1], x1[NX == 32 ? 2 : 1];  // this thread's words of the two rows' one-hot slots
   const uint32_t row_bytes = kHeadDim * 2, head_bytes = static_cast<uint32_t>(a.T) * row_bytes;
   const uint16_t* Kh = a.K + head * static_cast<int64_t>(a.T) * kHeadDim;
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
   // this lane's pieces of a K row: slots 2 kc + g of row ql
   int kat[4];
 #pragma unroll
-  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ (ql & 7));
+  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ ((ql >> 1) & 7));
 
   floatx16 oacc[2];
 #pragma unroll

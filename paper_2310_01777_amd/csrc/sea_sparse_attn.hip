@@ -272,10 +272,10 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
   const u32x4 Kres = buffer_words(K + head * static_cast<int64_t>(s.T) * kHeadDim, head_bytes);
   const u32x4 Vres = buffer_words(V + head * static_cast<int64_t>(s.T) * kHeadDim, head_bytes);
   const int srow = tid >> 3;
-  const uint32_t kpart = 16 * ((tid & 7) ^ (srow & 7)), vpart = 16 * ((tid & 7) ^ (((srow >> 1) & 1) << 2));
+  const uint32_t kpart = 16 * ((tid & 7) ^ ((srow >> 1) & 7)), vpart = 16 * ((tid & 7) ^ (((srow >> 1) & 1) << 2));
   int kat[4];  // this lane's pieces of a K row: slots 2 kc + g of row ql
 #pragma unroll
-  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ (ql & 7));
+  for (int kc = 0; kc < 4; ++kc) kat[kc] = ql * kRow + 8 * ((2 * kc + g) ^ ((ql >> 1) & 7));
 
   floatx16 oacc[2];
 #pragma unroll
