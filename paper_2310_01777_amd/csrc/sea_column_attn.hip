@@ -275,7 +275,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
 #pragma unroll
         for (int i = 0; i < 16; ++i) { oacc[0][i] *= corr; oacc[1][i] *= corr; }
         m_ref += delta;
-        m_thr = refresh ? kRefSlackFine : m_thr;
+        m_thr = refresh ? kRefSlack : m_thr;
 #pragma unroll
         for (int i = 0; i < 16; ++i) y[i] -= delta;
       }

@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
 #pragma unroll
           for (int i = 0; i < 16; ++i) { oacc[0][i] *= corr; oacc[1][i] *= corr; }
           m_ref += delta;
-          m_thr = refresh ? kRefSlackFine : m_thr;
+          m_thr = refresh ? kRefSlack : m_thr;
 #pragma unroll
           for (int i = 0; i < 16; ++i) y[i] -= delta;
         }

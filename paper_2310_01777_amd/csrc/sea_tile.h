@@ -49,16 +49,15 @@ __device__ __forceinline__ float max_of(const float (&y)[16]) {
   return max3(a, b, b);
 }
 
-// Running reference of a streaming softmax, log2 units.  Any reference gives the same weights up to a factor that
-// the row sum takes out again, so it only has to keep sums and products in range.
-// Weights rounded to bf16: a row's first reference, and every later one, lies kRefRise above the largest score met
-// so far, and stays until a score exceeds it by kRefSlack: rows whose largest scores lie up to 48 above those of
-// their first keys never rescale their accumulators.  Weights reach 2^16 (sums of 2^24 of them times values of 2^87
-// stay finite) and start at 2^-32, so those lost to underflow lie 2^-94 below the largest.
-// Weights kept to 24 bits: the reference is the largest score met when it was last moved, and stays until a score
-// exceeds it by kRefSlackFine.  The argument of exp2 is rounded to its own last bit, so the weights that count
-// have to have small arguments: 32 above them cost 1.3 bits of the result (rms 2^-21.8 -> 2^-20.4 of the row).
-constexpr float kRefRise = 32.f, kRefSlack = 16.f, kRefSlackFine = 8.f;
+// Running reference of a streaming softmax, log2 units: the largest score met when it was last moved.  It stays until a
+// score exceeds it by kRefSlack.  Any reference gives the same weights up to a factor that the row sum takes out again,
+// so it only has to keep sums and products in range: a row's largest weight lies between 1 and 2^8, so values down to
+// the smallest normal number keep their bits in its products, and sums of 2^14 such weights times values of 2^104 stay
+// finite.  References 32 above the scores, moved after a rise of 48, save half of the rescalings (c4 at T = 32768 and c2
+// 2 % faster) but cost 2^32 of that range below and 2^8 above.  The argument of exp2 is rounded to its own last bit, so
+// where weights keep 24 bits the ones that count have to have small arguments anyway (rms error of a row 2^-21.8 against
+// 2^-20.4).
+constexpr float kRefSlack = 8.f;
 
 // O^T += V^T P^T for one 32-key sub-chunk with weights p = 2^y held in fp32: a weight enters the bf16 product
 // as the sum of three bf16 values, its rounded value, the rounded remainder and what then remains.  Eight

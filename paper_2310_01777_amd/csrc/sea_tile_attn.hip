@@ -378,14 +378,13 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
       if (!STREAM) request_v();
       float ymax = max_of(y);
       // The reference only has to keep the exponentials in range: it is moved (and the accumulators
-      // rescaled) when some row's maximum exceeds it by more than kRefSlack, or when the row has none yet,
-      // and then goes kRefRise past that maximum (sea_tile.h).
+      // rescaled) when some row's maximum exceeds it by more than kRefSlack, or when the row has none yet.
       if (__ballot(ymax > m_thr) != 0ull) {
         // rows that did not ask keep their reference (factor exactly 1): a row's arithmetic
         // never depends on the other rows of its wave
         ymax = half_max(ymax);
         const bool refresh = ymax > m_thr;
-        const float delta = refresh ? ymax + kRefRise : 0.f;
+        const float delta = refresh ? ymax : 0.f;
         const float corr = (refresh && m_thr > 0.f) ? __builtin_amdgcn_exp2f(-delta) : 1.f;
         l_run *= corr;
 #pragma unroll
