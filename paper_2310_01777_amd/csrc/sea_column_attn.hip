@@ -63,8 +63,9 @@ struct ColumnArgs {
 // most 8 columns), 16 (3 or 4 keys) or 32 (1 or 2 keys).
 // RW waves side by side take 32 rows each; NS sets of them share the rows, each with every NS-th SC sub-chunks of
 // the list (see the launch).
-template <int NX, int RW, int NS, int SC>
-__global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_kernel(ColumnArgs a) {
+// ODD: K or V starts between two 4-byte words, so a step's pieces wait in registers (three waves per SIMD).
+template <int NX, int RW, int NS, int SC, bool ODD = false>
+__global__ __launch_bounds__(64 * RW * NS, NS == 1 && !ODD ? 4 : 3) void column_attn_kernel(ColumnArgs a) {
   constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS, kWaves = RW * NS;
   constexpr int kStep = 32 * SC * NS;  // keys per step
   static_assert(8 * kStep == 2 * kThreads, "two K and V pieces per thread and step");
@@ -135,6 +136,16 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
     return static_cast<uint32_t>(max(min(pos, len - 1), 0)) * row_bytes;
   };
   int32_t cs0 = 0, cs1 = 0, cs2 = 0;  // first columns of the fetched step's sub-chunks and of the one after
+  u32x4 odd[4];
+  auto park = [&](int place) __attribute__((always_inline)) {
+    if constexpr (ODD) {
+      uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
+      park16(at, odd[0]);
+      park16(at + 8 * kWaves * kRow, odd[1]);
+      park16(at + kStep * kRow, odd[2]);
+      park16(at + (kStep + 8 * kWaves) * kRow, odd[3]);
+    }
+  };
   auto fetch = [&](int place) __attribute__((always_inline)) {
     cs0 = scol;
     if (NS == 1) {
@@ -160,11 +171,18 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
     advance_half(ccol, crem);
     if (NS > 1) advance_by(tcol0, trem0, a.qs, a.rs);
     if (NS > 1) advance_by(tcol1, trem1, a.qs, a.rs);
-    uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
-    buffer_load_lds16(Kres, at, oa + kpart);
-    buffer_load_lds16(Kres, at + 8 * kWaves * kRow, ob + kpart);
-    buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
-    buffer_load_lds16(Vres, at + (kStep + 8 * kWaves) * kRow, ob + vpart);
+    if constexpr (ODD) {
+      odd[0] = load16_odd(Kres, oa + kpart);
+      odd[1] = load16_odd(Kres, ob + kpart);
+      odd[2] = load16_odd(Vres, oa + vpart);
+      odd[3] = load16_odd(Vres, ob + vpart);
+    } else {
+      uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
+      buffer_load_lds16(Kres, at, oa + kpart);
+      buffer_load_lds16(Kres, at + 8 * kWaves * kRow, ob + kpart);
+      buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
+      buffer_load_lds16(Vres, at + (kStep + 8 * kWaves) * kRow, ob + vpart);
+    }
     if (NX >= 16 || spart < NX / 2) {
 #pragma unroll
       for (int e = 0; e < (NX == 32 ? 2 : 1); ++e) {
@@ -207,6 +225,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
 
   const MinusOnes minus = minus_ones();
 
+  if (nsteps > 0) park(0);
   lds_loads_done();
   __syncthreads();
   // one step, its place in the double buffer known to the compiler
@@ -282,6 +301,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
       // O^T += V^T P^T, V^T fragments in the key order of the P registers
       l_run += add_weighted_rows(y, av, minus, oacc);
     }
+    if (step + 1 < nsteps) park(stage ^ 1);
     lds_loads_done();
     __syncthreads();
   };
@@ -330,12 +350,15 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 ? 4 : 3) void column_attn_ker
   });
 }
 
-template <int NX, int RW, int NS, int SC>
+template <int NX, int RW, int NS, int SC, bool ODD = false>
 void launch_column(const Shape& s, ColumnArgs a, hipStream_t st) {
+  if constexpr (!ODD) {
+    if (starts_odd(a.K) || starts_odd(a.V)) return launch_column<NX, RW, NS, SC, true>(s, a, st);
+  }
   constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS, kStep = 32 * SC * NS;  // (mask words arrive kThreads at a time)
   a.qh = kStep / 2 * a.A / a.D; a.rh = kStep / 2 * a.A % a.D;
   a.qs = kStep * a.A / a.D; a.rs = kStep * a.A % a.D;
-  hipLaunchKernelGGL((column_attn_kernel<NX, RW, NS, SC>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
+  hipLaunchKernelGGL((column_attn_kernel<NX, RW, NS, SC, ODD>), dim3(static_cast<uint32_t>(s.N) * ((s.T + kRows - 1) / kRows)),
                      dim3(64 * RW * NS), static_cast<size_t>((kRows * a.KW + kThreads - 1) / kThreads * kThreads) * sizeof(uint32_t), st, a);
 }
 
@@ -349,8 +372,7 @@ bool column_attn_supported(const Shape& s, sea_dtype dt) {
 hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
                               const uint32_t* mbits, uint16_t* O, hipStream_t st) {
   if (!column_attn_supported(s, SEA_BF16)) return hipErrorNotSupported;
-  if (starts_odd(K) || starts_odd(V) || column_gather_pays(s, SEA_BF16))
-    return launch_column_gather(s, SEA_BF16, Q, K, V, mbits, O, st);
+  if (column_gather_pays(s, SEA_BF16)) return launch_column_gather(s, SEA_BF16, Q, K, V, mbits, O, st);
   StageScope scope(SEA_STAGE_SPARSE, st);
   ColumnArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;

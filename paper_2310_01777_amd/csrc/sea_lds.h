@@ -18,8 +18,9 @@ __device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t bytes) 
   const uint64_t p = reinterpret_cast<uint64_t>(base);
   return u32x4{static_cast<uint32_t>(p), static_cast<uint32_t>(p >> 32) & 0xffffu, bytes, static_cast<uint32_t>(kBufferFlags)};
 }
-// The memory side needs whole 4-byte words; buffer_load_lds16_odd is for tensors of 2-byte elements that start between
-// two of them (their rows are whole words apart, so all loads of a tensor go the same way) and goes through registers.
+// The memory side needs whole 4-byte words.  Tensors of 2-byte elements that start between two of them (their rows are
+// whole words apart, so all loads of a tensor go the same way) pass through registers: load16_odd asks for a piece,
+// park16 puts it where buffer_load_lds16 would.
 // FRESH: the resource's words may come from vector instructions just before (read lanes), whose results a load may read
 // five wait states later.
 template <bool FRESH = false>
@@ -30,13 +31,14 @@ __device__ __forceinline__ void buffer_load_lds16(u32x4 r, uint16_t* at, uint32_
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
 }
-__device__ __forceinline__ void buffer_load_lds16_odd(u32x4 r, uint16_t* at, uint32_t byte_off) {
+__device__ __forceinline__ u32x4 load16_odd(u32x4 r, uint32_t byte_off) {
   typedef uint32_t anywhere __attribute__((ext_vector_type(4), aligned(2)));
   const auto* base = reinterpret_cast<const __attribute__((address_space(1))) char*>(r[0] | (static_cast<uint64_t>(r[1]) << 32));
-  const u32x4 v = *reinterpret_cast<const __attribute__((address_space(1))) anywhere*>(base + byte_off);
-  reinterpret_cast<u32x4*>(at)[threadIdx.x & 63] = v;
+  return *reinterpret_cast<const __attribute__((address_space(1))) anywhere*>(base + byte_off);
 }
-// the same with 4 bytes per lane: lane l writes word l
+__device__ __forceinline__ void park16(uint16_t* at, u32x4 v) { reinterpret_cast<u32x4*>(at)[threadIdx.x & 63] = v; }
+__device__ __forceinline__ void buffer_load_lds16_odd(u32x4 r, uint16_t* at, uint32_t byte_off) { park16(at, load16_odd(r, byte_off)); }
+// buffer_load_lds16 with 4 bytes per lane: lane l writes word l
 __device__ __forceinline__ void buffer_load_lds4(u32x4 r, uint32_t* at, uint32_t byte_off) {
   const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at));
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");

@@ -77,3 +77,36 @@ def test_lists(by):
     O_s = _shifted(torch.empty_like(O), by)
     sea.sea_sparse_attn(p, s["Q"], s["K"], s["V"], _shifted(idx, by), cnt, L, O_s)
     assert_close(to_np64(O_s), to_np64(O), TOL["bf16"], "O of tensors elsewhere")
+
+
+# dtype, B, H, T, m, K, k_hat, k_budget, causal, geometry: the splits of a block's waves and the slots of the mask product
+SAME_KERNEL = [
+    ("bf16", 1, 12, 601, 64, 100, 60, 0, True, 0),    # columns of any width: six sets of waves, 8 slots,
+    ("bf16", 1, 52, 601, 64, 100, 60, 0, True, 0),    # three,
+    ("bf16", 1, 52, 601, 64, 100, 60, 0, False, 0),   # one
+    ("bf16", 1, 2, 385, 64, 128, 100, 0, False, 0),   # 16 slots
+    ("bf16", 1, 70, 385, 64, 100, 90, 0, False, 0),
+    ("bf16", 2, 2, 129, 64, 128, 100, 0, True, 0),    # 32
+    ("bf16", 1, 50, 300, 64, 128, 100, 0, False, 0),
+    ("bf16", 1, 90, 300, 64, 128, 100, 0, False, 0),
+]
+
+
+@pytest.mark.parametrize("case", SAME_KERNEL, ids=lambda c: "_".join(str(v) for v in c))
+def test_same_kernel(case):
+    """Keys and values between two words take the form that the layer takes: the results are the same bit for bit."""
+    from paper_2310_01777_amd import binding as sea
+    dtype, B, H, T, m, K, kh, kb, causal, geometry = case
+    wl = synth.Workload("anywhere", B, H, T, 64, m, K, kh, kb, causal, dtype, 4)
+    d = {k: v.cuda() for k, v in synth.make_inputs(wl).items() if v is not None}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=m, K=K, k_hat=kh, k_budget=kb, causal=causal, scale=wl.scale, dtype=dtype,
+                      geometry=geometry)
+    ws, O = sea.alloc_workspace(p), torch.empty_like(d["Q"])
+    print(f"[case] same kernel {case}", flush=True)
+    sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], O, workspace=ws)
+    assert torch.isfinite(O).all()
+    for which in ("K", "V", "KV"):
+        s = {k: _shifted(v, 1) if k in which else v for k, v in d.items()}
+        O_s = torch.full_like(O, float("nan"))
+        sea.sea_forward(p, s["Q"], s["K"], s["V"], s["W"], O_s, workspace=ws)
+        assert torch.equal(O, O_s), which
