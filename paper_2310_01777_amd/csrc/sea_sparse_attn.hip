@@ -225,7 +225,8 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void list_rest_kernel(
   }
 }
 
-template <bool FLAT>
+// ODD: K or V starts between two 4-byte words, so a step's pieces wait in registers.
+template <bool FLAT, bool ODD>
 __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                            const uint16_t* __restrict__ K,
                                                            const uint16_t* __restrict__ V,
@@ -405,6 +406,7 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
     const uint32_t* uw = used[win & 1];
     // 64-key steps with a used key (uniform): lanes 0..15 look at one step each
     uint32_t steps = static_cast<uint32_t>(__ballot(lane < kWindow / 64 && (uw[2 * (lane & 15)] | uw[2 * (lane & 15) + 1]) != 0u));
+    u32x4 odd[4];
     auto fetch = [&](int step, int place) __attribute__((always_inline)) {
       // (rows of unused keys repeat the step's first used one)
       const uint32_t u0 = uw[2 * step], u1 = uw[2 * step + 1];
@@ -412,11 +414,27 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
       const uint32_t first = k0 + (u0 != 0u ? __ffs(u0) - 1 : 31 + __ffs(u1));
       const uint32_t oa = ((u0 >> srow) & 1u ? k0 + srow : first) * row_bytes;
       const uint32_t ob = ((u1 >> srow) & 1u ? k0 + 32 + srow : first) * row_bytes;
-      uint16_t* const at = &KVs[place][0][wid * 8 * kRow];
-      buffer_load_lds16(Kres, at, oa + kpart);
-      buffer_load_lds16(Kres, at + 32 * kRow, ob + kpart);
-      buffer_load_lds16(Vres, at + kChunk * kRow, oa + vpart);
-      buffer_load_lds16(Vres, at + (kChunk + 32) * kRow, ob + vpart);
+      if constexpr (ODD) {
+        odd[0] = load16_odd(Kres, oa + kpart);
+        odd[1] = load16_odd(Kres, ob + kpart);
+        odd[2] = load16_odd(Vres, oa + vpart);
+        odd[3] = load16_odd(Vres, ob + vpart);
+      } else {
+        uint16_t* const at = &KVs[place][0][wid * 8 * kRow];
+        buffer_load_lds16(Kres, at, oa + kpart);
+        buffer_load_lds16(Kres, at + 32 * kRow, ob + kpart);
+        buffer_load_lds16(Vres, at + kChunk * kRow, oa + vpart);
+        buffer_load_lds16(Vres, at + (kChunk + 32) * kRow, ob + vpart);
+      }
+    };
+    auto park = [&](int place) __attribute__((always_inline)) {
+      if constexpr (ODD) {
+        uint16_t* const at = &KVs[place][0][wid * 8 * kRow];
+        park16(at, odd[0]);
+        park16(at + 32 * kRow, odd[1]);
+        park16(at + kChunk * kRow, odd[2]);
+        park16(at + (kChunk + 32) * kRow, odd[3]);
+      }
     };
     auto walk = [&](auto place_c) __attribute__((always_inline)) {
       constexpr int place = decltype(place_c)::value;
@@ -469,11 +487,13 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         }
         l_run += add_weighted_rows(y, av, minus, oacc);
       }
+      if (steps != 0u) park(place ^ 1);
       lds_loads_done();
       __syncthreads();
     };
     if (steps != 0u) {
       fetch(__ffs(steps) - 1, 0);
+      park(0);
       lds_loads_done();
     }
     __syncthreads();
@@ -536,9 +556,10 @@ void launch_lists(const Shape& s, sea_dtype dt, const void* Q, const void* K, co
   // (rows the tiles leave are marked in O and read Q afterwards: not where O lies in the place of Q)
   const uintptr_t at_o = reinterpret_cast<uintptr_t>(o), at_q = reinterpret_cast<uintptr_t>(q), bytes = static_cast<uintptr_t>(nrows) * kHeadDim * 2;
   const bool apart = at_o >= at_q + bytes || at_q >= at_o + bytes;
-  if (apart && !starts_odd(k) && !starts_odd(v) && tiles_worth_a_launch(s, tiles, longest)) {
-    hipLaunchKernelGGL(list_tile_kernel<FLAT>, dim3(static_cast<uint32_t>(tiles)), dim3(256), 0, st, s, q, k, v, idx, cnt, L,
-                       crow, o, group_heads_for(s.N, s.T));
+  if (apart && tiles_worth_a_launch(s, tiles, longest)) {
+    const auto kernel = starts_odd(k) || starts_odd(v) ? &list_tile_kernel<FLAT, true> : &list_tile_kernel<FLAT, false>;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(tiles)), dim3(256), 0, st, s, q, k, v, idx, cnt, L, crow, o,
+                       group_heads_for(s.N, s.T));
     hipLaunchKernelGGL(list_rest_kernel<FLAT>, row_grid((nrows + kRestRows - 1) / kRestRows), block, 0, st, s, q, k, v, idx,
                        cnt, L, crow, o);
   } else {

@@ -110,3 +110,36 @@ def test_same_kernel(case):
         O_s = torch.full_like(O, float("nan"))
         sea.sea_forward(p, s["Q"], s["K"], s["V"], s["W"], O_s, workspace=ws)
         assert torch.equal(O, O_s), which
+
+
+@pytest.mark.parametrize("flat", [False, True])
+def test_lists_same_kernel(flat):
+    """The same for lists, as they are and in the FlatCSR tensor: enough blocks and entries for tiles."""
+    from paper_2310_01777_amd import binding as sea
+    H, T, L = 30, 1100, 600
+    wl = synth.Workload("anywhere", 1, H, T, 64, 32, 16, 4, 0, True, "bf16", 4)
+    d = {k: v.cuda() for k, v in synth.make_inputs(wl).items() if v is not None}
+    p = sea.SeaParams(B=1, H=H, T=T, d=64, m=32, K=16, k_hat=4, causal=True, scale=wl.scale, dtype="bf16")
+    t, x = torch.arange(T, device="cuda")[:, None], torch.arange(L, device="cuda")
+    # (every second key of the last 1200, the row's own among them)
+    n = ((t + 2) // 2).clamp(max=L)
+    idx = torch.where(x < n, t - 2 * (n - 1 - x), -1).int().expand(1, H, T, L).contiguous()
+    cnt = n.flatten().int().expand(1, H, T).contiguous()
+    crow, col = torch.empty(T + 1, dtype=torch.int64, device="cuda"), torch.empty(int(cnt.sum()), dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(256, sea.sea_flatcsr_workspace_bytes(p)), dtype=torch.uint8, device="cuda")
+    sea.sea_flatcsr(p, idx, cnt, L, crow, col, ws)
+
+    def attend(q, k, v):
+        O = torch.full_like(d["Q"], float("nan"))
+        if flat:
+            sea.sea_flatcsr_attn(p, q, k, v, crow, col, O)
+        else:
+            sea.sea_sparse_attn(p, q, k, v, idx, cnt, L, O)
+        return O
+
+    print(f"[case] lists, same kernel, flat {flat}", flush=True)
+    O = attend(d["Q"], d["K"], d["V"])
+    assert torch.isfinite(O).all()
+    for which in ("K", "V", "KV"):
+        s = {k: _shifted(v, 1) if k in which else v for k, v in d.items()}
+        assert torch.equal(O, attend(s["Q"], s["K"], s["V"])), which
