@@ -81,6 +81,9 @@ __device__ __forceinline__ int32_t compact_count(int32_t jmax, int32_t rlog, int
 // rows 2, 3 (mod 4) are exchanged, which does the same for the four rows of a transpose read.
 constexpr int kRow = kHeadDim;
 
+// waves per SIMD that a kernel's registers have to leave room for
+constexpr int tile_waves(int RW, int NS, bool odd) { return NS > 1 ? 4 : (RW == 4 && odd ? 3 : 16 / RW); }
+
 // Block = 4 waves = 128 consecutive query rows of one head (32 per wave); other splits below.  The block
 // walks the compact key list in steps of 64 keys (two 32-key sub-chunks); each step's K and V rows are fetched
 // once with full-line 128-bit loads, parked in LDS (K as rows, V transposed; double buffered, one barrier per
@@ -92,9 +95,9 @@ constexpr int kRow = kHeadDim;
 // bits).  MODE 2: "bucket" form for k^ = 1 -- every row selected exactly one column, rows are
 // grouped by that column, and a block takes 128 rows of one bucket against the r keys of its
 // column, so every visited tile is fully used no matter how scattered the choices are.
-// ODD: K or V starts between two 4-byte words.
+// ODD: K or V starts between two 4-byte words, so a step's pieces wait in registers.
 template <int RLOG, int MODE, int RW = 4, int NS = 1, int SC = 2, bool ODD = false>
-__global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_kernel(TileArgs a) {
+__global__ __launch_bounds__(64 * RW * NS, tile_waves(RW, NS, ODD)) void tile_attn_kernel(TileArgs a) {
   // RW = waves side by side: 32 RW query rows share every staged key step (8 instead of 4 halve the bytes a
   // head's keys and values travel from the L2s to LDS; two blocks per CU).
   // NS = sets of RW waves that share the block's rows: each takes every NS-th SC sub-chunks of the list, and
@@ -170,22 +173,36 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   auto slot_off = [&](int32_t step, int32_t slot) {
     return static_cast<uint32_t>(pos_of(min(ubase + step * kStep + slot, a.U - 1), a.rlog, a.w)) * row_bytes;
   };
-  auto load = [](u32x4 r, uint16_t* at, uint32_t off) __attribute__((always_inline)) {
-    if constexpr (ODD) buffer_load_lds16_odd(r, at, off); else buffer_load_lds16(r, at, off);
-  };
+  u32x4 odd[4];
   auto fetch = [&](int32_t step, int place) __attribute__((always_inline)) {
     if (!linear) {
       offa = slot_off(step, srow);
       if (kTwo) offb = slot_off(step, srow + kThreads / 8);
     }
-    uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
     const uint32_t oa = min(offa, off_max), ob = min(offb, off_max);
-    load(Kres, at, oa + kpart);
-    if (kTwo) load(Kres, at + kThreads / 8 * kRow, ob + kpart);
-    load(Vres, at + kStep * kRow, oa + vpart);
-    if (kTwo) load(Vres, at + (kStep + kThreads / 8) * kRow, ob + vpart);
+    if constexpr (ODD) {
+      odd[0] = load16_odd(Kres, oa + kpart);
+      if (kTwo) odd[1] = load16_odd(Kres, ob + kpart);
+      odd[2] = load16_odd(Vres, oa + vpart);
+      if (kTwo) odd[3] = load16_odd(Vres, ob + vpart);
+    } else {
+      uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
+      buffer_load_lds16(Kres, at, oa + kpart);
+      if (kTwo) buffer_load_lds16(Kres, at + kThreads / 8 * kRow, ob + kpart);
+      buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
+      if (kTwo) buffer_load_lds16(Vres, at + (kStep + kThreads / 8) * kRow, ob + vpart);
+    }
     offa += off_step;
     offb += off_step;
+  };
+  auto park = [&](int place) __attribute__((always_inline)) {
+    if constexpr (ODD) {
+      uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
+      park16(at, odd[0]);
+      if (kTwo) park16(at + kThreads / 8 * kRow, odd[1]);
+      park16(at + kStep * kRow, odd[2]);
+      if (kTwo) park16(at + (kStep + kThreads / 8) * kRow, odd[3]);
+    }
   };
   fetch(0, 0);
   // mask words of the block's rows -> LDS, KW words a row (words past the last row repeat the last one)
@@ -265,6 +282,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
   float m_ref = 0.f, m_thr = -INFINITY, l_run = 0.f;
 
   if (STREAM && nsteps > 0) fetch_words(0, mn0, mn1);
+  park(0);
   lds_loads_done();
   __syncthreads();
   // One step, its keys and values at a place that the compiler knows: all LDS addresses of the loop are then a
@@ -419,6 +437,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS > 1 ? 4 : 16 / RW) void tile_attn_
         for (int c2 = 0; c2 < 2; ++c2)
           oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mt][c2], bp[c2], oacc[mt], 0, 0, 0);
     }
+    if (step + 1 < nsteps) park(stage ^ 1);
     lds_loads_done();
     __syncthreads();
   };
@@ -871,8 +890,8 @@ static WaveSplit wave_split(const Shape& s, int32_t U, bool key_bits) {
 
 template <int RLOG, int MODE, int RW, int NS, int SC, bool ODD = false>
 static void launch_tile(const Shape& s, const TileArgs& a, hipStream_t st) {
-  if constexpr (!ODD) {  // (keys or values that start between two words: one split of the waves for all)
-    if (starts_odd(a.K) || starts_odd(a.V)) return launch_tile<RLOG, MODE, 4, 1, 2, true>(s, a, st);
+  if constexpr (!ODD) {
+    if (starts_odd(a.K) || starts_odd(a.V)) return launch_tile<RLOG, MODE, RW, NS, SC, true>(s, a, st);
   }
   constexpr int kRows = 32 * RW, kThreads = 64 * RW * NS;  // (mask words arrive kThreads at a time)
   const size_t shm = MODE == 0 ? static_cast<size_t>((kRows * a.KW + kThreads - 1) / kThreads * kThreads) * sizeof(uint32_t) : 0;
