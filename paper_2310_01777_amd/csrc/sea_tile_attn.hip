@@ -640,8 +640,8 @@ __global__ __launch_bounds__(256) void bucket_scatter_kernel(const uint32_t* __r
   }
 }
 
-// Attention of buckets whose columns hold at most 64 keys: a block takes CH consecutive 128-row chunks of a head, so
-// that a column's keys and values are staged once for the chunks of it that follow one another, and the next chunk's
+// Attention of buckets whose columns hold at most 64 keys: a block takes CH (see the launch) consecutive 128-row chunks of
+// a head, so that a column's keys and values are staged once for the chunks of it that follow one another, and the next chunk's
 // query rows are on their way while a chunk is computed.  All keys of a row are there at once: no running reference.
 // Bound: memory (rows gathered and scattered).  Rows come and go as whole lines, eight lanes of 16 bytes each, through
 // LDS: 12 heads of 131072 rows in 128 buckets, 64 keys each, 77 us (5.2 TB/s) against 118 with the one-chunk blocks of
@@ -1014,7 +1014,13 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
     const int32_t max_chunks = lay.max_chunks;
     const dim3 chunks(static_cast<uint32_t>(s.N) * max_chunks);
     const bool odd = starts_odd(K) || starts_odd(V);
-    if (rlog <= 6 && !odd && !starts_odd(Q))
+    // Four chunks per block save staging where the launch is many times what is resident at once (1024 blocks); below, they
+    // only make a block's chain longer.  Layers, us with one / four chunks a block: 1584 chunks (12 heads, T = 512, K = 128)
+    // 26.9 / 32.0, 1536 (8, 8192) 40.2 / 44.9, 4608 (12, 32768) 98.5 / 102.7, 8192 (32, 16384) 148.6 / 150.3, 9216 (96, 2048,
+    // two columns) 94.6 / 95.6, 13824 (12, 131072) 307 / 303.
+    if (rlog <= 6 && !odd && !starts_odd(Q) && chunks.x <= 8192u)
+      hipLaunchKernelGGL(bucket_attn_kernel<1>, chunks, dim3(256), 0, st, a);
+    else if (rlog <= 6 && !odd && !starts_odd(Q))
       hipLaunchKernelGGL(bucket_attn_kernel<4>, dim3(static_cast<uint32_t>(s.N) * ((max_chunks + 3) / 4)), dim3(256), 0, st, a);
     else if (odd)
       hipLaunchKernelGGL((tile_attn_kernel<0, 2, 4, 1, 2, true>), chunks, dim3(256), 0, st, a);

@@ -54,3 +54,37 @@ def test_buckets_of_few_keys(r, T, causal):
     want = oracle.sparse_attn(oracle_params(p), to_np64(q), to_np64(k), to_np64(v), idx.cpu().numpy(), cnt.cpu().numpy())
     assert np.isfinite(want).all()
     assert_close(to_np64(O), want, TOL["bf16"], "O")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("k_hat,H,T", [(1, 64, 1024), (2, 44, 4096)])
+def test_buckets_of_many_heads(k_hat, H, T, causal):
+    """More and fewer than 8192 chunks of 128 rows (one or four to a block): a head's rows come out alike.  The columns
+    differ in the number of their rows, from none to several chunks of them, and some rows have no column."""
+    from paper_2310_01777_amd import binding as sea
+    K = 128
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn(1, H, T, 64, generator=g, device="cuda").bfloat16() for _ in range(3))
+    col = (K * torch.rand(k_hat, 1, H, T, generator=g, device="cuda") ** 4).long()  # (the same one twice is one)
+    bits = torch.zeros(1, H, T, K, dtype=torch.bool, device="cuda")
+    for c in col:
+        bits.scatter_(-1, c[..., None], True)
+    bits[:, :, 7::50] = False
+    words = (bits.view(1, H, T, K // 32, 32).long() << torch.arange(32, device="cuda")).sum(-1)
+    mhat = torch.where(words >= 1 << 31, words - (1 << 32), words).int()
+
+    def attend(h):
+        n = h.stop - h.start
+        p = sea.SeaParams(B=1, H=n, T=T, d=64, m=64, K=K, k_hat=k_hat, k_budget=k_hat * T // K, causal=causal, scale=0.125, dtype="bf16")
+        O = torch.full((1, n, T, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ws = torch.empty(sea.sea_mask_attn_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        assert ws.numel() > 0  # rows are grouped by column
+        sea.sea_mask_attn(p, *(x[:, h].contiguous() for x in (q, k, v, mhat)), O, ws)
+        return O
+
+    print(f"[case] buckets of many heads {(k_hat, H, T, causal)}", flush=True)
+    many = attend(slice(0, H))
+    assert torch.isfinite(many).all() and bool((many[:, :, 7::50] == 0).all())
+    for h in range(0, H, 20):
+        some = slice(h, min(h + 20, H))
+        assert torch.equal(many[:, some], attend(some))
