@@ -178,10 +178,8 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 && !ODD ? 4 : 3) void column_
       odd[3] = load16_odd(Vres, ob + vpart);
     } else {
       uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
-      buffer_load_lds16(Kres, at, oa + kpart);
-      buffer_load_lds16(Kres, at + 8 * kWaves * kRow, ob + kpart);
-      buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
-      buffer_load_lds16(Vres, at + (kStep + 8 * kWaves) * kRow, ob + vpart);
+      buffer_load_lds16(Kres, at, oa + kpart, at + 8 * kWaves * kRow, ob + kpart);
+      buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart, at + (kStep + 8 * kWaves) * kRow, ob + vpart);
     }
     if (NX >= 16 || spart < NX / 2) {
 #pragma unroll

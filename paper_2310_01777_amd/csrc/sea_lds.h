@@ -21,15 +21,19 @@ __device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t bytes) 
 // The memory side needs whole 4-byte words.  Tensors of 2-byte elements that start between two of them (their rows are
 // whole words apart, so all loads of a tensor go the same way) pass through registers: load16_odd asks for a piece,
 // park16 puts it where buffer_load_lds16 would.
-// FRESH: the resource's words may come from vector instructions just before (read lanes), whose results a load may read
-// five wait states later.
-template <bool FRESH = false>
+// The five wait states in front of a load are for a resource whose words come from vector instructions just before (read
+// lanes, a scalar that the compiler spilled among them): the compiler does not see the load and keeps no distance itself.
 __device__ __forceinline__ void buffer_load_lds16(u32x4 r, uint16_t* at, uint32_t byte_off) {
   const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at));
-  if (FRESH)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory", "m0");
+}
+// two pieces a lane, which share those wait states
+__device__ __forceinline__ void buffer_load_lds16(u32x4 r, uint16_t* at0, uint32_t off0, uint16_t* at1, uint32_t off1) {
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at0));
+  const uint32_t lds1 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at1));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %2, %4, 0 offen lds\n\t"
+               "s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %4, 0 offen lds"
+               ::"s"(lds0), "s"(lds1), "v"(off0), "v"(off1), "s"(r) : "memory", "m0");
 }
 __device__ __forceinline__ u32x4 load16_odd(u32x4 r, uint32_t byte_off) {
   typedef uint32_t anywhere __attribute__((ext_vector_type(4), aligned(2)));
@@ -41,7 +45,7 @@ __device__ __forceinline__ void buffer_load_lds16_odd(u32x4 r, uint16_t* at, uin
 // buffer_load_lds16 with 4 bytes per lane: lane l writes word l
 __device__ __forceinline__ void buffer_load_lds4(u32x4 r, uint32_t* at, uint32_t byte_off) {
   const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)at));
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(byte_off), "s"(r) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // waits until at most n (uniform, below eight) of the loads asked for last are on their way

@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
           const int32_t n = __builtin_amdgcn_readlane(kl.n, next), cu = __builtin_amdgcn_readlane(cursor, next);
           const u32x4 list = buffer_words(row_base(next), static_cast<uint32_t>(min(n, 1 << 29)) * 4u);
           for (int32_t q = 0; q < c; ++q, ++issued)
-            buffer_load_lds16<true>(list, ring + (issued & (kRing - 1)) * 512, entry_off(cu + 256 * q + 4 * lane, n));
+            buffer_load_lds16(list, ring + (issued & (kRing - 1)) * 512, entry_off(cu + 256 * q + 4 * lane, n));
         }
         ++next;
       }
@@ -421,10 +421,8 @@ __global__ __launch_bounds__(256, 3) void list_tile_kernel(Shape s, const uint16
         odd[3] = load16_odd(Vres, ob + vpart);
       } else {
         uint16_t* const at = &KVs[place][0][wid * 8 * kRow];
-        buffer_load_lds16(Kres, at, oa + kpart);
-        buffer_load_lds16(Kres, at + 32 * kRow, ob + kpart);
-        buffer_load_lds16(Vres, at + kChunk * kRow, oa + vpart);
-        buffer_load_lds16(Vres, at + (kChunk + 32) * kRow, ob + vpart);
+        buffer_load_lds16(Kres, at, oa + kpart, at + 32 * kRow, ob + kpart);
+        buffer_load_lds16(Vres, at + kChunk * kRow, oa + vpart, at + (kChunk + 32) * kRow, ob + vpart);
       }
     };
     auto park = [&](int place) __attribute__((always_inline)) {

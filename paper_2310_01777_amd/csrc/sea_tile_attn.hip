@@ -187,10 +187,13 @@ __global__ __launch_bounds__(64 * RW * NS, tile_waves(RW, NS, ODD)) void tile_at
       if (kTwo) odd[3] = load16_odd(Vres, ob + vpart);
     } else {
       uint16_t* const at = &KVs[place][0][wall * 8 * kRow];
-      buffer_load_lds16(Kres, at, oa + kpart);
-      if (kTwo) buffer_load_lds16(Kres, at + kThreads / 8 * kRow, ob + kpart);
-      buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
-      if (kTwo) buffer_load_lds16(Vres, at + (kStep + kThreads / 8) * kRow, ob + vpart);
+      if (kTwo) {
+        buffer_load_lds16(Kres, at, oa + kpart, at + kThreads / 8 * kRow, ob + kpart);
+        buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart, at + (kStep + kThreads / 8) * kRow, ob + vpart);
+      } else {
+        buffer_load_lds16(Kres, at, oa + kpart);
+        buffer_load_lds16(Vres, at + kStep * kRow, oa + vpart);
+      }
     }
     offa += off_step;
     offb += off_step;

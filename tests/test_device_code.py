@@ -1,0 +1,37 @@
+"""The built library's own device code.  Loads that go straight to LDS are written as instructions, so the compiler keeps no
+distance in front of them: every one has to bring it along."""
+import glob
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="needs a disassembler")
+def test_loads_to_lds_keep_their_distance(tmp_path):
+    from paper_2310_01777_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
+    shutil.copy(build.LIB, tmp_path / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
+    loads = 0
+    for obj in glob.glob(str(tmp_path / "*gfx950")):
+        dump = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", obj], check=True, capture_output=True, text=True)
+        before = []  # the run of such loads and of what belongs to them, up to here
+        for line in dump.stdout.splitlines():
+            ins = " ".join(line.split("//")[0].split())
+            if re.match(r"buffer_load_dword(x4)? .* lds$", ins):
+                loads += 1
+                # scalars from vector instructions are read five wait states later, m0 from the scalar unit one
+                waits = [int(w[1]) + 1 if (w := re.match(r"s_nop (\d+)$", x)) else 1 for x in before]
+                assert sum(waits) >= 5 and re.match(r"s_nop \d+$", before[-1]) and before[-2].startswith("s_mov_b32 m0, "), (obj, before, ins)
+                before.append(ins)
+            elif ins.startswith("s_mov_b32 m0, ") or re.match(r"s_nop \d+$", ins):
+                before.append(ins)
+            elif ins:
+                before = []
+    assert loads > 0
