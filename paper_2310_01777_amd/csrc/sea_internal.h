@@ -11,12 +11,13 @@ constexpr int kWave = 64;
 constexpr int kHeadDim = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Do the lists of `rows` rows, L entries each, outgrow the caches so far that they are written and read past them?  A
-// tensor built from them and they themselves then exceed the 256 MB memory-side cache.  Selection with lists, FlatCSR
-// tensor and attention from it, us with cached / uncached lists: H = 12, T = 2048, B = 4, 403 MB 475 / 423 (both
-// kernels that touch the lists gain), T = 1024, B = 5, 126 MB 377 / 343; 101 MB of full lists 542 / 502, of half empty
-// ones 305 / 311; T = 512, B = 8, 50 MB 138 / 141.
-__host__ __device__ inline bool lists_outgrow_cache(int64_t rows, int32_t L) { return rows * L > (int64_t(104) << 20) / 4; }
+// Do the lists of `rows` rows, L entries each, outgrow the caches so far that they are written and read past them?  From
+// 128 MiB on they and a tensor built from them no longer share the 256 MB memory-side cache (judged by the room for
+// them: how full they are is not known here).  Selection with lists, FlatCSR tensor and attention from it, us with
+// cached / uncached lists: H = 12, T = 2048, B = 4, 403 MB 406 / 355 (both kernels that touch the lists gain), B = 2,
+// 201 MB 255 / 231, T = 1024, B = 8, 201 MB of full lists 262 / 253; B = 5, 126 MB full 184 / 177, half empty 154 / 154,
+// where the tensor alone, from lists that are in the cache, takes 47 / 52 and 38 / 48; 50 MB 153 / 155.
+__host__ __device__ inline bool lists_outgrow_cache(int64_t rows, int32_t L) { return rows * L > (int64_t(128) << 20) / 4; }
 
 // Shape block handed to kernels by value.
 struct Shape {

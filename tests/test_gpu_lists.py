@@ -141,9 +141,10 @@ def test_flatcsr_of_short_lists(B, H, T, L):
         assert np.array_equal(col[:cut].cpu().numpy(), col_o[:cut]) and bool((col[cut:] == -7).all())
 
 
-@pytest.mark.parametrize("B,H,T,k_hat", [(1, 12, 2048, 96), (1, 13, 2048, 64), (1, 14, 2048, 64), (2, 12, 2048, 48)])
+@pytest.mark.parametrize("B,H,T,k_hat", [(1, 12, 2048, 96), (1, 13, 2048, 64), (1, 14, 2048, 64), (2, 12, 2048, 48),
+                                         (1, 16, 2048, 64), (1, 17, 2048, 64)])
 def test_lists_past_the_caches(B, H, T, k_hat):
-    """Lists and the tensor built from them on both sides of the size at which they bypass the caches (27.3 M entries),
+    """Lists and the tensor built from them on both sides of the size at which they bypass the caches (33.6 M entries),
     against torch's own selection: every score distinct, whole columns of 16 keys."""
     from paper_2310_01777_amd import binding as sea
     K, w = 128, T // 128
