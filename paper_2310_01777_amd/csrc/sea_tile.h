@@ -51,12 +51,13 @@ __device__ __forceinline__ float max_of(const float (&y)[16]) {
 
 // Running reference of a streaming softmax, log2 units: the largest score met when it was last moved.  It stays until a
 // score exceeds it by kRefSlack.  Any reference gives the same weights up to a factor that the row sum takes out again,
-// so it only has to keep sums and products in range: a row's largest weight lies between 1 and 2^8, so values down to
-// the smallest normal number keep their bits in its products, and sums of 2^14 such weights times values of 2^104 stay
-// finite.  References 32 above the scores, moved after a rise of 48, save half of the rescalings (c4 at T = 32768 and c2
-// 2 % faster) but cost 2^32 of that range below and 2^8 above.  The argument of exp2 is rounded to its own last bit, so
-// where weights keep 24 bits the ones that count have to have small arguments anyway (rms error of a row 2^-21.8 against
-// 2^-20.4).
+// so it has to keep sums and products in range: a row's largest weight lies between 1 and 2^8, so values down to the
+// smallest normal number keep their bits in its products, and sums of 2^14 such weights times values of 2^104 stay
+// finite.  And it should be a score: that key's weight, mostly the row's largest, is then 1 and not rounded.
+// References further up are moved less often but cost both.  32 above, moved after a rise of 48: c4 at T = 32768 and c2
+// 2 % faster, error against 64 bits 2 % larger (c2 1.83e-3 -> 1.87e-3, weights of bf16), values below 2^-94 lost bits and
+// those from about 2^106 on overflowed; 8 above, moved after 16: 1 % faster, the same loss of precision.  Weights kept to
+// 24 bits lose more, because the argument of exp2 is rounded to its own last bit (rms 2^-21.8 -> 2^-20.4 of a row).
 constexpr float kRefSlack = 8.f;
 
 // O^T += V^T P^T for one 32-key sub-chunk with weights p = 2^y held in fp32: a weight enters the bf16 product

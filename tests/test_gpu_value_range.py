@@ -18,7 +18,7 @@ LAYERS = [("layer", 2, 64, 64, 0), ("layer", 70, 16, 16, 0), ("layer", 2, 64, 64
           ("dense", 2, 64, 64, 0), ("layer", 2, 60, 60, 0)]
 
 
-@pytest.mark.parametrize("exponent", [-118, 0, 106])
+@pytest.mark.parametrize("exponent", [-125, -118, 0, 106])
 @pytest.mark.parametrize("scores", SCORES)
 @pytest.mark.parametrize("how,H,K,k_hat,geometry", LAYERS)
 def test_values_of_any_size(how, H, K, k_hat, geometry, scores, exponent):
