@@ -86,8 +86,8 @@ constexpr int tile_waves(int RW, int NS, bool odd) { return NS > 1 ? 4 : (RW == 
 
 // Block = 4 waves = 128 consecutive query rows of one head (32 per wave); other splits below.  The block
 // walks the compact key list in steps of 64 keys (two 32-key sub-chunks); each step's K and V rows are fetched
-// once with full-line 128-bit loads, parked in LDS (K as rows, V transposed; double buffered, one barrier per
-// step) and read by all four waves as MFMA fragments.
+// once, straight to LDS as they lie in memory (double buffered, one barrier per step), and read by all four waves as
+// MFMA fragments, those of V through the transpose read.
 // RLOG = log2(keys per column) for 1..16 keys per column, 5 for 32 or more (then a 32-key
 // sub-chunk lies inside one column and the actual shift is a.rlog).
 //
