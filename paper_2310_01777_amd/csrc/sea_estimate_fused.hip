@@ -108,19 +108,6 @@ __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
-// raw projections w_f . x of 16 rows x m features: dots[ft][i] for feature 16 ft + 4 lg + i
-template <int MC>
-__device__ __forceinline__ void project_dots(const uint16_t* Ws, bf16x8 x0, bf16x8 x1, int lr, int lg,
-                                             floatx4 (&dots)[2 * MC]) {
-#pragma unroll
-  for (int ft = 0; ft < 2 * MC; ++ft) {
-    const uint16_t* w = &Ws[(ft * 16 + lr) * kWRow + 8 * lg];
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma16(*reinterpret_cast<const bf16x8*>(w), x0, acc);
-    dots[ft] = mfma16(*reinterpret_cast<const bf16x8*>(w + 32), x1, acc);
-  }
-}
-
 // exponent arguments (log2 domain) of 16 rows x m features: arg[ft][i] for feature 16 ft + 4 lg + i
 template <int MC>
 __device__ __forceinline__ void project(const uint16_t* Ws, bf16x8 x0, bf16x8 x1, int lr, int lg,
@@ -999,103 +986,242 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
 // ------------------------------------------------------------------------------------------
 // query side, bidirectional, one column of 65 to 128 per row (k^ = 1, m <= 128), every row active: with no
 // search to do, what is left of a row is two contractions and a maximum.  W and a head's whole state fit LDS
-// together (53 KB for m = K = 128), so a block stages them once per head and its waves take 16 rows after 16
+// together (48 KB for m = K = 128), so a block stages them once per head and its waves take 32 rows after 32
 // rows with no barrier in between (the kernel above stages W per 64 rows and steps the state through LDS
-// behind four barriers).  Two blocks of eight waves per CU, each with an equal share of all heads' row groups.
-// Same arithmetic per row, bit for bit.  B = 1, H = 12, T = 131072, m = K = 128: the whole
-// forward 381 -> 360 us.  The search for
-// k^ > 1 wants more waves than stay resident here (B = 32, H = 12, T = 512, K = 64, no padding: 97 -> 108 us for the whole
-// forward), shares of sequences of different lengths are unequal, K <= 64 needs no steps to begin with, and
-// two row tiles per wave (an operand read from LDS then serves twice) cost the occupancy they would need.
+// behind four barriers).  Two blocks of eight waves per CU, each with an equal share of all heads' tiles.  The winner of
+// a row is its largest raw score: scaling by the row's sum can only make scores equal that are within a few units in the
+// last place of each other, and a wave that holds such a row, or scores outside the middle of fp32's range, scales them
+// and lets the lowest of the equal columns win, as the kernel above does.  With that, and without a test per column, 32
+// rows take 540 vector instructions (1110 before, most of them tests and the scalars they spilled); with 32 rows per wave an
+// operand read from LDS serves twice the rows it does in tiles of 16 (48 KB each, 70 us of LDS time per launch).  Bound:
+// vector pipe 62 % and matrix pipe 38 % busy at the 1.9 GHz the chip keeps here, one after the other.  B = 1, H = 12,
+// T = 131072, m = K = 128: 152 -> 102 us (2.0 TB/s), the whole forward 303 -> 265.  1024 to 4096 blocks, or six or
+// twelve waves to a block: the same or slower.  The search for k^ > 1 wants more waves than stay resident here, shares of
+// sequences of different lengths are unequal, and K <= 64 needs no steps to begin with.
 // ------------------------------------------------------------------------------------------
 constexpr int kBidirWaves = 8, kBidirBlocks = 512;  // two blocks per CU
-template <int MC, int NCT>
-__global__ __launch_bounds__(64 * kBidirWaves, 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+// w with sixteen bits more at its low end: bit e is set iff the bits of v[e] are at or above floor (one comparison and one
+// addition each, the comparison's bit carried in)
+__device__ __forceinline__ uint32_t mark_at_least(floatx16 v, uint32_t floor, uint32_t w) {
+  asm(
+      "v_cmp_ge_u32 vcc, %16, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %15, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %14, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %13, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %12, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %11, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %10, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %9, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %8, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %7, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %6, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %5, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %4, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %3, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %2, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+      "v_cmp_ge_u32 vcc, %1, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
+      : "+v"(w)
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]),
+        "v"(v[8]), "v"(v[9]), "v"(v[10]), "v"(v[11]), "v"(v[12]), "v"(v[13]), "v"(v[14]), "v"(v[15]),
+        "v"(floor)
+      : "vcc");
+  return w;
+}
+template <int MC, int NCT, bool SCORES>
+__global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                                                   const uint16_t* __restrict__ W,
                                                                                   const uint16_t* __restrict__ state,
                                                                                   float* __restrict__ A_hat,
                                                                                   uint32_t* __restrict__ mbits, float c_dot,
                                                                                   float c_norm, Columns cg) {
-  s.k_hat = 1;  // (the search over several is not part of this kernel)
   constexpr int m = 32 * MC, kThreads = 64 * kBidirWaves;
+  constexpr int kTiles = NCT / 2;      // of 32 columns
+  constexpr int kPieces = m / 8;       // 16-byte pieces of a state row
+  static_assert(NCT == 8, "a lane's scores are two mask words");
+  // Rows end in a 16-byte pad: the sixteen lanes that an LDS read serves at a time (one piece of rows that differ mod 16)
+  // hit distinct banks.  Piece 2 ks + g of a state row, the eight features 32 (ks / 2) + 16 (e / 4) + 8 (ks % 2) + 4 g + e % 4,
+  // is the operand of lane half g in contraction step ks: registers 4 (ks % 2) + 8 (e / 4) + e % 4 of a feature tile hold the
+  // same ones.  Two steps add up in the order of one 16x16x32 product, so scores are those of the kernel above, bit for bit.
   constexpr int kSRow = m + 8;
-  constexpr int kGroup = 16 * kBidirWaves;    // rows per block and round
   extern __shared__ __attribute__((aligned(16))) uint16_t rows_lds[];
   uint16_t* const Ws = rows_lds;              // [m][kWRow]
   uint16_t* const Ss = rows_lds + m * kWRow;  // [16 NCT][kSRow]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 15, lg = lane >> 4;
-  // this block's share of all heads' groups, in order: [lo, hi)
-  const uint32_t groups = (s.T + kGroup - 1) / kGroup;
-  const uint64_t all = static_cast<uint64_t>(groups) * s.N;
+  const int lr = lane & 31, g = lane >> 5;
+  // this block's share of all heads' 32-row tiles, in order: [lo, hi)
+  const uint32_t tiles = (s.T + 31) / 32;
+  const uint64_t all = static_cast<uint64_t>(tiles) * s.N;
   const uint32_t lb = xcd_contiguous(blockIdx.x, gridDim.x);
   const uint32_t lo = static_cast<uint32_t>(all * lb / gridDim.x), hi = static_cast<uint32_t>(all * (lb + 1) / gridDim.x);
 
-  bf16x8 x0, x1;  // the next rows on their way
-  auto request = [&](uint32_t at) {
-    const uint32_t g = at % groups;
-    const uint16_t* X = Q + (static_cast<int64_t>(at / groups) * s.T + min(static_cast<int32_t>(g) * kGroup + 16 * wid + lr, s.T - 1)) * kHeadDim;
-    x0 = *reinterpret_cast<const bf16x8*>(X + 8 * lg);
-    x1 = *reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg);
-  };
-  request(lo);
   for (int v = tid; v < m * 8; v += kThreads)
-    *reinterpret_cast<uint4*>(&Ws[(v >> 3) * kWRow + (v & 7) * 8]) = *reinterpret_cast<const uint4*>(W + (v >> 3) * kHeadDim + (v & 7) * 8);
-  const int32_t ncnd_all = column_of(cg, s.T - 1) + 1;  // every column is a candidate of every row
-  int64_t staged = -1;
-  for (uint32_t at = lo; at < hi; ++at) {
-    const int64_t head = at / groups;
-    if (head != staged) {
-      if (staged >= 0) __syncthreads();  // every wave is done with the last head's state
-      const uint16_t* sh = state + head * static_cast<int64_t>(s.K) * m;
-      for (int v = tid; v < 16 * NCT * m / 8; v += kThreads) {
-        const int col = v / (m / 8), part = v % (m / 8);
-        *reinterpret_cast<uint4*>(&Ss[col * kSRow + 8 * part]) =
-            *reinterpret_cast<const uint4*>(sh + static_cast<int64_t>(min(col, s.K - 1)) * m + 8 * part);
+    *reinterpret_cast<uint4*>(Ws + (v >> 3) * kWRow + 8 * (v & 7)) = *reinterpret_cast<const uint4*>(W + 8 * v);
+  const int32_t ncnd = column_of(cg, s.T - 1) + 1;  // every column that holds a key is a candidate of every row
+  const uint16_t* const wrow = Ws + lr * kWRow + 8 * g;
+  const uint16_t* const srow = Ss + lr * kSRow + 8 * g;
+
+  for (uint32_t first = lo; first < hi;) {
+    const uint32_t head = first / tiles;
+    const uint32_t end = min(hi, (head + 1) * tiles);
+    if (first != lo) __syncthreads();  // every wave is done with the last head's state
+    const uint16_t* sh = state + head * static_cast<int64_t>(s.K) * m;
+    for (int v = tid; v < 16 * NCT * kPieces; v += kThreads) {
+      const int col = v / kPieces, p = v % kPieces;  // (columns that hold no key score zero)
+      uint4 x = {0u, 0u, 0u, 0u};
+      if (col < ncnd) x = *reinterpret_cast<const uint4*>(sh + static_cast<int64_t>(col) * m + 8 * p);
+      *reinterpret_cast<uint4*>(Ss + col * kSRow + 8 * p) = x;
+    }
+    __syncthreads();
+
+    bf16x8 x[4];  // the next rows on their way
+    auto request = [&](uint32_t tile) {
+      const uint16_t* X = Q + (static_cast<int64_t>(head) * s.T + min(static_cast<int32_t>(tile - head * tiles) * 32 + lr, s.T - 1)) * kHeadDim + 8 * g;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) x[ks] = *reinterpret_cast<const bf16x8*>(X + 16 * ks);
+    };
+    if (first + wid < end) request(first + wid);
+    for (uint32_t tile = first + wid; tile < end; tile += kBidirWaves) {
+      asm volatile("" ::: "memory");  // (operands are read from LDS where they are used, not ahead of the loop into spilled registers)
+      const int32_t trow = static_cast<int32_t>(tile - head * tiles) * 32 + lr;
+      const float n02 = sumsq8(x[0]) + sumsq8(x[2]), n13 = sumsq8(x[1]) + sumsq8(x[3]);
+      const float nx = (n02 + __shfl_xor(n02, 32, kWave)) + (n13 + __shfl_xor(n13, 32, kWave));
+      floatx16 dots[MC];
+      float dmax = -INFINITY;
+#pragma unroll
+      for (int ft = 0; ft < MC; ++ft) {
+        dots[ft] = floatx16{};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          dots[ft] = mfma32(*reinterpret_cast<const bf16x8*>(wrow + 32 * ft * kWRow + 16 * ks), x[ks], dots[ft]);
       }
-      __syncthreads();
-      staged = head;
-    }
-    const int32_t r0 = static_cast<int32_t>(at % groups) * kGroup + 16 * wid;
-    float nx = sumsq8(x0) + sumsq8(x1);
-    nx += __shfl_xor(nx, 16, kWave);
-    nx += __shfl_xor(nx, 32, kWave);
-    floatx4 dots[2 * MC];
-    project_dots<MC>(Ws, x0, x1, lr, lg, dots);
-    if (at + 1 < hi) request(at + 1);
-    float dmax = -INFINITY;
 #pragma unroll
-    for (int ft = 0; ft < 2 * MC; ++ft)
+      for (int ft = 0; ft < MC; ++ft)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dmax = fmaxf(dmax, dots[ft][i]);
-    dmax = fmaxf(dmax, __shfl_xor(dmax, 16, kWave));
-    dmax = fmaxf(dmax, __shfl_xor(dmax, 32, kWave));
-    const float bias = c_norm * nx;
-    const float shift = r0 + lr < s.T ? ceilf(fmaf(c_dot, dmax, -bias)) : INFINITY;
-    const float off = -(bias + shift);
-    bf16x8 afrag[MC];
+        for (int i = 0; i < 16; ++i) dmax = fmaxf(dmax, dots[ft][i]);
+      dmax = fmaxf(dmax, __shfl_xor(dmax, 32, kWave));
+      const float bias = c_norm * nx;
+      const float off = -(bias + ceilf(fmaf(c_dot, dmax, -bias)));  // (rows past T repeat the last one)
+      bf16x8 afrag[2 * MC];
 #pragma unroll
-    for (int kc = 0; kc < MC; ++kc) {
-      float lo[4], hi[4];
+      for (int ft = 0; ft < MC; ++ft)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        lo[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, dots[2 * kc][i], off));
-        hi[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, dots[2 * kc + 1][i], off));
+        for (int j = 0; j < 2; ++j) {
+          float a[4], b[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            a[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, dots[ft][4 * j + i], off));
+            b[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, dots[ft][8 + 4 * j + i], off));
+          }
+          afrag[2 * ft + j] = pack8(a, b);
+        }
+      if (tile + kBidirWaves < end) request(tile + kBidirWaves);
+      // scores of N x 32 columns from 32 ct on, register i: row trow, column 32 ct + 8 (i / 4) + 4 g + i % 4.  Operands are on
+      // their way for four products (left alone, the compiler reads each into the register of the one before it and waits).
+      auto scores = [&](int ct, auto& acc) {
+        constexpr int N = sizeof(acc) / sizeof(floatx16), kSteps = 2 * MC, kAhead = 4;
+        const uint16_t* from = srow + 32 * ct * kSRow;
+        auto operand = [&](int u) { return *reinterpret_cast<const bf16x8*>(from + 32 * (u / kSteps) * kSRow + 16 * (u % kSteps)); };
+        bf16x8 f[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) f[u] = operand(u);
+#pragma unroll
+        for (int u = 0; u < N * kSteps; ++u) {
+          asm volatile("" ::: "memory");
+          acc[u / kSteps] = mfma32(f[u % kAhead], afrag[u % kSteps], u % kSteps ? acc[u / kSteps] : floatx16{});
+          if (u + kAhead < N * kSteps) f[u % kAhead] = operand(u + kAhead);
+        }
+      };
+      // Half of the columns at a time (all of them would leave no registers to read operands ahead): the lane's largest
+      // (scores are not negative, their bit patterns have their order, NaN above all), and which ones are within four units
+      // in the last place of it.
+      uint32_t most[2], marks[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        floatx16 ab[2];
+        scores(2 * h, ab);
+        const floatx16 a = ab[0], b = ab[1];
+        uint32_t mx0 = 0, mx1 = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          mx0 = max(mx0, __float_as_uint(a[i]));
+          mx1 = max(mx1, __float_as_uint(b[i]));
+        }
+        most[h] = max(mx0, mx1);
+        marks[h] = mark_at_least(a, most[h] - 4u, mark_at_least(b, most[h] - 4u, 0u));
       }
-      afrag[kc] = pack8(lo, hi);
-    }
-    floatx4 acc[NCT];
+      uint32_t top = max(most[0], most[1]);
+      {
+        const auto o = __builtin_amdgcn_permlane32_swap(top, top, false, false);
+        top = max(o[0], o[1]);
+      }
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) {
-      const uint16_t* brow = &Ss[(16 * ct + lr) * kSRow + 8 * lg];
-      acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int h = 0; h < 2; ++h) marks[h] = most[h] >= top - 4u ? marks[h] : 0u;
+      const uint32_t cnt = __popc(marks[0]) + __popc(marks[1]);
+      const auto both = __builtin_amdgcn_permlane32_swap(cnt, cnt, false, false);
+      // 2^-100 < largest < 2^100, and no other within 2^-22 of it
+      const bool plain = both[0] + both[1] == 1u && top - 0x0d800000u < 0x71800000u - 0x0d800000u;
+      if (SCORES || __ballot(!plain) != 0ull) {
+        float r = 0.f;
+#pragma unroll 1
+        for (int ct = 0; ct < kTiles; ++ct) {
+          floatx16 a[1];
+          scores(ct, a);
 #pragma unroll
-      for (int kc = 0; kc < MC; ++kc) acc[ct] = mfma16(*reinterpret_cast<const bf16x8*>(brow + 32 * kc), afrag[kc], acc[ct]);
+          for (int i = 0; i < 16; ++i) r += a[0][i];
+        }
+        r += __shfl_xor(r, 32, kWave);
+        const float ninv = r > 0.f ? -1.f / r : -0.f;  // (as in finish_rows: the negated score is the key)
+        top = 0u;
+        marks[0] = marks[1] = 0u;
+#pragma unroll 1
+        for (int ct = 0; ct < kTiles; ++ct) {
+          floatx16 one[1];
+          scores(ct, one);
+          floatx16 a = one[0];
+          uint32_t mx = 0u;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int32_t c = 32 * ct + 8 * (i >> 2) + 4 * g + (i & 3);
+            const float x = a[i] * ninv;
+            if (SCORES && c < s.K && trow < s.T) A_hat[(static_cast<int64_t>(head) * s.T + trow) * s.K + c] = -x;
+            a[i] = c < ncnd ? x : __uint_as_float(0x40000000u);
+            mx = max(mx, __float_as_uint(a[i]));
+          }
+          const auto o = __builtin_amdgcn_permlane32_swap(mx, mx, false, false);
+          mx = max(o[0], o[1]);
+          if (mx > top) marks[0] = marks[1] = 0u;
+          top = max(top, mx);
+          const uint32_t w = mark_at_least(a, top, 0u) << (16 * (ct & 1));
+          marks[0] |= ct < 2 ? w : 0u;
+          marks[1] |= ct < 2 ? 0u : w;
+        }
+      }
+      if (SCORES && !mbits) continue;
+      // the lane's first marked column, and the row's
+      const int32_t e = marks[0] ? __builtin_ctz(marks[0]) : 32 + __builtin_ctz(marks[1] | 0x80000000u);
+      uint32_t col = 32 * (e >> 4) + 8 * ((e >> 2) & 3) + 4 * g + (e & 3);
+      if ((marks[0] | marks[1]) == 0u) col = 0xffffu;
+      const auto cc = __builtin_amdgcn_permlane32_swap(col, col, false, false);
+      col = min(cc[0], cc[1]);
+      if (trow < s.T) {  // this lane's two words of the row
+        const int32_t kw = (s.K + 31) >> 5;
+        const uint32_t bit = 1u << (col & 31), at = col >> 5;
+        uint32_t* mrow = mbits + (static_cast<int64_t>(head) * s.T + trow) * kw + 2 * g;
+        const uint2 words = make_uint2(at == 2 * g ? bit : 0u, at == 2 * g + 1 ? bit : 0u);
+        if (kw == 4) {
+          *reinterpret_cast<uint2*>(mrow) = words;
+        } else {
+          mrow[0] = words.x;
+          if (g == 0) mrow[1] = words.y;
+        }
+      }
     }
-    const int32_t trow = r0 + lr;
-    finish_rows<false, NCT>(s, acc, head, trow, trow < s.T ? ncnd_all : 0, r0 + 15 < s.T ? (ncnd_all - 1) >> 4 : 0, s.K, 0.f, lg,
-                            A_hat, mbits);
+    first = end;
   }
 }
 
@@ -1202,8 +1328,12 @@ void launch_bidir(const Shape& s, const uint16_t* Q, const uint16_t* W, float* A
                   float c_dot, float c_norm, hipStream_t st) {
   constexpr size_t lds = (static_cast<size_t>(32 * MC) * kWRow + static_cast<size_t>(16) * NCT * (32 * MC + 8)) * 2;
   static_assert(lds <= (64u << 10), "no larger LDS has to be asked for");
-  hipLaunchKernelGGL((estimate_rows_bidir_kernel<MC, NCT>), dim3(kBidirBlocks), dim3(64 * kBidirWaves), lds, st, s, Q, W, f.state,
-                     A_hat, mbits, c_dot, c_norm, columns_of(s.T, s.K));
+#define SEA_BIDIR(SCORES_) \
+  hipLaunchKernelGGL((estimate_rows_bidir_kernel<MC, NCT, SCORES_>), dim3(kBidirBlocks), dim3(64 * kBidirWaves), lds, st, s, Q, W, f.state, \
+                     A_hat, mbits, c_dot, c_norm, columns_of(s.T, s.K))
+  if (A_hat) SEA_BIDIR(true);
+  else SEA_BIDIR(false);
+#undef SEA_BIDIR
 }
 
 template <int MC, int WLOG>
@@ -1246,7 +1376,7 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
   if constexpr (MC <= 4) {
     // from two row groups per resident block on (equal to the other kernel there, ahead from four on)
     const int64_t groups = (s.T + 16 * kBidirWaves - 1) / (16 * kBidirWaves) * s.N;
-    if (!s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks && groups < (1ll << 31))
+    if (!s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks && groups < (1ll << 28))
       return launch_bidir<MC, 8>(s, Q, W, A_hat, mbits, f, c_dot, c_norm, st);
   }
   switch (wl) {
