@@ -606,6 +606,7 @@ template <bool CAUSAL, int NCT>
 __device__ __forceinline__ void finish_rows(const Shape& s, floatx4 (&acc)[NCT], int64_t head, int32_t trow, int32_t ncnd,
                                             int32_t ct_free, int32_t ncols_wave, float diag, int lg,
                                             float* __restrict__ A_hat, uint32_t* __restrict__ mbits) {
+  bool sums;  // the row's scores sum to one
   const int32_t e = ncnd - 1 - 4 * lg;  // column 16 ct + 4 lg + i is the last admissible one iff 16 ct + i == e
   float rsum = 0.f;
 #pragma unroll
@@ -630,6 +631,7 @@ __device__ __forceinline__ void finish_rows(const Shape& s, floatx4 (&acc)[NCT],
     // The normalised scores are kept NEGATED from here on: the bit pattern of -x (x >= +0) is
     // 0x80000000 | bits(x), which is the selection key itself, so the keys cost no instruction.
     const float ninv = r > 0.f ? -1.f / r : -0.f;
+    sums = r > 0x1p-100f && r < 0x1p100f;
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
@@ -674,7 +676,7 @@ __device__ __forceinline__ void finish_rows(const Shape& s, floatx4 (&acc)[NCT],
     }
   }
   uint32_t nib[NCT];
-  select_columns<NCT>(key, nsel, ncnd, CAUSAL ? min(NCT, (ncols_wave + 15) >> 4) : NCT, s.k_hat, lg, nib);
+  select_columns<NCT>(key, nsel, ncnd, CAUSAL ? min(NCT, (ncols_wave + 15) >> 4) : NCT, s.k_hat, search_top(nsel, sums), lg, nib);
   store_mask_words<NCT>(s, nib, head, trow, lg, mbits);
 }
 

@@ -360,8 +360,10 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
     // first key of column c: ceil(c (t + 1) / K)
     auto start = [&](int32_t c) { return c * w0 + div_small(c * rm + s.K - 1, invK); };
     uint32_t key[NCT][4];
+    bool sums = false;  // the row's scores sum to one
     if (wave < 2 * U) {
       const double inv = inv_s[row];
+      sums = inv > 0x1p-100 && inv < 0x1p100;
       const uint32_t by_part = 65536u / static_cast<uint32_t>(part_cols) + 1u;  // c / part_cols, exact for c < 256
       const double* const row_bins = lds + row * stride + 1;
 #pragma unroll
@@ -385,7 +387,7 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
     __syncthreads();  // the bins are in registers: their place takes the rows' key bits
     if (wave >= 2 * U) return;
     uint32_t nib[NCT];
-    select_columns<NCT>(key, nsel, ncnd, NCT, s.k_hat, lg, nib);
+    select_columns<NCT>(key, nsel, ncnd, NCT, s.k_hat, search_top(nsel, sums), lg, nib);
     if (mbits) {
       const int32_t kw = (s.K + 31) >> 5;
 #pragma unroll

@@ -6,36 +6,38 @@ namespace sea {
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
+// Where the search of a row starts from above: fewer than nsel keys have a high half at or above this.  Scores that sum to
+// one (`sums`) hold fewer than nsel of 1.02 / nsel; anything else below infinity lies under 0xc000.
+__device__ __forceinline__ float search_top(uint32_t nsel, bool sums) {
+  const uint32_t bound = __float_as_uint(1.02f * __builtin_amdgcn_rcpf(static_cast<float>(max(nsel, 1u))));
+  return static_cast<float>(sums ? (0x8000u | (bound >> 16)) + 1u : 0xc000u);
+}
+
 // Per-row top-k^ on 16 rows of a wave, in registers.  A row lives in the four lanes l % 16 + 16 q; key[ct][i]
 // is the order-preserving key of its column 16 ct + 4 lg + i (bit patterns of negated scores in [0, 1];
 // 0x40000000 for columns that are no candidates), nsel its quota, ncnd its number of candidates; columns
-// from 16 nct on hold no candidate of the wave's rows.  nib[ct]: bit i set iff that column is selected.
+// from 16 nct on hold no candidate of the wave's rows; top: see search_top.  nib[ct]: bit i set iff that column is
+// selected.
 template <int NCT>
 __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], uint32_t nsel, int32_t ncnd, int32_t nct_wave,
-                                               int32_t k_hat, int lg, uint32_t (&nib)[NCT]) {
+                                               int32_t k_hat, float top, int lg, uint32_t (&nib)[NCT]) {
   uint32_t tau = 0x80000000u, cge = static_cast<uint32_t>(ncnd);
   bool dropped = false;  // the row's threshold lies just above the one key too many that it had found
+  bool lacking = false;  // the row's threshold is the largest key below one that leaves it a key short
   bool counted = false;  // (uniform) some row's selection may hold equals of one key
   // The compare-and-count loop runs over the tiles that hold candidates of this wave's rows only
   // (causal: the leading ones), in even steps so that a handful of loop bodies covers all cases.
-  // Bits 29..16 are searched on the keys' high halves, two keys per register: both halves of
-  // hp - trial (16-bit wrap-around differences; candidates and trial lie in [0x8000, 0xc000),
-  // non-candidates are 0x4000) have bit 15 set exactly for keys below the trial; a byte permute
-  // spreads each sign over a byte, four differences at a time, and the matrix product adds the bytes
-  // up.  The trial's
-  // low half is zero in that phase, so the counts are those of the full keys.  Bits 15..0 then
-  // compare whole keys.
-#define SEA_SEARCH_STEP(COUNT_BODY_, REDUCE_)                                                    \
-    /* done when every row's count of keys >= tau is its quota or one more */                    \
-    if (__ballot(cge > nsel + 1u && nsel != 0u) == 0ull) break;                                  \
-    const bool pend = (cge != nsel) && (nsel != 0u);                                             \
-    const uint32_t trial = tau | (1u << bit);                                                    \
-    uint32_t cnt = 0;                                                                            \
-    COUNT_BODY_                                                                                  \
-    REDUCE_                                                                                      \
-    const bool take = pend && cnt >= nsel;                                                       \
-    tau = take ? trial : tau;                                                                    \
-    cge = take ? cnt : cge;
+  // The keys' high halves are searched first, two keys per register: both halves of hp - trial (16-bit
+  // wrap-around differences; candidates and trial lie in [0x8000, 0xc000), non-candidates are 0x4000) have bit 15 set
+  // exactly for keys below the trial; a byte permute spreads each sign over a byte, four differences at a time, and
+  // the matrix product adds the bytes up.  The trial's low half is zero in that phase, so the counts are those of the
+  // full keys.
+  // A row keeps `lo` with a keys more than its quota at or above it and `hi` with b keys fewer (b + 1/4 while hi is only
+  // known from `top`).  Bit patterns are a logarithmic scale, on which a row's scores are spread evenly enough for the next
+  // trial to come from a and b: 0.15 to 0.85 of the way (every step takes at least that off the range), at most eight octaves
+  // at a time.  Done when a row has its quota, one key more or one fewer.  Steps for the slowest of 16 rows, bit by bit
+  // (until the quota or one more) / so: c4 at T = 32768 11.2 / 6.4, c3 11.8 / 7.4, c2 10.6 / 5.8, c5 9.0 / 5.0, one sentence
+  // 7.3 / 3.1; weights of 0.6 to 0.9 and four to twelve octaves are within a tenth of that, halving takes 7 to 9.
 #define SEA_SEARCH(NT_)                                                                          \
   {                                                                                              \
     ushort2v hp[2 * (NT_)];                                                                      \
@@ -43,16 +45,15 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
       hp[2 * ct] = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(key[ct][1], key[ct][0], 0x07060302u)); \
       hp[2 * ct + 1] = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(key[ct][3], key[ct][2], 0x07060302u)); \
     }                                                                                            \
-    /* Count of the ROW's keys at or above a trial whose low half is zero.  A byte permute turns  \
+    /* Number of the ROW's keys below a trial whose low half is zero.  A byte permute turns      \
        the signs of four differences into four bytes 0x00 / 0xff (selectors 8..11 take the sign \
        of bytes 1, 3, 5, 7), i.e. 0 / -1 as 8-bit integers; sixteen of them are one operand of  \
        the 8-bit matrix product, whose column is the query row (lane % 16) and whose           \
        contraction runs over the lane's sixteen keys and the row's four lanes: against an      \
        all -1 operand every result row is the number of the row's keys BELOW the trial, summed \
        over the four lanes, so the counting and the cross-lane sum leave the vector pipe. */    \
-    auto count_high = [&](uint32_t trial_) {                                                     \
-      const uint32_t th = trial_ >> 16;                                                          \
-      const ushort2v th2 = __builtin_bit_cast(ushort2v, th | (th << 16));                        \
+    auto count_below = [&](uint32_t th) {                                                        \
+      const ushort2v th2 = __builtin_bit_cast(ushort2v, __builtin_amdgcn_perm(th, th, 0x01000100u)); \
       const intx4 neg1 = {-1, -1, -1, -1};                                                       \
       intx4 below = {0, 0, 0, 0};                                                                \
       _Pragma("unroll") for (int q4 = 0; q4 < ((NT_) + 3) / 4; ++q4) {                            \
@@ -67,44 +68,51 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
         }                                                                                        \
         below = __builtin_amdgcn_mfma_i32_16x16x64_i8(neg1, fl, below, 0, 0, 0);                 \
       }                                                                                          \
-      return 16u * static_cast<uint32_t>(NT_) - static_cast<uint32_t>(below[0]);                 \
+      return below[0];                                                                           \
     };                                                                                           \
-    /* Bits 29..27 at once: a row whose quota of scores lies at or above 2^-15 (rows sum to 1    \
-       over at most 256 columns, so nearly every row) would take all three bits, because the     \
-       count only grows as the trial falls; one count then stands for three steps.  A wave with  \
-       a row that fails the test searches from bit 29 as before. */                              \
-    int bit_top = 29;                                                                            \
-    {                                                                                            \
-      const bool pend = (cge != nsel) && (nsel != 0u);                                           \
-      const uint32_t trial = 0xb8000000u;                                                        \
-      const uint32_t cnt = count_high(trial);                                                    \
-      if (__ballot(pend && cnt < nsel) == 0ull) {                                                \
-        tau = pend ? trial : tau;                                                                \
-        cge = pend ? cnt : cge;                                                                  \
-        bit_top = 26;                                                                            \
-      }                                                                                          \
+    /* (rows without a quota start with nothing to search; whole numbers below 2^16 throughout) */ \
+    const float over = static_cast<float>(16 * (NT_)) - static_cast<float>(nsel);                \
+    float lo = nsel != 0u ? 32768.f : top - 1.f, hi = top;                                       \
+    float a = static_cast<float>(ncnd) - static_cast<float>(nsel), b = static_cast<float>(nsel) + 0.25f; \
+    _Pragma("unroll 1") while (__ballot(a > 1.f && b != 1.f && hi - lo > 1.f) != 0ull) {         \
+      const float part = fmaf(b * __builtin_amdgcn_rcpf(a + b), 0.7f, 0.15f);                    \
+      const float trial = truncf(fmaxf(fmaf(-part, fminf(hi - lo, 1024.f), hi), lo + 1.f));      \
+      const float d = over - static_cast<float>(count_below(static_cast<uint32_t>(trial)));      \
+      const bool enough = d >= 0.f;                                                              \
+      lo = enough ? trial : lo;                                                                  \
+      hi = enough ? hi : trial;                                                                  \
+      a = enough ? d : a;                                                                        \
+      b = enough ? b : -d;                                                                       \
     }                                                                                            \
-    _Pragma("unroll 1") for (int bit = bit_top; bit >= 16; --bit) {                               \
-      SEA_SEARCH_STEP(cnt = count_high(trial);, )                                                \
-    }                                                                                            \
+    lacking = a > 1.f && b == 1.f && nsel != 0u;                                                 \
+    cge = lacking ? nsel : nsel + static_cast<uint32_t>(a);                                      \
+    tau = static_cast<uint32_t>(lacking ? hi : lo) << 16;                                        \
   }                                                                                              \
+  /* rows with several keys of one high half around their quota: bits 15..0 on whole keys */     \
   _Pragma("unroll 1") for (int bit = 15; bit >= 0; --bit) {                                       \
-    SEA_SEARCH_STEP(                                                                             \
-      _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct)                                        \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= trial) ? 1u : 0u;,   \
-      cnt = rows_sum_u(cnt);)                                                                    \
+    if (__ballot(cge > nsel + 1u && nsel != 0u) == 0ull) break;                                  \
+    const bool pend = (cge != nsel) && (nsel != 0u);                                             \
+    const uint32_t trial = tau | (1u << bit);                                                    \
+    uint32_t cnt = 0;                                                                            \
+    _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct)                                          \
+      _Pragma("unroll") for (int i = 0; i < 4; ++i) cnt += (key[ct][i] >= trial) ? 1u : 0u;      \
+    cnt = rows_sum_u(cnt);                                                                       \
+    const bool take = pend && cnt >= nsel;                                                       \
+    tau = take ? trial : tau;                                                                    \
+    cge = take ? cnt : cge;                                                                      \
   }                                                                                              \
-  /* A row with one key too many drops its smallest at or above tau (differences that wrap belong \
-     to keys below tau).  The slowest of 16 rows would take three more steps of the search for   \
-     it, some of them on whole keys.  Layers, us without / with: c4 at T = 32768 758 / 727, c3   \
-     400 / 389, c5 74.0 / 70.7, one short sentence 17.4 / 16.1. */                               \
+  /* A row with one key too many drops its smallest at or above tau, a row with one too few takes its largest below tau    \
+     (differences that wrap belong to keys on the other side, and those of non-candidates are larger than any key's).      \
+     The slowest of 16 rows would take three more steps of the search for it, some of them on whole keys.  Layers, us       \
+     without / with the dropping: c4 at T = 32768 758 / 727, c3 400 / 389, c5 74.0 / 70.7, one short sentence 17.4 / 16.1. */ \
   dropped = cge == nsel + 1u && nsel != 0u;                                                      \
-  if (__ballot(dropped) != 0ull) {                                                               \
+  if (__ballot(dropped || lacking) != 0ull) {                                                    \
+    const uint32_t flip = lacking ? ~0u : 0u, from = lacking ? tau : 0u - tau;                   \
     uint32_t least = 0xffffffffu;                                                                \
     _Pragma("unroll") for (int ct = 0; ct < (NT_); ++ct)                                          \
-      _Pragma("unroll") for (int i = 0; i < 4; ++i) least = min(least, key[ct][i] - tau);         \
+      _Pragma("unroll") for (int i = 0; i < 4; ++i) least = min(least, (key[ct][i] ^ flip) + from); \
     least = rows_min_u(least);                                                                   \
-    tau = dropped ? tau + least + 1u : tau;                                                      \
+    tau = dropped ? tau + least + 1u : lacking ? tau - 1u - least : tau;                         \
     cge = dropped ? nsel : cge;                                                                  \
   }
   if (k_hat == 1) {
@@ -133,7 +141,6 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
     SEA_SEARCH(2)
   }
 #undef SEA_SEARCH
-#undef SEA_SEARCH_STEP
   // selection: keys >= tau; when more keys than the quota tie at tau (exact duplicates at the
   // boundary), the lowest columns among them win.  nib[ct]: bit i set iff column 16 ct + 4 lg + i
   // of this lane's row is selected.
@@ -146,7 +153,7 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
       for (int i = 0; i < 4; ++i) bits |= (nsel != 0u && key[ct][i] >= tau) ? (1u << i) : 0u;
       nib[ct] = bits;
     }
-    if (counted || __ballot(dropped) != 0ull) {  // where the key that went had equals, they went with it
+    if (counted || __ballot(dropped || lacking) != 0ull) {  // equals of the key that went went with it, of one that came came with it
       uint32_t cnt = 0;
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct) cnt += __popc(nib[ct]);
