@@ -556,7 +556,7 @@ __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg
 
 // the 16 rows' selected columns as mask words
 template <int NCT>
-__device__ __forceinline__ void store_mask_words(const Shape& s, const uint32_t (&nib)[NCT], int64_t head, int32_t trow, int lg,
+__device__ __forceinline__ void store_mask_words(const Shape& s, const uint32_t (&sel)[NCT / 2], int64_t head, int32_t trow, int lg,
                                                  uint32_t* __restrict__ mbits) {
   // mask words: word j holds columns 32 j .. 32 j + 31 = tiles 2 j (low half) and 2 j + 1; this lane's
   // four columns of a tile sit at bits 4 lg .. 4 lg + 3 of the tile's half.  The four lanes of a row
@@ -573,7 +573,7 @@ __device__ __forceinline__ void store_mask_words(const Shape& s, const uint32_t 
     for (int j = 0; j < kWords; j += 4) {
       uint32_t pw[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) pw[q] = (nib[2 * (j + q)] << (4 * lg)) | (nib[2 * (j + q) + 1] << (16 + 4 * lg));
+      for (int q = 0; q < 4; ++q) pw[q] = sel[j + q] << (4 * lg);
       const auto ab = __builtin_amdgcn_permlane16_swap(pw[0], pw[1], false, false);
       const auto cd = __builtin_amdgcn_permlane16_swap(pw[2], pw[3], false, false);
       const auto t = __builtin_amdgcn_permlane32_swap(ab[0] | ab[1], cd[0] | cd[1], false, false);
@@ -582,8 +582,7 @@ __device__ __forceinline__ void store_mask_words(const Shape& s, const uint32_t 
   } else {
     uint32_t words[kWords];
 #pragma unroll
-    for (int j = 0; j < kWords; ++j)
-      words[j] = rows_or_u((nib[2 * j] << (4 * lg)) | (nib[2 * j + 1] << (16 + 4 * lg)));
+    for (int j = 0; j < kWords; ++j) words[j] = rows_or_u(sel[j] << (4 * lg));
     if (trow >= s.T || lg != 0) return;
     uint32_t* mrow = mbits + (head * s.T + trow) * kw;
     if (kw == kWords) {
@@ -600,84 +599,116 @@ __device__ __forceinline__ void store_mask_words(const Shape& s, const uint32_t 
 // From raw scores to mask bits, for 16 rows of a wave.  acc[ct][i] = raw score of row trow, column
 // cc = 16 ct + 4 lg + i; ncnd = the row's number of admissible columns (0: inactive row), a causal row takes its
 // own column (the last of them) from diag.  Tiles below ct_free lie wholly below every row's last column and
-// need no test; tiles from column ncols_wave on are cleared.
+// need no test; tiles from column ncols_wave on hold nothing.
+// A column that is no candidate of its row is a positive NaN from its first test on: no factor changes that, and as a
+// selection key it lies below every score.  (Before, every column was tested in three passes, with copies that the compiler
+// made around the tests, and the selected columns were put together from comparisons and shifts: about 230 of the 1800 vector
+// instructions of a wave at m = K = 256.  Rows kernel alone, c4 at T = 32768 / c3: 320 -> 300 us, 166 -> 153 us.)
 // ------------------------------------------------------------------------------------------
+constexpr uint32_t kNoCandidate = 0x7fc00000u;
+// One tile of finish_rows' first pass, in place.  Tiles below ct_free add their scores to the sum; in the others that hold
+// candidates (`edges` = one past them) a lane's column `last` is its row's last candidate: that one takes diag (causal), the
+// ones past it become kNoCandidate, like all of the tiles past those, and the sum gains the rest.  (Written with its branches, which are uniform: where two
+// ways lead to the same four values the compiler copies them on both.  Masks are read two instructions after they are
+// written at the earliest.)
+template <bool CAUSAL>
+__device__ __forceinline__ void bound_tile(floatx4& v, int ct, int32_t ct_free, int32_t edges, int32_t last, float diag, float& sum) {
+  uint64_t m0, m1, m2, m3;
+  float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3], t, u;
+#define SEA_TILE_FREE \
+  "s_cmp_gt_i32 %[free], %[ct]\n\ts_cbranch_scc0 .Lsea_edge%=\n\t" \
+  "v_add_f32 %[t], %[x0], %[x1]\n\tv_add_f32 %[u], %[x2], %[x3]\n\tv_add_f32 %[t], %[t], %[u]\n\tv_add_f32 %[sum], %[sum], %[t]\n\t" \
+  "s_branch .Lsea_done%=\n.Lsea_edge%=:\n\ts_cmp_gt_i32 %[edges], %[ct]\n\ts_cbranch_scc0 .Lsea_none%=\n\t"
+#define SEA_TILE_DIAG \
+  "v_cmp_eq_u32 %[m0], 0, %[last]\n\tv_cmp_eq_u32 %[m1], 1, %[last]\n\tv_cmp_eq_u32 %[m2], 2, %[last]\n\tv_cmp_eq_u32 %[m3], 3, %[last]\n\t" \
+  "v_cndmask_b32 %[x0], %[x0], %[diag], %[m0]\n\tv_cndmask_b32 %[x1], %[x1], %[diag], %[m1]\n\t" \
+  "v_cndmask_b32 %[x2], %[x2], %[diag], %[m2]\n\tv_cndmask_b32 %[x3], %[x3], %[diag], %[m3]\n\t"
+#define SEA_TILE_EDGE \
+  "v_cmp_gt_i32 %[m0], 0, %[last]\n\tv_cmp_gt_i32 %[m1], 1, %[last]\n\tv_cmp_gt_i32 %[m2], 2, %[last]\n\tv_cmp_gt_i32 %[m3], 3, %[last]\n\t" \
+  "v_cndmask_b32 %[t], %[x0], 0, %[m0]\n\tv_add_f32 %[sum], %[sum], %[t]\n\tv_cndmask_b32 %[t], %[x1], 0, %[m1]\n\tv_add_f32 %[sum], %[sum], %[t]\n\t" \
+  "v_cndmask_b32 %[t], %[x2], 0, %[m2]\n\tv_add_f32 %[sum], %[sum], %[t]\n\tv_cndmask_b32 %[t], %[x3], 0, %[m3]\n\tv_add_f32 %[sum], %[sum], %[t]\n\t" \
+  "v_cndmask_b32 %[x0], %[x0], %[none], %[m0]\n\tv_cndmask_b32 %[x1], %[x1], %[none], %[m1]\n\t" \
+  "v_cndmask_b32 %[x2], %[x2], %[none], %[m2]\n\tv_cndmask_b32 %[x3], %[x3], %[none], %[m3]\n\t" \
+  "s_branch .Lsea_done%=\n.Lsea_none%=:\n\t" \
+  "v_mov_b32 %[x0], %[none]\n\tv_mov_b32 %[x1], %[none]\n\tv_mov_b32 %[x2], %[none]\n\tv_mov_b32 %[x3], %[none]\n.Lsea_done%=:"
+#define SEA_TILE_OPERANDS \
+  : [x0] "+v"(x0), [x1] "+v"(x1), [x2] "+v"(x2), [x3] "+v"(x3), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3), \
+    [sum] "+v"(sum), [t] "=&v"(t), [u] "=&v"(u) \
+  : [free] "s"(ct_free), [edges] "s"(edges), [ct] "n"(ct), [last] "v"(last), [diag] "v"(diag), [none] "v"(kNoCandidate) \
+  : "scc"
+  if constexpr (CAUSAL)
+    asm(SEA_TILE_FREE SEA_TILE_DIAG SEA_TILE_EDGE SEA_TILE_OPERANDS);
+  else
+    asm(SEA_TILE_FREE SEA_TILE_EDGE SEA_TILE_OPERANDS);
+#undef SEA_TILE_FREE
+#undef SEA_TILE_DIAG
+#undef SEA_TILE_EDGE
+#undef SEA_TILE_OPERANDS
+  v = floatx4{x0, x1, x2, x3};
+}
 template <bool CAUSAL, int NCT>
 __device__ __forceinline__ void finish_rows(const Shape& s, floatx4 (&acc)[NCT], int64_t head, int32_t trow, int32_t ncnd,
                                             int32_t ct_free, int32_t ncols_wave, float diag, int lg,
                                             float* __restrict__ A_hat, uint32_t* __restrict__ mbits) {
-  bool sums;  // the row's scores sum to one
   const int32_t e = ncnd - 1 - 4 * lg;  // column 16 ct + 4 lg + i is the last admissible one iff 16 ct + i == e
+  const int32_t edges = __builtin_amdgcn_readfirstlane((ncols_wave + 15) >> 4);
+  ct_free = __builtin_amdgcn_readfirstlane(ct_free);
   float rsum = 0.f;
+  // (what the instructions below read has left the matrix pipe: the compiler keeps that distance for its own only)
+#pragma unroll
+  for (int ct = 0; ct < NCT; ct += 4)
+    asm volatile("s_nop %5" : "+v"(rsum), "+v"(acc[ct]), "+v"(acc[ct + 1]), "+v"(acc[ct + 2]), "+v"(acc[ct + 3]) : "n"(ct + 4 < NCT ? 0 : 15));
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) {
-    if (ct < ct_free) {
-      rsum += (acc[ct][0] + acc[ct][1]) + (acc[ct][2] + acc[ct][3]);
-    } else if (ct * 16 < ncols_wave) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float v = acc[ct][i];
-        if (CAUSAL && ct * 16 + i == e) v = diag;
-        if (ct * 16 + i > e) v = 0.f;
-        acc[ct][i] = v;
-        rsum += v;
-      }
-    } else {
-      acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    bound_tile<CAUSAL>(acc[ct], ct, ct_free, edges, e - ct * 16, diag, rsum);
   }
-  {
-    const float r = rows_sum(rsum);
-    // The normalised scores are kept NEGATED from here on: the bit pattern of -x (x >= +0) is
-    // 0x80000000 | bits(x), which is the selection key itself, so the keys cost no instruction.
-    const float ninv = r > 0.f ? -1.f / r : -0.f;
-    sums = r > 0x1p-100f && r < 0x1p100f;
+  const float r = rows_sum(rsum);
+  // The normalised scores are kept NEGATED from here on: the bit pattern of -x (x >= +0) is
+  // 0x80000000 | bits(x), which is the selection key itself, so the keys cost no instruction.
+  const float ninv = r > 0.f ? -1.f / r : -0.f;
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
+  for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[ct][i] *= ninv;
-    if (A_hat && trow < s.T) {
-      float* out = A_hat + (head * s.T + trow) * s.K;
-      if ((s.K & 3) == 0) {
-        // a scratch A_hat read only by the grouped selection needs no zeros past a row's candidates
-        const int32_t cend = s.cand_only ? min(s.K, ncnd) : s.K;
+    for (int i = 0; i < 4; ++i) acc[ct][i] *= ninv;
+  if (A_hat && trow < s.T) {
+    float* out = A_hat + (head * s.T + trow) * s.K;
+    if ((s.K & 3) == 0) {
+      // a scratch A_hat read only by the grouped selection needs no zeros past a row's candidates
+      const int32_t cend = s.cand_only ? min(s.K, ncnd) : s.K;
 #pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-          if (ct * 16 + 4 * lg < cend)
-            *reinterpret_cast<float4*>(out + ct * 16 + 4 * lg) = make_float4(-acc[ct][0], -acc[ct][1], -acc[ct][2], -acc[ct][3]);
-      } else {
+      for (int ct = 0; ct < NCT; ++ct)
+        if (ct * 16 + 4 * lg < cend) {
+          float4 v = make_float4(-acc[ct][0], -acc[ct][1], -acc[ct][2], -acc[ct][3]);
+          if (ct >= ct_free) {
+            v.x = ct * 16 + 0 > e ? 0.f : v.x;
+            v.y = ct * 16 + 1 > e ? 0.f : v.y;
+            v.z = ct * 16 + 2 > e ? 0.f : v.z;
+            v.w = ct * 16 + 3 > e ? 0.f : v.w;
+          }
+          *reinterpret_cast<float4*>(out + ct * 16 + 4 * lg) = v;
+        }
+    } else {
 #pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
+      for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (ct * 16 + 4 * lg + i < s.K) out[ct * 16 + 4 * lg + i] = -acc[ct][i];
-      }
+        for (int i = 0; i < 4; ++i)
+          if (ct * 16 + 4 * lg + i < s.K) out[ct * 16 + 4 * lg + i] = ct * 16 + i > e ? 0.f : -acc[ct][i];
     }
   }
   if (!mbits) return;
 
   // ---- per-row top-k^ on the normalised scores, in registers (Sec. 3.1 "Grouped Top-k^
-  // Selection", per-query grouping).  A row lives in four lanes, 4 NCT scores each.  The k^-th
-  // largest score is found by a bitwise search on order-preserving integer keys (the bit patterns
-  // of the negated scores); the counts of a step are taken over the whole row by an 8-bit integer
-  // matrix product (high halves) or per lane with two row-swap steps (low halves).  Scores are in
-  // [0, 1], so the key's two top bits are known and the search starts below them.
+  // Selection", per-query grouping).  A row lives in four lanes, 4 NCT scores each.
   const uint32_t nsel = static_cast<uint32_t>(min(s.k_hat, ncnd));
   uint32_t key[NCT][4];
 #pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    if (ct < ct_free) {  // every column of the tile is a candidate of every row
+  for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) key[ct][i] = __float_as_uint(acc[ct][i]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        key[ct][i] = ct * 16 + i <= e ? __float_as_uint(acc[ct][i]) : 0x40000000u;
-    }
-  }
-  uint32_t nib[NCT];
-  select_columns<NCT>(key, nsel, ncnd, CAUSAL ? min(NCT, (ncols_wave + 15) >> 4) : NCT, s.k_hat, search_top(nsel, sums), lg, nib);
-  store_mask_words<NCT>(s, nib, head, trow, lg, mbits);
+    for (int i = 0; i < 4; ++i) key[ct][i] = __float_as_uint(acc[ct][i]);
+  uint32_t sel[NCT / 2];
+  select_columns<NCT>(key, nsel, ncnd, CAUSAL ? min(NCT, (ncols_wave + 15) >> 4) : NCT, s.k_hat,
+                      search_top(nsel, r > 0x1p-100f && r < 0x1p100f), lg, sel);
+  store_mask_words<NCT>(s, sel, head, trow, lg, mbits);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -690,8 +721,10 @@ constexpr int kColStage = 32;   // columns of the state staged in LDS per step
 // shape), kAnyWidth for widths that are none, or that differ from column to column (K does not divide T).
 constexpr int kAnyWidth = 6;
 
+// (Waves per SIMD: what LDS leaves room for at m = 256; at fewer features what the registers of the widest case need.  Left to
+// itself the compiler takes 150 registers for 65 to 128 columns where 84 do, and half of the waves are gone.)
 template <int MC, bool CAUSAL, int WLOG, int NCT>
-__global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const uint16_t* __restrict__ Q,
+__global__ __launch_bounds__(256, MC == 8 ? 3 : NCT == 16 ? 4 : 5) void estimate_rows_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                             const uint16_t* __restrict__ K,
                                                             const uint16_t* __restrict__ W,
                                                             const uint16_t* __restrict__ state,
@@ -954,7 +987,7 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
   // ---- A_hat tile = phi(Q) state^T, state streamed through LDS ----
   floatx4 acc[NCT];
 #pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int ct = 0; ct < NCT; ++ct) asm volatile("" : "=v"(acc[ct]));  // (anything: finish_rows sets the tiles that no stage reaches)
   const int32_t ncols_wave = CAUSAL ? __builtin_amdgcn_readfirstlane(min(s.K, col_of(min(r0 + 15, s.T - 1)) + 1)) : s.K;
 #pragma unroll
   for (int st = 0; st < NCT * 16 / kColStage; ++st) {
@@ -1002,36 +1035,8 @@ __global__ __launch_bounds__(256, 3) void estimate_rows_kernel(Shape s, const ui
 // sequences of different lengths are unequal, and K <= 64 needs no steps to begin with.
 // ------------------------------------------------------------------------------------------
 constexpr int kBidirWaves = 8, kBidirBlocks = 512;  // two blocks per CU
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-// w with sixteen bits more at its low end: bit e is set iff the bits of v[e] are at or above floor (one comparison and one
-// addition each, the comparison's bit carried in)
-__device__ __forceinline__ uint32_t mark_at_least(floatx16 v, uint32_t floor, uint32_t w) {
-  asm(
-      "v_cmp_ge_u32 vcc, %16, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %15, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %14, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %13, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %12, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %11, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %10, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %9, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %8, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %7, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %6, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %5, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %4, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %3, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %2, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-      "v_cmp_ge_u32 vcc, %1, %17\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
-      : "+v"(w)
-      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]),
-        "v"(v[8]), "v"(v[9]), "v"(v[10]), "v"(v[11]), "v"(v[12]), "v"(v[13]), "v"(v[14]), "v"(v[15]),
-        "v"(floor)
-      : "vcc");
-  return w;
 }
 template <int MC, int NCT, bool SCORES>
 __global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,

@@ -386,13 +386,13 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
     }
     __syncthreads();  // the bins are in registers: their place takes the rows' key bits
     if (wave >= 2 * U) return;
-    uint32_t nib[NCT];
-    select_columns<NCT>(key, nsel, ncnd, NCT, s.k_hat, search_top(nsel, sums), lg, nib);
+    uint32_t sel[NCT / 2];
+    select_columns<NCT>(key, nsel, ncnd, NCT, s.k_hat, search_top(nsel, sums), lg, sel);
     if (mbits) {
       const int32_t kw = (s.K + 31) >> 5;
 #pragma unroll
       for (int j = 0; j < NCT / 2; ++j) {
-        const uint32_t word = rows_or_u((nib[2 * j] << (4 * lg)) | (nib[2 * j + 1] << (16 + 4 * lg)));
+        const uint32_t word = rows_or_u(sel[j] << (4 * lg));
         if (lg == 0 && j < kw && t < s.T) mbits[(head * s.T + t) * kw + j] = word;
       }
     }
@@ -411,11 +411,11 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
       uint32_t carry = 0u;  // is column 16 ct - 1 selected (lane group 3 of the tile before)
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct) {
-        const uint32_t top = nib[ct] >> 3;
+        const uint32_t nib = (sel[ct / 2] >> (16 * (ct & 1))) & 15u, top = nib >> 3;
         const uint32_t below = __shfl_up(top, 16, kWave);  // bit 3 of the lane group below
-        const uint32_t prev = (nib[ct] << 1) | (lg == 0 ? carry : below);
+        const uint32_t prev = (nib << 1) | (lg == 0 ? carry : below);
         carry = __shfl(top, 48 + lr, kWave);
-        const uint32_t flips = (nib[ct] ^ prev) & 15u;
+        const uint32_t flips = (nib ^ prev) & 15u;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int32_t c = 16 * ct + 4 * lg + i, at = start(c);
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
       for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if ((nib[ct] >> i) & 1u) {
+          if ((sel[ct / 2] >> (16 * (ct & 1) + i)) & 1u) {
             const int32_t c = 16 * ct + 4 * lg + i, s0 = start(c), w = start(c + 1) - s0, r = min(w, s.rep_cap);
             for (int32_t e = 0; e < r; ++e) {
               const int32_t j = s0 + (e * w) / r;

@@ -6,6 +6,56 @@ namespace sea {
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
+// Marks of keys at or above a floor, one comparison and one addition each: the comparison's bit is carried into twice the
+// marks so far.  A comparison's mask is read two instructions later at the earliest, the distance that gfx950 wants between
+// a vector instruction that writes scalars and one that reads them.
+// bits i and 16 + i: a[i] and b[i]
+__device__ __forceinline__ uint32_t mark_at_least(const uint32_t (&a)[4], const uint32_t (&b)[4], uint32_t floor) {
+  uint32_t w = 0;
+  uint64_t m0, m1, m2;
+  asm(
+      "v_cmp_ge_u32 %1, %11, %12\n\tv_cmp_ge_u32 %2, %10, %12\n\t"
+      "v_cmp_ge_u32 %3, %9, %12\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_cmp_ge_u32 %1, %8, %12\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+      "v_cmp_ge_u32 %2, %7, %12\n\tv_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+      "v_cmp_ge_u32 %3, %6, %12\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_lshlrev_b32 %0, 12, %0\n\tv_cmp_ge_u32 %1, %5, %12\n\t"
+      "v_addc_co_u32 %0, vcc, %0, %0, %2\n\tv_cmp_ge_u32 %2, %4, %12\n\t"
+      "v_addc_co_u32 %0, vcc, %0, %0, %3\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_addc_co_u32 %0, vcc, %0, %0, %2"
+      : "+v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2)
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(floor)
+      : "vcc");
+  return w;
+}
+// w with sixteen bits more at its low end, bit i for the bits of v[i]
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ uint32_t mark_at_least(floatx16 v, uint32_t floor, uint32_t w) {
+  uint64_t m0, m1, m2;
+  asm(
+      "v_cmp_ge_u32 %1, %19, %20\n\tv_cmp_ge_u32 %2, %18, %20\n\t"
+      "v_cmp_ge_u32 %3, %17, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_cmp_ge_u32 %1, %16, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+      "v_cmp_ge_u32 %2, %15, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+      "v_cmp_ge_u32 %3, %14, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_cmp_ge_u32 %1, %13, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+      "v_cmp_ge_u32 %2, %12, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+      "v_cmp_ge_u32 %3, %11, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_cmp_ge_u32 %1, %10, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+      "v_cmp_ge_u32 %2, %9, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+      "v_cmp_ge_u32 %3, %8, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_cmp_ge_u32 %1, %7, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+      "v_cmp_ge_u32 %2, %6, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+      "v_cmp_ge_u32 %3, %5, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+      "v_cmp_ge_u32 %1, %4, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+      "v_addc_co_u32 %0, vcc, %0, %0, %3\n\tv_addc_co_u32 %0, vcc, %0, %0, %1"
+      : "+v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2)
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]),
+        "v"(v[8]), "v"(v[9]), "v"(v[10]), "v"(v[11]), "v"(v[12]), "v"(v[13]), "v"(v[14]), "v"(v[15]), "v"(floor)
+      : "vcc");
+  return w;
+}
+
 // Where the search of a row starts from above: fewer than nsel keys have a high half at or above this.  Scores that sum to
 // one (`sums`) hold fewer than nsel of 1.02 / nsel; anything else below infinity lies under 0xc000.
 __device__ __forceinline__ float search_top(uint32_t nsel, bool sums) {
@@ -15,12 +65,12 @@ __device__ __forceinline__ float search_top(uint32_t nsel, bool sums) {
 
 // Per-row top-k^ on 16 rows of a wave, in registers.  A row lives in the four lanes l % 16 + 16 q; key[ct][i]
 // is the order-preserving key of its column 16 ct + 4 lg + i (bit patterns of negated scores in [0, 1];
-// 0x40000000 for columns that are no candidates), nsel its quota, ncnd its number of candidates; columns
-// from 16 nct on hold no candidate of the wave's rows; top: see search_top.  nib[ct]: bit i set iff that column is
-// selected.
+// from 0x40000000 below 0x80000000 for columns that are no candidates), nsel its quota, ncnd its number of candidates; columns
+// from 16 nct on hold no candidate of the wave's rows; top: see search_top.  sel[j]: bit 16 h + i set iff column
+// 16 (2 j + h) + 4 lg + i is selected.
 template <int NCT>
 __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], uint32_t nsel, int32_t ncnd, int32_t nct_wave,
-                                               int32_t k_hat, float top, int lg, uint32_t (&nib)[NCT]) {
+                                               int32_t k_hat, float top, int lg, uint32_t (&sel)[NCT / 2]) {
   uint32_t tau = 0x80000000u, cge = static_cast<uint32_t>(ncnd);
   bool dropped = false;  // the row's threshold lies just above the one key too many that it had found
   bool lacking = false;  // the row's threshold is the largest key below one that leaves it a key short
@@ -28,7 +78,7 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
   // The compare-and-count loop runs over the tiles that hold candidates of this wave's rows only
   // (causal: the leading ones), in even steps so that a handful of loop bodies covers all cases.
   // The keys' high halves are searched first, two keys per register: both halves of hp - trial (16-bit
-  // wrap-around differences; candidates and trial lie in [0x8000, 0xc000), non-candidates are 0x4000) have bit 15 set
+  // wrap-around differences; candidates and trial lie in [0x8000, 0xc000), non-candidates in [0x4000, 0x8000)) have bit 15 set
   // exactly for keys below the trial; a byte permute spreads each sign over a byte, four differences at a time, and
   // the matrix product adds the bytes up.  The trial's low half is zero in that phase, so the counts are those of the
   // full keys.
@@ -141,22 +191,17 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
     SEA_SEARCH(2)
   }
 #undef SEA_SEARCH
-  // selection: keys >= tau; when more keys than the quota tie at tau (exact duplicates at the
-  // boundary), the lowest columns among them win.  nib[ct]: bit i set iff column 16 ct + 4 lg + i
-  // of this lane's row is selected.
+  // Selection: keys >= tau; when more keys than the quota tie at tau (exact duplicates at the
+  // boundary), the lowest columns among them win.
+  if (nsel == 0u) tau = 0xffffffffu;
   bool tied = __ballot(cge != nsel && nsel != 0u) != 0ull;
   if (!tied) {
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) {
-      uint32_t bits = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) bits |= (nsel != 0u && key[ct][i] >= tau) ? (1u << i) : 0u;
-      nib[ct] = bits;
-    }
+    for (int j = 0; j < NCT / 2; ++j) sel[j] = mark_at_least(key[2 * j], key[2 * j + 1], tau);
     if (counted || __ballot(dropped || lacking) != 0ull) {  // equals of the key that went went with it, of one that came came with it
       uint32_t cnt = 0;
 #pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) cnt += __popc(nib[ct]);
+      for (int j = 0; j < NCT / 2; ++j) cnt += __popc(sel[j]);
       tied = __ballot(rows_sum_u(cnt) != nsel) != 0ull;
     }
   }
@@ -170,7 +215,10 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
     cgt = rows_sum_u(cgt);
     int32_t need_eq = static_cast<int32_t>(nsel) - static_cast<int32_t>(cgt);  // ties still to take, in column order
 #pragma unroll
+    for (int j = 0; j < NCT / 2; ++j) sel[j] = 0u;
+#pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
+      asm volatile("" : "+v"(tau), "+v"(need_eq));  // (one tile after the other: side by side they double the kernel's registers)
       uint32_t eqm = 0, gtm = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -186,7 +234,7 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
         const int32_t rank = static_cast<int32_t>(below) + __popc(eqm & ((1u << i) - 1u));
         if (((eqm >> i) & 1u) && rank < need_eq) bits |= 1u << i;
       }
-      nib[ct] = bits;
+      sel[ct / 2] |= bits << (16 * (ct & 1));
       need_eq -= min(need_eq, static_cast<int32_t>(total));
     }
   }
