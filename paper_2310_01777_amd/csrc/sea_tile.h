@@ -130,10 +130,17 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
 // launches a CU takes its next block when it is done with one.  Attention stage, us without / with: H = 32, T = 2048,
 // B = 2, K = 256 (1024 blocks) 66.8 / 60.2, H = 12, T = 8192, whole columns (768) 192 / 172; c2 (768) 42.4 / 42.3;
 // columns of any width, T = 1701, 64 heads 98.3 / 89.9.
+// Three rounds are not evened out by one that runs backwards (c2: 46 to 56 steps of 64 keys per CU): there a CU's blocks have
+// ranks at8 and 31 - at8 / 2 and 15 - at8 / 2 (or the other way round), which add up to 46 or 47 everywhere (50 or 52 steps;
+// the layer 68.1 / 67.5).
 __device__ __forceinline__ uint32_t dealt_in_turn(uint32_t block, uint32_t grid, uint32_t per_cu, bool causal) {
-  if (!causal || grid > 256u * per_cu || ((block >> 8) & 1u) == 0u) return block;
-  const uint32_t lo = block & ~255u, n8 = min(256u, grid - lo) >> 3, at8 = (block - lo) >> 3;
-  return at8 < n8 ? lo + 8u * (n8 - 1u - at8) + (block & 7u) : block;
+  const uint32_t round = block >> 8;
+  if (!causal || grid > 256u * per_cu || round == 0u) return block;
+  const uint32_t lo = block & ~255u, at8 = (block - lo) >> 3, low = block & 7u;
+  if (grid == 768u) return lo + 8u * ((((at8 ^ round) & 1u) != 0u ? 31u : 15u) - (at8 >> 1)) + low;
+  if ((round & 1u) == 0u) return block;
+  const uint32_t n8 = min(256u, grid - lo) >> 3;
+  return at8 < n8 ? lo + 8u * (n8 - 1u - at8) + low : block;
 }
 
 #endif  // __HIPCC__
