@@ -87,10 +87,14 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 && !ODD ? 4 : 3) void column_
   const int32_t row0 = wg_tile * kRows, q0 = row0 + 32 * wid, t = q0 + ql;
   const int32_t b = static_cast<int32_t>(head / a.H);
   const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
+  if (row0 >= len) {  // nothing but padding: no keys are walked for it
+    zero_rows<kThreads>(a.O + (head * a.T + row0) * kHeadDim, min(kRows, a.T - row0));
+    return;
+  }
   const bool row_active = t < len;
   const int32_t wg_hi = min(row0 + kRows - 1, a.T - 1), t_hi = min(q0 + 31, a.T - 1);
   const int32_t u_end_wg = list_count(a.g, a.causal ? min(wg_hi, len - 1) : len - 1);
-  const int32_t u_end = q0 < a.T ? list_count(a.g, a.causal ? min(t_hi, len - 1) : len - 1) : 0;
+  const int32_t u_end = q0 < len ? list_count(a.g, a.causal ? min(t_hi, len - 1) : len - 1) : 0;
   // entries below u_free are admissible for every active row of the wave
   const int32_t u_free = min(u_end, list_count(a.g, a.causal ? min(q0, len - 1) : len - 1));
   const int32_t my_ucount = list_count(a.g, row_active ? (a.causal ? min(t, len - 1) : len - 1) : -1);

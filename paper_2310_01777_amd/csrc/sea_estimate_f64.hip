@@ -95,6 +95,12 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
   for (int e = 0; e < 16; ++e) nx = fma(xa[e], xa[e], nx);
   nx += __shfl_xor(nx, 16, kWave);
   nx += __shfl_xor(nx, 32, kWave);  // |x|^2 of token r0 + lr, in every lane group
+  if (r0 >= len) {  // nothing but padding (the block's tile, or this wave's)
+    double* const to = (which ? phiK : phiQ) + (head * s.T + r0) * s.m;
+    const int32_t n = min(16, s.T - r0) * s.m;
+    for (int32_t x = WPT == 4 ? threadIdx.x : lane; x < n; x += WPT == 4 ? 256 : 64) to[x] = 0.0;
+    return;
+  }
   // this lane's four result rows are tokens r0 + 4 i + lg
   double half_n[4];
 #pragma unroll
@@ -246,6 +252,11 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
   const int32_t r0 = static_cast<int32_t>(tiles - 1u - rank / static_cast<uint32_t>(s.N)) * 32 + 16 * rt;  // (may lie past T: the wave then only joins the barriers)
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
+  if (r0 - 16 * rt >= len) {  // nothing but padding (both row tiles)
+    const int64_t row = head * s.T + r0 - 16 * rt, rows = min(32, s.T - (r0 - 16 * rt));
+    for (int64_t x = threadIdx.x; x < rows * s.K; x += 512) A_hat[row * s.K + x] = 0.f;
+    return;
+  }
   // uniform bases and 32-bit lane offsets (a head's m K state and the 16 rows' m values index with 32 bits)
   const int32_t rbase = min(r0, s.T - 1);
   const double* qb_ = phiQ + (head * s.T + rbase) * s.m;   // A operand: token lr

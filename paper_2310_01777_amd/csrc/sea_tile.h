@@ -163,6 +163,12 @@ __device__ __forceinline__ void store_row(uint16_t* row, const floatx16 (&oacc)[
     }
 }
 
+// Rows of a result that lie past the sequence's end, by all threads of a block
+template <int THREADS>
+__device__ __forceinline__ void zero_rows(uint16_t* to, int32_t rows) {
+  for (int32_t x = threadIdx.x; x < rows * (kHeadDim / 8); x += THREADS) reinterpret_cast<uint4*>(to)[x] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // The 32 rows of a wave's result (O^T accumulators times inv, a row's factor) to memory as whole lines: through the
 // wave's 4 KB of LDS at `place`, piece p of row r at slot p ^ (r & 7), then eight lanes of 16 bytes per row.  dest(r) is
 // row r's place in memory, or nullptr; rows of the mask `marked` are written as all ones.  (With store_row, whose
