@@ -87,7 +87,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 && !ODD ? 4 : 3) void column_
   const int32_t row0 = wg_tile * kRows, q0 = row0 + 32 * wid, t = q0 + ql;
   const int32_t b = static_cast<int32_t>(head / a.H);
   const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
-  if (row0 >= len) {  // nothing but padding: no keys are walked for it
+  if (row0 >= len && padding_returns(gridDim.x, NS == 1 ? 4 : 1, a.causal)) {  // nothing but padding: no keys are walked for it
     zero_rows<kThreads>(a.O + (head * a.T + row0) * kHeadDim, min(kRows, a.T - row0));
     return;
   }

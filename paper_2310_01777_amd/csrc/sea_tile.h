@@ -133,6 +133,10 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
 // Three rounds are not evened out by one that runs backwards (c2: 46 to 56 steps of 64 keys per CU): there a CU's blocks have
 // ranks at8 and 31 - at8 / 2 and 15 - at8 / 2 (or the other way round), which add up to 46 or 47 everywhere (50 or 52 steps;
 // the layer 68.1 / 67.5).
+// (Blocks with nothing but padding have to keep their turn there: they walk their steps without products, which costs
+// little.  Where they return at once, the blocks behind them land on other CUs: B = 2, H = 32, T = 2048 padded by 0-25 %, K = 256,
+// 60 -> 63 us.  Longer launches, where the next block takes their place: padding_returns.)
+__device__ __forceinline__ bool padding_returns(uint32_t grid, uint32_t per_cu, bool causal) { return !causal || grid > 256u * per_cu; }
 __device__ __forceinline__ uint32_t dealt_in_turn(uint32_t block, uint32_t grid, uint32_t per_cu, bool causal) {
   const uint32_t round = block >> 8;
   if (!causal || grid > 256u * per_cu || round == 0u) return block;

@@ -226,13 +226,6 @@ __global__ __launch_bounds__(64 * RW * NS, tile_waves(RW, NS, ODD)) void tile_at
   }
   const int32_t b = static_cast<int32_t>(head / a.H);
   const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
-  // Nothing but padding: no keys are walked for it.  (Decided behind the first loads, as in the rows kernel: ahead of them
-  // it cost 32 sequences of 512 tokens 2 %.)
-  if (!BUCKET && wg_tile * kRows >= len) {
-    lds_loads_done();
-    zero_rows<kThreads>(a.O + (head * a.T + wg_tile * kRows) * kHeadDim, min(kRows, a.T - wg_tile * kRows));
-    return;
-  }
   const bool row_active = t >= 0 && t < len;
   const int32_t tq = min(max(t, 0), a.T - 1);
 
@@ -240,6 +233,13 @@ __global__ __launch_bounds__(64 * RW * NS, tile_waves(RW, NS, ODD)) void tile_at
   bf16x8 bq[4];
 #pragma unroll
   for (int kc = 0; kc < 4; ++kc) bq[kc] = *reinterpret_cast<const bf16x8*>(Qr + 16 * kc);
+  // Nothing but padding: no keys are walked for it.  (Decided behind the first loads, as in the rows kernel: ahead of them
+  // it cost 32 sequences of 512 tokens 2 %.)
+  if (!BUCKET && wg_tile * kRows >= len && padding_returns(gridDim.x, 16 / (RW * NS), a.causal)) {
+    lds_loads_done();
+    zero_rows<kThreads>(a.O + (head * a.T + wg_tile * kRows) * kHeadDim, min(kRows, a.T - wg_tile * kRows));
+    return;
+  }
   // Re-define the fragments through an empty asm: inside the loop they then count as plain
   // register values, not as results of memory loads the loop's own prefetch could be queued behind.
 #pragma unroll
@@ -1148,7 +1148,7 @@ __global__ __launch_bounds__(256, 2) void tile_attn_f32_kernel(TileF32Args a) {
   const int32_t t = q0 + qc;
   const int32_t b = static_cast<int32_t>(head / a.H);
   const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
-  if (q0 >= len) {  // nothing but padding: no keys are walked for it
+  if (q0 >= len && gridDim.x > 768) {  // nothing but padding: no keys are walked for it (in a launch of several rounds)
     if (q0 + (tid >> 4) < a.T)
       *reinterpret_cast<float4*>(a.O + (head * a.T + q0 + (tid >> 4)) * kHeadDim + 4 * (tid & 15)) = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
