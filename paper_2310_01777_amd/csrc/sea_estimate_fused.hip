@@ -26,13 +26,12 @@
 #include "sea_lds.h"
 #include "sea_rowlanes.h"
 #include "sea_select.h"
+#include "sea_tile.h"
 
 namespace sea {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef short shortx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWRow = 72;  // halfwords per staged W row (128 B + 16 B pad): conflict-free b128 reads
 
@@ -373,23 +372,23 @@ __global__ __launch_bounds__(256) void wide_columns_kernel(Shape s, const float*
 // key side for columns of any width.  A block takes G consecutive columns of one head (G <= 16, about
 // 256 keys) and walks their keys in 16-key tiles; wave w owns a quarter of the features, whose rows of W
 // stay in registers as operands.  Column sums are matrix products as well: with the block's columns as
-// accumulator rows, sum[c][f] += onehot[c][key] phi[key][f], in fp32 (v_mfma_f32_16x16x4_f32: the
-// accumulator layout of the projection is the operand layout of this product, so phi goes from one to
+// accumulator rows, sum[c][f] += onehot[c][key] phi[key][f], phi as the sum of three bf16 values (sea_tile.h; the
+// accumulator layout of the projection is the operand layout of these products, so phi goes from one to
 // the other in place), and the accumulators stay in registers over the whole walk -- no width, alignment
 // or column boundary needs a case of its own.  Norms and columns of a 64-key step are taken once per
 // block (wave w: its 16 keys) and shared through LDS.
-// Causal: the same product over the ROUNDED features (bf16, one 16x16x16 product per 16 features) gives
-// the running sum of the current column; before each tile that a column began in front of, the sum of
-// that column's earlier keys goes out as fp32.
+// The first of the three, the ROUNDED features, has accumulators of its own (one 16x16x16 product per 16 features; the
+// other two share the slots of one 16x16x32 product).  Causal: those are the running sum of the current column; before
+// each tile that a column began in front of, the sum of that column's earlier keys goes out as fp32.
 // A key whose features are not finite must not leave its column (causal rows before it do not know it): a block
 // that finds such a sum takes its columns one by one.
-// Bound: issue of products that wait for each other (vector pipe 46 %, matrix pipe 25 % busy, 2.7 waves per SIMD that
-// wait to issue for half of their residency).  B = 8, H = 32, T = 2000, K = 256, m = 256: 0.09 ms, 0.28 ms with the
-// rows kernel and the selection (1.54 ms with the three kernels that write the features to memory).  Columns of
-// four keys or more (BY4) take two fp32 products per 16 features and keys instead of four: 93 -> 87 us there.  The
-// rows of the next tile and step are requested ahead.
+// Bound: vector issue, two thirds of the time (135 instructions per 16 keys and wave, 100 of them exponentials and the
+// splits), and the loads of W and of the first keys in front of nine tiles.  B = 8, H = 32, T = 2000, K = 256, m = 256,
+// padded by 0-25 %: 91.3 -> 88.6 us against sums in fp32 products (two per 16 features and keys where a lane's four keys were
+// added up per column first, four for narrow columns; half of the matrix pipe's time), T = 2001, m = 128, 48 heads
+// 19.6 -> 19.0.  The rows of the next tile and step are requested ahead.
 // ------------------------------------------------------------------------------------------
-template <int MC, bool CAUSAL, bool BY4>
+template <int MC, bool CAUSAL>
 __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg, const uint16_t* __restrict__ K,
                                                           const uint16_t* __restrict__ W, uint16_t* __restrict__ state,
                                                           float* __restrict__ pref, float c_dot, float c_norm,
@@ -416,12 +415,10 @@ __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg
     w0[ft] = *reinterpret_cast<const bf16x8*>(W + f * kHeadDim + 8 * lg);
     w1[ft] = *reinterpret_cast<const bf16x8*>(W + f * kHeadDim + 32 + 8 * lg);
   }
-  floatx4 sum[FT], rsum[CAUSAL ? FT : 1];
+  floatx4 rsum[FT], rest[FT];  // sums of the rounded features, and of what rounding took off
 #pragma unroll
-  for (int ft = 0; ft < FT; ++ft) sum[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if (CAUSAL)
-#pragma unroll
-    for (int ft = 0; ft < FT; ++ft) rsum[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int ft = 0; ft < FT; ++ft) rsum[ft] = rest[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const MinusOnes minus = minus_ones();
 
   const int32_t base = key0 & ~15;
   const int32_t nsteps = key1 > key0 ? (key1 - base + 63) / 64 : 0;
@@ -458,25 +455,9 @@ __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg
       const float4 bias = *reinterpret_cast<const float4*>(&bias_s[buf][16 * tile + 4 * lg]);
       const int4 cl = *reinterpret_cast<const int4*>(&col_s[buf][16 * tile + 4 * lg]);
       const float bv[4] = {bias.x, bias.y, bias.z, bias.w};
-      const float oh[4] = {cl.x == lr ? 1.f : 0.f, cl.y == lr ? 1.f : 0.f, cl.z == lr ? 1.f : 0.f, cl.w == lr ? 1.f : 0.f};
-      // BY4 (columns of at least four keys): the lane's four keys lie in one column or two; they are added up
-      // per column, weighted 0 or 1, and the products take the two sums
-      float in0[4], in1[4], oh0 = 0.f, oh1 = 0.f;
-      if (BY4) {
-        const int32_t second = cl.y != cl.x ? cl.y : (cl.z != cl.x ? cl.z : cl.w);
-        const int32_t c4[4] = {cl.x, cl.y, cl.z, cl.w};
-        oh0 = oh[0];
-        oh1 = second == lr && second != cl.x ? 1.f : 0.f;
-#pragma unroll
-        for (int i = 1; i < 4; ++i) {
-          in0[i] = c4[i] == cl.x ? 1.f : 0.f;
-          in1[i] = c4[i] == second ? 1.f : 0.f;  // (oh1 = 0 where that is the first column)
-        }
-      }
-      shortx4 ohb;
+      const uint2 oh = {(cl.x == lr ? 0x3f80u : 0u) | (cl.y == lr ? 0x3f800000u : 0u),
+                        (cl.z == lr ? 0x3f80u : 0u) | (cl.w == lr ? 0x3f800000u : 0u)};
       if (CAUSAL) {
-        const uint2 u = {pack_bf16(oh[0], oh[1]), pack_bf16(oh[2], oh[3])};
-        ohb = __builtin_bit_cast(shortx4, u);
         // keys of the tile's first column that lie before the tile: their sum is accumulator row lc
         const int32_t lc = col_s[buf][16 * tile];  // (uniform; -1: the column belongs to another block)
         if (lc >= 0 && column_start(cg, c0 + lc) < r0) {
@@ -489,27 +470,29 @@ __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg
           }
         }
       }
+      const uint4 oh2 = {oh.x, oh.y, oh.x, oh.y};
 #pragma unroll
       for (int ft = 0; ft < FT; ++ft) {
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
         acc = mfma16(k0, w0[ft], acc);
         acc = mfma16(k1, w1[ft], acc);
-        float v[4];
+        bf16x2 part[3][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, acc[i], -bv[i]));
-        if (BY4) {
-          const float a = fmaf(in0[3], v[3], fmaf(in0[2], v[2], fmaf(in0[1], v[1], v[0])));
-          const float c = fmaf(in1[3], v[3], fmaf(in1[2], v[2], in1[1] * v[1]));
-          sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh0, a, sum[ft], 0, 0, 0);
-          sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh1, c, sum[ft], 0, 0, 0);
-        } else {
+        for (int e = 0; e < 2; ++e) {
+          floatx2 f = {__builtin_amdgcn_exp2f(fmaf(c_dot, acc[2 * e], -bv[2 * e])),
+                       __builtin_amdgcn_exp2f(fmaf(c_dot, acc[2 * e + 1], -bv[2 * e + 1]))};
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sum[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(oh[i], v[i], sum[ft], 0, 0, 0);
+          for (int n = 0; n < 3; ++n) {
+            part[n][e] = __builtin_convertvector(f, bf16x2);
+            if (n < 2)
+              f = floatx2{__builtin_amdgcn_fdot2_f32_bf16(part[n][e], minus.lo, f[0], false),
+                          __builtin_amdgcn_fdot2_f32_bf16(part[n][e], minus.hi, f[1], false)};
+          }
         }
-        if (CAUSAL) {
-          const uint2 u = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-          rsum[ft] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ohb, __builtin_bit_cast(shortx4, u), rsum[ft], 0, 0, 0);
-        }
+        const bf16x4 rounded = __builtin_shufflevector(part[0][0], part[0][1], 0, 1, 2, 3);
+        const bf16x2 left[4] = {part[1][0], part[1][1], part[2][0], part[2][1]};
+        rsum[ft] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, oh), __builtin_bit_cast(shortx4, rounded), rsum[ft], 0, 0, 0);
+        rest[ft] = mfma16(__builtin_bit_cast(bf16x8, oh2), join_pairs(left), rest[ft]);
       }
     }
   }
@@ -517,7 +500,7 @@ __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg
 #pragma unroll
   for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) zero = fmaf(0.f, sum[ft][i], CAUSAL ? fmaf(0.f, rsum[CAUSAL ? ft : 0][i], zero) : zero);
+    for (int i = 0; i < 4; ++i) zero = fmaf(0.f, rsum[ft][i], fmaf(0.f, rest[ft][i], zero));
   if (__ballot(zero != 0.f) != 0ull) {
     // A feature that is not finite has reached every column of the block (zero times it): the wave's sums again,
     // column by column from the keys of each alone.
@@ -563,7 +546,7 @@ __global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (c0 + 4 * lg + i < c1)
-        state[(head * s.K + c0 + 4 * lg + i) * m + 16 * (wid * FT + ft) + lr] = f32_to_bf16(sum[ft][i]);
+        state[(head * s.K + c0 + 4 * lg + i) * m + 16 * (wid * FT + ft) + lr] = f32_to_bf16(rsum[ft][i] + rest[ft][i]);
 }
 
 // the 16 rows' selected columns as mask words
@@ -1345,12 +1328,10 @@ void launch_key_columns(const Shape& s, const uint16_t* K, const uint16_t* W, co
   const dim3 grid(static_cast<uint32_t>(s.N) * ((s.K + G - 1) / G));
   float* pref = reinterpret_cast<float*>(f.pref);
   const Columns cg = columns_of(s.T, s.K);
-#define SEA_KEY_COLUMNS(CAUSAL_, BY4_) \
-  hipLaunchKernelGGL((key_columns_kernel<MC, CAUSAL_, BY4_>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G)
-  if (s.causal && w0 >= 4) SEA_KEY_COLUMNS(true, true);
-  else if (s.causal) SEA_KEY_COLUMNS(true, false);
-  else if (w0 >= 4) SEA_KEY_COLUMNS(false, true);
-  else SEA_KEY_COLUMNS(false, false);
+#define SEA_KEY_COLUMNS(CAUSAL_) \
+  hipLaunchKernelGGL((key_columns_kernel<MC, CAUSAL_>), grid, dim3(256), 0, st, s, cg, K, W, f.state, pref, c_dot, c_norm, G)
+  if (s.causal) SEA_KEY_COLUMNS(true);
+  else SEA_KEY_COLUMNS(false);
 #undef SEA_KEY_COLUMNS
 }
 
