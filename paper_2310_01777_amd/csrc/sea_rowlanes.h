@@ -38,6 +38,12 @@ __device__ __forceinline__ float rows_sum(float x) {
   const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
+__device__ __forceinline__ float rows_max(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 // sum over the rows and, for each lane, the sum over the rows below its own (rows in order 0..3)
 __device__ __forceinline__ uint32_t rows_sum_prefix_u(uint32_t x, int lg, uint32_t* below) {
   const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);   // a[0]: even row of the pair, a[1]: odd
