@@ -6,18 +6,22 @@
 // an accumulator tile (lane = row l % 16, registers = channels 4 (l / 16) + i) packed in pairs is the
 // operand of the next layer, with contraction slot 8 g + e of a 32-channel step meaning channel
 // 16 (e / 4) + 4 g + e % 4; the weights of nu are parked in that order.  All weights live in LDS (148 KB for
-// K = 128: one block of eight waves per CU); more than 256 outputs of nu go through in slabs.
+// K = 128: one block of twelve waves per CU); more than 256 outputs of nu go through in slabs.
 // Z and the hidden layer are rounded to bf16 as the layers are defined.
 //
-// Bound: memory latency (reads 2 x 192, writes 8 K / 2 bytes per row; with one block per CU the waves wait for 58 % of
-// their residency and 2.3 TB/s are moved).  B = 4, H = 12, T = 2048, K = 128: 0.14 -> 0.04 ms; before, the concatenated rows, Z and the hidden layer made a round trip each and the scalers read Z again.
+// Bound: memory latency (reads 2 x 192, writes 8 K / 2 bytes per row; 3 TB/s are moved).  B = 4, H = 12, T = 2048, K = 128:
+// 0.14 -> 0.04 ms; before, the concatenated rows, Z and the hidden layer made a round trip each and the scalers read Z again.
+// Twelve waves with a CU's neighbouring tiles dealt to them, the next tile's rows requested into the registers that the
+// first layer has just read, against eight with a register set of their own for the next tile: 37.6 -> 31.7 us there (12
+// tiles per CU: one round instead of a full and a half one).  Tiles dealt over all blocks instead: 34.7, and the
+// convolution that follows waits for lines written by several XCDs (bidirectional layer 152 -> 158 us).
 #include "sea_decoder.h"
 
 namespace sea {
 namespace {
 
 constexpr int kCpDim = 128;   // [V_I; V] through the Performer: two value widths
-constexpr int kMlpWaves = 8, kMlpThreads = 64 * kMlpWaves;
+constexpr int kMlpWaves = 12, kMlpThreads = 64 * kMlpWaves;
 constexpr int kMuSteps = 6, kHidSteps = 4;     // contraction steps of 32: 192 and 128 channels
 constexpr int kNu1Tiles = 9;                   // 128 outputs + one tile for the scalers
 constexpr int kSlabTiles = 16;                 // 256 outputs of nu's last layer per slab
@@ -33,9 +37,10 @@ struct MlpArgs {
   int32_t H, T, Wd, C;
   int64_t rows;         // B T H
   int32_t out2;         // outputs of nu's last layer, 4 Wd
+  int64_t per_block;    // 32-row tiles of a block, neighbours
 };
 
-__global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
+__global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint4 mlp_lds[];
   uint4* w_mu = mlp_lds;                                  // [6][8][64]
   uint4* w_nu1 = w_mu + kMuSteps * 8 * 64;                // [4][9][64]
@@ -84,8 +89,7 @@ __global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
   };
   stage_nu2(0);
 
-  const int64_t ntile = (a.rows + 31) / 32;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kMlpWaves;
+  const int64_t first = blockIdx.x * a.per_block, end = min(first + a.per_block, (a.rows + 31) / 32);
   // rows in the order (b, t, h), heads fastest: a wave's stores lie next to each other in the image
   auto split = [&](int64_t pp, int32_t* h, int32_t* t, int32_t* b) {
     const int64_t q = pp / a.H;
@@ -93,7 +97,7 @@ __global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
     *b = static_cast<int32_t>(q / a.T);
     *t = static_cast<int32_t>(q - static_cast<int64_t>(*b) * a.T);
   };
-  bf16x8 nx[kMuSteps][2];
+  bf16x8 xf[kMuSteps][2];
   auto request = [&](int64_t tile) {
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
@@ -101,26 +105,22 @@ __global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
       split(min(tile * 32 + 16 * mt + lr, a.rows - 1), &h, &t, &b);
       const int64_t r = (static_cast<int64_t>(b) * a.H + h) * a.T + t;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) nx[ks][mt] = load8(a.Cp + r * kCpDim + 32 * ks + 8 * lg);
+      for (int ks = 0; ks < 4; ++ks) xf[ks][mt] = load8(a.Cp + r * kCpDim + 32 * ks + 8 * lg);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) nx[4 + ks][mt] = load8(a.V + r * kHeadDim + 32 * ks + 8 * lg);
+      for (int ks = 0; ks < 2; ++ks) xf[4 + ks][mt] = load8(a.V + r * kHeadDim + 32 * ks + 8 * lg);
     }
   };
-  const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * kMlpWaves + wid;
-  if (tile0 < ntile) request(tile0);
+  const int64_t tile0 = first + wid;
+  if (tile0 < end) request(tile0);
   __syncthreads();
   // with one slab the loop has no barrier and a wave without a tile leaves it; with several, every wave of
   // the block stays for the barriers of the staging (the first wave's tile is the smallest)
-  for (int64_t tile = tile0; slabs == 1 ? tile < ntile : tile - wid < ntile; tile += stride) {
-    const bool on = tile < ntile;  // wave-uniform
+  for (int64_t tile = tile0; slabs == 1 ? tile < end : tile - wid < end; tile += kMlpWaves) {
+    const bool on = tile < end;  // wave-uniform
     bf16x8 zf[kHidSteps][2];
     int64_t orow[2];
     bool live[2], exists[2];
     if (on) {
-      bf16x8 xf[kMuSteps][2];
-#pragma unroll
-      for (int ks = 0; ks < kMuSteps; ++ks) { xf[ks][0] = nx[ks][0]; xf[ks][1] = nx[ks][1]; }
-      if (tile + stride < ntile) request(tile + stride);
       // mu, two 16-channel tiles at a time
 #pragma unroll
       for (int kc = 0; kc < kHidSteps; ++kc) {
@@ -141,6 +141,7 @@ __global__ __launch_bounds__(kMlpThreads, 2) void dec_mlp_kernel(MlpArgs a) {
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) zf[kc][mt] = pack8(relu4(acc[0][mt]), relu4(acc[1][mt]));
       }
+      if (tile + kMlpWaves < end) request(tile + kMlpWaves);  // the rows have left their registers
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
         const int64_t pp = tile * 32 + 16 * mt + lr;
@@ -233,8 +234,10 @@ hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const u
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dec_mlp_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;
-  const int64_t blocks = ((a.rows + 31) / 32 + kMlpWaves - 1) / kMlpWaves;
-  hipLaunchKernelGGL(dec_mlp_kernel, dim3(static_cast<uint32_t>(std::min<int64_t>(256, blocks))), dim3(kMlpThreads), lds, st, a);
+  // an equal share of the tiles for each CU: small launches use all of them, with few waves each
+  const int64_t tiles = (a.rows + 31) / 32;
+  a.per_block = (tiles + 255) / 256;
+  hipLaunchKernelGGL(dec_mlp_kernel, dim3(static_cast<uint32_t>((tiles + a.per_block - 1) / a.per_block)), dim3(kMlpThreads), lds, st, a);
   return hipGetLastError();
 }
 
