@@ -107,23 +107,12 @@ __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
-// exponent arguments (log2 domain) of 16 rows x m features: arg[ft][i] for feature 16 ft + 4 lg + i
-template <int MC>
-__device__ __forceinline__ void project(const uint16_t* Ws, bf16x8 x0, bf16x8 x1, int lr, int lg,
-                                        float c_dot, float bias, floatx4 (&arg)[2 * MC]) {
-#pragma unroll
-  for (int ft = 0; ft < 2 * MC; ++ft) {
-    const uint16_t* w = &Ws[(ft * 16 + lr) * kWRow + 8 * lg];
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma16(*reinterpret_cast<const bf16x8*>(w), x0, acc);
-    acc = mfma16(*reinterpret_cast<const bf16x8*>(w + 32), x1, acc);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) arg[ft][i] = fmaf(c_dot, acc[i], -bias);
-  }
-}
-
 // ------------------------------------------------------------------------------------------
 // key side: state[c] = bf16( sum over the keys of column c of phi(k_j) ), in fragment order.
+// Bound: vector issue (an exponential and a multiply-add per key and feature, 40 % of the instructions).  W straight to LDS in
+// unpadded rows, so that a CU holds a fourth block at m = 256 (three before, with twice the registers), and a tile's rows on
+// their way under the tile before: 256 heads of 2048 keys, m = 256, 48.6 -> 40.9 us, 32 of 32768 85.9 -> 80.1, 12 of 131072,
+// m = 128, 64.1 -> 60.6, 48 of 2048 7.0 -> 6.3.  (Two places for the sums in turn and one barrier less per tile: the same.)
 // Block = 4 waves = 64 keys of one head (8 waves = 128 keys for 128-key columns, so that a column
 // never spans two blocks; wider columns are finished by wide_columns_kernel).  WLOG = log2(column
 // width), 0..7.
@@ -134,20 +123,24 @@ __device__ __forceinline__ void project(const uint16_t* Ws, bf16x8 x0, bf16x8 x1
 // and three additions for four tiles), and no feature array is kept in registers.  Sums meet in LDS (one m-vector per wave and column part) and leave as
 // coalesced bf16 rows.
 // ------------------------------------------------------------------------------------------
+// W rows lie without padding, pieces exchanged as in the rows kernel: four blocks of four waves share a CU at m = 256.
+constexpr int key_waves(int WLOG) { return WLOG > 6 ? 8 : 4; }  // per block
 template <int MC, int WLOG>
-__global__ __launch_bounds__(WLOG > 6 ? 512 : 256) void key_state_kernel(
+__global__ __launch_bounds__(64 * key_waves(WLOG), MC == 8 && WLOG > 2 && WLOG < 7 ? 4 : 1) void key_state_kernel(
     Shape s, const uint16_t* __restrict__ K, const uint16_t* __restrict__ W, uint16_t* __restrict__ state,
     uint16_t* __restrict__ pref, float* __restrict__ bsum_u, float* __restrict__ bsum_r, float c_dot,
     float c_norm, int32_t iters) {
   constexpr int m = 32 * MC;
   constexpr int w = 1 << WLOG;
-  constexpr int kWaves = w > 64 ? w / 16 : 4;  // waves per block
+  constexpr int kWaves = key_waves(WLOG);
   constexpr int kRows = 16 * kWaves;
   constexpr int kPartsWave = (w >= 4 && w < 16) ? 16 / w : 1;  // column sums a wave leaves in LDS
   constexpr int kSlots = kWaves * kPartsWave;
-  __shared__ __attribute__((aligned(16))) uint16_t Ws[m * kWRow];
-  __shared__ float part[w >= 4 ? kSlots * m : 1];   // per wave and column part
-  __shared__ __attribute__((aligned(16))) float tpart[w > 16 ? kWaves * m : 1];  // per wave, over the bf16-rounded features
+  __shared__ __attribute__((aligned(16))) uint16_t Ws[m * kHeadDim];
+  // sums per wave and column part, and sums of the wave's bf16-rounded features
+  constexpr int kParts = w >= 4 ? kSlots * m : 0, kRounded = w > 16 ? kWaves * m : 0;
+  __shared__ __attribute__((aligned(16))) float part[kParts + kRounded > 0 ? kParts + kRounded : 1];
+  float* const tpart = part + kParts;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
@@ -156,15 +149,30 @@ __global__ __launch_bounds__(WLOG > 6 ? 512 : 256) void key_state_kernel(
   const uint32_t bph = (tiles + iters - 1) / iters;  // blocks per head
   const int64_t head = blockIdx.x / bph;
   const uint32_t tile_first = (blockIdx.x % bph) * iters;
-  for (int x = tid; x < m * 8; x += 64 * kWaves) {
-    const int r = x >> 3, part8 = x & 7;
-    *reinterpret_cast<uint4*>(&Ws[r * kWRow + part8 * 8]) =
-        *reinterpret_cast<const uint4*>(W + r * kHeadDim + part8 * 8);
+  bf16x8 y0, y1;  // the next tile's rows
+  auto request = [&](uint32_t tile) __attribute__((always_inline)) {
+    const uint16_t* X = K + (head * s.T + min(static_cast<int32_t>(tile) * kRows + 16 * wid + lr, s.T - 1)) * kHeadDim;
+    y0 = *reinterpret_cast<const bf16x8*>(X + 8 * lg);
+    y1 = *reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg);
+  };
+  {
+    const u32x4 Wres = buffer_words(W, m * kHeadDim * 2);
+    const uint32_t woff = (tid >> 3) * (kHeadDim * 2) + 16 * ((tid & 7) ^ ((tid >> 3) & 7));
+    if ((Wres[0] & 3u) == 0u) {
+#pragma unroll
+      for (int q = 0; q < m / (8 * kWaves); ++q) buffer_load_lds16(Wres, Ws + (q * kWaves + wid) * 512, woff + q * 1024u * kWaves);
+    } else {
+#pragma unroll 1
+      for (int q = 0; q < m / (8 * kWaves); ++q) buffer_load_lds16_odd(Wres, Ws + (q * kWaves + wid) * 512, woff + q * 1024u * kWaves);
+    }
   }
+  lds_loads_done();
+  request(tile_first);  // (behind W, which would wait for them)
   __syncthreads();
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
-  for (uint32_t tile = tile_first; tile < min(tile_first + static_cast<uint32_t>(iters), tiles); ++tile) {
+  const uint32_t tile_end = min(tile_first + static_cast<uint32_t>(iters), tiles);
+  for (uint32_t tile = tile_first; tile < tile_end; ++tile) {
   if (tile != tile_first) __syncthreads();  // the sums of the previous tile have left LDS
   const int32_t blk_r0 = static_cast<int32_t>(tile) * kRows;
   const int32_t r0 = blk_r0 + wid * 16;
@@ -181,9 +189,8 @@ __global__ __launch_bounds__(WLOG > 6 ? 512 : 256) void key_state_kernel(
     }
   } else {
   // operand rows: key r0 + lr; accumulator rows: keys r0 + 4 lg + i
-  const uint16_t* X = K + (head * s.T + min(r0 + lr, s.T - 1)) * kHeadDim;
-  const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(X + 8 * lg);
-  const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(X + 32 + 8 * lg);
+  const bf16x8 x0 = y0, x1 = y1;
+  if (tile + 1 < tile_end) request(tile + 1);
   float nx = sumsq8(x0) + sumsq8(x1);
   nx += __shfl_xor(nx, 16, kWave);
   nx += __shfl_xor(nx, 32, kWave);  // |k|^2 of key lr, in every lane group
@@ -203,16 +210,16 @@ __global__ __launch_bounds__(WLOG > 6 ? 512 : 256) void key_state_kernel(
   static_assert((2 * MC) % 4 == 0, "feature tiles in groups of four");
   // slot of this lane's feature in a fragment-ordered row, for the tile its lane group ends up with
   const int slot_lane = 8 * (lr >> 2) + (lr & 3);
+  const int wat0 = lr * kHeadDim + 8 * (lg ^ (lr & 7)), wat1 = lr * kHeadDim + 8 * ((lg + 4) ^ (lr & 7));
 #pragma unroll
   for (int ft0 = 0; ft0 < 2 * MC; ft0 += 4) {
     float sum4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int ft = ft0 + q;
-      const uint16_t* wr = &Ws[(ft * 16 + lr) * kWRow + 8 * lg];
       floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-      acc = mfma16(x0, *reinterpret_cast<const bf16x8*>(wr), acc);
-      acc = mfma16(x1, *reinterpret_cast<const bf16x8*>(wr + 32), acc);
+      acc = mfma16(x0, *reinterpret_cast<const bf16x8*>(Ws + ft * 16 * kHeadDim + wat0), acc);
+      acc = mfma16(x1, *reinterpret_cast<const bf16x8*>(Ws + ft * 16 * kHeadDim + wat1), acc);
       float v[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_exp2f(fmaf(c_dot, acc[i], -bias[i]));
@@ -1308,11 +1315,15 @@ void launch_rows(const Shape& s, const uint16_t* Q, const uint16_t* K, const uin
 template <int MC, int WLOG>
 void launch_key(const Shape& s, const uint16_t* K, const uint16_t* W, const FusedPtrs& f, float c_dot,
                 float c_norm, hipStream_t st) {
-  constexpr int kKeyWaves = (1 << WLOG) > 64 ? (1 << WLOG) / 16 : 4;
+  constexpr int kKeyWaves = key_waves(WLOG);
   const uint32_t ktiles = (s.T + 16 * kKeyWaves - 1) / (16 * kKeyWaves);
-  // tiles per block: as many as leave about eight blocks per CU
-  int32_t iters = static_cast<int32_t>((static_cast<int64_t>(s.N) * ktiles) / 2048);
-  iters = iters < 1 ? 1 : (iters > 8 ? 8 : iters);
+  // Tiles per block: as many as make one round of blocks where a block is short (eight blocks of four waves on a CU, three of
+  // eight: 12 heads of 131072 keys 60.6 -> 55.8 us against eight blocks per CU, 384 of 512 12.3 -> 11.4), two rounds and more
+  // at m = 256, where the rows kernel then starts under the last blocks (32 heads of 32768 keys 80.1 against 83.4 us in
+  // one round, 256 of 2048 40.9 / 42.7).
+  constexpr int kPerCu = kKeyWaves == 8 && MC < 8 ? 3 : 8;
+  const int64_t all = static_cast<int64_t>(s.N) * ktiles;
+  const int32_t iters = static_cast<int32_t>(std::min<int64_t>(32, (all + 256 * kPerCu - 1) / (256 * kPerCu)));
   const uint32_t bph = (ktiles + iters - 1) / iters;
   hipLaunchKernelGGL((key_state_kernel<MC, WLOG>), dim3(static_cast<uint32_t>(s.N) * bph), dim3(64 * kKeyWaves), 0, st,
                      s, K, W, f.state, f.pref, f.bsum_u, f.bsum_r, c_dot, c_norm, iters);
