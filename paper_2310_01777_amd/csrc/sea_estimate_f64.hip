@@ -64,10 +64,15 @@ __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_ca
 // NFT > 0: the exponent arguments of the wave's (at most NFT) feature tiles stay in registers between the
 // projection and the exponential, and the unrolled tile loop lets the loads of W run ahead;
 // NFT = 0: any m, the arguments take a round trip through the output buffer.
-template <int NFT, int WPT>
+// COLS (whole columns of 1, 2, 4, 8 or 16 keys to a tile, 2^wl each): the column sums leave as well, and phi(K) leaves as
+// its running sums inside the columns, which is what the rows kernel takes (bidirectional layers: not at all); a kernel of their
+// own took 7 us of a layer of 12 heads of 1024 rows, most of it its launch.
+template <int NFT, int WPT, bool COLS = false>
 __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float* __restrict__ Q,
                                                            const float* __restrict__ K, const float* __restrict__ W,
-                                                           double* __restrict__ phiQ, double* __restrict__ phiK) {
+                                                           double* __restrict__ phiQ, double* __restrict__ phiK,
+                                                           double* __restrict__ stateT, int32_t wl) {
+  static_assert(!COLS || NFT > 0, "the features stay in registers");
   __shared__ double rowmax[4][16];
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
@@ -99,6 +104,11 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
     double* const to = (which ? phiK : phiQ) + (head * s.T + r0) * s.m;
     const int32_t n = min(16, s.T - r0) * s.m;
     for (int32_t x = WPT == 4 ? threadIdx.x : lane; x < n; x += WPT == 4 ? 256 : 64) to[x] = 0.0;
+    if (COLS && which) {
+      const int32_t cols = 16 >> wl;
+      for (int32_t x = WPT == 4 ? threadIdx.x : lane; x < s.m * cols; x += WPT == 4 ? 256 : 64)
+        stateT[(head * s.m + x / cols) * s.K + (r0 >> wl) + x % cols] = 0.0;
+    }
     return;
   }
   // this lane's four result rows are tokens r0 + 4 i + lg
@@ -163,10 +173,44 @@ __global__ __launch_bounds__(256) void features_f64_kernel(Shape s, const float*
 #pragma unroll
     for (int f = 0; f < NFT; ++f) {
       if (WPT * f + part < ntiles) {
+        const int32_t feature = (WPT * f + part) * 16 + lr;
+        if (COLS && which) {
+          double v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int32_t t = r0 + 4 * i + lg;
-          if (t < s.T) out[static_cast<int64_t>(t) * s.m + (WPT * f + part) * 16 + lr] = t < len ? exp_f64(arg[f][i] - shift[i]) : 0.0;
+          for (int i = 0; i < 4; ++i) v[i] = r0 + 4 * i + lg < len ? exp_f64(arg[f][i] - shift[i]) : 0.0;
+          // inclusive sums over the tokens 4 i + lg of a column: over lane groups, then over registers
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (wl >= 1) {
+              const double below = __shfl_xor(v[i], 16, kWave);
+              v[i] += (lg & 1) ? below : 0.0;
+            }
+            if (wl >= 2) {
+              const double below = __shfl(v[i], lr + 16, kWave);
+              v[i] += (lg & 2) ? below : 0.0;
+            }
+          }
+          if (wl >= 3) {
+            v[1] += __shfl(v[0], lr + 48, kWave);
+            v[3] += __shfl(v[2], lr + 48, kWave);
+          }
+          if (wl == 4) {
+            const double below = __shfl(v[1], lr + 48, kWave);
+            v[2] += below;
+            v[3] += below;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int32_t t = r0 + 4 * i + lg;
+            if (((t + 1) & ((1 << wl) - 1)) == 0) stateT[(head * s.m + feature) * s.K + (t >> wl)] = v[i];
+            if (s.causal) out[static_cast<int64_t>(t) * s.m + feature] = v[i];
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int32_t t = r0 + 4 * i + lg;
+            if (t < s.T) out[static_cast<int64_t>(t) * s.m + feature] = t < len ? exp_f64(arg[f][i] - shift[i]) : 0.0;
+          }
         }
       }
     }
@@ -415,18 +459,32 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
   }
 }
 
+template <int NFT, int WPT>
+void start_features(const Shape& s, dim3 grid, const float* Q, const float* K, const float* W, double* phiQ, double* phiK,
+                    double* stateT, int32_t wl, hipStream_t st) {
+  if constexpr (NFT > 0) {
+    if (stateT) {
+      hipLaunchKernelGGL((features_f64_kernel<NFT, WPT, true>), grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK, stateT, wl);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((features_f64_kernel<NFT, WPT>), grid, dim3(256), 0, st, s, Q, K, W, phiQ, phiK, nullptr, 0);
+}
+// (stateT: the column sums of columns of 2^wl keys, from features_in_columns layers)
 void launch_features(const Shape& s, const float* Q, const float* K, const float* W, double* phiQ, double* phiK,
-                     hipStream_t st) {
+                     double* stateT, int32_t wl, hipStream_t st) {
   const int64_t tiles = 2 * static_cast<int64_t>(s.N) * ((s.T + 15) / 16);
   const dim3 split(static_cast<uint32_t>(tiles)), whole(static_cast<uint32_t>((tiles + 3) / 4));
-  if (s.m <= 128 && tiles >= (s.m <= 64 ? 2048 : 3072))
-    hipLaunchKernelGGL((features_f64_kernel<8, 1>), whole, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
-  else if (s.m <= 128)
-    hipLaunchKernelGGL((features_f64_kernel<2, 4>), split, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
-  else if (s.m <= 256)
-    hipLaunchKernelGGL((features_f64_kernel<4, 4>), split, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
-  else
-    hipLaunchKernelGGL((features_f64_kernel<0, 4>), split, dim3(256), 0, st, s, Q, K, W, phiQ, phiK);
+  if (s.m <= 128 && tiles >= (s.m <= 64 ? 2048 : 3072)) start_features<8, 1>(s, whole, Q, K, W, phiQ, phiK, stateT, wl, st);
+  else if (s.m <= 128) start_features<2, 4>(s, split, Q, K, W, phiQ, phiK, stateT, wl, st);
+  else if (s.m <= 256) start_features<4, 4>(s, split, Q, K, W, phiQ, phiK, stateT, wl, st);
+  else start_features<0, 4>(s, split, Q, K, W, phiQ, phiK, nullptr, 0, st);
+}
+// log2 of the keys per column where 16-key tiles hold whole columns and the features stay in registers, else -1
+int32_t features_in_columns(const Shape& s) {
+  if (s.T % 16 != 0 || s.T % s.K != 0 || s.m > 256) return -1;
+  const int32_t w = s.T / s.K;
+  return w <= 16 && (w & (w - 1)) == 0 ? __builtin_ctz(w) : -1;
 }
 
 }  // namespace
@@ -435,7 +493,7 @@ void launch_features(const Shape& s, const float* Q, const float* K, const float
 hipError_t launch_features_f64(const Shape& s, const float* Q, const float* K, const float* W, double* phiQ,
                                double* phiK, hipStream_t st) {
   if (s.m % 16 != 0) return hipErrorNotSupported;
-  launch_features(s, Q, K, W, phiQ, phiK, st);
+  launch_features(s, Q, K, W, phiQ, phiK, nullptr, 0, st);
   return hipGetLastError();
 }
 
@@ -451,11 +509,12 @@ hipError_t launch_estimate_f64(const Shape& s, const float* Q, const float* K, c
   double* phiQ = static_cast<double*>(ws);
   double* phiK = phiQ + ntm;
   double* stateT = phiK + ntm;
+  const int32_t wl = features_in_columns(s);
   {
     StageScope scope(SEA_STAGE_FEATURES, st);
-    launch_features(s, Q, K, W, phiQ, phiK, st);
+    launch_features(s, Q, K, W, phiQ, phiK, wl >= 0 ? stateT : nullptr, wl, st);
   }
-  {
+  if (wl < 0) {
     StageScope scope(SEA_STAGE_STATE, st);
     const int64_t total = static_cast<int64_t>(s.N) * s.K * s.m;
     hipLaunchKernelGGL(state_f64_kernel, dim3(static_cast<uint32_t>((total + 255) / 256)), dim3(256),
