@@ -131,11 +131,11 @@ bool bits_attn_supported(const Shape& s, sea_dtype dt) {
 }
 
 hipError_t launch_bits_attn(const Shape& s, const void* Q, const void* K, const void* V, const uint32_t* mbits,
-                            void* O, void* ws, hipStream_t st, bool counted = false) {
+                            void* O, void* ws, hipStream_t st, BucketCounts have = BucketCounts::none) {
   const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K),
                  *v = static_cast<const uint16_t*>(V);
   if (tile_attn_supported(s, SEA_BF16, nullptr))
-    return launch_tile_attn(s, q, k, v, mbits, static_cast<uint16_t*>(O), ws, st, counted);
+    return launch_tile_attn(s, q, k, v, mbits, static_cast<uint16_t*>(O), ws, st, have);
   return launch_column_attn(s, q, k, v, mbits, static_cast<uint16_t*>(O), st);
 }
 
@@ -394,9 +394,11 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
     uint32_t* mbits = mhat_opt ? mhat_opt : reinterpret_cast<uint32_t*>(w);
     w += align256(rows * ((s.K + 31) / 32) * sizeof(uint32_t));
     const bool need_lists = sel_opt || idx_opt || cnt_opt;
-    int32_t* counts = nullptr;  // rows per column, where the estimator counts them for the attention's buckets
+    BucketCounts have = BucketCounts::none;
     if (estimate_fused_supported(s) && s.grouping == 0) {
-      if (estimate_counts_columns(s)) counts = clear_bucket_counts(s, w, st);
+      // rows per column, which the estimator zeroes or counts for the attention's buckets
+      int32_t* const counts = bucket_counts(s, w);
+      if (counts) have = estimate_counts_columns(s);
       // estimate and per-row top-k^ in one kernel; the scores never leave the registers
       e = launch_estimate_fused(s, static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
                                 static_cast<const uint16_t*>(W), (A_hat_opt || need_lists) ? A_hat : nullptr,
@@ -414,7 +416,7 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
       e = launch_topk_mask(s, A_hat, sel_opt, idx_opt, cnt_opt, mbits, st);
     }
     if (e != hipSuccess) return fail_hip(e);
-    e = launch_bits_attn(s, Q, K, V, mbits, O, w, st, counts != nullptr);
+    e = launch_bits_attn(s, Q, K, V, mbits, O, w, st, have);
     return e == hipSuccess ? SEA_OK : fail_hip(e);
   }
   // per-row widths, no row lists wanted: the estimator selects and writes the key bits itself

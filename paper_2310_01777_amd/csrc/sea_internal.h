@@ -56,8 +56,9 @@ size_t estimate_fused_workspace(const Shape& s);
 // nullptr; at least one should be given
 hipError_t launch_estimate_fused(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W,
                                  float* A_hat, uint32_t* mbits, void* ws, hipStream_t st, int32_t* counts = nullptr);
-// layers whose rows kernel adds the rows that selected each column to counts [N][K] (given with mbits)
-bool estimate_counts_columns(const Shape& s);
+// what launch_estimate_fused does with the rows per column it is given (counts [N][K], with mbits)
+enum class BucketCounts { none, zeroed, counted };
+BucketCounts estimate_counts_columns(const Shape& s);
 
 // per-row width geometry (causal, m in {64,128,256}); fp32 tensors: fp64 features, tiles on the fp64 matrix
 // cores or a prefix table of phi(K); bf16 tensors: the bf16 matrix-core form below
@@ -107,10 +108,10 @@ bool tile_attn_f32_structured(const Shape& s);  // of these, K | T and a power-o
 hipError_t launch_tile_attn_f32(const Shape& s, const float* Q, const float* K, const float* V,
                                 const uint32_t* mbits, float* O, hipStream_t st);
 hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
-                            const uint32_t* mbits, uint16_t* O, void* ws, hipStream_t st, bool counted = false);
-// Rows per column in the workspace of launch_tile_attn, cleared on the stream; nullptr where it groups no rows by column.
-// Whoever fills them passes counted = true.
-int32_t* clear_bucket_counts(const Shape& s, void* ws, hipStream_t st);
+                            const uint32_t* mbits, uint16_t* O, void* ws, hipStream_t st, BucketCounts have = BucketCounts::none);
+// Rows per column [N][K] in the workspace of launch_tile_attn, which needs them zeroed and then counted; nullptr where it groups
+// no rows by column.
+int32_t* bucket_counts(const Shape& s, void* ws);
 size_t dense_attn_workspace(const Shape& s);
 
 // per-row lists (crow == nullptr: idx [N][T][L], cnt [N][T]) or the FlatCSR tensor (crow [B T + 1],

@@ -970,16 +970,13 @@ size_t tile_attn_workspace(const Shape& s) {
   return bucket_layout(s).total;
 }
 
-int32_t* clear_bucket_counts(const Shape& s, void* ws, hipStream_t st) {
+int32_t* bucket_counts(const Shape& s, void* ws) {
   if (!tile_attn_supported(s, SEA_BF16, nullptr) || !bucket_mode(s)) return nullptr;
-  int32_t* const cnt = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bucket_layout(s).cnt);
-  const int64_t n = static_cast<int64_t>(s.N) * s.K;
-  hipLaunchKernelGGL(zero_i32_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, st, cnt, n);
-  return cnt;
+  return reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bucket_layout(s).cnt);
 }
 
 hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
-                            const uint32_t* mbits, uint16_t* O, void* ws, hipStream_t st, bool counted) {
+                            const uint32_t* mbits, uint16_t* O, void* ws, hipStream_t st, BucketCounts have) {
   int32_t rlog = 0;
   if (!tile_attn_supported(s, SEA_BF16, &rlog)) return hipErrorNotSupported;
   const int32_t w = s.T / s.K, r = 1 << rlog;
@@ -996,13 +993,16 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
     int32_t* cstart = reinterpret_cast<int32_t*>(base + lay.cstart);
     int32_t* chunk_col = reinterpret_cast<int32_t*>(base + lay.chunk_col);
     const bool multi = s.k_hat > 1;
-    if (!counted) clear_bucket_counts(s, ws, st);
+    if (have == BucketCounts::none) {
+      const int64_t n = static_cast<int64_t>(s.N) * s.K;
+      hipLaunchKernelGGL(zero_i32_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, st, cnt, n);
+    }
     uint16_t* O_zero = multi ? nullptr : O;
     auto grid_of = [&](int rpt) { return dim3((s.T + 256 * rpt - 1) / (256 * rpt), static_cast<uint32_t>(s.N)); };
     // rows per thread: eight entries, fewer where that leaves less than two blocks per CU
     const int64_t rows256 = static_cast<int64_t>(s.N) * ((s.T + 255) / 256);
     const int rpt = rows256 >= 8 * 512 ? 8 : (rows256 >= 2 * 512 ? 2 : 1);
-    if (counted) {  // (by the kernel that selected the columns)
+    if (have == BucketCounts::counted) {  // (by the kernel that selected the columns)
     } else if (rpt == 8) hipLaunchKernelGGL(bucket_count_kernel<8>, grid_of(8), dim3(256), s.K * sizeof(int32_t), st, mbits, cnt, s.T, KW, s.K, s.k_hat);
     else if (rpt == 2) hipLaunchKernelGGL(bucket_count_kernel<2>, grid_of(2), dim3(256), s.K * sizeof(int32_t), st, mbits, cnt, s.T, KW, s.K, s.k_hat);
     else hipLaunchKernelGGL(bucket_count_kernel<1>, grid_of(1), dim3(256), s.K * sizeof(int32_t), st, mbits, cnt, s.T, KW, s.K, s.k_hat);
