@@ -1,5 +1,6 @@
 #pragma once
 #include "sea_rowlanes.h"
+#include "sea_search.h"
 
 namespace sea {
 
@@ -82,12 +83,7 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
   // exactly for keys below the trial; a byte permute spreads each sign over a byte, four differences at a time, and
   // the matrix product adds the bytes up.  The trial's low half is zero in that phase, so the counts are those of the
   // full keys.
-  // A row keeps `lo` with a keys more than its quota at or above it and `hi` with b keys fewer (b + 1/4 while hi is only
-  // known from `top`).  Bit patterns are a logarithmic scale, on which a row's scores are spread evenly enough for the next
-  // trial to come from a and b: 0.15 to 0.85 of the way (every step takes at least that off the range), at most eight octaves
-  // at a time.  Done when a row has its quota, one key more or one fewer.  Steps for the slowest of 16 rows, bit by bit
-  // (until the quota or one more) / so: c4 at T = 32768 11.2 / 6.4, c3 11.8 / 7.4, c2 10.6 / 5.8, c5 9.0 / 5.0, one sentence
-  // 7.3 / 3.1; weights of 0.6 to 0.9 and four to twelve octaves are within a tenth of that, halving takes 7 to 9.
+  // Trials between two counts (RowSearch); done when a row has its quota, one key more or one fewer.
 #define SEA_SEARCH(NT_)                                                                          \
   {                                                                                              \
     ushort2v hp[2 * (NT_)];                                                                      \
@@ -122,21 +118,15 @@ __device__ __forceinline__ void select_columns(const uint32_t (&key)[NCT][4], ui
     };                                                                                           \
     /* (rows without a quota start with nothing to search; whole numbers below 2^16 throughout) */ \
     const float over = static_cast<float>(16 * (NT_)) - static_cast<float>(nsel);                \
-    float lo = nsel != 0u ? 32768.f : top - 1.f, hi = top;                                       \
-    float a = static_cast<float>(ncnd) - static_cast<float>(nsel), b = static_cast<float>(nsel) + 0.25f; \
-    _Pragma("unroll 1") while (__ballot(a > 1.f && b != 1.f && hi - lo > 1.f) != 0ull) {         \
-      const float part = fmaf(b * __builtin_amdgcn_rcpf(a + b), 0.7f, 0.15f);                    \
-      const float trial = truncf(fmaxf(fmaf(-part, fminf(hi - lo, 1024.f), hi), lo + 1.f));      \
-      const float d = over - static_cast<float>(count_below(static_cast<uint32_t>(trial)));      \
-      const bool enough = d >= 0.f;                                                              \
-      lo = enough ? trial : lo;                                                                  \
-      hi = enough ? hi : trial;                                                                  \
-      a = enough ? d : a;                                                                        \
-      b = enough ? b : -d;                                                                       \
+    RowSearch row = {nsel != 0u ? 32768.f : top - 1.f, top, static_cast<float>(ncnd) - static_cast<float>(nsel), \
+                     static_cast<float>(nsel) + 0.25f};                                          \
+    _Pragma("unroll 1") for (int32_t step = 0; __ballot(row.pending()) != 0ull; ++step) {        \
+      const float trial = row.trial(step, __builtin_amdgcn_rcpf(row.a + row.b));                 \
+      row.counted(trial, over - static_cast<float>(count_below(static_cast<uint32_t>(trial))));  \
     }                                                                                            \
-    lacking = a > 1.f && b == 1.f && nsel != 0u;                                                 \
-    cge = lacking ? nsel : nsel + static_cast<uint32_t>(a);                                      \
-    tau = static_cast<uint32_t>(lacking ? hi : lo) << 16;                                        \
+    lacking = row.a > 1.f && row.b == 1.f && nsel != 0u;                                         \
+    cge = lacking ? nsel : nsel + static_cast<uint32_t>(row.a);                                  \
+    tau = static_cast<uint32_t>(lacking ? row.hi : row.lo) << 16;                                \
   }                                                                                              \
   /* rows with several keys of one high half around their quota: bits 15..0 on whole keys */     \
   _Pragma("unroll 1") for (int bit = 15; bit >= 0; --bit) {                                       \
