@@ -1061,11 +1061,10 @@ constexpr int kBidirWaves = 8, kBidirBlocks = 512;  // two blocks per CU
 __device__ __forceinline__ floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
-template <int MC, int NCT, bool SCORES>
-__global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,
+template <int MC, int NCT>
+__global__ __launch_bounds__(64 * kBidirWaves, 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                                                   const uint16_t* __restrict__ W,
                                                                                   const uint16_t* __restrict__ state,
-                                                                                  float* __restrict__ A_hat,
                                                                                   uint32_t* __restrict__ mbits,
                                                                                   int32_t* __restrict__ counts, float c_dot,
                                                                                   float c_norm, Columns cg) {
@@ -1207,16 +1206,22 @@ __global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_row
       const auto both = __builtin_amdgcn_permlane32_swap(cnt, cnt, false, false);
       // 2^-100 < largest < 2^100, and no other within 2^-22 of it
       const bool plain = both[0] + both[1] == 1u && top - 0x0d800000u < 0x71800000u - 0x0d800000u;
-      if (SCORES || __ballot(!plain) != 0ull) {
-        float r = 0.f;
+      if (__ballot(!plain) != 0ull) {
+        // The row's sum in the order of the kernel above, whose lane group 2 (j % 2) + g holds the columns of registers 4 j ..:
+        // whole tiles of 16 columns by fours, the one with the last column, and all of them in the last rows, one by one.
+        float rs[2] = {0.f, 0.f};
 #pragma unroll 1
         for (int ct = 0; ct < kTiles; ++ct) {
           floatx16 a[1];
           scores(ct, a);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) r += a[0][i];
+          for (int j = 0; j < 4; ++j) {
+            const float x0 = a[0][4 * j], x1 = a[0][4 * j + 1], x2 = a[0][4 * j + 2], x3 = a[0][4 * j + 3];
+            const float fours = rs[j & 1] + ((x0 + x1) + (x2 + x3)), ones = (((rs[j & 1] + x0) + x1) + x2) + x3;
+            rs[j & 1] = (trow | 15) >= s.T || 2 * ct + (j >> 1) >= (ncnd - 1) >> 4 ? ones : fours;
+          }
         }
-        r += __shfl_xor(r, 32, kWave);
+        const float r = (rs[0] + __shfl_xor(rs[0], 32, kWave)) + (rs[1] + __shfl_xor(rs[1], 32, kWave));
         const float ninv = r > 0.f ? -1.f / r : -0.f;  // (as in finish_rows: the negated score is the key)
         top = 0u;
         marks[0] = marks[1] = 0u;
@@ -1229,9 +1234,7 @@ __global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_row
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int32_t c = 32 * ct + 8 * (i >> 2) + 4 * g + (i & 3);
-            const float x = a[i] * ninv;
-            if (SCORES && c < s.K && trow < s.T) A_hat[(static_cast<int64_t>(head) * s.T + trow) * s.K + c] = -x;
-            a[i] = c < ncnd ? x : __uint_as_float(0x40000000u);
+            a[i] = c < ncnd ? a[i] * ninv : __uint_as_float(0x40000000u);
             mx = max(mx, __float_as_uint(a[i]));
           }
           const auto o = __builtin_amdgcn_permlane32_swap(mx, mx, false, false);
@@ -1243,7 +1246,6 @@ __global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_row
           marks[1] |= ct < 2 ? 0u : w;
         }
       }
-      if (SCORES && !mbits) continue;
       // the lane's first marked column, and the row's
       const int32_t e = marks[0] ? __builtin_ctz(marks[0]) : 32 + __builtin_ctz(marks[1] | 0x80000000u);
       uint32_t col = 32 * (e >> 4) + 8 * ((e >> 2) & 3) + 4 * g + (e & 3);
@@ -1376,16 +1378,12 @@ void launch_key_columns(const Shape& s, const uint16_t* K, const uint16_t* W, co
 }
 
 template <int MC, int NCT>
-void launch_bidir(const Shape& s, const uint16_t* Q, const uint16_t* W, float* A_hat, uint32_t* mbits, const FusedPtrs& f,
-                  float c_dot, float c_norm, hipStream_t st) {
+void launch_bidir(const Shape& s, const uint16_t* Q, const uint16_t* W, uint32_t* mbits, const FusedPtrs& f, float c_dot,
+                  float c_norm, hipStream_t st) {
   constexpr size_t lds = (static_cast<size_t>(32 * MC) * kWRow + static_cast<size_t>(16) * NCT * (32 * MC + 8)) * 2;
   static_assert(lds <= (64u << 10), "no larger LDS has to be asked for");
-#define SEA_BIDIR(SCORES_) \
-  hipLaunchKernelGGL((estimate_rows_bidir_kernel<MC, NCT, SCORES_>), dim3(kBidirBlocks), dim3(64 * kBidirWaves), lds, st, s, Q, W, f.state, \
-                     A_hat, mbits, f.counts, c_dot, c_norm, columns_of(s.T, s.K))
-  if (A_hat) SEA_BIDIR(true);
-  else SEA_BIDIR(false);
-#undef SEA_BIDIR
+  hipLaunchKernelGGL((estimate_rows_bidir_kernel<MC, NCT>), dim3(kBidirBlocks), dim3(64 * kBidirWaves), lds, st, s, Q, W, f.state,
+                     mbits, f.counts, c_dot, c_norm, columns_of(s.T, s.K));
 }
 
 template <int MC, int WLOG>
@@ -1404,11 +1402,15 @@ void launch_rows_k(const Shape& s, const uint16_t* Q, const uint16_t* K, const u
     launch_rows<MC, WLOG, 16>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, gh, grid, st);
 }
 
-// layers of the kernel for one column per row: from two row groups per resident block on (equal to the other kernel there,
-// ahead from four on)
-bool one_column_rows(const Shape& s) {
+// Layers of the kernel for one column per row: from two row groups per resident block on (equal to the other kernel there,
+// ahead from four on), and only where nobody asked for the scores.  (A variant that wrote them took the contraction three
+// times or held 145 registers, and its 32-row tiles write 32 bytes of a row at a time, the other kernel 64.  Estimate alone,
+// us, its kernel in three passes / in one / the other: 12 heads of 131072 rows, m = K = 128 568 / 338 / 344, m = 64, K = 100
+// 602 / 366 / 289, 12 of 32768 152 / 88 / 95, 16 of 8192 53 / 34 / 27, 32 of 16384, m = 64 195 / 122 / 100.)
+bool one_column_rows(const Shape& s, bool scores) {
   const int64_t groups = (s.T + 16 * kBidirWaves - 1) / (16 * kBidirWaves) * s.N;
-  return s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks && groups < (1ll << 28);
+  return !scores && s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks &&
+         groups < (1ll << 28);
 }
 
 template <int MC>
@@ -1433,7 +1435,7 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
   if constexpr (MC <= 4) {
-    if (one_column_rows(s)) return launch_bidir<MC, 8>(s, Q, W, A_hat, mbits, f, c_dot, c_norm, st);
+    if (one_column_rows(s, A_hat != nullptr)) return launch_bidir<MC, 8>(s, Q, W, mbits, f, c_dot, c_norm, st);
   }
   switch (wl) {
     case -1: launch_rows_k<MC, kAnyWidth>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;
@@ -1448,9 +1450,9 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
 
 }  // namespace
 
-BucketCounts estimate_counts_columns(const Shape& s) {
+BucketCounts estimate_counts_columns(const Shape& s, bool scores) {
   if (!estimate_fused_supported(s)) return BucketCounts::none;
-  return one_column_rows(s) ? BucketCounts::counted : BucketCounts::zeroed;
+  return one_column_rows(s, scores) ? BucketCounts::counted : BucketCounts::zeroed;
 }
 
 hipError_t launch_estimate_fused(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W,

@@ -1,6 +1,6 @@
 """Layers whose rows select one column each (bidirectional, 65 to 128 columns, from 131072 rows on: the kernel that keeps a
 head's whole state in LDS).  Values that name their column make the output name the selected column; it has to be the
-first of the row's largest scores."""
+first of the row's largest scores, which come from the kernel of all other layers."""
 import pytest
 import torch
 
@@ -28,6 +28,10 @@ def _columns(p, q, k, w):
     a = torch.empty(p.B, p.H, p.T, p.K, device="cuda")
     sea.sea_estimate(p, q, k, w, a, sea.alloc_workspace(p))
     assert torch.equal(o, o[..., :1].expand_as(o))
+    # the layer that writes its scores as well goes another way to the same result
+    o2, a2 = torch.full_like(o, float("nan")), torch.full_like(a, float("nan"))
+    sea.sea_forward(p, q, k, v, w, o2, a2, workspace=sea.alloc_workspace(p))
+    assert torch.equal(o, o2) and torch.equal(a, a2)
     return o[..., 0].float().cpu(), a.cpu()
 
 
@@ -65,3 +69,27 @@ def test_equal_columns(same):
     got, a = _columns(p, q, k, w)
     assert (got < 128 // same).all()
     assert torch.equal(got, _first_largest(a).float())
+
+
+# columns whose scores differ by a few units in the last place, which the row's sum makes equal or not
+@pytest.mark.parametrize("T,m,K", [(8192, 128, 128), (8200, 64, 100), (8195, 128, 65)])
+def test_nearly_equal_columns(T, m, K):
+    p, q, k, w = _layer(1, 16, T, m, K, seed=3)
+    g = torch.Generator().manual_seed(4)
+    k = k[:, :, :1] + 2.0 ** -6 * (torch.rand(1, 16, T, 64, generator=g) < 2.0 ** -10)
+    got, a = _columns(p, q, k, w)
+    assert torch.equal(got, _first_largest(a).float())
+
+
+# scores of a head are the same whatever the number of heads: these layers lie on both sides of the line
+@pytest.mark.parametrize("T,m,K", [(8192, 128, 128), (8195, 64, 100)])
+def test_scores_of_a_head_among_many(T, m, K):
+    p, q, k, w = _layer(1, 16, T, m, K, seed=5)
+    q, k, w = (x.to(torch.bfloat16).cuda() for x in (q, k, w))
+    out = []
+    for H in (2, 16):
+        p.H = H
+        a = torch.empty(1, H, T, K, device="cuda")
+        sea.sea_estimate(p, q[:, :H].contiguous(), k[:, :H].contiguous(), w, a, sea.alloc_workspace(p))
+        out.append(a[:, :2])
+    assert torch.equal(out[0], out[1])
