@@ -402,9 +402,12 @@ __global__ __launch_bounds__(256) void wide_columns_kernel(Shape s, const float*
 // padded by 0-25 %: 91.3 -> 88.6 us against sums in fp32 products (two per 16 features and keys where a lane's four keys were
 // added up per column first, four for narrow columns; half of the matrix pipe's time), T = 2001, m = 128, 48 heads
 // 19.6 -> 19.0.  The rows of the next tile and step are requested ahead.
+// Waves per SIMD, bidirectional: as many as with fp32 products, whose sums took half the registers (64 features keep two
+// registers in memory for it): B = 32, H = 12, T = 500, K = 64, m = 128 34.4 -> 28.0 us with 80 registers in place of 86, m = 64,
+// 512 heads 36.9 -> 33.0; launches of whole rounds are the same.
 // ------------------------------------------------------------------------------------------
 template <int MC, bool CAUSAL>
-__global__ __launch_bounds__(256, 4) void key_columns_kernel(Shape s, Columns cg, const uint16_t* __restrict__ K,
+__global__ __launch_bounds__(256, CAUSAL || MC == 8 ? 4 : MC == 4 ? 6 : 8) void key_columns_kernel(Shape s, Columns cg, const uint16_t* __restrict__ K,
                                                           const uint16_t* __restrict__ W, uint16_t* __restrict__ state,
                                                           float* __restrict__ pref, float c_dot, float c_norm,
                                                           int32_t G, int32_t* __restrict__ counts, uint32_t ncounts) {

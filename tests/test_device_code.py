@@ -9,6 +9,7 @@ import subprocess
 import pytest
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="needs a disassembler")
@@ -35,3 +36,30 @@ def test_loads_to_lds_keep_their_distance(tmp_path):
             elif ins:
                 before = []
     assert loads > 0
+
+
+@pytest.fixture(scope="module")
+def objects(tmp_path_factory):
+    """The device code objects of the built library, as files."""
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("needs a disassembler")
+    from paper_2310_01777_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
+    d = tmp_path_factory.mktemp("objects")
+    shutil.copy(build.LIB, d / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=d, check=True, capture_output=True)
+    return sorted(glob.glob(str(d / "*gfx950")))
+
+
+# Registers a kernel may use so that the waves it is written for stay resident together (512 a SIMD, in eights): the key
+# kernel of columns of any width, bidirectional, whose launches are a few rounds of blocks.
+@pytest.mark.parametrize("kernel,registers", [("key_columns_kernelILi4ELb0E", 80), ("key_columns_kernelILi2ELb0E", 64)])
+def test_registers_leave_room(objects, kernel, registers):
+    used = []
+    for obj in objects:
+        notes = subprocess.run([READELF, "--notes", obj], check=True, capture_output=True, text=True).stdout
+        for entry in notes.split("  - .agpr_count")[1:]:
+            if kernel in re.search(r"\.name: +(\S+)", entry)[1]:
+                used.append(int(re.search(r"\.vgpr_count: +(\d+)", entry)[1]))
+    assert used and max(used) <= registers
