@@ -130,21 +130,18 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
 // launches a CU takes its next block when it is done with one.  Attention stage, us without / with: H = 32, T = 2048,
 // B = 2, K = 256 (1024 blocks) 66.8 / 60.2, H = 12, T = 8192, whole columns (768) 192 / 172; c2 (768) 42.4 / 42.3;
 // columns of any width, T = 1701, 64 heads 98.3 / 89.9.
-// Three rounds are not evened out by one that runs backwards (c2: 46 to 56 steps of 64 keys per CU): there a CU's blocks have
-// ranks at8 and 31 - at8 / 2 and 15 - at8 / 2 (or the other way round), which add up to 46 or 47 everywhere (50 or 52 steps;
-// the layer 68.1 / 67.5).
+// Three rounds are not evened out by one that runs backwards (c2: 46 to 56 steps of 64 keys per CU), but an order that does
+// even them out, 50 or 52 steps everywhere, gives nothing that can be told from the spread of runs: attention stage without /
+// with, least of sixty, 768 blocks 46.1 / 45.7, 704 45.1 / 44.9, 640 44.2 / 43.9, 576 37.5 / 37.4, of 4096 rows 640 82.2 / 81.6;
+// columns of any width 768 72.1 / 73.2, 704 69.8 / 69.7.
 // (Blocks with nothing but padding have to keep their turn there: they walk their steps without products, which costs
 // little.  Where they return at once, the blocks behind them land on other CUs: B = 2, H = 32, T = 2048 padded by 0-25 %, K = 256,
 // 60 -> 63 us.  Longer launches, where the next block takes their place: padding_returns.)
 __device__ __forceinline__ bool padding_returns(uint32_t grid, uint32_t per_cu, bool causal) { return !causal || grid > 256u * per_cu; }
 __device__ __forceinline__ uint32_t dealt_in_turn(uint32_t block, uint32_t grid, uint32_t per_cu, bool causal) {
-  const uint32_t round = block >> 8;
-  if (!causal || grid > 256u * per_cu || round == 0u) return block;
-  const uint32_t lo = block & ~255u, at8 = (block - lo) >> 3, low = block & 7u;
-  if (grid == 768u) return lo + 8u * ((((at8 ^ round) & 1u) != 0u ? 31u : 15u) - (at8 >> 1)) + low;
-  if ((round & 1u) == 0u) return block;
-  const uint32_t n8 = min(256u, grid - lo) >> 3;
-  return at8 < n8 ? lo + 8u * (n8 - 1u - at8) + low : block;
+  if (!causal || grid > 256u * per_cu || ((block >> 8) & 1u) == 0u) return block;
+  const uint32_t lo = block & ~255u, n8 = min(256u, grid - lo) >> 3, at8 = (block - lo) >> 3;
+  return at8 < n8 ? lo + 8u * (n8 - 1u - at8) + (block & 7u) : block;
 }
 
 #endif  // __HIPCC__
