@@ -1409,17 +1409,15 @@ void launch_rows_k(const Shape& s, const uint16_t* Q, const uint16_t* K, const u
     launch_rows<MC, WLOG, 16>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, gh, grid, st);
 }
 
-// Layers of the kernel for one column per row: from one 32-row tile for every other resident wave on, where nobody asked for the
-// scores.  Layer with the other kernel / this one, us, m = K = 128: 32768 rows 26.1 / 27.0, 65536 32.7 / 31.3, 98304 40.0 / 38.7,
-// 131072 45.6 / 42.2, 262144 68.4 / 63.7; K = 96 65536 89.5 / 88.8; m = 64, K = 100 65536 80.7 / 79.1.
-// (A variant that wrote the scores took the contraction three times or held 145 registers, and its 32-row tiles write 32 bytes
-// of a row at a time, the other kernel 64.  Estimate alone, us, it in three passes / in one / the other kernel: 12 heads of
-// 131072 rows, m = K = 128 568 / 338 / 322, m = 64, K = 100 602 / 366 / 278, 12 of 32768 152 / 88 / 93, 16 of 8192
-// 53 / 34 / 27, 32 of 16384, m = 64 195 / 122 / 96.)
+// Layers of the kernel for one column per row: from two row groups per resident block on (equal to the other kernel there,
+// ahead from four on), and only where nobody asked for the scores.  (A variant that wrote them took the contraction three
+// times or held 145 registers, and its 32-row tiles write 32 bytes of a row at a time, the other kernel 64.  Estimate alone,
+// us, its kernel in three passes / in one / the other: 12 heads of 131072 rows, m = K = 128 568 / 338 / 322, m = 64, K = 100
+// 602 / 366 / 278, 12 of 32768 152 / 88 / 93, 16 of 8192 53 / 34 / 27, 32 of 16384, m = 64 195 / 122 / 96.)
 bool one_column_rows(const Shape& s, bool scores) {
-  const int64_t tiles = static_cast<int64_t>((s.T + 31) / 32) * s.N;
-  return !scores && s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 &&
-         tiles >= kBidirBlocks * kBidirWaves / 2 && tiles < (1ll << 30);
+  const int64_t groups = (s.T + 16 * kBidirWaves - 1) / (16 * kBidirWaves) * s.N;
+  return !scores && s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks &&
+         groups < (1ll << 28);
 }
 
 template <int MC>

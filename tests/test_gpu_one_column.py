@@ -1,4 +1,4 @@
-"""Layers whose rows select one column each (bidirectional, 65 to 128 columns, from 65536 rows on: the kernel that keeps a
+"""Layers whose rows select one column each (bidirectional, 65 to 128 columns, from 131072 rows on: the kernel that keeps a
 head's whole state in LDS).  Values that name their column make the output name the selected column; it has to be the
 first of the row's largest scores, which come from the kernel of all other layers."""
 import pytest
@@ -40,7 +40,7 @@ def _first_largest(a):
 
 
 # whole tiles and rows past the last one, columns that fill their tiles and not, both feature counts
-@pytest.mark.parametrize("B,H,T,m,K", [(1, 8, 8192, 128, 128), (1, 16, 8192, 128, 128), (2, 8, 8195, 64, 100), (1, 2, 65537, 128, 65),
+@pytest.mark.parametrize("B,H,T,m,K", [(1, 16, 8192, 128, 128), (2, 8, 8195, 64, 100), (1, 2, 65537, 128, 65),
                                        (1, 3, 43723, 64, 127), (1, 1, 131072, 128, 96)])
 def test_first_largest_score(B, H, T, m, K):
     p, q, k, w = _layer(B, H, T, m, K, seed=T)
@@ -81,7 +81,7 @@ def test_nearly_equal_columns(T, m, K):
     assert torch.equal(got, _first_largest(a).float())
 
 
-# scores of a head are the same whatever the number of heads
+# scores of a head are the same whatever the number of heads: these layers lie on both sides of the line
 @pytest.mark.parametrize("T,m,K", [(8192, 128, 128), (8195, 64, 100)])
 def test_scores_of_a_head_among_many(T, m, K):
     p, q, k, w = _layer(1, 16, T, m, K, seed=5)
