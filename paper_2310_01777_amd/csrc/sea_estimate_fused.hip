@@ -1396,11 +1396,7 @@ void launch_rows_k(const Shape& s, const uint16_t* Q, const uint16_t* K, const u
   const dim3 grid(static_cast<uint32_t>(s.N) * tiles);
   // heads whose state (K x m bf16 each) shares an XCD's L2 at one time: 2 MB worth
   const int64_t per_xcd = std::max<int64_t>(1, (int64_t(2) << 20) / (static_cast<int64_t>(s.K) * s.m * 2));
-  // Bidirectional layers that write their scores take a head that fills the chip by itself after the other, so that the scores
-  // leave in order: estimate, us, all heads in turn / one by one: 12 heads of 131072 rows 344 / 321, of 32768 100 / 94, 16 of
-  // 16384 81 / 77; 12 of 8192 rows 22.6 / 22.8, 256 of 2048 242 / 246, 384 of 512 30 / 35.
-  const bool one_by_one = A_hat && !s.causal && tiles >= 256;
-  const int32_t gh = one_by_one ? 1 : static_cast<int32_t>(std::min<int64_t>(s.N, 8 * per_xcd));
+  const int32_t gh = static_cast<int32_t>(std::min<int64_t>(s.N, 8 * per_xcd));
   if (s.K <= 64)
     launch_rows<MC, WLOG, 4>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, gh, grid, st);
   else if (s.K <= 128)
@@ -1412,8 +1408,8 @@ void launch_rows_k(const Shape& s, const uint16_t* Q, const uint16_t* K, const u
 // Layers of the kernel for one column per row: from two row groups per resident block on (equal to the other kernel there,
 // ahead from four on), and only where nobody asked for the scores.  (A variant that wrote them took the contraction three
 // times or held 145 registers, and its 32-row tiles write 32 bytes of a row at a time, the other kernel 64.  Estimate alone,
-// us, its kernel in three passes / in one / the other: 12 heads of 131072 rows, m = K = 128 568 / 338 / 322, m = 64, K = 100
-// 602 / 366 / 278, 12 of 32768 152 / 88 / 93, 16 of 8192 53 / 34 / 27, 32 of 16384, m = 64 195 / 122 / 96.)
+// us, its kernel in three passes / in one / the other: 12 heads of 131072 rows, m = K = 128 568 / 338 / 344, m = 64, K = 100
+// 602 / 366 / 289, 12 of 32768 152 / 88 / 95, 16 of 8192 53 / 34 / 27, 32 of 16384, m = 64 195 / 122 / 100.)
 bool one_column_rows(const Shape& s, bool scores) {
   const int64_t groups = (s.T + 16 * kBidirWaves - 1) / (16 * kBidirWaves) * s.N;
   return !scores && s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks &&
