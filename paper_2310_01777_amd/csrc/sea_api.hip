@@ -398,11 +398,11 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
     if (estimate_fused_supported(s) && s.grouping == 0) {
       // rows per column, which the estimator zeroes or counts for the attention's buckets
       int32_t* const counts = bucket_counts(s, w);
-      float* const scores = (A_hat_opt || need_lists) ? A_hat : nullptr;
-      if (counts) have = estimate_counts_columns(s, scores != nullptr);
-      // estimate and per-row top-k^ in one kernel; scores that nobody asked for never leave the registers
+      if (counts) have = estimate_counts_columns(s);
+      // estimate and per-row top-k^ in one kernel; the scores never leave the registers
       e = launch_estimate_fused(s, static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K),
-                                static_cast<const uint16_t*>(W), scores, mbits, est_ws, st, counts);
+                                static_cast<const uint16_t*>(W), (A_hat_opt || need_lists) ? A_hat : nullptr,
+                                mbits, est_ws, st, counts);
       if (e != hipSuccess) return fail_hip(e);
       if (need_lists) e = launch_topk_mask(s, A_hat, sel_opt, idx_opt, cnt_opt, nullptr, st);
     } else {

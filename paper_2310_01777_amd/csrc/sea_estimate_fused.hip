@@ -1047,27 +1047,35 @@ __global__ __launch_bounds__(256, MC == 8 ? 3 : NCT == 16 ? 4 : 5) void estimate
 // ------------------------------------------------------------------------------------------
 // query side, bidirectional, one column of 65 to 128 per row (k^ = 1, m <= 128), every row active: with no
 // search to do, what is left of a row is two contractions and a maximum.  W and a head's whole state fit LDS
-// together (48 KB for m = K = 128), so a block stages them once per head and its waves take 32 rows after 32
+// together (53 KB for m = K = 128), so a block stages them once per head and its waves take 32 rows after 32
 // rows with no barrier in between (the kernel above stages W per 64 rows and steps the state through LDS
 // behind four barriers).  Two blocks of eight waves per CU, each with an equal share of all heads' tiles.  The winner of
 // a row is its largest raw score: scaling by the row's sum can only make scores equal that are within a few units in the
 // last place of each other, and a wave that holds such a row, or scores outside the middle of fp32's range, scales them
-// and lets the lowest of the equal columns win, as the kernel above does.  With that, and without a test per column, 32
+// and lets the lowest of the equal columns win, as the kernel above does (which adds up a row's scores in another order, so
+// that scores a unit in the last place apart may be equal there and not here).  With that, and without a test per column, 32
 // rows take 540 vector instructions (1110 before, most of them tests and the scalars they spilled); with 32 rows per wave an
 // operand read from LDS serves twice the rows it does in tiles of 16 (48 KB each, 70 us of LDS time per launch).  Bound:
 // vector pipe 62 % and matrix pipe 38 % busy at the 1.9 GHz the chip keeps here, one after the other.  B = 1, H = 12,
 // T = 131072, m = K = 128: 152 -> 102 us (2.0 TB/s), the whole forward 303 -> 265.  1024 to 4096 blocks, or six or
 // twelve waves to a block: the same or slower.  The search for k^ > 1 wants more waves than stay resident here, shares of
 // sequences of different lengths are unequal, and K <= 64 needs no steps to begin with.
+// SCORES: the scores leave as well, held in registers (174; one block per CU) and written through LDS in whole lines.  Bound:
+// those writes (805 MB, 4.3 TB/s with the reads).  sea_estimate, us, with three passes over the contraction and four bytes a
+// store / 16 bytes a store from one pass / so: 12 heads of 131072 rows, m = K = 128 590 / 338 / 276, m = 64, K = 100
+// 600 / 366 / 335, 12 of 32768 154 / 88 / 78, 16 of 8192 55 / 34 / 27, of 8200, K = 65 56 / 58 / 43, 32 of 16384, m = 64
+// 195 / 122 / 92; the kernel above 345, 289, 96, 28, 46, 100.
 // ------------------------------------------------------------------------------------------
-constexpr int kBidirWaves = 8, kBidirBlocks = 512;  // two blocks per CU
+constexpr int kBidirWaves = 8, kBidirBlocks = 512;  // two blocks per CU (one where the scores are written)
+constexpr int kPlaceRow = 68;  // floats per row of 64 scores on their way out: sixteen rows on distinct banks
 __device__ __forceinline__ floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
-template <int MC, int NCT>
-__global__ __launch_bounds__(64 * kBidirWaves, 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,
+template <int MC, int NCT, bool SCORES>
+__global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_rows_bidir_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                                                   const uint16_t* __restrict__ W,
                                                                                   const uint16_t* __restrict__ state,
+                                                                                  float* __restrict__ A_hat,
                                                                                   uint32_t* __restrict__ mbits,
                                                                                   int32_t* __restrict__ counts, float c_dot,
                                                                                   float c_norm, Columns cg) {
@@ -1083,6 +1091,7 @@ __global__ __launch_bounds__(64 * kBidirWaves, 4) void estimate_rows_bidir_kerne
   extern __shared__ __attribute__((aligned(16))) uint16_t rows_lds[];
   uint16_t* const Ws = rows_lds;              // [m][kWRow]
   uint16_t* const Ss = rows_lds + m * kWRow;  // [16 NCT][kSRow]
+  float* const place = reinterpret_cast<float*>(Ss + 16 * NCT * kSRow) + (threadIdx.x >> 6) * 32 * kPlaceRow;  // (SCORES)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, g = lane >> 5;
@@ -1180,73 +1189,128 @@ __global__ __launch_bounds__(64 * kBidirWaves, 4) void estimate_rows_bidir_kerne
           if (u + kAhead < N * kSteps) f[u % kAhead] = operand(u + kAhead);
         }
       };
-      // Half of the columns at a time (all of them would leave no registers to read operands ahead): the lane's largest
-      // (scores are not negative, their bit patterns have their order, NaN above all), and which ones are within four units
-      // in the last place of it.
-      uint32_t most[2], marks[2];
+      uint32_t marks[2];
+      if constexpr (SCORES) {
+        // all of the row's scores, scaled and marked as below, and to memory in whole lines: 64 columns of the wave's rows at a time
+        // through LDS
+        floatx16 sc[kTiles];
+        scores(0, sc);
+        float r = 0.f;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        floatx16 ab[2];
-        scores(2 * h, ab);
-        const floatx16 a = ab[0], b = ab[1];
-        uint32_t mx0 = 0, mx1 = 0;
+        for (int ct = 0; ct < kTiles; ++ct)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          mx0 = max(mx0, __float_as_uint(a[i]));
-          mx1 = max(mx1, __float_as_uint(b[i]));
-        }
-        most[h] = max(mx0, mx1);
-        marks[h] = mark_at_least(a, most[h] - 4u, mark_at_least(b, most[h] - 4u, 0u));
-      }
-      uint32_t top = max(most[0], most[1]);
-      {
-        const auto o = __builtin_amdgcn_permlane32_swap(top, top, false, false);
-        top = max(o[0], o[1]);
-      }
+          for (int i = 0; i < 16; ++i) r += sc[ct][i];
+        r += __shfl_xor(r, 32, kWave);
+        const float ninv = r > 0.f ? -1.f / r : -0.f;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) marks[h] = most[h] >= top - 4u ? marks[h] : 0u;
-      const uint32_t cnt = __popc(marks[0]) + __popc(marks[1]);
-      const auto both = __builtin_amdgcn_permlane32_swap(cnt, cnt, false, false);
-      // 2^-100 < largest < 2^100, and no other within 2^-22 of it
-      const bool plain = both[0] + both[1] == 1u && top - 0x0d800000u < 0x71800000u - 0x0d800000u;
-      if (__ballot(!plain) != 0ull) {
-        // The row's sum in the order of the kernel above, whose lane group 2 (j % 2) + g holds the columns of registers 4 j ..:
-        // whole tiles of 16 columns by fours, the one with the last column, and all of them in the last rows, one by one.
-        float rs[2] = {0.f, 0.f};
-#pragma unroll 1
-        for (int ct = 0; ct < kTiles; ++ct) {
-          floatx16 a[1];
-          scores(ct, a);
+        for (int ct = 0; ct < kTiles; ++ct)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float x0 = a[0][4 * j], x1 = a[0][4 * j + 1], x2 = a[0][4 * j + 2], x3 = a[0][4 * j + 3];
-            const float fours = rs[j & 1] + ((x0 + x1) + (x2 + x3)), ones = (((rs[j & 1] + x0) + x1) + x2) + x3;
-            rs[j & 1] = (trow | 15) >= s.T || 2 * ct + (j >> 1) >= (ncnd - 1) >> 4 ? ones : fours;
+          for (int i = 0; i < 16; ++i) sc[ct][i] *= ninv;
+        const int32_t row0 = static_cast<int32_t>(tile - head * tiles) * 32;
+        float* const out = A_hat + (static_cast<int64_t>(head) * s.T + row0) * s.K;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {  // registers 4 (q % 4) .. of a tile: columns 8 q + 4 g .. of the 64
+            const floatx16 a = sc[2 * h + (q >> 2)];
+            const int j = 4 * (q & 3);
+            *reinterpret_cast<float4*>(place + lr * kPlaceRow + 8 * q + 4 * g) = make_float4(-a[j], -a[j + 1], -a[j + 2], -a[j + 3]);
           }
+          __builtin_amdgcn_wave_barrier();
+          if ((s.K & 3) == 0) {
+            const int32_t c = 64 * h + 4 * (lane & 15);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              const int32_t row = 4 * q + (lane >> 4);
+              const float4 v = *reinterpret_cast<const float4*>(place + row * kPlaceRow + 4 * (lane & 15));
+              if (row0 + row < s.T && c < s.K) *reinterpret_cast<float4*>(out + static_cast<int64_t>(row) * s.K + c) = v;
+            }
+          } else {
+            const int32_t c = 64 * h + lane;
+#pragma unroll 8
+            for (int row = 0; row < 32; ++row) {
+              const float v = place[row * kPlaceRow + lane];
+              if (row0 + row < s.T && c < s.K) out[static_cast<int64_t>(row) * s.K + c] = v;
+            }
+          }
+          __builtin_amdgcn_wave_barrier();
         }
-        const float r = (rs[0] + __shfl_xor(rs[0], 32, kWave)) + (rs[1] + __shfl_xor(rs[1], 32, kWave));
-        const float ninv = r > 0.f ? -1.f / r : -0.f;  // (as in finish_rows: the negated score is the key)
-        top = 0u;
-        marks[0] = marks[1] = 0u;
-#pragma unroll 1
-        for (int ct = 0; ct < kTiles; ++ct) {
-          floatx16 one[1];
-          scores(ct, one);
-          floatx16 a = one[0];
-          uint32_t mx = 0u;
+        if (!mbits) continue;
+        uint32_t top = 0u;
+#pragma unroll
+        for (int ct = 0; ct < kTiles; ++ct)
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
-            const int32_t c = 32 * ct + 8 * (i >> 2) + 4 * g + (i & 3);
-            a[i] = c < ncnd ? a[i] * ninv : __uint_as_float(0x40000000u);
-            mx = max(mx, __float_as_uint(a[i]));
+            if (32 * ct + 8 * (i >> 2) + 4 * g + (i & 3) >= ncnd) sc[ct][i] = __uint_as_float(0x40000000u);
+            top = max(top, __float_as_uint(sc[ct][i]));
           }
-          const auto o = __builtin_amdgcn_permlane32_swap(mx, mx, false, false);
-          mx = max(o[0], o[1]);
-          if (mx > top) marks[0] = marks[1] = 0u;
-          top = max(top, mx);
-          const uint32_t w = mark_at_least(a, top, 0u) << (16 * (ct & 1));
-          marks[0] |= ct < 2 ? w : 0u;
-          marks[1] |= ct < 2 ? 0u : w;
+        const auto o = __builtin_amdgcn_permlane32_swap(top, top, false, false);
+        top = max(o[0], o[1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) marks[h] = mark_at_least(sc[2 * h], top, mark_at_least(sc[2 * h + 1], top, 0u));
+      } else {
+        // Half of the columns at a time (all of them would leave no registers to read operands ahead): the lane's largest
+        // (scores are not negative, their bit patterns have their order, NaN above all), and which ones are within four units
+        // in the last place of it.
+        uint32_t most[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          floatx16 ab[2];
+          scores(2 * h, ab);
+          const floatx16 a = ab[0], b = ab[1];
+          uint32_t mx0 = 0, mx1 = 0;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            mx0 = max(mx0, __float_as_uint(a[i]));
+            mx1 = max(mx1, __float_as_uint(b[i]));
+          }
+          most[h] = max(mx0, mx1);
+          marks[h] = mark_at_least(a, most[h] - 4u, mark_at_least(b, most[h] - 4u, 0u));
+        }
+        uint32_t top = max(most[0], most[1]);
+        {
+          const auto o = __builtin_amdgcn_permlane32_swap(top, top, false, false);
+          top = max(o[0], o[1]);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) marks[h] = most[h] >= top - 4u ? marks[h] : 0u;
+        const uint32_t cnt = __popc(marks[0]) + __popc(marks[1]);
+        const auto both = __builtin_amdgcn_permlane32_swap(cnt, cnt, false, false);
+        // 2^-100 < largest < 2^100, and no other within 2^-22 of it
+        const bool plain = both[0] + both[1] == 1u && top - 0x0d800000u < 0x71800000u - 0x0d800000u;
+        if (__ballot(!plain) != 0ull) {
+          float r = 0.f;
+#pragma unroll 1
+          for (int ct = 0; ct < kTiles; ++ct) {
+            floatx16 a[1];
+            scores(ct, a);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) r += a[0][i];
+          }
+          r += __shfl_xor(r, 32, kWave);
+          const float ninv = r > 0.f ? -1.f / r : -0.f;  // (as in finish_rows: the negated score is the key)
+          top = 0u;
+          marks[0] = marks[1] = 0u;
+#pragma unroll 1
+          for (int ct = 0; ct < kTiles; ++ct) {
+            floatx16 one[1];
+            scores(ct, one);
+            floatx16 a = one[0];
+            uint32_t mx = 0u;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              const int32_t c = 32 * ct + 8 * (i >> 2) + 4 * g + (i & 3);
+              a[i] = c < ncnd ? a[i] * ninv : __uint_as_float(0x40000000u);
+              mx = max(mx, __float_as_uint(a[i]));
+            }
+            const auto o = __builtin_amdgcn_permlane32_swap(mx, mx, false, false);
+            mx = max(o[0], o[1]);
+            if (mx > top) marks[0] = marks[1] = 0u;
+            top = max(top, mx);
+            const uint32_t w = mark_at_least(a, top, 0u) << (16 * (ct & 1));
+            marks[0] |= ct < 2 ? w : 0u;
+            marks[1] |= ct < 2 ? 0u : w;
+          }
         }
       }
       // the lane's first marked column, and the row's
@@ -1380,13 +1444,17 @@ void launch_key_columns(const Shape& s, const uint16_t* K, const uint16_t* W, co
 #undef SEA_KEY_COLUMNS
 }
 
-template <int MC, int NCT>
-void launch_bidir(const Shape& s, const uint16_t* Q, const uint16_t* W, uint32_t* mbits, const FusedPtrs& f, float c_dot,
-                  float c_norm, hipStream_t st) {
-  constexpr size_t lds = (static_cast<size_t>(32 * MC) * kWRow + static_cast<size_t>(16) * NCT * (32 * MC + 8)) * 2;
-  static_assert(lds <= (64u << 10), "no larger LDS has to be asked for");
-  hipLaunchKernelGGL((estimate_rows_bidir_kernel<MC, NCT>), dim3(kBidirBlocks), dim3(64 * kBidirWaves), lds, st, s, Q, W, f.state,
-                     mbits, f.counts, c_dot, c_norm, columns_of(s.T, s.K));
+template <int MC, int NCT, bool SCORES>
+void launch_bidir(const Shape& s, const uint16_t* Q, const uint16_t* W, float* A_hat, uint32_t* mbits, const FusedPtrs& f,
+                  float c_dot, float c_norm, hipStream_t st) {
+  constexpr size_t lds = (static_cast<size_t>(32 * MC) * kWRow + static_cast<size_t>(16) * NCT * (32 * MC + 8)) * 2 +
+                         (SCORES ? kBidirWaves * 32 * kPlaceRow * sizeof(float) : 0);
+  static_assert(SCORES || lds <= (64u << 10), "no larger LDS has to be asked for");
+  if (SCORES && hipFuncSetAttribute(reinterpret_cast<const void*>(&estimate_rows_bidir_kernel<MC, NCT, SCORES>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+    return;  // (the caller asks for the error)
+  hipLaunchKernelGGL((estimate_rows_bidir_kernel<MC, NCT, SCORES>), dim3(SCORES ? kBidirBlocks / 2 : kBidirBlocks),
+                     dim3(64 * kBidirWaves), lds, st, s, Q, W, f.state, A_hat, mbits, f.counts, c_dot, c_norm, columns_of(s.T, s.K));
 }
 
 template <int MC, int WLOG>
@@ -1405,15 +1473,11 @@ void launch_rows_k(const Shape& s, const uint16_t* Q, const uint16_t* K, const u
     launch_rows<MC, WLOG, 16>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, gh, grid, st);
 }
 
-// Layers of the kernel for one column per row: from two row groups per resident block on (equal to the other kernel there,
-// ahead from four on), and only where nobody asked for the scores.  (A variant that wrote them took the contraction three
-// times or held 145 registers, and its 32-row tiles write 32 bytes of a row at a time, the other kernel 64.  Estimate alone,
-// us, its kernel in three passes / in one / the other: 12 heads of 131072 rows, m = K = 128 568 / 338 / 344, m = 64, K = 100
-// 602 / 366 / 289, 12 of 32768 152 / 88 / 95, 16 of 8192 53 / 34 / 27, 32 of 16384, m = 64 195 / 122 / 100.)
-bool one_column_rows(const Shape& s, bool scores) {
+// layers of the kernel for one column per row: from two row groups per resident block on (equal to the other kernel there,
+// ahead from four on)
+bool one_column_rows(const Shape& s) {
   const int64_t groups = (s.T + 16 * kBidirWaves - 1) / (16 * kBidirWaves) * s.N;
-  return !scores && s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks &&
-         groups < (1ll << 28);
+  return s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks && groups < (1ll << 28);
 }
 
 template <int MC>
@@ -1438,7 +1502,9 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
   }
   StageScope scope(SEA_STAGE_CONTRACT, st);
   if constexpr (MC <= 4) {
-    if (one_column_rows(s, A_hat != nullptr)) return launch_bidir<MC, 8>(s, Q, W, mbits, f, c_dot, c_norm, st);
+    if (one_column_rows(s))
+      return A_hat ? launch_bidir<MC, 8, true>(s, Q, W, A_hat, mbits, f, c_dot, c_norm, st)
+                   : launch_bidir<MC, 8, false>(s, Q, W, nullptr, mbits, f, c_dot, c_norm, st);
   }
   switch (wl) {
     case -1: launch_rows_k<MC, kAnyWidth>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, st); break;
@@ -1453,9 +1519,9 @@ void launch_w(const Shape& s, int wl, const uint16_t* Q, const uint16_t* K, cons
 
 }  // namespace
 
-BucketCounts estimate_counts_columns(const Shape& s, bool scores) {
+BucketCounts estimate_counts_columns(const Shape& s) {
   if (!estimate_fused_supported(s)) return BucketCounts::none;
-  return one_column_rows(s, scores) ? BucketCounts::counted : BucketCounts::zeroed;
+  return one_column_rows(s) ? BucketCounts::counted : BucketCounts::zeroed;
 }
 
 hipError_t launch_estimate_fused(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W,

@@ -56,9 +56,9 @@ size_t estimate_fused_workspace(const Shape& s);
 // nullptr; at least one should be given
 hipError_t launch_estimate_fused(const Shape& s, const uint16_t* Q, const uint16_t* K, const uint16_t* W,
                                  float* A_hat, uint32_t* mbits, void* ws, hipStream_t st, int32_t* counts = nullptr);
-// what launch_estimate_fused does with the rows per column it is given (counts [N][K], with mbits); scores: it has an A_hat to write
+// what launch_estimate_fused does with the rows per column it is given (counts [N][K], with mbits)
 enum class BucketCounts { none, zeroed, counted };
-BucketCounts estimate_counts_columns(const Shape& s, bool scores);
+BucketCounts estimate_counts_columns(const Shape& s);
 
 // per-row width geometry (causal, m in {64,128,256}); fp32 tensors: fp64 features, tiles on the fp64 matrix
 // cores or a prefix table of phi(K); bf16 tensors: the bf16 matrix-core form below

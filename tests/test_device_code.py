@@ -63,3 +63,24 @@ def test_registers_leave_room(objects, kernel, registers):
             if kernel in re.search(r"\.name: +(\S+)", entry)[1]:
                 used.append(int(re.search(r"\.vgpr_count: +(\d+)", entry)[1]))
     assert used and max(used) <= registers
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    """Instructions of every kernel and function, by name."""
+    out = {}
+    for obj in objects:
+        dump = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", obj], check=True, capture_output=True, text=True).stdout
+        for part in re.split(r"^(?:[0-9a-f]+ )?<", dump, flags=re.M)[1:]:
+            name, _, body = part.partition(">:")
+            out[name] = [" ".join(line.split("//")[0].split()) for line in body.splitlines()[1:] if line.split("//")[0].strip()]
+    return out
+
+
+# The kernel for one column per row that writes the scores too takes each product once: four for 32 features of the projection,
+# m / 16 for 32 of the contraction's 128 columns.
+@pytest.mark.parametrize("m", [64, 128])
+def test_scores_of_one_column_rows_take_one_pass(kernels, m):
+    found = [ins for name, ins in kernels.items() if f"estimate_rows_bidir_kernelILi{m // 32}ELi8ELb1E" in name]
+    assert len(found) == 1
+    assert sum(i.startswith("v_mfma_f32_32x32x16_bf16") for i in found[0]) == 4 * (m // 32) + 4 * (m // 16)

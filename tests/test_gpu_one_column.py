@@ -1,6 +1,6 @@
 """Layers whose rows select one column each (bidirectional, 65 to 128 columns, from 131072 rows on: the kernel that keeps a
 head's whole state in LDS).  Values that name their column make the output name the selected column; it has to be the
-first of the row's largest scores, which come from the kernel of all other layers."""
+first of the row's largest scores."""
 import pytest
 import torch
 
@@ -28,7 +28,7 @@ def _columns(p, q, k, w):
     a = torch.empty(p.B, p.H, p.T, p.K, device="cuda")
     sea.sea_estimate(p, q, k, w, a, sea.alloc_workspace(p))
     assert torch.equal(o, o[..., :1].expand_as(o))
-    # the layer that writes its scores as well goes another way to the same result
+    # a layer that writes its scores as well comes to the same result
     o2, a2 = torch.full_like(o, float("nan")), torch.full_like(a, float("nan"))
     sea.sea_forward(p, q, k, v, w, o2, a2, workspace=sea.alloc_workspace(p))
     assert torch.equal(o, o2) and torch.equal(a, a2)
@@ -81,15 +81,19 @@ def test_nearly_equal_columns(T, m, K):
     assert torch.equal(got, _first_largest(a).float())
 
 
-# scores of a head are the same whatever the number of heads: these layers lie on both sides of the line
-@pytest.mark.parametrize("T,m,K", [(8192, 128, 128), (8195, 64, 100)])
+# A head among few goes to the kernel of all other layers, among many to this one.  The scores before their scaling are the same
+# and the sum of a row's at most 128 is taken in another order: 35 and 65 additions in turn, (35 + 65 + 4) 2^-24 < 6.3e-6; two
+# roundings each are left between the scores of one row.
+@pytest.mark.parametrize("T,m,K", [(8192, 128, 128), (8195, 64, 100), (8200, 128, 65)])
 def test_scores_of_a_head_among_many(T, m, K):
     p, q, k, w = _layer(1, 16, T, m, K, seed=5)
     q, k, w = (x.to(torch.bfloat16).cuda() for x in (q, k, w))
     out = []
     for H in (2, 16):
         p.H = H
-        a = torch.empty(1, H, T, K, device="cuda")
+        a = torch.full((1, H, T, K), float("nan"), device="cuda")
         sea.sea_estimate(p, q[:, :H].contiguous(), k[:, :H].contiguous(), w, a, sea.alloc_workspace(p))
-        out.append(a[:, :2])
-    assert torch.equal(out[0], out[1])
+        out.append(a[:, :2].double())
+    ratio = out[1] / out[0]
+    assert (ratio - 1).abs().max() < 6.3e-6
+    assert (ratio.amax(-1) / ratio.amin(-1) - 1).max() < 4 * 2.0 ** -24 * 1.01
