@@ -1,5 +1,5 @@
-"""The built library's own device code.  Loads that go straight to LDS are written as instructions, so the compiler keeps no
-distance in front of them: every one has to bring it along."""
+"""The built library's own device code.  Loads that go straight to LDS, marks of selected columns and bounds of tiles are written
+as instructions, so the compiler keeps no distance in front of them: every one has to bring it along."""
 import glob
 import os
 import re
@@ -84,3 +84,62 @@ def test_scores_of_one_column_rows_take_one_pass(kernels, m):
     found = [ins for name, ins in kernels.items() if f"estimate_rows_bidir_kernelILi{m // 32}ELi8ELb1E" in name]
     assert len(found) == 1
     assert sum(i.startswith("v_mfma_f32_32x32x16_bf16") for i in found[0]) == 4 * (m // 32) + 4 * (m // 16)
+
+
+def _registers(operand):
+    """The scalar and vector registers an operand names."""
+    operand = operand.strip().lstrip("-").strip("|")
+    if m := re.fullmatch(r"([sv])\[(\d+):(\d+)\]", operand):
+        return {m[1] + str(i) for i in range(int(m[2]), int(m[3]) + 1)}
+    return {operand} if operand == "vcc" or re.fullmatch(r"[sv]\d+", operand) else set()
+
+
+def _distances(instructions):
+    """(writer, wait states between, reader) for scalars that vector instructions write and vector instructions read, and for
+    results of matrix instructions that other vector instructions read; straight-line code, a branch counted as one state."""
+    written = {}  # register: [its writer, wait states since]
+    for ins in instructions:
+        op, _, rest = ins.partition(" ")
+        ops = [o.split()[0] if o.split() else "" for o in re.split(r",\s*(?![^\[]*\])", rest)] if rest else []
+        outputs = 2 if re.match(r"v_(add|sub|subrev|addc|subb|subbrev)_co_|v_div_scale|v_mad_[ui]64", op) else 1
+        vector, matrix = op.startswith("v_"), "mfma" in op
+        if vector and not matrix:
+            for r in set().union(*map(_registers, ops[outputs:])) & set(written):
+                yield written[r][0], written[r][1], ins
+        states = int(ops[0]) + 1 if op == "s_nop" else 1
+        for r in list(written):
+            written[r][1] += states
+            if written[r][1] > 40:
+                del written[r]
+        for r in set().union(*map(_registers, ops[: outputs if vector else 1])):
+            if vector and (matrix or r[0] == "s" or r == "vcc"):
+                written[r] = [op, 0]
+            else:
+                written.pop(r, None)
+        if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+            written = {}
+
+
+# Wait states that gfx950 wants, which the compiler keeps for its own instructions only: the marks of selected columns and the
+# bounds of tiles are written as instructions, and some of them read what matrix instructions wrote.
+WAIT_STATES = {"v_mfma_f32_16x16x32_bf16": 8, "v_mfma_f32_32x32x16_bf16": 12, "v_mfma_i32_16x16x64_i8": 8}
+
+
+def _too_close(instructions):
+    return [d for d in _distances(instructions) if d[1] < (WAIT_STATES.get(d[0], 0) if "mfma" in d[0] else 2)]
+
+
+def test_vector_instructions_keep_their_distance(kernels):
+    assert any("v_addc_co_u32_e64" in i for ins in kernels.values() for i in ins)  # (marks)
+    assert {name: d for name, ins in kernels.items() if (d := _too_close(ins))} == {}
+
+
+def test_distances_are_seen():
+    marks = ["v_cmp_ge_u32_e64 s[4:5], v1, v9", "v_cmp_ge_u32_e64 s[6:7], v2, v9", "v_addc_co_u32_e64 v0, vcc, v0, v0, s[4:5]"]
+    assert _too_close(marks)
+    assert not _too_close(marks[:2] + ["s_nop 0"] + marks[2:])
+    assert _too_close(["v_cmp_lt_f32_e32 vcc, v1, v2", "v_cndmask_b32_e32 v3, v4, v5, vcc"])
+    product = ["v_mfma_f32_16x16x32_bf16 v[4:7], v[0:3], v[8:11], v[4:7]", "s_nop 6", "v_add_f32_e32 v1, v2, v6"]
+    assert _too_close(product)
+    assert not _too_close(product[:1] + ["s_nop 7"] + product[2:])
+    assert not _too_close(product[:1] + ["v_mov_b32_e32 v6, 0"] + product[2:])
