@@ -646,8 +646,8 @@ __device__ __forceinline__ void bound_tile(floatx4& v, int ct, int32_t ct_free, 
   "s_branch .Lsea_done%=\n.Lsea_none%=:\n\t" \
   "v_mov_b32 %[x0], %[none]\n\tv_mov_b32 %[x1], %[none]\n\tv_mov_b32 %[x2], %[none]\n\tv_mov_b32 %[x3], %[none]\n.Lsea_done%=:"
 #define SEA_TILE_OPERANDS \
-  : [x0] "+v"(x0), [x1] "+v"(x1), [x2] "+v"(x2), [x3] "+v"(x3), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3), \
-    [sum] "+v"(sum), [t] "=&v"(t), [u] "=&v"(u) \
+  : [x0] "+&v"(x0), [x1] "+&v"(x1), [x2] "+&v"(x2), [x3] "+&v"(x3), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3), \
+    [sum] "+&v"(sum), [t] "=&v"(t), [u] "=&v"(u) \
   : [free] "s"(ct_free), [edges] "s"(edges), [ct] "n"(ct), [last] "v"(last), [diag] "v"(diag), [none] "v"(kNoCandidate) \
   : "scc"
   if constexpr (CAUSAL)

@@ -24,7 +24,7 @@ __device__ __forceinline__ uint32_t mark_at_least(const uint32_t (&a)[4], const 
       "v_addc_co_u32 %0, vcc, %0, %0, %2\n\tv_cmp_ge_u32 %2, %4, %12\n\t"
       "v_addc_co_u32 %0, vcc, %0, %0, %3\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
       "v_addc_co_u32 %0, vcc, %0, %0, %2"
-      : "+v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2)
+      : "+&v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2)
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(floor)
       : "vcc");
   return w;
@@ -50,7 +50,7 @@ __device__ __forceinline__ uint32_t mark_at_least(floatx16 v, uint32_t floor, ui
       "v_cmp_ge_u32 %3, %5, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
       "v_cmp_ge_u32 %1, %4, %20\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
       "v_addc_co_u32 %0, vcc, %0, %0, %3\n\tv_addc_co_u32 %0, vcc, %0, %0, %1"
-      : "+v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2)
+      : "+&v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2)
       : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]),
         "v"(v[8]), "v"(v[9]), "v"(v[10]), "v"(v[11]), "v"(v[12]), "v"(v[13]), "v"(v[14]), "v"(v[15]), "v"(floor)
       : "vcc");

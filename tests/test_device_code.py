@@ -143,3 +143,19 @@ def test_distances_are_seen():
     assert _too_close(product)
     assert not _too_close(product[:1] + ["s_nop 7"] + product[2:])
     assert not _too_close(product[:1] + ["v_mov_b32_e32 v6, 0"] + product[2:])
+
+
+def test_outputs_of_several_instructions_are_early():
+    """An output that is written before all inputs are read must not share a register with one of them: `&`."""
+    from paper_2310_01777_amd import build
+    several = 0
+    for path in sorted(glob.glob(os.path.join(build.CSRC, "*"))):
+        with open(path) as f:
+            text = f.read()
+        # an asm statement, or a macro that is a part of one
+        for part in re.findall(r"\basm(?: volatile)?\s*\((?:[^;]|;(?!\n))*;|#define \w+_OPERANDS(?:.*\\\n)*.*", text):
+            code, _, operands = part.partition(":" if part.startswith("asm") else "OPERANDS")
+            if "\\n" in code or part.startswith("#define"):
+                several += 1
+                assert not re.findall(r'"[=+](?!&)[vs]"', operands), (path, part)
+    assert several >= 5
