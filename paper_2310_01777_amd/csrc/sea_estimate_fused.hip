@@ -614,8 +614,8 @@ __device__ __forceinline__ void store_mask_words(const Shape& s, const uint32_t 
 // cc = 16 ct + 4 lg + i; ncnd = the row's number of admissible columns (0: inactive row), a causal row takes its
 // own column (the last of them) from diag.  Tiles below ct_free lie wholly below every row's last column and
 // need no test; tiles from column ncols_wave on hold nothing.
-// A column that is no candidate of its row is a positive NaN from its first test on: no factor changes that, and as a
-// selection key it lies below every score.  (Before, every column was tested in three passes, with copies that the compiler
+// A column that is no candidate of its row is a positive NaN from its first test on: v_mul_f32 keeps its sign whatever the
+// factor, and as a selection key it lies below every score.  (Before, every column was tested in three passes, with copies that the compiler
 // made around the tests, and the selected columns were put together from comparisons and shifts: about 230 of the 1800 vector
 // instructions of a wave at m = K = 256.  Rows kernel alone, c4 at T = 32768 / c3: 320 -> 300 us, 166 -> 153 us.)
 // ------------------------------------------------------------------------------------------
@@ -680,10 +680,15 @@ __device__ __forceinline__ void finish_rows(const Shape& s, floatx4 (&acc)[NCT],
   // The normalised scores are kept NEGATED from here on: the bit pattern of -x (x >= +0) is
   // 0x80000000 | bits(x), which is the selection key itself, so the keys cost no instruction.
   const float ninv = r > 0.f ? -1.f / r : -0.f;
+  // (as instructions: the sign of a NaN is kept by the multiplier and not by the language, whose compiler may move a negation)
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[ct][i] *= ninv;
+    for (int i = 0; i < 4; ++i) {
+      float x = acc[ct][i];
+      asm("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(ninv));
+      acc[ct][i] = x;
+    }
   if (A_hat && trow < s.T) {
     float* out = A_hat + (head * s.T + trow) * s.K;
     if ((s.K & 3) == 0) {

@@ -117,3 +117,28 @@ def test_unlisted_keys_stay_out():
     print("[case] nonfinite lists", flush=True)
     sea.sea_sparse_attn(p, d["Q"], d["K"], d["V"], torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda(), L, O)
     _check(O, idx, cnt, x, wl, bad, True)
+
+
+@pytest.mark.parametrize("T,m,K,k_hat", [(512, 64, 128, 5), (700, 256, 100, 99), (1024, 128, 64, 40), (2048, 256, 256, 200)])
+def test_columns_past_a_row_are_never_selected(T, m, K, k_hat):
+    """Rows whose scores are ordinary, all zero, infinite or NaN: no column behind a causal row's own, none of padding."""
+    from paper_2310_01777_amd import binding as sea
+    wl = synth.Workload("nonfinite", 2, 5, T, 64, m, K, k_hat, 0, True, "bf16", 4)
+    x = synth.make_inputs(wl)
+    x["K"][:, 1] *= 1e3                              # features vanish: every score zero
+    x["Q"][:, 2, 3::7] = float("nan")
+    x["K"][:, 3, T // 3] = float("nan")
+    x["Q"][:, 4, 3::7, 9], x["K"][:, 4, T // 2, 3] = float("inf"), float("-inf")
+    lens = torch.tensor([T, T - T // 3], dtype=torch.int32)
+    p = sea.SeaParams(B=2, H=5, T=T, d=64, m=m, K=K, k_hat=k_hat, causal=True, scale=wl.scale, dtype="bf16", seq_len=lens.cuda())
+    words = torch.full((2, 5, T, (K + 31) // 32), -1, dtype=torch.int32, device="cuda")
+    d = {k: x[k].cuda() for k in "QKVW"}
+    print(f"[case] columns past a row {(T, m, K, k_hat)}", flush=True)
+    sea.sea_forward(p, d["Q"], d["K"], d["V"], d["W"], torch.empty_like(d["Q"]), workspace=sea.alloc_workspace(p), mhat=words)
+    got = ((words.cpu()[..., None] >> torch.arange(32, dtype=torch.int32)) & 1).flatten(-2)
+    t, c = torch.arange(T), torch.arange(got.shape[-1])
+    allowed = (c[None] <= (t[:, None] * K) // T) & (c[None] < K)
+    allowed = allowed[None] & (t[None, :, None] < lens[:, None, None])
+    assert not (got.bool() & ~allowed[:, None]).any()
+    quota = torch.minimum(allowed.sum(-1), torch.tensor(k_hat))
+    assert torch.equal(got.sum(-1)[:, :2], quota[:, None].expand(2, 2, T))  # rows without NaN take all of their quota
