@@ -742,7 +742,8 @@ constexpr int kColStage = 32;   // columns of the state staged in LDS per step
 constexpr int kAnyWidth = 6;
 
 // (Waves per SIMD: what LDS leaves room for at m = 256; at fewer features what the registers of the widest case need.  Left to
-// itself the compiler takes 150 registers for 65 to 128 columns where 84 do, and half of the waves are gone.)
+// itself the compiler takes 150 registers for 65 to 128 columns where 84 do, and half of the waves are gone.  Three everywhere / so:
+// c2 16.7 / 16.3 us, 48 heads of 4096, m = 128, K = 256 42.9 / 42.0, other shapes the same.)
 template <int MC, bool CAUSAL, int WLOG, int NCT>
 __global__ __launch_bounds__(256, MC == 8 ? 3 : NCT == 16 ? 4 : 5) void estimate_rows_kernel(Shape s, const uint16_t* __restrict__ Q,
                                                             const uint16_t* __restrict__ K,
@@ -1108,7 +1109,8 @@ __global__ __launch_bounds__(64 * kBidirWaves, SCORES ? 2 : 4) void estimate_row
   const uint32_t lo = static_cast<uint32_t>(all * lb / gridDim.x), hi = static_cast<uint32_t>(all * (lb + 1) / gridDim.x);
 
   // Rows of the head in hand per column, added to the layer's counters when the head changes: the attention that groups rows by
-  // column needs no pass over the mask for them (12 heads of 131072 rows: 9.7 us, this kernel the same; the layer 263.0 -> 256.6).
+  // column needs no pass over the mask for them (12 heads of 131072 rows: 9.7 us, this kernel the same, though at m = 128 four of its
+  // registers are kept in memory around the inner loop for it; the layer 263.0 -> 256.6).
   __shared__ int32_t taken[16 * NCT];
   if (tid < 16 * NCT) taken[tid] = 0;
   auto hand_in = [&](uint32_t head) {
