@@ -1481,8 +1481,11 @@ void launch_rows_k(const Shape& s, const uint16_t* Q, const uint16_t* K, const u
     launch_rows<MC, WLOG, 16>(s, Q, K, W, A_hat, mbits, f, c_dot, c_norm, gh, grid, st);
 }
 
-// layers of the kernel for one column per row: from two row groups per resident block on (equal to the other kernel there,
-// ahead from four on)
+// Layers of the kernel for one column per row: from two groups of 128 rows per resident block on.  Layer with the other kernel /
+// this one, us, m = K = 128: 32768 rows 26.1 / 27.0, 65536 32.7 / 31.3, 98304 40.0 / 38.7, 131072 45.6 / 42.2, 262144 68.4 / 63.7;
+// K = 96 65536 89.5 / 88.8; m = 64, K = 100 65536 80.7 / 79.1.  (By these the line could lie at half of that.  It stays where it
+// is: the two kernels add a row's scores up in different orders, so layers that change sides may take another of two columns
+// whose scores are a unit in the last place apart.)
 bool one_column_rows(const Shape& s) {
   const int64_t groups = (s.T + 16 * kBidirWaves - 1) / (16 * kBidirWaves) * s.N;
   return s.m <= 128 && !s.causal && !s.seq_len && s.k_hat == 1 && s.K > 64 && s.K <= 128 && groups >= 2 * kBidirBlocks && groups < (1ll << 28);
