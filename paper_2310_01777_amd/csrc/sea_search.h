@@ -8,8 +8,8 @@
 // a row far below its largest, or zero) would be walked down to in steps of a few octaves, so the reach, eight octaves at
 // first, doubles with every step, and from the ninth step on the range is halved: 8 + 14 steps at most.
 //
-// Steps for the slowest of 16 rows, bit by bit (as far as the quota or one key more) / so: scores of c4 9.2 / 5.1, of c3
-// (k^ = 64) 10.1 / 5.6, of c2 6.4 / 3.3; queries and keys of twice c3's size 8.9 / 6.5, of three times 8.5 / 8.1; a tenth of the
+// Steps for the slowest of 16 rows (simulated on one to three heads), bit by bit, as far as the quota or one key more / so: c4 9.2 / 5.1, c3
+// (k^ = 64) 10.1 / 5.6, c2 6.4 / 3.3; queries and keys of twice c3's size 8.9 / 6.5, of three times 8.5 / 8.1; a tenth of the
 // columns sixty octaves above the rest 8.6 / 8.0, most scores zero 11.5 / 12.8, all but twenty 15 / 19.  (With a reach of
 // eight octaves throughout and no halving: 4.9, 5.6, 3.0, 10.8, 27, 25, 36, 68.  The layer of c3 at three times the size: 481 us
 // bit by bit, 595 with that reach, 462 so; at its own size 396 / 377 / 377.)
