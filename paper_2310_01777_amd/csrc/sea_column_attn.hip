@@ -76,7 +76,7 @@ __global__ __launch_bounds__(64 * RW * NS, NS == 1 && !ODD ? 4 : 3) void column_
   const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wid = NS > 1 ? wall % RW : wall, set = NS > 1 ? wall / RW : 0;
   const int ql = lane & 31, g = lane >> 5;
-  // launch order as in the power-of-two kernel: heads in groups whose keys fit the L2s, longest tiles first
+  // launch order as in the power-of-two kernel: heads in groups, in a group the longest tiles first
   const uint32_t wgs = (a.T + kRows - 1) / kRows;
   const uint32_t per_group = static_cast<uint32_t>(a.group_heads) * wgs;
   const uint32_t place_b = dealt_in_turn(blockIdx.x, gridDim.x, NS == 1 ? 4 : 1, a.causal);
@@ -383,7 +383,7 @@ hipError_t launch_column_attn(const Shape& s, const uint16_t* Q, const uint16_t*
   a.A = a.g.r == 0 ? s.K : 1; a.D = a.g.r == 0 ? s.T : a.g.r;
   a.q32 = 32 * a.A / a.D; a.r32 = 32 * a.A % a.D;
   a.causal = s.causal; a.c = s.scale * kLog2e;
-  a.group_heads = group_heads_for(s.N, a.g.U);
+  a.group_heads = group_heads_for(s, a.g.U);
   // How the waves of a block are split: three sets of four waves where the launch leaves room (128-row blocks:
   // one per CU; causal, two, since half of them are short) or its longest lists dominate it, and six sets of
   // two on 64 rows where those still leave room.  Whole forward, K = 128, k^ = 48, H = 12, causal, us with one /

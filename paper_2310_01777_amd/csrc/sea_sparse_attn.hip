@@ -183,7 +183,7 @@ __device__ __forceinline__ bool takes_tiles(const Shape& s, int64_t head, int32_
   const float rows = 8.f * static_cast<float>(s.H), windows = static_cast<float>(min(last, s.T - 1) + 1) / static_cast<float>(kWindow);
   return n > 0 && fmaf(kRowKeyNs, static_cast<float>(n), kRowsNs * rows) >= rows * fmaxf(0.9f * kWindowNs * windows, kBlockNs);
 }
-// block -> (head, first row): heads in groups that share the L2s, the last (longest, if causal) rows first
+// block -> (head, first row): heads in groups, the last (longest, if causal) rows first
 __device__ __forceinline__ void tile_block(const Shape& s, int32_t group_heads, int64_t* head, int32_t* row0) {
   const uint32_t wgs = (s.T + kTileRows - 1) / kTileRows;
   const uint32_t per_group = static_cast<uint32_t>(group_heads) * wgs;
@@ -557,7 +557,7 @@ void launch_lists(const Shape& s, sea_dtype dt, const void* Q, const void* K, co
   if (apart && tiles_worth_a_launch(s, tiles, longest)) {
     const auto kernel = starts_odd(k) || starts_odd(v) ? &list_tile_kernel<FLAT, true> : &list_tile_kernel<FLAT, false>;
     hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(tiles)), dim3(256), 0, st, s, q, k, v, idx, cnt, L, crow, o,
-                       group_heads_for(s.N, s.T));
+                       group_heads_for(s, s.T));
     hipLaunchKernelGGL(list_rest_kernel<FLAT>, row_grid((nrows + kRestRows - 1) / kRestRows), block, 0, st, s, q, k, v, idx,
                        cnt, L, crow, o);
   } else {

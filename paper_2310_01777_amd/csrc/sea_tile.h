@@ -146,8 +146,8 @@ __device__ __forceinline__ uint32_t dealt_in_turn(uint32_t block, uint32_t grid,
 
 #endif  // __HIPCC__
 
-// heads whose keys and values (2 x U x 128 B each) share the L2s at one time
-int32_t group_heads_for(int32_t N, int64_t U);
+// heads whose row tiles are dealt out together, from a list of U keys each
+int32_t group_heads_for(const Shape& s, int64_t U);
 
 // A lane's half of its row of a result (O^T accumulators times inv), 8 bytes at a time
 __device__ __forceinline__ void store_row(uint16_t* row, const floatx16 (&oacc)[2], float inv) {

@@ -26,6 +26,7 @@
 #include "sea_internal.h"
 #include "sea_tile.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace sea {
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(64 * RW * NS, tile_waves(RW, NS, ODD)) void tile_at
     ubase = col << a.rlog;
     ulim = ubase + (1 << a.rlog);
   } else {
-    // Launch order = longest first: heads are taken in groups whose keys and values fit the L2s;
+    // Launch order = longest first: heads are taken in groups (group_heads_for);
     // inside a group the row tiles go from the last (most keys, causal) to the first, heads
     // fastest.  Blocks are dealt round-robin to the 8 XCDs, so with 8 | group size a head stays on
     // one XCD, and blocks that start late are the short ones that fill the gaps.
@@ -855,12 +856,22 @@ __global__ __launch_bounds__(256) void bucket_merge_kernel(const uint32_t* __res
 
 // Heads per scheduling group: the keys and values (2 x U x 128 B per head) of the heads an
 // XCD works on at one time should fit its 4 MB L2 with room to spare.
-int32_t group_heads_for(int32_t N, int64_t U) {
+// Causal: inside a group the long tiles come first, so a launch ends evenly only if the last group has blocks of all
+// lengths for every CU, and groups that fit the L2s (768 blocks at U = 2048, of 1024 that are resident) do not: a last
+// group of a few heads starts with its longest tiles when the others are nearly done.  From two blocks per resident one on
+// (2048) balance is worth more than the L2, whose misses the memory-side cache takes (twice the L2s' keys and values in
+// flight).  Layer, us, groups that fit the L2s / equal groups of at least 2048 blocks: H = 32, K = 256, k^ = 64, T = 2048, B = 8
+// (48 / 128 heads) 358 / 343, ragged T = 2000 473 / 440, T = 4096, B = 4 (48 / 64) 356 / 346, T = 8192, B = 2 (48 / 32) 368 / 361, with
+// whole columns (8 / 32) 850 / 793; H = 12, K = 128, B = 8, T = 2048 (48 / 96) 114.6 / 110.8, T = 4096 (24 / 96) 339 / 325.  Other
+// sizes at the first of these: 32, 64, 96, 160, 256 heads 351, 350, 346, 348, 352.
+int32_t group_heads_for(const Shape& s, int64_t U) {
   const int64_t per_head = 2 * U * kHeadDim * 2;
-  int64_t per_xcd = (3 << 20) / (per_head > 0 ? per_head : 1);
-  if (per_xcd < 1) per_xcd = 1;
-  const int64_t g = 8 * per_xcd;
-  return static_cast<int32_t>(g < N ? g : N);
+  int64_t g = 8 * std::max<int64_t>(1, (3 << 20) / std::max<int64_t>(per_head, 1));
+  if (s.causal) {
+    const int64_t groups = std::max<int64_t>(1, static_cast<int64_t>(s.N) * ((s.T + 127) / 128) / 2048);
+    g = std::max(g, ((s.N + groups - 1) / groups + 7) / 8 * 8);
+  }
+  return static_cast<int32_t>(std::min<int64_t>(g, s.N));
 }
 
 #ifndef SEA_NW8_MIN_BLOCKS
@@ -1056,7 +1067,7 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
   a.Q = Q; a.K = K; a.V = V; a.mbits = mbits; a.O = O; a.seq_len = s.seq_len;
   a.N = s.N; a.H = s.H; a.T = s.T; a.U = U; a.KW = (s.K + 31) / 32;
   a.rlog = rlog; a.w = w; a.causal = s.causal;
-  a.group_heads = group_heads_for(s.N, U);
+  a.group_heads = group_heads_for(s, U);
   a.c = s.scale * kLog2e;
   const WaveSplit split = wave_split(s, U, false);
 #define SEA_TILE(R_)                                                                        \
@@ -1440,7 +1451,7 @@ hipError_t launch_tile_attn_keybits(const Shape& s, const uint16_t* Q, const uin
   TileArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.mbits = kb; a.O = O; a.seq_len = s.seq_len;
   a.N = s.N; a.H = s.H; a.T = s.T; a.U = s.T; a.KW = (s.T + 31) / 32; a.rlog = 0; a.w = 1; a.causal = s.causal;
-  a.group_heads = group_heads_for(s.N, s.T);
+  a.group_heads = group_heads_for(s, s.T);
   a.c = s.scale * kLog2e;
   switch (wave_split(s, s.T, true)) {
     case kPairs: launch_tile<0, 3, 2, 4, 1>(s, a, st); break;
@@ -1464,7 +1475,7 @@ hipError_t launch_dense_attn(const Shape& s, sea_dtype dt, const void* Q, const 
   a.mbits = nullptr; a.O = static_cast<uint16_t*>(O); a.seq_len = s.seq_len;
   a.N = s.N; a.H = s.H; a.T = s.T; a.U = s.T; a.KW = 0; a.rlog = 0; a.w = 1;
   a.causal = s.causal; a.c = s.scale * kLog2e;
-  a.group_heads = group_heads_for(s.N, s.T);
+  a.group_heads = group_heads_for(s, s.T);
   if (wide_blocks(s)) launch_tile<0, 1, 8, 1, 2>(s, a, st);
   else launch_tile<0, 1, 4, 1, 2>(s, a, st);
   return hipGetLastError();

@@ -12,9 +12,10 @@ pytestmark = pytest.mark.gpu
 
 # (dtype, heads, T, K): 296 tiles of 128 rows (two sets of waves); 352 contraction and 693 attention tiles; 296 tiles of
 # ragged columns (three sets, in the ordinary order); 783 tiles with one set of waves, of both kinds of columns: the last
-# round that runs backwards has 15 of them; three whole rounds
+# round that runs backwards has 15 of them; three whole rounds; two groups of heads, 72 and 65, of both kinds of columns
 @pytest.mark.parametrize("dtype,H,T,K", [("bf16", 37, 1024, 64), ("f32", 11, 1000, 40), ("f32", 11, 1024, 128),
-                                         ("bf16", 37, 999, 60), ("bf16", 87, 1152, 72), ("bf16", 87, 1100, 60), ("bf16", 96, 1024, 128)])
+                                         ("bf16", 37, 999, 60), ("bf16", 87, 1152, 72), ("bf16", 87, 1100, 60), ("bf16", 96, 1024, 128),
+                                         ("bf16", 137, 4096, 128), ("bf16", 137, 4000, 120)])
 def test_a_head_among_many(dtype, H, T, K):
     from paper_2310_01777_amd import binding as sea
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
