@@ -184,7 +184,7 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
                                                             float* __restrict__ A_hat, int32_t parts,
                                                             int32_t part_cols, int32_t stride, int32_t cshift,
                                                             uint32_t* __restrict__ mbits, uint32_t* __restrict__ kb,
-                                                            int32_t KWk) {
+                                                            int32_t KWk, int32_t group_heads) {
   constexpr int kTileRows = 32 * U;  // query rows of the block
   extern __shared__ __align__(16) double lds[];  // [P][rows][stride] bins, [rows][P] row sums, [rows] inverses
   const int lane = threadIdx.x & 63, q = lane & 31, h = lane >> 5;
@@ -194,12 +194,21 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
   double* tot_s = lds + static_cast<size_t>(P) * kTileRows * stride;
   const uint32_t nch = (s.T + kChunk - 1) / kChunk;
   const uint32_t tiles = (s.T + kTileRows - 1) / kTileRows;
-  // Head-major, each XCD on a contiguous range of blocks: the row tiles of a head run close together
-  // on one XCD, whose L2 then serves all but the first read of the head's key features.  Within a
-  // head the longest (last) row tiles come first.
-  const uint32_t lb = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int64_t head = lb / tiles;
-  const uint32_t tile = tiles - 1 - lb % tiles;
+  // Heads in groups, in a group the longest (last) row tiles first and heads fastest: a head stays on one XCD, whose L2
+  // then serves all but the first read of its key features.  (No groups: head-major, each XCD on a run of blocks.)
+  uint32_t at = blockIdx.x, first = 0, nh = 1;
+  if (group_heads > 0) {
+    const uint32_t per_group = static_cast<uint32_t>(group_heads) * tiles, grp = at / per_group;
+    first = grp * group_heads;
+    nh = min(static_cast<uint32_t>(group_heads), static_cast<uint32_t>(s.N) - first);
+    at -= grp * per_group;
+  } else {
+    at = xcd_contiguous(at, gridDim.x);
+    first = at / tiles;
+    at -= first * tiles;
+  }
+  const int64_t head = first + at % nh;
+  const uint32_t tile = tiles - 1 - at / nh;
   const int32_t r0 = static_cast<int32_t>(tile) * kTileRows;
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
@@ -495,9 +504,16 @@ hipError_t launch_tiles(const Shape& s, const uint4* phiQ, const uint4* phiK, fl
                                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(p.lds));
     if (e != hipSuccess) return e;
   }
-  const uint32_t tiles = (s.T + 32 * U - 1) / (32 * U);
-  hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT, U>), dim3(static_cast<uint32_t>(s.N) * tiles), dim3(64 * p.waves), p.lds, st, s,
-                     phiQ, phiK, A_hat, p.parts, p.part_cols, p.stride, p.cshift, mbits, kb, (s.T + 31) / 32);
+  const uint32_t tiles = (s.T + 32 * U - 1) / (32 * U), blocks = static_cast<uint32_t>(s.N) * tiles;
+  // Heads whose key features share an XCD's L2, 2 MB worth, are dealt out together, so that what is left at a launch's end are
+  // short tiles; head after head, the last head's longest tiles began when the others were done.  Launches of at most one
+  // block per CU have no such end.  Layer, us, head after head / groups: K = 128, m = 128, H = 12, T = 2048, B = 4 163.2 / 159.4,
+  // B = 1 72.1 / 68.2, T = 4096, B = 4 467 / 450, B = 1 165 / 140, T = 1001, B = 2 51.1 / 48.7, T = 500, B = 1 (192 blocks) 30.4 / 31.0;
+  // H = 32, m = K = 256, T = 2048, B = 8 1553 / 1529, B = 2 412 / 400 (groups of 48 heads 1536 and 405, of 128 1616).
+  const int64_t per_xcd = std::max<int64_t>(1, (int64_t(2) << 20) / (static_cast<int64_t>(s.T) * s.m * 2));
+  const int32_t group_heads = blocks <= 256 ? 0 : static_cast<int32_t>(std::min<int64_t>(s.N, 8 * per_xcd));
+  hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT, U>), dim3(blocks), dim3(64 * p.waves), p.lds, st, s, phiQ, phiK, A_hat, p.parts,
+                     p.part_cols, p.stride, p.cshift, mbits, kb, (s.T + 31) / 32, group_heads);
   return hipGetLastError();
 }
 
