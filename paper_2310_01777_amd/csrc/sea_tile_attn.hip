@@ -889,23 +889,27 @@ static bool wide_blocks(const Shape& s) {
 // does, so sets of waves share the rows of a block and walk the list in parallel (the merge costs about one
 // 64-key chunk).  kPairs: 64 rows, four sets of two waves, while the 128-row blocks number at most one per CU
 // (half the rows halve a CU's longest work as well); per-key bits (MODE 3) cost more per step, so there a
-// little longer.  kFour, kTwo: 128 rows, four or two sets of four waves, up to what is resident at once (kFour
-// where the last rows of a causal list have many times the keys of the first; per-key bits again longer).
-// Whole forward, K = 128, k^ = 64, H = 12, causal, us as kOne / kTwo / kFour / kPairs: T = 512, B = 1 (48 blocks)
-// 30 / 29 / 29 / 25, B = 4 (192) 32 / 31 / 32 / 28; T = 1024, B = 4 (384) 43 / 38 / 41 / 39; T = 2048, B = 1
-// (192) 60 / 50 / 46 / 40, B = 3 (576) 67 / 60 / 72 / 64, B = 4 (768) 73 / 73 / 84 / 77; T = 4096, B = 1 (384)
-// 100 / 79 / 69 / 72; per-key bits, T = 2048, B = 1 125 / 102 / 99 / 88, B = 2 153 / 131 / 127 / 122, B = 4
-// 220 / 214 / 228 / 219; bidirectional, T = 1024, B = 4 52 / 49 / 55 / 48, T = 512, B = 8 42 / 43 / 50 / 42.
-// Where the lines of kTwo lie (kOne / kTwo): two of its blocks are resident per CU, 512, which is the line when all
-// blocks are equally long (bidirectional, T = 1536, H = 24, B = 2 (576) 76.7 / 79.4); per-key bits gain up to three
-// 128-row blocks per CU (the attention alone, H = 32, T = 3000 (768) 110 / 87, H = 16, T = 6000 (752) 187 / 147, H = 12,
-// T = 8000 (756) 290 / 220) and lose above (H = 32, T = 3500 (896) 138 / 151).
-enum WaveSplit { kOne, kTwo, kFour, kPairs };
+// little longer.  kHalves: 64 rows, two sets of two waves, whose blocks are as many waves as kOne's 128 rows: half the list and
+// half the rows per block, and two blocks end where one did, up to what is resident at once.  kFour: 128 rows, four sets of
+// four waves, where the last rows of a causal list have many times the keys of the first.  kTwo: 128 rows, two sets of four.
+// Whole forward, K = 128, H = 12, us as kOne / kTwo / kHalves / kPairs (kFour): causal, k^ = 48, T = 1024, B = 2 (192 blocks of 128)
+// 33.7 / 29.5 / 27.8 / 26.0, B = 3 (288) 35.3 / 31.4 / 28.8 / 31.1, B = 4 (384) 35.0 / 31.3 / 29.1 / 33.4, B = 6 (576) 39.8 / 39.8 / 39.1 / 44.0,
+// B = 8 (768) 45.0 / 48.1 / 46.6 / 53.1; T = 2048, B = 2 (384) 49.4 / 41.1 / 38.3 / 41.1, B = 3 (576) 55.4 / 51.8 / 49.4 / 55.6, B = 4 (768)
+// 60.9 / 62.3 / 60.8 / 66.9; H = 20, B = 1 (320) 49.2 / 41.1 / 37.5 / 38.2; T = 4096, B = 1 (384) 82.6 / 63.1 / 60.2 / 60.1 (57.8), H = 8, T = 8192
+// (512) 149 / 113 / 112.5 / 114 (108); T = 512, K = 64, k^ = 16, B = 10 (480) 28.9 / 28.1 / 27.1 / 33.3, B = 12 (576) 31.3 / 35.3 / 32.7 / 38.2;
+// T = 256, B = 18 (432) 24.7 / 25.4 / 25.0 / 30.6.  Bidirectional, T = 1024, B = 3 41.0 / 39.6 / 36.5 / 39.4, B = 4 40.9 / 39.5 / 37.2 / 39.5, B = 5 (480)
+// 43.9 / 43.0 / 44.5 / 48.4, B = 6 52.7 / 55.1 / 52.7 / 56.4; T = 2048, B = 2 59.5 / 55.6 / 52.7 / 54.6; T = 512, K = 64, B = 8 (384) 29.4 / 29.8 / 28.1 / 33.3, B = 10
+// 31.7 / 31.9 / 32.5 / 36.8.  Per-key bits, T = 2048, B = 1 94 / 78 / 77 / 68, B = 2 119 / 103 / 103 / 99, B = 3 149 / 134.4 / 133.9 / 142, B = 4 169 /
+// 165.2 / 163.5 / 175, T = 1024, B = 6 107 / 102.5 / 100.8 / 111, B = 8 123.0 / 124.9 / 122.3 / 132, T = 4096, B = 2 (768) 263 / 247 / 247 / 257, H = 32,
+// T = 3500 (896) 258 / 253 / 252 / 265.
+enum WaveSplit { kOne, kTwo, kFour, kPairs, kHalves };
 static WaveSplit wave_split(const Shape& s, int32_t U, bool key_bits) {
   const int64_t blocks = static_cast<int64_t>(s.N) * ((s.T + 127) / 128);
   if (U >= 256 && blocks <= (key_bits ? 384 : 256)) return kPairs;
   if (U >= 4096 && blocks <= 512 && s.causal) return kFour;
-  if (U >= 1024 && blocks <= (key_bits && U >= 2048 ? 768 : (s.causal ? 576 : 512))) return kTwo;
+  if (key_bits) return U >= 1024 && blocks <= (U >= 2048 ? 896 : 768) ? kHalves : kOne;
+  if (U >= 512 && blocks <= (!s.causal ? 384 : (U >= 1024 ? 576 : 512))) return kHalves;
+  if (U >= 1024 && blocks <= 512) return kTwo;
   return kOne;
 }
 
@@ -1073,6 +1077,7 @@ hipError_t launch_tile_attn(const Shape& s, const uint16_t* Q, const uint16_t* K
 #define SEA_TILE(R_)                                                                        \
   switch (split) {                                                                          \
     case kPairs: launch_tile<R_, 0, 2, 4, 1>(s, a, st); break;                              \
+    case kHalves: launch_tile<R_, 0, 2, 2, 1>(s, a, st); break;                             \
     case kFour: launch_tile<R_, 0, 4, 4, 2>(s, a, st); break;                               \
     case kTwo: launch_tile<R_, 0, 4, 2, 2>(s, a, st); break;                                \
     default: launch_tile<R_, 0, 4, 1, 2>(s, a, st); break;                                  \
@@ -1455,8 +1460,8 @@ hipError_t launch_tile_attn_keybits(const Shape& s, const uint16_t* Q, const uin
   a.c = s.scale * kLog2e;
   switch (wave_split(s, s.T, true)) {
     case kPairs: launch_tile<0, 3, 2, 4, 1>(s, a, st); break;
+    case kHalves: launch_tile<0, 3, 2, 2, 1>(s, a, st); break;
     case kFour: launch_tile<0, 3, 4, 4, 2>(s, a, st); break;
-    case kTwo: launch_tile<0, 3, 4, 2, 2>(s, a, st); break;
     default: launch_tile<0, 3, 4, 1, 2>(s, a, st); break;
   }
   return hipGetLastError();

@@ -91,9 +91,10 @@ SAME_KERNEL = [
     ("bf16", 1, 90, 300, 64, 128, 100, 0, False, 0),
     ("bf16", 1, 2, 512, 64, 64, 16, 0, True, 0),      # powers of two: 64 rows and four sets of waves,
     ("bf16", 1, 9, 4096, 64, 64, 16, 0, True, 0),     # 128 rows and four,
-    ("bf16", 1, 36, 1024, 64, 64, 16, 0, True, 0),    # two,
+    ("bf16", 1, 60, 1024, 64, 64, 16, 0, False, 0),   # two,
+    ("bf16", 1, 36, 1024, 64, 64, 16, 0, True, 0),    # 64 rows and two,
     ("bf16", 1, 70, 512, 64, 64, 16, 0, True, 0),     # one
-    ("bf16", 1, 2, 700, 64, 64, 16, 0, True, 1),      # per-row widths (key bits): the same four
+    ("bf16", 1, 2, 700, 64, 64, 16, 0, True, 1),      # per-row widths (key bits): the same
     ("bf16", 1, 13, 4096, 64, 64, 16, 0, True, 1),
     ("bf16", 1, 26, 2048, 64, 64, 16, 0, True, 1),
     ("bf16", 1, 100, 512, 64, 64, 16, 0, True, 1),

@@ -10,7 +10,7 @@ from util import TOL
 pytestmark = pytest.mark.gpu
 
 
-# (dtype, heads, T, K): 296 tiles of 128 rows (two sets of waves); 352 contraction and 693 attention tiles; 296 tiles of
+# (dtype, heads, T, K): 296 tiles of 128 rows (two sets of waves, 592 blocks); 352 contraction and 693 attention tiles; 296 tiles of
 # ragged columns (three sets, in the ordinary order); 783 tiles with one set of waves, of both kinds of columns: the last
 # round that runs backwards has 15 of them; three whole rounds; two groups of heads, 72 and 65, of both kinds of columns
 @pytest.mark.parametrize("dtype,H,T,K", [("bf16", 37, 1024, 64), ("f32", 11, 1000, 40), ("f32", 11, 1024, 128),

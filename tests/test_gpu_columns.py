@@ -58,8 +58,11 @@ ALIGNED_CASES = [
     (3, 4, 640, 64, 64, 20, 80, False, 0.5),     # the shortest list for sets, sequences of half a tile
     (1, 1, 4224, 64, 128, 16, 256, True, 0.0),   # 16 of 33
     (2, 2, 4096, 64, 64, 9, 0, True, 0.3),       # one column per chunk
-    (2, 17, 1000, 64, 250, 60, 0, True, 0.3),    # (too short for) two sets of four waves
-    (2, 17, 1024, 64, 256, 60, 0, True, 0.3),    # two sets of four waves
+    (2, 17, 1000, 64, 250, 60, 0, True, 0.3),    # two sets of two waves: a list that ends inside a chunk,
+    (2, 17, 1024, 64, 256, 60, 0, True, 0.3),    # four keys per column,
+    (3, 23, 512, 64, 512, 100, 0, True, 0.3),    # one: the shortest list for them,
+    (2, 19, 960, 64, 15, 4, 0, False, 0.3),      # 64, sequences of half a tile
+    (2, 26, 1024, 64, 256, 60, 0, False, 0.3),   # two sets of four waves
     (1, 9, 4096, 64, 128, 16, 0, True, 0.0),     # four
     (1, 2, 128, 64, 128, 31, 0, True, 0.0),      # one set, one key per column
     (2, 1, 200, 64, 100, 25, 0, False, 0.3),     # two

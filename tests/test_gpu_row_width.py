@@ -35,7 +35,7 @@ pytestmark = pytest.mark.gpu
     (1, 4, 4100, 128, 128, 20, 0, 0.0),
     (3, 28, 130, 64, 129, 40, 0, 0.0),     # K above 128: not there
     (1, 12, 4200, 64, 64, 4, 0, 0.0),      # attention: four sets of four waves (385 to 512 blocks of 128 rows)
-    (1, 25, 2050, 64, 64, 4, 0, 0.0),      # two sets (513 to 768)
+    (1, 25, 2050, 64, 64, 4, 0, 0.0),      # 64 rows and two sets of two waves (385 to 896)
     (1, 11, 4100, 256, 64, 4, 0, 0.3),     # groups of 8 and 3 heads
 ], ids=lambda c: "_".join(str(x) for x in c))
 def test_selection_in_the_estimate(case):
