@@ -54,5 +54,13 @@ hipError_t launch_dec_conv(const DecConv& c, uint16_t* out, hipStream_t st);
 // conv 3 on the image resized (nearest) to Tv x 2 X, and the softmax of its rows: A [B][Cout][Tout][2 X] fp32,
 // rows at or past seq_len zero
 hipError_t launch_dec_conv_softmax(const DecConv& c, int32_t Tv, float* A, const int32_t* seq_len, hipStream_t st);
+// all three layers of a causal image [B][T][X][4 H] in one launch; w, bias: the layers' in order
+struct DecChain {
+  const uint16_t* in;
+  const uint16_t* w[3];
+  const float* bias[3];
+  int32_t B, T, X, H;
+};
+hipError_t launch_dec_chain(const DecChain& c, float* A, const int32_t* seq_len, hipStream_t st);
 
 }  // namespace sea

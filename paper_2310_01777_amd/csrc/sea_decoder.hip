@@ -11,6 +11,8 @@
 // Kernels, in the order a call runs them:
 //   dec_linattn_kernel    C_perf from Q, K, V (sea_decoder_linattn.hip)
 //   dec_mlp_kernel        mu, nu, s_mix, s_prob (sea_decoder_mlp.hip)
+//   dec_conv_chain_kernel all three convolutions and the final softmax of causal layers with rows of 32 or 64 stored pixels
+//                         and 4, 8 or 12 heads (sea_decoder_chain.hip); others:
 //   dec_conv_tile_kernel, dec_conv_softmax_kernel
 //                         the convolutions of images with up to 64 channels and the final softmax
 //                         (sea_decoder_conv.hip); wider layers:
@@ -575,6 +577,15 @@ hipError_t launch_decoder_estimate(const Shape& s, const sea_decoder_weights& wt
   // mu, nu and the scalers: rows [C_perf; V] -> the CNN's input image [B][T][Wd][C], channels h c_h + ch
   e = launch_dec_mlp(s, wt, u16(lay.Cp), V, u16(lay.img), s_mix, s_prob, st);
   if (e != hipSuccess) return e;
+  if (s.causal) {  // (the strips of the one launch look back only)
+    DecChain n{};
+    n.in = u16(lay.img);
+    n.w[0] = static_cast<const uint16_t*>(wt.conv1_w); n.bias[0] = wt.conv1_b;
+    n.w[1] = static_cast<const uint16_t*>(wt.conv2_w); n.bias[1] = wt.conv2_b;
+    n.w[2] = static_cast<const uint16_t*>(wt.conv3_w); n.bias[2] = wt.conv3_b;
+    n.B = B; n.T = s.T; n.X = lay.Wd; n.H = s.H;
+    if ((e = launch_dec_chain(n, A_hat, s.seq_len, st)) != hipErrorNotSupported) return e;
+  }
   // conv 1: [B][T][Wd][C] -> [B][T1][Wd][C], ReLU.  Causal: rows t-2..t; else stride c_s, rows i c_s - 1 .. + 1
   DecConv c{};
   c.in = u16(lay.img); c.w = static_cast<const uint16_t*>(wt.conv1_w); c.bias = wt.conv1_b;
