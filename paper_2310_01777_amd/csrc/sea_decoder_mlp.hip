@@ -15,6 +15,9 @@
 // first layer has just read, against eight with a register set of their own for the next tile: 37.6 -> 31.7 us there (12
 // tiles per CU: one round instead of a full and a half one).  Tiles dealt over all blocks instead: 34.7, and the
 // convolution that follows waits for lines written by several XCDs (bidirectional layer 152 -> 158 us).
+// The weights a block stages are asked for in whole lines and all at once, before most rows: 30.3 -> 27.2 us there, K = 256 48 -> 42,
+// K = 64, T = 256, B = 1 13.2 -> 12.2 (before, a loop of one piece per thread after the other; with the rows of all waves in front,
+// the barrier behind the weights waits for those too).
 #include "sea_decoder.h"
 
 namespace sea {
@@ -22,6 +25,7 @@ namespace {
 
 constexpr int kCpDim = 128;   // [V_I; V] through the Performer: two value widths
 constexpr int kMlpWaves = 12, kMlpThreads = 64 * kMlpWaves;
+constexpr int kEarly = 4;                      // waves that ask for their rows in front of the weights: as many as do not hold those up
 constexpr int kMuSteps = 6, kHidSteps = 4;     // contraction steps of 32: 192 and 128 channels
 constexpr int kNu1Tiles = 9;                   // 128 outputs + one tile for the scalers
 constexpr int kSlabTiles = 16;                 // 256 outputs of nu's last layer per slab
@@ -40,6 +44,8 @@ struct MlpArgs {
   int64_t per_block;    // 32-row tiles of a block, neighbours
 };
 
+// Row: the type that row numbers are split with (a 64-bit division is a hundred instructions; rows past 2^32 need it)
+template <typename Row>
 __global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint4 mlp_lds[];
   uint4* w_mu = mlp_lds;                                  // [6][8][64]
@@ -53,49 +59,35 @@ __global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
   const int lr = lane & 15, lg = lane >> 4;
   const int32_t slabs = (a.out2 + 16 * kSlabTiles - 1) / (16 * kSlabTiles);
   const int32_t slab_tiles = min(kSlabTiles, (a.out2 + 15) / 16);
+  float* b_sc = reinterpret_cast<float*>(w_nu2 + kHidSteps * slab_tiles * 64);  // the scalers'
 
-  for (int32_t id = tid; id < kMuSteps * 8 * 64; id += kMlpThreads) {
-    const int32_t fl = id & 63, nt = (id >> 6) & 7, ks = id >> 9;
-    w_mu[id] = *reinterpret_cast<const uint4*>(a.mu_w + (16 * nt + (fl & 15)) * 192 + 32 * ks + 8 * (fl >> 4));
-  }
-  // eight channels of a 128-channel row in the order of packed accumulators
-  auto permuted = [](const uint16_t* row, int32_t ks, int32_t g) {
-    const uint2 p = *reinterpret_cast<const uint2*>(row + 32 * ks + 4 * g);
-    const uint2 q = *reinterpret_cast<const uint2*>(row + 32 * ks + 16 + 4 * g);
-    return make_uint4(p.x, p.y, q.x, q.y);
+  // Weights are read as they lie, a kilobyte of whole lines per wave (sixteen rows' 64-byte pieces at a time cost 80 clocks a load,
+  // with every CU at the same lines), all of them asked for before any is waited for, and take their order on the way to LDS.
+  // nu's rows of 128 channels in the order of packed accumulators: 16 bytes are the halves of two operands.
+  auto park_nu = [&](uint4* w, int32_t tiles, int32_t piece, uint4 v) __attribute__((always_inline)) {
+    const int32_t row = piece >> 4, p = piece & 15, half = (p >> 1) & 1;
+    uint2* const at = reinterpret_cast<uint2*>(w + ((p >> 2) * tiles + (row >> 4)) * 64 + 32 * (p & 1) + (row & 15)) + half;
+    at[0] = make_uint2(v.x, v.y);
+    at[32] = make_uint2(v.z, v.w);
   };
-  for (int32_t id = tid; id < kHidSteps * kNu1Tiles * 64; id += kMlpThreads) {
-    const int32_t fl = id & 63, q = id >> 6, ks = q / kNu1Tiles, nt = q - ks * kNu1Tiles;
-    const int32_t co = 16 * nt + (fl & 15);
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (co < 128) {
-      v = permuted(a.nu1_w + co * 128, ks, fl >> 4);
-    } else if (co < 130) {  // the scalers' vectors, whose alignment is only that of a pair
-      const uint32_t* r = reinterpret_cast<const uint32_t*>(co == 128 ? a.mix_w : a.prob_w) + 16 * ks + 2 * (fl >> 4);
-      v = make_uint4(r[0], r[1], r[8], r[9]);
-    }
-    w_nu1[id] = v;
-  }
-  if (tid < 128) b_mu[tid] = a.mu_b[tid];
-  else if (tid < 256) b_nu1[tid - 128] = a.nu1_b[tid - 128];
+  auto nu2_piece = [&](int32_t slab, int32_t piece) __attribute__((always_inline)) {
+    const int32_t co = slab * 16 * kSlabTiles + (piece >> 4);
+    const uint4 v = reinterpret_cast<const uint4*>(a.nu2_w)[static_cast<int64_t>(min(co, a.out2 - 1)) * 16 + (piece & 15)];
+    return co < a.out2 ? v : make_uint4(0u, 0u, 0u, 0u);
+  };
+  auto nu2_bias = [&](int32_t slab) { return a.nu2_b[min(slab * 16 * kSlabTiles + min(tid, 16 * slab_tiles - 1), a.out2 - 1)]; };
   auto stage_nu2 = [&](int32_t slab) {
-    for (int32_t id = tid; id < kHidSteps * slab_tiles * 64; id += kMlpThreads) {
-      const int32_t fl = id & 63, q = id >> 6, ks = q / slab_tiles, nt = q - ks * slab_tiles;
-      const int32_t co = (slab * kSlabTiles + nt) * 16 + (fl & 15);
-      const uint4 v = permuted(a.nu2_w + static_cast<int64_t>(min(co, a.out2 - 1)) * 128, ks, fl >> 4);
-      w_nu2[id] = co < a.out2 ? v : make_uint4(0u, 0u, 0u, 0u);
-    }
-    if (tid < 16 * slab_tiles) b_nu2[tid] = a.nu2_b[min(slab * 16 * kSlabTiles + tid, a.out2 - 1)];
+    for (int32_t id = tid; id < 256 * slab_tiles; id += kMlpThreads) park_nu(w_nu2, slab_tiles, id, nu2_piece(slab, id));
+    if (tid < 16 * slab_tiles) b_nu2[tid] = nu2_bias(slab);
   };
-  stage_nu2(0);
 
   const int64_t first = blockIdx.x * a.per_block, end = min(first + a.per_block, (a.rows + 31) / 32);
   // rows in the order (b, t, h), heads fastest: a wave's stores lie next to each other in the image
-  auto split = [&](int64_t pp, int32_t* h, int32_t* t, int32_t* b) {
-    const int64_t q = pp / a.H;
-    *h = static_cast<int32_t>(pp - q * a.H);
-    *b = static_cast<int32_t>(q / a.T);
-    *t = static_cast<int32_t>(q - static_cast<int64_t>(*b) * a.T);
+  auto split = [&](int64_t at, int32_t* h, int32_t* t, int32_t* b) {
+    const Row pp = static_cast<Row>(at), q = pp / static_cast<Row>(a.H);
+    *h = static_cast<int32_t>(pp - q * static_cast<Row>(a.H));
+    *b = static_cast<int32_t>(q / static_cast<Row>(a.T));
+    *t = static_cast<int32_t>(q - static_cast<Row>(*b) * static_cast<Row>(a.T));
   };
   bf16x8 xf[kMuSteps][2];
   auto request = [&](int64_t tile) {
@@ -111,8 +103,43 @@ __global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
     }
   };
   const int64_t tile0 = first + wid;
-  if (tile0 < end) request(tile0);
+  if (wid < kEarly && tile0 < end) request(tile0);
+  {
+    constexpr int kMu = 128 * 24 / kMlpThreads, kNu1 = (128 * 16 + kMlpThreads - 1) / kMlpThreads;
+    constexpr int kNu2 = (16 * kSlabTiles * 16 + kMlpThreads - 1) / kMlpThreads;
+    static_assert(kMu * kMlpThreads == 128 * 24, "whole rounds");
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 mu[kMu];  // (an array of uint4 that is only copied ends up in scratch memory)
+    uint4 nu1[kNu1], nu2[kNu2];
+#pragma unroll
+    for (int e = 0; e < kMu; ++e) mu[e] = reinterpret_cast<const u32x4*>(a.mu_w)[static_cast<uint32_t>(tid + kMlpThreads * e)];
+#pragma unroll
+    for (int e = 0; e < kNu1; ++e) nu1[e] = reinterpret_cast<const uint4*>(a.nu1_w)[static_cast<uint32_t>(min(tid + kMlpThreads * e, 128 * 16 - 1))];
+#pragma unroll
+    for (int e = 0; e < kNu2; ++e) nu2[e] = nu2_piece(0, min(tid + kMlpThreads * e, 256 * slab_tiles - 1));
+    // the scalers' vectors, whose alignment is only that of a pair: rows 0 and 1 of nu1's ninth tile
+    const uint32_t* const sv = reinterpret_cast<const uint32_t*>(lr & 1 ? a.prob_w : a.mix_w) + 16 * (wid & 3) + 2 * lg;
+    const uint4 sc = make_uint4(sv[0], sv[1], sv[8], sv[9]);
+    const float* const bp = tid < 128 ? a.mu_b + tid : (tid < 256 ? a.nu1_b + tid - 128 : (tid == 256 ? a.mix_b : a.prob_b));
+    const float bias = *bp, bias2 = nu2_bias(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < kMu; ++e) {
+      const int32_t id = tid + kMlpThreads * e, row = id / 24, p = id - row * 24;
+      reinterpret_cast<u32x4*>(w_mu)[((p >> 2) * 8 + (row >> 4)) * 64 + 16 * (p & 3) + (row & 15)] = mu[e];
+    }
+#pragma unroll
+    for (int e = 0; e < kNu1; ++e)
+      if (tid + kMlpThreads * e < 128 * 16) park_nu(w_nu1, kNu1Tiles, tid + kMlpThreads * e, nu1[e]);
+    if (wid < 4) w_nu1[(wid * kNu1Tiles + 8) * 64 + lane] = lr < 2 ? sc : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int e = 0; e < kNu2; ++e)
+      if (tid + kMlpThreads * e < 256 * slab_tiles) park_nu(w_nu2, slab_tiles, tid + kMlpThreads * e, nu2[e]);
+    if (tid < 258) (tid < 256 ? b_mu : b_sc - 256)[tid] = bias;  // (nu1's follow mu's)
+    if (tid < 16 * slab_tiles) b_nu2[tid] = bias2;
+  }
   __syncthreads();
+  if (wid >= kEarly && tile0 < end) request(tile0);
   // with one slab the loop has no barrier and a wave without a tile leaves it; with several, every wave of
   // the block stays for the barriers of the staging (the first wave's tile is the smallest)
   for (int64_t tile = tile0; slabs == 1 ? tile < end : tile - wid < end; tile += kMlpWaves) {
@@ -141,13 +168,17 @@ __global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) zf[kc][mt] = pack8(relu4(acc[0][mt]), relu4(acc[1][mt]));
       }
+      int32_t hh[2], tt[2], bb[2], lens[2];
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        split(min(tile * 32 + 16 * mt + lr, a.rows - 1), &hh[mt], &tt[mt], &bb[mt]);
+        lens[mt] = a.seq_len ? a.seq_len[bb[mt]] : a.T;
+      }
       if (tile + kMlpWaves < end) request(tile + kMlpWaves);  // the rows have left their registers
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
         const int64_t pp = tile * 32 + 16 * mt + lr;
-        int32_t h, t, b;
-        split(min(pp, a.rows - 1), &h, &t, &b);
-        const int32_t len = a.seq_len ? min(max(a.seq_len[b], 0), a.T) : a.T;
+        const int32_t h = hh[mt], t = tt[mt], b = bb[mt], len = min(max(lens[mt], 0), a.T);
         exists[mt] = pp < a.rows;
         live[mt] = t < len;
         orow[mt] = (static_cast<int64_t>(b) * a.T + t) * a.Wd * a.C + h * 4;
@@ -158,8 +189,8 @@ __global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
           sc = mfma16(__builtin_bit_cast(bf16x8, w_nu1[(kc * kNu1Tiles + 8) * 64 + lane]), zf[kc][mt], sc);
         if (lg == 0 && exists[mt]) {
           const int64_t r = (static_cast<int64_t>(b) * a.H + h) * a.T + t;
-          if (a.s_mix) a.s_mix[r] = live[mt] ? 1.f / (1.f + __expf(-(sc[0] + a.mix_b[0]))) : 0.f;
-          if (a.s_prob) a.s_prob[r] = live[mt] ? 1.f / (1.f + __expf(-(sc[1] + a.prob_b[0]))) : 0.f;
+          if (a.s_mix) a.s_mix[r] = live[mt] ? 1.f / (1.f + __expf(-(sc[0] + b_sc[0]))) : 0.f;
+          if (a.s_prob) a.s_prob[r] = live[mt] ? 1.f / (1.f + __expf(-(sc[1] + b_sc[1]))) : 0.f;
         }
       }
       // nu, first layer
@@ -230,14 +261,15 @@ hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const u
   a.H = s.H; a.T = s.T; a.Wd = s.K / 2; a.C = 4 * s.H; a.rows = static_cast<int64_t>(s.N) * s.T; a.out2 = 4 * a.Wd;
   const int32_t slab_tiles = std::min(kSlabTiles, (a.out2 + 15) / 16);
   const size_t lds = static_cast<size_t>(kMuSteps * 8 + kHidSteps * kNu1Tiles + kHidSteps * slab_tiles) * 1024 +
-                     (256 + 16 * kSlabTiles) * sizeof(float);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dec_mlp_kernel),
+                     (256 + 16 * kSlabTiles + 2) * sizeof(float);
+  const auto kernel = a.rows >> 32 ? &dec_mlp_kernel<int64_t> : &dec_mlp_kernel<uint32_t>;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;
   // an equal share of the tiles for each CU: small launches use all of them, with few waves each
   const int64_t tiles = (a.rows + 31) / 32;
   a.per_block = (tiles + 255) / 256;
-  hipLaunchKernelGGL(dec_mlp_kernel, dim3(static_cast<uint32_t>((tiles + a.per_block - 1) / a.per_block)), dim3(kMlpThreads), lds, st, a);
+  hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>((tiles + a.per_block - 1) / a.per_block)), dim3(kMlpThreads), lds, st, a);
   return hipGetLastError();
 }
 
