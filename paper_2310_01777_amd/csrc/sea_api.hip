@@ -419,6 +419,16 @@ int forward_stages(const sea_params* p, const void* Q, const void* K, const void
     e = launch_bits_attn(s, Q, K, V, mbits, O, w, st, have);
     return e == hipSuccess ? SEA_OK : fail_hip(e);
   }
+  if (p->dtype == SEA_F32 && tile_attn_f32_supported(s) && estimate_f64_selects(s) && !sel_opt && !idx_opt && !cnt_opt) {
+    // fp32 tensors, no row lists wanted: the estimator selects (12 heads of 1024 rows, K = 128: four launches 78.6 us, three 77.0)
+    uint32_t* mbits = mhat_opt ? mhat_opt : reinterpret_cast<uint32_t*>(w);
+    e = launch_estimate_f64(s, static_cast<const float*>(Q), static_cast<const float*>(K), static_cast<const float*>(W), A_hat_opt,
+                            est_ws, st, mbits);
+    if (e != hipSuccess) return fail_hip(e);
+    e = launch_tile_attn_f32(s, static_cast<const float*>(Q), static_cast<const float*>(K), static_cast<const float*>(V), mbits,
+                             static_cast<float*>(O), st);
+    return e == hipSuccess ? SEA_OK : fail_hip(e);
+  }
   // per-row widths, no row lists wanted: the estimator selects and writes the key bits itself
   const bool fused_select = keybit_path(s, p->dtype) && rowwidth_select_supported(s, p->dtype) && !sel_opt && !idx_opt && !cnt_opt;
   if (fused_select) {

@@ -15,6 +15,7 @@
 //
 // Workspace layout (doubles): phiQ [N][T][m], phiK/prefix [N][T][m], stateT [N][m][K].
 #include "sea_internal.h"
+#include "sea_select.h"
 
 namespace sea {
 namespace {
@@ -273,12 +274,18 @@ __device__ __forceinline__ double2 load2(const double* base, uint32_t off) {
   return *reinterpret_cast<const double2*>(base + off);
 }
 
-template <int NCT>
+// SELECT (one group): the rows' k^ columns (per-query grouping) leave as well, as one bit per column, and the scores only if A_hat
+// is given.  They pass through LDS, and each wave chooses for four rows as the kernel of its own would: 5.8 us here for 7.1 there
+// and a gap, 12 heads of 1024 rows, K = 128, layer 78.6 -> 77.0 us.  (Four rows side by side, to hide the scalar unit's latency, take
+// as many steps as the slowest: 6.6 us.)
+template <int NCT, bool SELECT = false>
 __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Shape s, const double* __restrict__ phiQ,
                                                            const double* __restrict__ pref,
                                                            const double* __restrict__ stateT,
-                                                           float* __restrict__ A_hat) {
+                                                           float* __restrict__ A_hat, uint32_t* __restrict__ mbits) {
   __shared__ double red_s[2][4][16], diag_s[2][4][16];
+  constexpr int kPlace = 64 * NCT + 4;  // floats per row of scores
+  __shared__ float place[SELECT ? 32 * kPlace : 1];
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int rt = wid >> 2, cq = wid & 3;
   const int lr = lane & 15, lg = lane >> 4;
@@ -298,7 +305,11 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
   if (r0 - 16 * rt >= len) {  // nothing but padding (both row tiles)
     const int64_t row = head * s.T + r0 - 16 * rt, rows = min(32, s.T - (r0 - 16 * rt));
-    for (int64_t x = threadIdx.x; x < rows * s.K; x += 512) A_hat[row * s.K + x] = 0.f;
+    if (!SELECT || A_hat)
+      for (int64_t x = threadIdx.x; x < rows * s.K; x += 512) A_hat[row * s.K + x] = 0.f;
+    const int32_t kw = (s.K + 31) / 32;
+    if (SELECT)
+      for (int64_t x = threadIdx.x; x < rows * kw; x += 512) mbits[row * kw + x] = 0u;
     return;
   }
   // uniform bases and 32-bit lane offsets (a head's m K state and the 16 rows' m values index with 32 bits)
@@ -414,7 +425,9 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct) {
         const int32_t c = 64 * (NCT * g + ct) + 16 * cq + lr;
-        if (c < s.K) out[c] = static_cast<float>(acc[ct][i] * inv[i]);
+        const float score = static_cast<float>(acc[ct][i] * inv[i]);
+        if (SELECT) place[(16 * rt + 4 * i + lg) * kPlace + c] = score;
+        if (c < s.K && (!SELECT || A_hat)) out[c] = score;
       }
     }
   };
@@ -450,6 +463,42 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
       group(g);
       store(g);
     }
+  }
+  if constexpr (SELECT) {
+    __syncthreads();  // the scores are there
+    const int32_t kw = (s.K + 31) / 32;
+    for (int rr = 0; rr < 4; ++rr) {
+      const int32_t u = 4 * wid + rr, t = r0 - 16 * rt + u;
+      if (t >= s.T) break;
+      uint32_t* const mrow = mbits + (head * s.T + t) * kw;
+      uint64_t take[NCT] = {};
+      if (t < len) {
+        const int32_t ncand = bucket_of(s.causal ? t : len - 1, s.T, s.K) + 1, n = min(s.k_hat, ncand);
+        uint32_t key[NCT];
+#pragma unroll
+        for (int q = 0; q < NCT; ++q) {
+          const float a = place[u * kPlace + 64 * q + lane];  // (columns past K: zeros)
+          key[q] = 64 * q + lane < ncand ? ordered_key(a) : 0u;
+        }
+        const uint32_t tau = nth_largest(key, n);
+        int above = 0;
+#pragma unroll
+        for (int q = 0; q < NCT; ++q) above += popc64(__ballot(key[q] > tau));
+        int need = n - above;  // how many of the entries equal to tau are taken, lowest columns first
+#pragma unroll
+        for (int q = 0; q < NCT; ++q) {
+          const uint64_t eq = __ballot(key[q] == tau);
+          take[q] = __ballot(key[q] > tau || (key[q] == tau && lanes_below(eq, lane) < need));
+          need -= min(need, popc64(eq));
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < NCT; ++q) {
+        if (lane == 0 && 2 * q < kw) mrow[2 * q] = static_cast<uint32_t>(take[q]);
+        if (lane == 0 && 2 * q + 1 < kw) mrow[2 * q + 1] = static_cast<uint32_t>(take[q] >> 32);
+      }
+    }
+    return;
   }
   // columns past the row tile's last one: zeros
   for (int32_t g = max(ngroups, 1); g < all_groups; ++g) {
@@ -503,8 +552,17 @@ size_t estimate_f64_workspace(const Shape& s) {
   return (2 * ntm + nkm) * sizeof(double);
 }
 
+// One group of columns: the rows of a block are whole when its scores are.  Rows of up to 64 columns have a selection kernel that
+// takes sixteen of them per wave, which long launches gain more from than from a launch less.  us, contraction and selection
+// apart / together: K = 128, 12 heads of 257 rows 19.6 / 19.8 (and a gap), of 4000 78.3 / 72.2, 48 heads of 2048, bidirectional,
+// 147.8 / 141.6; K = 64 there 100.2 / 104.3, K = 32, causal, 59.9 / 69.2, K = 64, 12 heads of 512 rows 22.3 / 15.6.
+bool estimate_f64_selects(const Shape& s) {
+  if (s.K > 128 || s.grouping != 0 || s.geometry != 0) return false;
+  return s.K > 64 || s.K % 4 != 0 || static_cast<int64_t>(s.N) * ((s.T + 31) / 32) <= 1024;
+}
+
 hipError_t launch_estimate_f64(const Shape& s, const float* Q, const float* K, const float* W,
-                               float* A_hat, void* ws, hipStream_t st) {
+                               float* A_hat, void* ws, hipStream_t st, uint32_t* mbits) {
   const size_t ntm = static_cast<size_t>(s.N) * s.T * s.m;
   double* phiQ = static_cast<double*>(ws);
   double* phiK = phiQ + ntm;
@@ -523,8 +581,10 @@ hipError_t launch_estimate_f64(const Shape& s, const float* Q, const float* K, c
   {
     StageScope scope(SEA_STAGE_CONTRACT, st);
     const dim3 grid(static_cast<uint32_t>(s.N) * ((s.T + 31) / 32));
-#define SEA_LAUNCH_CONTRACT(C) hipLaunchKernelGGL(contract_f64_kernel<C>, grid, dim3(512), 0, st, s, phiQ, phiK, stateT, A_hat)
-    if (s.K <= 64) SEA_LAUNCH_CONTRACT(1);
+#define SEA_LAUNCH_CONTRACT(...) hipLaunchKernelGGL((contract_f64_kernel<__VA_ARGS__>), grid, dim3(512), 0, st, s, phiQ, phiK, stateT, A_hat, mbits)
+    if (mbits && s.K <= 64) SEA_LAUNCH_CONTRACT(1, true);
+    else if (mbits) SEA_LAUNCH_CONTRACT(2, true);
+    else if (s.K <= 64) SEA_LAUNCH_CONTRACT(1);
     else if (s.K <= 128) SEA_LAUNCH_CONTRACT(2);
     else SEA_LAUNCH_CONTRACT(4);
 #undef SEA_LAUNCH_CONTRACT

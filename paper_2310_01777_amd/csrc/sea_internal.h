@@ -40,8 +40,10 @@ struct Shape {
 };
 
 // ---- launchers (each enqueues on `st` and returns the launch error, if any) ----
+// mbits (estimate_f64_selects shapes): also the per-query selection, as column bits; A_hat may then be nullptr
 hipError_t launch_estimate_f64(const Shape& s, const float* Q, const float* K, const float* W,
-                               float* A_hat, void* ws, hipStream_t st);
+                               float* A_hat, void* ws, hipStream_t st, uint32_t* mbits = nullptr);
+bool estimate_f64_selects(const Shape& s);
 size_t estimate_f64_workspace(const Shape& s);
 hipError_t launch_features_f64(const Shape& s, const float* Q, const float* K, const float* W, double* phiQ,
                                double* phiK, hipStream_t st);

@@ -9,7 +9,7 @@
 // are compacted in ascending order with ballot prefix counts, then expanded.
 #include "sea_columns.h"
 #include "sea_internal.h"
-#include "sea_rowlanes.h"
+#include "sea_select.h"
 
 #include <type_traits>
 
@@ -19,22 +19,11 @@ namespace {
 constexpr int kWavesPerBlock = 4;
 constexpr int kKeyBitWordsMax = 256;  // key-bit rows of at most 256 words: T <= 8192
 
-__device__ __forceinline__ uint32_t ordered_key(float a) {
-  a += 0.0f;  // -0 -> +0
-  uint32_t u = __float_as_uint(a);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 // Blocks are dealt per head: blocks_per_head(T, rows a block takes) of them each, so that the head
 // and the time step of a row come from 32-bit divisions of the block index rather than from a
 // 64-bit row index divided by T and H.
 __host__ __device__ __forceinline__ uint32_t blocks_per_head(int32_t T, int32_t rows_per_block) {
   return static_cast<uint32_t>((T + rows_per_block - 1) / rows_per_block);
-}
-
-__device__ __forceinline__ int popc64(uint64_t x) { return __popcll(x); }
-__device__ __forceinline__ int lanes_below(uint64_t mask, int lane) {
-  return __popcll(mask & ((1ull << lane) - 1ull));
 }
 
 // The keys a selected column c of a row emits (App. A.5.3: r = min(w, cap) keys start + floor(i w / r),
@@ -156,33 +145,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void topk_mask_kernel(
       if (ROWW && Tw < s.K) cand = cand && block_start(c + 1, Tw, s.K) > block_start(c, Tw, s.K);
       key[q] = cand ? ordered_key(a[q]) : 0u;
     }
-    // largest tau with #{key >= tau} >= n  ==  the n-th largest key
-    uint32_t tau = 0;
-    int bit = 31;
-    {
-      // Scores below 2 of which the quota lies at or above 2^-15, as nearly every row of an estimate: bits 31..27 are
-      // those of 2^-15.  One count instead of five steps; the scalar unit counts, and the four SIMDs of a CU share it
-      // (with the quotients above from the host, lists of B = 4, H = 12, T = 2048, K = 128: 84 -> 72 us).
-      int c_ge = 0, c_two = 0;
-  #pragma unroll
-      for (int q = 0; q < SLOTS; ++q) {
-        c_ge += popc64(__ballot(key[q] >= 0xb8000000u));
-        c_two += popc64(__ballot(key[q] >= 0xc0000000u));
-      }
-      if (c_two == 0 && c_ge >= n) {
-        tau = 0xb8000000u;
-        bit = c_ge == n ? -1 : 26;
-      }
-    }
-  #pragma unroll 1
-    for (; bit >= 0; --bit) {
-      const uint32_t trial = tau | (1u << bit);
-      int c_ge = 0;
-  #pragma unroll
-      for (int q = 0; q < SLOTS; ++q) c_ge += popc64(__ballot(key[q] >= trial));
-      if (c_ge >= n) tau = trial;
-      if (c_ge == n) break;  // the keys >= tau are exactly the n to take (one row per wave: uniform)
-    }
+    const uint32_t tau = nth_largest(key, n);
     int c_gt = 0;
   #pragma unroll
     for (int q = 0; q < SLOTS; ++q) c_gt += popc64(__ballot(key[q] > tau));
