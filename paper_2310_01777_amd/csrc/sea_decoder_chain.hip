@@ -222,21 +222,37 @@ __global__ __launch_bounds__(512, 2) void dec_conv_chain_kernel(ChainArgs g, flo
       }
     }
   };
-  request(0, 6, wid, 8);
-  static_assert(FL <= 8, "one fragment per wave");
-  if (wid < FL) wl[64 * wid + lane] = __builtin_bit_cast(uint4, weights_at<P>(g.c.w[0], FR + wid, lr, lg));
-  for (int32_t id = tid; id < K3 * 3 * 64; id += 512) {
-    const int32_t fl = id & 63, q = id >> 6, ks = q / 3, kx = q - 3 * ks;
-    const int32_t u = 4 * ks + (fl >> 4), ky = u / P, cu = u - ky * P, co = fl & 15;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (ky < 3 && co < H) v = *reinterpret_cast<const uint4*>(g.c.w[2] + static_cast<int64_t>(co * 9 + 3 * ky + kx) * C + 8 * cu);
-    w3[id] = v;
+  // What passes through registers on its way to LDS is asked for together and first, the first rows and each wave's weights together
+  // behind it: two waits for memory.
+  {
+    static_assert(FL <= 8, "one fragment per wave");
+    constexpr int kW3 = (K3 * 3 * 64 + 511) / 512;
+    bf16x8 l = zero8(), v[kW3];
+    if (FL > 0) l = weights_at<P>(g.c.w[0], FR + min(wid, FL - 1), lr, lg);
+    auto where = [&](int e, int32_t* ky, int32_t* co) {
+      const int32_t id = tid + 512 * e, fl = id & 63, q = id >> 6, ks = q / 3, kx = q - 3 * ks, u = 4 * ks + (fl >> 4);
+      *ky = u / P;
+      *co = fl & 15;
+      return (min(*co, H - 1) * 9 + 3 * min(*ky, 2) + kx) * C + 8 * (u - *ky * P);
+    };
+    int32_t ky, co;
+#pragma unroll
+    for (int e = 0; e < kW3; ++e) v[e] = load8(g.c.w[2] + where(e, &ky, &co));
+    const float bias = *(tid < C ? g.c.bias[0] + tid : tid < 2 * C ? g.c.bias[1] + (tid - C) : g.c.bias[2] + min(tid - 2 * C, H - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    if (wid < FL) wl[64 * wid + lane] = __builtin_bit_cast(uint4, l);
+#pragma unroll
+    for (int e = 0; e < kW3; ++e) {
+      where(e, &ky, &co);
+      if (tid + 512 * e < K3 * 3 * 64) w3[tid + 512 * e] = __builtin_bit_cast(uint4, ky < 3 && co < H ? v[e] : zero8());
+    }
+    if (tid < 2 * C + 16) bias_s[tid] = tid < 2 * C + H ? bias : 0.f;
   }
+  request(0, 6, wid, 8);
   for (int32_t id = tid; id < (kImgRows + 2 * kMidRows) * 2 * P; id += 512) {
     const int32_t row = id / (2 * P), u = id - row * (2 * P);
     img[row * kRow + (u < P ? u : kRow - 2 * P + u)] = make_uint4(0u, 0u, 0u, 0u);  // (the three images lie one after the other)
   }
-  if (tid < 2 * C + 16) bias_s[tid] = tid < C ? g.c.bias[0][tid] : tid < 2 * C ? g.c.bias[1][tid - C] : tid - 2 * C < H ? g.c.bias[2][tid - 2 * C] : 0.f;
   const int32_t len = seq_len ? min(max(seq_len[b], 0), T) : T;
 
   // what the steps derive from the lane they derive anew: kept through the loop it would be spilled
