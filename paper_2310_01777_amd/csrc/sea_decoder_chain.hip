@@ -291,7 +291,6 @@ __global__ __launch_bounds__(512, 2) void dec_conv_chain_kernel(ChainArgs g, flo
 
   // the two sets of waves: the same steps and the same barriers
   if (wid < 4) {
-    __builtin_amdgcn_s_setprio(1);  // the longer of the two chains
     bf16x8 wf[FR];
 #pragma unroll
     for (int e = 0; e < FR; ++e) wf[e] = weights_at<P>(g.c.w[0], e, lr, lg);
