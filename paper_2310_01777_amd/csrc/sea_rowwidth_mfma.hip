@@ -194,21 +194,22 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
   double* tot_s = lds + static_cast<size_t>(P) * kTileRows * stride;
   const uint32_t nch = (s.T + kChunk - 1) / kChunk;
   const uint32_t tiles = (s.T + kTileRows - 1) / kTileRows;
-  // Heads in groups, in a group the longest (last) row tiles first and heads fastest: a head stays on one XCD, whose L2
-  // then serves all but the first read of its key features.  (No groups: head-major, each XCD on a run of blocks.)
-  uint32_t at = blockIdx.x, first = 0, nh = 1;
+  // Heads in groups (heads_together), in a group the longest (last) row tiles first and heads fastest.  No groups: head-major, each
+  // XCD on a run of blocks, in a head the longest tiles first.  Either way most of a head's blocks are on one XCD or two, whose
+  // L2 serves all but the first read of its key features.
+  int64_t head;
+  uint32_t tile;
   if (group_heads > 0) {
-    const uint32_t per_group = static_cast<uint32_t>(group_heads) * tiles, grp = at / per_group;
-    first = grp * group_heads;
-    nh = min(static_cast<uint32_t>(group_heads), static_cast<uint32_t>(s.N) - first);
-    at -= grp * per_group;
+    const uint32_t per_group = static_cast<uint32_t>(group_heads) * tiles, grp = blockIdx.x / per_group;
+    const uint32_t first = grp * group_heads, nh = min(static_cast<uint32_t>(group_heads), static_cast<uint32_t>(s.N) - first);
+    const uint32_t at = blockIdx.x - grp * per_group, step = at / nh;
+    head = first + (at - step * nh);
+    tile = tiles - 1 - step;
   } else {
-    at = xcd_contiguous(at, gridDim.x);
-    first = at / tiles;
-    at -= first * tiles;
+    const uint32_t at = xcd_contiguous(blockIdx.x, gridDim.x), h = at / tiles;
+    head = h;
+    tile = tiles - 1 - (at - h * tiles);
   }
-  const int64_t head = first + at % nh;
-  const uint32_t tile = tiles - 1 - at / nh;
   const int32_t r0 = static_cast<int32_t>(tile) * kTileRows;
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
@@ -495,6 +496,32 @@ size_t side_bytes(const Shape& s) {
   return (static_cast<size_t>(s.N) * t32 * s.m * sizeof(uint16_t) + 255) & ~size_t(255);
 }
 
+// Heads that are dealt out together, 0: head after head.  Together, what is left at a launch's end are short tiles, and all XCDs
+// have the same work; head after head, the last head's longest tiles begin when the others are done, and with a few heads that
+// are no multiple of eight an XCD has the longer half of one.  But an XCD's L2 (4 MB) then holds the key features of several
+// heads.  Layer, us, head after head / together, K = m = 128, where nothing else is said:
+//   all heads in one group: 12 heads of 2048 rows 73.8 / 70.7, of 4096 171 / 144, 24 of 1024 56.2 / 51.9, 32 of 1024 63.8 / 56.5;
+//   not where a CU gets one block or none (<= 256), nor, of heads that share their XCDs with others (N % 8 == 4), those with few
+//   tiles or some two blocks per CU: 12 heads of 1400 rows 54.1 / 55.1, 36 of 640 44.6 / 45.8, of 256 32.1 / 32.9;
+//   not in launches that are hardly longer than one round of resident blocks and that hold several heads per XCD: m = 256, 24 heads of
+//   1536 91.2 / 96, 36 of 1024 84.4 / 87.8, m = 64, 36 of 1024 61.6 / 64.2 (of 2048 and more rows the end counts: K = 64, 24 of 3072 158 / 150);
+//   not with an odd number of heads, each on all XCDs, and more than 10 MB of features: 17 of 3000 139 / 151;
+//   more than 26 MB of features: groups whose features take 2 MB of an L2 (K = 128, 36 heads of 3072 238 / 236 and, all together, 239; B = 4,
+//   T = 4096 467 / 450).  Up to there such groups only if they fill the chip one and a half times and the last one is no small rest:
+//   48 of 2048 (32 and 16) 166.2 / 161.8, all together 166.3; but m = 256, 36 of 1024 (32 and 4) 94.6, K = 64, 36 of 2048 132, 116 together.
+// Left as they are: 16 heads of 2800 107 / 109, m = 64, 12 of 1536 53.5 / 54.5.
+int32_t heads_together(const Shape& s, int U, int32_t waves, uint32_t tiles) {
+  const int64_t blocks = static_cast<int64_t>(s.N) * tiles, resident = 256 * std::max(1, (U == 1 ? 16 : 8) / waves);
+  const int64_t head_bytes = static_cast<int64_t>(s.T) * s.m * 2;
+  if (blocks <= 256) return 0;
+  if (U == 1 && s.N % 8 == 4 && (s.T < 700 || (s.T < 1500 && blocks < 576))) return 0;
+  if (s.N % 2 != 0 && s.N * head_bytes > int64_t(10) << 20) return 0;
+  if (s.N >= 24 && s.T < 2048 && blocks > resident && 4 * blocks < 5 * resident) return 0;
+  const int64_t fit = 8 * std::max<int64_t>(1, (int64_t(2) << 20) / head_bytes);
+  if (s.N * head_bytes <= int64_t(26) << 20 && (2 * (s.N % fit) < fit || 2 * fit * tiles < 3 * resident)) return s.N;
+  return static_cast<int32_t>(std::min<int64_t>(s.N, fit));
+}
+
 template <int MS, bool WIDE, int NCT, int U>
 hipError_t launch_tiles(const Shape& s, const uint4* phiQ, const uint4* phiK, float* A_hat, uint32_t* mbits, uint32_t* kb,
                         hipStream_t st) {
@@ -505,13 +532,7 @@ hipError_t launch_tiles(const Shape& s, const uint4* phiQ, const uint4* phiK, fl
     if (e != hipSuccess) return e;
   }
   const uint32_t tiles = (s.T + 32 * U - 1) / (32 * U), blocks = static_cast<uint32_t>(s.N) * tiles;
-  // Heads whose key features share an XCD's L2, 2 MB worth, are dealt out together, so that what is left at a launch's end are
-  // short tiles; head after head, the last head's longest tiles began when the others were done.  Launches of at most one
-  // block per CU have no such end.  Layer, us, head after head / groups: K = 128, m = 128, H = 12, T = 2048, B = 4 163.2 / 159.4,
-  // B = 1 72.1 / 68.2, T = 4096, B = 4 467 / 450, B = 1 165 / 140, T = 1001, B = 2 51.1 / 48.7, T = 500, B = 1 (192 blocks) 30.4 / 31.0;
-  // H = 32, m = K = 256, T = 2048, B = 8 1553 / 1529, B = 2 412 / 400 (groups of 48 heads 1536 and 405, of 128 1616).
-  const int64_t per_xcd = std::max<int64_t>(1, (int64_t(2) << 20) / (static_cast<int64_t>(s.T) * s.m * 2));
-  const int32_t group_heads = blocks <= 256 ? 0 : static_cast<int32_t>(std::min<int64_t>(s.N, 8 * per_xcd));
+  const int32_t group_heads = heads_together(s, U, p.waves, tiles);
   hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT, U>), dim3(blocks), dim3(64 * p.waves), p.lds, st, s, phiQ, phiK, A_hat, p.parts,
                      p.part_cols, p.stride, p.cshift, mbits, kb, (s.T + 31) / 32, group_heads);
   return hipGetLastError();
