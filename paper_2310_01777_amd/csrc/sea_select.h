@@ -241,7 +241,8 @@ __device__ __forceinline__ int lanes_below(uint64_t mask, int lane) {
   return __popcll(mask & ((1ull << lane) - 1ull));
 }
 
-// One row per wave, column 64 q + lane in slot q: the largest tau with #{key >= tau} >= n, i.e. the n-th largest key.
+// One row per wave, column 64 q + lane in slot q: the largest tau with #{key >= tau} >= n, i.e. the n-th largest key
+// (topk_mask_kernel has the same steps in place).
 template <int SLOTS>
 __device__ __forceinline__ uint32_t nth_largest(const uint32_t (&key)[SLOTS], int n) {
   uint32_t tau = 0;
