@@ -482,8 +482,9 @@ __global__ __launch_bounds__(64 * RW * NS, tile_waves(RW, NS, ODD)) void tile_at
   // (behind the partial results of other waves, where there are such)
   constexpr int kPartBytes = NS > 1 ? NS / 2 * 64 * RW * kPartFloats * 4 : 0;
   static_assert(kPartBytes + RW * 32 * kRow * 2 <= static_cast<int>(sizeof(KVs)), "rows on their way out fit the keys' and values' place");
-  if constexpr (RW == 2) {
-    // (64-row blocks are for the smallest launches, which wait for the trip through LDS: 7.5 against 7.1 us)
+  if constexpr (RW == 2 && NS == 4) {
+    // (blocks of the smallest launches, which wait for the trip through LDS: 7.5 against 7.1 us.  Two sets fill the chip: with this
+    // store per-key bits, H = 12, T = 2048, B = 4 161.2 against 159.6, T = 1536, B = 3 97.2 / 96.4, columns, T = 512, B = 8 25.8 / 25.6)
     if (t < a.T) store_row(a.O + (head * a.T + t) * kHeadDim, oacc, inv);
     return;
   }
