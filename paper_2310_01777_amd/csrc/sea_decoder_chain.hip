@@ -349,8 +349,7 @@ __global__ __launch_bounds__(512, 2) void dec_conv_chain_kernel(ChainArgs g, flo
       }
       __syncthreads();  // everything is read
       if (j < nblk) store(y1, q, res);
-      lds_loads_done();
-      __syncthreads();
+      __syncthreads();  // (no wait for memory: the loads are the other set's, this one only stores A)
     }
   } else {
     bf16x8 wf[KS * NT];
