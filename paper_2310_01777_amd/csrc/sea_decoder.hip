@@ -559,6 +559,7 @@ hipError_t launch_decoder_estimate(const Shape& s, const sea_decoder_weights& wt
                                    const uint16_t* V, const uint16_t* W, float* A_hat, float* s_mix, float* s_prob,
                                    void* ws, hipStream_t st) {
   if (!decoder_supported(s, SEA_BF16)) return hipErrorNotSupported;
+  if (static_cast<int64_t>(s.N) * s.T >> 32) return hipErrorNotSupported;  // (Q, K and V of so many rows are 1.6 TB)
   const DecWs lay = dec_layout(s);
   char* base = static_cast<char*>(ws);
   auto u16 = [&](size_t off) { return reinterpret_cast<uint16_t*>(base + off); };

@@ -44,8 +44,6 @@ struct MlpArgs {
   int64_t per_block;    // 32-row tiles of a block, neighbours
 };
 
-// Row: the type that row numbers are split with (a 64-bit division is a hundred instructions; rows past 2^32 need it)
-template <typename Row>
 __global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint4 mlp_lds[];
   uint4* w_mu = mlp_lds;                                  // [6][8][64]
@@ -82,12 +80,13 @@ __global__ __launch_bounds__(kMlpThreads, 3) void dec_mlp_kernel(MlpArgs a) {
   };
 
   const int64_t first = blockIdx.x * a.per_block, end = min(first + a.per_block, (a.rows + 31) / 32);
-  // rows in the order (b, t, h), heads fastest: a wave's stores lie next to each other in the image
+  // rows in the order (b, t, h), heads fastest: a wave's stores lie next to each other in the image.  Their numbers are split in
+  // 32 bits, which the caller has seen to (a 64-bit division is a hundred instructions)
   auto split = [&](int64_t at, int32_t* h, int32_t* t, int32_t* b) {
-    const Row pp = static_cast<Row>(at), q = pp / static_cast<Row>(a.H);
-    *h = static_cast<int32_t>(pp - q * static_cast<Row>(a.H));
-    *b = static_cast<int32_t>(q / static_cast<Row>(a.T));
-    *t = static_cast<int32_t>(q - static_cast<Row>(*b) * static_cast<Row>(a.T));
+    const uint32_t pp = static_cast<uint32_t>(at), H = static_cast<uint32_t>(a.H), T = static_cast<uint32_t>(a.T), q = pp / H;
+    *h = static_cast<int32_t>(pp - q * H);
+    *b = static_cast<int32_t>(q / T);
+    *t = static_cast<int32_t>(q - static_cast<uint32_t>(*b) * T);
   };
   bf16x8 xf[kMuSteps][2];
   auto request = [&](int64_t tile) {
@@ -262,14 +261,13 @@ hipError_t launch_dec_mlp(const Shape& s, const sea_decoder_weights& wt, const u
   const int32_t slab_tiles = std::min(kSlabTiles, (a.out2 + 15) / 16);
   const size_t lds = static_cast<size_t>(kMuSteps * 8 + kHidSteps * kNu1Tiles + kHidSteps * slab_tiles) * 1024 +
                      (256 + 16 * kSlabTiles + 2) * sizeof(float);
-  const auto kernel = a.rows >> 32 ? &dec_mlp_kernel<int64_t> : &dec_mlp_kernel<uint32_t>;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dec_mlp_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;
   // an equal share of the tiles for each CU: small launches use all of them, with few waves each
   const int64_t tiles = (a.rows + 31) / 32;
   a.per_block = (tiles + 255) / 256;
-  hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>((tiles + a.per_block - 1) / a.per_block)), dim3(kMlpThreads), lds, st, a);
+  hipLaunchKernelGGL(dec_mlp_kernel, dim3(static_cast<uint32_t>((tiles + a.per_block - 1) / a.per_block)), dim3(kMlpThreads), lds, st, a);
   return hipGetLastError();
 }
 
