@@ -153,3 +153,22 @@ def test_lists_same_kernel(flat):
     for which in ("K", "V", "KV"):
         s = {k: _shifted(v, 1) if k in which else v for k, v in d.items()}
         assert torch.equal(O, attend(s["Q"], s["K"], s["V"])), which
+
+
+@pytest.mark.parametrize("by", [1, 2, 4])
+@pytest.mark.parametrize("B,H,T,K,causal", [(2, 12, 131, 128, True), (1, 4, 150, 64, False), (1, 2, 300, 258, True)])
+def test_decoder_weights(B, H, T, K, causal, by):
+    """The decoder's weights and results anywhere in memory: read in pieces of 16 bytes, whatever lies in front of them."""
+    from paper_2310_01777_amd import binding as sea
+    wl = synth.Workload("anywhere", B, H, T, 64, 64, K, 4, 0, causal, "bf16", 4)
+    d = {k: v.cuda() for k, v in synth.make_inputs(wl).items() if v is not None}
+    p = sea.SeaParams(B=B, H=H, T=T, d=64, m=64, K=K, k_hat=4, causal=causal, scale=wl.scale, dtype="bf16")
+    ws = torch.empty(sea.sea_decoder_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    weights = {k: v.cuda() for k, v in synth.decoder_weights(H, 64, K).items()}
+    out = [torch.empty(B, H, T, K, device="cuda"), torch.empty(B, H, T, device="cuda"), torch.empty(B, H, T, device="cuda")]
+    print(f"[case] decoder weights {by} elements in {(B, H, T, K, causal)}", flush=True)
+    sea.sea_decoder_estimate(p, weights, d["Q"], d["K"], d["V"], d["W"], out[0], ws, s_mix=out[1], s_prob=out[2])
+    got = [_shifted(torch.full_like(o, -1.0), by) for o in out]
+    shifted = {k: _shifted(v, by) for k, v in weights.items()}
+    sea.sea_decoder_estimate(p, shifted, d["Q"], d["K"], d["V"], d["W"], got[0], ws, s_mix=got[1], s_prob=got[2])
+    assert all(torch.equal(a, b) for a, b in zip(out, got))
