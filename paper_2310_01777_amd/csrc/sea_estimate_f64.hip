@@ -447,8 +447,7 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
       inv[i] = r > 0.0 ? 1.0 / r : 0.0;
     }
   };
-  const int32_t all_groups = (s.K + 64 * NCT - 1) / (64 * NCT);  // groups past ncols hold zeros only
-  if (ngroups <= 1) {
+  if (SELECT || ngroups <= 1) {
     group(0);
     add_sums();
     finish_sums();
@@ -501,6 +500,7 @@ __global__ __launch_bounds__(512, NCT <= 2 ? 4 : 2) void contract_f64_kernel(Sha
     return;
   }
   // columns past the row tile's last one: zeros
+  const int32_t all_groups = (s.K + 64 * NCT - 1) / (64 * NCT);  // groups past ncols hold zeros only
   for (int32_t g = max(ngroups, 1); g < all_groups; ++g) {
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) acc[ct] = doublex4{0.0, 0.0, 0.0, 0.0};
