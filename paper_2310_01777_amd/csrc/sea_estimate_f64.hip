@@ -552,13 +552,18 @@ size_t estimate_f64_workspace(const Shape& s) {
   return (2 * ntm + nkm) * sizeof(double);
 }
 
-// One group of columns: the rows of a block are whole when its scores are.  Rows of up to 64 columns have a selection kernel that
-// takes sixteen of them per wave, which long launches gain more from than from a launch less.  us, contraction and selection
-// apart / together: K = 128, 12 heads of 257 rows 19.6 / 19.8 (and a gap), of 4000 78.3 / 72.2, 48 heads of 2048, bidirectional,
-// 147.8 / 141.6; K = 64 there 100.2 / 104.3, K = 32, causal, 59.9 / 69.2, K = 64, 12 heads of 512 rows 22.3 / 15.6.
+// One group of columns: the rows of a block are whole when its scores are.  us, contraction and selection apart / together:
+//   K = 128, 12 heads of 4000 rows 78.3 / 72.2, 48 heads of 2048, bidirectional, 147.8 / 141.6; with few blocks the four rows that a
+//   wave takes one after the other show (a kernel of its own has a wave per row), the layer, k^ = 32, 12 heads of 320 rows (120
+//   blocks) 48.5 / 47.4, of 257 (108) 45.9 / 46.1, of 130 (60) 39.7 / 40.7, 4 heads of 257 (36) 39.0 / 40.0;
+//   K <= 64, K % 4 == 0, have a selection kernel that takes sixteen rows per wave, which long launches gain more from than from a
+//   launch less: K = 64, 48 heads of 2048 rows 100.2 / 104.3, K = 32, causal, 59.9 / 69.2, K = 64, 12 heads of 512 rows 22.3 / 15.6;
+//   other K <= 64, one slot of columns: the layer, K = 50, 12 heads of 130 rows 32.1 / 31.6.
 bool estimate_f64_selects(const Shape& s) {
   if (s.K > 128 || s.grouping != 0 || s.geometry != 0) return false;
-  return s.K > 64 || s.K % 4 != 0 || static_cast<int64_t>(s.N) * ((s.T + 31) / 32) <= 1024;
+  const int64_t blocks = static_cast<int64_t>(s.N) * ((s.T + 31) / 32);
+  if (s.K > 64) return blocks >= 112;
+  return s.K % 4 != 0 || blocks <= 1024;
 }
 
 hipError_t launch_estimate_f64(const Shape& s, const float* Q, const float* K, const float* W,

@@ -1,6 +1,6 @@
 """fp32 layers whose estimator selects the columns itself: the same mask as with the lists asked for, which takes the selection's own
-kernel.  One and two slots of 64 columns, partial mask words, rows past a multiple of the 32 of a block, quotas of one, of some and
-of all columns, rows of equal scores, and values that are not finite."""
+kernel.  One and, from 112 blocks of 32 rows on, two slots of 64 columns, partial mask words, rows past a multiple of the 32 of a
+block, quotas of one, of some and of all columns, rows of equal scores, and values that are not finite."""
 import pytest
 import torch
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("inputs", ["random", "equal", "nonfinite"])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("T,K,k_hat,pad", [(256, 64, 8, 0.0), (257, 64, 1, 0.3), (320, 128, 128, 0.0), (333, 100, 17, 0.4), (40, 33, 5, 0.0),
-                                           (96, 1, 1, 0.0)])
+                                           (96, 1, 1, 0.0), (700, 128, 128, 0.0), (690, 100, 17, 0.4), (673, 65, 65, 0.0)])
 def test_same_mask_as_with_lists(T, K, k_hat, pad, causal, inputs):
     from paper_2310_01777_amd import binding as sea
     B, H = 2, 3
