@@ -393,17 +393,19 @@ hipError_t start_chain(const ChainArgs& g, float* A, const int32_t* seq_len, hip
 
 }  // namespace
 
-// hipErrorNotSupported: the layers do not fit (weights of up to 48 channels in registers, rows of whole tiles and loads); the
-// caller has a kernel for each.  Where it fits it is the faster one at every size measured, from 64 blocks (above) to 16 rounds
-// of a CU (T = 4096, B = 4 108 against 182 us); fewer channels gain as much (H = 4 24 against 47 us at T = 2048, B = 4, H = 8
-// 38 against 70).
+// hipErrorNotSupported: no instance for these layers; the caller has a kernel for each.  Heads: 4 H channels, whole tiles of 16, and
+// at most 48, whose weights fit a wave's registers.  Rows: whole pairs of 16-pixel tiles (K = 32 stores 16 pixels).  Wider rows than
+// 64 pixels would fit in LDS with 8 heads to K = 192 (148 KB) and with 4 to K = 256 (96 KB), with 12 not (K = 192: 207 KB); no instances
+// are built.  Where it fits it is the faster one at every size measured, layers of one short sequence (estimate, three launches /
+// this: H = 4, K = 64, T = 64 31.6 / 23.1 us, H = 12, T = 256 49.3 / 42.3) to 16 rounds of a CU (the convolutions, T = 4096, B = 4 182 / 108); fewer
+// channels gain as much (H = 4 47 / 24 at T = 2048, B = 4, H = 8 70 / 38).
 hipError_t launch_dec_chain(const DecChain& c, float* A, const int32_t* seq_len, hipStream_t st) {
   if ((c.H != 4 && c.H != 8 && c.H != 12) || (c.X != 32 && c.X != 64)) return hipErrorNotSupported;
   if (c.T > 1 << 19) return hipErrorNotSupported;  // (32-bit offsets into a strip)
   ChainArgs g{};
   g.c = c;
   // strips: as many as fill the CUs once, or a few times if the last round would be short; a strip costs three steps
-  // beside its own
+  // beside its own.  (One block per CU; of four heads, with 86 or 122 registers, a second one would fit: not tried)
   const int64_t quads = (static_cast<int64_t>(c.T) + 3) / 4;
   int64_t best = 0;
   for (int64_t n = 1; n <= 4; ++n) {

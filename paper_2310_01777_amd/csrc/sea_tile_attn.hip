@@ -861,10 +861,12 @@ __global__ __launch_bounds__(256) void bucket_merge_kernel(const uint32_t* __res
 // lengths for every CU, and groups that fit the L2s (768 blocks at U = 2048, of 1024 that are resident) do not: a last
 // group of a few heads starts with its longest tiles when the others are nearly done.  From two blocks per resident one on
 // (2048) balance is worth more than the L2, whose misses the memory-side cache takes (twice the L2s' keys and values in
-// flight).  Layer, us, groups that fit the L2s / equal groups of at least 2048 blocks: H = 32, K = 256, k^ = 64, T = 2048, B = 8
-// (48 / 128 heads) 358 / 343, ragged T = 2000 473 / 440, T = 4096, B = 4 (48 / 64) 356 / 346, T = 8192, B = 2 (48 / 32) 368 / 361, with
-// whole columns (8 / 32) 850 / 793; H = 12, K = 128, B = 8, T = 2048 (48 / 96) 114.6 / 110.8, T = 4096 (24 / 96) 339 / 325.  Other
-// sizes at the first of these: 32, 64, 96, 160, 256 heads 351, 350, 346, 348, 352.
+// flight).  Groups of at least 2048 blocks then, alike up to the rounding to eight heads, which leaves some launches a short
+// last one (36 heads of 32768 rows 16, 16, 4; 17 of them 16 and 1).  Layer, us, groups that fit the L2s / these: H = 32, K = 256,
+// k^ = 64, T = 2048, B = 8 (48 / 128 heads) 373 / 364, ragged T = 2000 559 / 538, with padding 467 / 438, T = 8192, B = 2, whole columns (8 / 32)
+// 840 / 793; H = 12, K = 128, B = 8, T = 2048 (48 / 96) 112.4 / 107.5, T = 4096 (24 / 96) 334 / 319, B = 11 (24 / 72, 60) 460 / 442; 512 keys
+// per row, T = 4096, B = 4 358 / 355, T = 8192, B = 2 364 / 362; short last groups 36 heads 466 / 468, 17 2999 / 2992.  Other sizes at the
+// first of these: 32, 64, 96, 160, 256 heads 351, 350, 346, 348, 352 where 48 took 358 and 128 343.
 int32_t group_heads_for(const Shape& s, int64_t U) {
   const int64_t per_head = 2 * U * kHeadDim * 2;
   int64_t g = 8 * std::max<int64_t>(1, (3 << 20) / std::max<int64_t>(per_head, 1));
@@ -891,7 +893,9 @@ static bool wide_blocks(const Shape& s) {
 // 64-key chunk).  kPairs: 64 rows, four sets of two waves, while the 128-row blocks number at most one per CU
 // (half the rows halve a CU's longest work as well); per-key bits (MODE 3) cost more per step, so there a
 // little longer.  kHalves: 64 rows, two sets of two waves, whose blocks are as many waves as kOne's 128 rows: half the list and
-// half the rows per block, and two blocks end where one did, up to what is resident at once.  kFour: 128 rows, four sets of
+// half the rows per block, and two blocks end where one did, up to what is resident at once (its sets take alternate 32 keys, those
+// of kTwo 64, so some weights round to bf16 against another reference: per-key bits, T = 2048, B = 4 differ by 1.8e-3, and both are off the
+// 64-bit result by 1.846e-3, of which the result's own rounding is 1.632e-3).  kFour: 128 rows, four sets of
 // four waves, where the last rows of a causal list have many times the keys of the first.  kTwo: 128 rows, two sets of four.
 // Whole forward, K = 128, H = 12, us as kOne / kTwo / kHalves / kPairs (kFour): causal, k^ = 48, T = 1024, B = 2 (192 blocks of 128)
 // 33.7 / 29.5 / 27.8 / 26.0, B = 3 (288) 35.3 / 31.4 / 28.8 / 31.1, B = 4 (384) 35.0 / 31.3 / 29.1 / 33.4, B = 6 (576) 39.8 / 39.8 / 39.1 / 44.0,
