@@ -11,7 +11,7 @@
 // fp64: the LDS adds 64 doubles in about 11 clocks but needs about 170 for 64 floats (measured,
 // ds_add_f64 against ds_add_f32; with fp32 bins nothing else bounded this kernel).  Bound: key features from the
 // L2, products and binning take turns in a wave (B = 4, H = 12, T = 2048, m = K = 128 with the selection: vector pipe
-// 46 %, matrix pipe 12 %, LDS 15 % busy, 2.5 waves per SIMD).
+// 50 %, matrix pipe 13 %, LDS 15 % busy, 2.8 waves per SIMD).
 //
 //   rw_features_kernel   phi~(Q), phi~(K) -> HBM, already in the order the tile kernel's lanes
 //                        consume them: [head][32-token chunk][step][lane][8 features], so every
