@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void rw_features_kernel(Shape s, const uint16_
 // words.  B = 4, H = 12, T = 2048, K = 128: the pass over a score matrix in HBM that this replaces took
 // 57 us (one row per wave), the whole forward 214 us, now 181.
 // ------------------------------------------------------------------------------------------
-template <int MS, bool WIDE, int NCT, int U>  // MS = m / 16: contraction steps
+template <int MS, bool WIDE, int NCT, int U, bool TOGETHER>  // MS = m / 16: contraction steps
 __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shape s, const uint4* __restrict__ phiQ,
                                                             const uint4* __restrict__ phiK,
                                                             float* __restrict__ A_hat, int32_t parts,
@@ -197,19 +197,17 @@ __global__ __launch_bounds__(512, U == 1 ? 4 : 2) void rw_tiles_mfma_kernel(Shap
   // Heads in groups (heads_together), in a group the longest (last) row tiles first and heads fastest.  No groups: head-major, each
   // XCD on a run of blocks, in a head the longest tiles first.  Either way most of a head's blocks are on one XCD or two, whose
   // L2 serves all but the first read of its key features.
-  int64_t head;
-  uint32_t tile;
-  if (group_heads > 0) {
-    const uint32_t per_group = static_cast<uint32_t>(group_heads) * tiles, grp = blockIdx.x / per_group;
-    const uint32_t first = grp * group_heads, nh = min(static_cast<uint32_t>(group_heads), static_cast<uint32_t>(s.N) - first);
-    const uint32_t at = blockIdx.x - grp * per_group, step = at / nh;
-    head = first + (at - step * nh);
-    tile = tiles - 1 - step;
+  uint32_t lb = blockIdx.x, first = 0, in_turn = 1;  // heads in turn
+  if constexpr (TOGETHER) {
+    const uint32_t per_group = static_cast<uint32_t>(group_heads) * tiles, grp = lb / per_group;
+    first = grp * group_heads;
+    in_turn = min(static_cast<uint32_t>(group_heads), static_cast<uint32_t>(s.N) - first);
+    lb -= grp * per_group;
   } else {
-    const uint32_t at = xcd_contiguous(blockIdx.x, gridDim.x), h = at / tiles;
-    head = h;
-    tile = tiles - 1 - (at - h * tiles);
+    lb = xcd_contiguous(lb, gridDim.x);
   }
+  const int64_t head = TOGETHER ? first + lb % in_turn : lb / tiles;
+  const uint32_t tile = tiles - 1 - (TOGETHER ? lb / in_turn : lb % tiles);
   const int32_t r0 = static_cast<int32_t>(tile) * kTileRows;
   const int32_t b = static_cast<int32_t>(head / s.H);
   const int32_t len = s.seq_len ? min(max(s.seq_len[b], 0), s.T) : s.T;
@@ -505,7 +503,8 @@ size_t side_bytes(const Shape& s) {
 //   tiles or some two blocks per CU: 12 heads of 1400 rows 54.1 / 55.1, 36 of 640 44.6 / 45.8, of 256 32.1 / 32.9;
 //   not in launches that are hardly longer than one round of resident blocks and that hold several heads per XCD: m = 256, 24 heads of
 //   1536 91.2 / 96, 36 of 1024 84.4 / 87.8, m = 64, 36 of 1024 61.6 / 64.2 (of 2048 and more rows the end counts: K = 64, 24 of 3072 158 / 150);
-//   not with an odd number of heads, each on all XCDs, and more than 10 MB of features: 17 of 3000 139 / 151;
+//   not with an odd number of heads, each on all XCDs, beyond sixteen and with more than 8 MB of features: 17 of 3000 139 / 151, of 2048 88 / 90
+//   (few of them still gain by the even share: 9 of 4096, K = 100, 134 / 130; and so do blocks of two waves, K = 64, 17 of 2048 85 / 78);
 //   more than 26 MB of features: groups whose features take 2 MB of an L2 (K = 128, 36 heads of 3072 238 / 236 and, all together, 239; B = 4,
 //   T = 4096 467 / 450).  Up to there such groups only if they fill the chip one and a half times and the last one is no small rest:
 //   48 of 2048 (32 and 16) 166.2 / 161.8, all together 166.3; but m = 256, 36 of 1024 (32 and 4) 94.6, K = 64, 36 of 2048 132, 116 together.
@@ -515,27 +514,35 @@ int32_t heads_together(const Shape& s, int U, int32_t waves, uint32_t tiles) {
   const int64_t head_bytes = static_cast<int64_t>(s.T) * s.m * 2;
   if (blocks <= 256) return 0;
   if (U == 1 && s.N % 8 == 4 && (s.T < 700 || (s.T < 1500 && blocks < 576))) return 0;
-  if (s.N % 2 != 0 && s.N * head_bytes > int64_t(10) << 20) return 0;
+  if (s.N % 2 != 0 && s.N > 16 && s.K > 64 && s.N * head_bytes > int64_t(8) << 20) return 0;
   if (s.N >= 24 && s.T < 2048 && blocks > resident && 4 * blocks < 5 * resident) return 0;
   const int64_t fit = 8 * std::max<int64_t>(1, (int64_t(2) << 20) / head_bytes);
   if (s.N * head_bytes <= int64_t(26) << 20 && (2 * (s.N % fit) < fit || 2 * fit * tiles < 3 * resident)) return s.N;
   return static_cast<int32_t>(std::min<int64_t>(s.N, fit));
 }
 
+template <int MS, bool WIDE, int NCT, int U, bool TOGETHER>
+hipError_t start_tiles(const Shape& s, const Plan& p, int32_t group_heads, const uint4* phiQ, const uint4* phiK, float* A_hat,
+                       uint32_t* mbits, uint32_t* kb, hipStream_t st) {
+  if (p.lds > (64u << 10)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_tiles_mfma_kernel<MS, WIDE, NCT, U, TOGETHER>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(p.lds));
+    if (e != hipSuccess) return e;
+  }
+  const uint32_t blocks = static_cast<uint32_t>(s.N) * ((s.T + 32 * U - 1) / (32 * U));
+  hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT, U, TOGETHER>), dim3(blocks), dim3(64 * p.waves), p.lds, st, s, phiQ, phiK, A_hat,
+                     p.parts, p.part_cols, p.stride, p.cshift, mbits, kb, (s.T + 31) / 32, group_heads);
+  return hipGetLastError();
+}
+
+// (an instance for each order: the short launches, head after head, feel 0.3 us of the other one's divisions)
 template <int MS, bool WIDE, int NCT, int U>
 hipError_t launch_tiles(const Shape& s, const uint4* phiQ, const uint4* phiK, float* A_hat, uint32_t* mbits, uint32_t* kb,
                         hipStream_t st) {
   const Plan p = plan(s, 32 * U);
-  if (p.lds > (64u << 10)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&rw_tiles_mfma_kernel<MS, WIDE, NCT, U>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(p.lds));
-    if (e != hipSuccess) return e;
-  }
-  const uint32_t tiles = (s.T + 32 * U - 1) / (32 * U), blocks = static_cast<uint32_t>(s.N) * tiles;
-  const int32_t group_heads = heads_together(s, U, p.waves, tiles);
-  hipLaunchKernelGGL((rw_tiles_mfma_kernel<MS, WIDE, NCT, U>), dim3(blocks), dim3(64 * p.waves), p.lds, st, s, phiQ, phiK, A_hat, p.parts,
-                     p.part_cols, p.stride, p.cshift, mbits, kb, (s.T + 31) / 32, group_heads);
-  return hipGetLastError();
+  const int32_t group_heads = heads_together(s, U, p.waves, (s.T + 32 * U - 1) / (32 * U));
+  if (group_heads > 0) return start_tiles<MS, WIDE, NCT, U, true>(s, p, group_heads, phiQ, phiK, A_hat, mbits, kb, st);
+  return start_tiles<MS, WIDE, NCT, U, false>(s, p, 0, phiQ, phiK, A_hat, mbits, kb, st);
 }
 
 template <int MC>

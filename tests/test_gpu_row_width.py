@@ -36,7 +36,8 @@ pytestmark = pytest.mark.gpu
     (3, 28, 130, 64, 129, 40, 0, 0.0),     # K above 128: not there
     (1, 12, 4200, 64, 64, 4, 0, 0.0),      # attention: four sets of four waves (385 to 512 blocks of 128 rows)
     (1, 25, 2050, 64, 64, 4, 0, 0.0),      # 64 rows and two sets of two waves (385 to 896)
-    (1, 11, 4100, 256, 64, 4, 0, 0.3),     # head after head: an odd number of long ones
+    (1, 11, 4100, 256, 64, 4, 0, 0.3),     # all heads together, each on all XCDs
+    (1, 17, 2050, 128, 128, 4, 0, 0.3),    # head after head: an odd number
     (1, 12, 4100, 256, 250, 4, 0, 0.3),    # groups of 8 and 4 heads
     (1, 20, 2050, 256, 64, 4, 0, 0.3),     # all heads together, more than an L2's share
     (1, 12, 1601, 64, 128, 4, 0, 0.3),     # all heads together, on two XCDs each
